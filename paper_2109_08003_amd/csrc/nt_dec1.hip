@@ -1,0 +1,558 @@
+// The attention half of a decoder layer of one-head models of width 256 / 512, in one launch (gfx950).
+//
+// Between the fused Q | K | V projection and the output layer a decoder row passes through
+//   self-attention -> output projection + residual -> LayerNorm -> query projection -> cross-attention ->
+//   output projection + residual -> [LayerNorm -> FFN + residual ->] final LayerNorm,
+// and no step of it reads another row.  A workgroup of eight or sixteen waves carries 2, 4 or 16 rows through the whole chain (the
+// paper's cure for many small dependent nodes is fewer, larger ones, Sec. 3.3 "Graph Optimization"); what passes from one
+// phase to the next stays in the LDS.  As four launches (two attention kernels with a wave per row, two kernels that
+// streamed the 512 KB matrices for 32-row tiles) the chain took 24 + 24 + 28 + 16 us at 1,900 rows and 38 us at one row,
+// most of it the start and end of launches and, in the projections, 60 workgroups or fewer on 256 CUs.
+//
+// Attention phases: streams of 16-bit integer keys and values with one fp32 scale per vector (value = code * scale,
+// absmax / 32767: an rms error of about 3e-5 of a vector's spread where fp16 leaves 2.8e-4 of every element); the query,
+// scores, softmax and context are fp32 (Sec. 3.1 "FP16 Inference").  Lane l holds elements l * NE .. l * NE + NE - 1 of
+// every vector, so a wave instruction reads one whole vector.  Keys are taken four at a time: reduce-scatter butterfly,
+// wave-uniform scores, one rescale of the online softmax per block.  A row's blocks are dealt to 1 (1,024 rows or more)
+// or 4 partial softmaxes that are merged in order, however many waves compute them.
+//
+// Projection phases: every workgroup pulls the whole matrix through its CU (64 B per clock: 3.9 us for 512 KB at
+// 2.1 GHz), which is what bounds them.  A wave owns D / 8 or D / 16 output columns.  With at most four rows the head and
+// the tail plane of the activations share one 16-row operand (rows 0-7 head, 8-15 tail) and the two halves of the result
+// meet in one lane exchange; sixteen rows take one 16x16x32 MFMA per plane.  (A 32x32x16 operand would be mostly empty: four
+// times the matrix time.)  The weight fragments of the next projection are requested before the attention or LayerNorm
+// phase that precedes it.
+//
+// Measured per step of 1,900 / 45 / 1 rows, alone: 92 / 42 / 38 us as four launches, 71 / 30 / 25 us as one.
+//
+// Caches: row c (a sentence), position p: keys at kv[((c * row_positions + p) * 2) * d], values d elements later; scales
+// at sc[(c * row_positions + p) * 2 + {0: key, 1: value}].  The newest pair arrives as fp32 from the projection, is used
+// at full precision and appended in integer form.
+#include <math.h>
+
+#include <type_traits>
+
+#include "nt_kernels.h"
+
+namespace nt {
+
+typedef _Float16 half8 __attribute__((ext_vector_type(8)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
+constexpr int D1_NK = 4;     // keys per block
+constexpr int D1_SL = 4;     // ring of weight fragments: k-steps of 32 in flight per wave
+
+bool attn_i16_supported(int d, int heads, int clip) { return heads == 1 && clip == 0 && (d == 256 || d == 512); }
+
+__device__ __forceinline__ float d1_wave_sum(float v) {
+#pragma unroll
+  for (int m = 32; m >= 1; m >>= 1) v += __shfl_xor(v, m, 64);
+  return v;
+}
+__device__ __forceinline__ float d1_wave_max(float v) {
+#pragma unroll
+  for (int m = 32; m >= 1; m >>= 1) v = fmaxf(v, __shfl_xor(v, m, 64));
+  return v;
+}
+
+template <int NE>
+__device__ __forceinline__ void d1_load(const float *p, float (&x)[NE]) {
+#pragma unroll
+  for (int e = 0; e < NE; e += 4) {
+    const float4 t = *(const float4 *)(p + e);
+    x[e] = t.x, x[e + 1] = t.y, x[e + 2] = t.z, x[e + 3] = t.w;
+  }
+}
+
+// x (NE elements per lane, one vector per wave) -> integer codes at dst, scale at *sc
+template <int NE>
+__device__ __forceinline__ void d1_quantize_store(const float (&x)[NE], short *dst, float *sc, int lane) {
+  typedef short shortNE __attribute__((ext_vector_type(NE)));
+  float amax = 0.f;
+#pragma unroll
+  for (int e = 0; e < NE; e++) amax = fmaxf(amax, fabsf(x[e]));
+  amax = d1_wave_max(amax);
+  const float scale = amax > 0.f ? amax / 32767.f : 1.f;
+  const float inv = 1.f / scale;
+  shortNE qv;
+#pragma unroll
+  for (int e = 0; e < NE; e++) {
+    float c = rintf(x[e] * inv);
+    c = fminf(fmaxf(c, -32767.f), 32767.f);
+    qv[e] = (short)(int)c;
+  }
+  *(shortNE *)(dst + lane * NE) = qv;
+  if (lane == 0) *sc = scale;
+}
+
+// fp32 rows [M][2 d] (key | value of one position each) -> integer cache + scales
+template <int NE>
+__global__ __launch_bounds__(256) void quantize_kv_i16_kernel(const float *x, long M, short *cache, float *sc) {
+  constexpr int D = NE * 64;
+  const int lane = threadIdx.x & 63;
+  const long m = (long)blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (m >= M) return;
+#pragma unroll
+  for (int which = 0; which < 2; which++) {
+    float v[NE];
+    const float *src = x + (m * 2 + which) * D + lane * NE;
+#pragma unroll
+    for (int e = 0; e < NE; e += 4) {
+      const f32x4 t = __builtin_nontemporal_load((const f32x4 *)(src + e));  // read once
+      v[e] = t[0], v[e + 1] = t[1], v[e + 2] = t[2], v[e + 3] = t[3];
+    }
+    d1_quantize_store<NE>(v, cache + (m * 2 + which) * D, sc + m * 2 + which, lane);
+  }
+}
+
+hipError_t launch_quantize_kv_i16(const float *x, long M, int d, short *cache, float *sc, hipStream_t s) {
+  if (M <= 0) return hipSuccess;
+  const dim3 grid((unsigned)((M + 3) / 4)), block(256);
+  if (d == 512) hipLaunchKernelGGL(quantize_kv_i16_kernel<8>, grid, block, 0, s, x, M, cache, sc);
+  else if (d == 256) hipLaunchKernelGGL(quantize_kv_i16_kernel<4>, grid, block, 0, s, x, M, cache, sc);
+  else return hipErrorInvalidValue;
+  return hipGetLastError();
+}
+
+// One partial softmax over some of a row's keys.
+template <int NE>
+struct D1Part {
+  float m, l, acc[NE];
+  __device__ __forceinline__ void clear() {
+    m = -INFINITY, l = 0.f;
+#pragma unroll
+    for (int e = 0; e < NE; e++) acc[e] = 0.f;
+  }
+  __device__ __forceinline__ void merge(const D1Part &o) {
+    const float mn = fmaxf(m, o.m);
+    const float ca = (m == -INFINITY) ? 0.f : __expf(m - mn);
+    const float cb = (o.m == -INFINITY) ? 0.f : __expf(o.m - mn);
+    l = l * ca + o.l * cb;
+#pragma unroll
+    for (int e = 0; e < NE; e++) acc[e] = acc[e] * ca + o.acc[e] * cb;
+    m = mn;
+  }
+};
+
+// The keys of one block and their fold into a partial softmax; positions past the end repeat the last key and get
+// weight 0.
+template <int NE>
+struct D1Block {
+  typedef short shortNE __attribute__((ext_vector_type(NE)));
+  shortNE k[D1_NK], v[D1_NK];
+  float ks[D1_NK], vs[D1_NK];
+
+  __device__ __forceinline__ void load(const short *kv, const float *sc, long pos0, int j0, int n, int lane) {
+    constexpr int D = NE * 64;
+#pragma unroll
+    for (int i = 0; i < D1_NK; i++) {
+      const int j = j0 + i < n ? j0 + i : n - 1;
+      const long p = pos0 + j;
+      const short *kp = kv + p * 2 * D + lane * NE;
+      k[i] = *(const shortNE *)kp;
+      v[i] = *(const shortNE *)(kp + D);
+      ks[i] = sc[p * 2];
+      vs[i] = sc[p * 2 + 1];
+    }
+  }
+  __device__ __forceinline__ void fold(const float (&q)[NE], int j0, int n, int lane, D1Part<NE> &a) const {
+    float p[D1_NK];
+#pragma unroll
+    for (int i = 0; i < D1_NK; i++) {
+      float s = 0.f;
+#pragma unroll
+      for (int e = 0; e < NE; e++) s += q[e] * (float)k[i][e];
+      p[i] = s;
+    }
+    // reduce-scatter: after the exchanges over the two top lane bits a lane holds the sum over those bits of the key
+    // numbered by them; the remaining exchanges complete it.  Lanes 16 i .. 16 i + 15 then hold the product of key i
+    static_assert(D1_NK == 4, "blocks of four keys");
+    float r2[2], r1;
+    {
+      const bool up = lane & 32;
+#pragma unroll
+      for (int i = 0; i < 2; i++) {
+        const float send = up ? p[i] : p[i + 2], keep = up ? p[i + 2] : p[i];
+        r2[i] = keep + __shfl_xor(send, 32, 64);
+      }
+    }
+    {
+      const bool up = lane & 16;
+      const float send = up ? r2[0] : r2[1], keep = up ? r2[1] : r2[0];
+      r1 = keep + __shfl_xor(send, 16, 64);
+    }
+    r1 += __shfl_xor(r1, 8, 64);
+    r1 += __shfl_xor(r1, 4, 64);
+    r1 += __shfl_xor(r1, 2, 64);
+    r1 += __shfl_xor(r1, 1, 64);
+    float s[D1_NK], bm = -INFINITY;
+#pragma unroll
+    for (int i = 0; i < D1_NK; i++) {
+      s[i] = __uint_as_float((unsigned)__builtin_amdgcn_readlane((int)__float_as_uint(r1), 16 * i)) * ks[i];
+      if (j0 + i >= n) s[i] = -INFINITY;
+      bm = fmaxf(bm, s[i]);
+    }
+    const float mn = fmaxf(a.m, bm);  // j0 < n: at least one finite score
+    const float corr = (a.m == -INFINITY) ? 0.f : __expf(a.m - mn);
+    float w[D1_NK], wsum = 0.f;
+#pragma unroll
+    for (int i = 0; i < D1_NK; i++) {
+      w[i] = __expf(s[i] - mn);  // exp(-inf) = 0 for the positions past the end
+      wsum += w[i];
+      w[i] *= vs[i];
+    }
+    a.l = a.l * corr + wsum;
+#pragma unroll
+    for (int e = 0; e < NE; e++) {
+      float t = a.acc[e] * corr;
+#pragma unroll
+      for (int i = 0; i < D1_NK; i++) t += w[i] * (float)v[i][e];
+      a.acc[e] = t;
+    }
+    a.m = mn;
+  }
+};
+
+// D: model width.  RW: rows per workgroup (8 / RW waves each).  PARTS: partial softmaxes per row.  IND: row r uses cache
+// row origin[r] (< 0: no row, zero context).  FFN: the layer's FFN (of width D) is part of the chain.
+template <int D, int RW, int NWAVES, int PARTS, bool IND, bool FFN>
+__global__ __launch_bounds__(NWAVES * 64) void dec1_kernel(Dec1Args a) {
+  constexpr int NE = D / 64, WR = NWAVES / RW, PW = PARTS / WR;  // elements per lane; waves per row; partials per wave
+  constexpr int NC = D / NWAVES, NT = NC / 16;                   // output columns of a wave, in tiles of 16
+  constexpr int LD = D + 8, ZLD = D + 4, KS = D / 32, KS16 = D / 16;
+  static_assert(PARTS % WR == 0 && KS % D1_SL == 0, "");
+  typedef D1Part<NE> Part;
+  __shared__ __attribute__((aligned(16))) _Float16 sA[2 * RW * LD];               // head rows, then tail rows
+  __shared__ __attribute__((aligned(16))) float sZ[RW * ZLD];                     // residual stream
+  __shared__ __attribute__((aligned(16))) float sQ[RW * (D + 8)];                 // cross-attention query, later:
+  _Float16 *sU = (_Float16 *)sQ;                                                  // FFN hidden state, head rows, then tail rows
+  __shared__ float sPart[WR > 1 ? RW * (PARTS - PW) * (NE + 2) * 64 : 1];         // partial softmaxes of the waves pg > 0
+  const int tid = threadIdx.x, lane = tid & 63, h = lane >> 4, c16 = lane & 15;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int rw = wave / WR, pg = wave % WR;
+  const int row0 = blockIdx.x * RW;
+  const bool valid = row0 + rw < a.rows;
+  const int r = valid ? row0 + rw : 0;
+  int rc = r;
+  if (IND) rc = valid ? a.origin[r] : -1;
+  const bool live = valid && rc >= 0;
+  rc = __builtin_amdgcn_readfirstlane(live ? rc : 0);
+
+  // ---- weight fragments: [n / 64][k / 16][(n % 64) / 32][n % 32 + 32 * ((k % 16) / 8)][8]; a 16 x 32 operand is four
+  // runs of 256 bytes ----
+  half8 wb[D1_SL][NT];
+  const int n0 = wave * NC;
+  const int w_wave = (n0 >> 6) * (KS16 * 2048) + ((n0 >> 5) & 1) * 1024 + ((n0 >> 4) & 1) * 256;  // this wave's first columns
+  const int w_lane = (h >> 1) * 2048 + (h & 1) * 512 + c16 * 16;
+  auto w_load = [&](const __amdgpu_buffer_rsrc_t &rs, int ks, int t) {
+    return __builtin_bit_cast(half8, __builtin_amdgcn_raw_buffer_load_b128(rs, w_lane + ((t >> 1) & 1) * 1024 + (t & 1) * 256, w_wave + ks * 4096, 0));
+  };
+  auto matrix = [&](const _Float16 *W) { return __builtin_amdgcn_make_buffer_rsrc((void *)W, 0, D * D * 2, 0x00020000); };
+  auto preload = [&](const _Float16 *W) {
+    const __amdgpu_buffer_rsrc_t rs = matrix(W);
+#pragma unroll
+    for (int q = 0; q < D1_SL; q++)
+#pragma unroll
+      for (int t = 0; t < NT; t++) wb[q][t] = w_load(rs, q, t);
+  };
+  // acc[t][v], summed over both planes: row (h & 1) * 4 + v, column n0 + t * 16 + c16 (in lane groups h and h + 2 alike).
+  // The ring holds k-steps 0 .. D1_SL - 1 of W on entry.
+  f32x4 acc[NT];
+  auto project = [&](const _Float16 *W, const _Float16 *planes) {
+    const __amdgpu_buffer_rsrc_t rs = matrix(W);
+    const _Float16 *ap = planes + (RW == 16 ? c16 : (c16 < 8 ? 0 : RW) + (c16 & (RW - 1))) * LD + h * 8;
+#pragma unroll
+    for (int t = 0; t < NT; t++) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+    // D1_SL k-steps per turn; the slot just used is refilled for the next turn, the last turn refills nothing
+    auto turn = [&](int kb, auto refill_tag) {
+      constexpr bool REFILL = decltype(refill_tag)::value;
+      const _Float16 *xp = ap + kb * (D1_SL * 32);
+      half8 x[D1_SL], xl[D1_SL];
+#pragma unroll
+      for (int q = 0; q < D1_SL; q++) {
+        x[q] = *(const half8 *)(xp + q * 32);
+        if (RW == 16) xl[q] = *(const half8 *)(xp + RW * LD + q * 32);
+      }
+#pragma unroll
+      for (int q = 0; q < D1_SL; q++) {
+#pragma unroll
+        for (int t = 0; t < NT; t++) acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_f16(x[q], wb[q][t], acc[t], 0, 0, 0);
+        if (RW == 16) {
+#pragma unroll
+          for (int t = 0; t < NT; t++) acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_f16(xl[q], wb[q][t], acc[t], 0, 0, 0);
+        }
+        if (REFILL) {
+#pragma unroll
+          for (int t = 0; t < NT; t++) wb[q][t] = w_load(rs, (kb + 1) * D1_SL + q, t);
+        }
+        __builtin_amdgcn_sched_barrier(0);  // keeps the loads this far ahead of their use
+      }
+    };
+#pragma nounroll
+    for (int kb = 0; kb + 1 < KS / D1_SL; kb++) turn(kb, std::true_type{});
+    turn(KS / D1_SL - 1, std::false_type{});
+    if (RW == 16) return;
+#pragma unroll
+    for (int t = 0; t < NT; t++)
+#pragma unroll
+      for (int v = 0; v < 4; v++) acc[t][v] += __shfl_xor(acc[t][v], 32, 64);
+  };
+  // f(row, column, value) for every result of the wave; the lane groups that only duplicate rows stay out
+  auto results = [&](auto f) {
+    if (RW < 16 && (h >= 2 || (RW < 8 && h != 0))) return;
+#pragma unroll
+    for (int t = 0; t < NT; t++)
+#pragma unroll
+      for (int v = 0; v < (RW < 4 ? RW : 4); v++) f((RW == 16 ? h : h & 1) * 4 + v, n0 + t * 16 + c16, acc[t][v]);
+  };
+  auto add_residual = [&](const float *b) {
+    float bias[NT];
+#pragma unroll
+    for (int t = 0; t < NT; t++) bias[t] = b[n0 + t * 16 + c16];
+    results([&](int i, int n, float x) { float *z = sZ + i * ZLD + n; *z = x + bias[(n - n0) >> 4] + *z; });
+  };
+  auto store_planes = [&](const float (&y)[NE]) {
+    typedef _Float16 halfNE __attribute__((ext_vector_type(NE)));
+    halfNE hi, lo;
+#pragma unroll
+    for (int e = 0; e < NE; e++) {
+      hi[e] = (_Float16)y[e];
+      lo[e] = (_Float16)(y[e] - (float)hi[e]);
+    }
+    *(halfNE *)(sA + rw * LD + lane * NE) = hi;
+    *(halfNE *)(sA + (RW + rw) * LD + lane * NE) = lo;
+  };
+  // LayerNorm of this wave's row of the residual stream: fp32, mean first, then the variance of the centred values
+  auto normalise = [&](const float *gamma, const float *beta, float (&y)[NE]) {
+    float ga[NE], be[NE];
+    d1_load<NE>(gamma + lane * NE, ga);
+    d1_load<NE>(beta + lane * NE, be);
+    d1_load<NE>(sZ + rw * ZLD + lane * NE, y);
+    float s = 0.f;
+#pragma unroll
+    for (int e = 0; e < NE; e++) s += y[e];
+    const float mean = d1_wave_sum(s) / (float)D;
+    float q = 0.f;
+#pragma unroll
+    for (int e = 0; e < NE; e++) q += ln_term(y[e] - mean, a.eps.l1);
+    const float rs = ln_rscale(d1_wave_sum(q) / (float)D, a.eps);
+#pragma unroll
+    for (int e = 0; e < NE; e++) y[e] = ga[e] * ((y[e] - mean) * rs) + be[e];
+  };
+  // attention of this wave's row over n cached keys; the partials may hold the newest key already.  The merged context
+  // goes to the planes
+  auto attend = [&](const float (&q)[NE], const short *kv, const float *sc, long pos0, int n, Part (&st)[PW]) {
+    constexpr int STEP = PARTS * D1_NK;
+    // two blocks in flight: the next one of the wave's only partial, or one of each of its two
+    D1Block<NE> b[2];
+    const int j_first = pg * PW * D1_NK;
+    if constexpr (NWAVES == 16) {  // 128 registers: one block at a time
+      for (int j = j_first; j < n; j += STEP)
+#pragma unroll
+        for (int u = 0; u < PW; u++)
+          if (j + u * D1_NK < n) {
+            b[0].load(kv, sc, pos0, j + u * D1_NK, n, lane);
+            b[0].fold(q, j + u * D1_NK, n, lane, st[u]);
+          }
+    } else if constexpr (PW == 1) {
+      if (j_first < n) b[0].load(kv, sc, pos0, j_first, n, lane);
+      for (int j = j_first; j < n; j += 2 * STEP) {
+        if (j + STEP < n) b[1].load(kv, sc, pos0, j + STEP, n, lane);
+        b[0].fold(q, j, n, lane, st[0]);
+        if (j + 2 * STEP < n) b[0].load(kv, sc, pos0, j + 2 * STEP, n, lane);
+        if (j + STEP < n) b[1].fold(q, j + STEP, n, lane, st[0]);
+      }
+    } else {
+      static_assert(PW == 2, "one or two partials per wave");
+      for (int j = j_first; j < n; j += STEP) {
+        b[0].load(kv, sc, pos0, j, n, lane);
+        if (j + D1_NK < n) b[1].load(kv, sc, pos0, j + D1_NK, n, lane);
+        b[0].fold(q, j, n, lane, st[0]);
+        if (j + D1_NK < n) b[1].fold(q, j + D1_NK, n, lane, st[1]);
+      }
+    }
+    if constexpr (WR > 1) {
+      if (pg > 0) {
+#pragma unroll
+        for (int u = 0; u < PW; u++) {
+          float *p = sPart + ((rw * (PARTS - PW) + (pg - 1) * PW + u) * (NE + 2)) * 64 + lane;
+          p[0] = st[u].m;
+          p[64] = st[u].l;
+#pragma unroll
+          for (int e = 0; e < NE; e++) p[(2 + e) * 64] = st[u].acc[e];
+        }
+      }
+      __syncthreads();
+    }
+    if (pg == 0) {
+      Part &t = st[0];
+#pragma unroll
+      for (int k = 1; k < PARTS; k++) {
+        if (k < PW) {
+          t.merge(st[k]);
+        } else {
+          const float *p = sPart + ((rw * (PARTS - PW) + k - PW) * (NE + 2)) * 64 + lane;
+          Part o;
+          o.m = p[0];
+          o.l = p[64];
+#pragma unroll
+          for (int e = 0; e < NE; e++) o.acc[e] = p[(2 + e) * 64];
+          t.merge(o);
+        }
+      }
+      const float inv = (t.l > 0.f) ? 1.f / t.l : 0.f;
+      float ctx[NE];
+#pragma unroll
+      for (int e = 0; e < NE; e++) ctx[e] = t.acc[e] * inv;
+      store_planes(ctx);
+    }
+    __syncthreads();
+  };
+
+  // ---- self-attention ----
+  const int n_self = __builtin_amdgcn_readfirstlane(live ? a.n_keys : 0);
+  const int n_cross = __builtin_amdgcn_readfirstlane(live ? a.len[rc] : 0);
+  float q[NE];
+  d1_load<NE>(a.q + (long)r * D + lane * NE, q);
+  if (pg == 0) {
+    float z[NE];
+    d1_load<NE>(a.z + (long)r * D + lane * NE, z);
+#pragma unroll
+    for (int e = 0; e < NE; e += 4) *(float4 *)(sZ + rw * ZLD + lane * NE + e) = make_float4(z[e], z[e + 1], z[e + 2], z[e + 3]);
+  }
+  preload(a.Wo_self);
+  {
+    Part st[PW];
+#pragma unroll
+    for (int u = 0; u < PW; u++) st[u].clear();
+    const long pos0 = (long)rc * a.self_positions;
+    if (pg == 0 && n_self > 0) {  // the pair computed in this step: used as it is, and appended in integer form
+      float kx[NE], vx[NE];
+      d1_load<NE>(a.kv_new + (long)r * 2 * D + lane * NE, kx);
+      d1_load<NE>(a.kv_new + (long)r * 2 * D + D + lane * NE, vx);
+      float s = 0.f;
+#pragma unroll
+      for (int e = 0; e < NE; e++) s += q[e] * kx[e];
+      st[0].m = d1_wave_sum(s);
+      st[0].l = 1.f;
+#pragma unroll
+      for (int e = 0; e < NE; e++) st[0].acc[e] = vx[e];
+      const long p = pos0 + (n_self - 1);
+      d1_quantize_store<NE>(kx, a.self_kv + p * 2 * D, a.self_sc + p * 2, lane);
+      d1_quantize_store<NE>(vx, a.self_kv + p * 2 * D + D, a.self_sc + p * 2 + 1, lane);
+    }
+    attend(q, a.self_kv, a.self_sc, pos0, n_self > 0 ? n_self - 1 : 0, st);
+  }
+  // ---- output projection + residual, LayerNorm, cross-attention query ----
+  project(a.Wo_self, sA);
+  preload(a.Wq);
+  add_residual(a.bo_self);
+  __syncthreads();
+  {
+    float y[NE];
+    normalise(a.ln2.gamma, a.ln2.beta, y);
+    if (pg == 0) store_planes(y);
+  }
+  __syncthreads();
+  project(a.Wq, sA);
+  preload(a.Wo_cross);
+  {
+    float bias[NT];
+#pragma unroll
+    for (int t = 0; t < NT; t++) bias[t] = a.bq[n0 + t * 16 + c16];
+    results([&](int i, int n, float x) { sQ[i * ZLD + n] = (x + bias[(n - n0) >> 4]) * a.q_scale; });
+  }
+  __syncthreads();
+  // ---- cross-attention, output projection + residual ----
+  {
+    Part st[PW];
+#pragma unroll
+    for (int u = 0; u < PW; u++) st[u].clear();
+    d1_load<NE>(sQ + rw * ZLD + lane * NE, q);
+    attend(q, a.cross_kv, a.cross_sc, (long)rc * a.cross_positions, n_cross, st);
+  }
+  project(a.Wo_cross, sA);
+  if (FFN) preload(a.W1);
+  add_residual(a.bo_cross);
+  __syncthreads();
+  if constexpr (FFN) {
+    float y[NE];
+    normalise(a.ln3.gamma, a.ln3.beta, y);
+    if (pg == 0) store_planes(y);
+    __syncthreads();
+    project(a.W1, sA);
+    preload(a.W2);
+    float bias[NT];
+#pragma unroll
+    for (int t = 0; t < NT; t++) bias[t] = a.b1[n0 + t * 16 + c16];
+    results([&](int i, int n, float x) {
+      const float u = fmaxf(x + bias[(n - n0) >> 4], 0.f);
+      const _Float16 hi = (_Float16)u;
+      sU[i * LD + n] = hi;
+      sU[(RW + i) * LD + n] = (_Float16)(u - (float)hi);
+    });
+    __syncthreads();
+    project(a.W2, sU);
+    add_residual(a.b2);
+    __syncthreads();
+  }
+  // ---- the residual stream back, and / or the final hidden state as planes with the norm of the tail ----
+  if (pg != 0 || !valid) return;
+  if (a.write_z) {
+    float z[NE];
+    d1_load<NE>(sZ + rw * ZLD + lane * NE, z);
+#pragma unroll
+    for (int e = 0; e < NE; e += 4) *(float4 *)(a.z + (long)r * D + lane * NE + e) = make_float4(z[e], z[e + 1], z[e + 2], z[e + 3]);
+  }
+  if (a.h_hi) {
+    typedef _Float16 halfNE __attribute__((ext_vector_type(NE)));
+    float y[NE];
+    normalise(a.lnf.gamma, a.lnf.beta, y);
+    halfNE hi, lo;
+    float tail2 = 0.f;
+#pragma unroll
+    for (int e = 0; e < NE; e++) {
+      hi[e] = (_Float16)y[e];
+      lo[e] = (_Float16)(y[e] - (float)hi[e]);
+      tail2 += (float)lo[e] * (float)lo[e];
+    }
+    tail2 = d1_wave_sum(tail2);
+    *(halfNE *)(a.h_hi + (long)r * D + lane * NE) = hi;
+    *(halfNE *)(a.h_hi + a.h_lo_offset + (long)r * D + lane * NE) = lo;
+    if (lane == 0) a.lo_norm[r] = sqrtf(tail2) * 1.0001f;  // rounded up: it is used as a bound
+  }
+}
+
+template <int D, bool FFN>
+static hipError_t d1_launch(const Dec1Args &a, hipStream_t s) {
+  // Partial softmaxes per row: four below 1,024 rows, one from there on (they differ in the last bit, so the choice
+  // goes by shape_rows; the number of rows per workgroup changes no result there).
+  // 1,024 rows and more: sixteen rows per workgroup.  With eight the launch alone is as fast (71 us at 1,900 rows), but
+  // its 238 workgroups pull the matrices through twice as many CUs for the same rows; with 119 the other lanes' matrix
+  // kernels get the rest of the chip and the job is 4 % faster (200,000 sentences: 560 against 582 ms).
+  // Fewer rows, alone on the chip: two per workgroup as long as one round of workgroups covers them (320 rows of 180
+  // tokens: 24.4 against 26.7 ms).  With other lanes busy four rows from 64 on (a 4,096-token budget: 29.9 against 30.5
+  // ms): half the weight traffic.
+  const bool parts = (a.shape_rows > 0 ? a.shape_rows : a.rows) < 1024;
+#define NT_D1(RW_, NW_, P_)                                                                                             \
+  do {                                                                                                                  \
+    const dim3 grid((unsigned)((a.rows + RW_ - 1) / RW_));                                                              \
+    if (a.origin) hipLaunchKernelGGL((dec1_kernel<D, RW_, NW_, P_, true, FFN>), grid, dim3(64 * NW_), 0, s, a);         \
+    else hipLaunchKernelGGL((dec1_kernel<D, RW_, NW_, P_, false, FFN>), grid, dim3(64 * NW_), 0, s, a);                 \
+  } while (0)
+  if (!parts) NT_D1(16, 16, 1);
+  else if (a.rows <= (a.crowded ? 64 : 512)) NT_D1(2, 8, 4);
+  else NT_D1(4, 16, 4);
+#undef NT_D1
+  return hipGetLastError();
+}
+
+hipError_t launch_dec1(const Dec1Args &a, int d, hipStream_t s) {
+  if (a.rows <= 0) return hipSuccess;
+  const bool ffn = a.W1 != nullptr;
+  if (d == 512) return ffn ? d1_launch<512, true>(a, s) : d1_launch<512, false>(a, s);
+  if (d == 256) return ffn ? d1_launch<256, true>(a, s) : d1_launch<256, false>(a, s);
+  return hipErrorInvalidValue;
+}
+
+}  // namespace nt

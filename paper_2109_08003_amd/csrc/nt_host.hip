@@ -150,12 +150,12 @@ struct DecLayer {
 enum KernelId {
   K_EMBED_SRC, K_LN_ENC, K_GEMM_ENC_QKV, K_ATTN_ENC, K_GEMM_ENC_O, K_GEMM_ENC_FFN, K_GEMM_CROSS_KV,
   K_STEP_BEGIN, K_LN_DEC, K_GEMM_DEC_QKV, K_ATTN_DEC_SELF, K_GEMM_DEC_O, K_GEMM_DEC_Q, K_ATTN_DEC_CROSS,
-  K_GEMM_DEC_FFN, K_VOCAB_ARGMAX, K_GEMM_LOGITS, K_DEC_O_LN_PROJ, K_DEC_O_LN_OUT, K_KV_QUANT, K_VOCAB_ARGMAX_SMALL, K_COUNT
+  K_GEMM_DEC_FFN, K_VOCAB_ARGMAX, K_GEMM_LOGITS, K_DEC_O_LN_PROJ, K_DEC_O_LN_OUT, K_KV_QUANT, K_VOCAB_ARGMAX_SMALL, K_DEC_ATTN, K_COUNT
 };
 const char *const kKernelNames[K_COUNT] = {
   "embed_src", "layer_norm_enc", "gemm_enc_qkv", "attention_enc", "gemm_enc_o", "gemm_enc_ffn", "gemm_cross_kv",
   "step_begin", "layer_norm_dec", "gemm_dec_qkv", "attn_decode_self", "gemm_dec_o", "gemm_dec_q", "attn_decode_cross",
-  "gemm_dec_ffn", "vocab_argmax", "gemm_logits", "dec_o_ln_proj", "dec_o_ln_out", "cross_kv_quantize", "vocab_argmax_small"};
+  "gemm_dec_ffn", "vocab_argmax", "gemm_logits", "dec_o_ln_proj", "dec_o_ln_out", "cross_kv_quantize", "vocab_argmax_small", "attn_decode_layer"};
 
 struct Timing {
   uint64_t mask = 0;  // bit per KernelId; 0 = off
@@ -208,7 +208,7 @@ struct nt_model {
   std::vector<void *> cross;   // per decoder layer [Mt,2d]    (fp32 if kCrossF32 else fp16; int16 codes if kv_i16)
   std::vector<float *> self_kv;   // per decoder layer [self_positions, 2d]  (int16 codes if kv_i16)
   // Single-head decoders of width 256 / 512 without relative keys keep both caches as 16-bit integers with one fp32
-  // scale per vector (nt_attn16.hip): half the bytes of the fp32 self cache, and far less rounding than fp16.
+  // scale per vector (nt_dec1.hip): half the bytes of the fp32 self cache, and far less rounding than fp16.
   bool kv_i16 = false;
   // which encoder projections multiply the tail plane of their activations as well (bit 0: LayerNorm -> Q|K|V,
   // bit 1: attention context -> output projection, bit 2: final LayerNorm -> cross K|V, bit 3: the FFN's first matrix;
@@ -246,6 +246,7 @@ struct nt_model {
   };
   static constexpr int kStagings = 2;
   Staging stage[kStagings];
+  bool crowded = false;  // other lanes have batches in flight (nt_translate_batch sets it while it runs)
   // state left by nt_encode
   int32_t B = 0, S = 0;
   bool encoded = false;
@@ -1047,12 +1048,39 @@ int decode_step(nt_model *m, DecodeCursor &cu, hipStream_t s) {
              6 * Rd * dd * dd, nt::launch_dec_qkv(q, s));
         } else if ((rc = dec_gemm(K_GEMM_DEC_QKV, m->z, d, L.self.Wqkv, L.self.Wqkv_p, 3 * d, &L.ln1, e))) return rc;
         if (m->kv_i16) {
-          nt::AttnI16Args at{};
-          at.q = m->q32; at.kv = (short *)m->self_kv[l]; at.sc = m->self_sc[l]; at.row_positions = T; at.n_keys = t + 1;
-          at.rows = R; at.shape_rows = rows_for_choice; at.d = d; at.kv_new = m->kv_new; at.origin = origin; at.ctx = m->ctx32;
-          at.ctx_lo_offset = streams(d, d, L.self.Wo_p, false) ? lo_rows * d : 0;
-          KT(K_ATTN_DEC_SELF, Rd * t * (2 * dd * 2 + 8) + Rd * dd * 20, 4 * Rd * (t + 1) * dd, nt::launch_attn_decode_i16(at, s));
-        } else
+          // everything between the projection and the output layer in one launch; an FFN as wide as the model is part of it
+          const bool ffn_inside = F == d && L.ffn.W1_p != nullptr && L.ffn.W2_p != nullptr;
+          const bool to_final = last && (F == 0 || ffn_inside) && !c.q8_output;
+          nt::Dec1Args at{};
+          at.rows = R; at.shape_rows = rows_for_choice; at.crowded = m->crowded; at.origin = origin; at.eps = lne; at.z = m->z; at.write_z = !to_final;
+          at.q = m->q32; at.kv_new = m->kv_new; at.self_kv = (short *)m->self_kv[l]; at.self_sc = m->self_sc[l];
+          at.self_positions = T; at.n_keys = t + 1;
+          at.Wo_self = L.self.Wo_p; at.bo_self = L.self.bo; at.Wq = L.cross.Wq_p; at.bq = L.cross.bq; at.Wo_cross = L.cross.Wo_p;
+          at.bo_cross = L.cross.bo; at.q_scale = qscale; at.ln2 = nt::GemmLayerNorm{L.ln2.g, L.ln2.b, lne};
+          at.cross_kv = (const short *)m->cross[l]; at.cross_sc = m->cross_sc[l]; at.cross_positions = S; at.len = m->len;
+          if (ffn_inside) {
+            at.ln3 = nt::GemmLayerNorm{L.ln3.g, L.ln3.b, lne}; at.W1 = L.ffn.W1_p; at.b1 = L.ffn.b1; at.W2 = L.ffn.W2_p; at.b2 = L.ffn.b2;
+          }
+          if (to_final) {
+            at.lnf = nt::GemmLayerNorm{m->dec_final.g, m->dec_final.b, lne};
+            at.h_hi = h_hi; at.h_lo_offset = (long)m->max_rows * d; at.lo_norm = m->lo_norm;
+            final_ln_done = true;
+          }
+          const double ffn_flops = ffn_inside ? 4 * Rd * dd * F : 0.0;
+          KT(K_DEC_ATTN, (Rd * t + cross_keys) * (2 * dd * 2 + 8) + Rd * dd * 28 + 3 * dd * dd * 2,
+             (4 * Rd * (t + 1) + 4 * cross_keys + 6 * Rd * dd) * dd + ffn_flops, nt::launch_dec1(at, d, s));
+          if (F > 0 && !ffn_inside) {
+            const bool u_planes = streams(F, d, L.ffn.W1_p, true) && streams(d, F, L.ffn.W2_p, false);
+            nt::GemmEpilogue f1;
+            f1.bias = L.ffn.b1; f1.relu = 1; f1.dst0 = m->u32; f1.ld0 = F; f1.n_split = F;
+            f1.dst_lo_offset = u_planes ? lo_rows * F : 0;
+            if ((rc = dec_gemm(K_GEMM_DEC_FFN, m->z, d, L.ffn.W1, L.ffn.W1_p, F, &L.ln3, f1, !u_planes))) return rc;
+            nt::GemmEpilogue f2;
+            f2.bias = L.ffn.b2; f2.resid = m->z; f2.ldr = d; f2.dst0 = m->z; f2.ld0 = d; f2.n_split = d;
+            if ((rc = dec_gemm(K_GEMM_DEC_FFN, m->u32, F, L.ffn.W2, u_planes ? L.ffn.W2_p : nullptr, d, nullptr, f2))) return rc;
+          }
+          continue;
+        }
         KT(K_ATTN_DEC_SELF, Rd * (t + 1) * 2 * dd * 4 + Rd * dd * 8, 4 * Rd * (t + 1) * dd,
            nt::launch_attn_decode(m->q32, m->self_kv[l], true, self_stride, nullptr, t + 1, R, d, H, L.self.rk,
                                   c.rpr_clip, t, m->ctx32, s, streams(d, d, L.self.Wo_p, false) ? lo_rows * d : 0, origin,
@@ -1069,13 +1097,6 @@ int decode_step(nt_model *m, DecodeCursor &cu, hipStream_t s) {
           ch.W2p = L.cross.Wq_p; ch.N2 = d; ch.e2 = e;
           KT(K_DEC_O_LN_PROJ, 2 * gemm_bytes(Rd, d, d, true) - Rd * dd * 4, 4 * Rd * dd * dd, nt::launch_dec_chain(ch, d, true, s));
         } else if ((rc = dec_gemm(K_GEMM_DEC_Q, m->z, d, L.cross.Wq, L.cross.Wq_p, d, &L.ln2, e))) return rc;
-        if (m->kv_i16) {
-          nt::AttnI16Args at{};
-          at.q = m->q32; at.kv = (short *)m->cross[l]; at.sc = m->cross_sc[l]; at.row_positions = S; at.len = m->len;
-          at.rows = R; at.shape_rows = rows_for_choice; at.d = d; at.origin = origin; at.ctx = m->ctx32;
-          at.ctx_lo_offset = streams(d, d, L.cross.Wo_p, false) ? lo_rows * d : 0;
-          KT(K_ATTN_DEC_CROSS, cross_keys * (2 * dd * 2 + 8) + Rd * dd * 8, 4 * cross_keys * dd, nt::launch_attn_decode_i16(at, s));
-        } else
         KT(K_ATTN_DEC_CROSS, cross_keys * 2 * dd * ca + Rd * dd * 8, 4 * cross_keys * dd,
            nt::launch_attn_decode(m->q32, m->cross[l], kCrossF32, (long)S * 2 * d, m->len, 0, R, d, H, nullptr, 0, 0,
                                   m->ctx32, s, streams(d, d, L.cross.Wo_p, false) ? lo_rows * d : 0, origin));
@@ -1540,6 +1561,7 @@ struct Pipeline {
       HIP_TRY(hipStreamWaitEvent(ln->lane_stream, m->lane_start, 0));
       for (auto &st : ln->stage) st.busy = false;
       ln->timing.mask = m->timing.mask;
+      ln->crowded = lane.size() > 1 && plan.nb > 1;
     }
     return NT_OK;
   }
@@ -1608,6 +1630,7 @@ struct Pipeline {
         if (first_err == NT_OK) first_err = collect(ln->stage[(older + j) % nt_model::kStagings]);
       (void)hipStreamSynchronize(ln->lane_stream);
       for (auto &st : ln->stage) st.busy = false;
+      ln->crowded = false;
     }
     return first_err;
   }

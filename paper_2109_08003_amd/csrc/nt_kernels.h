@@ -335,26 +335,46 @@ hipError_t launch_attn_decode(const float *q, const void *kv, bool kv_f32, long 
                               float *ctx, hipStream_t s, long ctx_lo_offset = 0, const int32_t *origin = nullptr,
                               const float *kv_new = nullptr);
 
-// ---- single-query attention against 16-bit integer caches (nt_attn16.hip): one head, d = 256 / 512, no relative keys
+// ---- attention half of a decoder layer with one head, d = 256 / 512, no relative keys (nt_dec1.hip) -----------------
+// Both caches hold 16-bit integers with one fp32 scale per vector.  Cache row c, position p: key codes at
+// kv + ((c * positions + p) * 2) * d, value codes d elements later; their scales at sc[(c * positions + p) * 2] and
+// [... + 1] (value = code * scale).
 bool attn_i16_supported(int d, int heads, int clip);
-// Cache row c, position p: key codes at kv + ((c * row_positions + p) * 2) * d, value codes d elements later; their
-// scales at sc[(c * row_positions + p) * 2] and [... + 1] (value = code * scale).
-struct AttnI16Args {
-  const float *q;        // [rows, d] fp32, already scaled
-  short *kv;
-  float *sc;
-  long row_positions;    // positions a cache row holds (self: steps of the decode, cross: padded source length)
-  const int32_t *len;    // cross-attention: keys of each cache row; nullptr for self-attention
-  int n_keys;            // self-attention: t + 1; the last key/value pair is kv_new's, appended to the cache by the kernel
-  int rows, d;
+struct Dec1Args {
+  int rows;
   int shape_rows;        // row count that selects the kernel form (0: rows).  The forms differ in the last bit, so a
                          // caller whose row count depends on timing passes one that does not
-  const float *kv_new;   // self-attention: [rows, 2 d] fp32 (key | value of this step); nullptr for cross-attention
-  const int32_t *origin; // optional: query row r uses cache row origin[r] (< 0: zero context)
-  float *ctx;            // [rows, d] fp32, or (ctx_lo_offset != 0) head/tail fp16 planes
-  long ctx_lo_offset;
+  int crowded;           // other lanes' kernels share the chip: fewer, larger workgroups
+  const int32_t *origin; // optional: row r uses cache row origin[r] (< 0: zero context)
+  LnEps eps;
+  float *z;              // [rows, d] residual stream; written back if write_z
+  int write_z;
+  // self-attention: scaled query and this step's key | value pair (fp32), appended to the cache at position n_keys - 1
+  const float *q, *kv_new;
+  short *self_kv;
+  float *self_sc;
+  long self_positions;
+  int n_keys;
+  // output projection, LayerNorm, cross-attention query (matrices in fragment order)
+  const _Float16 *Wo_self, *Wq, *Wo_cross;
+  const float *bo_self, *bq, *bo_cross;
+  float q_scale;
+  GemmLayerNorm ln2;
+  const short *cross_kv;
+  const float *cross_sc;
+  long cross_positions;
+  const int32_t *len;    // keys of each cache row
+  // FFN of width d (W1 == nullptr: none, or not part of this launch)
+  GemmLayerNorm ln3;
+  const _Float16 *W1, *W2;
+  const float *b1, *b2;
+  // final hidden state: LayerNorm as head / tail planes and the norm of the tail (h_hi == nullptr: not wanted)
+  GemmLayerNorm lnf;
+  _Float16 *h_hi;
+  long h_lo_offset;
+  float *lo_norm;
 };
-hipError_t launch_attn_decode_i16(const AttnI16Args &a, hipStream_t s);
+hipError_t launch_dec1(const Dec1Args &a, int d, hipStream_t s);
 // x [M][2 d] fp32 (key | value of M positions) -> codes [M][2][d] and scales [M][2]
 hipError_t launch_quantize_kv_i16(const float *x, long M, int d, short *cache, float *sc, hipStream_t s);
 

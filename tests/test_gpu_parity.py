@@ -867,3 +867,47 @@ def test_c2_full_workload_sampled_against_oracle(nt, oracle):
     frac = 1.0 - bad / len(sample)
     print(f"C2 greedy: {len(sample) - bad}/{len(sample)} sampled sentences identical ({100 * frac:.2f} %), worst gap {worst:.2e}")
     assert frac >= 0.99
+
+
+# ------------------------------------------------------------------------------ row-count edges of the decoder kernels
+@pytest.mark.parametrize("d,ffn,eos", [(512, 0, False), (512, 512, False), (256, 0, False), (256, 256, True)])
+def test_one_head_decoder_at_row_count_edges(nt, oracle, torch_cuda, d, ffn, eos):
+    """A one-head decoder layer at the row counts where its kernels change form or leave a workgroup partly filled:
+    every sentence of a small-vocabulary model against the oracle."""
+    torch = torch_cuda
+    cfg = nt_synth.model_config("C1", d_model=d, vocab=300, n_enc=1, max_len=64, dec_d_ffn=ffn or -1)
+    blob = nt_synth.make_weights(cfg, seed=5, random_affine=True, eos_gain=2.0 if eos else None)
+    gm, om = nt.Model(cfg, blob, max_batch_tokens=16384, pipeline_lanes=1), oracle.Model(cfg, blob)
+    rng = np.random.default_rng(d + ffn)
+    src = [rng.integers(4, 300, size=n).astype(np.int32) for n in rng.integers(3, 13, size=1100)]
+    want = [om.greedy(s)[0] for s in src[:60]]
+    for rows in (1, 2, 3, 5, 17, 63, 65, 511, 513, 1023, 1025, 1041):
+        pick = sort_desc(src[:min(rows, 60)] + src[64:64 + rows - min(rows, 60)])
+        ids, lens = pad(pick, cfg["pad_id"])
+        steps = np.array([nt.n_steps(int(n)) for n in lens], dtype=np.int32)
+        out = torch.full((rows, int(steps[0])), -7, dtype=torch.int32, device="cuda")
+        gm.encode(torch.from_numpy(ids).cuda(), torch.from_numpy(lens).cuda())
+        if eos:
+            out_len = torch.empty(rows, dtype=torch.int32, device="cuda")
+            gm.decode_greedy_eos(rows, int(steps[0]), nt_synth.EOS_ID, out, out_len, row_steps=steps)
+            torch.cuda.synchronize()
+            steps = out_len.cpu().numpy()
+        else:
+            gm.decode_greedy(rows, int(steps[0]), out, row_steps=steps)
+        got = out.cpu().numpy()
+        known = {s.tobytes(): w for s, w in zip(src[:60], want)}
+        ref, mine, some = [], [], []
+        for r, s in enumerate(pick):
+            if s.tobytes() in known:
+                w = known[s.tobytes()]
+                if eos:
+                    hit = np.nonzero(w == nt_synth.EOS_ID)[0]
+                    w = w[: hit[0] + 1] if len(hit) else w
+                if len(w) != steps[r]:     # an end-symbol near-tie: the audit below needs equal lengths
+                    n = min(len(w), int(steps[r]))
+                    assert not np.array_equal(w[:n], got[r, :n])
+                    continue
+                ref.append(w), mine.append(got[r, : steps[r]]), some.append(s)
+        bad, _ = audit_mismatches(om, some, mine, ref, cfg)
+        assert bad <= 2 and len(some) >= min(rows, 60) - 2, (rows, bad)
+    gm.close()
