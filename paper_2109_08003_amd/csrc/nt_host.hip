@@ -246,7 +246,7 @@ struct nt_model {
   };
   static constexpr int kStagings = 2;
   Staging stage[kStagings];
-  bool crowded = false;  // other lanes have batches in flight (nt_translate_batch sets it while it runs)
+  bool crowded = false;  // two or more other lanes have batches in flight (set by the translate calls while they run)
   // state left by nt_encode
   int32_t B = 0, S = 0;
   bool encoded = false;
@@ -359,8 +359,9 @@ int alloc_lane_state(nt_model *m, hipStream_t s) {
       for (int tiled = 0; tiled < 2; tiled++) {  // either family of arg-max kernels may be selected later
         nt::VocabWeights w = m->vw;
         w.force_tiled = tiled != 0;
-        worst = std::max(worst, rows * nt::vocab_argmax_partials(w, (int)rows, false));
-        worst = std::max(worst, rows * nt::vocab_argmax_partials(w, (int)rows, true));
+        for (int crowded = 0; crowded < 2; crowded++)
+          worst = std::max(worst, rows * nt::vocab_argmax_partials(w, (int)rows, false, crowded != 0));
+        worst = std::max(worst, rows * nt::vocab_argmax_partials(w, (int)rows, true, false));
       }
       if (cfg->q8_output) worst = std::max(worst, rows * nt::vocab_q8_partials((int)rows));
     }
@@ -1167,14 +1168,15 @@ int decode_step(nt_model *m, DecodeCursor &cu, hipStream_t s) {
          nt::launch_gemm(nt::A_PLANES, true, h_hi, h_lo, d, m->Wout, R, V, d, e, s));
     } else {
       cu.prev_cert = R >= kCertMinRows;
-      const int np_ = nt::vocab_argmax_partials(m->vw, R, cu.prev_cert);
+      const bool crowded = m->crowded || rows_for_choice > nt::kVocabWideRows;
+      const int np_ = nt::vocab_argmax_partials(m->vw, R, cu.prev_cert, crowded);
       if (cu.prev_cert)
         KT(K_VOCAB_ARGMAX, (double)V * dd * 2 + Rd * dd * 4 + Rd * np_ * 8, 2 * Rd * dd * V,
            nt::launch_vocab_argmax_certified(h_hi, h_lo, d, m->vw, R, m->lo_norm, m->w_norm_max, m->pk, m->ps,
                                              m->tok, m->slot_of_row, m->cert_list, m->flags + 4, m->final_key, m->need_mask, s));
       else  // below the certified variant's row count the step is bound by the stream of the output matrix
         KT(K_VOCAB_ARGMAX_SMALL, (double)V * dd * 2 + Rd * dd * 4 + Rd * np_ * 8, 2 * Rd * dd * V,
-           nt::launch_vocab_argmax(h_hi, h_lo, d, m->vw, R, m->pk, s));
+           nt::launch_vocab_argmax(h_hi, h_lo, d, m->vw, R, m->pk, crowded, s));
       cu.partials_prev = np_;
     }
   }
@@ -1561,7 +1563,7 @@ struct Pipeline {
       HIP_TRY(hipStreamWaitEvent(ln->lane_stream, m->lane_start, 0));
       for (auto &st : ln->stage) st.busy = false;
       ln->timing.mask = m->timing.mask;
-      ln->crowded = lane.size() > 1 && plan.nb > 1;
+      ln->crowded = lane.size() > 2 && plan.nb > 2;
     }
     return NT_OK;
   }
