@@ -308,12 +308,15 @@ __device__ __forceinline__ void split8u(const float *f, half8 &hi, half8 &lo) {
 
 // QK16: the scaled query and the key come as plain fp16 from qk16 [B*S, 2d] (q | k) and the value as fp32 from
 // qkv = v [B*S, d]; one MFMA per score product.
-template <int DH, int NKB, bool QK16>
-__global__ __launch_bounds__(256, NKB == 1 ? 3 : NKB == 2 ? 2 : 1) void enc_attention_wave_kernel(const float *qkv, const _Float16 *qk16, const int32_t *len, _Float16 *ctx,
+// WPU = 4: the four waves of a workgroup share a unit, for batches with fewer units than the chip has SIMDs: each computes
+// the scores (the same MFMAs in the same order, with more of their operands in flight) and takes a quarter of the value
+// columns, whose 16 blocks in turn are most of a lone wave's time (one sentence of 22 tokens: 23 us with one wave).
+template <int DH, int NKB, bool QK16, int WPU>
+__global__ __launch_bounds__(256, WPU == 4 ? 1 : NKB == 1 ? 3 : NKB == 2 ? 2 : 1) void enc_attention_wave_kernel(const float *qkv, const _Float16 *qk16, const int32_t *len, _Float16 *ctx,
                                                                  long ctx_lo_offset, int B, int S, int d, int heads,
                                                                  int q_tiles) {
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, li = lane & 31, g = lane >> 5;
-  const long unit = (long)blockIdx.x * 4 + wave;  // uniform over the wave, and known to be: addresses below are a
+  const long unit = WPU == 4 ? (long)blockIdx.x : (long)blockIdx.x * 4 + wave;  // uniform over the wave, and known to be: addresses below are a
                                                    // uniform 64-bit base plus a 32-bit lane offset
   if (unit >= (long)B * heads * q_tiles) return;
   const int qt = (int)(unit % q_tiles), h = (int)((unit / q_tiles) % heads), b = (int)(unit / ((long)q_tiles * heads));
@@ -321,6 +324,7 @@ __global__ __launch_bounds__(256, NKB == 1 ? 3 : NKB == 2 ? 2 : 1) void enc_atte
   const long row0 = (long)b * S, ld = QK16 ? (long)d : 3L * d;  // row stride of the fp32 array (v alone, or q|k|v)
   const int hoff = h * DH;
   if (q0 >= L) {  // padding queries: defined output, no work
+    if (WPU == 4 && wave != 0) return;
     for (int i = lane; i < 32 * DH; i += 64) {
       const int r = i / DH, c = i % DH;
       if (q0 + r < S) {
@@ -331,6 +335,7 @@ __global__ __launch_bounds__(256, NKB == 1 ? 3 : NKB == 2 ? 2 : 1) void enc_atte
     return;
   }
   const int nkb = (L + 31) / 32;  // <= NKB, checked by the launcher through S
+  constexpr int CU = WPU == 4 ? (NKB == 1 ? 4 : 2) : 1;  // 64-wide slices of the scores requested together
 
   // ---- scores, transposed: sc[kb][v] = q_(q0+li) . k_(kb*32 + (v/4)*8 + g*4 + v%4) ----
   floatx16 sc[NKB];
@@ -341,20 +346,35 @@ __global__ __launch_bounds__(256, NKB == 1 ? 3 : NKB == 2 ? 2 : 1) void enc_atte
   if constexpr (QK16) {
     const _Float16 *qp16 = qk16 + (row0 + min(q0 + li, L - 1)) * (2L * d) + hoff + g * 32;
 #pragma nounroll
-    for (int c = 0; c < DH / 64; c++) {
-      half8 qh[4];
+    for (int c0 = 0; c0 < DH / 64; c0 += CU) {
+      half8 qh[CU][4], kh[NKB][CU][4];
 #pragma unroll
-      for (int u = 0; u < 4; u++) qh[u] = *(const half8 *)(qp16 + c * 64 + u * 8);  // one 64-byte half line
+      for (int c = 0; c < CU; c++)
+#pragma unroll
+        for (int u = 0; u < 4; u++) qh[c][u] = *(const half8 *)(qp16 + (c0 + c) * 64 + u * 8);  // one 64-byte half line
 #pragma unroll
       for (int kb = 0; kb < NKB; kb++) {
         if (kb < nkb) {
-          const _Float16 *kp16 = qk16 + (row0 + min(kb * 32 + li, L - 1)) * (2L * d) + d + hoff + g * 32 + c * 64;
-          half8 kh[4];
+          const _Float16 *kp16 = qk16 + (row0 + min(kb * 32 + li, L - 1)) * (2L * d) + d + hoff + g * 32 + c0 * 64;
 #pragma unroll
-          for (int u = 0; u < 4; u++) kh[u] = *(const half8 *)(kp16 + u * 8);
+          for (int c = 0; c < CU; c++)
 #pragma unroll
-          for (int u = 0; u < 4; u++) sc[kb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(kh[u], qh[u], sc[kb], 0, 0, 0);
+            for (int u = 0; u < 4; u++) kh[kb][c][u] = *(const half8 *)(kp16 + c * 64 + u * 8);
+          if (CU == 1) {
+#pragma unroll
+            for (int u = 0; u < 4; u++) sc[kb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(kh[kb][0][u], qh[0][u], sc[kb], 0, 0, 0);
+          }
         }
+      }
+      if (CU > 1) {
+#pragma unroll
+        for (int kb = 0; kb < NKB; kb++)
+          if (kb < nkb) {
+#pragma unroll
+            for (int c = 0; c < CU; c++)
+#pragma unroll
+              for (int u = 0; u < 4; u++) sc[kb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(kh[kb][c][u], qh[c][u], sc[kb], 0, 0, 0);
+          }
       }
     }
   }
@@ -427,7 +447,9 @@ __global__ __launch_bounds__(256, NKB == 1 ? 3 : NKB == 2 ? 2 : 1) void enc_atte
   // registers do not allow it).
   const char *vbase = (const char *)(qkv + row0 * ld + (QK16 ? 0 : 2 * d) + hoff);
   char *obase = (char *)(ctx + row0 * d + hoff);
-  constexpr bool PREFETCH = NKB == 2;
+  constexpr bool PREFETCH = NKB == 2 || (WPU == 4 && NKB == 1);
+  constexpr int STEP = WPU, NCB = DH / 32;
+  const int cb_first = WPU == 4 ? wave : 0;
   float fv[PREFETCH ? 2 : 1][NKB][2][8];
   auto request = [&](int cb, int slot) {
     // the block's base stays one opaque scalar pair: otherwise every one of the 16 addresses becomes a 64-bit
@@ -478,18 +500,18 @@ __global__ __launch_bounds__(256, NKB == 1 ? 3 : NKB == 2 ? 2 : 1) void enc_atte
     }
   };
   if constexpr (PREFETCH) {
-    static_assert((DH / 32) % 2 == 0, "the two slots alternate over an even number of column blocks");
-    request(0, 0);
+    static_assert(NCB % (2 * STEP) == 0, "the two slots alternate over an even number of column blocks");
+    request(cb_first, 0);
 #pragma nounroll
-    for (int cb = 0; cb < DH / 32; cb += 2) {
-      request(cb + 1, 1);
+    for (int cb = cb_first; cb < NCB; cb += 2 * STEP) {
+      request(cb + STEP, 1);
       block(cb, 0);
-      if (cb + 2 < DH / 32) request(cb + 2, 0);
-      block(cb + 1, 1);
+      if (cb + 2 * STEP < NCB) request(cb + 2 * STEP, 0);
+      block(cb + STEP, 1);
     }
   } else {
 #pragma nounroll
-    for (int cb = 0; cb < DH / 32; cb++) {
+    for (int cb = cb_first; cb < NCB; cb += STEP) {
       request(cb, 0);
       block(cb, 0);
     }
@@ -501,11 +523,17 @@ static hipError_t enc_attention_wave_launch(const float *qkv, const int32_t *len
                                             int B, int S, int d, int heads, hipStream_t s, const _Float16 *qk16 = nullptr) {
   const int q_tiles = (S + 31) / 32;
   const long units = (long)B * heads * q_tiles;
-  dim3 grid((unsigned)((units + 3) / 4)), block(256);
-#define NT_WAVE_CASE(NKB)                                                                                          \
-  case NKB:                                                                                                        \
-    hipLaunchKernelGGL((enc_attention_wave_kernel<DH, NKB, QK16>), grid, block, 0, s, qkv, qk16, len, ctx, ctx_lo_offset, \
-                       B, S, d, heads, q_tiles);                                                                   \
+  const dim3 block(256);
+  // wide heads only: a narrow one has a few column blocks in all
+  const bool share = DH >= 256 && units < 1024;
+#define NT_WAVE_CASE(NKB)                                                                                                  \
+  case NKB:                                                                                                                \
+    if (share)                                                                                                             \
+      hipLaunchKernelGGL((enc_attention_wave_kernel<DH, NKB, QK16, DH >= 256 ? 4 : 1>), dim3((unsigned)units), block, 0, s, \
+                         qkv, qk16, len, ctx, ctx_lo_offset, B, S, d, heads, q_tiles);                                     \
+    else                                                                                                                   \
+      hipLaunchKernelGGL((enc_attention_wave_kernel<DH, NKB, QK16, 1>), dim3((unsigned)((units + 3) / 4)), block, 0, s, qkv, \
+                         qk16, len, ctx, ctx_lo_offset, B, S, d, heads, q_tiles);                                          \
     break;
   switch (q_tiles) {
     NT_WAVE_CASE(1)

@@ -39,10 +39,14 @@ bool gemm_stream_supported(int N, int K) { return (K == 256 || K == 512) && N % 
 // the biased variance of the centred values) and split into head/tail planes while it is written to the LDS, which
 // saves the separate LayerNorm kernel and the round trip of its output through memory.
 // TAIL = false: only the head plane of A is multiplied (11 significant bits: half the MFMA work and half the tile).
+// NB = 32-column blocks per wave.  2: strips of 64 columns through a ring of eight k-steps.  1: strips of 32 columns whose
+// fragments (all of them for K = 256 / 512, sixteen k-steps ahead for several passes) are requested before the tile is
+// filled - for launches of few workgroups, whose time is the latency of a wave's stream: half the columns and one turn of the
+// memory system instead of five.  The sums are the same, term by term.
 // NC > 1: the contraction runs over NC * K columns of A in NC passes over the K-wide tile (K = 512, planes from memory):
 // between passes the tile is refilled behind a barrier while the weight ring keeps streaming, and every wave keeps the
 // accumulators of its one strip (N is 512 per column group) - the second matrix of an FFN, whose K is the FFN width.
-template <int RB, int K, bool C_F32, bool LN, bool TAIL, int NC>
+template <int RB, int K, bool C_F32, bool LN, bool TAIL, int NC, int NB>
 __global__ __launch_bounds__(GS_WAVES * 64) void gemm_stream_kernel(const _Float16 *__restrict__ A_hi,
                                                                    const _Float16 *__restrict__ A_lo, long lda, int M,
                                                                    const _Float16 *__restrict__ Wp, int N, int col_groups,
@@ -54,7 +58,9 @@ __global__ __launch_bounds__(GS_WAVES * 64) void gemm_stream_kernel(const _Float
   constexpr int KS = K / 16;
   // register slots of W fragments per wave; the lookahead is SL - 1 k-steps.  (A deeper ring did not shorten the
   // decoder-sized launches, and fewer registers leave room for other kernels' waves on the same CU.)
-  constexpr int SL = 8;
+  constexpr int SL = NB == 2 ? 8 : NC > 1 ? 16 : KS;
+  constexpr int LA = SL == KS && NC == 1 ? SL : SL - 1;  // k-steps requested ahead
+  constexpr int SW = 32 * NB;                            // columns of a strip
   constexpr int NOPS = (TAIL ? 2 : 1) * RB;
   static_assert(KS % SL == 0, "the ring of W slots must divide the k-steps of a strip");
   static_assert(NC == 1 || (K == 512 && !LN), "several passes: 512-wide tiles of planes only");
@@ -63,14 +69,28 @@ __global__ __launch_bounds__(GS_WAVES * 64) void gemm_stream_kernel(const _Float
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int mt = blockIdx.x / col_groups, cg = blockIdx.x % col_groups;
   const int m0 = mt * TM;
-  const int NS = N >> 6;
+  const int NS = N / SW;
   const int sb0 = (int)((long)cg * NS / col_groups), sb1 = (int)((long)(cg + 1) * NS / col_groups);
+  // first fragment of a strip
+  auto strip_at = [&](int s) { return NB == 2 ? s * (KST * 2048) : (s >> 1) * (KST * 2048) + (s & 1) * 1024; };
 
-  const __amdgpu_buffer_rsrc_t wrs = __builtin_amdgcn_make_buffer_rsrc((void *)Wp, 0, NS * 64 * (NC * K) * 2, 0x00020000);
+  const __amdgpu_buffer_rsrc_t wrs = __builtin_amdgcn_make_buffer_rsrc((void *)Wp, 0, N * (NC * K) * 2, 0x00020000);
   const int wlane = lane * 16;
   auto wload = [&](int soff, int nb) -> half8 {
     u32x4 t = __builtin_amdgcn_raw_buffer_load_b128(wrs, wlane + nb * 1024, soff, 0);
     return __builtin_bit_cast(half8, t);
+  };
+
+  half8 wb[SL][NB];
+  int strip = sb0 + wave;
+  const bool have = strip < sb1;
+  auto preload = [&]() {
+    if (!have) return;
+    const int sp = strip_at(strip);
+#pragma unroll
+    for (int q = 0; q < LA; q++)
+#pragma unroll
+      for (int nb = 0; nb < NB; nb++) wb[q][nb] = wload(sp + q * 2048, nb);
   };
 
   // ---- the A tile: global memory -> LDS.  Rows past M repeat row M - 1 (their results are never stored) ----
@@ -108,6 +128,10 @@ __global__ __launch_bounds__(GS_WAVES * 64) void gemm_stream_kernel(const _Float
         const f32x4 t = RB == 2 ? __builtin_nontemporal_load((const f32x4 *)(xr + j)) : *(const f32x4 *)(xr + j);
         xv[i][j] = t[0], xv[i][j + 1] = t[1], xv[i][j + 2] = t[2], xv[i][j + 3] = t[3];
       }
+    }
+    if (NB == 1) {  // behind the rows: their wait does not include the fragments
+      __builtin_amdgcn_sched_barrier(0);
+      preload();
     }
     float gam[NE], bet[NE];
 #pragma unroll
@@ -169,8 +193,10 @@ __global__ __launch_bounds__(GS_WAVES * 64) void gemm_stream_kernel(const _Float
     }
   } else if (K == 512) {
     fill_planes(0);
+    if (NB == 1) preload();
   } else {
     constexpr int CPR = K / 8, PER_T = ROWS * CPR / (GS_WAVES * 64);
+    if (NB == 1) preload();
     u32x4 fr[PER_T];
 #pragma unroll
     for (int i = 0; i < PER_T; i++) {
@@ -186,26 +212,27 @@ __global__ __launch_bounds__(GS_WAVES * 64) void gemm_stream_kernel(const _Float
       *(u32x4 *)(sh + R * LD + kc * 8) = fr[i];
     }
   }
-  half8 wb[SL][2];
-  int strip = sb0 + wave;
-  const bool have = strip < sb1;
-  if (have) {
-    const int sp = strip * (KST * 2048);
-#pragma unroll
-    for (int q = 0; q < SL - 1; q++) {
-      wb[q][0] = wload(sp + q * 2048, 0);
-      wb[q][1] = wload(sp + q * 2048, 1);
-    }
-  }
+  if (NB == 2) preload();
   __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): this wave's rows have landed in the LDS before the barrier
   __syncthreads();
-  if (!have) return;
+  if (!have) {
+    if (NC > 1) {  // a wave without a strip still fills its rows of every pass
+#pragma unroll 1
+      for (int c = 1; c < NC; c++) {
+        __syncthreads();
+        fill_planes(c);
+        __builtin_amdgcn_s_waitcnt(0x0F70);
+        __syncthreads();
+      }
+    }
+    return;
+  }
   // Two waves share a SIMD.  With equal priority they take turns at the matrix pipe, finish their strips together
   // and then both sit in the store phase of the epilogue (the long one when the output is fp32) while the pipe
   // idles.  Giving one of them priority makes the phases alternate instead.
   if (wave < GS_WAVES / 2) __builtin_amdgcn_s_setprio(2);
 
-  floatx16 acc[RB][2];
+  floatx16 acc[RB][NB];
   // fragment row of operand op: head rows of block op % RB, then the tail rows; two base registers, because the
   // byte offsets of the upper half do not fit the 16-bit offset field
   const _Float16 *hrow = sh + li * LD + g * 8;
@@ -225,38 +252,39 @@ __global__ __launch_bounds__(GS_WAVES * 64) void gemm_stream_kernel(const _Float
 #pragma unroll
     for (int rb = 0; rb < RB; rb++)
 #pragma unroll
-      for (int nb = 0; nb < 2; nb++)
+      for (int nb = 0; nb < NB; nb++)
 #pragma unroll
         for (int v = 0; v < 16; v++) acc[rb][nb][v] = 0.f;
   }
   for (; strip < sb1; strip += GS_WAVES) {
     const bool more = strip + GS_WAVES < sb1;
-    int pcur = strip * (KST * 2048);
-    const int pnext = (more ? strip + GS_WAVES : strip) * (KST * 2048);
+    int pcur = strip_at(strip);
+    const int pend = pcur + (KST - 1) * 2048;
+    const int pnext = strip_at(more ? strip + GS_WAVES : strip);
     // bias and scale of the strip's columns, requested here so that the epilogue does not wait for them behind the
     // weight fragments in flight
-    float bias[2] = {0.f, 0.f}, scl[2];
+    float bias[NB], scl[NB];
 #pragma unroll
-    for (int nb = 0; nb < 2; nb++) {
-      const int n = strip * 64 + nb * 32 + li;
-      if (e.bias) bias[nb] = e.bias[n];
+    for (int nb = 0; nb < NB; nb++) {
+      const int n = strip * SW + nb * 32 + li;
+      bias[nb] = e.bias ? e.bias[n] : 0.f;
       scl[nb] = (n < e.scale_cols) ? e.scale : 1.f;
     }
     // The k-loop of a strip, over the head plane's row blocks alone (NO = RB) or over both planes' (NO = NOPS): the
     // epilogue's tail_col0 .. tail_col1 name the output columns whose strips take the tail plane as well.
-    auto k_loop = [&](auto nops_tag, const float (&bias_)[2], const float (&scl_)[2]) {
+    auto k_loop = [&](auto nops_tag, const float (&bias_)[NB], const float (&scl_)[NB]) {
       constexpr int NO = decltype(nops_tag)::value;
 #pragma unroll
       for (int ks = 0; ks < KS; ks++) {
-        const int tgt = ks + SL - 1;
-        // several passes: the ring simply runs on into the next pass's fragments of the same strip (past the last
-        // pass it reads the next strip, or zeros beyond the matrix: unused either way)
-        const int pf = (NC > 1 || tgt < KS) ? pcur + tgt * 2048 : pnext + (tgt - KS) * 2048;
+        const int tgt = ks + LA;
+        // several passes: the ring simply runs on into the next pass's fragments of the same strip (at the end of the
+        // last pass it re-reads the strip's last fragment)
+        const int pf = NC > 1 ? min(pcur + tgt * 2048, pend) : tgt < KS ? pcur + tgt * 2048 : pnext + (tgt - KS) * 2048;
         const int ksn = (ks + 1) % KS;
 #pragma unroll
         for (int op = 0; op < NO; op++) {
 #pragma unroll
-          for (int nb = 0; nb < 2; nb++) {
+          for (int nb = 0; nb < NB; nb++) {
             if (NC == 1 && ks == 0 && op < RB) {
               const floatx16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
               acc[op % RB][nb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(hf[op], wb[ks % SL][nb], zero, 0, 0, 0);
@@ -266,18 +294,18 @@ __global__ __launch_bounds__(GS_WAVES * 64) void gemm_stream_kernel(const _Float
           }
           // refill what was just consumed; the scheduling barrier keeps the loads this far ahead of their use
           hf[op] = frag(op, ksn);
-          if (op == 0) {
-            wb[tgt % SL][0] = wload(pf, 0);
-            wb[tgt % SL][1] = wload(pf, 1);
+          if (LA < SL && op == 0) {
+#pragma unroll
+            for (int nb = 0; nb < NB; nb++) wb[tgt % SL][nb] = wload(pf, nb);
           }
           __builtin_amdgcn_sched_barrier(0);
         }
         // the wait for bias and scale is taken here, where it counts only the fragments requested since; left to the
         // epilogue it becomes a wait for everything in flight
-        if (ks == SL) asm volatile("" ::"v"(bias_[0]), "v"(bias_[1]), "v"(scl_[0]), "v"(scl_[1]));
+        if (NB == 2 && ks == SL) asm volatile("" ::"v"(bias_[0]), "v"(bias_[NB - 1]), "v"(scl_[0]), "v"(scl_[NB - 1]));
       }
     };
-    const bool with_tail = TAIL && strip * 64 >= e.tail_col0 && strip * 64 < e.tail_col1;
+    const bool with_tail = TAIL && strip * SW >= e.tail_col0 && strip * SW < e.tail_col1;
 #pragma unroll 1
     for (int c = 0; c < NC; c++) {
       if (NC > 1 && c > 0) {
@@ -306,13 +334,13 @@ __global__ __launch_bounds__(GS_WAVES * 64) void gemm_stream_kernel(const _Float
     // may be the destination itself (in-place update); a block's residual values are requested before the
     // stores of the block before it, so that waiting for them does not wait for those stores.
     constexpr int CE = C_F32 ? 4 : 2;
-    constexpr int NBLK = 2 * RB;  // 32 x 32 blocks of the strip: block = nb * RB + rb
+    constexpr int NBLK = NB * RB;  // 32 x 32 blocks of the strip: block = nb * RB + rb
     // ce: bytes per element of the block's destination (fp32 kernels may write their first destination as plain
     // fp16: GemmEpilogue::first_f16; the choice is uniform over a block)
     auto block_at = [&](int blk, char *&dblock, const char *&rblock, unsigned &dlane, unsigned &rlane, long &ld,
                         int &mb, int &ce) {
       const int nb = blk / RB, rb = blk % RB;
-      const int nbase = strip * 64 + nb * 32;  // uniform
+      const int nbase = strip * SW + nb * 32;  // uniform
       const bool first = nbase < e.n_split;
       char *dst = (char *)(first ? e.dst0 : e.dst1);
       ld = first ? e.ld0 : e.ld1;
@@ -409,10 +437,10 @@ __global__ __launch_bounds__(GS_WAVES * 64) void gemm_stream_kernel(const _Float
   }
 }
 
-template <int RB, int K, bool C_F32, bool LN, bool TAIL, int NC = 1>
+template <int RB, int K, bool C_F32, bool LN, bool TAIL, int NC = 1, int NB = 2>
 static hipError_t gs_launch(const _Float16 *A, const _Float16 *A_lo, long lda, int M, const _Float16 *Wp, int N,
                             const GemmEpilogue &e, const GemmLayerNorm &ln, hipStream_t s) {
-  auto kern = gemm_stream_kernel<RB, K, C_F32, LN, TAIL, NC>;
+  auto kern = gemm_stream_kernel<RB, K, C_F32, LN, TAIL, NC, NB>;
   const size_t lds = (size_t)(TAIL ? 64 : 32) * RB * (K + 8) * 2;
   // raising the dynamic LDS limit is per kernel, once per process (several host threads may get here at once)
   static std::once_flag once;
@@ -421,7 +449,7 @@ static hipError_t gs_launch(const _Float16 *A, const _Float16 *A_lo, long lda, i
     attr_err = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   });
   if (attr_err != hipSuccess) return attr_err;
-  const int row_tiles = (M + 32 * RB - 1) / (32 * RB), NS = N / 64;
+  const int row_tiles = (M + 32 * RB - 1) / (32 * RB), NS = N / (32 * NB);
   // enough workgroups for the chip: split the strips of a row tile over several workgroups as long as every wave
   // of a workgroup still gets a strip and the grid stays within a few rounds
   int col_groups = 1;
@@ -431,10 +459,17 @@ static hipError_t gs_launch(const _Float16 *A, const _Float16 *A_lo, long lda, i
       break;
     }
   if (NC > 1) col_groups = NS / GS_WAVES;  // several passes: exactly one strip per wave
+  if (NB == 1) col_groups = NS % 4 == 0 ? NS / 4 : NS / 2;  // N % 64 == 0: two or four strips per workgroup
   hipLaunchKernelGGL(kern, dim3(row_tiles * col_groups), dim3(GS_WAVES * 64), lds, s, A, A_lo, lda, M, Wp, N, col_groups, e,
                      ln);
   return hipGetLastError();
 }
+
+// 32-column strips, four to a workgroup, while that is one round of workgroups: there the launch is one wave's latency (22 rows,
+// N = 1536 / 512: 10.1 / 7.4 us against 15.7 / 13.4; a 30 + 6 layer model at an 8,192-token budget 138 against 158 ms).
+// Beyond, filling the same rows for more workgroups costs the other lanes more than the launch gains (up to two rounds:
+// 127.7 against 125.3 ms on the 8-head model at 16,384 tokens).
+static bool gs_narrow(int M, int N) { return (long)((M + 31) / 32) * (N / 128) <= 256; }
 
 template <bool LN>
 static hipError_t gs_dispatch(bool c_f32, const _Float16 *A, const _Float16 *A_lo, long lda, const _Float16 *Wp, int M,
@@ -442,6 +477,14 @@ static hipError_t gs_dispatch(bool c_f32, const _Float16 *A, const _Float16 *A_l
   if (M <= 0 || N <= 0) return hipSuccess;
   if (!gemm_stream_supported(N, K) || e.n_split % 32 != 0) return hipErrorInvalidValue;
   const bool small = M <= 8192;  // 32-row tiles: twice the workgroups
+  if (gs_narrow(M, N)) {
+#define NT_GS_CASE(K_, CF_)                                                                              \
+  if (K == K_ && c_f32 == CF_)                                                                           \
+    return tail ? gs_launch<1, K_, CF_, LN, true, 1, 1>(A, A_lo, lda, M, Wp, N, e, ln, s)                \
+                : gs_launch<1, K_, CF_, LN, false, 1, 1>(A, A_lo, lda, M, Wp, N, e, ln, s);
+    NT_GS_CASE(512, true) NT_GS_CASE(512, false) NT_GS_CASE(256, true) NT_GS_CASE(256, false)
+#undef NT_GS_CASE
+  }
 #define NT_GS_CASE(RB_, K_, CF_)                                                                                       \
   if (small == (RB_ == 1) && K == K_ && c_f32 == CF_)                                                                  \
     return tail ? gs_launch<RB_, K_, CF_, LN, true>(A, A_lo, lda, M, Wp, N, e, ln, s)                                  \
@@ -463,7 +506,7 @@ hipError_t launch_gemm_stream_k(bool c_f32, const _Float16 *A, const _Float16 *A
   const GemmLayerNorm ln{};
 #define NT_GSK_CASE(NC_, CF_, TL_)                        \
   if (K == 512 * NC_ && c_f32 == CF_ && tail == TL_)      \
-    return M <= 8192 ? gs_launch<1, 512, CF_, false, TL_, NC_>(A, A_lo, lda, M, Wp, N, e, ln, s) \
+    return gs_narrow(M, N) ? gs_launch<1, 512, CF_, false, TL_, NC_, 1>(A, A_lo, lda, M, Wp, N, e, ln, s) : M <= 8192 ? gs_launch<1, 512, CF_, false, TL_, NC_>(A, A_lo, lda, M, Wp, N, e, ln, s) \
                      : gs_launch<2, 512, CF_, false, TL_, NC_>(A, A_lo, lda, M, Wp, N, e, ln, s);
   NT_GSK_CASE(2, true, true) NT_GSK_CASE(2, true, false) NT_GSK_CASE(4, true, true) NT_GSK_CASE(4, true, false)
 #undef NT_GSK_CASE

@@ -990,7 +990,7 @@ int decode_step(nt_model *m, DecodeCursor &cu, hipStream_t s) {
     const bool few_rows = !fused && rows_for_choice <= kSkinnyMaxRows;
     auto streams = [&](int N, int K, const _Float16 *Wp, bool with_ln) -> bool {
       if (few_rows && nt::skinny_gemm_supported(K, with_ln)) return false;
-      return Wp != nullptr && nt::gemm_stream_supported(N, K);
+      return Wp != nullptr && (nt::gemm_stream_supported(N, K) || (!with_ln && nt::gemm_stream_k_supported(N, K)));
     };
     auto dec_gemm = [&](int id, const float *A, int K, const _Float16 *Wt, const _Float16 *Wp, int N, const LN *ln,
                         const nt::GemmEpilogue &e, bool c_f32 = true) -> int {
