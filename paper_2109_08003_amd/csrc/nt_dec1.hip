@@ -3,7 +3,7 @@
 // Between the fused Q | K | V projection and the output layer a decoder row passes through
 //   self-attention -> output projection + residual -> LayerNorm -> query projection -> cross-attention ->
 //   output projection + residual -> [LayerNorm -> FFN + residual ->] final LayerNorm,
-// and no step of it reads another row.  A workgroup of eight or sixteen waves carries 2, 4 or 16 rows through the whole chain (the
+// and no step of it reads another row.  A workgroup of eight or sixteen waves carries 2 to 16 rows through the whole chain (the
 // paper's cure for many small dependent nodes is fewer, larger ones, Sec. 3.3 "Graph Optimization"); what passes from one
 // phase to the next stays in the LDS.  As four launches (two attention kernels with a wave per row, two kernels that
 // streamed the 512 KB matrices for 32-row tiles) the chain took 24 + 24 + 28 + 16 us at 1,900 rows and 38 us at one row,
@@ -17,7 +17,7 @@
 // or 4 partial softmaxes that are merged in order, however many waves compute them.
 //
 // Projection phases: every workgroup pulls the whole matrix through its CU (64 B per clock: 3.9 us for 512 KB at
-// 2.1 GHz), which is what bounds them.  A wave owns D / 8 or D / 16 output columns.  With at most four rows the head and
+// 2.1 GHz), which is what bounds them.  A wave owns D / 8 or D / 16 output columns.  With at most eight rows the head and
 // the tail plane of the activations share one 16-row operand (rows 0-7 head, 8-15 tail) and the two halves of the result
 // meet in one lane exchange; sixteen rows take one 16x16x32 MFMA per plane.  (A 32x32x16 operand would be mostly empty: four
 // times the matrix time.)  The weight fragments of the next projection are requested before the attention or LayerNorm
@@ -221,6 +221,9 @@ __global__ __launch_bounds__(NWAVES * 64) void dec1_kernel(Dec1Args a) {
   constexpr int NC = D / NWAVES, NT = NC / 16;                   // output columns of a wave, in tiles of 16
   constexpr int LD = D + 8, ZLD = D + 4, KS = D / 32, KS16 = D / 16;
   static_assert(PARTS % WR == 0 && KS % D1_SL == 0, "");
+  // whether the next matrix's first fragments are requested before an attention phase: 32 of 128 registers, which a wave
+  // with several partial softmaxes does not have
+  constexpr bool EARLY = !(NWAVES == 16 && PW > 1);
   typedef D1Part<NE> Part;
   __shared__ __attribute__((aligned(16))) _Float16 sA[2 * RW * LD];               // head rows, then tail rows
   __shared__ __attribute__((aligned(16))) float sZ[RW * ZLD];                     // residual stream
@@ -420,7 +423,7 @@ __global__ __launch_bounds__(NWAVES * 64) void dec1_kernel(Dec1Args a) {
 #pragma unroll
     for (int e = 0; e < NE; e += 4) *(float4 *)(sZ + rw * ZLD + lane * NE + e) = make_float4(z[e], z[e + 1], z[e + 2], z[e + 3]);
   }
-  preload(a.Wo_self);
+  if (EARLY) preload(a.Wo_self);
   {
     Part st[PW];
 #pragma unroll
@@ -444,6 +447,7 @@ __global__ __launch_bounds__(NWAVES * 64) void dec1_kernel(Dec1Args a) {
     attend(q, a.self_kv, a.self_sc, pos0, n_self > 0 ? n_self - 1 : 0, st);
   }
   // ---- output projection + residual, LayerNorm, cross-attention query ----
+  if (!EARLY) preload(a.Wo_self);
   project(a.Wo_self, sA);
   preload(a.Wq);
   add_residual(a.bo_self);
@@ -455,7 +459,7 @@ __global__ __launch_bounds__(NWAVES * 64) void dec1_kernel(Dec1Args a) {
   }
   __syncthreads();
   project(a.Wq, sA);
-  preload(a.Wo_cross);
+  if (EARLY) preload(a.Wo_cross);
   {
     float bias[NT];
 #pragma unroll
@@ -471,6 +475,7 @@ __global__ __launch_bounds__(NWAVES * 64) void dec1_kernel(Dec1Args a) {
     d1_load<NE>(sQ + rw * ZLD + lane * NE, q);
     attend(q, a.cross_kv, a.cross_sc, (long)rc * a.cross_positions, n_cross, st);
   }
+  if (!EARLY) preload(a.Wo_cross);
   project(a.Wo_cross, sA);
   if (FFN) preload(a.W1);
   add_residual(a.bo_cross);
@@ -532,7 +537,7 @@ static hipError_t d1_launch(const Dec1Args &a, hipStream_t s) {
   // kernels get the rest of the chip and the job is 4 % faster (200,000 sentences: 560 against 582 ms).
   // Fewer rows, alone on the chip: two per workgroup as long as one round of workgroups covers them (320 rows of 180
   // tokens: 24.4 against 26.7 ms).  With other lanes busy four rows from 64 on (a 4,096-token budget: 29.9 against 30.5
-  // ms): half the weight traffic.
+  // ms), eight from 257 on (65,536 tokens: 550 against 554 ms): less weight traffic, and CUs for the others.
   const bool parts = (a.shape_rows > 0 ? a.shape_rows : a.rows) < 1024;
 #define NT_D1(RW_, NW_, P_)                                                                                             \
   do {                                                                                                                  \
@@ -542,7 +547,8 @@ static hipError_t d1_launch(const Dec1Args &a, hipStream_t s) {
   } while (0)
   if (!parts) NT_D1(16, 16, 1);
   else if (a.rows <= (a.crowded ? 64 : 512)) NT_D1(2, 8, 4);
-  else NT_D1(4, 16, 4);
+  else if (a.rows <= 256 || !a.crowded) NT_D1(4, 16, 4);
+  else NT_D1(8, 16, 4);
 #undef NT_D1
   return hipGetLastError();
 }

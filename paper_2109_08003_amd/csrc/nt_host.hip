@@ -3,6 +3,7 @@
 // EOS-terminated) and the pipeline lanes.  No CPU fallback exists: every numerical step of the path is a kernel in
 // nt_gemm.hip / nt_gemm_stream.hip / nt_vocab.hip / nt_vocab_q8.hip / nt_rows.hip / nt_attn.hip.
 #include <algorithm>
+#include <atomic>
 #include <chrono>
 #include <cmath>
 #include <cstdarg>
@@ -1651,22 +1652,12 @@ int nt_translate_batch(nt_model *m, const int32_t *h_tokens, const int64_t *h_of
   // host packs batches and unpacks finished ones while the device works.
   Pipeline pl{m, plan, h_tokens, h_offsets, h_out, h_out_offsets, nullptr, {}};
   if ((rc = pl.begin(as_stream(hip_stream)))) return rc;
-  // A batch goes to the lane with the least estimated work so far (batches come in descending length, which is
-  // close to descending cost: longest-processing-time-first), so that the lanes finish together.  Cost in
-  // microseconds, fitted to solo batch times on the 200,000-sentence workload: a decode step costs about
-  // 130 us of launch and weight-stream latency plus 0.08 us per row, the encoder 0.06 us per padded token.
+  // Batches are dealt as the lanes come free: a lane takes the next one (they come in descending length, close to
+  // descending cost) when one of its two staging sets is free, and near the end, with no more batches left than lanes, only
+  // when it has nothing queued, so that the lanes finish together.  (Dealing by estimated cost beforehand left lanes idle
+  // at the end when the estimate met other lanes' kernels: 73 to 95 ms for the same 27 batches of 16,384 tokens.)
   const size_t n_lanes = pl.lane.size();
-  std::vector<double> lane_cost(n_lanes, 0.0);
-  std::vector<std::vector<int64_t>> lane_batches(n_lanes);
-  for (int64_t k = 0; k < plan.nb; k++) {
-    const size_t li = (size_t)(std::min_element(lane_cost.begin(), lane_cost.end()) - lane_cost.begin());
-    const int64_t i0 = plan.starts[(size_t)k], i1 = plan.starts[(size_t)k + 1];
-    const int32_t S = plan.lens[(size_t)plan.order[(size_t)i0]];
-    double row_steps = 0.0;
-    for (int64_t i = i0; i < i1; i++) row_steps += nt_n_steps(plan.lens[(size_t)plan.order[(size_t)i]]);
-    lane_cost[li] += 130.0 * nt_n_steps(S) + 0.08 * row_steps + 0.06 * (double)(i1 - i0) * S;
-    lane_batches[li].push_back(k);
-  }
+  std::atomic<int64_t> next_batch{0};
   auto run_batch = [&](size_t li, int64_t k, int64_t nth) -> int {
     nt_model *ln = pl.lane[li];
     nt_model::Staging &st = ln->stage[nth % nt_model::kStagings];
@@ -1678,7 +1669,7 @@ int nt_translate_batch(nt_model *m, const int32_t *h_tokens, const int64_t *h_of
   int first_err = NT_OK, dev = 0;
   // Small batches (a 4,096-token budget: ten thousand launches of a few microseconds of host time each for 4,096
   // sentences) are bound by the host: there every lane is fed by a thread of its own (+5 to 9 % on that workload).
-  // With large batches the launches are not the bound and one thread feeding the lanes in turn is as fast or faster
+  // With large batches the launches are not the bound and one thread feeding the lanes is as fast or faster
   // (threads: -1 to 2 % at 65,536 tokens).
   if (n_lanes > 1 && plan.nb >= 2 && token_budget < 32768) {
     if (hipGetDevice(&dev) != hipSuccess) return pl.drain(fail(NT_EHIP, "hipGetDevice failed"));
@@ -1687,8 +1678,15 @@ int nt_translate_batch(nt_model *m, const int32_t *h_tokens, const int64_t *h_of
     auto feed = [&](size_t li) {
       try {
         if (hipSetDevice(dev) != hipSuccess) lane_rc[li] = fail(NT_EHIP, "hipSetDevice failed in a lane's thread");
-        for (size_t n = 0; n < lane_batches[li].size() && lane_rc[li] == NT_OK; n++)
-          lane_rc[li] = run_batch(li, lane_batches[li][n], (int64_t)n);
+        for (int64_t nth = 0; lane_rc[li] == NT_OK; nth++) {
+          nt_model *ln = pl.lane[li];
+          if ((lane_rc[li] = pl.collect(ln->stage[nth % nt_model::kStagings]))) break;
+          if (plan.nb - next_batch.load() <= (int64_t)n_lanes &&
+              (lane_rc[li] = pl.collect(ln->stage[(nth + 1) % nt_model::kStagings]))) break;
+          const int64_t k = next_batch++;
+          if (k >= plan.nb) break;
+          lane_rc[li] = run_batch(li, k, nth);
+        }
       } catch (const std::bad_alloc &) {
         lane_rc[li] = fail(NT_ENOMEM, "host allocation failed");
       } catch (...) {
@@ -1708,15 +1706,20 @@ int nt_translate_batch(nt_model *m, const int32_t *h_tokens, const int64_t *h_of
     for (size_t li = 0; li < n_lanes && first_err == NT_OK; li++)
       if (lane_rc[li]) { first_err = lane_rc[li]; g_err = lane_err[li]; }
   } else {
-    // one thread, batches in their order: batch k goes to its lane as soon as the ones before it are queued
-    std::vector<size_t> lane_of((size_t)plan.nb, 0);
-    std::vector<int64_t> nth((size_t)plan.nb, 0);
-    for (size_t li = 0; li < n_lanes; li++)
-      for (size_t n = 0; n < lane_batches[li].size(); n++) {
-        lane_of[(size_t)lane_batches[li][n]] = li;
-        nth[(size_t)lane_batches[li][n]] = (int64_t)n;
+    // one thread: the next batch goes to the first lane found ready for it
+    std::vector<int64_t> nth(n_lanes, 0);
+    auto free_now = [&](nt_model::Staging &st) { return !st.busy || hipEventQuery(st.done) == hipSuccess; };
+    for (int64_t k = 0; k < plan.nb && first_err == NT_OK;) {
+      bool placed = false;
+      for (size_t li = 0; li < n_lanes && first_err == NT_OK && k < plan.nb; li++) {
+        nt_model *ln = pl.lane[li];
+        const bool last = plan.nb - k <= (int64_t)n_lanes;
+        if (!free_now(ln->stage[nth[li] % nt_model::kStagings]) || (last && !free_now(ln->stage[(nth[li] + 1) % nt_model::kStagings]))) continue;
+        first_err = run_batch(li, k++, nth[li]++);
+        placed = true;
       }
-    for (int64_t k = 0; k < plan.nb && first_err == NT_OK; k++) first_err = run_batch(lane_of[(size_t)k], k, nth[(size_t)k]);
+      if (!placed) std::this_thread::yield();
+    }
   }
   return pl.drain(first_err);
 } catch (const std::bad_alloc &) {
