@@ -23,6 +23,12 @@
 // times the matrix time.)  The weight fragments of the next projection are requested before the attention or LayerNorm
 // phase that precedes it.
 //
+// Folded cross cache (batches of up to kDec1FoldRows rows).  q . k = (W y + b) . k = y . (W^T k) + b . k, and
+// Wo (sum p v) + bo = sum p (Wo v + bo): with the keys and values of a sentence multiplied by the two matrices once, when
+// the batch is encoded, a step needs neither projection - 8 of the 20 us at one row.  The products are formed from the
+// rounded (integer) vectors, so nothing is rounded that was not before, and kept in fp32: twice the bytes, which is why
+// larger batches, whose time is those bytes, do without.
+//
 // Measured per step of 1,900 / 45 / 1 rows, alone: 92 / 42 / 38 us as four launches, 71 / 30 / 25 us as one.
 //
 // Caches: row c (a sentence), position p: keys at kv[((c * row_positions + p) * 2) * d], values d elements later; scales
@@ -64,9 +70,9 @@ __device__ __forceinline__ void d1_load(const float *p, float (&x)[NE]) {
   }
 }
 
-// x (NE elements per lane, one vector per wave) -> integer codes at dst, scale at *sc
+// x (NE elements per lane, one vector per wave) -> integer codes at dst, scale at *sc; x becomes code * scale
 template <int NE>
-__device__ __forceinline__ void d1_quantize_store(const float (&x)[NE], short *dst, float *sc, int lane) {
+__device__ __forceinline__ void d1_quantize_store(float (&x)[NE], short *dst, float *sc, int lane) {
   typedef short shortNE __attribute__((ext_vector_type(NE)));
   float amax = 0.f;
 #pragma unroll
@@ -80,14 +86,16 @@ __device__ __forceinline__ void d1_quantize_store(const float (&x)[NE], short *d
     float c = rintf(x[e] * inv);
     c = fminf(fmaxf(c, -32767.f), 32767.f);
     qv[e] = (short)(int)c;
+    x[e] = c * scale;
   }
   *(shortNE *)(dst + lane * NE) = qv;
   if (lane == 0) *sc = scale;
 }
 
-// fp32 rows [M][2 d] (key | value of one position each) -> integer cache + scales
-template <int NE>
-__global__ __launch_bounds__(256) void quantize_kv_i16_kernel(const float *x, long M, short *cache, float *sc) {
+// fp32 rows [M][2 d] (key | value of one position each) -> integer cache + scales.
+// PLANES (the folded cross cache below): the rounded vectors also as head / tail planes, and key_const[m] = u . key.
+template <int NE, bool PLANES>
+__global__ __launch_bounds__(256) void quantize_kv_i16_kernel(const float *x, long M, short *cache, float *sc, KvPlanes pl) {
   constexpr int D = NE * 64;
   const int lane = threadIdx.x & 63;
   const long m = (long)blockIdx.x * 4 + (threadIdx.x >> 6);
@@ -102,15 +110,37 @@ __global__ __launch_bounds__(256) void quantize_kv_i16_kernel(const float *x, lo
       v[e] = t[0], v[e + 1] = t[1], v[e + 2] = t[2], v[e + 3] = t[3];
     }
     d1_quantize_store<NE>(v, cache + (m * 2 + which) * D, sc + m * 2 + which, lane);
+    if constexpr (PLANES) {  // v holds code * scale now
+      typedef _Float16 halfNE __attribute__((ext_vector_type(NE)));
+      halfNE hi, lo;
+#pragma unroll
+      for (int e = 0; e < NE; e++) {
+        hi[e] = (_Float16)v[e];
+        lo[e] = (_Float16)(v[e] - (float)hi[e]);
+      }
+      _Float16 *dst = (which ? pl.v : pl.k) + m * D + lane * NE;
+      *(halfNE *)dst = hi;
+      *(halfNE *)(dst + pl.lo_offset) = lo;
+      if (which == 0) {
+        float u[NE], s = 0.f;
+        d1_load<NE>(pl.u + lane * NE, u);
+#pragma unroll
+        for (int e = 0; e < NE; e++) s += u[e] * v[e];
+        s = d1_wave_sum(s);
+        if (lane == 0) pl.key_const[m] = s * pl.scale;
+      }
+    }
   }
 }
 
-hipError_t launch_quantize_kv_i16(const float *x, long M, int d, short *cache, float *sc, hipStream_t s) {
+hipError_t launch_quantize_kv_i16(const float *x, long M, int d, short *cache, float *sc, const KvPlanes *planes, hipStream_t s) {
   if (M <= 0) return hipSuccess;
   const dim3 grid((unsigned)((M + 3) / 4)), block(256);
-  if (d == 512) hipLaunchKernelGGL(quantize_kv_i16_kernel<8>, grid, block, 0, s, x, M, cache, sc);
-  else if (d == 256) hipLaunchKernelGGL(quantize_kv_i16_kernel<4>, grid, block, 0, s, x, M, cache, sc);
-  else return hipErrorInvalidValue;
+  if (d != 512 && d != 256) return hipErrorInvalidValue;
+#define NT_QKV(NE_, P_) hipLaunchKernelGGL((quantize_kv_i16_kernel<NE_, P_>), grid, block, 0, s, x, M, cache, sc, planes ? *planes : KvPlanes{})
+  if (d == 512) { if (planes) NT_QKV(8, true); else NT_QKV(8, false); }
+  else { if (planes) NT_QKV(4, true); else NT_QKV(4, false); }
+#undef NT_QKV
   return hipGetLastError();
 }
 
@@ -135,24 +165,27 @@ struct D1Part {
 };
 
 // The keys of one block and their fold into a partial softmax; positions past the end repeat the last key and get
-// weight 0.
-template <int NE>
+// weight 0.  F32: fp32 keys and values, each key with an additive constant (sc[p]), instead of integers with scales.
+template <int NE, bool F32>
 struct D1Block {
   typedef short shortNE __attribute__((ext_vector_type(NE)));
-  shortNE k[D1_NK], v[D1_NK];
+  typedef float floatNE __attribute__((ext_vector_type(NE)));
+  typedef typename std::conditional<F32, floatNE, shortNE>::type Vec;
+  typedef typename std::conditional<F32, float, short>::type Elt;
+  Vec k[D1_NK], v[D1_NK];
   float ks[D1_NK], vs[D1_NK];
 
-  __device__ __forceinline__ void load(const short *kv, const float *sc, long pos0, int j0, int n, int lane) {
+  __device__ __forceinline__ void load(const void *kv, const float *sc, long pos0, int j0, int n, int lane) {
     constexpr int D = NE * 64;
 #pragma unroll
     for (int i = 0; i < D1_NK; i++) {
       const int j = j0 + i < n ? j0 + i : n - 1;
       const long p = pos0 + j;
-      const short *kp = kv + p * 2 * D + lane * NE;
-      k[i] = *(const shortNE *)kp;
-      v[i] = *(const shortNE *)(kp + D);
-      ks[i] = sc[p * 2];
-      vs[i] = sc[p * 2 + 1];
+      const Elt *kp = (const Elt *)kv + p * 2 * D + lane * NE;
+      k[i] = *(const Vec *)kp;
+      v[i] = *(const Vec *)(kp + D);
+      ks[i] = F32 ? sc[p] : sc[p * 2];
+      vs[i] = F32 ? 1.f : sc[p * 2 + 1];
     }
   }
   __device__ __forceinline__ void fold(const float (&q)[NE], int j0, int n, int lane, D1Part<NE> &a) const {
@@ -188,7 +221,8 @@ struct D1Block {
     float s[D1_NK], bm = -INFINITY;
 #pragma unroll
     for (int i = 0; i < D1_NK; i++) {
-      s[i] = __uint_as_float((unsigned)__builtin_amdgcn_readlane((int)__float_as_uint(r1), 16 * i)) * ks[i];
+      const float dot = __uint_as_float((unsigned)__builtin_amdgcn_readlane((int)__float_as_uint(r1), 16 * i));
+      s[i] = F32 ? dot + ks[i] : dot * ks[i];
       if (j0 + i >= n) s[i] = -INFINITY;
       bm = fmaxf(bm, s[i]);
     }
@@ -199,7 +233,7 @@ struct D1Block {
     for (int i = 0; i < D1_NK; i++) {
       w[i] = __expf(s[i] - mn);  // exp(-inf) = 0 for the positions past the end
       wsum += w[i];
-      w[i] *= vs[i];
+      if (!F32) w[i] *= vs[i];
     }
     a.l = a.l * corr + wsum;
 #pragma unroll
@@ -214,8 +248,9 @@ struct D1Block {
 };
 
 // D: model width.  RW: rows per workgroup (8 / RW waves each).  PARTS: partial softmaxes per row.  IND: row r uses cache
-// row origin[r] (< 0: no row, zero context).  FFN: the layer's FFN (of width D) is part of the chain.
-template <int D, int RW, int NWAVES, int PARTS, bool IND, bool FFN>
+// row origin[r] (< 0: no row, zero context).  FFN: the layer's FFN (of width D) is part of the chain.  FOLD: the cross cache
+// holds folded fp32 vectors.
+template <int D, int RW, int NWAVES, int PARTS, bool IND, bool FFN, bool FOLD>
 __global__ __launch_bounds__(NWAVES * 64) void dec1_kernel(Dec1Args a) {
   constexpr int NE = D / 64, WR = NWAVES / RW, PW = PARTS / WR;  // elements per lane; waves per row; partials per wave
   constexpr int NC = D / NWAVES, NT = NC / 16;                   // output columns of a wave, in tiles of 16
@@ -343,11 +378,11 @@ __global__ __launch_bounds__(NWAVES * 64) void dec1_kernel(Dec1Args a) {
     for (int e = 0; e < NE; e++) y[e] = ga[e] * ((y[e] - mean) * rs) + be[e];
   };
   // attention of this wave's row over n cached keys; the partials may hold the newest key already.  The merged context
-  // goes to the planes
-  auto attend = [&](const float (&q)[NE], const short *kv, const float *sc, long pos0, int n, Part (&st)[PW]) {
+  // goes to done(ctx) in the row's first wave
+  auto attend = [&](auto f32_tag, const float (&q)[NE], const void *kv, const float *sc, long pos0, int n, Part (&st)[PW], auto done) {
     constexpr int STEP = PARTS * D1_NK;
     // two blocks in flight: the next one of the wave's only partial, or one of each of its two
-    D1Block<NE> b[2];
+    D1Block<NE, decltype(f32_tag)::value> b[2];
     const int j_first = pg * PW * D1_NK;
     if constexpr (NWAVES == 16) {  // 128 registers: one block at a time
       for (int j = j_first; j < n; j += STEP)
@@ -407,7 +442,7 @@ __global__ __launch_bounds__(NWAVES * 64) void dec1_kernel(Dec1Args a) {
       float ctx[NE];
 #pragma unroll
       for (int e = 0; e < NE; e++) ctx[e] = t.acc[e] * inv;
-      store_planes(ctx);
+      done(ctx);
     }
     __syncthreads();
   };
@@ -444,42 +479,56 @@ __global__ __launch_bounds__(NWAVES * 64) void dec1_kernel(Dec1Args a) {
       d1_quantize_store<NE>(kx, a.self_kv + p * 2 * D, a.self_sc + p * 2, lane);
       d1_quantize_store<NE>(vx, a.self_kv + p * 2 * D + D, a.self_sc + p * 2 + 1, lane);
     }
-    attend(q, a.self_kv, a.self_sc, pos0, n_self > 0 ? n_self - 1 : 0, st);
+    attend(std::false_type{}, q, a.self_kv, a.self_sc, pos0, n_self > 0 ? n_self - 1 : 0, st, store_planes);
   }
   // ---- output projection + residual, LayerNorm, cross-attention query ----
   if (!EARLY) preload(a.Wo_self);
   project(a.Wo_self, sA);
-  preload(a.Wq);
+  if (!FOLD) preload(a.Wq);
   add_residual(a.bo_self);
   __syncthreads();
-  {
-    float y[NE];
-    normalise(a.ln2.gamma, a.ln2.beta, y);
-    if (pg == 0) store_planes(y);
-  }
-  __syncthreads();
-  project(a.Wq, sA);
-  if (EARLY) preload(a.Wo_cross);
-  {
-    float bias[NT];
-#pragma unroll
-    for (int t = 0; t < NT; t++) bias[t] = a.bq[n0 + t * 16 + c16];
-    results([&](int i, int n, float x) { sQ[i * ZLD + n] = (x + bias[(n - n0) >> 4]) * a.q_scale; });
-  }
-  __syncthreads();
-  // ---- cross-attention, output projection + residual ----
-  {
+  if constexpr (FOLD) {
+    // ---- cross-attention over the folded cache: the normalised row is the query, the context adds to the residual ----
+    normalise(a.ln2.gamma, a.ln2.beta, q);
+    if (FFN) preload(a.W1);
     Part st[PW];
 #pragma unroll
     for (int u = 0; u < PW; u++) st[u].clear();
-    d1_load<NE>(sQ + rw * ZLD + lane * NE, q);
-    attend(q, a.cross_kv, a.cross_sc, (long)rc * a.cross_positions, n_cross, st);
+    attend(std::true_type{}, q, a.cross_kv, a.cross_sc, (long)rc * a.cross_positions, n_cross, st, [&](const float (&ctx)[NE]) {
+      float *z = sZ + rw * ZLD + lane * NE;
+#pragma unroll
+      for (int e = 0; e < NE; e++) z[e] += ctx[e];
+    });
+  } else {
+    {
+      float y[NE];
+      normalise(a.ln2.gamma, a.ln2.beta, y);
+      if (pg == 0) store_planes(y);
+    }
+    __syncthreads();
+    project(a.Wq, sA);
+    if (EARLY) preload(a.Wo_cross);
+    {
+      float bias[NT];
+#pragma unroll
+      for (int t = 0; t < NT; t++) bias[t] = a.bq[n0 + t * 16 + c16];
+      results([&](int i, int n, float x) { sQ[i * ZLD + n] = (x + bias[(n - n0) >> 4]) * a.q_scale; });
+    }
+    __syncthreads();
+    // ---- cross-attention, output projection + residual ----
+    {
+      Part st[PW];
+#pragma unroll
+      for (int u = 0; u < PW; u++) st[u].clear();
+      d1_load<NE>(sQ + rw * ZLD + lane * NE, q);
+      attend(std::false_type{}, q, a.cross_kv, a.cross_sc, (long)rc * a.cross_positions, n_cross, st, store_planes);
+    }
+    if (!EARLY) preload(a.Wo_cross);
+    project(a.Wo_cross, sA);
+    if (FFN) preload(a.W1);
+    add_residual(a.bo_cross);
+    __syncthreads();
   }
-  if (!EARLY) preload(a.Wo_cross);
-  project(a.Wo_cross, sA);
-  if (FFN) preload(a.W1);
-  add_residual(a.bo_cross);
-  __syncthreads();
   if constexpr (FFN) {
     float y[NE];
     normalise(a.ln3.gamma, a.ln3.beta, y);
@@ -539,16 +588,17 @@ static hipError_t d1_launch(const Dec1Args &a, hipStream_t s) {
   // tokens: 24.4 against 26.7 ms).  With other lanes busy four rows from 64 on (a 4,096-token budget: 29.9 against 30.5
   // ms), eight from 257 on (65,536 tokens: 550 against 554 ms): less weight traffic, and CUs for the others.
   const bool parts = (a.shape_rows > 0 ? a.shape_rows : a.rows) < 1024;
-#define NT_D1(RW_, NW_, P_)                                                                                             \
+#define NT_D1(RW_, NW_, P_, F_)                                                                                          \
   do {                                                                                                                  \
     const dim3 grid((unsigned)((a.rows + RW_ - 1) / RW_));                                                              \
-    if (a.origin) hipLaunchKernelGGL((dec1_kernel<D, RW_, NW_, P_, true, FFN>), grid, dim3(64 * NW_), 0, s, a);         \
-    else hipLaunchKernelGGL((dec1_kernel<D, RW_, NW_, P_, false, FFN>), grid, dim3(64 * NW_), 0, s, a);                 \
+    if (a.origin) hipLaunchKernelGGL((dec1_kernel<D, RW_, NW_, P_, true, FFN, F_>), grid, dim3(64 * NW_), 0, s, a);     \
+    else hipLaunchKernelGGL((dec1_kernel<D, RW_, NW_, P_, false, FFN, F_>), grid, dim3(64 * NW_), 0, s, a);             \
   } while (0)
-  if (!parts) NT_D1(16, 16, 1);
-  else if (a.rows <= (a.crowded ? 64 : 512)) NT_D1(2, 8, 4);
-  else if (a.rows <= 256 || !a.crowded) NT_D1(4, 16, 4);
-  else NT_D1(8, 16, 4);
+  if (a.folded) NT_D1(2, 8, 4, true);
+  else if (!parts) NT_D1(16, 16, 1, false);
+  else if (a.rows <= (a.crowded ? 64 : 512)) NT_D1(2, 8, 4, false);
+  else if (a.rows <= 256 || !a.crowded) NT_D1(4, 16, 4, false);
+  else NT_D1(8, 16, 4, false);
 #undef NT_D1
   return hipGetLastError();
 }

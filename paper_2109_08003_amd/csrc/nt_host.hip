@@ -127,6 +127,7 @@ struct Attn {
   const _Float16 *Wo = nullptr;    // [d][d]
   // the same matrices in MFMA fragment order (streaming GEMM), nullptr where the shape is not supported
   const _Float16 *Wqkv_p = nullptr, *Wq_p = nullptr, *Wkv_p = nullptr, *Wo_p = nullptr;
+  const _Float16 *Wq_back_p = nullptr;  // Wq the other way round (its product with a key): folded cross caches
   const float *bqkv = nullptr, *bq = nullptr, *bkv = nullptr, *bo = nullptr;
   const float *rk = nullptr;       // [2c+1][dh]
 };
@@ -215,6 +216,11 @@ struct nt_model {
   // bit 1: attention context -> output projection, bit 2: final LayerNorm -> cross K|V, bit 3: the FFN's first matrix;
   // with bit 0 clear, bits 4 / 5 / 6: the q / k / v columns of Q|K|V alone; bit 7: q and k stored as plain fp16)
   unsigned enc_tails = kEncTailsAll;
+  // Small batches additionally keep the cross cache multiplied by the query and output matrices, in fp32 (nt_dec1.hip):
+  // per decoder layer [fold_positions, 2d] and one constant per key; folded says whether the encoded batch has it
+  std::vector<float *> cross_fold, fold_const;
+  int64_t fold_positions = 0;
+  bool folded = false;
   std::vector<float *> cross_sc, self_sc;  // per decoder layer [Mt,2] / [self_positions,2] scales
   float *z = nullptr, *a32 = nullptr, *q32 = nullptr, *ctx32 = nullptr, *u32 = nullptr;  // [Br, d|F]
   unsigned long long *pk = nullptr;
@@ -372,6 +378,12 @@ int alloc_lane_state(nt_model *m, hipStream_t s) {
   const size_t o_x = cv.take((size_t)Mt * d * 4), o_a16 = cv.take((size_t)Mt * d * kEncElt),
                o_qkv = cv.take((size_t)Mt * 3 * d * kEncElt), o_ctx16 = cv.take((size_t)Mt * d * kEncElt),
                o_u16 = cv.take((size_t)Mt * std::max(F, 1) * kEncElt), o_enc = cv.take((size_t)Mt * d * kEncElt);
+  m->fold_positions = m->kv_i16 ? std::min<int64_t>(Mt, (int64_t)nt::kDec1FoldRows * cfg->max_len) : 0;
+  std::vector<size_t> o_fold(cfg->n_dec), o_fconst(cfg->n_dec);
+  for (int l = 0; l < cfg->n_dec; l++) {
+    o_fold[l] = cv.take((size_t)m->fold_positions * 2 * d * 4 + 16);
+    o_fconst[l] = cv.take((size_t)m->fold_positions * 4 + 16);
+  }
   std::vector<size_t> o_cross(cfg->n_dec), o_self(cfg->n_dec), o_cross_sc(cfg->n_dec), o_self_sc(cfg->n_dec);
   for (int l = 0; l < cfg->n_dec; l++) o_cross[l] = cv.take((size_t)Mt * 2 * d * (m->kv_i16 ? 2 : kCrossElt));
   for (int l = 0; l < cfg->n_dec; l++) o_self[l] = cv.take((size_t)m->self_positions * 2 * d * (m->kv_i16 ? 2 : 4));
@@ -396,6 +408,7 @@ int alloc_lane_state(nt_model *m, hipStream_t s) {
   m->ctx_enc = A + o_ctx16; m->u_enc = A + o_u16; m->enc_out = A + o_enc;
   for (int l = 0; l < cfg->n_dec; l++) {
     m->cross.push_back(A + o_cross[l]); m->self_kv.push_back(at<float>(A, o_self[l]));
+    m->cross_fold.push_back(at<float>(A, o_fold[l])); m->fold_const.push_back(at<float>(A, o_fconst[l]));
     m->cross_sc.push_back(at<float>(A, o_cross_sc[l])); m->self_sc.push_back(at<float>(A, o_self_sc[l]));
   }
   m->z = at<float>(A, o_z); m->a32 = at<float>(A, o_a32); m->q32 = at<float>(A, o_q32); m->ctx32 = at<float>(A, o_ctx32);
@@ -630,6 +643,11 @@ int nt_load_weights(const nt_config *cfg, const void *h_blob_fp16, size_t blob_b
     if (!cross) fused(0, 3, (const void **)&a.Wqkv, (const void **)&a.bqkv, (const void **)&a.Wqkv_p);
     else {
       fused(0, 1, (const void **)&a.Wq, (const void **)&a.bq, (const void **)&a.Wq_p);
+      if (m->kv_i16) {
+        const size_t ob = pk.reserve(nt::vocab_pack_bytes(d, d));
+        nt::vocab_pack(W[0], d, d, (_Float16 *)(pk.img.data() + ob));
+        fixes.push_back({ob, (const void **)&a.Wq_back_p});
+      }
       fused(1, 2, (const void **)&a.Wkv, (const void **)&a.bkv, (const void **)&a.Wkv_p);
     }
     fused(3, 1, (const void **)&a.Wo, (const void **)&a.bo, (const void **)&a.Wo_p);
@@ -735,7 +753,7 @@ int nt_load_weights(const nt_config *cfg, const void *h_blob_fp16, size_t blob_b
       for (auto &st : ln->stage) st = nt_model::Staging();
       ln->lane_stream = nullptr; ln->lane_start = nullptr;
       ln->h_progress = nullptr; ln->d_progress = nullptr; ln->decode_seq = 0;  // lane 0's: never freed through a clone
-      ln->cross.clear(); ln->self_kv.clear(); ln->cross_sc.clear(); ln->self_sc.clear();
+      ln->cross_fold.clear(); ln->fold_const.clear(); ln->cross.clear(); ln->self_kv.clear(); ln->cross_sc.clear(); ln->self_sc.clear();
       m->lanes.push_back(ln);
       rc = alloc_lane_state(ln, s);
       if (rc) return rc;
@@ -847,6 +865,8 @@ int nt_encode(nt_model *m, const int32_t *d_src, const int32_t *d_len, int32_t B
   if (!all_fused)
     KT(K_LN_ENC, Md * dd * (4 + ea), 8 * Md * dd,
        nt::launch_layer_norm(m->x, M, d, m->enc_final.g, m->enc_final.b, lne, m->enc_out, ln_mode, lo_d, s));
+  m->folded = m->kv_i16 && B <= nt::kDec1FoldRows && M <= m->fold_positions;
+  const float dec_qscale = 1.0f / std::sqrt((float)(d / dec_heads(&c)));
   for (int l = 0; l < c.n_dec; l++) {
     nt::GemmEpilogue e;
     e.bias = m->dec[l].cross.bkv; e.dst0 = m->cross[l]; e.ld0 = 2 * d; e.n_split = 2 * d;
@@ -861,9 +881,20 @@ int nt_encode(nt_model *m, const int32_t *d_src, const int32_t *d_len, int32_t B
     else
       KT(K_GEMM_CROSS_KV, gemm_bytes(Md, dd, 2 * dd, ea, ca, false), 4 * Md * dd * dd,
          nt::launch_gemm(amode, c32, m->enc_out, lo_of(m->enc_out, lo_d), d, m->dec[l].cross.Wkv, M, 2 * d, d, e, s, m->dec[l].cross.Wkv_p));
-    if (m->kv_i16)
+    if (m->kv_i16) {
+      const nt::KvPlanes pl{(_Float16 *)m->ctx_enc, (_Float16 *)m->a_enc, lo_d, m->dec[l].cross.bq, dec_qscale, m->fold_const[l]};
       KT(K_KV_QUANT, Md * 2 * dd * 6, Md * 2 * dd * 4,
-         nt::launch_quantize_kv_i16((const float *)m->qkv, M, d, (short *)m->cross[l], m->cross_sc[l], s));
+         nt::launch_quantize_kv_i16((const float *)m->qkv, M, d, (short *)m->cross[l], m->cross_sc[l], m->folded ? &pl : nullptr, s));
+      if (m->folded) {  // keys times the query matrix (and its scale), values times the output matrix (and its bias)
+        nt::GemmEpilogue k, v;
+        k.scale = dec_qscale; k.scale_cols = d; k.dst0 = m->cross_fold[l]; k.ld0 = 2 * d; k.n_split = d;
+        v.bias = m->dec[l].cross.bo; v.dst0 = m->cross_fold[l] + d; v.ld0 = 2 * d; v.n_split = d;
+        KT(K_GEMM_CROSS_KV, gemm_bytes(Md, dd, dd, ea, 4, false), 2 * Md * dd * dd,
+           nt::launch_gemm(amode, true, pl.k, pl.k + lo_d, d, nullptr, M, d, d, k, s, m->dec[l].cross.Wq_back_p));
+        KT(K_GEMM_CROSS_KV, gemm_bytes(Md, dd, dd, ea, 4, false), 2 * Md * dd * dd,
+           nt::launch_gemm(amode, true, pl.v, pl.v + lo_d, d, m->dec[l].cross.Wo, M, d, d, v, s, m->dec[l].cross.Wo_p));
+      }
+    }
   }
   m->len_prefix.clear();
   m->B = B; m->S = S; m->encoded = true;
@@ -1059,7 +1090,9 @@ int decode_step(nt_model *m, DecodeCursor &cu, hipStream_t s) {
           at.self_positions = T; at.n_keys = t + 1;
           at.Wo_self = L.self.Wo_p; at.bo_self = L.self.bo; at.Wq = L.cross.Wq_p; at.bq = L.cross.bq; at.Wo_cross = L.cross.Wo_p;
           at.bo_cross = L.cross.bo; at.q_scale = qscale; at.ln2 = nt::GemmLayerNorm{L.ln2.g, L.ln2.b, lne};
-          at.cross_kv = (const short *)m->cross[l]; at.cross_sc = m->cross_sc[l]; at.cross_positions = S; at.len = m->len;
+          at.folded = m->folded; at.cross_positions = S; at.len = m->len;
+          at.cross_kv = m->folded ? (const void *)m->cross_fold[l] : m->cross[l];
+          at.cross_sc = m->folded ? m->fold_const[l] : m->cross_sc[l];
           if (ffn_inside) {
             at.ln3 = nt::GemmLayerNorm{L.ln3.g, L.ln3.b, lne}; at.W1 = L.ffn.W1_p; at.b1 = L.ffn.b1; at.W2 = L.ffn.W2_p; at.b2 = L.ffn.b2;
           }

@@ -363,8 +363,9 @@ struct Dec1Args {
   const float *bo_self, *bq, *bo_cross;
   float q_scale;
   GemmLayerNorm ln2;
-  const short *cross_kv;
-  const float *cross_sc;
+  const void *cross_kv;  // integers with scales in cross_sc, or (folded) fp32 [position][2 d] with one constant per key in
+  const float *cross_sc; // cross_sc: keys multiplied by the query matrix and scale, values by the output matrix (+ bias)
+  int folded;
   long cross_positions;
   const int32_t *len;    // keys of each cache row
   // FFN of width d (W1 == nullptr: none, or not part of this launch)
@@ -378,8 +379,17 @@ struct Dec1Args {
   float *lo_norm;
 };
 hipError_t launch_dec1(const Dec1Args &a, int d, hipStream_t s);
-// x [M][2 d] fp32 (key | value of M positions) -> codes [M][2][d] and scales [M][2]
-hipError_t launch_quantize_kv_i16(const float *x, long M, int d, short *cache, float *sc, hipStream_t s);
+constexpr int kDec1FoldRows = 64;
+// x [M][2 d] fp32 (key | value of M positions) -> codes [M][2][d] and scales [M][2]; planes (optional): the rounded
+// vectors as head / tail planes [M][d] (tail lo_offset elements after the head) and key_const[m] = scale * (u . key)
+struct KvPlanes {
+  _Float16 *k, *v;
+  long lo_offset;
+  const float *u;
+  float scale;
+  float *key_const;
+};
+hipError_t launch_quantize_kv_i16(const float *x, long M, int d, short *cache, float *sc, const KvPlanes *planes, hipStream_t s);
 
 // max dynamic LDS the encoder attention needs for (S, dh); used to validate shapes at load.
 size_t enc_attention_lds_bytes(int S, int dh, bool f32);
