@@ -27,7 +27,8 @@
 // Wo (sum p v) + bo = sum p (Wo v + bo): with the keys and values of a sentence multiplied by the two matrices once, when
 // the batch is encoded, a step needs neither projection - 8 of the 20 us at one row.  The products are formed from the
 // rounded (integer) vectors, so nothing is rounded that was not before, and kept in fp32: twice the bytes, which is why
-// larger batches, whose time is those bytes, do without.
+// larger batches, whose time is those bytes, do without (a 4,096-token budget, batches of 36 to 341 rows: 29.0 ms folded up to
+// 64 rows, 27.6 up to 256 or 512; 320 long sentences: 24.2 ms without, 25.4 with).
 //
 // Measured per step of 1,900 / 45 / 1 rows, alone: 92 / 42 / 38 us as four launches, 71 / 30 / 25 us as one.
 //

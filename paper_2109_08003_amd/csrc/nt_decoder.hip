@@ -225,22 +225,14 @@ __device__ __forceinline__ void dc_planes_to_lds(const float (&y)[DC_TM / DC_WAV
   }
 }
 
-__device__ __forceinline__ unsigned long long dc_wave_max_u64(unsigned long long x) {
-#pragma unroll
-  for (int m = 32; m >= 1; m >>= 1) {
-    const unsigned long long o = shfl_xor_u64(x, m);
-    x = o > x ? o : x;
-  }
-  return x;
-}
-
 // -----------------------------------------------------------------------------------------------------------------
 // Start of a decoder step fused into the self-attention projection.
 // Grid: row tiles of rows_prev x col_groups.  Every workgroup of a row tile gathers and normalises the tile (cheap);
 // the first of them also collects the tokens of the previous step and writes the residual stream z.  Row tiles
 // beyond rows_now exist only to collect tokens of rows that have just finished.
 // -----------------------------------------------------------------------------------------------------------------
-template <int K>
+// SPLIT: one strip per workgroup, its k-range dealt to the eight waves.
+template <int K, bool SPLIT>
 __global__ __launch_bounds__(DC_WAVES * 64) void dec_qkv_kernel(DecQkvArgs a, int col_groups) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   _Float16 *sh = (_Float16 *)smem;
@@ -255,40 +247,94 @@ __global__ __launch_bounds__(DC_WAVES * 64) void dec_qkv_kernel(DecQkvArgs a, in
   if (m0 >= M && cg != 0) return;  // a tile kept only for the collection of tokens: one workgroup is enough
   if (sb.cert_count && blockIdx.x == 0 && tid == 0) *sb.cert_count = 0;
 
-  // ---- the tokens: result of the previous step's arg-max (collected into out), or given ----
+  // the weights travel while the tokens are found and the rows normalised
+  const int NS = a.N >> 6;
+  const int sb0 = (int)((long)cg * NS / col_groups), sb1 = (int)((long)(cg + 1) * NS / col_groups);
+  const DcWeights w(a.Wp, NS, K, lane);
+  constexpr int KSW = S::KS / DC_WAVES;  // k-steps of a wave when the waves share a strip
+  half8 wb[SPLIT ? KSW : DC_SL][2];
+  int strip = SPLIT ? sb0 : sb0 + wave;
+  const bool have = m0 < M && strip < sb1;
+  if constexpr (SPLIT) {
+    if (have) {
+#pragma unroll
+      for (int q = 0; q < KSW; q++) {
+        wb[q][0] = w.load((strip * S::KS + wave * KSW + q) * 2048, 0);
+        wb[q][1] = w.load((strip * S::KS + wave * KSW + q) * 2048, 1);
+      }
+    }
+  } else {
+    if (have) dc_preload<K>(w, strip, wb);
+  }
+
+  // ---- the tokens: result of the previous step's arg-max (collected into out), or given.  The loads and exchanges of the
+  // wave's rows advance together ----
   int y[RPW];
+  if (a.tok_in) {
+#pragma unroll
+    for (int i = 0; i < RPW; i++) {
+      const int r = m0 + wave + DC_WAVES * i;
+      y[i] = r < M ? a.tok_in[r] : sb.pad_id;
+    }
+  } else if (sb.t > 0 && (sb.prev_cert || sb.pk)) {
+    if (sb.prev_cert) {
+      int sl[RPW];
+#pragma unroll
+      for (int i = 0; i < RPW; i++) {
+        const int r = m0 + wave + DC_WAVES * i;
+        sl[i] = r < sb.rows_prev ? sb.slot_of_row[r] : -1;
+        y[i] = r < sb.rows_prev ? sb.tok[r] : sb.pad_id;
+      }
+#pragma unroll
+      for (int i = 0; i < RPW; i++)
+        if (sl[i] >= 0) y[i] = (int)(0xFFFFFFFFu - (unsigned int)sb.final_key[sl[i]]);
+    } else {
+      unsigned long long k[RPW];
+#pragma unroll
+      for (int i = 0; i < RPW; i++) k[i] = 0ull;
+      for (int q = lane; q < sb.n_partials; q += 64) {
+#pragma unroll
+        for (int i = 0; i < RPW; i++) {
+          const int r = m0 + wave + DC_WAVES * i;
+          if (r < sb.rows_prev) {
+            const unsigned long long c = sb.pk[(long)r * sb.n_partials + q];
+            k[i] = c > k[i] ? c : k[i];
+          }
+        }
+      }
+#pragma unroll
+      for (int m = 32; m >= 1; m >>= 1) {
+#pragma unroll
+        for (int i = 0; i < RPW; i++) {
+          const unsigned long long o = shfl_xor_u64(k[i], m);
+          k[i] = o > k[i] ? o : k[i];
+        }
+      }
+#pragma unroll
+      for (int i = 0; i < RPW; i++) y[i] = (int)(0xFFFFFFFFu - (unsigned int)k[i]);
+    }
+#pragma unroll
+    for (int i = 0; i < RPW; i++) {
+      const int r = m0 + wave + DC_WAVES * i;
+      if (y[i] < 0 || y[i] >= sb.vocab) y[i] = sb.pad_id;  // cannot happen: every key holds a valid id
+      if (cg == 0 && lane == 0 && r < sb.rows_prev) sb.out[(long)r * sb.out_ld + sb.t - 1] = y[i];
+    }
+  } else {
+#pragma unroll
+    for (int i = 0; i < RPW; i++) y[i] = sb.bos_id;
+  }
 #pragma unroll
   for (int i = 0; i < RPW; i++) {
     const int r = m0 + wave + DC_WAVES * i;
-    int tokn = sb.bos_id;
-    if (a.tok_in) {
-      tokn = r < M ? a.tok_in[r] : sb.pad_id;
-    } else if (sb.t > 0 && r < sb.rows_prev && (sb.prev_cert || sb.pk)) {
-      if (sb.prev_cert) {
-        const int sl = sb.slot_of_row[r];
-        tokn = (sl < 0) ? sb.tok[r] : (int)(0xFFFFFFFFu - (unsigned int)sb.final_key[sl]);
-      } else {
-        unsigned long long k = 0ull;
-        const unsigned long long *p = sb.pk + (long)r * sb.n_partials;
-        for (int q = lane; q < sb.n_partials; q += 64) {
-          const unsigned long long c = p[q];
-          k = c > k ? c : k;
-        }
-        k = dc_wave_max_u64(k);
-        tokn = (int)(0xFFFFFFFFu - (unsigned int)k);
-      }
-      if (tokn < 0 || tokn >= sb.vocab) tokn = sb.pad_id;  // cannot happen: every key holds a valid id
-      if (cg == 0 && lane == 0) sb.out[(long)r * sb.out_ld + sb.t - 1] = tokn;
-    }
     if (sb.forced && r < M) {
-      tokn = sb.forced[(long)r * sb.forced_ld + sb.t];
-      if (tokn < 0 || tokn >= sb.vocab) {
+      y[i] = sb.forced[(long)r * sb.forced_ld + sb.t];
+      if (y[i] < 0 || y[i] >= sb.vocab) {
         if (lane == 0) sb.flags[0] = 1;
-        tokn = sb.pad_id;
+        y[i] = sb.pad_id;
       }
     }
-    if (r >= M) tokn = sb.pad_id;  // rows past the active ones compute on the padding token and store nothing
-    y[i] = __builtin_amdgcn_readfirstlane(tokn);
+    if (r >= M) y[i] = sb.pad_id;  // rows past the active ones compute on the padding token and store nothing
+    y[i] = __builtin_amdgcn_readfirstlane(y[i]);
   }
   if (m0 >= M) return;  // uniform over the workgroup
 
@@ -322,23 +368,53 @@ __global__ __launch_bounds__(DC_WAVES * 64) void dec_qkv_kernel(DecQkvArgs a, in
   dc_planes_to_lds<K>(xv, sh, wave, lane);
 
   // ---- Q|K|V projection of the tile: strips sb0 .. sb1 of this column group, wave by wave ----
-  const int NS = a.N >> 6;
-  const int sb0 = (int)((long)cg * NS / col_groups), sb1 = (int)((long)(cg + 1) * NS / col_groups);
-  const DcWeights w(a.Wp, NS, K, lane);
-  half8 wb[DC_SL][2];
-  int strip = sb0 + wave;
-  const bool have = strip < sb1;
-  if (have) dc_preload<K>(w, strip, wb);
   __syncthreads();
-  if (!have) return;
   const _Float16 *hrow = sh + li * LD + g * 8;
-  half8 hf[2];
-  hf[0] = *(const half8 *)hrow;
-  hf[1] = *(const half8 *)(hrow + DC_TM * LD);
-  for (; strip < sb1; strip += DC_WAVES) {
+  if constexpr (SPLIT) {
+    // one strip per workgroup, every wave an eighth of its k-steps; partial tiles meet in the LDS (over the planes)
     floatx16 acc[2];
-    dc_strip<K>(w, hrow, hf, wb, strip, strip + DC_WAVES < sb1 ? strip + DC_WAVES : strip, acc);
-    dc_store_strip<true>(acc, a.e, strip, m0, M, li, g);
+#pragma unroll
+    for (int nb = 0; nb < 2; nb++)
+#pragma unroll
+      for (int v = 0; v < 16; v++) acc[nb][v] = 0.f;
+#pragma unroll
+    for (int q = 0; q < KSW; q++)
+#pragma unroll
+      for (int op = 0; op < 2; op++) {
+        const half8 h = *(const half8 *)(hrow + op * DC_TM * LD + (wave * KSW + q) * 16);
+#pragma unroll
+        for (int nb = 0; nb < 2; nb++) acc[nb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(h, wb[q][nb], acc[nb], 0, 0, 0);
+      }
+    f32x4 *red = (f32x4 *)smem;  // [wave][register group][lane]
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < 8; q++)
+      red[(wave * 8 + q) * 64 + lane] = f32x4{acc[q >> 2][(q & 3) * 4], acc[q >> 2][(q & 3) * 4 + 1], acc[q >> 2][(q & 3) * 4 + 2], acc[q >> 2][(q & 3) * 4 + 3]};
+    __syncthreads();
+    f32x4 t = red[wave * 64 + lane];  // this wave's register group: block wave / 4, rows (wave % 4) * 8 + g * 4 ..
+#pragma unroll
+    for (int p = 1; p < DC_WAVES; p++) t += red[(p * 8 + wave) * 64 + lane];
+    const GemmEpilogue &e = a.e;
+    const int nbase = strip * 64 + (wave >> 2) * 32, n = nbase + li;
+    const float bias = e.bias ? e.bias[n] : 0.f, scl = n < e.scale_cols ? e.scale : 1.f;
+    const bool first = nbase < e.n_split;
+    float *dst = first ? (float *)e.dst0 + n : (float *)e.dst1 + (n - e.n_split);
+    const long ld = first ? e.ld0 : e.ld1;
+#pragma unroll
+    for (int v = 0; v < 4; v++) {
+      const int r = m0 + (wave & 3) * 8 + g * 4 + v;
+      if (r < M) dst[(long)r * ld] = (t[v] + bias) * scl;
+    }
+  } else {
+    if (!have) return;
+    half8 hf[2];
+    hf[0] = *(const half8 *)hrow;
+    hf[1] = *(const half8 *)(hrow + DC_TM * LD);
+    for (; strip < sb1; strip += DC_WAVES) {
+      floatx16 acc[2];
+      dc_strip<K>(w, hrow, hf, wb, strip, strip + DC_WAVES < sb1 ? strip + DC_WAVES : strip, acc);
+      dc_store_strip<true>(acc, a.e, strip, m0, M, li, g);
+    }
   }
 }
 
@@ -509,22 +585,20 @@ static hipError_t dc_raise_lds(KernT kern, size_t lds, std::once_flag &once, hip
   return err;
 }
 
-template <int K>
+template <int K, bool SPLIT>
 static hipError_t dq_launch(const DecQkvArgs &a, hipStream_t s) {
-  auto kern = dec_qkv_kernel<K>;
-  const size_t lds = DcShape<K>::plane_bytes;
+  auto kern = dec_qkv_kernel<K, SPLIT>;
+  constexpr size_t planes = DcShape<K>::plane_bytes, red = SPLIT ? (size_t)DC_WAVES * 8 * 64 * 16 : 0;
+  constexpr size_t lds = planes > red ? planes : red;
   static std::once_flag once;
   static hipError_t attr_err = hipSuccess;
   if (dc_raise_lds(kern, lds, once, attr_err) != hipSuccess) return attr_err;
   const int rows = a.sb.rows_prev > a.sb.rows_now ? a.sb.rows_prev : a.sb.rows_now;
   const int row_tiles = (rows + DC_TM - 1) / DC_TM, NS = a.N / 64;
-  int col_groups = 1;
-  // Column groups: as many workgroups share the weight stream of a row tile.  With thousands of rows a strip per wave
-  // (three groups for Q|K|V) is best; up to 512 rows - a handful of row tiles, the launch is the latency of one
-  // workgroup's stream - two strips per workgroup are: +3 to 4 % on a 4,096-token budget (more groups at 1,900 rows:
-  // 21.3 / 25.4 us with four / two busy waves against 20.8).
-  const int busy = rows <= 512 ? 2 : DC_WAVES;
-  for (int cg = NS / busy; cg > 1; cg--)
+  // Column groups: as many workgroups share the weight stream of a row tile.  A strip per wave (three groups for
+  // Q|K|V) with thousands of rows: more groups at 1,900 rows took 21.3 / 25.4 us with four / two busy waves against 20.8.
+  int col_groups = SPLIT ? NS : 1;
+  for (int cg = NS / DC_WAVES; !SPLIT && cg > 1; cg--)
     if (NS % cg == 0 && (long)row_tiles * cg <= 1024) {
       col_groups = cg;
       break;
@@ -537,7 +611,12 @@ hipError_t launch_dec_qkv(const DecQkvArgs &a, hipStream_t s) {
   const int K = a.sb.d;
   if (a.sb.rows_prev <= 0 && a.sb.rows_now <= 0) return hipSuccess;
   if (!dec_fused_supported(K) || a.N % 64 != 0 || a.e.n_split % 32 != 0 || a.sb.rows_now > a.sb.rows_prev) return hipErrorInvalidValue;
-  return K == 512 ? dq_launch<512>(a, s) : dq_launch<256>(a, s);
+  // Up to 512 rows the launch is the latency of one workgroup's chain (token, embedding, LayerNorm, weight stream), so the
+  // stream is cut as short as it gets: one strip per workgroup, an eighth of its k-steps per wave (the sums run in another
+  // order, so the choice goes by shape_rows)
+  const bool split = (a.shape_rows > 0 ? a.shape_rows : a.sb.rows_now) <= 512;
+  if (K == 512) return split ? dq_launch<512, true>(a, s) : dq_launch<512, false>(a, s);
+  return split ? dq_launch<256, true>(a, s) : dq_launch<256, false>(a, s);
 }
 
 template <int K, bool SECOND, bool C2_F32>

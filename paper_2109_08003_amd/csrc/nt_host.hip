@@ -1076,7 +1076,7 @@ int decode_step(nt_model *m, DecodeCursor &cu, hipStream_t s) {
             q.tok_in = m->eos_tok;
           }
           q.sb.gamma = L.ln1.g; q.sb.beta = L.ln1.b; q.sb.eps = lne;
-          q.Wp = L.self.Wqkv_p; q.N = 3 * d; q.e = e;
+          q.Wp = L.self.Wqkv_p; q.N = 3 * d; q.e = e; q.shape_rows = rows_for_choice;
           KT(K_GEMM_DEC_QKV, gemm_bytes(Rd, d, 3 * d, false) + (eos ? 0.0 : rows_prev * (partials_prev * 8.0 + 4)) + Rd * dd * 6,
              6 * Rd * dd * dd, nt::launch_dec_qkv(q, s));
         } else if ((rc = dec_gemm(K_GEMM_DEC_QKV, m->z, d, L.self.Wqkv, L.self.Wqkv_p, 3 * d, &L.ln1, e))) return rc;

@@ -245,6 +245,7 @@ struct DecQkvArgs {
   const _Float16 *Wp;
   int N;
   GemmEpilogue e;
+  int shape_rows;  // row count that selects the kernel form (0: rows_now), as in Dec1Args
 };
 hipError_t launch_dec_qkv(const DecQkvArgs &a, hipStream_t s);
 // One launch for: z' = A * W1^T + b1 + z (A: head/tail planes [M][lda], W1 [K][K] in fragment order; z' is written
@@ -379,7 +380,7 @@ struct Dec1Args {
   float *lo_norm;
 };
 hipError_t launch_dec1(const Dec1Args &a, int d, hipStream_t s);
-constexpr int kDec1FoldRows = 64;
+constexpr int kDec1FoldRows = 256;
 // x [M][2 d] fp32 (key | value of M positions) -> codes [M][2][d] and scales [M][2]; planes (optional): the rounded
 // vectors as head / tail planes [M][d] (tail lo_offset elements after the head) and key_const[m] = scale * (u . key)
 struct KvPlanes {
