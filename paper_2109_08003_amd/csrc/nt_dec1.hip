@@ -1,4 +1,4 @@
-// The attention half of a decoder layer of one-head models of width 256 / 512, in one launch (gfx950).
+// The attention half of a decoder layer in one launch (gfx950): one-head models of width 256 / 512, and eight heads of 64.
 //
 // Between the fused Q | K | V projection and the output layer a decoder row passes through
 //   self-attention -> output projection + residual -> LayerNorm -> query projection -> cross-attention ->
@@ -32,6 +32,12 @@
 //
 // Measured per step of 1,900 / 45 / 1 rows, alone: 92 / 42 / 38 us as four launches, 71 / 30 / 25 us as one.
 //
+// Eight heads of 64 (HEADS): the caches stay fp32 (self) and fp16 (cross); a vector still lies across one wave instruction, a
+// head on eight of its lanes, so that every lane keeps its own head's softmax and a score costs three DPP adds.  Relative keys
+// enter as one number per (head, clipped distance), computed once per row.  Against two attention launches, two chains and a
+// projection per layer: 2,048 sentences through the 30 + 6 layer teacher 139 -> 123 ms, 16,384 through the model with 8 heads
+// and FFN 2,048 119 -> 115 ms.  (Four instead of eight rows per workgroup from 257 rows on: 115.5 and 125 ms.)
+//
 // Caches: row c (a sentence), position p: keys at kv[((c * row_positions + p) * 2) * d], values d elements later; scales
 // at sc[(c * row_positions + p) * 2 + {0: key, 1: value}].  The newest pair arrives as fp32 from the projection, is used
 // at full precision and appended in integer form.
@@ -50,6 +56,7 @@ constexpr int D1_NK = 4;     // keys per block
 constexpr int D1_SL = 4;     // ring of weight fragments: k-steps of 32 in flight per wave
 
 bool attn_i16_supported(int d, int heads, int clip) { return heads == 1 && clip == 0 && (d == 256 || d == 512); }
+bool dec1_heads_supported(int d, int heads) { return d == 512 && heads == 8; }
 
 __device__ __forceinline__ float d1_wave_sum(float v) {
 #pragma unroll
@@ -165,6 +172,15 @@ struct D1Part {
   }
 };
 
+// Relative keys of one row (several heads only): what a key adds to the score of this lane's head, by its distance to the
+// query, clipped; p == nullptr: none.
+constexpr int D1_MAX_CLIP = 16;
+struct D1Rel {
+  const float *p = nullptr;
+  int clip = 0, t = 0;  // the query's position
+  __device__ __forceinline__ float at(int j) const { return p[max(j - t + clip, 0) * 8]; }
+};
+
 // The keys of one block and their fold into a partial softmax; positions past the end repeat the last key and get
 // weight 0.  F32: fp32 keys and values, each key with an additive constant (sc[p]), instead of integers with scales.
 template <int NE, bool F32>
@@ -189,7 +205,7 @@ struct D1Block {
       vs[i] = F32 ? 1.f : sc[p * 2 + 1];
     }
   }
-  __device__ __forceinline__ void fold(const float (&q)[NE], int j0, int n, int lane, D1Part<NE> &a) const {
+  __device__ __forceinline__ void fold(const float (&q)[NE], int j0, int n, int lane, D1Part<NE> &a, const D1Rel &) const {
     float p[D1_NK];
 #pragma unroll
     for (int i = 0; i < D1_NK; i++) {
@@ -248,10 +264,71 @@ struct D1Block {
   }
 };
 
+// The same for heads of eight lanes (64 of 512 columns each): every lane keeps its head's maximum and sum, a score is the sum
+// over eight lanes (three DPP adds), and nothing is uniform over the wave but the positions.
+__device__ __forceinline__ float d1_head_sum(float v) {
+  auto add = [](float x, auto ctrl) {
+    return x + __uint_as_float((unsigned)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(x), decltype(ctrl)::value, 0xf, 0xf, true));
+  };
+  v = add(v, std::integral_constant<int, 0xB1>{});   // quad_perm: lane ^ 1
+  v = add(v, std::integral_constant<int, 0x4E>{});   // quad_perm: lane ^ 2
+  return add(v, std::integral_constant<int, 0x141>{});  // mirrored within eight lanes: the other four
+}
+
+template <int NE, typename Elt>
+struct D1HeadBlock {
+  typedef Elt Vec __attribute__((ext_vector_type(NE)));
+  Vec k[D1_NK], v[D1_NK];
+
+  __device__ __forceinline__ void load(const void *kv, const float *, long pos0, int j0, int n, int lane) {
+    constexpr int D = NE * 64;
+#pragma unroll
+    for (int i = 0; i < D1_NK; i++) {
+      const int j = j0 + i < n ? j0 + i : n - 1;
+      const Elt *kp = (const Elt *)kv + (pos0 + j) * 2 * D + lane * NE;
+      k[i] = *(const Vec *)kp;
+      v[i] = *(const Vec *)(kp + D);
+    }
+  }
+  __device__ __forceinline__ void fold(const float (&q)[NE], int j0, int n, int, D1Part<NE> &a, const D1Rel &rel) const {
+    float s[D1_NK], mn = a.m;
+#pragma unroll
+    for (int i = 0; i < D1_NK; i++) {
+      float p = 0.f;
+#pragma unroll
+      for (int e = 0; e < NE; e++) p += q[e] * (float)k[i][e];
+      s[i] = d1_head_sum(p);
+      if (rel.p) s[i] += rel.at(j0 + i < n ? j0 + i : n - 1);
+      if (j0 + i >= n) s[i] = -INFINITY;
+      mn = fmaxf(mn, s[i]);
+    }
+    const float corr = (a.m == -INFINITY) ? 0.f : __expf(a.m - mn);
+    float w[D1_NK], wsum = 0.f;
+#pragma unroll
+    for (int i = 0; i < D1_NK; i++) {
+      w[i] = __expf(s[i] - mn);
+      wsum += w[i];
+    }
+    a.l = a.l * corr + wsum;
+#pragma unroll
+    for (int e = 0; e < NE; e++) {
+      float t = a.acc[e] * corr;
+#pragma unroll
+      for (int i = 0; i < D1_NK; i++) t += w[i] * (float)v[i][e];
+      a.acc[e] = t;
+    }
+    a.m = mn;
+  }
+};
+template <typename T>
+struct D1Tag {
+  typedef T type;
+};
+
 // D: model width.  RW: rows per workgroup (8 / RW waves each).  PARTS: partial softmaxes per row.  IND: row r uses cache
 // row origin[r] (< 0: no row, zero context).  FFN: the layer's FFN (of width D) is part of the chain.  FOLD: the cross cache
-// holds folded fp32 vectors.
-template <int D, int RW, int NWAVES, int PARTS, bool IND, bool FFN, bool FOLD>
+// holds folded fp32 vectors.  HEADS: eight heads of 64 columns, self cache fp32, cross cache fp16, optional relative keys.
+template <int D, int RW, int NWAVES, int PARTS, bool IND, bool FFN, bool FOLD, bool HEADS>
 __global__ __launch_bounds__(NWAVES * 64) void dec1_kernel(Dec1Args a) {
   constexpr int NE = D / 64, WR = NWAVES / RW, PW = PARTS / WR;  // elements per lane; waves per row; partials per wave
   constexpr int NC = D / NWAVES, NT = NC / 16;                   // output columns of a wave, in tiles of 16
@@ -259,13 +336,17 @@ __global__ __launch_bounds__(NWAVES * 64) void dec1_kernel(Dec1Args a) {
   static_assert(PARTS % WR == 0 && KS % D1_SL == 0, "");
   // whether the next matrix's first fragments are requested before an attention phase: 32 of 128 registers, which a wave
   // with several partial softmaxes does not have
-  constexpr bool EARLY = !(NWAVES == 16 && PW > 1);
+  constexpr bool EARLY = !(NWAVES == 16 && (PW > 1 || HEADS));
+  static_assert(!HEADS || (D == 512 && !FOLD && !FFN), "heads are eight lanes of eight elements");
+  typedef typename std::conditional<HEADS, D1HeadBlock<NE, float>, D1Block<NE, false>>::type SelfBlock;
+  typedef typename std::conditional<HEADS, D1HeadBlock<NE, _Float16>, D1Block<NE, FOLD>>::type CrossBlock;
   typedef D1Part<NE> Part;
   __shared__ __attribute__((aligned(16))) _Float16 sA[2 * RW * LD];               // head rows, then tail rows
   __shared__ __attribute__((aligned(16))) float sZ[RW * ZLD];                     // residual stream
   __shared__ __attribute__((aligned(16))) float sQ[RW * (D + 8)];                 // cross-attention query, later:
   _Float16 *sU = (_Float16 *)sQ;                                                  // FFN hidden state, head rows, then tail rows
   __shared__ float sPart[WR > 1 ? RW * (PARTS - PW) * (NE + 2) * 64 : 1];         // partial softmaxes of the waves pg > 0
+  __shared__ float sRel[HEADS ? RW * (D1_MAX_CLIP + 1) * 8 : 1];                  // per row: [distance][head]
   const int tid = threadIdx.x, lane = tid & 63, h = lane >> 4, c16 = lane & 15;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int rw = wave / WR, pg = wave % WR;
@@ -380,10 +461,10 @@ __global__ __launch_bounds__(NWAVES * 64) void dec1_kernel(Dec1Args a) {
   };
   // attention of this wave's row over n cached keys; the partials may hold the newest key already.  The merged context
   // goes to done(ctx) in the row's first wave
-  auto attend = [&](auto f32_tag, const float (&q)[NE], const void *kv, const float *sc, long pos0, int n, Part (&st)[PW], auto done) {
+  auto attend = [&](auto tag, const float (&q)[NE], const void *kv, const float *sc, long pos0, int n, const D1Rel &rel, Part (&st)[PW], auto done) {
     constexpr int STEP = PARTS * D1_NK;
     // two blocks in flight: the next one of the wave's only partial, or one of each of its two
-    D1Block<NE, decltype(f32_tag)::value> b[2];
+    typename decltype(tag)::type b[2];
     const int j_first = pg * PW * D1_NK;
     if constexpr (NWAVES == 16) {  // 128 registers: one block at a time
       for (int j = j_first; j < n; j += STEP)
@@ -391,23 +472,23 @@ __global__ __launch_bounds__(NWAVES * 64) void dec1_kernel(Dec1Args a) {
         for (int u = 0; u < PW; u++)
           if (j + u * D1_NK < n) {
             b[0].load(kv, sc, pos0, j + u * D1_NK, n, lane);
-            b[0].fold(q, j + u * D1_NK, n, lane, st[u]);
+            b[0].fold(q, j + u * D1_NK, n, lane, st[u], rel);
           }
     } else if constexpr (PW == 1) {
       if (j_first < n) b[0].load(kv, sc, pos0, j_first, n, lane);
       for (int j = j_first; j < n; j += 2 * STEP) {
         if (j + STEP < n) b[1].load(kv, sc, pos0, j + STEP, n, lane);
-        b[0].fold(q, j, n, lane, st[0]);
+        b[0].fold(q, j, n, lane, st[0], rel);
         if (j + 2 * STEP < n) b[0].load(kv, sc, pos0, j + 2 * STEP, n, lane);
-        if (j + STEP < n) b[1].fold(q, j + STEP, n, lane, st[0]);
+        if (j + STEP < n) b[1].fold(q, j + STEP, n, lane, st[0], rel);
       }
     } else {
       static_assert(PW == 2, "one or two partials per wave");
       for (int j = j_first; j < n; j += STEP) {
         b[0].load(kv, sc, pos0, j, n, lane);
         if (j + D1_NK < n) b[1].load(kv, sc, pos0, j + D1_NK, n, lane);
-        b[0].fold(q, j, n, lane, st[0]);
-        if (j + D1_NK < n) b[1].fold(q, j + D1_NK, n, lane, st[1]);
+        b[0].fold(q, j, n, lane, st[0], rel);
+        if (j + D1_NK < n) b[1].fold(q, j + D1_NK, n, lane, st[1], rel);
       }
     }
     if constexpr (WR > 1) {
@@ -460,6 +541,21 @@ __global__ __launch_bounds__(NWAVES * 64) void dec1_kernel(Dec1Args a) {
     for (int e = 0; e < NE; e += 4) *(float4 *)(sZ + rw * ZLD + lane * NE + e) = make_float4(z[e], z[e + 1], z[e + 2], z[e + 3]);
   }
   if (EARLY) preload(a.Wo_self);
+  D1Rel rel;
+  if constexpr (HEADS) {
+    if (a.rk) {  // this row's query against the relative keys it can meet (distances -clip .. 0), shared by the row's waves
+      rel.p = sRel + rw * (D1_MAX_CLIP + 1) * 8 + (lane >> 3), rel.clip = a.clip, rel.t = n_self - 1;
+      for (int o = pg; o <= a.clip; o += WR) {
+        float k[NE], s = 0.f;
+        d1_load<NE>(a.rk + o * 64 + (lane & 7) * 8, k);
+#pragma unroll
+        for (int e = 0; e < NE; e++) s += q[e] * k[e];
+        s = d1_head_sum(s);
+        if ((lane & 7) == 0) sRel[rw * (D1_MAX_CLIP + 1) * 8 + o * 8 + (lane >> 3)] = s;
+      }
+      __syncthreads();
+    }
+  }
   {
     Part st[PW];
 #pragma unroll
@@ -472,15 +568,25 @@ __global__ __launch_bounds__(NWAVES * 64) void dec1_kernel(Dec1Args a) {
       float s = 0.f;
 #pragma unroll
       for (int e = 0; e < NE; e++) s += q[e] * kx[e];
-      st[0].m = d1_wave_sum(s);
+      st[0].m = HEADS ? d1_head_sum(s) + (rel.p ? rel.at(rel.t) : 0.f) : d1_wave_sum(s);
       st[0].l = 1.f;
 #pragma unroll
       for (int e = 0; e < NE; e++) st[0].acc[e] = vx[e];
       const long p = pos0 + (n_self - 1);
-      d1_quantize_store<NE>(kx, a.self_kv + p * 2 * D, a.self_sc + p * 2, lane);
-      d1_quantize_store<NE>(vx, a.self_kv + p * 2 * D + D, a.self_sc + p * 2 + 1, lane);
+      if constexpr (HEADS) {
+        float *dst = (float *)a.self_kv + p * 2 * D + lane * NE;
+#pragma unroll
+        for (int e = 0; e < NE; e += 4) {
+          *(float4 *)(dst + e) = make_float4(kx[e], kx[e + 1], kx[e + 2], kx[e + 3]);
+          *(float4 *)(dst + D + e) = make_float4(vx[e], vx[e + 1], vx[e + 2], vx[e + 3]);
+        }
+      } else {
+        short *dst = (short *)a.self_kv + p * 2 * D;
+        d1_quantize_store<NE>(kx, dst, a.self_sc + p * 2, lane);
+        d1_quantize_store<NE>(vx, dst + D, a.self_sc + p * 2 + 1, lane);
+      }
     }
-    attend(std::false_type{}, q, a.self_kv, a.self_sc, pos0, n_self > 0 ? n_self - 1 : 0, st, store_planes);
+    attend(D1Tag<SelfBlock>{}, q, a.self_kv, a.self_sc, pos0, n_self > 0 ? n_self - 1 : 0, rel, st, store_planes);
   }
   // ---- output projection + residual, LayerNorm, cross-attention query ----
   if (!EARLY) preload(a.Wo_self);
@@ -495,7 +601,7 @@ __global__ __launch_bounds__(NWAVES * 64) void dec1_kernel(Dec1Args a) {
     Part st[PW];
 #pragma unroll
     for (int u = 0; u < PW; u++) st[u].clear();
-    attend(std::true_type{}, q, a.cross_kv, a.cross_sc, (long)rc * a.cross_positions, n_cross, st, [&](const float (&ctx)[NE]) {
+    attend(D1Tag<CrossBlock>{}, q, a.cross_kv, a.cross_sc, (long)rc * a.cross_positions, n_cross, D1Rel{}, st, [&](const float (&ctx)[NE]) {
       float *z = sZ + rw * ZLD + lane * NE;
 #pragma unroll
       for (int e = 0; e < NE; e++) z[e] += ctx[e];
@@ -522,7 +628,7 @@ __global__ __launch_bounds__(NWAVES * 64) void dec1_kernel(Dec1Args a) {
 #pragma unroll
       for (int u = 0; u < PW; u++) st[u].clear();
       d1_load<NE>(sQ + rw * ZLD + lane * NE, q);
-      attend(std::false_type{}, q, a.cross_kv, a.cross_sc, (long)rc * a.cross_positions, n_cross, st, store_planes);
+      attend(D1Tag<CrossBlock>{}, q, a.cross_kv, a.cross_sc, (long)rc * a.cross_positions, n_cross, D1Rel{}, st, store_planes);
     }
     if (!EARLY) preload(a.Wo_cross);
     project(a.Wo_cross, sA);
@@ -578,7 +684,7 @@ __global__ __launch_bounds__(NWAVES * 64) void dec1_kernel(Dec1Args a) {
   }
 }
 
-template <int D, bool FFN>
+template <int D, bool FFN, bool HEADS>
 static hipError_t d1_launch(const Dec1Args &a, hipStream_t s) {
   // Partial softmaxes per row: four below 1,024 rows, one from there on (they differ in the last bit, so the choice
   // goes by shape_rows; the number of rows per workgroup changes no result there).
@@ -592,11 +698,16 @@ static hipError_t d1_launch(const Dec1Args &a, hipStream_t s) {
 #define NT_D1(RW_, NW_, P_, F_)                                                                                          \
   do {                                                                                                                  \
     const dim3 grid((unsigned)((a.rows + RW_ - 1) / RW_));                                                              \
-    if (a.origin) hipLaunchKernelGGL((dec1_kernel<D, RW_, NW_, P_, true, FFN, F_>), grid, dim3(64 * NW_), 0, s, a);     \
-    else hipLaunchKernelGGL((dec1_kernel<D, RW_, NW_, P_, false, FFN, F_>), grid, dim3(64 * NW_), 0, s, a);             \
+    if (a.origin) hipLaunchKernelGGL((dec1_kernel<D, RW_, NW_, P_, true, FFN, F_, HEADS>), grid, dim3(64 * NW_), 0, s, a);     \
+    else hipLaunchKernelGGL((dec1_kernel<D, RW_, NW_, P_, false, FFN, F_, HEADS>), grid, dim3(64 * NW_), 0, s, a);             \
   } while (0)
-  if (a.folded) NT_D1(2, 8, 4, true);
-  else if (!parts) NT_D1(16, 16, 1, false);
+  if constexpr (!HEADS) {
+    if (a.folded) {
+      NT_D1(2, 8, 4, true);
+      return hipGetLastError();
+    }
+  }
+  if (!parts) NT_D1(16, 16, 1, false);
   else if (a.rows <= (a.crowded ? 64 : 512)) NT_D1(2, 8, 4, false);
   else if (a.rows <= 256 || !a.crowded) NT_D1(4, 16, 4, false);
   else NT_D1(8, 16, 4, false);
@@ -607,8 +718,12 @@ static hipError_t d1_launch(const Dec1Args &a, hipStream_t s) {
 hipError_t launch_dec1(const Dec1Args &a, int d, hipStream_t s) {
   if (a.rows <= 0) return hipSuccess;
   const bool ffn = a.W1 != nullptr;
-  if (d == 512) return ffn ? d1_launch<512, true>(a, s) : d1_launch<512, false>(a, s);
-  if (d == 256) return ffn ? d1_launch<256, true>(a, s) : d1_launch<256, false>(a, s);
+  if (a.heads > 1) {
+    if (!dec1_heads_supported(d, a.heads) || ffn || a.folded || a.clip > D1_MAX_CLIP) return hipErrorInvalidValue;
+    return d1_launch<512, false, true>(a, s);
+  }
+  if (d == 512) return ffn ? d1_launch<512, true, false>(a, s) : d1_launch<512, false, false>(a, s);
+  if (d == 256) return ffn ? d1_launch<256, true, false>(a, s) : d1_launch<256, false, false>(a, s);
   return hipErrorInvalidValue;
 }
 

@@ -976,6 +976,9 @@ int decode_step(nt_model *m, DecodeCursor &cu, hipStream_t s) {
     // next projection, output projection + final LayerNorm.
     const bool fused = nt::dec_fused_supported(d) && m->dec[0].self.Wqkv_p != nullptr;
     const bool fused_start = fused && rows_now > 0;
+    // decoder layers whose attention half is one launch (nt_dec1.hip): the integer caches, or eight heads of 64
+    const bool heads_layer = !m->kv_i16 && fused && !kCrossF32 && nt::dec1_heads_supported(d, H);
+    const bool layer1 = m->kv_i16 || heads_layer;
     // the EOS mode keeps the rows still decoding as a dense prefix: origin maps a dense row to its batch row
     int32_t *origin = eos ? m->origin[t & 1] : nullptr;
     if (eos) {
@@ -1066,7 +1069,7 @@ int decode_step(nt_model *m, DecodeCursor &cu, hipStream_t s) {
         e.bias = L.self.bqkv; e.scale = qscale; e.scale_cols = d; e.dst0 = m->q32; e.ld0 = d; e.n_split = d;
         e.dst1 = m->self_kv[l] + (long)t * 2 * d; e.ld1 = self_stride;
         // the EOS mode and the integer caches: the pair goes to kv_new and the attention kernel appends it to the cache
-        if (eos || m->kv_i16) { e.dst1 = m->kv_new; e.ld1 = 2 * d; }
+        if (eos || layer1) { e.dst1 = m->kv_new; e.ld1 = 2 * d; }
         if (fused_start && l == 0) {
           nt::DecQkvArgs q{};
           q.sb = sba;
@@ -1080,14 +1083,14 @@ int decode_step(nt_model *m, DecodeCursor &cu, hipStream_t s) {
           KT(K_GEMM_DEC_QKV, gemm_bytes(Rd, d, 3 * d, false) + (eos ? 0.0 : rows_prev * (partials_prev * 8.0 + 4)) + Rd * dd * 6,
              6 * Rd * dd * dd, nt::launch_dec_qkv(q, s));
         } else if ((rc = dec_gemm(K_GEMM_DEC_QKV, m->z, d, L.self.Wqkv, L.self.Wqkv_p, 3 * d, &L.ln1, e))) return rc;
-        if (m->kv_i16) {
+        if (layer1) {
           // everything between the projection and the output layer in one launch; an FFN as wide as the model is part of it
-          const bool ffn_inside = F == d && L.ffn.W1_p != nullptr && L.ffn.W2_p != nullptr;
+          const bool ffn_inside = m->kv_i16 && F == d && L.ffn.W1_p != nullptr && L.ffn.W2_p != nullptr;
           const bool to_final = last && (F == 0 || ffn_inside) && !c.q8_output;
           nt::Dec1Args at{};
           at.rows = R; at.shape_rows = rows_for_choice; at.crowded = m->crowded; at.origin = origin; at.eps = lne; at.z = m->z; at.write_z = !to_final;
-          at.q = m->q32; at.kv_new = m->kv_new; at.self_kv = (short *)m->self_kv[l]; at.self_sc = m->self_sc[l];
-          at.self_positions = T; at.n_keys = t + 1;
+          at.q = m->q32; at.kv_new = m->kv_new; at.self_kv = m->self_kv[l]; at.self_sc = m->self_sc[l];
+          at.self_positions = T; at.n_keys = t + 1; at.heads = heads_layer ? H : 1; at.rk = L.self.rk; at.clip = c.rpr_clip;
           at.Wo_self = L.self.Wo_p; at.bo_self = L.self.bo; at.Wq = L.cross.Wq_p; at.bq = L.cross.bq; at.Wo_cross = L.cross.Wo_p;
           at.bo_cross = L.cross.bo; at.q_scale = qscale; at.ln2 = nt::GemmLayerNorm{L.ln2.g, L.ln2.b, lne};
           at.folded = m->folded; at.cross_positions = S; at.len = m->len;
@@ -1102,7 +1105,7 @@ int decode_step(nt_model *m, DecodeCursor &cu, hipStream_t s) {
             final_ln_done = true;
           }
           const double ffn_flops = ffn_inside ? 4 * Rd * dd * F : 0.0;
-          KT(K_DEC_ATTN, (Rd * t + cross_keys) * (2 * dd * 2 + 8) + Rd * dd * 28 + 3 * dd * dd * 2,
+          KT(K_DEC_ATTN, (heads_layer ? Rd * t * dd * 8 + cross_keys * dd * 4 : (Rd * t + cross_keys) * (2 * dd * 2 + 8)) + Rd * dd * 28 + 3 * dd * dd * 2,
              (4 * Rd * (t + 1) + 4 * cross_keys + 6 * Rd * dd) * dd + ffn_flops, nt::launch_dec1(at, d, s));
           if (F > 0 && !ffn_inside) {
             const bool u_planes = streams(F, d, L.ffn.W1_p, true) && streams(d, F, L.ffn.W2_p, false);

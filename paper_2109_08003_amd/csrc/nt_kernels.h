@@ -339,12 +339,17 @@ hipError_t launch_attn_decode(const float *q, const void *kv, bool kv_f32, long 
                               float *ctx, hipStream_t s, long ctx_lo_offset = 0, const int32_t *origin = nullptr,
                               const float *kv_new = nullptr);
 
-// ---- attention half of a decoder layer with one head, d = 256 / 512, no relative keys (nt_dec1.hip) -----------------
-// Both caches hold 16-bit integers with one fp32 scale per vector.  Cache row c, position p: key codes at
+// ---- attention half of a decoder layer, d = 256 / 512 (nt_dec1.hip) ---------------------------------------------------
+// Several heads (dec1_heads_supported): fp32 self cache, fp16 cross cache, laid out as for launch_attn_decode; optional
+// relative keys.  One head, no relative keys (attn_i16_supported): both caches hold 16-bit integers with one fp32 scale per vector.  Cache row c, position p: key codes at
 // kv + ((c * positions + p) * 2) * d, value codes d elements later; their scales at sc[(c * positions + p) * 2] and
 // [... + 1] (value = code * scale).
 bool attn_i16_supported(int d, int heads, int clip);
+bool dec1_heads_supported(int d, int heads);
 struct Dec1Args {
+  int heads;             // 0 / 1: one head
+  const float *rk;       // several heads: relative keys [2 clip + 1][64], or nullptr
+  int clip;
   int rows;
   int shape_rows;        // row count that selects the kernel form (0: rows).  The forms differ in the last bit, so a
                          // caller whose row count depends on timing passes one that does not
@@ -355,7 +360,7 @@ struct Dec1Args {
   int write_z;
   // self-attention: scaled query and this step's key | value pair (fp32), appended to the cache at position n_keys - 1
   const float *q, *kv_new;
-  short *self_kv;
+  void *self_kv;
   float *self_sc;
   long self_positions;
   int n_keys;

@@ -870,12 +870,13 @@ def test_c2_full_workload_sampled_against_oracle(nt, oracle):
 
 
 # ------------------------------------------------------------------------------ row-count edges of the decoder kernels
-@pytest.mark.parametrize("d,ffn,eos", [(512, 0, False), (512, 512, False), (256, 0, False), (256, 256, True)])
-def test_one_head_decoder_at_row_count_edges(nt, oracle, torch_cuda, d, ffn, eos):
-    """A one-head decoder layer at the row counts where its kernels change form or leave a workgroup partly filled:
+@pytest.mark.parametrize("d,ffn,eos,heads,clip", [(512, 0, False, 1, 0), (512, 512, False, 1, 0), (256, 0, False, 1, 0), (256, 256, True, 1, 0),
+                                                  (512, 0, False, 8, 0), (512, 512, False, 8, 3), (512, 0, True, 8, 16)])
+def test_decoder_layer_at_row_count_edges(nt, oracle, torch_cuda, d, ffn, eos, heads, clip):
+    """A decoder layer at the row counts where its kernels change form or leave a workgroup partly filled:
     every sentence of a small-vocabulary model against the oracle."""
     torch = torch_cuda
-    cfg = nt_synth.model_config("C1", d_model=d, vocab=300, n_enc=1, max_len=64, dec_d_ffn=ffn or -1)
+    cfg = nt_synth.model_config("C1", d_model=d, vocab=300, n_enc=1, max_len=64, dec_d_ffn=ffn or -1, n_heads=heads, rpr_clip=clip)
     blob = nt_synth.make_weights(cfg, seed=5, random_affine=True, eos_gain=2.0 if eos else None)
     gm, om = nt.Model(cfg, blob, max_batch_tokens=16384, pipeline_lanes=1), oracle.Model(cfg, blob)
     rng = np.random.default_rng(d + ffn)
