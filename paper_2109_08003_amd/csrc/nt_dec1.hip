@@ -23,12 +23,16 @@
 // times the matrix time.)  The weight fragments of the next projection are requested before the attention or LayerNorm
 // phase that precedes it.
 //
-// Folded cross cache (batches of up to kDec1FoldRows rows).  q . k = (W y + b) . k = y . (W^T k) + b . k, and
-// Wo (sum p v) + bo = sum p (Wo v + bo): with the keys and values of a sentence multiplied by the two matrices once, when
-// the batch is encoded, a step needs neither projection - 8 of the 20 us at one row.  The products are formed from the
-// rounded (integer) vectors, so nothing is rounded that was not before, and kept in fp32: twice the bytes, which is why
-// larger batches, whose time is those bytes, do without (a 4,096-token budget, batches of 36 to 341 rows: 29.0 ms folded up to
-// 64 rows, 27.6 up to 256 or 512; 320 long sentences: 24.2 ms without, 25.4 with).
+// Folded attention (one-layer decoders, batches of up to kDec1FoldRows rows).  q . k = (W y + b) . k = y . (W^T k) + b . k,
+// and Wo (sum p v) + bo = sum p (Wo v + bo).  With the cross keys and values of a sentence multiplied by the two matrices once,
+// when the batch is encoded, and the self values projected by the product of value and output matrix (formed at load, kept as
+// head + tail), a step's attention half has no projection left.  The cross products are formed from the rounded (integer)
+// vectors, so nothing is rounded that was not before, and kept in fp32: twice the bytes, which is why larger batches, whose
+// time is those bytes, do without (a 4,096-token budget, batches of 36 to 341 rows: 29.0 ms folded up to 64 rows, 27.6 up to
+// 256 or 512; 320 long sentences: 24.2 ms without, 25.4 with).  What is left is latency: a row per workgroup of four waves, the
+// first cross keys requested before the self-attention.  One row 20.6 us without folding, 12.8 with the cross cache folded,
+// 45 rows 26 and 17.8; with the self values too, one sentence 1119 -> 1012 us, 45 sentences 3742 -> 3207 us, 8 sentences of
+// the 256-wide model 1253 -> 1175 us, a 4,096-token budget 28.0 -> 27.5 ms.
 //
 // Measured per step of 1,900 / 45 / 1 rows, alone: 92 / 42 / 38 us as four launches, 71 / 30 / 25 us as one.
 //
@@ -320,11 +324,6 @@ struct D1HeadBlock {
     a.m = mn;
   }
 };
-template <typename T>
-struct D1Tag {
-  typedef T type;
-};
-
 // D: model width.  RW: rows per workgroup (8 / RW waves each).  PARTS: partial softmaxes per row.  IND: row r uses cache
 // row origin[r] (< 0: no row, zero context).  FFN: the layer's FFN (of width D) is part of the chain.  FOLD: the cross cache
 // holds folded fp32 vectors.  HEADS: eight heads of 64 columns, self cache fp32, cross cache fp16, optional relative keys.
@@ -461,11 +460,15 @@ __global__ __launch_bounds__(NWAVES * 64) void dec1_kernel(Dec1Args a) {
   };
   // attention of this wave's row over n cached keys; the partials may hold the newest key already.  The merged context
   // goes to done(ctx) in the row's first wave
-  auto attend = [&](auto tag, const float (&q)[NE], const void *kv, const float *sc, long pos0, int n, const D1Rel &rel, Part (&st)[PW], auto done) {
-    constexpr int STEP = PARTS * D1_NK;
-    // two blocks in flight: the next one of the wave's only partial, or one of each of its two
-    typename decltype(tag)::type b[2];
-    const int j_first = pg * PW * D1_NK;
+  // Two blocks in flight: the next one of the wave's only partial, or one of each of its two.  b holds a single partial's
+  // first two blocks already if PRELOADED (see first_blocks)
+  constexpr int STEP = PARTS * D1_NK;
+  const int j_first = pg * PW * D1_NK;
+  auto first_blocks = [&](auto (&b)[2], const void *kv, const float *sc, long pos0, int n) {
+    if (j_first < n) b[0].load(kv, sc, pos0, j_first, n, lane);
+    if (j_first + STEP < n) b[1].load(kv, sc, pos0, j_first + STEP, n, lane);
+  };
+  auto attend = [&](auto (&b)[2], auto preloaded, const float (&q)[NE], const void *kv, const float *sc, long pos0, int n, const D1Rel &rel, Part (&st)[PW], auto done) {
     if constexpr (NWAVES == 16) {  // 128 registers: one block at a time
       for (int j = j_first; j < n; j += STEP)
 #pragma unroll
@@ -475,12 +478,12 @@ __global__ __launch_bounds__(NWAVES * 64) void dec1_kernel(Dec1Args a) {
             b[0].fold(q, j + u * D1_NK, n, lane, st[u], rel);
           }
     } else if constexpr (PW == 1) {
-      if (j_first < n) b[0].load(kv, sc, pos0, j_first, n, lane);
+      if (!decltype(preloaded)::value) first_blocks(b, kv, sc, pos0, n);
       for (int j = j_first; j < n; j += 2 * STEP) {
-        if (j + STEP < n) b[1].load(kv, sc, pos0, j + STEP, n, lane);
         b[0].fold(q, j, n, lane, st[0], rel);
         if (j + 2 * STEP < n) b[0].load(kv, sc, pos0, j + 2 * STEP, n, lane);
         if (j + STEP < n) b[1].fold(q, j + STEP, n, lane, st[0], rel);
+        if (j + 3 * STEP < n) b[1].load(kv, sc, pos0, j + 3 * STEP, n, lane);
       }
     } else {
       static_assert(PW == 2, "one or two partials per wave");
@@ -540,7 +543,16 @@ __global__ __launch_bounds__(NWAVES * 64) void dec1_kernel(Dec1Args a) {
 #pragma unroll
     for (int e = 0; e < NE; e += 4) *(float4 *)(sZ + rw * ZLD + lane * NE + e) = make_float4(z[e], z[e + 1], z[e + 2], z[e + 3]);
   }
-  if (EARLY) preload(a.Wo_self);
+  if (EARLY && !FOLD) preload(a.Wo_self);
+  SelfBlock sb[2];
+  CrossBlock cb[2];
+  const long cross0 = (long)rc * a.cross_positions;
+  if constexpr (FOLD) first_blocks(cb, a.cross_kv, a.cross_sc, cross0, n_cross);  // they depend on nothing computed here
+  auto add_context = [&](const float (&ctx)[NE]) {
+    float *z = sZ + rw * ZLD + lane * NE;
+#pragma unroll
+    for (int e = 0; e < NE; e++) z[e] += ctx[e];
+  };
   D1Rel rel;
   if constexpr (HEADS) {
     if (a.rk) {  // this row's query against the relative keys it can meet (distances -clip .. 0), shared by the row's waves
@@ -586,14 +598,17 @@ __global__ __launch_bounds__(NWAVES * 64) void dec1_kernel(Dec1Args a) {
         d1_quantize_store<NE>(vx, dst + D, a.self_sc + p * 2 + 1, lane);
       }
     }
-    attend(D1Tag<SelfBlock>{}, q, a.self_kv, a.self_sc, pos0, n_self > 0 ? n_self - 1 : 0, rel, st, store_planes);
+    if constexpr (FOLD) attend(sb, std::false_type{}, q, a.self_kv, a.self_sc, pos0, n_self > 0 ? n_self - 1 : 0, rel, st, add_context);
+    else attend(sb, std::false_type{}, q, a.self_kv, a.self_sc, pos0, n_self > 0 ? n_self - 1 : 0, rel, st, store_planes);
   }
   // ---- output projection + residual, LayerNorm, cross-attention query ----
-  if (!EARLY) preload(a.Wo_self);
-  project(a.Wo_self, sA);
-  if (!FOLD) preload(a.Wq);
-  add_residual(a.bo_self);
-  __syncthreads();
+  if constexpr (!FOLD) {
+    if (!EARLY) preload(a.Wo_self);
+    project(a.Wo_self, sA);
+    preload(a.Wq);
+    add_residual(a.bo_self);
+    __syncthreads();
+  }
   if constexpr (FOLD) {
     // ---- cross-attention over the folded cache: the normalised row is the query, the context adds to the residual ----
     normalise(a.ln2.gamma, a.ln2.beta, q);
@@ -601,11 +616,7 @@ __global__ __launch_bounds__(NWAVES * 64) void dec1_kernel(Dec1Args a) {
     Part st[PW];
 #pragma unroll
     for (int u = 0; u < PW; u++) st[u].clear();
-    attend(D1Tag<CrossBlock>{}, q, a.cross_kv, a.cross_sc, (long)rc * a.cross_positions, n_cross, D1Rel{}, st, [&](const float (&ctx)[NE]) {
-      float *z = sZ + rw * ZLD + lane * NE;
-#pragma unroll
-      for (int e = 0; e < NE; e++) z[e] += ctx[e];
-    });
+    attend(cb, std::true_type{}, q, a.cross_kv, a.cross_sc, cross0, n_cross, D1Rel{}, st, add_context);
   } else {
     {
       float y[NE];
@@ -628,7 +639,7 @@ __global__ __launch_bounds__(NWAVES * 64) void dec1_kernel(Dec1Args a) {
 #pragma unroll
       for (int u = 0; u < PW; u++) st[u].clear();
       d1_load<NE>(sQ + rw * ZLD + lane * NE, q);
-      attend(D1Tag<CrossBlock>{}, q, a.cross_kv, a.cross_sc, (long)rc * a.cross_positions, n_cross, D1Rel{}, st, store_planes);
+      attend(cb, std::false_type{}, q, a.cross_kv, a.cross_sc, cross0, n_cross, D1Rel{}, st, store_planes);
     }
     if (!EARLY) preload(a.Wo_cross);
     project(a.Wo_cross, sA);
@@ -703,7 +714,8 @@ static hipError_t d1_launch(const Dec1Args &a, hipStream_t s) {
   } while (0)
   if constexpr (!HEADS) {
     if (a.folded) {
-      NT_D1(2, 8, 4, true);
+      if constexpr (FFN) NT_D1(2, 8, 4, true);
+      else NT_D1(1, 4, 4, true);
       return hipGetLastError();
     }
   }

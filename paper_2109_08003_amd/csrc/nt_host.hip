@@ -127,6 +127,9 @@ struct Attn {
   const _Float16 *Wo = nullptr;    // [d][d]
   // the same matrices in MFMA fragment order (streaming GEMM), nullptr where the shape is not supported
   const _Float16 *Wqkv_p = nullptr, *Wq_p = nullptr, *Wkv_p = nullptr, *Wo_p = nullptr;
+  const _Float16 *Wvo_p = nullptr;      // head | tail of 1 / vo_inv * Wv Wo (folded self values)
+  const float *bvo = nullptr;           // bv Wo + bo
+  float vo_inv = 1.f;
   const _Float16 *Wq_back_p = nullptr;  // Wq the other way round (its product with a key): folded cross caches
   const float *bqkv = nullptr, *bq = nullptr, *bkv = nullptr, *bo = nullptr;
   const float *rk = nullptr;       // [2c+1][dh]
@@ -216,8 +219,8 @@ struct nt_model {
   // bit 1: attention context -> output projection, bit 2: final LayerNorm -> cross K|V, bit 3: the FFN's first matrix;
   // with bit 0 clear, bits 4 / 5 / 6: the q / k / v columns of Q|K|V alone; bit 7: q and k stored as plain fp16)
   unsigned enc_tails = kEncTailsAll;
-  // Small batches additionally keep the cross cache multiplied by the query and output matrices, in fp32 (nt_dec1.hip):
-  // per decoder layer [fold_positions, 2d] and one constant per key; folded says whether the encoded batch has it
+  // One-layer decoders: small batches additionally keep the cross cache multiplied by the query and output matrices, in fp32,
+  // and their self values are computed with the output matrix already in them (nt_dec1.hip): per decoder layer [fold_positions, 2d] and one constant per key; folded says whether the encoded batch has it
   std::vector<float *> cross_fold, fold_const;
   int64_t fold_positions = 0;
   bool folded = false;
@@ -378,7 +381,7 @@ int alloc_lane_state(nt_model *m, hipStream_t s) {
   const size_t o_x = cv.take((size_t)Mt * d * 4), o_a16 = cv.take((size_t)Mt * d * kEncElt),
                o_qkv = cv.take((size_t)Mt * 3 * d * kEncElt), o_ctx16 = cv.take((size_t)Mt * d * kEncElt),
                o_u16 = cv.take((size_t)Mt * std::max(F, 1) * kEncElt), o_enc = cv.take((size_t)Mt * d * kEncElt);
-  m->fold_positions = m->kv_i16 ? std::min<int64_t>(Mt, (int64_t)nt::kDec1FoldRows * cfg->max_len) : 0;
+  m->fold_positions = m->kv_i16 && cfg->n_dec == 1 ? std::min<int64_t>(Mt, (int64_t)nt::kDec1FoldRows * cfg->max_len) : 0;
   std::vector<size_t> o_fold(cfg->n_dec), o_fconst(cfg->n_dec);
   for (int l = 0; l < cfg->n_dec; l++) {
     o_fold[l] = cv.take((size_t)m->fold_positions * 2 * d * 4 + 16);
@@ -624,7 +627,7 @@ int nt_load_weights(const nt_config *cfg, const void *h_blob_fp16, size_t blob_b
     put_f32(br.take(d), d, (const void **)&ln.b);
   };
   // self-attention: Wq|Wk|Wv fused into one [3d][d] matrix; cross-attention: Wq and Wk|Wv
-  auto put_attn = [&](Attn &a, bool cross, bool rpr, int dh) {
+  auto put_attn = [&](Attn &a, bool cross, bool rpr, int dh, bool fold_values = false) {
     const _Float16 *W[4], *b[4];
     for (int i = 0; i < 4; i++) { W[i] = br.take((int64_t)d * d); b[i] = br.take(d); }
     auto fused = [&](int first, int count, const void **wslot, const void **bslot, const void **pslot) {
@@ -641,6 +644,39 @@ int nt_load_weights(const nt_config *cfg, const void *h_blob_fp16, size_t blob_b
       fixes.push_back({ob, bslot});
     };
     if (!cross) fused(0, 3, (const void **)&a.Wqkv, (const void **)&a.bqkv, (const void **)&a.Wqkv_p);
+    if (fold_values) {  // value matrix times output matrix, in double; scaled by a power of two so that the tail keeps its bits
+      std::vector<double> prod((size_t)d * d, 0.0), wo((size_t)d * d), bias((size_t)d);
+      for (int64_t i = 0; i < (int64_t)d * d; i++) wo[(size_t)i] = (double)(float)W[3][i];
+      for (int j = 0; j < d; j++) bias[(size_t)j] = (double)(float)b[3][j];
+      double largest = 0.0;
+      for (int i = 0; i <= d; i++) {  // row d: the bias
+        double *row = i < d ? &prod[(size_t)i * d] : bias.data();
+        for (int k = 0; k < d; k++) {
+          const double x = (double)(float)(i < d ? W[2][(int64_t)i * d + k] : b[2][k]);
+          const double *o = &wo[(size_t)k * d];
+          for (int j = 0; j < d; j++) row[j] += x * o[j];
+        }
+        for (int j = 0; i < d && j < d; j++) largest = std::max(largest, std::fabs(row[j]));
+      }
+      int exp2 = 0;
+      if (largest > 0.0) (void)std::frexp(largest, &exp2);
+      const double scale = std::ldexp(1.0, 14 - exp2);  // the largest entry between 2^13 and 2^14
+      a.vo_inv = (float)(1.0 / scale);
+      std::vector<_Float16> rows((size_t)2 * d * d);  // [out][in], head then tail
+      for (int i = 0; i < d; i++)
+        for (int j = 0; j < d; j++) {
+          const double x = prod[(size_t)i * d + j] * scale;
+          const _Float16 hi = (_Float16)x;
+          rows[(size_t)j * d + i] = hi;
+          rows[(size_t)(d + j) * d + i] = (_Float16)(x - (double)(float)hi);
+        }
+      const size_t ov = pk.reserve(nt::vocab_pack_bytes(2 * d, d));
+      nt::vocab_pack(rows.data(), 2 * d, d, (_Float16 *)(pk.img.data() + ov));
+      fixes.push_back({ov, (const void **)&a.Wvo_p});
+      const size_t ob = pk.reserve((size_t)d * 4);
+      for (int j = 0; j < d; j++) ((float *)(pk.img.data() + ob))[j] = (float)bias[(size_t)j];
+      fixes.push_back({ob, (const void **)&a.bvo});
+    }
     else {
       fused(0, 1, (const void **)&a.Wq, (const void **)&a.bq, (const void **)&a.Wq_p);
       if (m->kv_i16) {
@@ -687,7 +723,7 @@ int nt_load_weights(const nt_config *cfg, const void *h_blob_fp16, size_t blob_b
   put_ln(m->enc_final);
   for (auto &L : m->dec) {
     put_ln(L.ln1);
-    put_attn(L.self, false, true, dhd);
+    put_attn(L.self, false, true, dhd, m->kv_i16 && cfg->n_dec == 1);
     put_ln(L.ln2);
     put_attn(L.cross, true, false, dhd);
     if (Fd > 0) { put_ln(L.ln3); put_ffn(L.ffn, Fd); }
@@ -865,7 +901,7 @@ int nt_encode(nt_model *m, const int32_t *d_src, const int32_t *d_len, int32_t B
   if (!all_fused)
     KT(K_LN_ENC, Md * dd * (4 + ea), 8 * Md * dd,
        nt::launch_layer_norm(m->x, M, d, m->enc_final.g, m->enc_final.b, lne, m->enc_out, ln_mode, lo_d, s));
-  m->folded = m->kv_i16 && B <= nt::kDec1FoldRows && M <= m->fold_positions;
+  m->folded = m->kv_i16 && c.n_dec == 1 && B <= nt::kDec1FoldRows && M <= m->fold_positions;
   const float dec_qscale = 1.0f / std::sqrt((float)(d / dec_heads(&c)));
   for (int l = 0; l < c.n_dec; l++) {
     nt::GemmEpilogue e;
@@ -1080,6 +1116,7 @@ int decode_step(nt_model *m, DecodeCursor &cu, hipStream_t s) {
           }
           q.sb.gamma = L.ln1.g; q.sb.beta = L.ln1.b; q.sb.eps = lne;
           q.Wp = L.self.Wqkv_p; q.N = 3 * d; q.e = e; q.shape_rows = rows_for_choice;
+          if (m->folded) { q.Wvo_p = L.self.Wvo_p; q.vo_inv = L.self.vo_inv; q.b_vo = L.self.bvo; }
           KT(K_GEMM_DEC_QKV, gemm_bytes(Rd, d, 3 * d, false) + (eos ? 0.0 : rows_prev * (partials_prev * 8.0 + 4)) + Rd * dd * 6,
              6 * Rd * dd * dd, nt::launch_dec_qkv(q, s));
         } else if ((rc = dec_gemm(K_GEMM_DEC_QKV, m->z, d, L.self.Wqkv, L.self.Wqkv_p, 3 * d, &L.ln1, e))) return rc;

@@ -245,6 +245,11 @@ struct DecQkvArgs {
   const _Float16 *Wp;
   int N;
   GemmEpilogue e;
+  // optional, up to 512 rows: the value columns (2 d .. 3 d - 1) come from this matrix instead, head and tail (fragment order,
+  // d rows each) of scale * W_v W_o, and leave as product * vo_inv + b_vo (folded self values, see Dec1Args)
+  const _Float16 *Wvo_p;
+  float vo_inv;
+  const float *b_vo;
   int shape_rows;  // row count that selects the kernel form (0: rows_now), as in Dec1Args
 };
 hipError_t launch_dec_qkv(const DecQkvArgs &a, hipStream_t s);
@@ -371,7 +376,7 @@ struct Dec1Args {
   GemmLayerNorm ln2;
   const void *cross_kv;  // integers with scales in cross_sc, or (folded) fp32 [position][2 d] with one constant per key in
   const float *cross_sc; // cross_sc: keys multiplied by the query matrix and scale, values by the output matrix (+ bias)
-  int folded;
+  int folded;            // the self values (kv_new, self cache) then are already multiplied by the output matrix (+ bias), too
   long cross_positions;
   const int32_t *len;    // keys of each cache row
   // FFN of width d (W1 == nullptr: none, or not part of this launch)
