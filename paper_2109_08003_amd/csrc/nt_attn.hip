@@ -286,10 +286,10 @@ static hipError_t enc_attention_launch(const void *qkv, const int32_t *len, void
 }
 
 // ---------------------------------------------------------------------------------------
-// Wave-per-tile variant for sentences of up to 32*NKB tokens (fp32 inputs, no relative keys).
+// Wave-per-tile variant for sentences of up to 32*NKB tokens (fp32 inputs).
 //
 // One wave owns 32 queries of one (sentence, head) and runs the whole attention in registers:
-// no LDS, no workgroup barrier, four independent waves per workgroup.  The score blocks are
+// no LDS (but for relative keys), no workgroup barrier, four independent waves per workgroup.  The score blocks are
 // computed transposed (A operand = key rows, B operand = query rows), so a lane owns one query
 // and its accumulator registers run over the keys: the softmax reduction stays inside the lane
 // plus one exchange between the two lane groups, and the probabilities are already laid out as
@@ -311,10 +311,13 @@ __device__ __forceinline__ void split8u(const float *f, half8 &hi, half8 &lo) {
 // WPU = 4: the four waves of a workgroup share a unit, for batches with fewer units than the chip has SIMDs: each computes
 // the scores (the same MFMAs in the same order, with more of their operands in flight) and takes a quarter of the value
 // columns, whose 16 blocks in turn are most of a lone wave's time (one sentence of 22 tokens: 23 us with one wave).
-template <int DH, int NKB, bool QK16, int WPU>
+// REL: relative keys of clip distance <= 15, taken as one more block of keys: rk . q for the 2 clip + 1 offsets comes out of the
+// MFMAs with a query per lane, goes through the LDS and is added to the scores by clipped distance.
+template <int DH, int NKB, bool QK16, int WPU, bool REL>
 __global__ __launch_bounds__(256, WPU == 4 ? 1 : NKB == 1 ? 3 : NKB == 2 ? 2 : 1) void enc_attention_wave_kernel(const float *qkv, const _Float16 *qk16, const int32_t *len, _Float16 *ctx,
                                                                  long ctx_lo_offset, int B, int S, int d, int heads,
-                                                                 int q_tiles) {
+                                                                 int q_tiles, const float *rk, int clip) {
+  __shared__ float sRel[REL ? 4 : 1][REL ? 32 * 32 : 1];  // per wave [offset][query]
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, li = lane & 31, g = lane >> 5;
   const long unit = WPU == 4 ? (long)blockIdx.x : (long)blockIdx.x * 4 + wave;  // uniform over the wave, and known to be: addresses below are a
                                                    // uniform 64-bit base plus a 32-bit lane offset
@@ -382,30 +385,75 @@ __global__ __launch_bounds__(256, WPU == 4 ? 1 : NKB == 1 ? 3 : NKB == 2 ? 2 : 1
   // A lane takes its 32 consecutive values of a 64-wide slice (one whole 128-byte line) in one go: taking them in
   // two halves, the second half a loop iteration later, was measured to fetch 17 % more from HBM (the line is
   // evicted in between) for no gain in time.
+  // The key slices of up to AHEAD blocks are in flight: with more than four blocks a SIMD holds one wave, and nothing else
+  // covers their latency.
+  constexpr int AHEAD = NKB > 4 ? 4 : 1;
+  floatx16 ar;  // REL: rk_o . q, offsets o as the keys of a block
+  if constexpr (REL) {
+#pragma unroll
+    for (int v = 0; v < 16; v++) ar[v] = 0.f;
+  }
 #pragma nounroll
   for (int c = 0; c < (QK16 ? 0 : DH / 64); c++) {
-    float f[32];
+    float fq[32], f[AHEAD][32];
 #pragma unroll
-    for (int u = 0; u < 8; u++) *(float4 *)(f + 4 * u) = *(const float4 *)(qp + c * 64 + u * 4);
+    for (int u = 0; u < 8; u++) *(float4 *)(fq + 4 * u) = *(const float4 *)(qp + c * 64 + u * 4);
+    auto key_slice = [&](int kb) {
+      const float *kp = qkv + (row0 + min(kb * 32 + li, L - 1)) * ld + d + hoff + g * 32 + c * 64;
+#pragma unroll
+      for (int u = 0; u < 8; u++) *(float4 *)(f[kb % AHEAD] + 4 * u) = *(const float4 *)(kp + u * 4);
+    };
+    if constexpr (AHEAD > 1) {
+#pragma unroll
+      for (int kb = 0; kb < AHEAD - 1; kb++)
+        if (kb < nkb) key_slice(kb);
+    }
     half8 qh[4], ql[4];
 #pragma unroll
-    for (int u = 0; u < 4; u++) split8u(f + 8 * u, qh[u], ql[u]);
+    for (int u = 0; u < 4; u++) split8u(fq + 8 * u, qh[u], ql[u]);
+    if constexpr (REL) {
+      const float *rp = rk + min(li, 2 * clip) * DH + g * 32 + c * 64;
+#pragma unroll
+      for (int u = 0; u < 4; u++) {
+        half8 rh;  // the tables are fp16 in the model: exact
+#pragma unroll
+        for (int e = 0; e < 8; e++) rh[e] = (_Float16)rp[u * 8 + e];
+        ar = __builtin_amdgcn_mfma_f32_32x32x16_f16(rh, qh[u], ar, 0, 0, 0);
+        ar = __builtin_amdgcn_mfma_f32_32x32x16_f16(rh, ql[u], ar, 0, 0, 0);
+      }
+    }
 #pragma unroll
     for (int kb = 0; kb < NKB; kb++) {
       if (kb < nkb) {
-        const float *kp = qkv + (row0 + min(kb * 32 + li, L - 1)) * ld + d + hoff + g * 32 + c * 64;
-#pragma unroll
-        for (int u = 0; u < 8; u++) *(float4 *)(f + 4 * u) = *(const float4 *)(kp + u * 4);
+        if (kb + AHEAD - 1 < nkb) key_slice(kb + AHEAD - 1);
 #pragma unroll
         for (int u = 0; u < 4; u++) {
           half8 kh, kl;
-          split8u(f + 8 * u, kh, kl);
+          split8u(f[kb % AHEAD] + 8 * u, kh, kl);
           sc[kb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(kh, qh[u], sc[kb], 0, 0, 0);
           sc[kb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(kl, qh[u], sc[kb], 0, 0, 0);
           sc[kb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(kh, ql[u], sc[kb], 0, 0, 0);
         }
+        if (AHEAD > 1) __builtin_amdgcn_sched_barrier(0);  // keeps the requests ahead
       }
     }
+  }
+  if constexpr (REL) {
+    float *tab = sRel[wave];
+#pragma unroll
+    for (int v = 0; v < 16; v++) tab[((v >> 2) * 8 + g * 4 + (v & 3)) * 32 + li] = ar[v];
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+#pragma unroll
+    for (int kb = 0; kb < NKB; kb++)
+      if (kb < nkb) {
+#pragma unroll
+        for (int v = 0; v < 16; v++) {
+          const int j = kb * 32 + (v >> 2) * 8 + g * 4 + (v & 3), rel = max(-clip, min(clip, j - (q0 + li)));
+          sc[kb][v] += tab[(rel + clip) * 32 + li];
+        }
+      }
   }
 
   // ---- fp32 softmax over the keys: in-lane, then one exchange between the lane groups ----
@@ -518,9 +566,10 @@ __global__ __launch_bounds__(256, WPU == 4 ? 1 : NKB == 1 ? 3 : NKB == 2 ? 2 : 1
   }
 }
 
-template <int DH, bool QK16 = false>
+template <int DH, bool QK16 = false, bool REL = false>
 static hipError_t enc_attention_wave_launch(const float *qkv, const int32_t *len, _Float16 *ctx, long ctx_lo_offset,
-                                            int B, int S, int d, int heads, hipStream_t s, const _Float16 *qk16 = nullptr) {
+                                            int B, int S, int d, int heads, hipStream_t s, const _Float16 *qk16 = nullptr,
+                                            const float *rk = nullptr, int clip = 0) {
   const int q_tiles = (S + 31) / 32;
   const long units = (long)B * heads * q_tiles;
   const dim3 block(256);
@@ -529,18 +578,29 @@ static hipError_t enc_attention_wave_launch(const float *qkv, const int32_t *len
 #define NT_WAVE_CASE(NKB)                                                                                                  \
   case NKB:                                                                                                                \
     if (share)                                                                                                             \
-      hipLaunchKernelGGL((enc_attention_wave_kernel<DH, NKB, QK16, DH >= 256 ? 4 : 1>), dim3((unsigned)units), block, 0, s, \
-                         qkv, qk16, len, ctx, ctx_lo_offset, B, S, d, heads, q_tiles);                                     \
+      hipLaunchKernelGGL((enc_attention_wave_kernel<DH, NKB, QK16, DH >= 256 ? 4 : 1, REL>), dim3((unsigned)units), block, 0, s, \
+                         qkv, qk16, len, ctx, ctx_lo_offset, B, S, d, heads, q_tiles, rk, clip);                           \
     else                                                                                                                   \
-      hipLaunchKernelGGL((enc_attention_wave_kernel<DH, NKB, QK16, 1>), dim3((unsigned)((units + 3) / 4)), block, 0, s, qkv, \
-                         qk16, len, ctx, ctx_lo_offset, B, S, d, heads, q_tiles);                                          \
+      hipLaunchKernelGGL((enc_attention_wave_kernel<DH, NKB, QK16, 1, REL>), dim3((unsigned)((units + 3) / 4)), block, 0, s, qkv, \
+                         qk16, len, ctx, ctx_lo_offset, B, S, d, heads, q_tiles, rk, clip);                                \
     break;
   switch (q_tiles) {
     NT_WAVE_CASE(1)
     NT_WAVE_CASE(2)
     NT_WAVE_CASE(3)
     NT_WAVE_CASE(4)
-    default: return hipErrorInvalidValue;
+    default: break;
+  }
+  if constexpr (!QK16 && (DH == 64 || DH == 512)) {
+    switch (q_tiles) {
+      case 1: case 2: case 3: case 4: return hipGetLastError();
+      NT_WAVE_CASE(5)
+      NT_WAVE_CASE(6)
+      NT_WAVE_CASE(7)
+      default: return hipErrorInvalidValue;
+    }
+  } else if (q_tiles > 4) {
+    return hipErrorInvalidValue;
   }
 #undef NT_WAVE_CASE
   return hipGetLastError();
@@ -561,6 +621,19 @@ hipError_t launch_enc_attention(const void *qkv, bool f32, const int32_t *len, v
                                 int S, int d, int heads, const float *rk, int clip, hipStream_t s) {
   if (B <= 0 || S <= 0) return hipSuccess;
   if (clip > MAX_CLIP) return hipErrorInvalidValue;
+  // The wave-per-tile kernel where its registers reach (seven key blocks; eight spill), for the two head widths in use.  Against
+  // the tiled kernel, whose LDS leaves one workgroup per CU: 320 sentences of 100 to 200 tokens, one head 476 -> 291 us a
+  // layer; eight heads with relative keys, 8,192 tokens in short sentences, 100 -> 44 us.  With fewer than 256 units (a lone
+  // long sentence) the tiled kernel's four waves share the keys of a unit and it stays.
+  const long units = (long)B * heads * ((S + 31) / 32);
+  if (f32 && rk && d / heads == 64 && clip <= 15 && S <= 224)
+    return enc_attention_wave_launch<64, false, true>((const float *)qkv, len, (_Float16 *)ctx, ctx_lo_offset, B, S, d, heads, s, nullptr, rk, clip);
+  if (f32 && !rk && S > 128 && S <= 224 && units >= 256) {
+    if (d / heads == 64)
+      return enc_attention_wave_launch<64>((const float *)qkv, len, (_Float16 *)ctx, ctx_lo_offset, B, S, d, heads, s);
+    if (d / heads == 512)
+      return enc_attention_wave_launch<512>((const float *)qkv, len, (_Float16 *)ctx, ctx_lo_offset, B, S, d, heads, s);
+  }
   if (f32 && !rk && S <= 128) {  // register-resident wave-per-tile kernel
     switch (d / heads) {
       case 64: return enc_attention_wave_launch<64>((const float *)qkv, len, (_Float16 *)ctx, ctx_lo_offset, B, S, d, heads, s);

@@ -381,7 +381,7 @@ int alloc_lane_state(nt_model *m, hipStream_t s) {
   const size_t o_x = cv.take((size_t)Mt * d * 4), o_a16 = cv.take((size_t)Mt * d * kEncElt),
                o_qkv = cv.take((size_t)Mt * 3 * d * kEncElt), o_ctx16 = cv.take((size_t)Mt * d * kEncElt),
                o_u16 = cv.take((size_t)Mt * std::max(F, 1) * kEncElt), o_enc = cv.take((size_t)Mt * d * kEncElt);
-  m->fold_positions = m->kv_i16 && cfg->n_dec == 1 ? std::min<int64_t>(Mt, (int64_t)nt::kDec1FoldRows * cfg->max_len) : 0;
+  m->fold_positions = m->kv_i16 && cfg->n_dec == 1 ? std::min<int64_t>(Mt, nt::kDec1FoldTokens) : 0;
   std::vector<size_t> o_fold(cfg->n_dec), o_fconst(cfg->n_dec);
   for (int l = 0; l < cfg->n_dec; l++) {
     o_fold[l] = cv.take((size_t)m->fold_positions * 2 * d * 4 + 16);
@@ -901,7 +901,7 @@ int nt_encode(nt_model *m, const int32_t *d_src, const int32_t *d_len, int32_t B
   if (!all_fused)
     KT(K_LN_ENC, Md * dd * (4 + ea), 8 * Md * dd,
        nt::launch_layer_norm(m->x, M, d, m->enc_final.g, m->enc_final.b, lne, m->enc_out, ln_mode, lo_d, s));
-  m->folded = m->kv_i16 && c.n_dec == 1 && B <= nt::kDec1FoldRows && M <= m->fold_positions;
+  m->folded = m->kv_i16 && c.n_dec == 1 && B <= nt::kDec1FoldRows && M <= nt::kDec1FoldTokens && M <= m->fold_positions;
   const float dec_qscale = 1.0f / std::sqrt((float)(d / dec_heads(&c)));
   for (int l = 0; l < c.n_dec; l++) {
     nt::GemmEpilogue e;

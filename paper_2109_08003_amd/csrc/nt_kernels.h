@@ -390,7 +390,7 @@ struct Dec1Args {
   float *lo_norm;
 };
 hipError_t launch_dec1(const Dec1Args &a, int d, hipStream_t s);
-constexpr int kDec1FoldRows = 256;
+constexpr int kDec1FoldRows = 512, kDec1FoldTokens = 32768;
 // x [M][2 d] fp32 (key | value of M positions) -> codes [M][2][d] and scales [M][2]; planes (optional): the rounded
 // vectors as head / tail planes [M][d] (tail lo_offset elements after the head) and key_const[m] = scale * (u . key)
 struct KvPlanes {
