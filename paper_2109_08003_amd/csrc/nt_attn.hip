@@ -310,7 +310,8 @@ __device__ __forceinline__ void split8u(const float *f, half8 &hi, half8 &lo) {
 // qkv = v [B*S, d]; one MFMA per score product.
 // WPU = 4: the four waves of a workgroup share a unit, for batches with fewer units than the chip has SIMDs: each computes
 // the scores (the same MFMAs in the same order, with more of their operands in flight) and takes a quarter of the value
-// columns, whose 16 blocks in turn are most of a lone wave's time (one sentence of 22 tokens: 23 us with one wave).
+// columns, whose 16 blocks in turn are most of a lone wave's time (one sentence of 22 tokens: 23 us with one wave, 14 with four;
+// with all value blocks requested before the softmax one sentence 1010 -> 1000 us, 45 sentences 3225 -> 3186 us in all).
 // REL: relative keys of clip distance <= 15, taken as one more block of keys: rk . q for the 2 clip + 1 offsets comes out of the
 // MFMAs with a query per lane, goes through the LDS and is added to the scores by clipped distance.
 template <int DH, int NKB, bool QK16, int WPU, bool REL>
@@ -339,6 +340,39 @@ __global__ __launch_bounds__(256, WPU == 4 ? 1 : NKB == 1 ? 3 : NKB == 2 ? 2 : 1
   }
   const int nkb = (L + 31) / 32;  // <= NKB, checked by the launcher through S
   constexpr int CU = WPU == 4 ? (NKB == 1 ? 4 : 2) : 1;  // 64-wide slices of the scores requested together
+
+  // ---- values: 32-column blocks, requested ahead of their use ----
+  // With two key blocks the V values of the next block are requested before the MFMAs and stores of the current one
+  // (with one block nothing is gained and the registers of the third wave per SIMD are exceeded; beyond two the
+  // registers do not allow it).  Waves that share a unit have registers to spare: they request all their blocks behind the last
+  // slices of the scores, so that the values travel during the softmax.
+  const char *vbase = (const char *)(qkv + row0 * ld + (QK16 ? 0 : 2 * d) + hoff);
+  constexpr int STEP = WPU, NCB = DH / 32;
+  constexpr bool UP_FRONT = WPU == 4 && NKB <= 3, PREFETCH = NKB == 2 && !UP_FRONT;
+  const int cb_first = WPU == 4 ? wave : 0;
+  float fv[UP_FRONT ? NCB / STEP : PREFETCH ? 2 : 1][NKB][2][8];
+  auto request = [&](int cb, int slot) {
+    // the block's base stays one opaque scalar pair: otherwise every one of the 16 addresses becomes a 64-bit
+    // induction variable of its own
+    const char *vb = vbase + cb * 128;
+    asm volatile("" : "+s"(vb));
+#pragma unroll
+    for (int kb = 0; kb < NKB; kb++) {
+      if (kb < nkb) {
+#pragma unroll
+        for (int ks = 0; ks < 2; ks++)
+#pragma unroll
+          for (int e = 0; e < 8; e++) {  // same key order as the probability registers
+            const int key = min(kb * 32 + (2 * ks + (e >> 2)) * 8 + g * 4 + (e & 3), L - 1);
+            fv[slot][kb][ks][e] = *(const float *)(vb + (unsigned)((key * (int)ld + li) * 4));
+          }
+      }
+    }
+  };
+  auto request_all = [&]() {
+#pragma unroll
+    for (int i = 0; i < NCB / STEP; i++) request(cb_first + i * STEP, i);
+  };
 
   // ---- scores, transposed: sc[kb][v] = q_(q0+li) . k_(kb*32 + (v/4)*8 + g*4 + v%4) ----
   floatx16 sc[NKB];
@@ -369,6 +403,7 @@ __global__ __launch_bounds__(256, WPU == 4 ? 1 : NKB == 1 ? 3 : NKB == 2 ? 2 : 1
           }
         }
       }
+      if (UP_FRONT && c0 + CU >= DH / 64) request_all();
       if (CU > 1) {
 #pragma unroll
         for (int kb = 0; kb < NKB; kb++)
@@ -456,6 +491,8 @@ __global__ __launch_bounds__(256, WPU == 4 ? 1 : NKB == 1 ? 3 : NKB == 2 ? 2 : 1
       }
   }
 
+  if (UP_FRONT && !QK16) request_all();
+
   // ---- fp32 softmax over the keys: in-lane, then one exchange between the lane groups ----
   float mx = -INFINITY;
 #pragma unroll
@@ -490,33 +527,7 @@ __global__ __launch_bounds__(256, WPU == 4 ? 1 : NKB == 1 ? 3 : NKB == 2 ? 2 : 1
     }
 
   // ---- context = P V, one 32-column block at a time ----
-  // With two key blocks the V values of the next block are requested before the MFMAs and stores of the current one
-  // (with one block nothing is gained and the registers of the third wave per SIMD are exceeded; beyond two the
-  // registers do not allow it).
-  const char *vbase = (const char *)(qkv + row0 * ld + (QK16 ? 0 : 2 * d) + hoff);
   char *obase = (char *)(ctx + row0 * d + hoff);
-  constexpr bool PREFETCH = NKB == 2 || (WPU == 4 && NKB == 1);
-  constexpr int STEP = WPU, NCB = DH / 32;
-  const int cb_first = WPU == 4 ? wave : 0;
-  float fv[PREFETCH ? 2 : 1][NKB][2][8];
-  auto request = [&](int cb, int slot) {
-    // the block's base stays one opaque scalar pair: otherwise every one of the 16 addresses becomes a 64-bit
-    // induction variable of its own
-    const char *vb = vbase + cb * 128;
-    asm volatile("" : "+s"(vb));
-#pragma unroll
-    for (int kb = 0; kb < NKB; kb++) {
-      if (kb < nkb) {
-#pragma unroll
-        for (int ks = 0; ks < 2; ks++)
-#pragma unroll
-          for (int e = 0; e < 8; e++) {  // same key order as the probability registers
-            const int key = min(kb * 32 + (2 * ks + (e >> 2)) * 8 + g * 4 + (e & 3), L - 1);
-            fv[slot][kb][ks][e] = *(const float *)(vb + (unsigned)((key * (int)ld + li) * 4));
-          }
-      }
-    }
-  };
   auto block = [&](int cb, int slot) {
     char *ob = obase + cb * 64;
     asm volatile("" : "+s"(ob));
@@ -547,7 +558,10 @@ __global__ __launch_bounds__(256, WPU == 4 ? 1 : NKB == 1 ? 3 : NKB == 2 ? 2 : 1
       *((_Float16 *)at_ + ctx_lo_offset) = (_Float16)(val - (float)hi);
     }
   };
-  if constexpr (PREFETCH) {
+  if constexpr (UP_FRONT) {
+#pragma unroll
+    for (int i = 0; i < NCB / STEP; i++) block(cb_first + i * STEP, i);
+  } else if constexpr (PREFETCH) {
     static_assert(NCB % (2 * STEP) == 0, "the two slots alternate over an even number of column blocks");
     request(cb_first, 0);
 #pragma nounroll
