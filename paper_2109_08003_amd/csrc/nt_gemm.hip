@@ -399,12 +399,12 @@ __global__ __launch_bounds__(256) void gemm_mid_kernel(const void *A, const void
 }
 
 hipError_t launch_gemm(int a_mode, bool c_f32, const void *A, const void *A_lo, long lda, const _Float16 *Wt, int M,
-                       int N, int K, const GemmEpilogue &e, hipStream_t s, const _Float16 *Wp, bool tail) {
+                       int N, int K, const GemmEpilogue &e, hipStream_t s, const _Float16 *Wp, bool tail, int shape_rows) {
   if (M <= 0 || N <= 0) return hipSuccess;
   if (a_mode == A_PLANES && Wp && gemm_stream_supported(N, K) && e.n_split % 32 == 0)
     return launch_gemm_stream(c_f32, (const _Float16 *)A, (const _Float16 *)A_lo, lda, Wp, M, N, K, e, s, tail);
   if (a_mode == A_PLANES && Wp && c_f32 && gemm_stream_k_supported(N, K) && e.n_split % 32 == 0)
-    return launch_gemm_stream_k(c_f32, (const _Float16 *)A, (const _Float16 *)A_lo, lda, Wp, M, N, K, e, s, tail);
+    return launch_gemm_stream_k(c_f32, (const _Float16 *)A, (const _Float16 *)A_lo, lda, Wp, M, N, K, e, s, tail, shape_rows);
   const int big_tiles = ((M + BM - 1) / BM) * ((N + BN - 1) / BN);
   const bool mid = big_tiles < 2 * 256;  // fewer than two 128x128 tiles per CU: use the 64x64 variant
   dim3 grid(mid ? tile_grid((M + MID - 1) / MID, (N + MID - 1) / MID) : tile_grid((M + BM - 1) / BM, (N + BN - 1) / BN)),

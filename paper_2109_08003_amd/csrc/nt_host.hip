@@ -1080,7 +1080,7 @@ int decode_step(nt_model *m, DecodeCursor &cu, hipStream_t s) {
         A = m->a32;
       }
       if (planes)  // A is a plane pair written by the attention kernel
-        KT(id, by, fl, nt::launch_gemm(nt::A_PLANES, true, A, (const _Float16 *)A + lo_rows * K, K, Wt, R, N, K, e, s, Wp));
+        KT(id, by, fl, nt::launch_gemm(nt::A_PLANES, true, A, (const _Float16 *)A + lo_rows * K, K, Wt, R, N, K, e, s, Wp, true, rows_for_choice));
       else
         KT(id, by, fl, nt::launch_gemm(nt::A_F32, true, A, nullptr, K, Wt, R, N, K, e, s));
       return NT_OK;

@@ -53,8 +53,10 @@ enum AMode { A_F16 = 0, A_PLANES = 1, A_F32 = 2 };
 // fp32, else fp16.  K must be a multiple of 64; lda in elements.
 // Wp (optional): the same weights in MFMA fragment order (vocab_pack layout); with A_PLANES and a supported
 // shape the streaming kernel is used, and tail = false then leaves the tail plane out of the product.
+// shape_rows selects the kernel form (0: M), as in Dec1Args.
 hipError_t launch_gemm(int a_mode, bool c_f32, const void *A, const void *A_lo, long lda, const _Float16 *Wt, int M,
-                       int N, int K, const GemmEpilogue &e, hipStream_t s, const _Float16 *Wp = nullptr, bool tail = true);
+                       int N, int K, const GemmEpilogue &e, hipStream_t s, const _Float16 *Wp = nullptr, bool tail = true,
+                       int shape_rows = 0);
 
 // Streaming form for K = 256 / 512 and N % 64 == 0 (nt_gemm_stream.hip): the A tile (head/tail planes) stays in
 // the LDS, the weights stream through registers in fragment order.
@@ -68,7 +70,7 @@ bool gemm_stream_supported(int N, int K);
 // Wp = vocab_pack of Wt [N][K]; N a multiple of 512.
 bool gemm_stream_k_supported(int N, int K);
 hipError_t launch_gemm_stream_k(bool c_f32, const _Float16 *A, const _Float16 *A_lo, long lda, const _Float16 *Wp, int M,
-                                int N, int K, const GemmEpilogue &e, hipStream_t s, bool tail = true);
+                                int N, int K, const GemmEpilogue &e, hipStream_t s, bool tail = true, int shape_rows = 0);
 // tail = false: only the head plane of A enters the product (fp16 activations: half the matrix-core work)
 hipError_t launch_gemm_stream_ln(bool c_f32, const float *X, long ldx, const GemmLayerNorm &ln, const _Float16 *Wp, int M,
                                  int N, int K, const GemmEpilogue &e, hipStream_t s, bool tail = true);

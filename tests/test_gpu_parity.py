@@ -871,7 +871,8 @@ def test_c2_full_workload_sampled_against_oracle(nt, oracle):
 
 # ------------------------------------------------------------------------------ row-count edges of the decoder kernels
 @pytest.mark.parametrize("d,ffn,eos,heads,clip", [(512, 0, False, 1, 0), (512, 512, False, 1, 0), (256, 0, False, 1, 0), (256, 256, True, 1, 0),
-                                                  (512, 0, False, 8, 0), (512, 512, False, 8, 3), (512, 0, True, 8, 16)])
+                                                  (512, 0, False, 8, 0), (512, 512, False, 8, 3), (512, 0, True, 8, 16), (512, 1024, False, 8, 0),
+                                                  (512, 2048, True, 8, 0)])
 def test_decoder_layer_at_row_count_edges(nt, oracle, torch_cuda, d, ffn, eos, heads, clip):
     """A decoder layer at the row counts where its kernels change form or leave a workgroup partly filled:
     every sentence of a small-vocabulary model against the oracle."""
@@ -882,7 +883,7 @@ def test_decoder_layer_at_row_count_edges(nt, oracle, torch_cuda, d, ffn, eos, h
     rng = np.random.default_rng(d + ffn)
     src = [rng.integers(4, 300, size=n).astype(np.int32) for n in rng.integers(3, 13, size=1100)]
     want = [om.greedy(s)[0] for s in src[:60]]
-    for rows in (1, 2, 3, 5, 17, 63, 65, 511, 513, 1023, 1025, 1041):
+    for rows in (1, 2, 3, 5, 17, 63, 65, 256, 257, 511, 513, 1023, 1025, 1041):
         pick = sort_desc(src[:min(rows, 60)] + src[64:64 + rows - min(rows, 60)])
         ids, lens = pad(pick, cfg["pad_id"])
         steps = np.array([nt.n_steps(int(n)) for n in lens], dtype=np.int32)
@@ -911,4 +912,35 @@ def test_decoder_layer_at_row_count_edges(nt, oracle, torch_cuda, d, ffn, eos, h
                 ref.append(w), mine.append(got[r, : steps[r]]), some.append(s)
         bad, _ = audit_mismatches(om, some, mine, ref, cfg)
         assert bad <= 2 and len(some) >= min(rows, 60) - 2, (rows, bad)
+    gm.close()
+
+
+# ------------------------------------------------------------------------------ key-block edges of the encoder attention
+@pytest.mark.parametrize("heads,clip,longest", [(1, 0, (129, 160, 193, 224, 225)), (8, 0, (129, 224, 225)),
+                                                (8, 15, (1, 31, 33, 64, 97, 128, 129, 224, 225)), (8, 16, (40, 130))])
+def test_encoder_attention_at_key_block_edges(nt, oracle, torch_cuda, heads, clip, longest):
+    """One encoder layer where the attention changes form: blocks of 32 keys, their last one full, single or missing, the
+    longest sentence a wave holds in registers, relative keys as a block of their own and without room for one.
+    Bounds on the error's 2-norm: with eight heads every activation carries a head and a tail plane, 2^-22 each, and fp32 sums
+    of up to 512 terms leave about 1e-6; one key too many or too few is 1/225 of a context.  The one-head plan multiplies the
+    query and key columns with 11-bit activations (2^-11 of a score of order one)."""
+    torch = torch_cuda
+    cfg = nt_synth.model_config("C1", d_model=512, vocab=300, n_enc=1, max_len=256, dec_d_ffn=-1, n_heads=heads, rpr_clip=clip)
+    blob = nt_synth.make_weights(cfg, seed=9, random_affine=True)
+    gm, om = nt.Model(cfg, blob, max_batch_tokens=65536, pipeline_lanes=1), oracle.Model(cfg, blob)
+    rng = np.random.default_rng(heads + clip)
+    for S in longest:
+        tiles = (S + 31) // 32
+        lens = [S] + [n for n in (S - 1, 129, 128, 97, 33, 32, 31, 2, 1) if 0 < n < S]
+        lens = [S] * max(0, -(-256 // (heads * tiles)) - len(lens)) + lens    # as many units as the long form asks for
+        src = [rng.integers(4, 300, size=n).astype(np.int32) for n in lens]
+        ids, ln = pad(src, cfg["pad_id"])
+        gm.encode(torch.from_numpy(ids).cuda(), torch.from_numpy(ln).cuda())
+        out = torch.empty(*ids.shape, 512, dtype=torch.float32, device="cuda")
+        gm.debug_encoder_out(out)
+        out = out.cpu().numpy().astype(np.float64)
+        assert np.isfinite(out).all()
+        for i in sorted({0, *range(max(0, len(src) - 10), len(src))}):
+            err = rel_l2(out[i, : lens[i]], om.encode(src[i]))
+            assert err <= (5e-4 if heads == 1 else 5e-5), (S, lens[i], err)
     gm.close()
