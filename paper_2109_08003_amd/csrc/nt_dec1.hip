@@ -29,7 +29,10 @@
 // head + tail), a step's attention half has no projection left.  The cross products are formed from the rounded (integer)
 // vectors, so nothing is rounded that was not before, and kept in fp32: twice the bytes, which is why larger batches, whose
 // time is those bytes, do without (a 4,096-token budget, batches of 36 to 341 rows: 27.5 ms folded up to 256 rows, 26.7 up to
-// 512; 320 sentences of 150 tokens: 24.0 ms with, 23.9 without, which puts the line for kDec1FoldTokens below that).  What is left is latency: a row per workgroup of four waves, the
+// 512; batches alone on the chip, 300 / 450 rows of 35 padded tokens: 3.14 -> 2.74 / 3.89 -> 3.52 ms folded; 320 rows of 180:
+// 24.0 ms with, 23.9 without, which puts the line for kDec1FoldTokens below that.  Beside other lanes, who share the
+// bandwidth, it lies lower - a 16,384-token budget 80.0 ms folded, 78.8 without - but a batch's tokens may not depend on what
+// runs beside it).  What is left is latency: a row per workgroup of four waves, the
 // first cross keys requested before the self-attention.  One row 20.6 us without folding, 12.8 with the cross cache folded,
 // 45 rows 26 and 17.8; with the self values too, one sentence 1119 -> 1012 us, 45 sentences 3742 -> 3207 us, 8 sentences of
 // the 256-wide model 1253 -> 1175 us, a 4,096-token budget 28.0 -> 27.5 ms.

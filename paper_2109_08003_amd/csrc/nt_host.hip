@@ -1,7 +1,7 @@
 // Host side of libnt: C ABI entry points, weight re-layout (and, for the 8-bit output layer, quantisation), arena
 // planning, the token-budget batcher, the step scheduler that enqueues the gfx950 kernels (fixed-length and
 // EOS-terminated) and the pipeline lanes.  No CPU fallback exists: every numerical step of the path is a kernel in
-// nt_gemm.hip / nt_gemm_stream.hip / nt_vocab.hip / nt_vocab_q8.hip / nt_rows.hip / nt_attn.hip.
+// nt_gemm.hip / nt_gemm_stream.hip / nt_vocab.hip / nt_vocab_q8.hip / nt_rows.hip / nt_attn.hip / nt_dec1.hip / nt_decoder.hip.
 #include <algorithm>
 #include <atomic>
 #include <chrono>
@@ -256,7 +256,9 @@ struct nt_model {
   };
   static constexpr int kStagings = 2;
   Staging stage[kStagings];
-  bool crowded = false;  // two or more other lanes have batches in flight (set by the translate calls while they run)
+  // two or more other lanes have batches in flight (set by the translate calls while they run): rows per workgroup only, never
+  // anything that changes a sum - a batch gives the same tokens alone and beside others
+  bool crowded = false;
   // state left by nt_encode
   int32_t B = 0, S = 0;
   bool encoded = false;
@@ -369,8 +371,8 @@ int alloc_lane_state(nt_model *m, hipStream_t s) {
       for (int tiled = 0; tiled < 2; tiled++) {  // either family of arg-max kernels may be selected later
         nt::VocabWeights w = m->vw;
         w.force_tiled = tiled != 0;
-        for (int crowded = 0; crowded < 2; crowded++)
-          worst = std::max(worst, rows * nt::vocab_argmax_partials(w, (int)rows, false, crowded != 0));
+        for (int wide = 0; wide < 2; wide++)
+          worst = std::max(worst, rows * nt::vocab_argmax_partials(w, (int)rows, false, wide != 0));
         worst = std::max(worst, rows * nt::vocab_argmax_partials(w, (int)rows, true, false));
       }
       if (cfg->q8_output) worst = std::max(worst, rows * nt::vocab_q8_partials((int)rows));
@@ -901,7 +903,8 @@ int nt_encode(nt_model *m, const int32_t *d_src, const int32_t *d_len, int32_t B
   if (!all_fused)
     KT(K_LN_ENC, Md * dd * (4 + ea), 8 * Md * dd,
        nt::launch_layer_norm(m->x, M, d, m->enc_final.g, m->enc_final.b, lne, m->enc_out, ln_mode, lo_d, s));
-  m->folded = m->kv_i16 && c.n_dec == 1 && B <= nt::kDec1FoldRows && M <= nt::kDec1FoldTokens && M <= m->fold_positions;
+  m->folded = m->kv_i16 && c.n_dec == 1 && B <= nt::kDec1FoldRows &&
+              M <= std::min<int64_t>(nt::kDec1FoldTokens, m->fold_positions);
   const float dec_qscale = 1.0f / std::sqrt((float)(d / dec_heads(&c)));
   for (int l = 0; l < c.n_dec; l++) {
     nt::GemmEpilogue e;
@@ -1242,15 +1245,15 @@ int decode_step(nt_model *m, DecodeCursor &cu, hipStream_t s) {
          nt::launch_gemm(nt::A_PLANES, true, h_hi, h_lo, d, m->Wout, R, V, d, e, s));
     } else {
       cu.prev_cert = R >= kCertMinRows;
-      const bool crowded = m->crowded || rows_for_choice > nt::kVocabWideRows;
-      const int np_ = nt::vocab_argmax_partials(m->vw, R, cu.prev_cert, crowded);
+      const bool wide = rows_for_choice <= nt::kVocabWideRows;
+      const int np_ = nt::vocab_argmax_partials(m->vw, R, cu.prev_cert, wide);
       if (cu.prev_cert)
         KT(K_VOCAB_ARGMAX, (double)V * dd * 2 + Rd * dd * 4 + Rd * np_ * 8, 2 * Rd * dd * V,
            nt::launch_vocab_argmax_certified(h_hi, h_lo, d, m->vw, R, m->lo_norm, m->w_norm_max, m->pk, m->ps,
                                              m->tok, m->slot_of_row, m->cert_list, m->flags + 4, m->final_key, m->need_mask, s));
       else  // below the certified variant's row count the step is bound by the stream of the output matrix
         KT(K_VOCAB_ARGMAX_SMALL, (double)V * dd * 2 + Rd * dd * 4 + Rd * np_ * 8, 2 * Rd * dd * V,
-           nt::launch_vocab_argmax(h_hi, h_lo, d, m->vw, R, m->pk, crowded, s));
+           nt::launch_vocab_argmax(h_hi, h_lo, d, m->vw, R, m->pk, wide, s));
       cu.partials_prev = np_;
     }
   }

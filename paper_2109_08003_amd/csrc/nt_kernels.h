@@ -124,13 +124,13 @@ void vocab_pack(const _Float16 *Wt, int N, int K, _Float16 *dst);
 
 // n_partials of the launch configuration used with M rows (exact: head + tail planes; certified:
 // head plane first).
-// crowded: other lanes' kernels share the chip.  If not, up to kVocabWideRows rows take a kernel of its own (exact only;
-// its sums run in another order, so a caller whose M depends on timing decides by a row count that does not).
+// wide: up to kVocabWideRows rows take a kernel of its own (exact only; its sums run in another order, so a caller whose M
+// depends on timing decides by a row count that does not, and nobody by what else is running).
 constexpr int kVocabWideRows = 64;
-int vocab_argmax_partials(const VocabWeights &w, int M, bool certified, bool crowded);
+int vocab_argmax_partials(const VocabWeights &w, int M, bool certified, bool wide);
 // h is a head/tail pair of fp16 planes.
 hipError_t launch_vocab_argmax(const _Float16 *h, const _Float16 *h_lo, long ldh, const VocabWeights &w, int M,
-                               unsigned long long *pk, bool crowded, hipStream_t s);
+                               unsigned long long *pk, bool wide, hipStream_t s);
 
 // Same result as launch_vocab_argmax, usually at half the MFMA work: a head-only pass whose winner is
 // certified against a rigorous bound on the contribution of the tail (lo_norm[m] = ||tail of row m||,

@@ -471,23 +471,22 @@ __global__ __launch_bounds__(512) void vocab_wide_kernel(const _Float16 *__restr
 // Strips per workgroup of the wide kernel: one (eight k-parts) as long as that is one round of workgroups, else two
 static int vw_strips(int N) { return (N + 63) / 64 <= 256 ? 1 : 2; }
 static int vw_groups(int N) { return ((N + 63) / 64 + vw_strips(N) - 1) / vw_strips(N); }
-// Taken for up to 64 rows when no other lane's kernels share the chip (they would wait for its workgroups: see
-// VS_EXACT_MAX_RANGES), and for vocabularies that need at most two rounds of workgroups.
-static bool use_wide(const VocabWeights &w, int M, bool crowded) { return !crowded && M <= kVocabWideRows && vw_groups(w.N) <= 512; }
+// Taken for up to 64 rows and vocabularies that need at most two rounds of workgroups.
+static bool use_wide(const VocabWeights &w, int M, bool wide) { return wide && M <= kVocabWideRows && vw_groups(w.N) <= 512; }
 
 static bool use_stream(const VocabWeights &w) { return !w.force_tiled && w.Wp && vocab_stream_supported(w.K); }
 
-int vocab_argmax_partials(const VocabWeights &w, int M, bool certified, bool crowded) {
+int vocab_argmax_partials(const VocabWeights &w, int M, bool certified, bool wide) {
   if (!use_stream(w)) return vocab_argmax_partials_tiled(M, w.N);
-  if (!certified && use_wide(w, M, crowded)) return vw_groups(w.N);
+  if (!certified && use_wide(w, M, wide)) return vw_groups(w.N);
   return certified ? vs_split(M, 128, 64).G : vs_split(M, 64, VS_EXACT_MAX_RANGES).G;
 }
 
 hipError_t launch_vocab_argmax(const _Float16 *h, const _Float16 *h_lo, long ldh, const VocabWeights &w, int M,
-                               unsigned long long *pk, bool crowded, hipStream_t s) {
+                               unsigned long long *pk, bool wide, hipStream_t s) {
   if (M <= 0) return hipSuccess;
   if (!use_stream(w)) return launch_vocab_argmax_tiled(h, h_lo, ldh, w.Wt, M, w.N, w.K, pk, s);
-  if (use_wide(w, M, crowded)) {
+  if (use_wide(w, M, wide)) {
     const int G = vw_groups(w.N), spw = vw_strips(w.N);
 #define NT_VW(K_, S_) \
   if (w.K == K_ && spw == S_) hipLaunchKernelGGL((vocab_wide_kernel<K_, S_>), dim3(G), dim3(512), 0, s, h, h_lo, ldh, M, w.Wp, w.N, G, pk);

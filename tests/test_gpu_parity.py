@@ -237,6 +237,24 @@ def test_lane_count_and_feeding_threads_do_not_change_translations(nt):
             assert np.array_equal(ro, oo) and np.array_equal(ref, out), (budget, rep)
 
 
+def test_batches_give_the_same_tokens_alone_and_beside_others(nt):
+    """Kernel forms are chosen by a batch's own sizes alone: one lane, where every batch has the chip to itself, and four
+    lanes give the same tokens, bit for bit, on enough sentences that a sum in another order would show (about one token in
+    20,000 lies on the other side of a near-tie then)."""
+    cfg = nt_synth.model_config("C1")
+    blob = nt_synth.make_weights(cfg, seed=0)
+    tokens, offsets = nt_synth.workload("C2", 30000)
+    one = nt.Model(cfg, blob, max_batch_tokens=65536, pipeline_lanes=1)
+    four = nt.Model(cfg, blob, max_batch_tokens=65536, pipeline_lanes=4)
+    for budget, n in ((4096, 6000), (16384, 16000), (65536, 30000)):
+        t, o = tokens[:offsets[n]], offsets[:n + 1]
+        ref, ro = one.translate_batch(t, o, token_budget=budget)
+        out, oo = four.translate_batch(t, o, token_budget=budget)
+        assert np.array_equal(ro, oo) and np.array_equal(ref, out), (budget, int((ref != out).sum()))
+    one.close()
+    four.close()
+
+
 # ------------------------------------------------------------------------------ edge cases
 def test_edge_cases(c0, nt, oracle):
     cfg, blob, src, gm, om = c0
