@@ -700,15 +700,15 @@ __global__ __launch_bounds__(NWAVES * 64) void dec1_kernel(Dec1Args a) {
 
 template <int D, bool FFN, bool HEADS>
 static hipError_t d1_launch(const Dec1Args &a, hipStream_t s) {
-  // Partial softmaxes per row: four below 1,024 rows, one from there on (they differ in the last bit, so the choice
-  // goes by shape_rows; the number of rows per workgroup changes no result there).
+  // The form goes by shape_rows, never by what else is running or by a count the host happened to read: the forms differ in
+  // the last bit (number of partial softmaxes, contraction of products and sums).
   // 1,024 rows and more: sixteen rows per workgroup.  With eight the launch alone is as fast (71 us at 1,900 rows), but
   // its 238 workgroups pull the matrices through twice as many CUs for the same rows; with 119 the other lanes' matrix
   // kernels get the rest of the chip and the job is 4 % faster (200,000 sentences: 560 against 582 ms).
-  // Fewer rows, alone on the chip: two per workgroup as long as one round of workgroups covers them (320 rows of 180
-  // tokens: 24.4 against 26.7 ms).  With other lanes busy four rows from 64 on (a 4,096-token budget: 29.9 against 30.5
-  // ms), eight from 257 on (65,536 tokens: 550 against 554 ms): less weight traffic, and CUs for the others.
-  const bool parts = (a.shape_rows > 0 ? a.shape_rows : a.rows) < 1024;
+  // Up to 512 rows two per workgroup (320 rows of 180 tokens alone: 24.4 against 26.7 ms with four), in between eight
+  // (65,536 tokens: 550 against 554 ms with four).  Eight heads, whose waves hold fp32 keys: four from 65 rows on and eight
+  // from 257 on.
+  const int shape = a.shape_rows > 0 ? a.shape_rows : a.rows;
 #define NT_D1(RW_, NW_, P_, F_)                                                                                          \
   do {                                                                                                                  \
     const dim3 grid((unsigned)((a.rows + RW_ - 1) / RW_));                                                              \
@@ -722,9 +722,9 @@ static hipError_t d1_launch(const Dec1Args &a, hipStream_t s) {
       return hipGetLastError();
     }
   }
-  if (!parts) NT_D1(16, 16, 1, false);
-  else if (a.rows <= (a.crowded ? 64 : 512)) NT_D1(2, 8, 4, false);
-  else if (a.rows <= 256 || !a.crowded) NT_D1(4, 16, 4, false);
+  if (shape >= 1024) NT_D1(16, 16, 1, false);
+  else if (shape <= (HEADS ? 64 : 512)) NT_D1(2, 8, 4, false);
+  else if (HEADS && shape <= 256) NT_D1(4, 16, 4, false);
   else NT_D1(8, 16, 4, false);
 #undef NT_D1
   return hipGetLastError();

@@ -256,9 +256,6 @@ struct nt_model {
   };
   static constexpr int kStagings = 2;
   Staging stage[kStagings];
-  // two or more other lanes have batches in flight (set by the translate calls while they run): rows per workgroup only, never
-  // anything that changes a sum - a batch gives the same tokens alone and beside others
-  bool crowded = false;
   // state left by nt_encode
   int32_t B = 0, S = 0;
   bool encoded = false;
@@ -1128,7 +1125,7 @@ int decode_step(nt_model *m, DecodeCursor &cu, hipStream_t s) {
           const bool ffn_inside = m->kv_i16 && F == d && L.ffn.W1_p != nullptr && L.ffn.W2_p != nullptr;
           const bool to_final = last && (F == 0 || ffn_inside) && !c.q8_output;
           nt::Dec1Args at{};
-          at.rows = R; at.shape_rows = rows_for_choice; at.crowded = m->crowded; at.origin = origin; at.eps = lne; at.z = m->z; at.write_z = !to_final;
+          at.rows = R; at.shape_rows = rows_for_choice; at.origin = origin; at.eps = lne; at.z = m->z; at.write_z = !to_final;
           at.q = m->q32; at.kv_new = m->kv_new; at.self_kv = m->self_kv[l]; at.self_sc = m->self_sc[l];
           at.self_positions = T; at.n_keys = t + 1; at.heads = heads_layer ? H : 1; at.rk = L.self.rk; at.clip = c.rpr_clip;
           at.Wo_self = L.self.Wo_p; at.bo_self = L.self.bo; at.Wq = L.cross.Wq_p; at.bq = L.cross.bq; at.Wo_cross = L.cross.Wo_p;
@@ -1640,7 +1637,6 @@ struct Pipeline {
       HIP_TRY(hipStreamWaitEvent(ln->lane_stream, m->lane_start, 0));
       for (auto &st : ln->stage) st.busy = false;
       ln->timing.mask = m->timing.mask;
-      ln->crowded = lane.size() > 2 && plan.nb > 2;
     }
     return NT_OK;
   }
@@ -1709,7 +1705,6 @@ struct Pipeline {
         if (first_err == NT_OK) first_err = collect(ln->stage[(older + j) % nt_model::kStagings]);
       (void)hipStreamSynchronize(ln->lane_stream);
       for (auto &st : ln->stage) st.busy = false;
-      ln->crowded = false;
     }
     return first_err;
   }

@@ -360,7 +360,6 @@ struct Dec1Args {
   int rows;
   int shape_rows;        // row count that selects the kernel form (0: rows).  The forms differ in the last bit, so a
                          // caller whose row count depends on timing passes one that does not
-  int crowded;           // other lanes' kernels share the chip: fewer, larger workgroups
   const int32_t *origin; // optional: row r uses cache row origin[r] (< 0: zero context)
   LnEps eps;
   float *z;              // [rows, d] residual stream; written back if write_z
