@@ -1777,19 +1777,26 @@ int nt_translate_batch(nt_model *m, const int32_t *h_tokens, const int64_t *h_of
     for (size_t li = 0; li < n_lanes && first_err == NT_OK; li++)
       if (lane_rc[li]) { first_err = lane_rc[li]; g_err = lane_err[li]; }
   } else {
-    // one thread: the next batch goes to the first lane found ready for it
+    // one thread: the next batch goes to the first lane found ready for it.  Only hipErrorNotReady means "still running": a
+    // failed batch never becomes ready, its error ends the call
     std::vector<int64_t> nth(n_lanes, 0);
-    auto free_now = [&](nt_model::Staging &st) { return !st.busy || hipEventQuery(st.done) == hipSuccess; };
+    auto is_free = [&](nt_model::Staging &st) {
+      const hipError_t q = st.busy ? hipEventQuery(st.done) : hipSuccess;
+      if (q != hipSuccess && q != hipErrorNotReady) first_err = fail(NT_EHIP, "a batch in flight failed: %s", hipGetErrorString(q));
+      return q == hipSuccess;
+    };
     for (int64_t k = 0; k < plan.nb && first_err == NT_OK;) {
       bool placed = false;
       for (size_t li = 0; li < n_lanes && first_err == NT_OK && k < plan.nb; li++) {
         nt_model *ln = pl.lane[li];
         const bool last = plan.nb - k <= (int64_t)n_lanes;
-        if (!free_now(ln->stage[nth[li] % nt_model::kStagings]) || (last && !free_now(ln->stage[(nth[li] + 1) % nt_model::kStagings]))) continue;
+        if (!is_free(ln->stage[nth[li] % nt_model::kStagings]) || (last && !is_free(ln->stage[(nth[li] + 1) % nt_model::kStagings]))) continue;
         first_err = run_batch(li, k++, nth[li]++);
         placed = true;
       }
-      if (!placed) std::this_thread::yield();
+      // any of several events may come first, so this cannot block on one; batches run for milliseconds, and but for the last
+      // ones a lane has its next batch queued already
+      if (!placed && first_err == NT_OK) std::this_thread::sleep_for(std::chrono::microseconds(20));
     }
   }
   return pl.drain(first_err);

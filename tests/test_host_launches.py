@@ -1,0 +1,74 @@
+"""Host side of libnt on a HIP runtime that runs nothing (hip_stub.c): which kernels a call launches with which grids, what a
+load puts on the device, and what happens when the device reports an error.  Each case is a child process, because the stub
+has to be loaded before the library."""
+import json
+import os
+import subprocess
+import sys
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+PREAMBLE = """
+import ctypes as C, json, sys
+stub = C.CDLL(sys.argv[1], mode=C.RTLD_GLOBAL)
+stub.stub_func.restype = stub.stub_launch.restype = C.c_char_p
+import numpy as np
+import nt_synth
+import paper_2109_08003_amd as nt
+
+class Stream:
+    cuda_stream = 0
+
+def config(**kw):
+    return dict(nt_synth.model_config("C1"), vocab=256, max_len=256, **kw)
+
+def load(cfg, tokens=4096, lanes=1):
+    return nt.Model(cfg, np.zeros(nt.param_count(cfg), dtype=np.float16), max_batch_tokens=tokens, stream=Stream, pipeline_lanes=lanes)
+
+def encode(model, rows, length):
+    # the launches of one encode: (kernel, blocks)
+    a = np.zeros(1, dtype=np.int32)
+    stub.stub_clear()
+    nt.binding._check(nt.binding.lib().nt_encode(model._h, a.ctypes.data, a.ctypes.data, rows, length, None))
+    return launches()
+
+def launches():
+    grid, out = (C.c_uint32 * 3)(), []
+    for i in range(stub.stub_n_launches()):
+        out.append((stub.stub_launch(i, grid).decode(), grid[0] * grid[1] * grid[2]))
+    return out
+"""
+
+
+@pytest.fixture(scope="session")
+def host(tmp_path_factory):
+    so = str(tmp_path_factory.mktemp("stub") / "libhipstub.so")
+    subprocess.run(["gcc", "-O1", "-shared", "-fPIC", "-w", "-o", so, os.path.join(ROOT, "tests", "hip_stub.c")], check=True)
+
+    def run(code, timeout=120):
+        """Runs code after the preamble; returns what it printed last, as JSON."""
+        res = subprocess.run([sys.executable, "-c", PREAMBLE + code, so], cwd=ROOT, timeout=timeout, capture_output=True, text=True,
+                             env=dict(os.environ, PYTHONPATH=ROOT))
+        assert res.returncode == 0, res.stderr
+        return json.loads(res.stdout.strip().splitlines()[-1])
+
+    return run
+
+
+# one lane, a large budget, and four lanes; batches of one sentence each, so that every staging set is used several times
+@pytest.mark.parametrize("lanes,budget", [(1, 16), (4, 32768), (4, 16)])
+def test_translate_returns_a_device_error(host, lanes, budget):
+    """Every event reports a launch failure: the call ends with NT_EHIP and does not wait for what never becomes ready."""
+    rc, message = host(f"""
+model = load(config(), lanes={lanes})
+offsets = np.arange(0, 16 * 13, 16, dtype=np.int64)
+C.c_int.in_dll(stub, "stub_event_status").value = 719
+try:
+    model.translate_batch(np.full(192, 5, dtype=np.int32), offsets, {budget}, max_rows=1, stream=Stream)
+    print(json.dumps((0, "")))
+except nt.NtError as e:
+    print(json.dumps((e.code, str(e))))
+""", timeout=60)
+    assert rc == -5 and "stub error" in message
