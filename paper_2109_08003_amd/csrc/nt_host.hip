@@ -625,8 +625,9 @@ int nt_load_weights(const nt_config *cfg, const void *h_blob_fp16, size_t blob_b
     put_f32(br.take(d), d, (const void **)&ln.g);
     put_f32(br.take(d), d, (const void **)&ln.b);
   };
-  // self-attention: Wq|Wk|Wv fused into one [3d][d] matrix; cross-attention: Wq and Wk|Wv
-  auto put_attn = [&](Attn &a, bool cross, bool rpr, int dh, bool fold_values = false) {
+  // self-attention: Wq|Wk|Wv fused into one [3d][d] matrix; cross-attention: Wq and Wk|Wv; fold: what folded batches need besides
+  const bool fold_dec = m->kv_i16 && cfg->n_dec == 1;
+  auto put_attn = [&](Attn &a, bool cross, bool rpr, int dh, bool fold = false) {
     const _Float16 *W[4], *b[4];
     for (int i = 0; i < 4; i++) { W[i] = br.take((int64_t)d * d); b[i] = br.take(d); }
     auto fused = [&](int first, int count, const void **wslot, const void **bslot, const void **pslot) {
@@ -642,8 +643,18 @@ int nt_load_weights(const nt_config *cfg, const void *h_blob_fp16, size_t blob_b
       for (int i = 0; i < count; i++) Packer::widen(b[first + i], d, (float *)(pk.img.data() + ob) + (size_t)i * d);
       fixes.push_back({ob, bslot});
     };
-    if (!cross) fused(0, 3, (const void **)&a.Wqkv, (const void **)&a.bqkv, (const void **)&a.Wqkv_p);
-    if (fold_values) {  // value matrix times output matrix, in double; scaled by a power of two so that the tail keeps its bits
+    if (!cross) {
+      fused(0, 3, (const void **)&a.Wqkv, (const void **)&a.bqkv, (const void **)&a.Wqkv_p);
+    } else {
+      fused(0, 1, (const void **)&a.Wq, (const void **)&a.bq, (const void **)&a.Wq_p);
+      if (fold) {
+        const size_t ob = pk.reserve(nt::vocab_pack_bytes(d, d));
+        nt::vocab_pack(W[0], d, d, (_Float16 *)(pk.img.data() + ob));
+        fixes.push_back({ob, (const void **)&a.Wq_back_p});
+      }
+      fused(1, 2, (const void **)&a.Wkv, (const void **)&a.bkv, (const void **)&a.Wkv_p);
+    }
+    if (fold && !cross) {  // value matrix times output matrix, in double; scaled by a power of two so that the tail keeps its bits
       std::vector<double> prod((size_t)d * d, 0.0), wo((size_t)d * d), bias((size_t)d);
       for (int64_t i = 0; i < (int64_t)d * d; i++) wo[(size_t)i] = (double)(float)W[3][i];
       for (int j = 0; j < d; j++) bias[(size_t)j] = (double)(float)b[3][j];
@@ -675,15 +686,6 @@ int nt_load_weights(const nt_config *cfg, const void *h_blob_fp16, size_t blob_b
       const size_t ob = pk.reserve((size_t)d * 4);
       for (int j = 0; j < d; j++) ((float *)(pk.img.data() + ob))[j] = (float)bias[(size_t)j];
       fixes.push_back({ob, (const void **)&a.bvo});
-    }
-    else {
-      fused(0, 1, (const void **)&a.Wq, (const void **)&a.bq, (const void **)&a.Wq_p);
-      if (m->kv_i16) {
-        const size_t ob = pk.reserve(nt::vocab_pack_bytes(d, d));
-        nt::vocab_pack(W[0], d, d, (_Float16 *)(pk.img.data() + ob));
-        fixes.push_back({ob, (const void **)&a.Wq_back_p});
-      }
-      fused(1, 2, (const void **)&a.Wkv, (const void **)&a.bkv, (const void **)&a.Wkv_p);
     }
     fused(3, 1, (const void **)&a.Wo, (const void **)&a.bo, (const void **)&a.Wo_p);
     if (rpr && c > 0) put_f32(br.take((int64_t)(2 * c + 1) * dh), (2 * c + 1) * dh, (const void **)&a.rk);
@@ -722,9 +724,9 @@ int nt_load_weights(const nt_config *cfg, const void *h_blob_fp16, size_t blob_b
   put_ln(m->enc_final);
   for (auto &L : m->dec) {
     put_ln(L.ln1);
-    put_attn(L.self, false, true, dhd, m->kv_i16 && cfg->n_dec == 1);
+    put_attn(L.self, false, true, dhd, fold_dec);
     put_ln(L.ln2);
-    put_attn(L.cross, true, false, dhd);
+    put_attn(L.cross, true, false, dhd, fold_dec);
     if (Fd > 0) { put_ln(L.ln3); put_ffn(L.ffn, Fd); }
   }
   put_ln(m->dec_final);

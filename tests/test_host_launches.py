@@ -72,3 +72,21 @@ except nt.NtError as e:
     print(json.dumps((e.code, str(e))))
 """, timeout=60)
     assert rc == -5 and "stub error" in message
+
+
+@pytest.mark.parametrize("kw,i16", [(dict(), True), (dict(n_heads=8, d_ffn=64), False), (dict(dec_n_heads=2), False)])
+def test_a_layer_holds_the_matrices_its_kernels_read(host, kw, i16):
+    """One more encoder layer costs its own matrices and no others; one more decoder layer those of its two attentions and its
+    caches (several decoder layers are never folded, so the matrices for folding are not there either)."""
+    d, F = 512, kw.get("d_ffn", 0)
+    enc, dec = host(f"""
+size = lambda **kw: load(config(**dict({kw!r}, **kw)), tokens=64).device_bytes()
+print(json.dumps((size(n_enc=3) - size(n_enc=2), size(n_enc=1, n_dec=3) - size(n_enc=1, n_dec=2))))
+""")
+    norm, parts = 2 * 4 * d, 40                       # parts: each is rounded up to 256 bytes
+    attention = norm + 2 * (4 * d * d * 2) + 4 * 4 * d  # four matrices in two layouts, four biases
+    ffn = norm + 2 * (2 * d * F) + 2 * d * F + 4 * (F + d) if F else 0  # the second matrix, K = 64, has no fragment order
+    positions = 64, (6 * 64 + 4) // 5 + 3 * 64 + 8    # of the cross and of the self cache
+    caches = positions[0] * 2 * d * 2 + positions[1] * 2 * d * (2 if i16 else 4) + (8 * sum(positions) if i16 else 0)
+    assert abs(enc - attention - ffn) <= 256 * parts, enc
+    assert abs(dec - 2 * attention - ffn - caches) <= 256 * parts, dec
