@@ -45,8 +45,9 @@ size_t enc_attention_lds_bytes(int S, int dh, bool f32) {
 __device__ __forceinline__ void split8(const float *f, half8 &hi, half8 &lo) {
 #pragma unroll
   for (int e = 0; e < 8; e++) {
-    hi[e] = (_Float16)f[e];
-    lo[e] = (_Float16)((f[e] - (float)hi[e]) * LO_SCALE);
+    const float x = as_f32(f[e]);
+    hi[e] = (_Float16)x;
+    lo[e] = (_Float16)((x - (float)hi[e]) * LO_SCALE);
   }
 }
 
@@ -190,7 +191,7 @@ __global__ __launch_bounds__(256) void enc_attention_kernel(const void *qkv_, co
     for (int m = 4; m >= 1; m >>= 1) sum += __shfl_xor(sum, m, 64);
     const float inv = 1.f / sum;
     for (int j = sub; j < nk; j += 8) {
-      const float pv = sS[i * SLD + j] * inv;
+      const float pv = as_f32(sS[i * SLD + j] * inv);
       const _Float16 hi = (_Float16)pv;
       sPh[i * PLD + j] = hi;
       if (F32) sPl[i * PLD + j] = (_Float16)((pv - (float)hi) * LO_SCALE);
@@ -260,7 +261,7 @@ __global__ __launch_bounds__(256) void enc_attention_kernel(const void *qkv_, co
         float val = o[cb][v];
         if (F32) val += ox[cb][v] * LO_INV;
         if (q >= S) continue;
-        if (q >= L) val = 0.f;
+        val = as_f32(q >= L ? 0.f : val);
         const _Float16 hi = (_Float16)val;
         ctx[(row0 + q) * d + hoff + col] = hi;
         if (F32) ctx[(row0 + q) * d + hoff + col + ctx_lo_offset] = (_Float16)(val - (float)hi);
@@ -301,8 +302,9 @@ static hipError_t enc_attention_launch(const void *qkv, const int32_t *len, void
 __device__ __forceinline__ void split8u(const float *f, half8 &hi, half8 &lo) {
 #pragma unroll
   for (int e = 0; e < 8; e++) {
-    hi[e] = (_Float16)f[e];
-    lo[e] = (_Float16)(f[e] - (float)hi[e]);
+    const float x = as_f32(f[e]);
+    hi[e] = (_Float16)x;
+    lo[e] = (_Float16)(x - (float)hi[e]);
   }
 }
 
@@ -551,7 +553,7 @@ __global__ __launch_bounds__(256, WPU == 4 ? 1 : NKB == 1 ? 3 : NKB == 2 ? 2 : 1
     for (int v = 0; v < 16; v++) {
       const int q = q0 + (v >> 2) * 8 + g * 4 + (v & 3);
       if (q >= S) continue;
-      const float val = (q < L) ? o[v] : 0.f;
+      const float val = as_f32((q < L) ? o[v] : 0.f);
       const _Float16 hi = (_Float16)val;
       char *at_ = ob + (unsigned)((q * d + li) * 2);
       *(_Float16 *)at_ = hi;
@@ -817,7 +819,7 @@ __global__ __launch_bounds__(256) void attn_decode_kernel(const float *q, const 
       half8v hi, lo;
 #pragma unroll
       for (int e = 0; e < 8; e++) {
-        const float val = p.acc[e] * inv;
+        const float val = as_f32(p.acc[e] * inv);
         hi[e] = (_Float16)val;
         lo[e] = (_Float16)(val - (float)hi[e]);
       }

@@ -130,6 +130,7 @@ __global__ __launch_bounds__(256) void quantize_kv_i16_kernel(const float *x, lo
       halfNE hi, lo;
 #pragma unroll
       for (int e = 0; e < NE; e++) {
+        v[e] = as_f32(v[e]);
         hi[e] = (_Float16)v[e];
         lo[e] = (_Float16)(v[e] - (float)hi[e]);
       }
@@ -438,8 +439,9 @@ __global__ __launch_bounds__(NWAVES * 64) void dec1_kernel(Dec1Args a) {
     halfNE hi, lo;
 #pragma unroll
     for (int e = 0; e < NE; e++) {
-      hi[e] = (_Float16)y[e];
-      lo[e] = (_Float16)(y[e] - (float)hi[e]);
+      const float x = as_f32(y[e]);
+      hi[e] = (_Float16)x;
+      lo[e] = (_Float16)(x - (float)hi[e]);
     }
     *(halfNE *)(sA + rw * LD + lane * NE) = hi;
     *(halfNE *)(sA + (RW + rw) * LD + lane * NE) = lo;
@@ -661,7 +663,7 @@ __global__ __launch_bounds__(NWAVES * 64) void dec1_kernel(Dec1Args a) {
 #pragma unroll
     for (int t = 0; t < NT; t++) bias[t] = a.b1[n0 + t * 16 + c16];
     results([&](int i, int n, float x) {
-      const float u = fmaxf(x + bias[(n - n0) >> 4], 0.f);
+      const float u = as_f32(fmaxf(x + bias[(n - n0) >> 4], 0.f));
       const _Float16 hi = (_Float16)u;
       sU[i * LD + n] = hi;
       sU[(RW + i) * LD + n] = (_Float16)(u - (float)hi);
@@ -687,8 +689,9 @@ __global__ __launch_bounds__(NWAVES * 64) void dec1_kernel(Dec1Args a) {
     float tail2 = 0.f;
 #pragma unroll
     for (int e = 0; e < NE; e++) {
-      hi[e] = (_Float16)y[e];
-      lo[e] = (_Float16)(y[e] - (float)hi[e]);
+      const float x = as_f32(y[e]);
+      hi[e] = (_Float16)x;
+      lo[e] = (_Float16)(x - (float)hi[e]);
       tail2 += (float)lo[e] * (float)lo[e];
     }
     tail2 = d1_wave_sum(tail2);

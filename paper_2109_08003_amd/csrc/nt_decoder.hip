@@ -136,6 +136,7 @@ __device__ __forceinline__ void dc_store_strip(const floatx16 (&acc)[2], const G
       if (C_F32) {
         *(float *)at_ = val;
       } else {
+        val = as_f32(val);
         const _Float16 hi = (_Float16)val;
         *(_Float16 *)at_ = hi;
         if (e.dst_lo_offset) *((_Float16 *)at_ + e.dst_lo_offset) = (_Float16)(val - (float)hi);
@@ -216,8 +217,9 @@ __device__ __forceinline__ void dc_planes_to_lds(const float (&y)[DC_TM / DC_WAV
     halfNE hi, lo;
 #pragma unroll
     for (int j = 0; j < NE; j++) {
-      hi[j] = (_Float16)y[i][j];
-      lo[j] = (_Float16)(y[i][j] - (float)hi[j]);
+      const float x = as_f32(y[i][j]);
+      hi[j] = (_Float16)x;
+      lo[j] = (_Float16)(x - (float)hi[j]);
     }
     const int R = wave + DC_WAVES * i;
     *(halfNE *)(sh + R * LD + lane * NE) = hi;
@@ -566,8 +568,9 @@ __global__ __launch_bounds__(DC_WAVES * 64) void dec_chain_kernel(DecChainArgs a
       float tail2 = 0.f;
 #pragma unroll
       for (int j = 0; j < NE; j++) {
-        hi[j] = (_Float16)xv[i][j];
-        lo[j] = (_Float16)(xv[i][j] - (float)hi[j]);
+        const float x = as_f32(xv[i][j]);
+        hi[j] = (_Float16)x;
+        lo[j] = (_Float16)(x - (float)hi[j]);
         tail2 += (float)lo[j] * (float)lo[j];
       }
 #pragma unroll

@@ -174,6 +174,7 @@ __device__ __forceinline__ void blocks_epilogue(const floatx16 *acc, const int *
     if (C_F32) {
       *(float *)at_ = val;
     } else {
+      val = as_f32(val);
       const _Float16 hi = (_Float16)val;
       *(_Float16 *)at_ = hi;
       if (e.dst_lo_offset) *((_Float16 *)at_ + e.dst_lo_offset) = (_Float16)(val - (float)hi);
@@ -729,7 +730,7 @@ __global__ __launch_bounds__(256) void skinny_gemm_kernel(const float *A, long l
       }
 #pragma unroll
       for (int c = 0; c < CPL; c++) {
-        const float f[4] = {ra[r][c].x, ra[r][c].y, ra[r][c].z, ra[r][c].w};
+        const float f[4] = {as_f32(ra[r][c].x), as_f32(ra[r][c].y), as_f32(ra[r][c].z), as_f32(ra[r][c].w)};
         half4 hi, lo;
 #pragma unroll
         for (int j = 0; j < 4; j++) {

@@ -183,7 +183,7 @@ __global__ __launch_bounds__(GS_WAVES * 64) void gemm_stream_kernel(const _Float
       halfNE hi, lo;
 #pragma unroll
       for (int j = 0; j < NE; j++) {
-        const float y = gam[j] * ((xv[i][j] - mean[i]) * rstd[i]) + bet[j];
+        const float y = as_f32(gam[j] * ((xv[i][j] - mean[i]) * rstd[i]) + bet[j]);
         hi[j] = (_Float16)y;
         lo[j] = (_Float16)(y - (float)hi[j]);
       }
@@ -367,6 +367,7 @@ __global__ __launch_bounds__(GS_WAVES * 64) void gemm_stream_kernel(const _Float
         if (RB == 2) __builtin_nontemporal_store(val, (float *)at_);
         else *(float *)at_ = val;
       } else {
+        val = as_f32(val);
         const _Float16 hi = (_Float16)val;
         *(_Float16 *)at_ = hi;  // 64 bytes per row and instruction: the other half of the line follows, keep it cached
         if (e.dst_lo_offset) *((_Float16 *)at_ + e.dst_lo_offset) = (_Float16)(val - (float)hi);

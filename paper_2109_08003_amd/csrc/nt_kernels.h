@@ -18,6 +18,15 @@ struct LnEps {
   int l1 = 0;
 };
 #ifdef __HIPCC__
+// A computed value, as the fp32 number it is, before it is split into an fp16 head and the tail against it.  Left alone, the
+// compiler folds the product that formed x into the conversion to fp16 where it can (v_fma_mixlo_f16: one rounding) and
+// converts the rounded x where it packs two heads (v_cvt_pk_f16_f32).  Near the middle between two fp16 numbers (one value in
+// 8,192) the two differ: the head that is stored or multiplied and the head that the tail was formed against are then one fp16
+// step apart, and the pair is good to 2^-11 instead of 2^-22.
+__device__ __forceinline__ float as_f32(float x) {
+  asm("" : "+v"(x));
+  return x;
+}
 // what a row sums over its centred elements, and how the mean of those terms becomes the scale r
 __device__ __forceinline__ float ln_term(float c, int l1) { return l1 ? fabsf(c) : c * c; }
 __device__ __forceinline__ float ln_rscale(float mean_term, LnEps e) {

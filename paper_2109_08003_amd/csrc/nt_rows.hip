@@ -124,10 +124,11 @@ __global__ __launch_bounds__(256) void layer_norm_kernel(const float *x, int M, 
       if (MODE == OUT_F32) {
         ((float *)out)[o] = v[i];
       } else {
-        const _Float16 hi = (_Float16)v[i];
+        const float y = as_f32(v[i]);
+        const _Float16 hi = (_Float16)y;
         ((_Float16 *)out)[o] = hi;
         if (MODE == OUT_PLANES) {
-          const _Float16 lo = (_Float16)(v[i] - (float)hi);
+          const _Float16 lo = (_Float16)(y - (float)hi);
           ((_Float16 *)out)[o + lo_offset] = lo;
           tail2 += (float)lo * (float)lo;
         }

@@ -962,3 +962,34 @@ def test_encoder_attention_at_key_block_edges(nt, oracle, torch_cuda, heads, cli
             err = rel_l2(out[i, : lens[i]], om.encode(src[i]))
             assert err <= (5e-4 if heads == 1 else 5e-5), (S, lens[i], err)
     gm.close()
+
+
+# ------------------------------------------------------------------------------ head and tail of a split value
+@pytest.mark.parametrize("d,n_dec,heads", [(512, 1, 8), (512, 2, 1), (256, 2, 1)])
+def test_heads_and_tails_are_of_the_same_value(nt, oracle, torch_cuda, d, n_dec, heads):
+    """With the identity as the self-attentions' output matrix and as output matrix the logits are the normalised sum of the
+    embedding and the contexts, the contexts read as head + tail by the projection.  Where a tail is formed against another
+    rounding of the value than the head beside it, the sum is a step of fp16 off: 5e-4 at 1/2, 1e-3 at 1, one value in 8,192.
+    Eight heads keep everything else in fp32 or as pairs: 2^-22 per pair and sums of 512 products, 2^-24 sqrt(512) each, about
+    1.5e-6; four times that.  One head has its old keys and values as 16-bit integers, a step of 3.3 / 32767 of a vector's
+    spread, at most half of it per value and layer (5e-5), a score error of the same order; two layers, 2.5e-4."""
+    torch = torch_cuda
+    cfg = nt_synth.model_config("C1", d_model=d, vocab=d, n_enc=0, n_dec=n_dec, max_len=64, n_heads=heads)
+    blob = nt_synth.make_weights(cfg, seed=11, random_affine=True)
+    nt_synth.blob_view(cfg, blob, "W_out")[:] = np.eye(d)
+    for l in range(n_dec):
+        nt_synth.blob_view(cfg, blob, f"dec{l}.self.Wo")[:] = np.eye(d)
+        nt_synth.blob_view(cfg, blob, f"dec{l}.cross.Wo")[:] = 0
+    gm, om = nt.Model(cfg, blob, max_batch_tokens=4096, pipeline_lanes=1), oracle.Model(cfg, blob)
+    src, T = np.array([5, 6, 7], dtype=np.int32), 4
+    tgt = np.random.default_rng(d).integers(4, d, size=(1100, T)).astype(np.int32)
+    want = np.stack([om.teacher_forced(src, t) for t in tgt])
+    for rows in (60, 300, 600, 1100):     # the forms of the decoder layer
+        ids, lens = pad([src] * rows, cfg["pad_id"])
+        gm.encode(torch.from_numpy(ids).cuda(), torch.from_numpy(lens).cuda())
+        logits = torch.empty(rows, T, d, dtype=torch.float32, device="cuda")
+        gm.debug_teacher_forced_logits(torch.from_numpy(tgt[:rows].copy()).cuda(), logits)
+        err = np.abs(logits.cpu().numpy() - want[:rows]) / np.maximum(np.abs(want[:rows]), 1.0)
+        print(f"{rows} rows: worst element {err.max():.1e}")
+        assert err.max() <= (6e-6 if heads == 8 else 2.5e-4), rows
+    gm.close()
