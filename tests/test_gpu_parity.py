@@ -964,6 +964,34 @@ def test_encoder_attention_at_key_block_edges(nt, oracle, torch_cuda, heads, cli
     gm.close()
 
 
+@pytest.mark.parametrize("heads,clip,rows,S", [(1, 0, 150, 200), (1, 0, 40, 200), (1, 0, 70, 129), (1, 0, 300, 100), (1, 0, 60, 22),
+                                               (8, 0, 8, 200), (8, 8, 2, 200), (8, 8, 40, 150), (8, 15, 30, 22), (8, 0, 100, 60)])
+def test_encoder_attention_keeps_22_bits(nt, oracle, torch_cuda, heads, clip, rows, S):
+    """One encoder layer whose value and output matrices are large, so that the output is the context: probabilities of order
+    1 / S, their tails and those of q and v keep their bits in every form (512-wide heads: one wave per unit from 1,024 units
+    on, four below).  Bound: a pair is good to 2^-23 at worst, 7e-8 rms, and the layer multiplies six of them (two normalised
+    rows, q, k, the probabilities with v, the context); fp32 sums of 512 terms in blocks of 16 add 2^-25 sqrt(32) = 1.7e-7 each
+    in three products: 3.4e-7 together, and twice that.  Tails left as fp16 subnormals give 1.2e-6 and more from 60 keys on."""
+    torch = torch_cuda
+    cfg = nt_synth.model_config("C1", d_model=512, vocab=300, n_enc=1, max_len=256, dec_d_ffn=-1, n_heads=heads, rpr_clip=clip)
+    blob = nt_synth.make_weights(cfg, seed=9)
+    for name in ("Wv", "Wo"):
+        nt_synth.blob_view(cfg, blob, f"enc0.self.{name}")[:] *= np.float16(8)
+    gm, om = nt.Model(cfg, blob, max_batch_tokens=32768, pipeline_lanes=1), oracle.Model(cfg, blob)
+    gm.debug_set_encoder_tails(15)
+    rng = np.random.default_rng(S)
+    src = [rng.integers(4, 300, size=n).astype(np.int32) for n in [S] * (rows - 1) + [S - 7]]
+    ids, lens = pad(src, cfg["pad_id"])
+    gm.encode(torch.from_numpy(ids).cuda(), torch.from_numpy(lens).cuda())
+    out = torch.empty(rows, S, 512, dtype=torch.float32, device="cuda")
+    gm.debug_encoder_out(out)
+    out = out.cpu().numpy().astype(np.float64)
+    err = max(rel_l2(out[i, : lens[i]], om.encode(src[i])) for i in sorted({0, rows // 2, rows - 2, rows - 1}))
+    print(f"heads {heads}, clip {clip}, {rows} x {S}: {err:.1e}")
+    assert err <= 7e-7
+    gm.close()
+
+
 # ------------------------------------------------------------------------------ head and tail of a split value
 @pytest.mark.parametrize("d,n_dec,heads", [(512, 1, 8), (512, 2, 1), (256, 2, 1)])
 def test_heads_and_tails_are_of_the_same_value(nt, oracle, torch_cuda, d, n_dec, heads):
