@@ -26,7 +26,10 @@
 // Folded attention (one-layer decoders, batches of up to kDec1FoldRows rows).  q . k = (W y + b) . k = y . (W^T k) + b . k,
 // and Wo (sum p v) + bo = sum p (Wo v + bo).  With the cross keys and values of a sentence multiplied by the two matrices once,
 // when the batch is encoded, and the self values projected by the product of value and output matrix (formed at load, kept as
-// head + tail), a step's attention half has no projection left.  The cross products are formed from the rounded (integer)
+// head + tail), a step's attention half has no projection left.  The self values are cached without their constant, which a
+// softmax passes through unchanged, and with every column divided by its norm: either would set the one scale of a vector's
+// integers for all its elements (eight output biases of 16, or eight output columns 16 times as large, leave 1.3e-5 / 1.1e-4 of
+// the context's norm instead of 2.5e-6 / 2.7e-5).  The cross products are formed from the rounded (integer)
 // vectors, so nothing is rounded that was not before, and kept in fp32: twice the bytes, which is why larger batches, whose
 // time is those bytes, do without (a 4,096-token budget, batches of 36 to 341 rows: 27.5 ms folded up to 256 rows, 26.7 up to
 // 512; batches alone on the chip, 300 / 450 rows of 35 padded tokens: 3.14 -> 2.74 / 3.89 -> 3.52 ms folded; 320 rows of 180:
@@ -346,7 +349,7 @@ __global__ __launch_bounds__(NWAVES * 64) void dec1_kernel(Dec1Args a) {
   typedef D1Part<NE> Part;
   __shared__ __attribute__((aligned(16))) _Float16 sA[2 * RW * LD];               // head rows, then tail rows
   __shared__ __attribute__((aligned(16))) float sZ[RW * ZLD];                     // residual stream
-  __shared__ __attribute__((aligned(16))) float sQ[RW * (D + 8)];                 // cross-attention query, later:
+  __shared__ __attribute__((aligned(16))) float sQ[RW * (D + 8)];                 // FOLD: scales; cross-attention query, later:
   _Float16 *sU = (_Float16 *)sQ;                                                  // FFN hidden state, head rows, then tail rows
   __shared__ float sPart[WR > 1 ? RW * (PARTS - PW) * (NE + 2) * 64 : 1];         // partial softmaxes of the waves pg > 0
   __shared__ float sRel[HEADS ? RW * (D1_MAX_CLIP + 1) * 8 : 1];                  // per row: [distance][head]
@@ -545,6 +548,15 @@ __global__ __launch_bounds__(NWAVES * 64) void dec1_kernel(Dec1Args a) {
   if (pg == 0) {
     float z[NE];
     d1_load<NE>(a.z + (long)r * D + lane * NE, z);
+    if constexpr (FOLD) {  // the bias of the self-attention's output, which no projection adds, and the values' column scales
+      float b[NE], c[NE];
+      d1_load<NE>(a.bo_self + lane * NE, b);
+      d1_load<NE>(a.fold_scale + lane * NE, c);
+#pragma unroll
+      for (int e = 0; e < NE; e++) z[e] += b[e];
+#pragma unroll
+      for (int e = 0; e < NE; e += 4) *(float4 *)(sQ + rw * ZLD + lane * NE + e) = make_float4(c[e], c[e + 1], c[e + 2], c[e + 3]);
+    }
 #pragma unroll
     for (int e = 0; e < NE; e += 4) *(float4 *)(sZ + rw * ZLD + lane * NE + e) = make_float4(z[e], z[e + 1], z[e + 2], z[e + 3]);
   }
@@ -557,6 +569,11 @@ __global__ __launch_bounds__(NWAVES * 64) void dec1_kernel(Dec1Args a) {
     float *z = sZ + rw * ZLD + lane * NE;
 #pragma unroll
     for (int e = 0; e < NE; e++) z[e] += ctx[e];
+  };
+  auto add_self_context = [&](const float (&ctx)[NE]) {
+    float *z = sZ + rw * ZLD + lane * NE;
+#pragma unroll
+    for (int e = 0; e < NE; e++) z[e] += ctx[e] * sQ[rw * ZLD + lane * NE + e];
   };
   D1Rel rel;
   if constexpr (HEADS) {
@@ -603,7 +620,7 @@ __global__ __launch_bounds__(NWAVES * 64) void dec1_kernel(Dec1Args a) {
         d1_quantize_store<NE>(vx, dst + D, a.self_sc + p * 2 + 1, lane);
       }
     }
-    if constexpr (FOLD) attend(sb, std::false_type{}, q, a.self_kv, a.self_sc, pos0, n_self > 0 ? n_self - 1 : 0, rel, st, add_context);
+    if constexpr (FOLD) attend(sb, std::false_type{}, q, a.self_kv, a.self_sc, pos0, n_self > 0 ? n_self - 1 : 0, rel, st, add_self_context);
     else attend(sb, std::false_type{}, q, a.self_kv, a.self_sc, pos0, n_self > 0 ? n_self - 1 : 0, rel, st, store_planes);
   }
   // ---- output projection + residual, LayerNorm, cross-attention query ----

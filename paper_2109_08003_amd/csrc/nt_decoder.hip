@@ -412,14 +412,14 @@ __global__ __launch_bounds__(DC_WAVES * 64) void dec_qkv_kernel(DecQkvArgs a, in
     for (int p = 1; p < DC_WAVES; p++) t += red[(p * 8 + wave) * 64 + lane];
     const GemmEpilogue &e = a.e;
     const int nbase = strip * 64 + (wave >> 2) * 32, n = nbase + li;
-    const float bias = vo ? a.b_vo[n - 2 * K] : e.bias ? e.bias[n] : 0.f, scl = n < e.scale_cols ? e.scale : 1.f;
+    const float bias = !vo && e.bias ? e.bias[n] : 0.f, scl = n < e.scale_cols ? e.scale : 1.f;
     const bool first = nbase < e.n_split;
     float *dst = first ? (float *)e.dst0 + n : (float *)e.dst1 + (n - e.n_split);
     const long ld = first ? e.ld0 : e.ld1;
 #pragma unroll
     for (int v = 0; v < 4; v++) {
       const int r = m0 + (wave & 3) * 8 + g * 4 + v;
-      if (r < M) dst[(long)r * ld] = vo ? t[v] * a.vo_inv + bias : (t[v] + bias) * scl;
+      if (r < M) dst[(long)r * ld] = vo ? t[v] * kFoldInv : (t[v] + bias) * scl;
     }
   } else {
     if (!have) return;

@@ -127,9 +127,9 @@ struct Attn {
   const _Float16 *Wo = nullptr;    // [d][d]
   // the same matrices in MFMA fragment order (streaming GEMM), nullptr where the shape is not supported
   const _Float16 *Wqkv_p = nullptr, *Wq_p = nullptr, *Wkv_p = nullptr, *Wo_p = nullptr;
-  const _Float16 *Wvo_p = nullptr;      // head | tail of 1 / vo_inv * Wv Wo (folded self values)
+  const _Float16 *Wvo_p = nullptr;      // head | tail of Wv Wo, columns scaled (folded self values)
   const float *bvo = nullptr;           // bv Wo + bo
-  float vo_inv = 1.f;
+  const float *vo_scale = nullptr;      // what the columns were divided by
   const _Float16 *Wq_back_p = nullptr;  // Wq the other way round (its product with a key): folded cross caches
   const float *bqkv = nullptr, *bq = nullptr, *bkv = nullptr, *bo = nullptr;
   const float *rk = nullptr;       // [2c+1][dh]
@@ -654,11 +654,11 @@ int nt_load_weights(const nt_config *cfg, const void *h_blob_fp16, size_t blob_b
       }
       fused(1, 2, (const void **)&a.Wkv, (const void **)&a.bkv, (const void **)&a.Wkv_p);
     }
-    if (fold && !cross) {  // value matrix times output matrix, in double; scaled by a power of two so that the tail keeps its bits
+    if (fold && !cross) {  // value matrix times output matrix, in double, each column divided by its norm
       std::vector<double> prod((size_t)d * d, 0.0), wo((size_t)d * d), bias((size_t)d);
       for (int64_t i = 0; i < (int64_t)d * d; i++) wo[(size_t)i] = (double)(float)W[3][i];
       for (int j = 0; j < d; j++) bias[(size_t)j] = (double)(float)b[3][j];
-      double largest = 0.0;
+      std::vector<double> norm2((size_t)d, 0.0), scale((size_t)d, 1.0);
       for (int i = 0; i <= d; i++) {  // row d: the bias
         double *row = i < d ? &prod[(size_t)i * d] : bias.data();
         for (int k = 0; k < d; k++) {
@@ -666,16 +666,14 @@ int nt_load_weights(const nt_config *cfg, const void *h_blob_fp16, size_t blob_b
           const double *o = &wo[(size_t)k * d];
           for (int j = 0; j < d; j++) row[j] += x * o[j];
         }
-        for (int j = 0; i < d && j < d; j++) largest = std::max(largest, std::fabs(row[j]));
+        for (int j = 0; i < d && j < d; j++) norm2[(size_t)j] += row[j] * row[j];
       }
-      int exp2 = 0;
-      if (largest > 0.0) (void)std::frexp(largest, &exp2);
-      const double scale = std::ldexp(1.0, 14 - exp2);  // the largest entry between 2^13 and 2^14
-      a.vo_inv = (float)(1.0 / scale);
+      for (int j = 0; j < d; j++)
+        if (norm2[(size_t)j] > 0.0) scale[(size_t)j] = (double)(float)std::sqrt(norm2[(size_t)j]);
       std::vector<_Float16> rows((size_t)2 * d * d);  // [out][in], head then tail
       for (int i = 0; i < d; i++)
         for (int j = 0; j < d; j++) {
-          const double x = prod[(size_t)i * d + j] * scale;
+          const double x = prod[(size_t)i * d + j] / scale[(size_t)j] / (double)nt::kFoldInv;
           const _Float16 hi = (_Float16)x;
           rows[(size_t)j * d + i] = hi;
           rows[(size_t)(d + j) * d + i] = (_Float16)(x - (double)(float)hi);
@@ -686,6 +684,9 @@ int nt_load_weights(const nt_config *cfg, const void *h_blob_fp16, size_t blob_b
       const size_t ob = pk.reserve((size_t)d * 4);
       for (int j = 0; j < d; j++) ((float *)(pk.img.data() + ob))[j] = (float)bias[(size_t)j];
       fixes.push_back({ob, (const void **)&a.bvo});
+      const size_t os = pk.reserve((size_t)d * 4);
+      for (int j = 0; j < d; j++) ((float *)(pk.img.data() + os))[j] = (float)scale[(size_t)j];
+      fixes.push_back({os, (const void **)&a.vo_scale});
     }
     fused(3, 1, (const void **)&a.Wo, (const void **)&a.bo, (const void **)&a.Wo_p);
     if (rpr && c > 0) put_f32(br.take((int64_t)(2 * c + 1) * dh), (2 * c + 1) * dh, (const void **)&a.rk);
@@ -1118,7 +1119,7 @@ int decode_step(nt_model *m, DecodeCursor &cu, hipStream_t s) {
           }
           q.sb.gamma = L.ln1.g; q.sb.beta = L.ln1.b; q.sb.eps = lne;
           q.Wp = L.self.Wqkv_p; q.N = 3 * d; q.e = e; q.shape_rows = rows_for_choice;
-          if (m->folded) { q.Wvo_p = L.self.Wvo_p; q.vo_inv = L.self.vo_inv; q.b_vo = L.self.bvo; }
+          if (m->folded) q.Wvo_p = L.self.Wvo_p;
           KT(K_GEMM_DEC_QKV, gemm_bytes(Rd, d, 3 * d, false) + (eos ? 0.0 : rows_prev * (partials_prev * 8.0 + 4)) + Rd * dd * 6,
              6 * Rd * dd * dd, nt::launch_dec_qkv(q, s));
         } else if ((rc = dec_gemm(K_GEMM_DEC_QKV, m->z, d, L.self.Wqkv, L.self.Wqkv_p, 3 * d, &L.ln1, e))) return rc;
@@ -1130,7 +1131,7 @@ int decode_step(nt_model *m, DecodeCursor &cu, hipStream_t s) {
           at.rows = R; at.shape_rows = rows_for_choice; at.origin = origin; at.eps = lne; at.z = m->z; at.write_z = !to_final;
           at.q = m->q32; at.kv_new = m->kv_new; at.self_kv = m->self_kv[l]; at.self_sc = m->self_sc[l];
           at.self_positions = T; at.n_keys = t + 1; at.heads = heads_layer ? H : 1; at.rk = L.self.rk; at.clip = c.rpr_clip;
-          at.Wo_self = L.self.Wo_p; at.bo_self = L.self.bo; at.Wq = L.cross.Wq_p; at.bq = L.cross.bq; at.Wo_cross = L.cross.Wo_p;
+          at.Wo_self = L.self.Wo_p; at.bo_self = m->folded ? L.self.bvo : L.self.bo; at.fold_scale = L.self.vo_scale; at.Wq = L.cross.Wq_p; at.bq = L.cross.bq; at.Wo_cross = L.cross.Wo_p;
           at.bo_cross = L.cross.bo; at.q_scale = qscale; at.ln2 = nt::GemmLayerNorm{L.ln2.g, L.ln2.b, lne};
           at.folded = m->folded; at.cross_positions = S; at.len = m->len;
           at.cross_kv = m->folded ? (const void *)m->cross_fold[l] : m->cross[l];

@@ -257,12 +257,14 @@ struct DecQkvArgs {
   int N;
   GemmEpilogue e;
   // optional, up to 512 rows: the value columns (2 d .. 3 d - 1) come from this matrix instead, head and tail (fragment order,
-  // d rows each) of scale * W_v W_o, and leave as product * vo_inv + b_vo (folded self values, see Dec1Args)
+  // d rows each) of W_v W_o with its columns scaled, and leave as product * kFoldInv without a bias (folded self values, see
+  // Dec1Args)
   const _Float16 *Wvo_p;
-  float vo_inv;
-  const float *b_vo;
   int shape_rows;  // row count that selects the kernel form (0: rows_now), as in Dec1Args
 };
+// Folded self values: column j of W_v W_o is divided by its norm fold_scale[j], and multiplied by 1 / kFoldInv so that its
+// fp16 tail keeps its bits.
+constexpr float kFoldInv = 1.f / 16384.f;
 hipError_t launch_dec_qkv(const DecQkvArgs &a, hipStream_t s);
 // One launch for: z' = A * W1^T + b1 + z (A: head/tail planes [M][lda], W1 [K][K] in fragment order; z' is written
 // back to z if write_z), y = LayerNorm(z'), then either (W2p == nullptr) y as head/tail planes at h_hi /
@@ -386,7 +388,11 @@ struct Dec1Args {
   GemmLayerNorm ln2;
   const void *cross_kv;  // integers with scales in cross_sc, or (folded) fp32 [position][2 d] with one constant per key in
   const float *cross_sc; // cross_sc: keys multiplied by the query matrix and scale, values by the output matrix (+ bias)
-  int folded;            // the self values (kv_new, self cache) then are already multiplied by the output matrix (+ bias), too
+  // folded: the self values (kv_new, self cache) then are already multiplied by the output matrix, too, column j divided by
+  // fold_scale[j]; bo_self is the whole constant, b_v W_o + b_o.  Neither a bias nor the columns' different sizes may enter the
+  // cache: its integers have one scale per vector, which the largest element sets for all
+  int folded;
+  const float *fold_scale;
   long cross_positions;
   const int32_t *len;    // keys of each cache row
   // FFN of width d (W1 == nullptr: none, or not part of this launch)

@@ -1021,3 +1021,41 @@ def test_heads_and_tails_are_of_the_same_value(nt, oracle, torch_cuda, d, n_dec,
         print(f"{rows} rows: worst element {err.max():.1e}")
         assert err.max() <= (6e-6 if heads == 8 else 2.5e-4), rows
     gm.close()
+
+
+@pytest.mark.parametrize("ffn", [0, 512])
+@pytest.mark.parametrize("what", ["plain", "bias", "columns"])
+def test_folded_self_values_are_as_exact_as_the_others(nt, oracle, torch_cuda, what, ffn):
+    """Batches of up to 512 rows cache the self values with the output matrix in them.  A few outputs that are much larger than
+    the rest, by their bias or by their column of the matrix, must not cost the rest their precision: the state of a step that
+    attends to three cached keys (the identity as output matrix shows it) has the error of batches that are not folded.  Bound:
+    integers of absmax / 32767 are off by 3.4 / 32767 / sqrt(12) = 3e-5 of a value's spread, a little less after averaging over
+    the keys and as much again for the scores; the outputs left out are the eight large ones, which the normalisation
+    divides by as well."""
+    torch = torch_cuda
+    d = 512
+    cfg = nt_synth.model_config("C1", vocab=d, n_enc=0, max_len=64, dec_d_ffn=ffn or -1)
+    blob = nt_synth.make_weights(cfg, seed=12, random_affine=True)
+    nt_synth.blob_view(cfg, blob, "W_out")[:] = np.eye(d)
+    nt_synth.blob_view(cfg, blob, "dec0.cross.Wo")[:] = 0
+    large = np.arange(0, d, 64)
+    if what == "bias":
+        nt_synth.blob_view(cfg, blob, "dec0.self.bo")[large] = 16
+    if what == "columns":
+        nt_synth.blob_view(cfg, blob, "dec0.self.Wo")[:, large] *= np.float16(16)
+    gm, om = nt.Model(cfg, blob, max_batch_tokens=4096, pipeline_lanes=1), oracle.Model(cfg, blob)
+    src, T = np.array([5, 6, 7], dtype=np.int32), 4
+    tgt = np.random.default_rng(3).integers(4, d, size=(600, T)).astype(np.int32)
+    want = np.stack([om.teacher_forced(src, t) for t in tgt])
+    rest = np.setdiff1d(np.arange(d), large)
+    rms = {}
+    for rows in (60, 600):                # folded, not folded
+        ids, lens = pad([src] * rows, cfg["pad_id"])
+        gm.encode(torch.from_numpy(ids).cuda(), torch.from_numpy(lens).cuda())
+        logits = torch.empty(rows, T, d, dtype=torch.float32, device="cuda")
+        gm.debug_teacher_forced_logits(torch.from_numpy(tgt[:rows].copy()).cuda(), logits)
+        err, ref = (logits.cpu().numpy() - want[:rows])[:, 1:, rest], want[:rows][:, 1:, rest]
+        rms[rows] = float(np.sqrt((err ** 2).mean() / (ref ** 2).mean()))
+    print(f"{what}: folded {rms[60]:.1e}, not folded {rms[600]:.1e}")
+    assert max(rms.values()) <= 4e-5
+    gm.close()
