@@ -438,6 +438,9 @@ __global__ __launch_bounds__(GS_WAVES * 64) void gemm_stream_kernel(const _Float
   }
 }
 
+// workgroups per row tile with 32-column strips: four strips each, or two where N is an odd multiple of 64
+static int gs_narrow_groups(int N) { return N % 128 == 0 ? N / 128 : N / 64; }
+
 template <int RB, int K, bool C_F32, bool LN, bool TAIL, int NC = 1, int NB = 2>
 static hipError_t gs_launch(const _Float16 *A, const _Float16 *A_lo, long lda, int M, const _Float16 *Wp, int N,
                             const GemmEpilogue &e, const GemmLayerNorm &ln, hipStream_t s) {
@@ -460,17 +463,20 @@ static hipError_t gs_launch(const _Float16 *A, const _Float16 *A_lo, long lda, i
       break;
     }
   if (NC > 1) col_groups = NS / GS_WAVES;  // several passes: exactly one strip per wave
-  if (NB == 1) col_groups = NS % 4 == 0 ? NS / 4 : NS / 2;  // N % 64 == 0: two or four strips per workgroup
+  if (NB == 1) col_groups = gs_narrow_groups(N);
   hipLaunchKernelGGL(kern, dim3(row_tiles * col_groups), dim3(GS_WAVES * 64), lds, s, A, A_lo, lda, M, Wp, N, col_groups, e,
                      ln);
   return hipGetLastError();
 }
 
-// 32-column strips, four to a workgroup, while that is one round of workgroups: there the launch is one wave's latency (22 rows,
+// 32-column strips, two or four to a workgroup, while that is one round of workgroups: there the launch is one wave's latency (22 rows,
 // N = 1536 / 512: 10.1 / 7.4 us against 15.7 / 13.4; a 30 + 6 layer model at an 8,192-token budget 138 against 158 ms).
 // Beyond, filling the same rows for more workgroups costs the other lanes more than the launch gains (up to two rounds:
 // 127.7 against 125.3 ms on the 8-head model at 16,384 tokens).
-static bool gs_narrow(int M, int N) { return (long)((M + 31) / 32) * (N / 128) <= 256; }
+// N = 192 (three groups) at 3,200 / 8,000 rows, a whole encoder: 0.45 / 0.70 ms narrow, 0.40 / 0.62 wide.  A matrix of 64 columns is narrow at any
+// number of rows: its one wide strip leaves one of eight waves working, two narrow ones two (19,200 / 64,000 rows, a whole
+// encoder: 1.36 / 3.52 ms narrow, 1.45 / 3.64 wide).
+static bool gs_narrow(int M, int N) { return N == 64 || (long)((M + 31) / 32) * gs_narrow_groups(N) <= 256; }
 
 template <bool LN>
 static hipError_t gs_dispatch(bool c_f32, const _Float16 *A, const _Float16 *A_lo, long lda, const _Float16 *Wp, int M,

@@ -32,6 +32,7 @@ void **__hipRegisterFatBinary(const void *data) { return &module_handle; }
 void __hipUnregisterFatBinary(void **m) {}
 void __hipRegisterFunction(void **m, const void *f, char *df, const char *name, unsigned limit, void *t, void *b, dim3 *bd,
                            dim3 *gd, int *ws) {
+  if (strncmp(name, "_ZN2nt", 6)) return; /* other libraries' kernels */
   if (n_funcs < MAX_FUNCS) funcs[n_funcs].f = f, funcs[n_funcs].name = strdup(name), n_funcs++;
 }
 void __hipRegisterVar(void **m, void *var, char *hv, char *dv, int ext, size_t size, int constant, int global) {}

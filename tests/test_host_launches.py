@@ -3,6 +3,7 @@ load puts on the device, and what happens when the device reports an error.  Eac
 has to be loaded before the library."""
 import json
 import os
+import re
 import subprocess
 import sys
 
@@ -90,3 +91,21 @@ print(json.dumps((size(n_enc=3) - size(n_enc=2), size(n_enc=1, n_dec=3) - size(n
     caches = positions[0] * 2 * d * 2 + positions[1] * 2 * d * (2 if i16 else 4) + (8 * sum(positions) if i16 else 0)
     assert abs(enc - attention - ffn) <= 256 * parts, enc
     assert abs(dec - 2 * attention - ffn - caches) <= 256 * parts, dec
+
+
+def test_narrow_projections_are_one_round_of_workgroups(host):
+    """The form with 32-column strips is for launches of at most 256 workgroups, whatever the matrix's width (an FFN of 192
+    columns, an odd multiple of 64, has three groups of them), and for the matrix with one wide strip, of 64 columns."""
+    got = host("""
+out = []
+for ffn in (0, 64, 192, 256, 2048):
+    model = load(config(n_heads=8, d_ffn=ffn, n_enc=1), tokens=40000)
+    for rows in (1, 85, 86, 100, 250, 640, 1000):
+        out += [(ffn, rows, n, b) for n, b in encode(model, rows, 32) if "gemm_stream_kernel" in n]
+print(json.dumps(out))
+""")
+    narrow = [x for x in got if re.search(r"gemm_stream_kernelILi\d+ELi\d+ELb.ELb.ELb.ELi\d+ELi1EE", x[2])]
+    assert len(narrow) > 10 and len(got) - len(narrow) > 10
+    assert max(blocks for ffn, _, _, blocks in narrow if ffn != 64) <= 256
+    first = lambda ffn: {rows for f, rows, name, _ in narrow if f == ffn and "Li512ELb0ELb1" in name}  # fp16 out: the FFN's first matrix
+    assert first(192) == {1, 85} and first(64) == {1, 85, 86, 100, 250, 640, 1000} and first(2048) == {1}
