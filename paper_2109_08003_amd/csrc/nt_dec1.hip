@@ -3,8 +3,9 @@
 // Between the fused Q | K | V projection and the output layer a decoder row passes through
 //   self-attention -> output projection + residual -> LayerNorm -> query projection -> cross-attention ->
 //   output projection + residual -> [LayerNorm -> FFN + residual ->] final LayerNorm,
-// and no step of it reads another row.  A workgroup of eight or sixteen waves carries 2 to 16 rows through the whole chain (the
-// paper's cure for many small dependent nodes is fewer, larger ones, Sec. 3.3 "Graph Optimization"); what passes from one
+// and no step of it reads another row.  A workgroup carries its rows through the whole chain - 2 with eight waves, 4 to 16 with
+// sixteen, 1 with four where nothing is left but attention (the paper's cure for many small dependent nodes is fewer, larger
+// ones, Sec. 3.3 "Graph Optimization"); what passes from one
 // phase to the next stays in the LDS.  As four launches (two attention kernels with a wave per row, two kernels that
 // streamed the 512 KB matrices for 32-row tiles) the chain took 24 + 24 + 28 + 16 us at 1,900 rows and 38 us at one row,
 // most of it the start and end of launches and, in the projections, 60 workgroups or fewer on 256 CUs.
@@ -331,7 +332,7 @@ struct D1HeadBlock {
     a.m = mn;
   }
 };
-// D: model width.  RW: rows per workgroup (8 / RW waves each).  PARTS: partial softmaxes per row.  IND: row r uses cache
+// D: model width.  RW: rows per workgroup, NWAVES / RW waves each.  PARTS: partial softmaxes per row.  IND: row r uses cache
 // row origin[r] (< 0: no row, zero context).  FFN: the layer's FFN (of width D) is part of the chain.  FOLD: the cross cache
 // holds folded fp32 vectors.  HEADS: eight heads of 64 columns, self cache fp32, cross cache fp16, optional relative keys.
 template <int D, int RW, int NWAVES, int PARTS, bool IND, bool FFN, bool FOLD, bool HEADS>
@@ -742,10 +743,19 @@ static hipError_t d1_launch(const Dec1Args &a, hipStream_t s) {
       return hipGetLastError();
     }
   }
-  if (shape >= 1024) NT_D1(16, 16, 1, false);
-  else if (shape <= (HEADS ? 64 : 512)) NT_D1(2, 8, 4, false);
-  else if (HEADS && shape <= 256) NT_D1(4, 16, 4, false);
-  else NT_D1(8, 16, 4, false);
+  if (shape >= 1024) {
+    NT_D1(16, 16, 1, false);
+  } else if (shape <= (HEADS ? 64 : 512)) {
+    NT_D1(2, 8, 4, false);
+  } else {
+    if constexpr (HEADS) {
+      if (shape <= 256) {
+        NT_D1(4, 16, 4, false);
+        return hipGetLastError();
+      }
+    }
+    NT_D1(8, 16, 4, false);
+  }
 #undef NT_D1
   return hipGetLastError();
 }

@@ -109,3 +109,24 @@ print(json.dumps(out))
     assert max(blocks for ffn, _, _, blocks in narrow if ffn != 64) <= 256
     first = lambda ffn: {rows for f, rows, name, _ in narrow if f == ffn and "Li512ELb0ELb1" in name}  # fp16 out: the FFN's first matrix
     assert first(192) == {1, 85} and first(64) == {1, 85, 86, 100, 250, 640, 1000} and first(2048) == {1}
+
+
+def test_decoder_layer_forms_are_all_in_use(host):
+    """Every decoder layer kernel in the library's code object is launched by some row count of some model (those that reach
+    their rows through a row map are the EOS mode's, whose loop waits for the device: the same forms)."""
+    used = host("""
+out = set()
+for kw in (dict(), dict(dec_d_ffn=512), dict(n_heads=8), dict(n_dec=2), dict(n_dec=2, dec_d_ffn=512), dict(d_model=256),
+           dict(d_model=256, dec_d_ffn=256), dict(d_model=256, n_dec=2), dict(d_model=256, n_dec=2, dec_d_ffn=256)):
+    model = load(config(**dict(kw, n_enc=1)), tokens=4096)
+    a = np.zeros(4096, dtype=np.int32)
+    for rows in (1, 64, 65, 256, 257, 512, 513, 1023, 1024, 2000):
+        encode(model, rows, 2)
+        nt.binding._check(nt.binding.lib().nt_decode_greedy(model._h, rows, 1, None, a.ctypes.data, None))
+        out |= {n for n, _ in launches() if "dec1_kernel" in n}
+print(json.dumps(sorted(out)))
+""")
+    with open(os.path.join(ROOT, "paper_2109_08003_amd", "libnt.so"), "rb") as f:
+        built = {n.decode() for n in re.findall(rb"_ZN2nt11dec1_kernelI(?:Li\d+E)+(?:Lb[01]E)+EEvNS_8Dec1ArgsE", f.read())}
+    rows_direct = {n for n in built if re.search(r"Li\d+ELb0E", n)}
+    assert len(used) > 10 and rows_direct == set(used)
