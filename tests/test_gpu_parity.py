@@ -1059,3 +1059,30 @@ def test_folded_self_values_are_as_exact_as_the_others(nt, oracle, torch_cuda, w
     print(f"{what}: folded {rms[60]:.1e}, not folded {rms[600]:.1e}")
     assert max(rms.values()) <= 4e-5
     gm.close()
+
+
+@pytest.mark.parametrize("rows,S", [(512, 64), (512, 65), (513, 63), (256, 128), (256, 129), (163, 201), (164, 201)])
+def test_batches_at_the_line_of_the_folded_caches(nt, oracle, torch_cuda, rows, S):
+    """Batches of exactly 512 rows or 32,768 tokens, whose folded caches fill their part of the arena to the last position, and
+    the next larger ones without: logits of the first, last and middle rows over five steps against the oracle.  Bound: all
+    tails on, the 16-bit integers of the caches leave 3e-5 of a key or value (see above), about as much of a logit; five times that."""
+    torch = torch_cuda
+    cfg = nt_synth.model_config("C1", vocab=300, n_enc=1)
+    blob = nt_synth.make_weights(cfg, seed=21, random_affine=True)
+    gm, om = nt.Model(cfg, blob, max_batch_tokens=34000, pipeline_lanes=1), oracle.Model(cfg, blob)
+    gm.debug_set_encoder_tails(15)
+    rng = np.random.default_rng(rows + S)
+    lens = np.sort(np.concatenate([[S, S], rng.integers(1, S + 1, size=rows - 3), [1]]))[::-1]
+    lens = np.concatenate([lens[:-1], [S]])          # the last row reaches the batch's last position
+    src = [rng.integers(4, 300, size=n).astype(np.int32) for n in lens]
+    tgt = rng.integers(4, 300, size=(rows, 5)).astype(np.int32)
+    ids, ln = pad(src, cfg["pad_id"])
+    gm.encode(torch.from_numpy(ids).cuda(), torch.from_numpy(ln).cuda())
+    logits = torch.empty(rows, 5, 300, dtype=torch.float32, device="cuda")
+    gm.debug_teacher_forced_logits(torch.from_numpy(tgt).cuda(), logits)
+    gm.check_device_flags()
+    logits = logits.cpu().numpy().astype(np.float64)
+    err = max(rel_l2(logits[i], om.teacher_forced(src[i], tgt[i])) for i in (0, 1, rows // 2, rows - 2, rows - 1))
+    print(f"{rows} x {S}: {err:.1e}")
+    assert err <= 1.5e-4
+    gm.close()

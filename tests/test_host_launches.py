@@ -130,3 +130,20 @@ print(json.dumps(sorted(out)))
         built = {n.decode() for n in re.findall(rb"_ZN2nt11dec1_kernelI(?:Li\d+E)+(?:Lb[01]E)+EEvNS_8Dec1ArgsE", f.read())}
     rows_direct = {n for n in built if re.search(r"Li\d+ELb0E", n)}
     assert len(used) > 10 and rows_direct == set(used)
+
+
+def test_folded_caches_end_at_512_rows_and_32768_tokens(host):
+    """The decoder layer's form with folded caches, on both sides of both lines."""
+    got = host("""
+model, out = load(config(n_enc=1), tokens=40000), []
+a = np.zeros(40000, dtype=np.int32)
+for rows, length in ((512, 1), (513, 1), (512, 64), (512, 65), (256, 128), (256, 129), (163, 201), (164, 201)):
+    encode(model, rows, length)
+    stub.stub_clear()
+    nt.binding._check(nt.binding.lib().nt_decode_greedy(model._h, rows, 1, None, a.ctypes.data, None))
+    out.append([n for n, _ in launches() if "dec1_kernel" in n])
+print(json.dumps(out))
+""")
+    folded = [bool(re.search(r"Lb[01]ELb0ELb1ELb0EEE", names[0])) for names in got]
+    assert [len(names) for names in got] == [1] * 8
+    assert folded == [True, False, True, False, True, False, True, False]
