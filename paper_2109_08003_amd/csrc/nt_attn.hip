@@ -657,9 +657,13 @@ hipError_t launch_enc_attention(const void *qkv, bool f32, const int32_t *len, v
   if (B <= 0 || S <= 0) return hipSuccess;
   if (clip > MAX_CLIP) return hipErrorInvalidValue;
   // The wave-per-tile kernel where its registers reach (seven key blocks; eight spill), for the two head widths in use.  Against
-  // the tiled kernel, whose LDS leaves one workgroup per CU: 320 sentences of 100 to 200 tokens, one head 476 -> 291 us a
-  // layer; eight heads with relative keys, 8,192 tokens in short sentences, 100 -> 44 us.  With fewer than 256 units (a lone
-  // long sentence) the tiled kernel's four waves share the keys of a unit and it stays.
+  // the tiled kernel, whose LDS leaves one workgroup per CU: 16 sentences of 200 tokens, eight heads with relative keys
+  // (896 units) 72 -> 28 us, 320 sentences of 100 to 200 tokens, one head, 476 -> 291 us.  Below 256 units both are one round,
+  // and the tiled kernel's four waves share the keys of a unit: 200 tokens, one sentence, one head 50 us tiled and 77 by waves
+  // (224 units 66 and 82), eight heads 17 and 23 (224 units 19 and 23).  With relative keys that does not make up for their
+  // products with every query, which the tiled kernel forms in plain fp32: one sentence of 10 / 32 / 64 / 128 / 150 / 200
+  // tokens, eight heads, 13.7 / 14.2 / 15.9 / 19.4 / 22.3 / 25.6 us tiled and 6.3 / 7.8 / 10.4 / 16.5 / 19.5 / 26.0 by waves, so
+  // those go there at any unit count.
   const long units = (long)B * heads * ((S + 31) / 32);
   if (f32 && rk && d / heads == 64 && clip <= 15 && S <= 224)
     return enc_attention_wave_launch<64, false, true>((const float *)qkv, len, (_Float16 *)ctx, ctx_lo_offset, B, S, d, heads, s, nullptr, rk, clip);

@@ -41,6 +41,9 @@
 // 45 rows 26 and 17.8; with the self values too, one sentence 1119 -> 1012 us, 45 sentences 3742 -> 3207 us, 8 sentences of
 // the 256-wide model 1253 -> 1175 us, a 4,096-token budget 28.0 -> 27.5 ms.
 //
+// Registers: three forms spill some of theirs - eight heads with two rows (8, 36 bytes of scratch per lane) and with eight rows
+// (17, 72 bytes), folded with the FFN at d = 512 (70, 152 bytes).  The others use no scratch.
+//
 // Measured per step of 1,900 / 45 / 1 rows, alone: 92 / 42 / 38 us as four launches, 71 / 30 / 25 us as one.
 //
 // Eight heads of 64 (HEADS): the caches stay fp32 (self) and fp16 (cross); a vector still lies across one wave instruction, a
