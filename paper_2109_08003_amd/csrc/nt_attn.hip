@@ -14,6 +14,7 @@
 // Relative position keys (Sec. 2.1, clip distance c): score_ij += q_i . rk[clamp(j-i,-c,c)+c].
 #include <math.h>
 
+#include <mutex>
 #include <type_traits>
 
 #include "nt_kernels.h"
@@ -272,14 +273,14 @@ __global__ __launch_bounds__(256) void enc_attention_kernel(const void *qkv_, co
 template <int DH, bool F32>
 static hipError_t enc_attention_launch(const void *qkv, const int32_t *len, void *ctx, long ctx_lo_offset, int B, int S,
                                        int d, int heads, const float *rk, int clip, hipStream_t s) {
-  static size_t configured = 0;
-  size_t lds = enc_attention_lds_bytes(S, DH, F32);
-  if (lds > configured) {
-    hipError_t e = hipFuncSetAttribute((const void *)enc_attention_kernel<DH, F32>,
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e != hipSuccess) return e;
-    configured = lds;
-  }
+  // the limit is raised once, to all there is: several host threads get here with sentences of different lengths
+  static std::once_flag once;
+  static hipError_t attr_err = hipSuccess;
+  std::call_once(once, [] {
+    attr_err = hipFuncSetAttribute((const void *)enc_attention_kernel<DH, F32>, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+  });
+  if (attr_err != hipSuccess) return attr_err;
+  const size_t lds = enc_attention_lds_bytes(S, DH, F32);
   dim3 grid((S + QT - 1) / QT, heads, B), block(256);
   hipLaunchKernelGGL((enc_attention_kernel<DH, F32>), grid, block, lds, s, qkv, len, ctx, ctx_lo_offset, S, d, rk, clip);
   return hipGetLastError();

@@ -147,3 +147,21 @@ print(json.dumps(out))
     folded = [bool(re.search(r"Lb[01]ELb0ELb1ELb0EEE", names[0])) for names in got]
     assert [len(names) for names in got] == [1] * 8
     assert folded == [True, False, True, False, True, False, True, False]
+
+
+def test_lanes_with_different_sentence_lengths_share_a_kernel(host):
+    """Four threads meet the tiled encoder attention for the first time with four lengths: none may lower the LDS limit under
+    another's launches."""
+    rc, message = host("""
+model = load(config(n_enc=4), lanes=4)
+C.c_int.in_dll(stub, "stub_slow_limits").value = 1
+lens = np.array([199, 190, 150, 140, 135, 134, 131, 130])
+offsets = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+try:
+    model.translate_batch(np.full(offsets[-1], 5, dtype=np.int32), offsets, 200, stream=Stream)
+    assert any("enc_attention_kernel" in n for n, _ in launches())
+    print(json.dumps((0, "")))
+except nt.NtError as e:
+    print(json.dumps((e.code, str(e))))
+""")
+    assert rc == 0, message
