@@ -659,7 +659,7 @@ hipError_t launch_enc_attention(const void *qkv, bool f32, const int32_t *len, v
   if (clip > MAX_CLIP) return hipErrorInvalidValue;
   // The wave-per-tile kernel where its registers reach (seven key blocks; eight spill), for the two head widths in use.  Against
   // the tiled kernel, whose LDS leaves one workgroup per CU: 16 sentences of 200 tokens, eight heads with relative keys
-  // (896 units) 72 -> 28 us, 320 sentences of 100 to 200 tokens, one head, 476 -> 291 us.  Below 256 units both are one round,
+  // (896 units) 72 -> 28 us, 320 sentences of 100 to 200 tokens, one head, 476 -> 310 us.  Below 256 units both are one round,
   // and the tiled kernel's four waves share the keys of a unit: 200 tokens, one sentence, one head 50 us tiled and 77 by waves
   // (224 units 66 and 82), eight heads 17 and 23 (224 units 19 and 23).  With relative keys that does not make up for their
   // products with every query, which the tiled kernel forms in plain fp32: one sentence of 10 / 32 / 64 / 128 / 150 / 200
