@@ -48,7 +48,7 @@ def host(tmp_path_factory):
     so = str(tmp_path_factory.mktemp("stub") / "libhipstub.so")
     subprocess.run(["gcc", "-O1", "-shared", "-fPIC", "-w", "-o", so, os.path.join(ROOT, "tests", "hip_stub.c")], check=True)
 
-    def run(code, timeout=120):
+    def run(code, timeout=300):
         """Runs code after the preamble; returns what it printed last, as JSON."""
         res = subprocess.run([sys.executable, "-c", PREAMBLE + code, so], cwd=ROOT, timeout=timeout, capture_output=True, text=True,
                              env=dict(os.environ, PYTHONPATH=ROOT))
@@ -71,7 +71,7 @@ try:
     print(json.dumps((0, "")))
 except nt.NtError as e:
     print(json.dumps((e.code, str(e))))
-""", timeout=60)
+""", timeout=180)
     assert rc == -5 and "stub error" in message
 
 
