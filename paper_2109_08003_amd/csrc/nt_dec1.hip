@@ -1,6 +1,6 @@
 // The attention half of a decoder layer in one launch (gfx950): one-head models of width 256 / 512, and eight heads of 64.
 //
-// Between the fused Q | K | V projection and the output layer a decoder row passes through
+// Between the Q | K | V projection and the output layer a decoder row passes through
 //   self-attention -> output projection + residual -> LayerNorm -> query projection -> cross-attention ->
 //   output projection + residual -> [LayerNorm -> FFN + residual ->] final LayerNorm,
 // and no step of it reads another row.  A workgroup carries its rows through the whole chain - 2 with eight waves, 4 to 16 with
@@ -16,6 +16,15 @@
 // every vector, so a wave instruction reads one whole vector.  Keys are taken four at a time: reduce-scatter butterfly,
 // wave-uniform scores, one rescale of the online softmax per block.  A row's blocks are dealt to 1 (1,024 rows or more)
 // or 4 partial softmaxes that are merged in order, however many waves compute them.
+//
+// First layer: token -> z, query, key and value by table (Dec1Table in nt_kernels.h), so the step starts here: one sentence reads
+// one row of 8 KB where a launch of its own streamed the 1.5 MB matrix (9 to 11 us up to 512 rows, 15 to 21 us from there on, of
+// which 1 to 3 us remain here, most of them hidden behind the caches' first blocks).  The table of a 32,000-entry vocabulary at
+// d = 512 has 262 MB with the folded values and takes 2.7 ms of a load of 200 ms.  With the launch against by table: one sentence
+// 1,008 -> 811 us, 45 sentences 3,225 -> 2,505, 8 sentences of the 256-wide model 1,188 -> 920 us, a 4,096-token budget
+// 28.4 -> 25.2 ms, 16,384 tokens 76.0 -> 68.2, 65,536 tokens 559 -> 521, 320 rows of 180 tokens 22.7 -> 20.5, the model with
+// 8 heads and FFN 2,048 116.8 -> 109.0 ms, the 30 + 6 layer teacher 110.4 -> 109.1.  It is the faster form at every row count, so
+// every layer of this file's kinds takes it; only the shapes without a layer in one launch keep dec_qkv_kernel.
 //
 // Projection phases: every workgroup pulls the whole matrix through its CU (64 B per clock: 3.9 us for 512 KB at
 // 2.1 GHz), which is what bounds them.  A wave owns D / 8 or D / 16 output columns.  With at most eight rows the head and
@@ -39,10 +48,10 @@
 // runs beside it).  What is left is latency: a row per workgroup of four waves, the
 // first cross keys requested before the self-attention.  One row 20.6 us without folding, 12.8 with the cross cache folded,
 // 45 rows 26 and 17.8; with the self values too, one sentence 1119 -> 1012 us, 45 sentences 3742 -> 3207 us, 8 sentences of
-// the 256-wide model 1253 -> 1175 us, a 4,096-token budget 28.0 -> 27.5 ms.
+// the 256-wide model 1253 -> 1175 us, a 4,096-token budget 28.0 -> 27.5 ms (each with the projection as a launch of its own).
 //
-// Registers: three forms spill some of theirs - eight heads with two rows (8, 36 bytes of scratch per lane) and with eight rows
-// (17, 72 bytes), folded with the FFN at d = 512 (70, 152 bytes).  The others use no scratch.
+// Registers: three forms spill some of theirs - eight heads with two rows (5, 24 bytes of scratch per lane) and with eight rows
+// (13, 56 bytes), folded with the FFN at d = 512 (48, 100 bytes).  The others use no scratch.
 //
 // Measured per step of 1,900 / 45 / 1 rows, alone: 92 / 42 / 38 us as four launches, 71 / 30 / 25 us as one.
 //
@@ -57,6 +66,7 @@
 // at full precision and appended in integer form.
 #include <math.h>
 
+#include <algorithm>
 #include <type_traits>
 
 #include "nt_kernels.h"
@@ -164,6 +174,67 @@ hipError_t launch_quantize_kv_i16(const float *x, long M, int d, short *cache, f
   if (d == 512) { if (planes) NT_QKV(8, true); else NT_QKV(8, false); }
   else { if (planes) NT_QKV(4, true); else NT_QKV(4, false); }
 #undef NT_QKV
+  return hipGetLastError();
+}
+
+// The first layer's projection table (Dec1Table): centred rows x B in double, once per load.  64 rows x 64 columns per
+// workgroup, 4 x 4 per lane.
+constexpr int DT_T = 64, DT_K = 32;
+__global__ __launch_bounds__(256) void dec1_table_kernel(const _Float16 *E, const float *pe, const float *gamma, const float *beta,
+                                                         const double *B, const double *bias, int vocab, int max_len, int d, int N, float *rows) {
+  __shared__ double sa[DT_K][DT_T + 2], sb[DT_K][DT_T], sm[DT_T];
+  const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4, n0 = blockIdx.x % (N / DT_T) * DT_T;
+  const long r0 = (long)(blockIdx.x / (N / DT_T)) * DT_T, R = (long)vocab + max_len + 1;
+  const double root = sqrt((double)d);
+  auto element = [&](long r, int k) { return r < vocab ? root * (double)(float)E[r * d + k] : r < R - 1 ? (double)pe[(r - vocab) * d + k] : 0.0; };
+  {  // means of the rows, four lanes each
+    double s = 0.0;
+    for (int k = tid & 3; k < d; k += 4) s += element(r0 + (tid >> 2), k);
+    s += __shfl_xor(s, 1, 64);
+    s += __shfl_xor(s, 2, 64);
+    if ((tid & 3) == 0) sm[tid >> 2] = s / (double)d;
+  }
+  __syncthreads();
+  double acc[4][4] = {};
+  for (int k0 = 0; k0 < d; k0 += DT_K) {
+    for (int i = tid; i < DT_T * DT_K; i += 256) {
+      const int k = k0 + i % DT_K;
+      const long r = r0 + i / DT_K;
+      sa[i % DT_K][i / DT_K] = r < R - 1 ? (element(r, k) - sm[i / DT_K]) * (double)gamma[k] : r == R - 1 ? (double)beta[k] : 0.0;
+      sb[i / DT_T][i % DT_T] = B[(long)(k0 + i / DT_T) * N + n0 + i % DT_T];
+    }
+    __syncthreads();
+    for (int k = 0; k < DT_K; k++) {
+      double x[4], w[4];
+#pragma unroll
+      for (int i = 0; i < 4; i++) x[i] = sa[k][ty * 4 + i], w[i] = sb[k][tx + i * 16];
+#pragma unroll
+      for (int i = 0; i < 4; i++)
+#pragma unroll
+        for (int j = 0; j < 4; j++) acc[i][j] += x[i] * w[j];
+    }
+    __syncthreads();
+  }
+#pragma unroll
+  for (int i = 0; i < 4; i++) {
+    const long r = r0 + ty * 4 + i;
+#pragma unroll
+    for (int j = 0; j < 4; j++) {
+      const int n = n0 + tx + j * 16;
+      if (r < R) rows[r * N + n] = (float)(acc[i][j] + (r == R - 1 ? bias[n] : 0.0));
+    }
+  }
+}
+
+size_t dec1_table_bytes(int vocab, int max_len, int d, int parts) { return ((size_t)vocab + max_len + 1) * parts * d * sizeof(float); }
+
+hipError_t launch_dec1_table(const _Float16 *E, const float *pe, const float *gamma, const float *beta, const double *B, const double *bias,
+                             int vocab, int max_len, int d, int parts, float *rows, hipStream_t s) {
+  const long R = (long)vocab + max_len + 1;
+  const int N = parts * d;
+  if (d % DT_K != 0 || N % DT_T != 0) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(dec1_table_kernel, dim3((unsigned)((R + DT_T - 1) / DT_T * (N / DT_T))), dim3(256), 0, s, E, pe, gamma, beta, B, bias,
+                     vocab, max_len, d, N, rows);
   return hipGetLastError();
 }
 
@@ -335,6 +406,108 @@ struct D1HeadBlock {
     a.m = mn;
   }
 };
+// The input token of a wave's row, in two halves so that the loads between them travel with it: BOS, the given token, or the
+// arg-max of the previous step, which the row's first wave also stores.
+struct D1Token {
+  unsigned long long key;  // a lane's first partial key
+  int tok, slot;
+  __device__ __forceinline__ void request(const Dec1Args &a, int row, int lane) {
+    const StepBeginArgs &b = a.sb;
+    key = 0ull, tok = b.pad_id, slot = -1;
+    if (a.tok_in) {
+      if (row < a.rows) tok = a.tok_in[row];
+    } else if (b.t > 0 && row < b.rows_prev) {
+      if (b.prev_cert) {
+        tok = b.tok[row];
+        slot = b.slot_of_row[row];
+      } else if (b.pk && lane < b.n_partials) {
+        key = b.pk[(long)row * b.n_partials + lane];
+      }
+    }
+  }
+  __device__ __forceinline__ int resolve(const Dec1Args &a, int row, bool first_wave, int lane) {
+    const StepBeginArgs &b = a.sb;
+    int y = tok;
+    if (!a.tok_in) {
+      if (b.t == 0) {
+        y = b.bos_id;
+      } else if (row < b.rows_prev && (b.prev_cert || b.pk)) {
+        if (b.prev_cert) {
+          if (slot >= 0) y = (int)(0xFFFFFFFFu - (unsigned int)b.final_key[slot]);
+        } else {
+          for (int q = lane + 64; q < b.n_partials; q += 64) {
+            const unsigned long long c = b.pk[(long)row * b.n_partials + q];
+            key = c > key ? c : key;
+          }
+#pragma unroll
+          for (int m = 32; m >= 1; m >>= 1) {
+            const unsigned long long o = shfl_xor_u64(key, m);
+            key = o > key ? o : key;
+          }
+          y = (int)(0xFFFFFFFFu - (unsigned int)key);
+        }
+        if (y < 0 || y >= b.vocab) y = b.pad_id;  // cannot happen: every key holds a valid id
+        if (first_wave && lane == 0) b.out[(long)row * b.out_ld + b.t - 1] = y;
+      }
+      if (b.forced && row < a.rows) {
+        y = b.forced[(long)row * b.forced_ld + b.t];
+        if (y < 0 || y >= b.vocab) {
+          if (lane == 0) b.flags[0] = 1;
+          y = b.pad_id;
+        }
+      }
+      if (b.cert_count && blockIdx.x == 0 && threadIdx.x == 0) *b.cert_count = 0;
+    }
+    if (row >= a.rows) y = b.pad_id;  // computes on the padding token and stores nothing
+    return __builtin_amdgcn_readfirstlane(y);
+  }
+};
+
+// First layer: z = sqrt(d) E[y] + PE[t], and from its mean and scale the query, and (first wave of a row) the key and value,
+// by the table (see Dec1Table).  Every wave of a row computes the statistics for itself.
+template <int NE>
+__device__ __forceinline__ void first_layer_start(const Dec1Args &a, int y, int lane, bool first_wave, float (&q)[NE], float (&z)[NE],
+                                                  float (&kx)[NE], float (&vx)[NE]) {
+  constexpr int D = NE * 64;
+  typedef _Float16 halfNE __attribute__((ext_vector_type(NE)));
+  const long ld = (long)a.table.parts * D;
+  const float *by_token = a.table.rows + y * ld + lane * NE, *by_pos = a.table.rows + (a.sb.vocab + a.sb.t) * ld + lane * NE,
+              *offset = a.table.rows + (a.sb.vocab + a.table.max_len) * ld + lane * NE;
+  const halfNE ev = *(const halfNE *)(a.sb.E + (long)y * D + lane * NE);
+  float pv[NE], tq[NE], tk[NE], tv[NE];
+  d1_load<NE>(a.sb.pe + (long)a.sb.t * D + lane * NE, pv);
+  d1_load<NE>(by_token, tq);
+  const int vcol = (a.table.parts - 1) * D;
+  if (first_wave) {
+    d1_load<NE>(by_token + D, tk);
+    d1_load<NE>(by_token + (a.folded ? vcol : 2 * D), tv);
+  }
+  const float sc = sqrtf((float)D);
+  float s = 0.f;
+#pragma unroll
+  for (int e = 0; e < NE; e++) {
+    z[e] = sc * (float)ev[e] + pv[e];
+    s += z[e];
+  }
+  const float mean = d1_wave_sum(s) / (float)D;
+  float v = 0.f;
+#pragma unroll
+  for (int e = 0; e < NE; e++) v += ln_term(z[e] - mean, a.eps.l1);
+  const float rs = ln_rscale(d1_wave_sum(v) / (float)D, a.eps);
+  auto combine = [&](const float (&t)[NE], int col, float (&x)[NE]) {
+    float p[NE], c[NE];
+    d1_load<NE>(by_pos + col, p);
+    d1_load<NE>(offset + col, c);
+#pragma unroll
+    for (int e = 0; e < NE; e++) x[e] = rs * (t[e] + p[e]) + c[e];
+  };
+  combine(tq, 0, q);
+  if (first_wave) {
+    combine(tk, D, kx);
+    combine(tv, a.folded ? vcol : 2 * D, vx);
+  }
+}
+
 // D: model width.  RW: rows per workgroup, NWAVES / RW waves each.  PARTS: partial softmaxes per row.  IND: row r uses cache
 // row origin[r] (< 0: no row, zero context).  FFN: the layer's FFN (of width D) is part of the chain.  FOLD: the cross cache
 // holds folded fp32 vectors.  HEADS: eight heads of 64 columns, self cache fp32, cross cache fp16, optional relative keys.
@@ -362,6 +535,8 @@ __global__ __launch_bounds__(NWAVES * 64) void dec1_kernel(Dec1Args a) {
   const int rw = wave / WR, pg = wave % WR;
   const int row0 = blockIdx.x * RW;
   const bool valid = row0 + rw < a.rows;
+  D1Token token;
+  if (a.table.rows) token.request(a, row0 + rw, lane);
   const int r = valid ? row0 + rw : 0;
   int rc = r;
   if (IND) rc = valid ? a.origin[r] : -1;
@@ -547,11 +722,29 @@ __global__ __launch_bounds__(NWAVES * 64) void dec1_kernel(Dec1Args a) {
   // ---- self-attention ----
   const int n_self = __builtin_amdgcn_readfirstlane(live ? a.n_keys : 0);
   const int n_cross = __builtin_amdgcn_readfirstlane(live ? a.len[rc] : 0);
-  float q[NE];
-  d1_load<NE>(a.q + (long)r * D + lane * NE, q);
+  if (EARLY && !FOLD) preload(a.Wo_self);
+  SelfBlock sb[2];
+  CrossBlock cb[2];
+  const long cross0 = (long)rc * a.cross_positions, self0 = (long)rc * a.self_positions;
+  const int n_cached = n_self > 0 ? n_self - 1 : 0;
+  if constexpr (FOLD) {  // the first blocks of both caches depend on nothing computed here
+    first_blocks(sb, a.self_kv, a.self_sc, self0, n_cached);
+    first_blocks(cb, a.cross_kv, a.cross_sc, cross0, n_cross);
+  }
+  float q[NE], z[NE], kx[NE], vx[NE];  // z, kx, vx: the row's first wave
+  if (a.table.rows) {
+    const int y = token.resolve(a, row0 + rw, pg == 0, lane);
+    if (row0 >= a.rows) return;  // rows that were kept to collect their last tokens
+    first_layer_start<NE>(a, y, lane, pg == 0, q, z, kx, vx);
+  } else {
+    d1_load<NE>(a.q + (long)r * D + lane * NE, q);
+    if (pg == 0) {
+      d1_load<NE>(a.z + (long)r * D + lane * NE, z);
+      d1_load<NE>(a.kv_new + (long)r * 2 * D + lane * NE, kx);
+      d1_load<NE>(a.kv_new + (long)r * 2 * D + D + lane * NE, vx);
+    }
+  }
   if (pg == 0) {
-    float z[NE];
-    d1_load<NE>(a.z + (long)r * D + lane * NE, z);
     if constexpr (FOLD) {  // the bias of the self-attention's output, which no projection adds, and the values' column scales
       float b[NE], c[NE];
       d1_load<NE>(a.bo_self + lane * NE, b);
@@ -564,11 +757,6 @@ __global__ __launch_bounds__(NWAVES * 64) void dec1_kernel(Dec1Args a) {
 #pragma unroll
     for (int e = 0; e < NE; e += 4) *(float4 *)(sZ + rw * ZLD + lane * NE + e) = make_float4(z[e], z[e + 1], z[e + 2], z[e + 3]);
   }
-  if (EARLY && !FOLD) preload(a.Wo_self);
-  SelfBlock sb[2];
-  CrossBlock cb[2];
-  const long cross0 = (long)rc * a.cross_positions;
-  if constexpr (FOLD) first_blocks(cb, a.cross_kv, a.cross_sc, cross0, n_cross);  // they depend on nothing computed here
   auto add_context = [&](const float (&ctx)[NE]) {
     float *z = sZ + rw * ZLD + lane * NE;
 #pragma unroll
@@ -598,11 +786,7 @@ __global__ __launch_bounds__(NWAVES * 64) void dec1_kernel(Dec1Args a) {
     Part st[PW];
 #pragma unroll
     for (int u = 0; u < PW; u++) st[u].clear();
-    const long pos0 = (long)rc * a.self_positions;
     if (pg == 0 && n_self > 0) {  // the pair computed in this step: used as it is, and appended in integer form
-      float kx[NE], vx[NE];
-      d1_load<NE>(a.kv_new + (long)r * 2 * D + lane * NE, kx);
-      d1_load<NE>(a.kv_new + (long)r * 2 * D + D + lane * NE, vx);
       float s = 0.f;
 #pragma unroll
       for (int e = 0; e < NE; e++) s += q[e] * kx[e];
@@ -610,7 +794,7 @@ __global__ __launch_bounds__(NWAVES * 64) void dec1_kernel(Dec1Args a) {
       st[0].l = 1.f;
 #pragma unroll
       for (int e = 0; e < NE; e++) st[0].acc[e] = vx[e];
-      const long p = pos0 + (n_self - 1);
+      const long p = self0 + (n_self - 1);
       if constexpr (HEADS) {
         float *dst = (float *)a.self_kv + p * 2 * D + lane * NE;
 #pragma unroll
@@ -624,8 +808,8 @@ __global__ __launch_bounds__(NWAVES * 64) void dec1_kernel(Dec1Args a) {
         d1_quantize_store<NE>(vx, dst + D, a.self_sc + p * 2 + 1, lane);
       }
     }
-    if constexpr (FOLD) attend(sb, std::false_type{}, q, a.self_kv, a.self_sc, pos0, n_self > 0 ? n_self - 1 : 0, rel, st, add_self_context);
-    else attend(sb, std::false_type{}, q, a.self_kv, a.self_sc, pos0, n_self > 0 ? n_self - 1 : 0, rel, st, store_planes);
+    if constexpr (FOLD) attend(sb, std::true_type{}, q, a.self_kv, a.self_sc, self0, n_cached, rel, st, add_self_context);
+    else attend(sb, std::false_type{}, q, a.self_kv, a.self_sc, self0, n_cached, rel, st, store_planes);
   }
   // ---- output projection + residual, LayerNorm, cross-attention query ----
   if constexpr (!FOLD) {
@@ -733,9 +917,10 @@ static hipError_t d1_launch(const Dec1Args &a, hipStream_t s) {
   // (65,536 tokens: 550 against 554 ms with four).  Eight heads, whose waves hold fp32 keys: four from 65 rows on and eight
   // from 257 on.
   const int shape = a.shape_rows > 0 ? a.shape_rows : a.rows;
+  const int rows = a.table.rows && !a.tok_in ? std::max(a.rows, a.sb.rows_prev) : a.rows;  // those that only collect a token, too
 #define NT_D1(RW_, NW_, P_, F_)                                                                                          \
   do {                                                                                                                  \
-    const dim3 grid((unsigned)((a.rows + RW_ - 1) / RW_));                                                              \
+    const dim3 grid((unsigned)((rows + RW_ - 1) / RW_));                                                                \
     if (a.origin) hipLaunchKernelGGL((dec1_kernel<D, RW_, NW_, P_, true, FFN, F_, HEADS>), grid, dim3(64 * NW_), 0, s, a);     \
     else hipLaunchKernelGGL((dec1_kernel<D, RW_, NW_, P_, false, FFN, F_, HEADS>), grid, dim3(64 * NW_), 0, s, a);             \
   } while (0)

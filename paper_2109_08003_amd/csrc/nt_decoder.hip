@@ -11,6 +11,9 @@
 //                     projection (cross-attention query, first FFN matrix) or, after the last sub-layer, the final
 //                     hidden state as a head/tail pair of fp16 planes plus the norm of its tail
 //
+// Decoders whose layers are one launch (nt_dec1.hip) use neither: these are for other head counts at d = 256 / 512, and one head
+// with relative keys.
+//
 // Both are built on the streaming form of nt_gemm_stream.hip: the 32-row tile of activations (head and tail fp16
 // planes, about 22 significant bits) stays in the LDS, the weights come in MFMA fragment order through a ring of
 // registers that runs seven k-steps ahead, both planes are multiplied with the same weight fragment into one fp32
@@ -254,25 +257,15 @@ __global__ __launch_bounds__(DC_WAVES * 64) void dec_qkv_kernel(DecQkvArgs a, in
   const int sb0 = (int)((long)cg * NS / col_groups), sb1 = (int)((long)(cg + 1) * NS / col_groups);
   const DcWeights w(a.Wp, NS, K, lane);
   constexpr int KSW = S::KS / DC_WAVES;  // k-steps of a wave when the waves share a strip
-  half8 wb[SPLIT ? KSW : DC_SL][2], wt[SPLIT ? KSW : 1][2];
+  half8 wb[SPLIT ? KSW : DC_SL][2];
   int strip = SPLIT ? sb0 : sb0 + wave;
   const bool have = m0 < M && strip < sb1;
-  const bool vo = SPLIT && a.Wvo_p && strip * 64 >= 2 * K;  // a strip of folded values: its matrix has a tail plane
   if constexpr (SPLIT) {
     if (have) {
-      const DcWeights wv(vo ? a.Wvo_p : a.Wp, vo ? 2 * K / 64 : NS, K, lane);
-      const int head = vo ? strip - 2 * K / 64 : strip;
 #pragma unroll
       for (int q = 0; q < KSW; q++) {
-        wb[q][0] = wv.load((head * S::KS + wave * KSW + q) * 2048, 0);
-        wb[q][1] = wv.load((head * S::KS + wave * KSW + q) * 2048, 1);
-      }
-      if (vo) {
-#pragma unroll
-        for (int q = 0; q < KSW; q++) {
-          wt[q][0] = wv.load(((head + K / 64) * S::KS + wave * KSW + q) * 2048, 0);
-          wt[q][1] = wv.load(((head + K / 64) * S::KS + wave * KSW + q) * 2048, 1);
-        }
+        wb[q][0] = w.load((strip * S::KS + wave * KSW + q) * 2048, 0);
+        wb[q][1] = w.load((strip * S::KS + wave * KSW + q) * 2048, 1);
       }
     }
   } else {
@@ -396,10 +389,6 @@ __global__ __launch_bounds__(DC_WAVES * 64) void dec_qkv_kernel(DecQkvArgs a, in
         const half8 h = *(const half8 *)(hrow + op * DC_TM * LD + (wave * KSW + q) * 16);
 #pragma unroll
         for (int nb = 0; nb < 2; nb++) acc[nb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(h, wb[q][nb], acc[nb], 0, 0, 0);
-        if (vo) {
-#pragma unroll
-          for (int nb = 0; nb < 2; nb++) acc[nb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(h, wt[q][nb], acc[nb], 0, 0, 0);
-        }
       }
     f32x4 *red = (f32x4 *)smem;  // [wave][register group][lane]
     __syncthreads();
@@ -412,14 +401,14 @@ __global__ __launch_bounds__(DC_WAVES * 64) void dec_qkv_kernel(DecQkvArgs a, in
     for (int p = 1; p < DC_WAVES; p++) t += red[(p * 8 + wave) * 64 + lane];
     const GemmEpilogue &e = a.e;
     const int nbase = strip * 64 + (wave >> 2) * 32, n = nbase + li;
-    const float bias = !vo && e.bias ? e.bias[n] : 0.f, scl = n < e.scale_cols ? e.scale : 1.f;
+    const float bias = e.bias ? e.bias[n] : 0.f, scl = n < e.scale_cols ? e.scale : 1.f;
     const bool first = nbase < e.n_split;
     float *dst = first ? (float *)e.dst0 + n : (float *)e.dst1 + (n - e.n_split);
     const long ld = first ? e.ld0 : e.ld1;
 #pragma unroll
     for (int v = 0; v < 4; v++) {
       const int r = m0 + (wave & 3) * 8 + g * 4 + v;
-      if (r < M) dst[(long)r * ld] = vo ? t[v] * kFoldInv : (t[v] + bias) * scl;
+      if (r < M) dst[(long)r * ld] = (t[v] + bias) * scl;
     }
   } else {
     if (!have) return;
@@ -632,7 +621,6 @@ hipError_t launch_dec_qkv(const DecQkvArgs &a, hipStream_t s) {
   // stream is cut as short as it gets: one strip per workgroup, an eighth of its k-steps per wave (the sums run in another
   // order, so the choice goes by shape_rows)
   const bool split = (a.shape_rows > 0 ? a.shape_rows : a.sb.rows_now) <= 512;
-  if (a.Wvo_p && !split) return hipErrorInvalidValue;
   if (K == 512) return split ? dq_launch<512, true>(a, s) : dq_launch<512, false>(a, s);
   return split ? dq_launch<256, true>(a, s) : dq_launch<256, false>(a, s);
 }

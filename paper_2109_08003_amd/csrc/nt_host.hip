@@ -127,9 +127,8 @@ struct Attn {
   const _Float16 *Wo = nullptr;    // [d][d]
   // the same matrices in MFMA fragment order (streaming GEMM), nullptr where the shape is not supported
   const _Float16 *Wqkv_p = nullptr, *Wq_p = nullptr, *Wkv_p = nullptr, *Wo_p = nullptr;
-  const _Float16 *Wvo_p = nullptr;      // head | tail of Wv Wo, columns scaled (folded self values)
-  const float *bvo = nullptr;           // bv Wo + bo
-  const float *vo_scale = nullptr;      // what the columns were divided by
+  const float *bvo = nullptr;           // bv Wo + bo (folded self values)
+  const float *vo_scale = nullptr;      // what the columns of Wv Wo were divided by
   const _Float16 *Wq_back_p = nullptr;  // Wq the other way round (its product with a key): folded cross caches
   const float *bqkv = nullptr, *bq = nullptr, *bkv = nullptr, *bo = nullptr;
   const float *rk = nullptr;       // [2c+1][dh]
@@ -198,6 +197,9 @@ struct nt_model {
   float *q8_scale = nullptr;                        // arena: [Br] per-row scale
   int32_t *q8_c = nullptr, *q8_sa = nullptr;        // arena: [Br] 128 - zero point, sum of the signed codes
   const float *pe = nullptr;
+  nt::Dec1Table dec_table{};  // Q | K | V of the first decoder layer by token and position (decoder layers in one launch)
+  float *d_table = nullptr;   // its allocation
+  size_t table_bytes = 0;
   std::vector<EncLayer> enc;
   std::vector<DecLayer> dec;
   LN enc_final, dec_final;
@@ -492,7 +494,7 @@ int nt_debug_set_cert_distrust(nt_model *m, int on) {
 
 int64_t nt_device_bytes(const nt_model *m) {
   if (!m) return 0;
-  int64_t n = (int64_t)(m->w_bytes + m->arena_bytes);
+  int64_t n = (int64_t)(m->w_bytes + m->table_bytes + m->arena_bytes);
   for (const nt_model *ln : m->lanes) n += (int64_t)ln->arena_bytes;
   return n;
 }
@@ -512,6 +514,7 @@ void nt_free(nt_model *m) {
   if (m->lane_stream) (void)hipStreamDestroy(m->lane_stream);
   if (m->lane_start) (void)hipEventDestroy(m->lane_start);
   if (m->d_w && m->owns_weights) (void)hipFree(m->d_w);
+  if (m->d_table && m->owns_weights) (void)hipFree(m->d_table);
   if (m->d_arena) (void)hipFree(m->d_arena);
   for (auto &st : m->stage) {
     if (st.done) (void)hipEventDestroy(st.done);
@@ -627,7 +630,11 @@ int nt_load_weights(const nt_config *cfg, const void *h_blob_fp16, size_t blob_b
   };
   // self-attention: Wq|Wk|Wv fused into one [3d][d] matrix; cross-attention: Wq and Wk|Wv; fold: what folded batches need besides
   const bool fold_dec = m->kv_i16 && cfg->n_dec == 1;
-  auto put_attn = [&](Attn &a, bool cross, bool rpr, int dh, bool fold = false) {
+  // The first decoder layer's Q | K | V comes from a table (Dec1Table); what it is made of: matrix [d][parts d] and bias, in double
+  const bool tabled = m->kv_i16 || (!kCrossF32 && nt::dec1_heads_supported(d, dec_heads(cfg)));
+  const int parts = tabled ? (fold_dec ? 4 : 3) : 0;
+  std::vector<double> tabW((size_t)d * parts * d), tabB((size_t)parts * d);
+  auto put_attn = [&](Attn &a, bool cross, bool rpr, int dh, bool fold = false, bool table = false) {
     const _Float16 *W[4], *b[4];
     for (int i = 0; i < 4; i++) { W[i] = br.take((int64_t)d * d); b[i] = br.take(d); }
     auto fused = [&](int first, int count, const void **wslot, const void **bslot, const void **pslot) {
@@ -643,7 +650,15 @@ int nt_load_weights(const nt_config *cfg, const void *h_blob_fp16, size_t blob_b
       for (int i = 0; i < count; i++) Packer::widen(b[first + i], d, (float *)(pk.img.data() + ob) + (size_t)i * d);
       fixes.push_back({ob, bslot});
     };
-    if (!cross) {
+    if (table) {
+      const double qscale = (double)(1.0f / std::sqrt((float)dh));
+      for (int p = 0; p < 3; p++)
+        for (int j = 0; j < d; j++) {
+          for (int k = 0; k < d; k++)
+            tabW[((size_t)k * parts + p) * d + j] = (double)(float)W[p][(int64_t)k * d + j] * (p == 0 ? qscale : 1.0);
+          tabB[(size_t)p * d + j] = (double)(float)b[p][j] * (p == 0 ? qscale : 1.0);
+        }
+    } else if (!cross) {
       fused(0, 3, (const void **)&a.Wqkv, (const void **)&a.bqkv, (const void **)&a.Wqkv_p);
     } else {
       fused(0, 1, (const void **)&a.Wq, (const void **)&a.bq, (const void **)&a.Wq_p);
@@ -670,17 +685,8 @@ int nt_load_weights(const nt_config *cfg, const void *h_blob_fp16, size_t blob_b
       }
       for (int j = 0; j < d; j++)
         if (norm2[(size_t)j] > 0.0) scale[(size_t)j] = (double)(float)std::sqrt(norm2[(size_t)j]);
-      std::vector<_Float16> rows((size_t)2 * d * d);  // [out][in], head then tail
       for (int i = 0; i < d; i++)
-        for (int j = 0; j < d; j++) {
-          const double x = prod[(size_t)i * d + j] / scale[(size_t)j] / (double)nt::kFoldInv;
-          const _Float16 hi = (_Float16)x;
-          rows[(size_t)j * d + i] = hi;
-          rows[(size_t)(d + j) * d + i] = (_Float16)(x - (double)(float)hi);
-        }
-      const size_t ov = pk.reserve(nt::vocab_pack_bytes(2 * d, d));
-      nt::vocab_pack(rows.data(), 2 * d, d, (_Float16 *)(pk.img.data() + ov));
-      fixes.push_back({ov, (const void **)&a.Wvo_p});
+        for (int j = 0; j < d; j++) tabW[((size_t)i * parts + 3) * d + j] = prod[(size_t)i * d + j] / scale[(size_t)j];
       const size_t ob = pk.reserve((size_t)d * 4);
       for (int j = 0; j < d; j++) ((float *)(pk.img.data() + ob))[j] = (float)bias[(size_t)j];
       fixes.push_back({ob, (const void **)&a.bvo});
@@ -725,7 +731,7 @@ int nt_load_weights(const nt_config *cfg, const void *h_blob_fp16, size_t blob_b
   put_ln(m->enc_final);
   for (auto &L : m->dec) {
     put_ln(L.ln1);
-    put_attn(L.self, false, true, dhd, fold_dec);
+    put_attn(L.self, false, true, dhd, fold_dec, tabled && &L == &m->dec[0]);
     put_ln(L.ln2);
     put_attn(L.cross, true, false, dhd, fold_dec);
     if (Fd > 0) { put_ln(L.ln3); put_ffn(L.ffn, Fd); }
@@ -761,6 +767,21 @@ int nt_load_weights(const nt_config *cfg, const void *h_blob_fp16, size_t blob_b
   HIP_TRY(hipMemcpyAsync(m->d_w, pk.img.data(), m->w_bytes, hipMemcpyHostToDevice, s));
   for (auto &f : fixes) *f.slot = m->d_w + f.off;
   if (cfg->tie_output) m->Wout = m->E;
+  struct Temp {
+    void *p = nullptr;
+    ~Temp() { if (p) (void)hipFree(p); }
+  } tab;
+  if (tabled) {
+    m->table_bytes = nt::dec1_table_bytes(V, cfg->max_len, d, parts);
+    if (hipMalloc((void **)&m->d_table, m->table_bytes) != hipSuccess) return fail(NT_ENOMEM, "hipMalloc of %zu table bytes failed", m->table_bytes);
+    const size_t wb = tabW.size() * sizeof(double), bb = tabB.size() * sizeof(double);
+    if (hipMalloc(&tab.p, wb + bb) != hipSuccess) return fail(NT_ENOMEM, "hipMalloc of %zu bytes failed", wb + bb);
+    HIP_TRY(hipMemcpyAsync(tab.p, tabW.data(), wb, hipMemcpyHostToDevice, s));
+    HIP_TRY(hipMemcpyAsync((char *)tab.p + wb, tabB.data(), bb, hipMemcpyHostToDevice, s));
+    HIP_TRY(nt::launch_dec1_table(m->E, m->pe, m->dec[0].ln1.g, m->dec[0].ln1.b, (const double *)tab.p, (const double *)((char *)tab.p + wb), V,
+                                  cfg->max_len, d, parts, m->d_table, s));
+    m->dec_table = nt::Dec1Table{m->d_table, parts, cfg->max_len};
+  }
   m->vw.Wt = m->Wout; m->vw.Wp = m->Wout_frag; m->vw.N = V; m->vw.K = d;
   {  // largest row norm of the output matrix, rounded up (bound used by the certified arg-max)
     const _Float16 *Wo = (const _Float16 *)h_blob_fp16 + (cfg->tie_output ? 0 : (int64_t)V * d);
@@ -1013,7 +1034,7 @@ int decode_step(nt_model *m, DecodeCursor &cu, hipStream_t s) {
     // (measured on the 4,096-token budget, where batches have 36-341 rows: 2.38 M source tokens/s against 2.01 M with
     // the one-round-trip kernels below 128 rows): step start + LayerNorm + Q|K|V, output projection + LayerNorm +
     // next projection, output projection + final LayerNorm.
-    const bool fused = nt::dec_fused_supported(d) && m->dec[0].self.Wqkv_p != nullptr;
+    const bool fused = nt::dec_fused_supported(d) && (m->dec_table.rows != nullptr || m->dec[0].self.Wqkv_p != nullptr);
     const bool fused_start = fused && rows_now > 0;
     // decoder layers whose attention half is one launch (nt_dec1.hip): the integer caches, or eight heads of 64
     const bool heads_layer = !m->kv_i16 && fused && !kCrossF32 && nt::dec1_heads_supported(d, H);
@@ -1109,17 +1130,20 @@ int decode_step(nt_model *m, DecodeCursor &cu, hipStream_t s) {
         e.dst1 = m->self_kv[l] + (long)t * 2 * d; e.ld1 = self_stride;
         // the EOS mode and the integer caches: the pair goes to kv_new and the attention kernel appends it to the cache
         if (eos || layer1) { e.dst1 = m->kv_new; e.ld1 = 2 * d; }
-        if (fused_start && l == 0) {
+        // the first layer's projection starts the step: by table inside the layer's launch, or in one with the embedding
+        const bool by_table = l == 0 && layer1;
+        nt::StepBeginArgs start = sba;
+        if (eos) {  // tokens and row map come from the compaction kernel; nothing to collect here
+          start.t = t; start.rows_prev = R; start.rows_now = R; start.d = d; start.vocab = V; start.bos_id = c.bos_id;
+          start.pad_id = c.pad_id; start.E = m->E; start.pe = m->pe; start.z = m->z; start.flags = m->flags;
+        }
+        if (by_table) {
+        } else if (fused_start && l == 0) {
           nt::DecQkvArgs q{};
-          q.sb = sba;
-          if (eos) {  // tokens and row map come from the compaction kernel; nothing to collect here
-            q.sb.t = t; q.sb.rows_prev = R; q.sb.rows_now = R; q.sb.d = d; q.sb.vocab = V; q.sb.bos_id = c.bos_id;
-            q.sb.pad_id = c.pad_id; q.sb.E = m->E; q.sb.pe = m->pe; q.sb.z = m->z; q.sb.flags = m->flags;
-            q.tok_in = m->eos_tok;
-          }
+          q.sb = start;
+          if (eos) q.tok_in = m->eos_tok;
           q.sb.gamma = L.ln1.g; q.sb.beta = L.ln1.b; q.sb.eps = lne;
           q.Wp = L.self.Wqkv_p; q.N = 3 * d; q.e = e; q.shape_rows = rows_for_choice;
-          if (m->folded) q.Wvo_p = L.self.Wvo_p;
           KT(K_GEMM_DEC_QKV, gemm_bytes(Rd, d, 3 * d, false) + (eos ? 0.0 : rows_prev * (partials_prev * 8.0 + 4)) + Rd * dd * 6,
              6 * Rd * dd * dd, nt::launch_dec_qkv(q, s));
         } else if ((rc = dec_gemm(K_GEMM_DEC_QKV, m->z, d, L.self.Wqkv, L.self.Wqkv_p, 3 * d, &L.ln1, e))) return rc;
@@ -1128,6 +1152,7 @@ int decode_step(nt_model *m, DecodeCursor &cu, hipStream_t s) {
           const bool ffn_inside = m->kv_i16 && F == d && L.ffn.W1_p != nullptr && L.ffn.W2_p != nullptr;
           const bool to_final = last && (F == 0 || ffn_inside) && !c.q8_output;
           nt::Dec1Args at{};
+          if (by_table) { at.table = m->dec_table; at.sb = start; at.tok_in = eos ? m->eos_tok : nullptr; }
           at.rows = R; at.shape_rows = rows_for_choice; at.origin = origin; at.eps = lne; at.z = m->z; at.write_z = !to_final;
           at.q = m->q32; at.kv_new = m->kv_new; at.self_kv = m->self_kv[l]; at.self_sc = m->self_sc[l];
           at.self_positions = T; at.n_keys = t + 1; at.heads = heads_layer ? H : 1; at.rk = L.self.rk; at.clip = c.rpr_clip;
@@ -1145,7 +1170,8 @@ int decode_step(nt_model *m, DecodeCursor &cu, hipStream_t s) {
             final_ln_done = true;
           }
           const double ffn_flops = ffn_inside ? 4 * Rd * dd * F : 0.0;
-          KT(K_DEC_ATTN, (heads_layer ? Rd * t * dd * 8 + cross_keys * dd * 4 : (Rd * t + cross_keys) * (2 * dd * 2 + 8)) + Rd * dd * 28 + 3 * dd * dd * 2,
+          KT(K_DEC_ATTN, (heads_layer ? Rd * t * dd * 8 + cross_keys * dd * 4 : (Rd * t + cross_keys) * (2 * dd * 2 + 8)) + Rd * dd * 28 + 3 * dd * dd * 2 +
+                             (by_table && !eos ? rows_prev * (partials_prev * 8.0 + 4) : 0.0),
              (4 * Rd * (t + 1) + 4 * cross_keys + 6 * Rd * dd) * dd + ffn_flops, nt::launch_dec1(at, d, s));
           if (F > 0 && !ffn_inside) {
             const bool u_planes = streams(F, d, L.ffn.W1_p, true) && streams(d, F, L.ffn.W2_p, false);

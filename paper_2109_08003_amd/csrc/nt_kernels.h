@@ -256,15 +256,8 @@ struct DecQkvArgs {
   const _Float16 *Wp;
   int N;
   GemmEpilogue e;
-  // optional, up to 512 rows: the value columns (2 d .. 3 d - 1) come from this matrix instead, head and tail (fragment order,
-  // d rows each) of W_v W_o with its columns scaled, and leave as product * kFoldInv without a bias (folded self values, see
-  // Dec1Args)
-  const _Float16 *Wvo_p;
   int shape_rows;  // row count that selects the kernel form (0: rows_now), as in Dec1Args
 };
-// Folded self values: column j of W_v W_o is divided by its norm fold_scale[j], and multiplied by 1 / kFoldInv so that its
-// fp16 tail keeps its bits.
-constexpr float kFoldInv = 1.f / 16384.f;
 hipError_t launch_dec_qkv(const DecQkvArgs &a, hipStream_t s);
 // One launch for: z' = A * W1^T + b1 + z (A: head/tail planes [M][lda], W1 [K][K] in fragment order; z' is written
 // back to z if write_z), y = LayerNorm(z'), then either (W2p == nullptr) y as head/tail planes at h_hi /
@@ -364,7 +357,26 @@ hipError_t launch_attn_decode(const float *q, const void *kv, bool kv_f32, long 
 // [... + 1] (value = code * scale).
 bool attn_i16_supported(int d, int heads, int clip);
 bool dec1_heads_supported(int d, int heads);
+// The first layer's Q | K | V projection depends on the input token y and the position t alone, and LayerNorm is affine in
+// the row once its scale r is known: with c(v) = v - mean(v),
+//   q|k|v = r (sqrt(d) (gamma c(E[y])) W + (gamma c(PE[t])) W) + (beta W + b).
+// The three products are formed at load, in double, and kept in fp32: rows 0 .. vocab - 1 by token, then max_len rows by
+// position, then beta W + b.  A row has `parts` groups of d columns: scaled query, key, value, and (folded batches,
+// parts == 4) the value multiplied by the output matrix with its columns scaled.
+struct Dec1Table {
+  const float *rows;  // nullptr: no table
+  int parts, max_len;
+};
+size_t dec1_table_bytes(int vocab, int max_len, int d, int parts);
+// B [d][parts * d] and bias [parts * d] in double on the device
+hipError_t launch_dec1_table(const _Float16 *E, const float *pe, const float *gamma, const float *beta, const double *B,
+                             const double *bias, int vocab, int max_len, int d, int parts, float *rows, hipStream_t s);
 struct Dec1Args {
+  // first layer (table.rows != nullptr): the launch is the start of the step as launch_dec_qkv has it - the previous step's
+  // tokens are collected, rows beyond `rows` only for that, z is computed here - and q, kv_new are not read
+  Dec1Table table;
+  StepBeginArgs sb;        // gamma / beta / a / rows_now unused
+  const int32_t *tok_in;   // EOS mode: tokens of the dense rows
   int heads;             // 0 / 1: one head
   const float *rk;       // several heads: relative keys [2 clip + 1][64], or nullptr
   int clip;

@@ -1023,6 +1023,42 @@ def test_heads_and_tails_are_of_the_same_value(nt, oracle, torch_cuda, d, n_dec,
     gm.close()
 
 
+@pytest.mark.parametrize("l1", [0, 1])
+@pytest.mark.parametrize("d,n_dec,heads,T", [(512, 1, 8, 4), (512, 2, 8, 4), (512, 1, 1, 1), (256, 1, 1, 1), (256, 2, 1, 1)])
+def test_first_layer_projection_by_table(nt, oracle, torch_cuda, d, n_dec, heads, T, l1):
+    """Query, key and value of the first decoder layer come from a table by token and position.  Embedding rows with a mean four
+    times their spread (what the normalisation takes away again), a vocabulary and a position range that end inside a tile of the
+    table, tokens from both ends of it.  Identities as output matrices show the normalised sum of embedding and context;
+    eight heads keep their caches in fp32, one head shows its first step, whose pair is not rounded.  Bound: the row itself
+    is rounded to fp32 at four times its spread, 4 2^-24 = 2.4e-7 an element, as are the table's entries and their sum; with
+    pairs of 2^-22 and sums of 512 products behind them (1.5e-6) about 2e-6, three times that."""
+    torch = torch_cuda
+    V = d + 37
+    cfg = nt_synth.model_config("C1", d_model=d, vocab=V, n_enc=0, n_dec=n_dec, max_len=61, n_heads=heads, ln_l1=l1)
+    blob = nt_synth.make_weights(cfg, seed=13, random_affine=True)
+    W = nt_synth.blob_view(cfg, blob, "W_out")
+    W[:] = 0
+    W[:d] = np.eye(d)
+    nt_synth.blob_view(cfg, blob, "E")[:] += np.float16(4 * d ** -0.5)
+    for l in range(n_dec):
+        nt_synth.blob_view(cfg, blob, f"dec{l}.self.Wo")[:] = np.eye(d)
+        nt_synth.blob_view(cfg, blob, f"dec{l}.cross.Wo")[:] = 0
+    gm, om = nt.Model(cfg, blob, max_batch_tokens=4096, pipeline_lanes=1), oracle.Model(cfg, blob)
+    src = np.array([5, 6, 7], dtype=np.int32)
+    tgt = np.random.default_rng(d).integers(0, V, size=(1100, T)).astype(np.int32)
+    tgt[0], tgt[1] = V - 1, 0
+    want = np.stack([om.teacher_forced(src, t) for t in tgt])[:, :, :d]
+    for rows in (1, 60, 300, 600, 1100):  # the forms of the decoder layer
+        ids, lens = pad([src] * rows, cfg["pad_id"])
+        gm.encode(torch.from_numpy(ids).cuda(), torch.from_numpy(lens).cuda())
+        logits = torch.empty(rows, T, V, dtype=torch.float32, device="cuda")
+        gm.debug_teacher_forced_logits(torch.from_numpy(tgt[:rows].copy()).cuda(), logits)
+        err = np.abs(logits.cpu().numpy()[:, :, :d] - want[:rows]) / np.maximum(np.abs(want[:rows]), 1.0)
+        print(f"{rows} rows: worst element {err.max():.1e}")
+        assert err.max() <= 6e-6, rows
+    gm.close()
+
+
 @pytest.mark.parametrize("ffn", [0, 512])
 @pytest.mark.parametrize("what", ["plain", "bias", "columns"])
 def test_folded_self_values_are_as_exact_as_the_others(nt, oracle, torch_cuda, what, ffn):
