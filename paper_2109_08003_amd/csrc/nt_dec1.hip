@@ -903,6 +903,7 @@ __global__ __launch_bounds__(NWAVES * 64) void dec1_kernel(Dec1Args a) {
     *(halfNE *)(a.h_hi + (long)r * D + lane * NE) = hi;
     *(halfNE *)(a.h_hi + a.h_lo_offset + (long)r * D + lane * NE) = lo;
     if (lane == 0) a.lo_norm[r] = sqrtf(tail2) * 1.0001f;  // rounded up: it is used as a bound
+    if (a.scout.codes) scout_emit<NE>(y, a.scout, r, lane);
   }
 }
 

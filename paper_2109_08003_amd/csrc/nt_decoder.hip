@@ -568,6 +568,7 @@ __global__ __launch_bounds__(DC_WAVES * 64) void dec_chain_kernel(DecChainArgs a
         *(halfNE *)(a.h_hi + (long)m * K + lane * NE) = hi;
         *(halfNE *)(a.h_hi + a.h_lo_offset + (long)m * K + lane * NE) = lo;
         if (a.lo_norm && lane == 0) a.lo_norm[m] = sqrtf(tail2) * 1.0001f;
+        if (a.scout.codes) scout_emit<NE>(xv[i], a.scout, m, lane);
       }
     }
     return;

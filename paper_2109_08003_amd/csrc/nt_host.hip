@@ -80,8 +80,8 @@ constexpr bool kCrossF32 = false;
 // Model widths without the fused decoder kernels: projections with at most this many active rows use the
 // one-round-trip kernel.
 constexpr int kSkinnyMaxRows = 128;
-// The output projection uses the certified single-pass arg-max from this many active rows on; below,
-// the step is bound by the weight stream and the two-plane kernel costs the same.
+// Where only the tiled arg-max kernels fit, their certified single pass is used from this many active rows on; below, the step is
+// bound by the weight stream and a pass with both planes costs the same.
 constexpr int kCertMinRows = 512;
 // Batches nt_translate_batch keeps in flight when the configuration does not say (pipeline_lanes = 0).
 constexpr int kDefaultLanes = 4;
@@ -190,6 +190,11 @@ struct nt_model {
   const _Float16 *E = nullptr, *Wout = nullptr;
   const _Float16 *Wout_frag = nullptr;  // the output matrix in MFMA fragment order (streaming arg-max kernels)
   nt::VocabWeights vw;
+  // scout of the output layer: packed matrix, and in the arena codes and constants of the current step's rows, and its scratch
+  void *Wscout = nullptr;  // an allocation of its own
+  int8_t *scout_codes = nullptr;
+  float4 *scout_rc = nullptr;
+  void *scout_scratch = nullptr;
   // 8-bit output layer (q8_output): codes in MFMA fragment order, per-entry constants
   const int8_t *Wq8 = nullptr;
   const void *q8_consts = nullptr;
@@ -199,7 +204,7 @@ struct nt_model {
   const float *pe = nullptr;
   nt::Dec1Table dec_table{};  // Q | K | V of the first decoder layer by token and position (decoder layers in one launch)
   float *d_table = nullptr;   // its allocation
-  size_t table_bytes = 0;
+  size_t table_bytes = 0, scout_bytes = 0;
   std::vector<EncLayer> enc;
   std::vector<DecLayer> dec;
   LN enc_final, dec_final;
@@ -231,7 +236,7 @@ struct nt_model {
   unsigned long long *pk = nullptr;
   float *ps = nullptr, *lo_norm = nullptr;             // certified arg-max: runner-up partials, tail norms
   int32_t *tok = nullptr, *slot_of_row = nullptr, *cert_list = nullptr;
-  unsigned long long *final_key = nullptr, *need_mask = nullptr;
+  unsigned long long *final_key = nullptr;
   bool enc_out_valid = false;  // false while the encoder output lives only inside the fused cross projections
   float w_norm_max = 0.f;                              // max_v ||W_out[v,:]||, or huge while nothing may be certified
   float w_norm_true = 0.f;                             // the value computed at load
@@ -397,14 +402,16 @@ int alloc_lane_state(nt_model *m, hipStream_t s) {
                o_ctx32 = cv.take((size_t)Br * d * 4), o_u32 = cv.take((size_t)Br * std::max(Fd, 1) * 4),
                o_pk = cv.take((size_t)m->pk_elems * 8), o_ps = cv.take((size_t)m->pk_elems * 4),
                o_lon = cv.take((size_t)Br * 4), o_tok = cv.take((size_t)Br * 4), o_slot = cv.take((size_t)Br * 4),
-               o_clist = cv.take((size_t)Br * 4), o_fkey = cv.take((size_t)Br * 8), o_nmask = cv.take((size_t)Br * 8),
+               o_clist = cv.take((size_t)Br * 4), o_fkey = cv.take((size_t)Br * 8), 
                o_len = cv.take((size_t)Br * 4), o_flags = cv.take(64),
                o_src = cv.take((size_t)Mt * 4), o_lin = cv.take((size_t)Br * 4), o_out = cv.take((size_t)m->self_positions * 4),
                o_org0 = cv.take((size_t)Br * 4), o_org1 = cv.take((size_t)Br * 4), o_ey = cv.take((size_t)Br * 4),
                o_etok = cv.take((size_t)Br * 4), o_cap = cv.take((size_t)Br * 4), o_olen = cv.take((size_t)Br * 4),
                o_kvn = cv.take((size_t)Br * 2 * d * 4),
                o_q8c = cv.take(cfg->q8_output ? (size_t)Br * d : 16), o_q8s = cv.take((size_t)Br * 4),
-               o_q8z = cv.take((size_t)Br * 4), o_q8a = cv.take((size_t)Br * 4);
+               o_q8z = cv.take((size_t)Br * 4), o_q8a = cv.take((size_t)Br * 4),
+               o_sco = cv.take(m->Wscout ? (size_t)Br * d : 16), o_scr = cv.take(m->Wscout ? (size_t)Br * 16 : 16),
+               o_scs = cv.take(m->Wscout ? nt::vocab_scout_scratch_bytes(cfg->vocab, (int)Br) : 16);
   m->arena_bytes = cv.off;
   if (hipMalloc((void **)&m->d_arena, m->arena_bytes) != hipSuccess) return fail(NT_ENOMEM, "hipMalloc of %zu arena bytes failed", m->arena_bytes);
   char *A = m->d_arena;
@@ -419,7 +426,7 @@ int alloc_lane_state(nt_model *m, hipStream_t s) {
   m->u32 = at<float>(A, o_u32); m->pk = at<unsigned long long>(A, o_pk); m->len = at<int32_t>(A, o_len);
   m->ps = at<float>(A, o_ps); m->lo_norm = at<float>(A, o_lon); m->tok = at<int32_t>(A, o_tok);
   m->slot_of_row = at<int32_t>(A, o_slot); m->cert_list = at<int32_t>(A, o_clist);
-  m->final_key = at<unsigned long long>(A, o_fkey); m->need_mask = at<unsigned long long>(A, o_nmask);
+  m->final_key = at<unsigned long long>(A, o_fkey);
   m->flags = at<int32_t>(A, o_flags); m->d_src = at<int32_t>(A, o_src); m->d_len_in = at<int32_t>(A, o_lin);
   m->d_out = at<int32_t>(A, o_out);
   m->origin[0] = at<int32_t>(A, o_org0); m->origin[1] = at<int32_t>(A, o_org1); m->eos_y = at<int32_t>(A, o_ey);
@@ -427,6 +434,7 @@ int alloc_lane_state(nt_model *m, hipStream_t s) {
   m->kv_new = at<float>(A, o_kvn);
   m->q8_codes = at<int8_t>(A, o_q8c); m->q8_scale = at<float>(A, o_q8s); m->q8_c = at<int32_t>(A, o_q8z);
   m->q8_sa = at<int32_t>(A, o_q8a);
+  m->scout_codes = at<int8_t>(A, o_sco); m->scout_rc = at<float4>(A, o_scr); m->scout_scratch = A + o_scs;
   HIP_TRY(hipMemsetAsync(m->d_arena, 0, m->arena_bytes, s));  // load time only: no kernel ever reads an undefined word
   for (auto &st : m->stage) {
     if (hipHostMalloc((void **)&st.h_src, (size_t)Mt * 4) != hipSuccess || hipHostMalloc((void **)&st.h_len, (size_t)Br * 4) != hipSuccess ||
@@ -494,7 +502,7 @@ int nt_debug_set_cert_distrust(nt_model *m, int on) {
 
 int64_t nt_device_bytes(const nt_model *m) {
   if (!m) return 0;
-  int64_t n = (int64_t)(m->w_bytes + m->table_bytes + m->arena_bytes);
+  int64_t n = (int64_t)(m->w_bytes + m->table_bytes + m->scout_bytes + m->arena_bytes);
   for (const nt_model *ln : m->lanes) n += (int64_t)ln->arena_bytes;
   return n;
 }
@@ -515,6 +523,7 @@ void nt_free(nt_model *m) {
   if (m->lane_start) (void)hipEventDestroy(m->lane_start);
   if (m->d_w && m->owns_weights) (void)hipFree(m->d_w);
   if (m->d_table && m->owns_weights) (void)hipFree(m->d_table);
+  if (m->Wscout && m->owns_weights) (void)hipFree(m->Wscout);
   if (m->d_arena) (void)hipFree(m->d_arena);
   for (auto &st : m->stage) {
     if (st.done) (void)hipEventDestroy(st.done);
@@ -783,6 +792,11 @@ int nt_load_weights(const nt_config *cfg, const void *h_blob_fp16, size_t blob_b
     m->dec_table = nt::Dec1Table{m->d_table, parts, cfg->max_len};
   }
   m->vw.Wt = m->Wout; m->vw.Wp = m->Wout_frag; m->vw.N = V; m->vw.K = d;
+  if (m->Wout_frag && !cfg->q8_output) {
+    m->scout_bytes = nt::vocab_scout_bytes(V, d);
+    if (hipMalloc(&m->Wscout, m->scout_bytes) != hipSuccess) return fail(NT_ENOMEM, "hipMalloc of %zu bytes failed", m->scout_bytes);
+    HIP_TRY(nt::vocab_scout_build(m->Wout, V, d, m->Wscout, s));
+  }
   {  // largest row norm of the output matrix, rounded up (bound used by the certified arg-max)
     const _Float16 *Wo = (const _Float16 *)h_blob_fp16 + (cfg->tie_output ? 0 : (int64_t)V * d);
     double mx = 0.0;
@@ -1110,6 +1124,12 @@ int decode_step(nt_model *m, DecodeCursor &cu, hipStream_t s) {
       return NT_OK;
     };
     int rc;
+    // The scout's sums run in another order than the wide kernel's: chosen as above.  (The tiled kernels' certified form gives the
+    // full pass's result at any row count.)
+    const bool wide = rows_for_choice <= nt::kVocabWideRows;
+    const bool scouted = nt::vocab_scouted(m->vw, wide) && m->Wscout;
+    const bool certified = !d_logits && !c.q8_output && (scouted || (nt::vocab_tiled(m->vw) && R >= kCertMinRows));
+    const nt::ScoutOut scout_out = certified && scouted ? nt::ScoutOut{m->scout_codes, m->scout_rc} : nt::ScoutOut{};
     // final hidden state as a head/tail plane pair (the planes share the a32 buffer)
     _Float16 *h_hi = (_Float16 *)m->a32, *h_lo = h_hi + (long)m->max_rows * d;
     bool final_ln_done = false;
@@ -1166,7 +1186,7 @@ int decode_step(nt_model *m, DecodeCursor &cu, hipStream_t s) {
           }
           if (to_final) {
             at.lnf = nt::GemmLayerNorm{m->dec_final.g, m->dec_final.b, lne};
-            at.h_hi = h_hi; at.h_lo_offset = (long)m->max_rows * d; at.lo_norm = m->lo_norm;
+            at.h_hi = h_hi; at.h_lo_offset = (long)m->max_rows * d; at.lo_norm = m->lo_norm; at.scout = scout_out;
             final_ln_done = true;
           }
           const double ffn_flops = ffn_inside ? 4 * Rd * dd * F : 0.0;
@@ -1218,7 +1238,7 @@ int decode_step(nt_model *m, DecodeCursor &cu, hipStream_t s) {
         f1.dst_lo_offset = u_planes ? lo_rows * F : 0;
         if (o_to_final) {
           nt::DecChainArgs ch = chain_from(L.cross.Wo_p, L.cross.bo, m->dec_final);
-          ch.write_z = 0; ch.h_hi = h_hi; ch.h_lo_offset = (long)m->max_rows * d; ch.lo_norm = m->lo_norm;
+          ch.write_z = 0; ch.h_hi = h_hi; ch.h_lo_offset = (long)m->max_rows * d; ch.lo_norm = m->lo_norm; ch.scout = scout_out;
           KT(K_DEC_O_LN_OUT, gemm_bytes(Rd, d, d, true), 2 * Rd * dd * dd, nt::launch_dec_chain(ch, d, true, s));
           final_ln_done = true;
         } else if (o_to_ffn) {
@@ -1234,7 +1254,7 @@ int decode_step(nt_model *m, DecodeCursor &cu, hipStream_t s) {
           if (fused && u_planes && F == d && last && !c.q8_output) {  // second FFN matrix + residual + final LayerNorm
             nt::DecChainArgs ch = chain_from(L.ffn.W2_p, L.ffn.b2, m->dec_final);
             ch.A_hi = (const _Float16 *)m->u32; ch.A_lo = ch.A_hi + lo_rows * F; ch.lda = F;
-            ch.write_z = 0; ch.h_hi = h_hi; ch.h_lo_offset = (long)m->max_rows * d; ch.lo_norm = m->lo_norm;
+            ch.write_z = 0; ch.h_hi = h_hi; ch.h_lo_offset = (long)m->max_rows * d; ch.lo_norm = m->lo_norm; ch.scout = scout_out;
             KT(K_DEC_O_LN_OUT, gemm_bytes(Rd, F, d, true), 2 * Rd * dd * F, nt::launch_dec_chain(ch, d, true, s));
             final_ln_done = true;
           } else if ((rc = dec_gemm(K_GEMM_DEC_FFN, m->u32, F, L.ffn.W2, u_planes ? L.ffn.W2_p : nullptr, d, nullptr, f2))) return rc;
@@ -1263,21 +1283,21 @@ int decode_step(nt_model *m, DecodeCursor &cu, hipStream_t s) {
     if (!final_ln_done)
       KT(K_LN_DEC, Rd * dd * 8, 8 * Rd * dd,
          nt::launch_layer_norm(m->z, R, d, m->dec_final.g, m->dec_final.b, lne, h_hi, nt::OUT_PLANES,
-                               (long)m->max_rows * d, s, m->lo_norm));
+                               (long)m->max_rows * d, s, m->lo_norm, scout_out));
     if (d_logits) {
       nt::GemmEpilogue e;
       e.dst0 = d_logits + (long)t * V; e.ld0 = (long)T * V; e.n_split = V;
       KT(K_GEMM_LOGITS, gemm_bytes(Rd, dd, V, false), 2 * Rd * dd * V,
          nt::launch_gemm(nt::A_PLANES, true, h_hi, h_lo, d, m->Wout, R, V, d, e, s));
     } else {
-      cu.prev_cert = R >= kCertMinRows;
-      const bool wide = rows_for_choice <= nt::kVocabWideRows;
+      cu.prev_cert = certified;
       const int np_ = nt::vocab_argmax_partials(m->vw, R, cu.prev_cert, wide);
       if (cu.prev_cert)
-        KT(K_VOCAB_ARGMAX, (double)V * dd * 2 + Rd * dd * 4 + Rd * np_ * 8, 2 * Rd * dd * V,
-           nt::launch_vocab_argmax_certified(h_hi, h_lo, d, m->vw, R, m->lo_norm, m->w_norm_max, m->pk, m->ps,
-                                             m->tok, m->slot_of_row, m->cert_list, m->flags + 4, m->final_key, m->need_mask, s));
-      else  // below the certified variant's row count the step is bound by the stream of the output matrix
+        KT(K_VOCAB_ARGMAX, scouted ? (double)V * dd + Rd * dd * 5 + Rd * V * 0.5 : (double)V * dd * 2 + Rd * dd * 4 + Rd * np_ * 8, 2 * Rd * dd * V,
+           nt::launch_vocab_argmax_certified(nt::VocabScout{m->Wscout, m->scout_codes, m->scout_rc, m->scout_scratch}, h_hi, h_lo, d, m->vw,
+                                             R, m->lo_norm, m->w_norm_max, m->pk, m->ps, m->tok, m->slot_of_row, m->cert_list, m->flags + 4,
+                                             m->final_key, s));
+      else
         KT(K_VOCAB_ARGMAX_SMALL, (double)V * dd * 2 + Rd * dd * 4 + Rd * np_ * 8, 2 * Rd * dd * V,
            nt::launch_vocab_argmax(h_hi, h_lo, d, m->vw, R, m->pk, wide, s));
       cu.partials_prev = np_;

@@ -131,39 +131,101 @@ size_t vocab_pack_bytes(int N, int K);
 // host: dst[vocab_pack_bytes] <- fragment order of Wt [N][K]
 void vocab_pack(const _Float16 *Wt, int N, int K, _Float16 *dst);
 
-// n_partials of the launch configuration used with M rows (exact: head + tail planes; certified:
-// head plane first).
-// wide: up to kVocabWideRows rows take a kernel of its own (exact only; its sums run in another order, so a caller whose M
-// depends on timing decides by a row count that does not, and nobody by what else is running).
-constexpr int kVocabWideRows = 64;
+// n_partials of the launch configuration used with M rows (exact: head + tail planes; certified: tiled kernels' head plane
+// first, none in the scout's).
+// wide: up to kVocabWideRows rows take a kernel of its own, more the scout (whose sums run in another order, so a caller whose M
+// depends on timing decides by a row count that does not, and nobody by what else is running).  A decoder step of 32 / 48 / 64 rows
+// alone takes 21.4 / 24.6 / 26.1 us with the wide kernel and 24.5 / 24.9 / 25.3 with the scout; a 4,096-token budget, whose lanes
+// share the chip, 21.9 ms with the line at 64 rows and 21.1 at 8.  In between.
+constexpr int kVocabWideRows = 40;
 int vocab_argmax_partials(const VocabWeights &w, int M, bool certified, bool wide);
 // h is a head/tail pair of fp16 planes.
 hipError_t launch_vocab_argmax(const _Float16 *h, const _Float16 *h_lo, long ldh, const VocabWeights &w, int M,
                                unsigned long long *pk, bool wide, hipStream_t s);
 
-// Same result as launch_vocab_argmax, usually at half the MFMA work: a head-only pass whose winner is
-// certified against a rigorous bound on the contribution of the tail (lo_norm[m] = ||tail of row m||,
+// Arg-max of many rows (nt_vocab_scout.hip): an 8-bit pass with a rigorous bound leaves a few candidates per row, which get
+// exact logits.  K = 256 / 512.
+struct VocabScout {
+  const void *matrix;   // vocab_scout_build of the output matrix
+  int8_t *codes;        // [rows][K] and
+  float4 *row_consts;   // [rows]: written by the kernel that writes the hidden state (scout_round)
+  void *scratch;        // vocab_scout_scratch_bytes
+};
+size_t vocab_scout_bytes(int N, int K);
+// dst [vocab_scout_bytes] <- W [N][K], both on the device; returns when it is done (load time)
+hipError_t vocab_scout_build(const _Float16 *W, int N, int K, void *dst, hipStream_t s);
+size_t vocab_scout_scratch_bytes(int N, int rows);
+// Where a hidden state goes besides its planes (codes == nullptr: nowhere)
+struct ScoutOut {
+  int8_t *codes = nullptr;
+  float4 *row_consts = nullptr;
+};
+#ifdef __HIPCC__
+// One row, NE elements per lane of a wave: codes in [-127, 127] and {scale, ||y - scale code||, ||scale code||, 0}, the norms
+// rounded up (they are bounds).
+template <int NE>
+__device__ __forceinline__ float4 scout_round(const float (&y)[NE], int (&code)[NE]) {
+  float top = 0.f;
+#pragma unroll
+  for (int e = 0; e < NE; e++) top = fmaxf(top, fabsf(y[e]));
+#pragma unroll
+  for (int m = 32; m >= 1; m >>= 1) top = fmaxf(top, __shfl_xor(top, m, 64));
+  const float scale = top > 0.f ? top / 127.f : 1.f, inv = 1.f / scale;
+  float e2 = 0.f, a2 = 0.f;
+#pragma unroll
+  for (int e = 0; e < NE; e++) {
+    const float c = fminf(fmaxf(rintf(y[e] * inv), -127.f), 127.f), a = c * scale;
+    code[e] = (int)c;
+    e2 += (y[e] - a) * (y[e] - a);
+    a2 += a * a;
+  }
+#pragma unroll
+  for (int m = 32; m >= 1; m >>= 1) {
+    const float o = __shfl_xor(e2, m, 64), q = __shfl_xor(a2, m, 64);
+    e2 += o;
+    a2 += q;
+  }
+  return make_float4(scale, sqrtf(e2) * 1.001f, sqrtf(a2) * 1.0001f, 0.f);
+}
+// the same for a row whose lanes hold consecutive elements
+template <int NE>
+__device__ __forceinline__ void scout_emit(const float (&y)[NE], const ScoutOut &o, long row, int lane) {
+  int code[NE];
+  const float4 rc = scout_round<NE>(y, code);
+#pragma unroll
+  for (int e = 0; e < NE; e += 4)
+    *(unsigned int *)(o.codes + row * (NE * 64) + lane * NE + e) =
+        (code[e] & 0xFF) | (code[e + 1] & 0xFF) << 8 | (code[e + 2] & 0xFF) << 16 | (unsigned int)code[e + 3] << 24;
+  if (lane == 0) o.row_consts[row] = rc;
+}
+#endif
+// Results: tok[m], and slot_of_row[m] = -1.  distrust: every row has every logit computed.
+hipError_t launch_vocab_scout(const VocabScout &v, const _Float16 *h, const _Float16 *h_lo, long ldh, const VocabWeights &w, int M,
+                              bool distrust, int32_t *tok, int32_t *slot_of_row, hipStream_t s);
+
+// Same result as launch_vocab_argmax for many rows, usually at less work: the scout above, or (tiled kernels) a head-only
+// pass whose winner is certified against a rigorous bound on the contribution of the tail (lo_norm[m] = ||tail of row m||,
 // w_norm_max = max_v ||W_out[v,:]||); rows that cannot be certified are recomputed with both planes.
 // Results: tok[m] when slot_of_row[m] < 0, else the key in final_key[slot_of_row[m]].
-// *count must be 0 when the call starts (the step-begin kernel clears it).  need_mask [M]: scratch, per recompute
-// slot the ranges of the vocabulary that can still hold the arg-max (the recompute skips the others).
-hipError_t launch_vocab_argmax_certified(const _Float16 *h, const _Float16 *h_lo, long ldh, const VocabWeights &w, int M,
-                                         const float *lo_norm, float w_norm_max, unsigned long long *pk, float *ps,
-                                         int32_t *tok, int32_t *slot_of_row, int32_t *list, int32_t *count,
-                                         unsigned long long *final_key, unsigned long long *need_mask, hipStream_t s);
+// *count must be 0 when the call starts (the start of the step clears it).  list [M]: scratch of the recompute.
+bool vocab_tiled(const VocabWeights &w);               // only the tiled kernels fit (or are forced)
+bool vocab_scouted(const VocabWeights &w, bool wide);  // the scout is the kernel for this choice
+hipError_t launch_vocab_argmax_certified(const VocabScout &v, const _Float16 *h, const _Float16 *h_lo, long ldh,
+                                         const VocabWeights &w, int M, const float *lo_norm, float w_norm_max,
+                                         unsigned long long *pk, float *ps, int32_t *tok, int32_t *slot_of_row, int32_t *list,
+                                         int32_t *count, unsigned long long *final_key, hipStream_t s);
 
-// the tiled implementations (nt_gemm.hip) and the certification kernel shared by both
+// the tiled implementations (nt_gemm.hip) and their certification kernel
 int vocab_argmax_partials_tiled(int M, int N);
 hipError_t launch_vocab_argmax_tiled(const _Float16 *h, const _Float16 *h_lo, long ldh, const _Float16 *Wt, int M, int N,
                                      int K, unsigned long long *pk, hipStream_t s);
 hipError_t launch_vocab_argmax_certified_tiled(const _Float16 *h, const _Float16 *h_lo, long ldh, const _Float16 *Wt, int M,
                                                int N, int K, const float *lo_norm, float w_norm_max,
                                                unsigned long long *pk, float *ps, int32_t *tok, int32_t *slot_of_row,
-                                               int32_t *list, int32_t *count, unsigned long long *final_key,
-                                               unsigned long long *need_mask, hipStream_t s);
+                                               int32_t *list, int32_t *count, unsigned long long *final_key, hipStream_t s);
 hipError_t launch_argmax_select(const unsigned long long *pk, const float *ps, int n_partials, int M, const float *lo_norm,
                                 float w_norm_max, int32_t *tok, int32_t *slot_of_row, int32_t *list, int32_t *count,
-                                unsigned long long *final_key, unsigned long long *need_mask, hipStream_t s);
+                                unsigned long long *final_key, hipStream_t s);
 
 // ---- 8-bit output layer fused with the row arg-max (nt_vocab_q8.hip; Sec. 3.2, Eq. 3-6) ----------------------------
 bool vocab_q8_supported(int K);
@@ -196,9 +258,9 @@ hipError_t launch_embed_src(const int32_t *src, const int32_t *len, int32_t *len
 
 // out = gamma * (x - mean) * r + beta per row of d, r as LnEps says.
 enum OutMode { OUT_F16 = 0, OUT_F32 = 1, OUT_PLANES = 2 };  // OUT_PLANES: fp16 head at out, tail at out + lo_offset
-// lo_norm (OUT_PLANES only, optional): receives the Euclidean norm of every row's tail plane.
+// lo_norm (OUT_PLANES only, optional): receives the Euclidean norm of every row's tail plane.  scout (OUT_PLANES, d = 256 / 512).
 hipError_t launch_layer_norm(const float *x, int M, int d, const float *gamma, const float *beta, LnEps eps,
-                             void *out, int out_mode, long lo_offset, hipStream_t s, float *lo_norm = nullptr);
+                             void *out, int out_mode, long lo_offset, hipStream_t s, float *lo_norm = nullptr, ScoutOut scout = ScoutOut());
 
 // out[i] = hi[i] + lo[i] (debug readback of a head/tail plane pair)
 hipError_t launch_planes_to_float(const _Float16 *hi, const _Float16 *lo, float *out, long n, hipStream_t s);
@@ -277,6 +339,7 @@ struct DecChainArgs {
   _Float16 *h_hi;
   long h_lo_offset;
   float *lo_norm;
+  ScoutOut scout;
   const _Float16 *W2p;
   int N2;
   GemmEpilogue e2;
@@ -416,6 +479,7 @@ struct Dec1Args {
   _Float16 *h_hi;
   long h_lo_offset;
   float *lo_norm;
+  ScoutOut scout;
 };
 hipError_t launch_dec1(const Dec1Args &a, int d, hipStream_t s);
 constexpr int kDec1FoldRows = 512, kDec1FoldTokens = 32768;

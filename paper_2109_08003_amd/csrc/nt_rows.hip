@@ -109,7 +109,7 @@ hipError_t launch_embed_src(const int32_t *src, const int32_t *len, int32_t *len
 template <int MODE, int NE>
 __global__ __launch_bounds__(256) void layer_norm_kernel(const float *x, int M, int d, const float *gamma,
                                                          const float *beta, LnEps eps, void *out, long lo_offset,
-                                                         float *lo_norm) {
+                                                         float *lo_norm, ScoutOut scout) {
   const int lane = threadIdx.x & 63;
   const long r = (long)blockIdx.x * 4 + (threadIdx.x >> 6);
   if (r >= M) return;
@@ -138,23 +138,35 @@ __global__ __launch_bounds__(256) void layer_norm_kernel(const float *x, int M, 
     tail2 = wave_sum(tail2);
     if (lane == 0) lo_norm[r] = sqrtf(tail2) * 1.0001f;  // rounded up: it is used as an upper bound
   }
+  if constexpr (MODE == OUT_PLANES && (NE == 4 || NE == 8)) {
+    if (scout.codes) {
+      float y[NE];
+      int code[NE];
+#pragma unroll
+      for (int i = 0; i < NE; i++) y[i] = v[i];
+      const float4 rc = scout_round<NE>(y, code);
+#pragma unroll
+      for (int i = 0; i < NE; i++) scout.codes[r * d + lane + 64 * i] = (int8_t)code[i];
+      if (lane == 0) scout.row_consts[r] = rc;
+    }
+  }
 }
 
 hipError_t launch_layer_norm(const float *x, int M, int d, const float *gamma, const float *beta, LnEps eps,
-                             void *out, int out_mode, long lo_offset, hipStream_t s, float *lo_norm) {
+                             void *out, int out_mode, long lo_offset, hipStream_t s, float *lo_norm, ScoutOut scout) {
   if (M <= 0) return hipSuccess;
   dim3 grid((M + 3) / 4), block(256);
 #define NT_CASE(NE_)                                                                                             \
   case NE_:                                                                                                      \
     if (out_mode == OUT_F32)                                                                                     \
       hipLaunchKernelGGL((layer_norm_kernel<OUT_F32, NE_>), grid, block, 0, s, x, M, d, gamma, beta, eps, out,     \
-                         lo_offset, lo_norm);                                                                    \
+                         lo_offset, lo_norm, scout);                                                                    \
     else if (out_mode == OUT_PLANES)                                                                             \
       hipLaunchKernelGGL((layer_norm_kernel<OUT_PLANES, NE_>), grid, block, 0, s, x, M, d, gamma, beta, eps, out,  \
-                         lo_offset, lo_norm);                                                                    \
+                         lo_offset, lo_norm, scout);                                                                    \
     else                                                                                                         \
       hipLaunchKernelGGL((layer_norm_kernel<OUT_F16, NE_>), grid, block, 0, s, x, M, d, gamma, beta, eps, out,     \
-                         lo_offset, lo_norm);                                                                    \
+                         lo_offset, lo_norm, scout);                                                                    \
     break;
   switch (ne_case(d)) { NT_CASE(4) NT_CASE(8) NT_CASE(16) NT_CASE(0) }
 #undef NT_CASE

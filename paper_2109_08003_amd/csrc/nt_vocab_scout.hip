@@ -1,0 +1,563 @@
+// Output projection with row arg-max for many rows (gfx950): an 8-bit scout pass over the whole vocabulary, exact logits for the
+// entries it cannot rule out.
+//
+// Greedy search wants one id per row, and all but a few of the 32,000 logits lose by far.  The scout multiplies 8-bit codes of the
+// states with 8-bit codes of the matrix on the int8 matrix cores - twice the rate and half the bytes of fp16 - and what it leaves
+// out is bounded: with x = a + e (a the rounded state, e the rest) and w = b + f likewise,
+//     x . w - a . b = e . w + a . f,     |x . w - a . b| <= ||e|| ||w|| + ||a|| ||f||        (Cauchy-Schwarz)
+// where ||e||, ||a|| come per row from the kernel that writes the state and ||w||, ||f|| per strip from load time.  An entry whose
+// scout logit plus its bound stays below the best scout logit minus that one's bound is not the arg-max.  What is left (16 of
+// 32,000 entries per row on flat random logits, d = 512; 5 of 4,000 at d = 256) gets its logit from the state's head + tail planes
+// and the fp16 matrix in fp32, and the largest of these wins, lowest id on ties: the same tokens as a pass over everything with
+// both planes, but for ties within fp32 rounding.  A row with more than kPickCap candidates has every logit computed.
+//
+// The matrix is centred before it is rounded: its mean row adds the same to every logit of a row, so it changes no arg-max, and
+// a common offset of the entries would only widen the range of the codes.  Entries are sorted by their largest element, so that the
+// 64 entries of a strip, which share one scale, are alike.
+//
+// The scout has the shape of the 8-bit output layer's kernel (nt_vocab_q8.hip): 128 rows of codes in the LDS, fragments of the
+// matrix through a ring of registers, a wave owns a strip of 64 entries for all rows of the tile, a lane owns a row of each 32-row
+// block.  A lane's 32 products of a strip are one group (|sum| <= 127^2 512 < 2^23): the largest and the runner-up leave with their
+// places and a bound on the third, in two integers, so that only a group that may hold three candidates (one row in a thousand)
+// has all its entries computed; four instructions per product.
+//
+// Measured, d = 512, 32,000 entries: scout 30.5 us (2.0 POP/s) and pick 13.5 us at 1,460 rows on average (40,000 sentences, 65,536-token budget),
+// 11.5 and 9.2 at 400, 8.0 and 8.9 at 260, where a pass over the head plane that certified its winners, the certification and the recompute
+// of the rest took 61, 5.5 and 11 us at 1,900 rows, and a pass with both planes 14 to 28 us for 65 to 512.  The scout is bound by the matrix
+// cores (operand loads, folds and the ends of strips take a good half, as in nt_vocab_q8.hip), the pick by its chain of dependent loads.
+// One scale per strip instead of per entry costs 16 candidates a row instead of 13 and saves two instructions per product.
+#include "nt_kernels.h"
+
+#include <algorithm>
+#include <cmath>
+#include <cstring>
+#include <mutex>
+#include <numeric>
+#include <type_traits>
+#include <vector>
+
+namespace nt {
+
+typedef int i32x4 __attribute__((ext_vector_type(4)));
+typedef int i32x2 __attribute__((ext_vector_type(2)));
+typedef int i32x16 __attribute__((ext_vector_type(16)));
+typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+typedef _Float16 half8 __attribute__((ext_vector_type(8)));
+
+constexpr int SC_ROWS = 128, SC_WAVES = 8;
+constexpr int SC_NONE = -(1 << 30);  // below every packed product (places past the end of the vocabulary)
+constexpr int SC_LOW = -(1 << 23);   // below every product
+constexpr int SC_APART = 13;         // the distance to the third leaves in units of 2^13
+constexpr int kPickCap = 256;        // candidates of a row
+
+static size_t scout_code_bytes(int N, int K) { return (size_t)((N + 63) / 64) * 64 * K; }
+// codes, then per strip {scale, largest ||w||, largest ||f||, unused}, then the id of every place (-1: none), then the matrix's rows in
+// the order of the places (the exact logits then need no look-up before their row)
+size_t vocab_scout_bytes(int N, int K) { return scout_code_bytes(N, K) + (size_t)((N + 63) / 64) * (16 + 64 * 4 + 64 * (size_t)K * 2); }
+
+// ---- at load, on the device (50 MB for 32,000 x 512; the same loops on the host took 350 ms of a load of 200) ----------------------
+constexpr int SP_ROWS = 256;  // rows per partial sum of the mean
+
+__global__ __launch_bounds__(512) void scout_sum_kernel(const _Float16 *W, int N, int K, double *sums) {
+  const int k = threadIdx.x, v0 = blockIdx.x * SP_ROWS, v1 = v0 + SP_ROWS < N ? v0 + SP_ROWS : N;
+  double s = 0.0;
+  for (int v = v0; v < v1; v++) s += (double)(float)W[(long)v * K + k];
+  sums[(long)blockIdx.x * K + k] = s;
+}
+__global__ __launch_bounds__(512) void scout_mean_kernel(const double *sums, int n, int N, int K, float *mean) {
+  double s = 0.0;
+  for (int i = 0; i < n; i++) s += sums[(long)i * K + threadIdx.x];
+  mean[threadIdx.x] = (float)(s / (double)N);
+}
+// largest centred element of every row, a wave each
+__global__ __launch_bounds__(256) void scout_top_kernel(const _Float16 *W, int N, int K, const float *mean, float *top) {
+  const int lane = threadIdx.x & 63, v = blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (v >= N) return;
+  float m = 0.f;
+  for (int k = lane; k < K; k += 64) m = fmaxf(m, fabsf((float)W[(long)v * K + k] - mean[k]));
+#pragma unroll
+  for (int x = 32; x >= 1; x >>= 1) m = fmaxf(m, __shfl_xor(m, x, 64));
+  if (lane == 0) top[v] = m;
+}
+// one strip per workgroup, sixteen rows per wave
+__global__ __launch_bounds__(256) void scout_pack_kernel(const _Float16 *W, int N, int K, const float *mean, const float *top, const int32_t *order,
+                                                         int8_t *codes, float4 *consts, int32_t *ids, _Float16 *sorted) {
+  __shared__ float norms[2][4];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, s = blockIdx.x, KS = K / 32;
+  const int n = N - s * 64 < 64 ? N - s * 64 : 64;
+  const float largest = top[order[s * 64 + n - 1]], scale = largest > 0.f ? largest / 127.f : 1.f, inv = 1.f / scale;
+  float wn = 0.f, fn = 0.f;
+  for (int i = wave * 16; i < wave * 16 + 16; i++) {
+    const int v = i < n ? order[s * 64 + i] : -1;
+    if (lane == 0) ids[s * 64 + i] = v;
+    double w2 = 0.0, f2 = 0.0;
+    for (int k = lane; k < K; k += 64) {
+      const _Float16 w = v >= 0 ? W[(long)v * K + k] : (_Float16)0.f;
+      const float x = v >= 0 ? (float)w - mean[k] : 0.f;
+      const float c = fminf(fmaxf(rintf(x * inv), -127.f), 127.f);
+      const double f = (double)x - (double)c * (double)scale;
+      w2 += (double)x * (double)x;
+      f2 += f * f;
+      sorted[((long)s * 64 + i) * K + k] = w;
+      // the fragment order of nt_vocab_q8.hip
+      codes[((((long)s * KS + k / 32) * 2 + i / 32) * 64 + i % 32 + 32 * ((k % 32) / 16)) * 16 + k % 16] = (int8_t)(int)c;
+    }
+#pragma unroll
+    for (int x = 32; x >= 1; x >>= 1) {
+      w2 += __shfl_xor(w2, x, 64);
+      f2 += __shfl_xor(f2, x, 64);
+    }
+    wn = fmaxf(wn, (float)(sqrt(w2) * 1.0001));
+    fn = fmaxf(fn, (float)(sqrt(f2) * 1.0001));
+  }
+  if (lane == 0) norms[0][wave] = wn, norms[1][wave] = fn;
+  __syncthreads();
+  if (threadIdx.x == 0)
+    consts[s] = make_float4(scale, fmaxf(fmaxf(norms[0][0], norms[0][1]), fmaxf(norms[0][2], norms[0][3])),
+                            fmaxf(fmaxf(norms[1][0], norms[1][1]), fmaxf(norms[1][2], norms[1][3])), 0.f);
+}
+
+hipError_t vocab_scout_build(const _Float16 *W, int N, int K, void *dst, hipStream_t s) {
+  if (K != 256 && K != 512) return hipErrorInvalidValue;
+  const int NS = (N + 63) / 64, parts = (N + SP_ROWS - 1) / SP_ROWS;
+  int8_t *codes = (int8_t *)dst;
+  float4 *consts = (float4 *)(codes + scout_code_bytes(N, K));
+  int32_t *ids = (int32_t *)(consts + NS);
+  _Float16 *sorted = (_Float16 *)(ids + 64 * (size_t)NS);
+  char *tmp = nullptr;
+  hipError_t e = hipMalloc((void **)&tmp, (size_t)parts * K * 8 + (size_t)K * 4 + (size_t)N * 8);
+  if (e != hipSuccess) return e;
+  double *sums = (double *)tmp;
+  float *mean = (float *)(sums + (size_t)parts * K), *top = mean + K;
+  int32_t *order = (int32_t *)(top + N);
+  hipLaunchKernelGGL(scout_sum_kernel, dim3(parts), dim3(K), 0, s, W, N, K, sums);
+  hipLaunchKernelGGL(scout_mean_kernel, dim3(1), dim3(K), 0, s, sums, parts, N, K, mean);
+  hipLaunchKernelGGL(scout_top_kernel, dim3((N + 3) / 4), dim3(256), 0, s, W, N, K, mean, top);
+  e = hipGetLastError();
+  std::vector<float> h_top((size_t)N);
+  std::vector<int32_t> h_order((size_t)N);
+  if (e == hipSuccess) e = hipMemcpyAsync(h_top.data(), top, (size_t)N * 4, hipMemcpyDeviceToHost, s);
+  if (e == hipSuccess) e = hipStreamSynchronize(s);
+  std::iota(h_order.begin(), h_order.end(), 0);
+  for (float &t : h_top) t = t == t ? t : INFINITY;  // an order for every matrix
+  std::stable_sort(h_order.begin(), h_order.end(), [&](int32_t a, int32_t b) { return h_top[(size_t)a] < h_top[(size_t)b]; });
+  if (e == hipSuccess) e = hipMemcpyAsync(order, h_order.data(), (size_t)N * 4, hipMemcpyHostToDevice, s);
+  if (e == hipSuccess) {
+    hipLaunchKernelGGL(scout_pack_kernel, dim3(NS), dim3(256), 0, s, W, N, K, mean, top, order, codes, consts, ids, sorted);
+    e = hipGetLastError();
+  }
+  const hipError_t done = hipStreamSynchronize(s);
+  (void)hipFree(tmp);
+  return e != hipSuccess ? e : done;
+}
+
+// ---------------------------------------------------------------------------------------------------------------------
+struct ScSplit {
+  int m_tiles, G, per_xcd;
+};
+static ScSplit sc_split(int M, int NS) {
+  ScSplit p;
+  p.m_tiles = (M + SC_ROWS - 1) / SC_ROWS;
+  p.G = std::max(1, std::min(256 / p.m_tiles, NS));
+  p.per_xcd = (p.m_tiles * p.G + 7) / 8;
+  return p;
+}
+
+// part[m][2 strip + g]: {largest product << 5 | place, runner-up << 8 | min(7, distance to the third >> SC_APART) << 5 | place}
+template <int K>
+__global__ __launch_bounds__(SC_WAVES * 64) void vocab_scout_kernel(const int8_t *__restrict__ codes, int M, const int8_t *__restrict__ Wq,
+                                                                   int N, int m_tiles, int G, int per_xcd, int ns_div_g, int ns_mod_g,
+                                                                   unsigned int m_tiles_magic, i32x2 *__restrict__ part) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  constexpr int LD = K + 16;  // bytes per LDS row: the pad keeps the 16-byte fragment reads conflict-free
+  constexpr int KS = K / 32;
+  constexpr int SL = 4;       // ring of fragment slots per wave (lookahead SL - 1 k-steps)
+  static_assert(KS % SL == 0, "the ring of slots must divide the k-steps of a strip");
+  const int tid = threadIdx.x, lane = tid & 63, li = lane & 31, g = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int total = m_tiles * G;
+  const int idx = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
+  {
+    const int end = ((blockIdx.x & 7) + 1) * per_xcd;
+    if (idx >= (end < total ? end : total)) return;  // uniform over the workgroup
+  }
+  // idx / m_tiles by multiply-high, which stays in scalar registers (exact for idx * m_tiles < 2^32)
+  const int gi = m_tiles_magic ? (int)__umulhi((unsigned int)idx, m_tiles_magic) : idx;
+  const int m0 = (idx - gi * m_tiles) * SC_ROWS;
+  const int NS = (N + 63) >> 6;
+  const int sb0 = gi * ns_div_g + (gi < ns_mod_g ? gi : ns_mod_g);
+  const int sb1 = sb0 + ns_div_g + (gi < ns_mod_g ? 1 : 0);
+
+  const __amdgpu_buffer_rsrc_t wrs = __builtin_amdgcn_make_buffer_rsrc((void *)Wq, 0, NS * 64 * K, 0x00020000);
+  const int wlane = lane * 16;
+  auto wload = [&](int soff, int nb) -> i32x4 {
+    u32x4 t = __builtin_amdgcn_raw_buffer_load_b128(wrs, wlane + nb * 1024, soff, 0);
+    return __builtin_bit_cast(i32x4, t);
+  };
+  i32x4 wb[SL][2];
+  int strip = sb0 + wave;
+  const bool have = strip < sb1;
+  {  // the tile of codes: global memory -> registers -> LDS.  Rows past M repeat row M - 1 (never stored)
+    constexpr int CPR = K / 16, PER_T = SC_ROWS * CPR / (SC_WAVES * 64);
+    u32x4 fr[PER_T];
+#pragma unroll
+    for (int i = 0; i < PER_T; i++) {
+      const int c = tid + SC_WAVES * 64 * i, R = c / CPR, kc = c % CPR;
+      const int m = m0 + R < M ? m0 + R : M - 1;
+      fr[i] = *(const u32x4 *)(codes + (long)m * K + kc * 16);
+    }
+    if (have) {
+#pragma unroll
+      for (int q = 0; q < SL - 1; q++) {
+        wb[q][0] = wload(strip * (KS * 2048) + q * 2048, 0);
+        wb[q][1] = wload(strip * (KS * 2048) + q * 2048, 1);
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < PER_T; i++) {
+      const int c = tid + SC_WAVES * 64 * i, R = c / CPR, kc = c % CPR;
+      *(u32x4 *)(smem + R * LD + kc * 16) = fr[i];
+    }
+  }
+  __syncthreads();
+  if (!have) return;
+
+  i32x16 acc[4][2];
+  const unsigned char *hrow = smem + li * LD + g * 16;
+  int off2 = 64 * LD;  // second base register: the offsets of rows 64.. do not fit the 16-bit immediate
+  asm volatile("" : "+v"(off2));
+  const unsigned char *hrow2 = hrow + off2;
+  i32x4 hf[4];
+#pragma unroll
+  for (int op = 0; op < 4; op++) hf[op] = *(const i32x4 *)((op < 2 ? hrow : hrow2) + (op & 1) * 32 * LD);
+  i32x2 *out = part + (long)(m0 + li) * (2 * NS) + g;
+  const bool full = m0 + SC_ROWS <= M;
+  for (; strip < sb1; strip += SC_WAVES) {
+    const bool more = strip + SC_WAVES < sb1;
+    const int pcur = strip * (KS * 2048);
+    const int pnext = (more ? strip + SC_WAVES : strip) * (KS * 2048);
+#pragma unroll
+    for (int ks = 0; ks < KS; ks++) {
+      const int tgt = ks + SL - 1;
+      const int pf = tgt < KS ? pcur + tgt * 2048 : pnext + (tgt - KS) * 2048;
+      const int ksn = (ks + 1) % KS;
+#pragma unroll
+      for (int op = 0; op < 4; op++) {
+#pragma unroll
+        for (int nb = 0; nb < 2; nb++) {
+          if (ks == 0) {
+            const i32x16 zero = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
+            acc[op][nb] = __builtin_amdgcn_mfma_i32_32x32x32_i8(wb[ks % SL][nb], hf[op], zero, 0, 0, 0);
+          } else {
+            acc[op][nb] = __builtin_amdgcn_mfma_i32_32x32x32_i8(wb[ks % SL][nb], hf[op], acc[op][nb], 0, 0, 0);
+          }
+        }
+        // refill what was just consumed; the scheduling barrier keeps the loads this far ahead of their use
+        hf[op] = *(const i32x4 *)((op < 2 ? hrow : hrow2) + (op & 1) * 32 * LD + ksn * 32);
+        if (op == 0) {
+          wb[tgt % SL][0] = wload(pf, 0);
+          wb[tgt % SL][1] = wload(pf, 1);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+    // ---- strip done: the three largest of this lane's 32 products per row, with their places ----
+    int top[4][3];
+    auto fold = [&](auto masked_tag) {
+      constexpr bool MASKED = decltype(masked_tag)::value;
+#pragma unroll
+      for (int a = 0; a < 4; a++) top[a][0] = top[a][1] = top[a][2] = SC_NONE;
+#pragma unroll
+      for (int nb = 0; nb < 2; nb++)
+#pragma unroll
+        for (int v = 0; v < 16; v++)
+#pragma unroll
+          for (int a = 0; a < 4; a++) {
+            int x = (acc[a][nb][v] << 5) | (nb * 16 + v), second, third;
+            if (MASKED) x = strip * 64 + nb * 32 + (v >> 2) * 8 + g * 4 + (v & 3) < N ? x : SC_NONE;
+            asm("v_med3_i32 %0, %1, %2, %3" : "=v"(third) : "v"(top[a][1]), "v"(top[a][2]), "v"(x));
+            asm("v_med3_i32 %0, %1, %2, %3" : "=v"(second) : "v"(top[a][0]), "v"(top[a][1]), "v"(x));
+            top[a][2] = third;
+            top[a][1] = second;
+            top[a][0] = top[a][0] > x ? top[a][0] : x;
+          }
+    };
+    auto pair = [&](int a) {
+      const int apart = ((top[a][1] >> 5) - (top[a][2] >> 5)) >> SC_APART;
+      const int second = top[a][1] > SC_NONE / 2 ? top[a][1] : SC_LOW << 5;
+      return i32x2{top[a][0], (second >> 5) << 8 | (apart > 7 ? 7 : apart) << 5 | (second & 31)};
+    };
+    if (strip * 64 + 64 <= N) fold(std::false_type{}); else fold(std::true_type{});
+    // straight-line stores for whole tiles (a guard around each makes it wait for the one before)
+    if (full) {
+#pragma unroll
+      for (int a = 0; a < 4; a++) out[(long)a * 32 * (2 * NS) + 2 * strip] = pair(a);
+    } else {
+#pragma unroll
+      for (int a = 0; a < 4; a++)
+        if (m0 + a * 32 + li < M) out[(long)a * 32 * (2 * NS) + 2 * strip] = pair(a);
+    }
+  }
+}
+
+// ---------------------------------------------------------------------------------------------------------------------
+// The candidates the scout has left, their exact logits, the arg-max: four rows per workgroup.  Two waves find a row's candidates;
+// the logits of all its rows are then dealt to groups of 16 lanes, because the rows differ (16 on average, 70 at most in a thousand)
+// and one wave with its own row's took as long as the worst row.
+// Rows with more than kPickCap candidates have every entry computed, by the same function, once all others are done.
+// ---------------------------------------------------------------------------------------------------------------------
+constexpr int PK_ROWS = 4, PK_WAVES = 8;  // two waves find a row's candidates
+
+// Reductions over a wave in the vector unit (data-parallel primitives: rows of 16 lanes, then their broadcasts): a tenth of the
+// latency of an exchange through the LDS unit.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ int pk_dpp(int old, int x) {
+  return __builtin_amdgcn_update_dpp(old, x, CTRL, ROWS, 0xf, false);
+}
+__device__ __forceinline__ int pk_scan(int x) {  // inclusive sum over the lanes
+  x += pk_dpp<0x111, 0xf>(0, x);  // row_shr 1, 2, 4, 8
+  x += pk_dpp<0x112, 0xf>(0, x);
+  x += pk_dpp<0x114, 0xf>(0, x);
+  x += pk_dpp<0x118, 0xf>(0, x);
+  x += pk_dpp<0x142, 0xa>(0, x);  // the last lane of rows 0 and 2 to rows 1 and 3, then of row 1 to rows 2 and 3
+  return x + pk_dpp<0x143, 0xc>(0, x);
+}
+__device__ __forceinline__ float pk_max(float x) {  // over all lanes
+  auto step = [](float v, auto ctrl, auto rows) {
+    return fmaxf(v, __int_as_float(pk_dpp<decltype(ctrl)::value, decltype(rows)::value>(__float_as_int(-INFINITY), __float_as_int(v))));
+  };
+  typedef std::integral_constant<int, 0xf> all;
+  x = step(x, std::integral_constant<int, 0x111>{}, all{});
+  x = step(x, std::integral_constant<int, 0x112>{}, all{});
+  x = step(x, std::integral_constant<int, 0x114>{}, all{});
+  x = step(x, std::integral_constant<int, 0x118>{}, all{});
+  x = step(x, std::integral_constant<int, 0x142>{}, std::integral_constant<int, 0xa>{});
+  x = step(x, std::integral_constant<int, 0x143>{}, std::integral_constant<int, 0xc>{});
+  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), 63));
+}
+__device__ __forceinline__ float pk_sum16(float x) {  // over 16 lanes (rotations: every lane gets it)
+  x += __int_as_float(pk_dpp<0x128, 0xf>(0, __float_as_int(x)));
+  x += __int_as_float(pk_dpp<0x124, 0xf>(0, __float_as_int(x)));
+  x += __int_as_float(pk_dpp<0x122, 0xf>(0, __float_as_int(x)));
+  return x + __int_as_float(pk_dpp<0x121, 0xf>(0, __float_as_int(x)));
+}
+
+template <int K>
+__global__ __launch_bounds__(PK_WAVES * 64) void vocab_pick_kernel(const i32x4 *__restrict__ part, const float4 *__restrict__ row_consts,
+                                                                   const float4 *__restrict__ strip_consts, const int32_t *__restrict__ ids,
+                                                                   int NS, int row0, int M, float distrust,
+                                                                   const _Float16 *__restrict__ h_hi, const _Float16 *__restrict__ h_lo, long ldh,
+                                                                   const _Float16 *__restrict__ Ws, int32_t *tok, int32_t *slot_of_row) {
+  constexpr int CH = 4;               // strips per lane at a time
+  constexpr int STEP = 2 * 64 * CH;   // both waves of a row
+  constexpr int KC = K / 128;         // runs of 128 elements: 16 lanes x 8
+  constexpr int NG = PK_WAVES * 4;    // groups of 16 lanes
+  constexpr int NE = K / 64, FLY = 4;  // entries in flight per group
+  __shared__ __attribute__((aligned(16))) float sx[PK_ROWS][K];
+  __shared__ int32_t cand[PK_ROWS][kPickCap];
+  __shared__ int count[PK_ROWS];
+  __shared__ float floors[PK_WAVES];
+  __shared__ unsigned long long best[PK_ROWS];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), e16 = lane & 15, group = threadIdx.x >> 4;
+  const int own_row = wave >> 1, half = wave & 1;
+  const int i = blockIdx.x * PK_ROWS + own_row;
+  const bool valid = i < M;
+  const int r = row0 + (valid ? i : 0);
+  {
+    typedef _Float16 halfNE __attribute__((ext_vector_type(NE)));
+    const i32x4 *mine = part + (long)(valid ? i : 0) * NS;
+    i32x4 p[CH];
+    float4 sc[CH];
+    auto load = [&](int s0) {
+#pragma unroll
+      for (int c = 0; c < CH; c++) {
+        const int s = s0 + (2 * c + half) * 64 + lane;
+        const int at = s < NS ? s : NS - 1;  // past the end: the last strip again, left out below
+        p[c] = mine[at];
+        sc[c] = strip_consts[at];
+      }
+    };
+    load(0);
+    const float4 rc = row_consts[r];  // {scale, ||e||, ||a||}
+    const halfNE xh = *(const halfNE *)(h_hi + (long)r * ldh + lane * NE), xl = *(const halfNE *)(h_lo + (long)r * ldh + lane * NE);
+    // what a strip's scout logits may be off by, with what fp32 loses on either side
+    auto bound = [&](const float4 &c) { return 1.0001f * (rc.y * c.y + rc.z * c.z) + 2e-6f * (rc.y + rc.z) * c.y + distrust; };
+    float floor_ = -INFINITY;
+    for (int s0 = 0;;) {
+#pragma unroll
+      for (int c = 0; c < CH; c++) {
+        const int top = (p[c][0] > p[c][2] ? p[c][0] : p[c][2]) >> 5;
+        floor_ = fmaxf(floor_, rc.x * sc[c].x * (float)top - bound(sc[c]));
+      }
+      if ((s0 += STEP) >= NS) break;
+      load(s0);
+    }
+    floor_ = pk_max(floor_);
+    if (lane == 0) {
+      floors[wave] = floor_;
+      if (half == 0) count[own_row] = 0, best[own_row] = 0ull;
+    }
+    if (half == 0) {
+#pragma unroll
+      for (int e = 0; e < NE; e += 4)
+        *(float4 *)&sx[own_row][lane * NE + e] = make_float4((float)xh[e] + (float)xl[e], (float)xh[e + 1] + (float)xl[e + 1],
+                                                             (float)xh[e + 2] + (float)xl[e + 2], (float)xh[e + 3] + (float)xl[e + 3]);
+    }
+    __syncthreads();
+    floor_ = fmaxf(floors[2 * own_row], floors[2 * own_row + 1]);
+    // every lane counts its own groups' candidates, then all write theirs
+    for (int s0 = 0; s0 < NS && valid; s0 += STEP) {
+      if (NS > STEP) load(s0);
+      unsigned firsts = 0u, seconds = 0u, thirds = 0u;
+#pragma unroll
+      for (int c = 0; c < CH; c++) {
+        const float unit = rc.x * sc[c].x, least = floor_ - bound(sc[c]);
+        const bool there = s0 + (2 * c + half) * 64 + lane < NS;
+#pragma unroll
+        for (int g = 0; g < 2; g++) {
+          const int second = p[c][2 * g + 1] >> 8, apart = p[c][2 * g + 1] >> 5 & 7;
+          auto in = [&](int product) { return !(unit * (float)product < least); };  // (a NaN is a candidate)
+          const bool one = there && p[c][2 * g] > SC_NONE / 2 && in(p[c][2 * g] >> 5), two = one && second > SC_LOW && in(second);
+          firsts |= one ? 1u << (2 * c + g) : 0u;
+          seconds |= two ? 1u << (2 * c + g) : 0u;
+          thirds |= two && in(second - (apart << SC_APART)) ? 1u << (2 * c + g) : 0u;  // as large as a third can be
+        }
+      }
+      const int own = __popc(firsts) + __popc(seconds) + 32 * __popc(thirds), upto = pk_scan(own);
+      const int all = __builtin_amdgcn_readlane(upto, 63);
+      if (all == 0) continue;
+      int base = 0;
+      if (lane == 0) base = atomicAdd(&count[own_row], all);
+      int at = __builtin_amdgcn_readfirstlane(base) + upto - own;
+      auto add = [&](int c, int g, int code) {
+        if (at < kPickCap)
+          cand[own_row][at] = (s0 + (2 * c + half) * 64 + lane) * 64 + (code >> 4) * 32 + ((code & 15) >> 2) * 8 + g * 4 + (code & 3);
+        at++;
+      };
+#pragma unroll
+      for (int c = 0; c < CH; c++)
+#pragma unroll
+        for (int g = 0; g < 2; g++) {
+          if (firsts >> (2 * c + g) & 1u) add(c, g, p[c][2 * g] & 31);
+          if (seconds >> (2 * c + g) & 1u) add(c, g, p[c][2 * g + 1] & 31);
+          if (thirds >> (2 * c + g) & 1u)  // rare: all 32 of the group
+            for (int code = 0; code < 32; code++) add(c, g, code);
+        }
+    }
+  }
+  __syncthreads();
+  // logit of row `row` and the entry whose elements lane e16 of a group holds in w; every lane of the group gets it
+  auto dot = [&](const half8 (&w)[KC], int row) {
+    float s = 0.f;
+#pragma unroll
+    for (int j = 0; j < KC; j++) {
+      const float4 x0 = *(const float4 *)&sx[row][j * 128 + e16 * 8], x1 = *(const float4 *)&sx[row][j * 128 + e16 * 8 + 4];
+      const float x[8] = {x0.x, x0.y, x0.z, x0.w, x1.x, x1.y, x1.z, x1.w};
+#pragma unroll
+      for (int t = 0; t < 8; t++) s += x[t] * (float)w[j][t];
+    }
+    return pk_sum16(s);
+  };
+  auto fetch = [&](half8 (&w)[KC], int place) {
+#pragma unroll
+    for (int j = 0; j < KC; j++) w[j] = *(const half8 *)(Ws + (long)place * K + j * 128 + e16 * 8);
+  };
+  int first[PK_ROWS + 1];  // of the rows' candidates, laid end to end
+  unsigned many = 0u;
+  first[0] = 0;
+#pragma unroll
+  for (int w = 0; w < PK_ROWS; w++) {
+    const int n = count[w];
+    many |= n > kPickCap ? 1u << w : 0u;
+    first[w + 1] = first[w] + (n > kPickCap ? 0 : n);
+  }
+  for (int c0 = 0; c0 < first[PK_ROWS]; c0 += FLY * NG) {
+    int id[FLY], row[FLY];
+    half8 w[FLY][KC];
+#pragma unroll
+    for (int u = 0; u < FLY; u++) {
+      const int c = c0 + u * NG + group;
+      int from = 0;
+      row[u] = 0;
+#pragma unroll
+      for (int q = 1; q < PK_ROWS; q++)
+        if (c >= first[q]) row[u] = q, from = first[q];
+      const int place = c < first[PK_ROWS] ? cand[row[u]][c - from] : 0;
+      fetch(w[u], place);
+      id[u] = c < first[PK_ROWS] ? ids[place] : -1;
+    }
+#pragma unroll
+    for (int u = 0; u < FLY; u++) {
+      const float s = dot(w[u], row[u]);
+      if (e16 == 0 && id[u] >= 0) atomicMax(&best[row[u]], argmax_key(s, id[u]));
+    }
+  }
+  if (many) {
+    unsigned long long mine[PK_ROWS] = {};
+    for (int v0 = 0; v0 < NS * 64; v0 += NG) {
+      const int id = ids[v0 + group];
+      half8 w[KC];
+      fetch(w, v0 + group);
+#pragma unroll
+      for (int q = 0; q < PK_ROWS; q++)
+        if (many >> q & 1u) {
+          const unsigned long long key = argmax_key(dot(w, q), id);
+          mine[q] = id >= 0 && key > mine[q] ? key : mine[q];
+        }
+    }
+#pragma unroll
+    for (int q = 0; q < PK_ROWS; q++)
+      if (e16 == 0 && (many >> q & 1u)) atomicMax(&best[q], mine[q]);
+  }
+  __syncthreads();
+  if (lane == 0 && half == 0 && valid) {
+    tok[r] = (int32_t)(0xFFFFFFFFu - (unsigned int)best[own_row]);
+    slot_of_row[r] = -1;
+  }
+}
+
+// Rows per launch: their pairs stay within 64 MiB
+static int scout_chunk(int N) {
+  const size_t per_row = (size_t)((N + 63) / 64) * 16;
+  return (int)std::max<size_t>(SC_ROWS, std::min<size_t>(8192, ((size_t)64 << 20) / per_row / SC_ROWS * SC_ROWS));
+}
+size_t vocab_scout_scratch_bytes(int N, int rows) {
+  return (size_t)std::min(scout_chunk(N), (rows + SC_ROWS - 1) / SC_ROWS * SC_ROWS) * (size_t)((N + 63) / 64) * 16;
+}
+
+template <int K>
+static hipError_t scout_launch(const VocabScout &v, const _Float16 *h, const _Float16 *h_lo, long ldh, const VocabWeights &w, int M, bool distrust,
+                               int32_t *tok, int32_t *slot_of_row, hipStream_t s) {
+  const int NS = (w.N + 63) / 64, chunk = scout_chunk(w.N);
+  const int8_t *Wq = (const int8_t *)v.matrix;
+  const float4 *consts = (const float4 *)(Wq + scout_code_bytes(w.N, K));
+  const int32_t *ids = (const int32_t *)(consts + NS);
+  constexpr int lds = SC_ROWS * (K + 16);  // 66 KiB at K = 512
+  // raising the dynamic LDS limit is per kernel, once per process (several host threads may get here at once)
+  static std::once_flag once;
+  static hipError_t attr_err = hipSuccess;
+  std::call_once(once, [] { attr_err = hipFuncSetAttribute((const void *)vocab_scout_kernel<K>, hipFuncAttributeMaxDynamicSharedMemorySize, lds); });
+  if (attr_err != hipSuccess) return attr_err;
+  for (int r0 = 0; r0 < M; r0 += chunk) {
+    const int rows = std::min(chunk, M - r0);
+    const ScSplit p = sc_split(rows, NS);
+    const unsigned int magic = p.m_tiles > 1 ? (unsigned int)((0x100000000ull + (unsigned)p.m_tiles - 1) / (unsigned)p.m_tiles) : 0u;
+    hipLaunchKernelGGL((vocab_scout_kernel<K>), dim3(8 * p.per_xcd), dim3(SC_WAVES * 64), lds, s, v.codes + (long)r0 * K, rows, Wq, w.N,
+                       p.m_tiles, p.G, p.per_xcd, NS / p.G, NS % p.G, magic, (i32x2 *)v.scratch);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((vocab_pick_kernel<K>), dim3((rows + PK_ROWS - 1) / PK_ROWS), dim3(PK_WAVES * 64), 0, s, (const i32x4 *)v.scratch,
+                       (const float4 *)v.row_consts, consts, ids, NS, r0, rows, distrust ? INFINITY : 0.f, h, h_lo, ldh, (const _Float16 *)(ids + 64 * NS), tok, slot_of_row);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+  }
+  return hipSuccess;
+}
+
+hipError_t launch_vocab_scout(const VocabScout &v, const _Float16 *h, const _Float16 *h_lo, long ldh, const VocabWeights &w, int M, bool distrust,
+                              int32_t *tok, int32_t *slot_of_row, hipStream_t s) {
+  if (w.K == 512) return scout_launch<512>(v, h, h_lo, ldh, w, M, distrust, tok, slot_of_row, s);
+  if (w.K == 256) return scout_launch<256>(v, h, h_lo, ldh, w, M, distrust, tok, slot_of_row, s);
+  return hipErrorInvalidValue;
+}
+
+}  // namespace nt

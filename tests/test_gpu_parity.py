@@ -436,6 +436,47 @@ def test_certified_argmax_equals_full_recompute(nt):
     assert np.array_equal(ref, out)
 
 
+@pytest.mark.parametrize("d,V", [(512, 40), (512, 64), (512, 4001), (256, 4033), (512, 33000)])
+@pytest.mark.parametrize("what", ["plain", "offset", "outliers", "equal"])
+def test_scouted_argmax(nt, torch_cuda, d, V, what):
+    """The arg-max of more than 64 rows: an 8-bit pass with a bound, exact logits of what it leaves.  Vocabularies below one strip
+    of 64 entries, of one, with a ragged end, of more strips than a workgroup scans at once; row counts around a tile; a
+    matrix whose entries share a large offset, one with entries 16 times the others, one of equal entries (everything is a candidate,
+    the lowest id wins).  Every token has the largest of the logits that the GEMM path computes, to fp32 rounding: two sums
+    of 512 products, 2 * 2^-24 sqrt(512) of |h| |w|, about 3e-6; four times that."""
+    torch = torch_cuda
+    cfg = nt_synth.model_config("C1", d_model=d, vocab=V, n_enc=0, max_len=16)
+    blob = nt_synth.make_weights(cfg, seed=17, random_affine=True)
+    W = nt_synth.blob_view(cfg, blob, "W_out")
+    rng = np.random.default_rng(V)
+    if what == "offset":
+        W += (4 * d ** -0.5 * rng.standard_normal(d)).astype(np.float16)
+    elif what == "outliers":
+        W[rng.integers(0, V, size=7)] *= np.float16(16)
+    elif what == "equal":
+        W[:] = W[0]
+    norm = float(np.linalg.norm(W.astype(np.float64), axis=1).max())
+    gm = nt.Model(cfg, blob, max_batch_tokens=2048, pipeline_lanes=1)
+    T = 3
+    for rows in (65, 127, 128, 129, 517):
+        src = torch.from_numpy(rng.integers(0, V, size=(rows, 2)).astype(np.int32)).cuda()
+        lens = torch.full((rows,), 2, dtype=torch.int32, device="cuda")
+        out = torch.empty(rows, T, dtype=torch.int32, device="cuda")
+        gm.encode(src, lens)
+        gm.decode_greedy(rows, T, out)
+        given = torch.cat([torch.full((rows, 1), cfg["bos_id"], dtype=torch.int32, device="cuda"), out[:, :-1]], dim=1).contiguous()
+        logits = torch.empty(rows, T, V, dtype=torch.float32, device="cuda")
+        gm.encode(src, lens)
+        gm.debug_teacher_forced_logits(given, logits)
+        got = logits.gather(2, out.long().unsqueeze(2)).squeeze(2)
+        short = float((logits.max(dim=2).values - got).max()) / (norm * d ** 0.5)
+        print(f"{what} {d} x {V}, {rows} rows: short of the largest by {short:.1e} of |h| |w|")
+        assert short <= 1.2e-5
+        if what == "equal":
+            assert int(out.max()) == 0
+    gm.close()
+
+
 # ------------------------------------------------------------------------------ restored components (C3) and teacher shape (C4)
 def _check_workload_sample(nt, oracle, name, n_sent, budget, n_audit=None, **overrides):
     """Translate n_sent sentences of a workload at a token budget and audit a seeded sample of n_audit of them (all,
