@@ -454,14 +454,18 @@ static hipError_t gs_launch(const _Float16 *A, const _Float16 *A_lo, long lda, i
   });
   if (attr_err != hipSuccess) return attr_err;
   const int row_tiles = (M + 32 * RB - 1) / (32 * RB), NS = N / (32 * NB);
-  // enough workgroups for the chip: split the strips of a row tile over several workgroups as long as every wave
-  // of a workgroup still gets a strip and the grid stays within a few rounds
+  // The strips of a row tile are split over several workgroups where that shortens the launch: rounds of workgroups (one to a CU)
+  // times the fill of the tile, which takes as long as a strip, and a wave's strips.  With as many workgroups as fit a few rounds
+  // instead, every round began with a fill of its own: an encoder of six layers 516 against 439 us at 8,192 tokens, 888 against 754
+  // at 16,384, 1,341 against 1,206 at 32,768; 8 heads and FFN 2,048 1,113 / 941, 2,039 / 1,767, 3,580 / 3,386 (20,480 tokens, just past
+  // a round: the same both ways).
   int col_groups = 1;
-  for (int cg = NS / GS_WAVES; cg > 1; cg--)
-    if (NS % cg == 0 && (long)row_tiles * cg <= 1024) {
-      col_groups = cg;
-      break;
-    }
+  long best = 0;
+  for (int cg = 1; cg * GS_WAVES <= NS; cg++) {
+    if (NS % cg != 0) continue;
+    const long cost = ((long)row_tiles * cg + 255) / 256 * (1 + (NS / cg + GS_WAVES - 1) / GS_WAVES);
+    if (best == 0 || cost < best) best = cost, col_groups = cg;
+  }
   if (NC > 1) col_groups = NS / GS_WAVES;  // several passes: exactly one strip per wave
   if (NB == 1) col_groups = gs_narrow_groups(N);
   hipLaunchKernelGGL(kern, dim3(row_tiles * col_groups), dim3(GS_WAVES * 64), lds, s, A, A_lo, lda, M, Wp, N, col_groups, e,
