@@ -521,7 +521,7 @@ __global__ __launch_bounds__(256, WPU == 4 ? 1 : NKB == 1 ? 3 : NKB == 2 ? 2 : 1
       sc[kb][v] = (kb < nkb && key < L) ? sc[kb][v] : -INFINITY;  // masked keys get weight exactly 0
       mx = fmaxf(mx, sc[kb][v]);
     }
-  mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+  mx = wave_pair32(mx, mx, WaveMax{});
   float sum = 0.f;
 #pragma unroll
   for (int kb = 0; kb < NKB; kb++)
@@ -530,7 +530,7 @@ __global__ __launch_bounds__(256, WPU == 4 ? 1 : NKB == 1 ? 3 : NKB == 2 ? 2 : 1
       sc[kb][v] = expf(sc[kb][v] - mx);
       sum += sc[kb][v];
     }
-  sum += __shfl_xor(sum, 32, 64);
+  sum = wave_pair32(sum, sum, WaveAdd{});
   const float inv = (QK16 ? 1.f : P_SCALE) / sum;
   // probabilities (QK16: as they are, else times P_SCALE) as A-operand fragments: k-step ks of block kb uses registers ks*8 .. ks*8+7
   half8 ph[NKB][2], pl[NKB][2];

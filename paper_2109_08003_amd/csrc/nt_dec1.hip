@@ -50,8 +50,8 @@
 // 45 rows 26 and 17.8; with the self values too, one sentence 1119 -> 1012 us, 45 sentences 3742 -> 3207 us, 8 sentences of
 // the 256-wide model 1253 -> 1175 us, a 4,096-token budget 28.0 -> 27.5 ms (each with the projection as a launch of its own).
 //
-// Registers: three forms spill some of theirs - eight heads with two rows (5, 24 bytes of scratch per lane) and with eight rows
-// (13, 56 bytes), folded with the FFN at d = 512 (48, 100 bytes).  The others use no scratch.
+// Registers: three forms spill some of theirs - eight heads with two rows (6, 28 bytes of scratch per lane) and with eight rows
+// (13, 56 bytes), folded with the FFN at d = 512 (35, 76 bytes).  The others use no scratch.
 //
 // Measured per step of 1,900 / 45 / 1 rows, alone: 92 / 42 / 38 us as four launches, 71 / 30 / 25 us as one.
 //
@@ -82,17 +82,6 @@ constexpr int D1_SL = 4;     // ring of weight fragments: k-steps of 32 in fligh
 bool attn_i16_supported(int d, int heads, int clip) { return heads == 1 && clip == 0 && (d == 256 || d == 512); }
 bool dec1_heads_supported(int d, int heads) { return d == 512 && heads == 8; }
 
-__device__ __forceinline__ float d1_wave_sum(float v) {
-#pragma unroll
-  for (int m = 32; m >= 1; m >>= 1) v += __shfl_xor(v, m, 64);
-  return v;
-}
-__device__ __forceinline__ float d1_wave_max(float v) {
-#pragma unroll
-  for (int m = 32; m >= 1; m >>= 1) v = fmaxf(v, __shfl_xor(v, m, 64));
-  return v;
-}
-
 template <int NE>
 __device__ __forceinline__ void d1_load(const float *p, float (&x)[NE]) {
 #pragma unroll
@@ -109,7 +98,7 @@ __device__ __forceinline__ void d1_quantize_store(float (&x)[NE], short *dst, fl
   float amax = 0.f;
 #pragma unroll
   for (int e = 0; e < NE; e++) amax = fmaxf(amax, fabsf(x[e]));
-  amax = d1_wave_max(amax);
+  amax = wave_max(amax);
   const float scale = amax > 0.f ? amax / 32767.f : 1.f;
   const float inv = 1.f / scale;
   shortNE qv;
@@ -159,7 +148,7 @@ __global__ __launch_bounds__(256) void quantize_kv_i16_kernel(const float *x, lo
         d1_load<NE>(pl.u + lane * NE, u);
 #pragma unroll
         for (int e = 0; e < NE; e++) s += u[e] * v[e];
-        s = d1_wave_sum(s);
+        s = wave_sum(s);
         if (lane == 0) pl.key_const[m] = s * pl.scale;
       }
     }
@@ -303,24 +292,8 @@ struct D1Block {
     // reduce-scatter: after the exchanges over the two top lane bits a lane holds the sum over those bits of the key
     // numbered by them; the remaining exchanges complete it.  Lanes 16 i .. 16 i + 15 then hold the product of key i
     static_assert(D1_NK == 4, "blocks of four keys");
-    float r2[2], r1;
-    {
-      const bool up = lane & 32;
-#pragma unroll
-      for (int i = 0; i < 2; i++) {
-        const float send = up ? p[i] : p[i + 2], keep = up ? p[i + 2] : p[i];
-        r2[i] = keep + __shfl_xor(send, 32, 64);
-      }
-    }
-    {
-      const bool up = lane & 16;
-      const float send = up ? r2[0] : r2[1], keep = up ? r2[1] : r2[0];
-      r1 = keep + __shfl_xor(send, 16, 64);
-    }
-    r1 += __shfl_xor(r1, 8, 64);
-    r1 += __shfl_xor(r1, 4, 64);
-    r1 += __shfl_xor(r1, 2, 64);
-    r1 += __shfl_xor(r1, 1, 64);
+    float r1 = wave_pair16(wave_pair32(p[0], p[2], WaveAdd{}), wave_pair32(p[1], p[3], WaveAdd{}), WaveAdd{});
+    r1 = wave_fold16(r1, WaveAdd{});
     float s[D1_NK], bm = -INFINITY;
 #pragma unroll
     for (int i = 0; i < D1_NK; i++) {
@@ -409,19 +382,23 @@ struct D1HeadBlock {
 // The input token of a wave's row, in two halves so that the loads between them travel with it: BOS, the given token, or the
 // arg-max of the previous step, which the row's first wave also stores.
 struct D1Token {
-  unsigned long long key;  // a lane's first partial key
+  unsigned long long key[4];  // a lane's first partial keys
   int tok, slot;
   __device__ __forceinline__ void request(const Dec1Args &a, int row, int lane) {
     const StepBeginArgs &b = a.sb;
-    key = 0ull, tok = b.pad_id, slot = -1;
+    tok = b.pad_id, slot = -1;
+#pragma unroll
+    for (int u = 0; u < 4; u++) key[u] = 0ull;
     if (a.tok_in) {
       if (row < a.rows) tok = a.tok_in[row];
     } else if (b.t > 0 && row < b.rows_prev) {
       if (b.prev_cert) {
         tok = b.tok[row];
         slot = b.slot_of_row[row];
-      } else if (b.pk && lane < b.n_partials) {
-        key = b.pk[(long)row * b.n_partials + lane];
+      } else if (b.pk) {
+#pragma unroll
+        for (int u = 0; u < 4; u++)
+          if (lane + 64 * u < b.n_partials) key[u] = b.pk[(long)row * b.n_partials + lane + 64 * u];
       }
     }
   }
@@ -435,16 +412,14 @@ struct D1Token {
         if (b.prev_cert) {
           if (slot >= 0) y = (int)(0xFFFFFFFFu - (unsigned int)b.final_key[slot]);
         } else {
-          for (int q = lane + 64; q < b.n_partials; q += 64) {
-            const unsigned long long c = b.pk[(long)row * b.n_partials + q];
-            key = c > key ? c : key;
-          }
+          unsigned long long top = 0ull;
 #pragma unroll
-          for (int m = 32; m >= 1; m >>= 1) {
-            const unsigned long long o = shfl_xor_u64(key, m);
-            key = o > key ? o : key;
+          for (int u = 0; u < 4; u++) top = key[u] > top ? key[u] : top;
+          for (int q = lane + 256; q < b.n_partials; q += 64) {
+            const unsigned long long c = b.pk[(long)row * b.n_partials + q];
+            top = c > top ? c : top;
           }
-          y = (int)(0xFFFFFFFFu - (unsigned int)key);
+          y = (int)(0xFFFFFFFFu - (unsigned int)wave_max_u64(top));
         }
         if (y < 0 || y >= b.vocab) y = b.pad_id;  // cannot happen: every key holds a valid id
         if (first_wave && lane == 0) b.out[(long)row * b.out_ld + b.t - 1] = y;
@@ -489,11 +464,11 @@ __device__ __forceinline__ void first_layer_start(const Dec1Args &a, int y, int 
     z[e] = sc * (float)ev[e] + pv[e];
     s += z[e];
   }
-  const float mean = d1_wave_sum(s) / (float)D;
+  const float mean = wave_sum(s) / (float)D;
   float v = 0.f;
 #pragma unroll
   for (int e = 0; e < NE; e++) v += ln_term(z[e] - mean, a.eps.l1);
-  const float rs = ln_rscale(d1_wave_sum(v) / (float)D, a.eps);
+  const float rs = ln_rscale(wave_sum(v) / (float)D, a.eps);
   auto combine = [&](const float (&t)[NE], int col, float (&x)[NE]) {
     float p[NE], c[NE];
     d1_load<NE>(by_pos + col, p);
@@ -600,7 +575,7 @@ __global__ __launch_bounds__(NWAVES * 64) void dec1_kernel(Dec1Args a) {
 #pragma unroll
     for (int t = 0; t < NT; t++)
 #pragma unroll
-      for (int v = 0; v < 4; v++) acc[t][v] += __shfl_xor(acc[t][v], 32, 64);
+      for (int v = 0; v < 4; v++) acc[t][v] = wave_pair32(acc[t][v], acc[t][v], WaveAdd{});
   };
   // f(row, column, value) for every result of the wave; the lane groups that only duplicate rows stay out
   auto results = [&](auto f) {
@@ -637,11 +612,11 @@ __global__ __launch_bounds__(NWAVES * 64) void dec1_kernel(Dec1Args a) {
     float s = 0.f;
 #pragma unroll
     for (int e = 0; e < NE; e++) s += y[e];
-    const float mean = d1_wave_sum(s) / (float)D;
+    const float mean = wave_sum(s) / (float)D;
     float q = 0.f;
 #pragma unroll
     for (int e = 0; e < NE; e++) q += ln_term(y[e] - mean, a.eps.l1);
-    const float rs = ln_rscale(d1_wave_sum(q) / (float)D, a.eps);
+    const float rs = ln_rscale(wave_sum(q) / (float)D, a.eps);
 #pragma unroll
     for (int e = 0; e < NE; e++) y[e] = ga[e] * ((y[e] - mean) * rs) + be[e];
   };
@@ -790,7 +765,7 @@ __global__ __launch_bounds__(NWAVES * 64) void dec1_kernel(Dec1Args a) {
       float s = 0.f;
 #pragma unroll
       for (int e = 0; e < NE; e++) s += q[e] * kx[e];
-      st[0].m = HEADS ? d1_head_sum(s) + (rel.p ? rel.at(rel.t) : 0.f) : d1_wave_sum(s);
+      st[0].m = HEADS ? d1_head_sum(s) + (rel.p ? rel.at(rel.t) : 0.f) : wave_sum(s);
       st[0].l = 1.f;
 #pragma unroll
       for (int e = 0; e < NE; e++) st[0].acc[e] = vx[e];
@@ -899,7 +874,7 @@ __global__ __launch_bounds__(NWAVES * 64) void dec1_kernel(Dec1Args a) {
       lo[e] = (_Float16)(x - (float)hi[e]);
       tail2 += (float)lo[e] * (float)lo[e];
     }
-    tail2 = d1_wave_sum(tail2);
+    tail2 = wave_sum(tail2);
     *(halfNE *)(a.h_hi + (long)r * D + lane * NE) = hi;
     *(halfNE *)(a.h_hi + a.h_lo_offset + (long)r * D + lane * NE) = lo;
     if (lane == 0) a.lo_norm[r] = sqrtf(tail2) * 1.0001f;  // rounded up: it is used as a bound

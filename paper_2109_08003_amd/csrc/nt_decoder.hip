@@ -178,13 +178,7 @@ __device__ __forceinline__ void dc_layer_norm(float (&xv)[DC_TM / DC_WAVES][DcSh
     mean[i] = sum;
   }
 #pragma unroll
-  for (int m = 32; m >= 1; m >>= 1) {
-    float o[RPW];
-#pragma unroll
-    for (int i = 0; i < RPW; i++) o[i] = __shfl_xor(mean[i], m, 64);
-#pragma unroll
-    for (int i = 0; i < RPW; i++) mean[i] += o[i];
-  }
+  for (int i = 0; i < RPW; i++) mean[i] = wave_sum(mean[i]);
 #pragma unroll
   for (int i = 0; i < RPW; i++) {
     mean[i] = mean[i] / (float)K;
@@ -194,13 +188,7 @@ __device__ __forceinline__ void dc_layer_norm(float (&xv)[DC_TM / DC_WAVES][DcSh
     rstd[i] = q;
   }
 #pragma unroll
-  for (int m = 32; m >= 1; m >>= 1) {
-    float o[RPW];
-#pragma unroll
-    for (int i = 0; i < RPW; i++) o[i] = __shfl_xor(rstd[i], m, 64);
-#pragma unroll
-    for (int i = 0; i < RPW; i++) rstd[i] += o[i];
-  }
+  for (int i = 0; i < RPW; i++) rstd[i] = wave_sum(rstd[i]);
 #pragma unroll
   for (int i = 0; i < RPW; i++) {
     rstd[i] = ln_rscale(rstd[i] / (float)K, eps);
@@ -308,13 +296,7 @@ __global__ __launch_bounds__(DC_WAVES * 64) void dec_qkv_kernel(DecQkvArgs a, in
         }
       }
 #pragma unroll
-      for (int m = 32; m >= 1; m >>= 1) {
-#pragma unroll
-        for (int i = 0; i < RPW; i++) {
-          const unsigned long long o = shfl_xor_u64(k[i], m);
-          k[i] = o > k[i] ? o : k[i];
-        }
-      }
+      for (int i = 0; i < RPW; i++) k[i] = wave_max_u64(k[i]);
 #pragma unroll
       for (int i = 0; i < RPW; i++) y[i] = (int)(0xFFFFFFFFu - (unsigned int)k[i]);
     }
@@ -562,8 +544,7 @@ __global__ __launch_bounds__(DC_WAVES * 64) void dec_chain_kernel(DecChainArgs a
         lo[j] = (_Float16)(x - (float)hi[j]);
         tail2 += (float)lo[j] * (float)lo[j];
       }
-#pragma unroll
-      for (int s = 32; s >= 1; s >>= 1) tail2 += __shfl_xor(tail2, s, 64);
+      tail2 = wave_sum(tail2);
       if (m < M) {
         *(halfNE *)(a.h_hi + (long)m * K + lane * NE) = hi;
         *(halfNE *)(a.h_hi + a.h_lo_offset + (long)m * K + lane * NE) = lo;

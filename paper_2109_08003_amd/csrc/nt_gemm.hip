@@ -639,12 +639,6 @@ struct SkinnyCfg {
   static constexpr size_t LDS = (size_t)3 * PANEL * 2 + 4 * 32 * 33 * 4;
 };
 
-__device__ __forceinline__ float wave_sum_f(float v) {
-#pragma unroll
-  for (int m = 32; m >= 1; m >>= 1) v += __shfl_xor(v, m, 64);
-  return v;
-}
-
 template <int KC, bool C_F32>
 __global__ __launch_bounds__(256) void skinny_gemm_kernel(const float *A, long lda, const _Float16 *Wt, int M, int N,
                                                           int K, const float *ln_g, const float *ln_b, LnEps ln_eps,
@@ -695,7 +689,7 @@ __global__ __launch_bounds__(256) void skinny_gemm_kernel(const float *A, long l
         float s = 0.f;
 #pragma unroll
         for (int c = 0; c < CPL; c++) s += ra[r][c].x + ra[r][c].y + ra[r][c].z + ra[r][c].w;
-        const float mean = wave_sum_f(s) / (float)KC;
+        const float mean = wave_sum(s) / (float)KC;
         float q = 0.f;
 #pragma unroll
         for (int c = 0; c < CPL; c++) {
@@ -703,7 +697,7 @@ __global__ __launch_bounds__(256) void skinny_gemm_kernel(const float *A, long l
           x.x -= mean; x.y -= mean; x.z -= mean; x.w -= mean;
           q += ln_term(x.x, ln_eps.l1) + ln_term(x.y, ln_eps.l1) + ln_term(x.z, ln_eps.l1) + ln_term(x.w, ln_eps.l1);
         }
-        const float rstd = ln_rscale(wave_sum_f(q) / (float)KC, ln_eps);
+        const float rstd = ln_rscale(wave_sum(q) / (float)KC, ln_eps);
 #pragma unroll
         for (int c = 0; c < CPL; c++) {
           float4 &x = ra[r][c];

@@ -150,13 +150,7 @@ __global__ __launch_bounds__(GS_WAVES * 64) void gemm_stream_kernel(const _Float
       mean[i] = sum;
     }
 #pragma unroll
-    for (int m = 32; m >= 1; m >>= 1) {
-      float o[RPW];
-#pragma unroll
-      for (int i = 0; i < RPW; i++) o[i] = __shfl_xor(mean[i], m, 64);
-#pragma unroll
-      for (int i = 0; i < RPW; i++) mean[i] += o[i];
-    }
+    for (int i = 0; i < RPW; i++) mean[i] = wave_sum(mean[i]);
 #pragma unroll
     for (int i = 0; i < RPW; i++) {
       mean[i] = mean[i] / (float)K;
@@ -169,13 +163,7 @@ __global__ __launch_bounds__(GS_WAVES * 64) void gemm_stream_kernel(const _Float
       rstd[i] = q;
     }
 #pragma unroll
-    for (int m = 32; m >= 1; m >>= 1) {
-      float o[RPW];
-#pragma unroll
-      for (int i = 0; i < RPW; i++) o[i] = __shfl_xor(rstd[i], m, 64);
-#pragma unroll
-      for (int i = 0; i < RPW; i++) rstd[i] += o[i];
-    }
+    for (int i = 0; i < RPW; i++) rstd[i] = wave_sum(rstd[i]);
 #pragma unroll
     for (int i = 0; i < RPW; i++) {
       rstd[i] = ln_rscale(rstd[i] / (float)K, ln.eps);

@@ -18,23 +18,6 @@ constexpr int MAX_PER_LANE = 16;  // d <= 1024
   _Pragma("unroll") for (int i = 0; i < (NE ? NE : MAX_PER_LANE); i++) if (NE || i < ne)
 static int ne_case(int d) { return (d == 256 || d == 512 || d == 1024) ? d / 64 : 0; }
 
-__device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-  for (int m = 32; m >= 1; m >>= 1) v += __shfl_xor(v, m, 64);
-  return v;
-}
-
-__device__ __forceinline__ unsigned long long wave_max_u64(unsigned long long x) {
-#pragma unroll
-  for (int m = 32; m >= 1; m >>= 1) {
-    unsigned int lo = __shfl_xor((unsigned int)x, m, 64), hi = __shfl_xor((unsigned int)(x >> 32), m, 64);
-    unsigned long long o = ((unsigned long long)hi << 32) | lo;
-    x = o > x ? o : x;
-  }
-  return x;
-}
-
-// lane holds elements lane + 64*i, i < ne
 template <int NE>
 __device__ __forceinline__ void row_layer_norm(float (&v)[MAX_PER_LANE], int ne, int d, LnEps eps, int lane,
                                                const float *gamma, const float *beta) {

@@ -110,12 +110,6 @@ void vocab_q8_pack(const _Float16 *Wt, int N, int K, int8_t *codes, void *consts
 }
 
 // ---- activations: [LayerNorm and] 8-bit codes per row ------------------------------------------------------------
-__device__ __forceinline__ float q8_wave_sum(float v) {
-#pragma unroll
-  for (int m = 32; m >= 1; m >>= 1) v += __shfl_xor(v, m, 64);
-  return v;
-}
-
 // One wave per row; a lane owns NE = d / 64 consecutive elements.  codes: [M][d] signed bytes (u - 128);
 // a_scale, c (= 128 - a_zero), sa (= sum of the signed codes) per row.  Eq. 5, 6 in fp32, one rounding per
 // operation:  scale = (max - min) / 255,  zero = clamp(rint(255 - max / scale)),  u = clamp(rint(h / scale + zero)),
@@ -137,11 +131,11 @@ __global__ __launch_bounds__(256) void q8_rows_kernel(const float *__restrict__ 
     float s = 0.f;
 #pragma unroll
     for (int j = 0; j < NE; j++) s += v[j];
-    const float mean = q8_wave_sum(s) / (float)d;
+    const float mean = wave_sum(s) / (float)d;
     float q = 0.f;
 #pragma unroll
     for (int j = 0; j < NE; j++) q += ln_term(v[j] - mean, eps.l1);
-    const float rs = ln_rscale(q8_wave_sum(q) / (float)d, eps);
+    const float rs = ln_rscale(wave_sum(q) / (float)d, eps);
 #pragma unroll
     for (int j = 0; j < NE; j++) v[j] = gamma[lane * NE + j] * ((v[j] - mean) * rs) + beta[lane * NE + j];
   }
@@ -151,11 +145,8 @@ __global__ __launch_bounds__(256) void q8_rows_kernel(const float *__restrict__ 
     mn = fminf(mn, v[j]);
     mx = fmaxf(mx, v[j]);
   }
-#pragma unroll
-  for (int m = 32; m >= 1; m >>= 1) {
-    mn = fminf(mn, __shfl_xor(mn, m, 64));
-    mx = fmaxf(mx, __shfl_xor(mx, m, 64));
-  }
+  mn = wave_fold(mn, WaveMin{});
+  mx = wave_max(mx);
   const float range = mx - mn;
   const float scale = range > 0.f ? range / 255.0f : 1.0f;
   const float ratio = mx / scale;
@@ -172,8 +163,7 @@ __global__ __launch_bounds__(256) void q8_rows_kernel(const float *__restrict__ 
     if ((j & 3) == 0) packed[j >> 2] = 0u;
     packed[j >> 2] |= (unsigned int)(sgn & 0xFF) << (8 * (j & 3));
   }
-#pragma unroll
-  for (int m = 32; m >= 1; m >>= 1) sum += __shfl_xor(sum, m, 64);
+  sum = wave_fold(sum, WaveAdd{});
   unsigned int *dst = (unsigned int *)(codes + r * d + lane * NE);
 #pragma unroll
   for (int j = 0; j < NE / 4; j++) dst[j] = packed[j];

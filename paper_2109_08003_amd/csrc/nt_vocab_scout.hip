@@ -75,8 +75,7 @@ __global__ __launch_bounds__(256) void scout_top_kernel(const _Float16 *W, int N
   if (v >= N) return;
   float m = 0.f;
   for (int k = lane; k < K; k += 64) m = fmaxf(m, fabsf((float)W[(long)v * K + k] - mean[k]));
-#pragma unroll
-  for (int x = 32; x >= 1; x >>= 1) m = fmaxf(m, __shfl_xor(m, x, 64));
+  m = wave_max(m);
   if (lane == 0) top[v] = m;
 }
 // one strip per workgroup, sixteen rows per wave
