@@ -34,6 +34,57 @@ constexpr int GS_WAVES = 8;
 
 bool gemm_stream_supported(int N, int K) { return (K == 256 || K == 512) && N % 64 == 0; }
 
+// Rows wave, wave + 8, ... of a tile, element lane * NE + j of the i-th in xv[i][j]: LayerNorm (fp32 statistics: mean first, then the
+// biased variance or mean absolute deviation of the centred values), split into head (and tail) planes in the LDS.
+template <int NE, int RPW, int TM, bool TAIL>
+__device__ __forceinline__ void gs_normalise(const float (&xv)[RPW][NE], const GemmLayerNorm &ln, _Float16 *sh, int wave, int lane) {
+  constexpr int K = NE * 64, LD = K + 8;
+  float gam[NE], bet[NE];
+#pragma unroll
+  for (int j = 0; j < NE; j += 4) {
+    *(float4 *)&gam[j] = *(const float4 *)(ln.gamma + lane * NE + j);
+    *(float4 *)&bet[j] = *(const float4 *)(ln.beta + lane * NE + j);
+  }
+  float mean[RPW], rstd[RPW];
+#pragma unroll
+  for (int i = 0; i < RPW; i++) {
+    float sum = 0.f;
+#pragma unroll
+    for (int j = 0; j < NE; j++) sum += xv[i][j];
+    mean[i] = sum;
+  }
+#pragma unroll
+  for (int i = 0; i < RPW; i++) mean[i] = wave_sum(mean[i]);
+#pragma unroll
+  for (int i = 0; i < RPW; i++) {
+    mean[i] = mean[i] / (float)K;
+    float q = 0.f;
+#pragma unroll
+    for (int j = 0; j < NE; j++) {
+      const float c = xv[i][j] - mean[i];
+      q += ln_term(c, ln.eps.l1);
+    }
+    rstd[i] = q;
+  }
+#pragma unroll
+  for (int i = 0; i < RPW; i++) rstd[i] = wave_sum(rstd[i]);
+#pragma unroll
+  for (int i = 0; i < RPW; i++) {
+    rstd[i] = ln_rscale(rstd[i] / (float)K, ln.eps);
+    typedef _Float16 halfNE __attribute__((ext_vector_type(NE)));
+    halfNE hi, lo;
+#pragma unroll
+    for (int j = 0; j < NE; j++) {
+      const float y = as_f32(gam[j] * ((xv[i][j] - mean[i]) * rstd[i]) + bet[j]);
+      hi[j] = (_Float16)y;
+      lo[j] = (_Float16)(y - (float)hi[j]);
+    }
+    const int R = wave + GS_WAVES * i;
+    *(halfNE *)(sh + R * LD + lane * NE) = hi;
+    if (TAIL) *(halfNE *)(sh + (R + TM) * LD + lane * NE) = lo;
+  }
+}
+
 // RB = 32-row blocks per tile (1: decoder-sized M; 2: encoder-sized M).
 // LN = true: A_hi points to fp32 rows X[M][lda] instead; the tile is LayerNorm-ed (fp32 statistics: mean first, then
 // the biased variance of the centred values) and split into head/tail planes while it is written to the LDS, which
@@ -133,52 +184,7 @@ __global__ __launch_bounds__(GS_WAVES * 64) void gemm_stream_kernel(const _Float
       __builtin_amdgcn_sched_barrier(0);
       preload();
     }
-    float gam[NE], bet[NE];
-#pragma unroll
-    for (int j = 0; j < NE; j += 4) {
-      *(float4 *)&gam[j] = *(const float4 *)(ln.gamma + lane * NE + j);
-      *(float4 *)&bet[j] = *(const float4 *)(ln.beta + lane * NE + j);
-    }
-    // The butterflies of all rows advance together, one exchange step at a time: a step of one row waits for the
-    // cross-lane exchange before it (about 150 clocks), and row after row these waits were most of the fill.
-    float mean[RPW], rstd[RPW];
-#pragma unroll
-    for (int i = 0; i < RPW; i++) {
-      float sum = 0.f;
-#pragma unroll
-      for (int j = 0; j < NE; j++) sum += xv[i][j];
-      mean[i] = sum;
-    }
-#pragma unroll
-    for (int i = 0; i < RPW; i++) mean[i] = wave_sum(mean[i]);
-#pragma unroll
-    for (int i = 0; i < RPW; i++) {
-      mean[i] = mean[i] / (float)K;
-      float q = 0.f;
-#pragma unroll
-      for (int j = 0; j < NE; j++) {
-        const float c = xv[i][j] - mean[i];
-        q += ln_term(c, ln.eps.l1);
-      }
-      rstd[i] = q;
-    }
-#pragma unroll
-    for (int i = 0; i < RPW; i++) rstd[i] = wave_sum(rstd[i]);
-#pragma unroll
-    for (int i = 0; i < RPW; i++) {
-      rstd[i] = ln_rscale(rstd[i] / (float)K, ln.eps);
-      typedef _Float16 halfNE __attribute__((ext_vector_type(NE)));
-      halfNE hi, lo;
-#pragma unroll
-      for (int j = 0; j < NE; j++) {
-        const float y = as_f32(gam[j] * ((xv[i][j] - mean[i]) * rstd[i]) + bet[j]);
-        hi[j] = (_Float16)y;
-        lo[j] = (_Float16)(y - (float)hi[j]);
-      }
-      const int R = wave + GS_WAVES * i;
-      *(halfNE *)(sh + R * LD + lane * NE) = hi;
-      if (TAIL) *(halfNE *)(sh + (R + TM) * LD + lane * NE) = lo;
-    }
+    gs_normalise<NE, RPW, TM, TAIL>(xv, ln, sh, wave, lane);
   } else if (K == 512) {
     fill_planes(0);
     if (NB == 1) preload();
@@ -426,6 +432,153 @@ __global__ __launch_bounds__(GS_WAVES * 64) void gemm_stream_kernel(const _Float
   }
 }
 
+// ---------------------------------------------------------------------------------------------------------------------
+// An FFN in one launch: x += relu(LayerNorm(x) W1^T + b1) W2^T + b2, d = 512, hidden width 512 NC.  A workgroup has 32 rows; 512 hidden
+// columns at a time go from the first product's accumulators through ReLU and the split into a second pair of planes in the LDS
+// and straight into the second product, whose accumulators a wave keeps for its 64 output columns.  As two launches the hidden state
+// travelled through memory as planes, 8 KB a row each way: 108 + 76 us at 16,384 tokens and 313 + 262 at 65,536 (F = 2,048), 131 and about
+// 490 as one; 30 + 6 layer teacher 107.0 -> 102.2 ms, 8 heads and FFN 95.5 -> 91.4, submitted student 101.7 -> 97.4.  The matrix cores
+// are busy 54 % of the time; the stream of both matrices (4 MB a tile at the CU's 64 bytes a clock) takes as long as their products.  The weight ring runs through both products without a break; a
+// workgroup takes the tiles blockIdx.x, + gridDim.x, ... and requests the next tile's rows before the last product of this one.  The
+// sums are those of the two launches, term by term.
+// ---------------------------------------------------------------------------------------------------------------------
+template <int NC>
+__global__ __launch_bounds__(GS_WAVES * 64) void gemm_ffn_kernel(float *__restrict__ x, int M, GemmLayerNorm ln, const _Float16 *__restrict__ W1p,
+                                                                const float *__restrict__ b1, const _Float16 *__restrict__ W2p,
+                                                                const float *__restrict__ b2) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  constexpr int K = 512, TM = 32, LD = K + 8, KS = K / 16, SL = 8, NE = K / 64, RPW = TM / GS_WAVES;
+  typedef float f32x4 __attribute__((ext_vector_type(4)));
+  _Float16 *sx = (_Float16 *)smem, *su = sx + 2 * TM * LD;  // planes of the rows and of the hidden state: head rows, then tail rows
+  const int tid = threadIdx.x, lane = tid & 63, li = lane & 31, g = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int tiles = (M + TM - 1) / TM;
+  const __amdgpu_buffer_rsrc_t r1 = __builtin_amdgcn_make_buffer_rsrc((void *)W1p, 0, NC * K * K * 2, 0x00020000);
+  const __amdgpu_buffer_rsrc_t r2 = __builtin_amdgcn_make_buffer_rsrc((void *)W2p, 0, NC * K * K * 2, 0x00020000);
+  auto wload = [&](const __amdgpu_buffer_rsrc_t &r, int soff, int nb) -> half8 {
+    return __builtin_bit_cast(half8, (u32x4)__builtin_amdgcn_raw_buffer_load_b128(r, lane * 16 + nb * 1024, soff, 0));
+  };
+  auto at1 = [&](int c) { return (c * GS_WAVES + wave) * (KS * 2048); };       // this wave's strip of chunk c of the first matrix
+  auto at2 = [&](int c) { return wave * (NC * KS * 2048) + c * (KS * 2048); };  // and the k-range of chunk c of its strip of the second
+
+  half8 wb[SL][2];
+  floatx16 acc2[2];
+  float xv[RPW][NE];
+  auto request_rows = [&](int m0) {  // rows past M repeat row M - 1
+#pragma unroll
+    for (int i = 0; i < RPW; i++) {
+      const float *xr = x + (long)min(m0 + wave + GS_WAVES * i, M - 1) * K + lane * NE;
+#pragma unroll
+      for (int j = 0; j < NE; j += 4) {
+        const f32x4 t = *(const f32x4 *)(xr + j);
+        xv[i][j] = t[0], xv[i][j + 1] = t[1], xv[i][j + 2] = t[2], xv[i][j + 3] = t[3];
+      }
+    }
+  };
+  // 32 k-steps over both planes; the ring holds k-steps 0 .. SL - 2 of `cur` on entry and of `next` on exit
+  auto k_loop = [&](const _Float16 *planes, const __amdgpu_buffer_rsrc_t &rc, int cur, const __amdgpu_buffer_rsrc_t &rn, int next, floatx16 (&acc)[2],
+                    auto fresh_tag) __attribute__((always_inline)) {
+    constexpr bool FRESH = decltype(fresh_tag)::value;
+    const _Float16 *hrow = planes + li * LD + g * 8;
+    half8 hf[2];
+    hf[0] = *(const half8 *)hrow;
+    hf[1] = *(const half8 *)(hrow + TM * LD);
+#pragma unroll
+    for (int ks = 0; ks < KS; ks++)
+#pragma unroll
+      for (int op = 0; op < 2; op++) {
+#pragma unroll
+        for (int nb = 0; nb < 2; nb++) {
+          if (FRESH && ks == 0 && op == 0) {
+            const floatx16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+            acc[nb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(hf[op], wb[ks % SL][nb], zero, 0, 0, 0);
+          } else {
+            acc[nb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(hf[op], wb[ks % SL][nb], acc[nb], 0, 0, 0);
+          }
+        }
+        // refill what was just consumed; the scheduling barrier keeps the loads this far ahead of their use
+        hf[op] = *(const half8 *)(hrow + op * TM * LD + (ks + 1) % KS * 16);
+        if (op == 0) {
+          const int tgt = ks + SL - 1;
+#pragma unroll
+          for (int nb = 0; nb < 2; nb++) wb[tgt % SL][nb] = tgt < KS ? wload(rc, cur + tgt * 2048, nb) : wload(rn, next + (tgt - KS) * 2048, nb);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+  };
+
+  int tile = blockIdx.x;
+  if (tile >= tiles) return;
+  request_rows(tile * TM);
+#pragma unroll
+  for (int q = 0; q < SL - 1; q++)
+#pragma unroll
+    for (int nb = 0; nb < 2; nb++) wb[q][nb] = wload(r1, at1(0) + q * 2048, nb);
+  float bias2[2];
+#pragma unroll
+  for (int nb = 0; nb < 2; nb++) bias2[nb] = b2[wave * 64 + nb * 32 + li];
+  if (wave < GS_WAVES / 2) __builtin_amdgcn_s_setprio(2);  // as in gemm_stream_kernel
+
+  for (; tile < tiles; tile += gridDim.x) {
+    const int m0 = tile * TM;
+    gs_normalise<NE, RPW, TM, true>(xv, ln, sx, wave, lane);
+    __syncthreads();
+#pragma unroll
+    for (int nb = 0; nb < 2; nb++)
+#pragma unroll
+      for (int v = 0; v < 16; v++) acc2[nb][v] = 0.f;
+    float res[2][16];
+    float *xo = x + (long)(m0 + g * 4) * K + wave * 64 + li;
+    auto chunk = [&](int c, auto last_tag) __attribute__((always_inline)) {
+      constexpr bool LAST = decltype(last_tag)::value;
+      float bias1[2];
+#pragma unroll
+      for (int nb = 0; nb < 2; nb++) bias1[nb] = b1[(c * GS_WAVES + wave) * 64 + nb * 32 + li];
+      floatx16 acc1[2];
+      k_loop(sx, r1, at1(c), r2, at2(c), acc1, std::true_type{});
+      __syncthreads();  // every wave is done with the hidden planes of the chunk before
+#pragma unroll
+      for (int nb = 0; nb < 2; nb++)
+#pragma unroll
+        for (int v = 0; v < 16; v++) {
+          const float u = as_f32(fmaxf(acc1[nb][v] + bias1[nb], 0.f));
+          const _Float16 hi = (_Float16)u;
+          _Float16 *p = su + ((v >> 2) * 8 + g * 4 + (v & 3)) * LD + wave * 64 + nb * 32 + li;
+          p[0] = hi;
+          p[TM * LD] = (_Float16)(u - (float)hi);
+        }
+      __syncthreads();
+      if (LAST) {  // residual, and the next tile's rows (the last tile reads its own again)
+#pragma unroll
+        for (int nb = 0; nb < 2; nb++)
+#pragma unroll
+          for (int v = 0; v < 16; v++) {
+            const int r = (v >> 2) * 8 + (v & 3);
+            res[nb][v] = xo[(long)(min(m0 + g * 4 + r, M - 1) - m0 - g * 4) * K + nb * 32];
+          }
+        request_rows((tile + (int)gridDim.x < tiles ? tile + (int)gridDim.x : tile) * TM);
+      }
+      k_loop(su, r2, at2(c), r1, at1(LAST ? 0 : c + 1), acc2, std::false_type{});
+    };
+#pragma unroll 1
+    for (int c = 0; c < NC - 1; c++) chunk(c, std::false_type{});
+    chunk(NC - 1, std::true_type{});
+    if (__builtin_expect(m0 + TM <= M, 1)) {  // straight-line stores, as in gemm_stream_kernel
+#pragma unroll
+      for (int nb = 0; nb < 2; nb++)
+#pragma unroll
+        for (int v = 0; v < 16; v++) xo[((v >> 2) * 8 + (v & 3)) * K + nb * 32] = acc2[nb][v] + bias2[nb] + res[nb][v];
+    } else {
+#pragma unroll
+      for (int nb = 0; nb < 2; nb++)
+#pragma unroll
+        for (int v = 0; v < 16; v++)
+          if (m0 + g * 4 + (v >> 2) * 8 + (v & 3) < M) xo[((v >> 2) * 8 + (v & 3)) * K + nb * 32] = acc2[nb][v] + bias2[nb] + res[nb][v];
+      __builtin_amdgcn_s_waitcnt(0x0F70);
+    }
+  }
+}
+
 // workgroups per row tile with 32-column strips: four strips each, or two where N is an odd multiple of 64
 static int gs_narrow_groups(int N) { return N % 128 == 0 ? N / 128 : N / 64; }
 
@@ -573,6 +726,29 @@ hipError_t launch_gemm_stream_k(bool c_f32, const _Float16 *A, const _Float16 *A
                      : gs_launch<2, 512, CF_, false, TL_, NC_>(A, A_lo, lda, M, Wp, N, e, ln, s);
   NT_GSK_CASE(2, true, true) NT_GSK_CASE(2, true, false) NT_GSK_CASE(4, true, true) NT_GSK_CASE(4, true, false)
 #undef NT_GSK_CASE
+  return hipErrorInvalidValue;
+}
+
+bool gemm_ffn_supported(int M, int d, int F) { return d == 512 && (F == 1024 || F == 2048) && M >= kFfnMinRows; }
+
+template <int NC>
+static hipError_t gf_launch(float *x, int M, const GemmLayerNorm &ln, const _Float16 *W1p, const float *b1, const _Float16 *W2p, const float *b2, hipStream_t s) {
+  auto kern = gemm_ffn_kernel<NC>;
+  constexpr int lds = 4 * 32 * (512 + 8) * 2;
+  static std::once_flag once;
+  static hipError_t attr_err = hipSuccess;
+  std::call_once(once, [&] { attr_err = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds); });
+  if (attr_err != hipSuccess) return attr_err;
+  const int tiles = (M + 31) / 32;
+  hipLaunchKernelGGL(kern, dim3((unsigned)(tiles < 256 ? tiles : 256)), dim3(GS_WAVES * 64), lds, s, x, M, ln, W1p, b1, W2p, b2);
+  return hipGetLastError();
+}
+
+hipError_t launch_gemm_ffn(float *x, int M, int F, const GemmLayerNorm &ln, const _Float16 *W1p, const float *b1, const _Float16 *W2p, const float *b2,
+                           hipStream_t s) {
+  if (M <= 0) return hipSuccess;
+  if (F == 1024) return gf_launch<2>(x, M, ln, W1p, b1, W2p, b2, s);
+  if (F == 2048) return gf_launch<4>(x, M, ln, W1p, b1, W2p, b2, s);
   return hipErrorInvalidValue;
 }
 

@@ -910,7 +910,10 @@ int nt_encode(nt_model *m, const int32_t *d_src, const int32_t *d_len, int32_t B
     KT(K_GEMM_ENC_O, gemm_bytes(Md, dd, dd, ea, 4, true), 2 * Md * dd * dd,
        nt::launch_gemm(amode, true, m->ctx_enc, lo_of(m->ctx_enc, lo_d), d, L.self.Wo, M, d, d, o, s, L.self.Wo_p,
                        (m->enc_tails & 2u) != 0));
-    if (F > 0) {
+    if (kEncF32 && (m->enc_tails & 8u) && L.ffn.W1_p && L.ffn.W2_p && nt::gemm_ffn_supported(M, d, F)) {
+      KT(K_GEMM_ENC_FFN, Md * dd * 8 + 4 * dd * F, 4 * Md * dd * F,
+         nt::launch_gemm_ffn(m->x, M, F, nt::GemmLayerNorm{L.ln2.g, L.ln2.b, lne}, L.ffn.W1_p, L.ffn.b1, L.ffn.W2_p, L.ffn.b2, s));
+    } else if (F > 0) {
       nt::GemmEpilogue f1;
       f1.bias = L.ffn.b1; f1.relu = 1; f1.dst0 = m->u_enc; f1.ld0 = F; f1.n_split = F;
       f1.dst_lo_offset = kEncF32 ? lo_F : 0;

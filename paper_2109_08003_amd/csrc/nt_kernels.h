@@ -88,6 +88,15 @@ hipError_t launch_gemm_stream_ln(bool c_f32, const float *X, long ldx, const Gem
 hipError_t launch_gemm_stream(bool c_f32, const _Float16 *A, const _Float16 *A_lo, long lda, const _Float16 *Wp, int M,
                               int N, int K, const GemmEpilogue &e, hipStream_t s, bool tail = true);
 
+// x [M][512] += relu(LayerNorm(x) W1^T + b1) W2^T + b2 in one launch; both matrices in fragment order, hidden width F.  A tile of 32 rows takes
+// its workgroup 65 us at F = 2,048, so the line lies where two launches, which spread a tile over several, take as long: six layers with 8
+// heads at 2,048 / 3,072 / 4,096 tokens 469 / 509 / 541 us with it and 418 / 562 / 625 without; 8,192, 16,384, 65,536: 832 / 1,535 / 6,079
+// against 976 / 1,828 / 6,581.
+constexpr int kFfnMinRows = 2560;
+bool gemm_ffn_supported(int M, int d, int F);  // and worth it
+hipError_t launch_gemm_ffn(float *x, int M, int F, const GemmLayerNorm &ln, const _Float16 *W1p, const float *b1, const _Float16 *W2p, const float *b2,
+                           hipStream_t s);
+
 // Decoder-step variant for small M (fp32 A and C): 32 x 32 tiles, whole-K operand panels loaded
 // in one round trip.  If ln_g != nullptr the rows of A are LayerNorm-ed first (requires K to be
 // the row width, 256 or 512).  K must be a multiple of 256.

@@ -1033,6 +1033,31 @@ def test_encoder_attention_keeps_22_bits(nt, oracle, torch_cuda, heads, clip, ro
     gm.close()
 
 
+# ------------------------------------------------------------------------------ the encoder's FFN in one launch
+@pytest.mark.parametrize("ffn", [1024, 2048])
+@pytest.mark.parametrize("rows,S,l1", [(80, 32, 0), (197, 13, 1), (274, 30, 0), (1031, 19, 0)])
+def test_encoder_ffn_in_one_launch(nt, oracle, torch_cuda, ffn, rows, S, l1):
+    """At its line (2,560 tokens), one tile of 32 tokens more and partly filled, past one tile per workgroup (8,220 tokens) and past two
+    (19,589, the last tile partly filled).  Sentences of one token at the ends of the batch.  Bound: as the attention test above has
+    it for its six pairs and three products, with four pairs and two products of 512 and ffn terms more: 5e-7, and twice that."""
+    torch = torch_cuda
+    cfg = nt_synth.model_config("C1", d_model=512, vocab=300, n_enc=1, max_len=64, dec_d_ffn=-1, n_heads=8, d_ffn=ffn, ln_l1=l1)
+    blob = nt_synth.make_weights(cfg, seed=21, random_affine=True)
+    gm, om = nt.Model(cfg, blob, max_batch_tokens=32768, pipeline_lanes=1), oracle.Model(cfg, blob)
+    rng = np.random.default_rng(rows)
+    src = [rng.integers(4, 300, size=n).astype(np.int32) for n in [1] + [S] * (rows - 2) + [1]]
+    ids, lens = pad(src, cfg["pad_id"])
+    gm.encode(torch.from_numpy(ids).cuda(), torch.from_numpy(lens).cuda())
+    out = torch.empty(rows, S, 512, dtype=torch.float32, device="cuda")
+    gm.debug_encoder_out(out)
+    out = out.cpu().numpy().astype(np.float64)
+    assert np.isfinite(out).all()
+    err = max(rel_l2(out[i, : lens[i]], om.encode(src[i])) for i in sorted({0, 1, rows // 3, rows // 2, rows - 2, rows - 1}))
+    print(f"ffn {ffn}, {rows} x {S}: {err:.1e}")
+    assert err <= 1e-6
+    gm.close()
+
+
 # ------------------------------------------------------------------------------ head and tail of a split value
 @pytest.mark.parametrize("d,n_dec,heads", [(512, 1, 8), (512, 2, 1), (256, 2, 1)])
 def test_heads_and_tails_are_of_the_same_value(nt, oracle, torch_cuda, d, n_dec, heads):
