@@ -326,15 +326,20 @@ __device__ __forceinline__ void split8u(const float *f, half8 &hi, half8 &lo) {
 // the scores (the same MFMAs in the same order, with more of their operands in flight) and takes a quarter of the value
 // columns, whose 16 blocks in turn are most of a lone wave's time (one sentence of 22 tokens: 23 us with one wave, 14 with four;
 // with all value blocks requested before the softmax one sentence 1010 -> 1000 us, 45 sentences 3225 -> 3186 us in all).
+// WPU = 16: the same over four workgroups, a wave per block of value columns, as long as that is one round (up to 64 units of 512-wide
+// heads): the encoder of one sentence of 22 / 64 / 128 tokens 203 -> 189 / 231 -> 211 / 310 -> 269 us, 32 of 32 tokens 256 -> 238.  With 256-wide
+// heads, whose eight blocks leave four waves two each, it gains nothing at one sentence and costs 2 to 11 % from 32 units on.
 // REL: relative keys of clip distance <= 15, taken as one more block of keys: rk . q for the 2 clip + 1 offsets comes out of the
 // MFMAs with a query per lane, goes through the LDS and is added to the scores by clipped distance.
 template <int DH, int NKB, bool QK16, int WPU, bool REL>
-__global__ __launch_bounds__(256, WPU == 4 ? 1 : NKB == 1 ? 3 : NKB == 2 ? 2 : 1) void enc_attention_wave_kernel(const float *qkv, const _Float16 *qk16, const int32_t *len, _Float16 *ctx,
+__global__ __launch_bounds__(256, WPU >= 4 ? 1 : NKB == 1 ? 3 : NKB == 2 ? 2 : 1) void enc_attention_wave_kernel(const float *qkv, const _Float16 *qk16, const int32_t *len, _Float16 *ctx,
                                                                  long ctx_lo_offset, int B, int S, int d, int heads,
                                                                  int q_tiles, const float *rk, int clip) {
   __shared__ float sRel[REL ? 4 : 1][REL ? 32 * 32 : 1];  // per wave [offset][query]
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, li = lane & 31, g = lane >> 5;
-  const long unit = WPU == 4 ? (long)blockIdx.x : (long)blockIdx.x * 4 + wave;  // uniform over the wave, and known to be: addresses below are a
+  constexpr int WGU = WPU >= 4 ? WPU / 4 : 1;  // workgroups per unit
+  const int part = WPU >= 4 ? (int)(blockIdx.x % WGU) * 4 + wave : 0;  // this wave's share of the unit
+  const long unit = WPU >= 4 ? (long)(blockIdx.x / WGU) : (long)blockIdx.x * 4 + wave;  // uniform over the wave, and known to be: addresses below are a
                                                    // uniform 64-bit base plus a 32-bit lane offset
   if (unit >= (long)B * heads * q_tiles) return;
   const int qt = (int)(unit % q_tiles), h = (int)((unit / q_tiles) % heads), b = (int)(unit / ((long)q_tiles * heads));
@@ -342,7 +347,7 @@ __global__ __launch_bounds__(256, WPU == 4 ? 1 : NKB == 1 ? 3 : NKB == 2 ? 2 : 1
   const long row0 = (long)b * S, ld = QK16 ? (long)d : 3L * d;  // row stride of the fp32 array (v alone, or q|k|v)
   const int hoff = h * DH;
   if (q0 >= L) {  // padding queries: defined output, no work
-    if (WPU == 4 && wave != 0) return;
+    if (part != 0) return;
     for (int i = lane; i < 32 * DH; i += 64) {
       const int r = i / DH, c = i % DH;
       if (q0 + r < S) {
@@ -353,7 +358,7 @@ __global__ __launch_bounds__(256, WPU == 4 ? 1 : NKB == 1 ? 3 : NKB == 2 ? 2 : 1
     return;
   }
   const int nkb = (L + 31) / 32;  // <= NKB, checked by the launcher through S
-  constexpr int CU = WPU == 4 ? (NKB == 1 ? 4 : 2) : 1;  // 64-wide slices of the scores requested together
+  constexpr int CU = WPU >= 4 ? (NKB == 1 ? 4 : 2) : 1;  // 64-wide slices of the scores requested together
 
   // ---- values: 32-column blocks, requested ahead of their use ----
   // With two key blocks the V values of the next block are requested before the MFMAs and stores of the current one
@@ -362,8 +367,8 @@ __global__ __launch_bounds__(256, WPU == 4 ? 1 : NKB == 1 ? 3 : NKB == 2 ? 2 : 1
   // slices of the scores, so that the values travel during the softmax.
   const char *vbase = (const char *)(qkv + row0 * ld + (QK16 ? 0 : 2 * d) + hoff);
   constexpr int STEP = WPU, NCB = DH / 32;
-  constexpr bool UP_FRONT = WPU == 4 && NKB <= 3, PREFETCH = NKB == 2 && !UP_FRONT;
-  const int cb_first = WPU == 4 ? wave : 0;
+  constexpr bool UP_FRONT = WPU >= 4 && NKB <= 3, PREFETCH = NKB == 2 && !UP_FRONT;
+  const int cb_first = part;
   float fv[UP_FRONT ? NCB / STEP : PREFETCH ? 2 : 1][NKB][2][8];
   auto request = [&](int cb, int slot) {
     // the block's base stays one opaque scalar pair: otherwise every one of the 16 addresses becomes a 64-bit
@@ -611,9 +616,13 @@ static hipError_t enc_attention_wave_launch(const float *qkv, const int32_t *len
   const dim3 block(256);
   // wide heads only: a narrow one has a few column blocks in all
   const bool share = DH >= 256 && units < 1024;
+  const bool spread = DH == 512 && units <= 64;
 #define NT_WAVE_CASE(NKB)                                                                                                  \
   case NKB:                                                                                                                \
-    if (share)                                                                                                             \
+    if (spread)                                                                                                            \
+      hipLaunchKernelGGL((enc_attention_wave_kernel<DH, NKB, QK16, DH == 512 ? 16 : 1, REL>), dim3((unsigned)(units * 4)), block, 0, s, \
+                         qkv, qk16, len, ctx, ctx_lo_offset, B, S, d, heads, q_tiles, rk, clip);                           \
+    else if (share)                                                                                                        \
       hipLaunchKernelGGL((enc_attention_wave_kernel<DH, NKB, QK16, DH >= 256 ? 4 : 1, REL>), dim3((unsigned)units), block, 0, s, \
                          qkv, qk16, len, ctx, ctx_lo_offset, B, S, d, heads, q_tiles, rk, clip);                           \
     else                                                                                                                   \
