@@ -622,13 +622,12 @@ __global__ __launch_bounds__(NWAVES * 64) void dec1_kernel(Dec1Args a) {
   };
   // attention of this wave's row over n cached keys; the partials may hold the newest key already.  The merged context
   // goes to done(ctx) in the row's first wave
-  // Two blocks in flight: the next one of the wave's only partial, or one of each of its two.  b holds a single partial's
-  // first two blocks already if PRELOADED (see first_blocks)
+  // Two blocks in flight: the next one of the wave's only partial, or one of each of its two.  b holds the first
+  // `preloaded` blocks of a single partial already (see first_block)
   constexpr int STEP = PARTS * D1_NK;
   const int j_first = pg * PW * D1_NK;
-  auto first_blocks = [&](auto (&b)[2], const void *kv, const float *sc, long pos0, int n) {
-    if (j_first < n) b[0].load(kv, sc, pos0, j_first, n, lane);
-    if (j_first + STEP < n) b[1].load(kv, sc, pos0, j_first + STEP, n, lane);
+  auto first_block = [&](auto &b, int which, const void *kv, const float *sc, long pos0, int n) {
+    if (j_first + which * STEP < n) b.load(kv, sc, pos0, j_first + which * STEP, n, lane);
   };
   auto attend = [&](auto (&b)[2], auto preloaded, const float (&q)[NE], const void *kv, const float *sc, long pos0, int n, const D1Rel &rel, Part (&st)[PW], auto done) {
     if constexpr (NWAVES == 16) {  // 128 registers: one block at a time
@@ -640,7 +639,8 @@ __global__ __launch_bounds__(NWAVES * 64) void dec1_kernel(Dec1Args a) {
             b[0].fold(q, j + u * D1_NK, n, lane, st[u], rel);
           }
     } else if constexpr (PW == 1) {
-      if (!decltype(preloaded)::value) first_blocks(b, kv, sc, pos0, n);
+#pragma unroll
+      for (int u = decltype(preloaded)::value; u < 2; u++) first_block(b[u], u, kv, sc, pos0, n);
       for (int j = j_first; j < n; j += 2 * STEP) {
         b[0].fold(q, j, n, lane, st[0], rel);
         if (j + 2 * STEP < n) b[0].load(kv, sc, pos0, j + 2 * STEP, n, lane);
@@ -703,8 +703,8 @@ __global__ __launch_bounds__(NWAVES * 64) void dec1_kernel(Dec1Args a) {
   const long cross0 = (long)rc * a.cross_positions, self0 = (long)rc * a.self_positions;
   const int n_cached = n_self > 0 ? n_self - 1 : 0;
   if constexpr (FOLD) {  // the first blocks of both caches depend on nothing computed here
-    first_blocks(sb, a.self_kv, a.self_sc, self0, n_cached);
-    first_blocks(cb, a.cross_kv, a.cross_sc, cross0, n_cross);
+    first_block(sb[0], 0, a.self_kv, a.self_sc, self0, n_cached);
+    first_block(cb[0], 0, a.cross_kv, a.cross_sc, cross0, n_cross);
   }
   float q[NE], z[NE], kx[NE], vx[NE];  // z, kx, vx: the row's first wave
   if (a.table.rows) {
@@ -718,6 +718,11 @@ __global__ __launch_bounds__(NWAVES * 64) void dec1_kernel(Dec1Args a) {
       d1_load<NE>(a.kv_new + (long)r * 2 * D + lane * NE, kx);
       d1_load<NE>(a.kv_new + (long)r * 2 * D + D + lane * NE, vx);
     }
+  }
+  if constexpr (FOLD) {  // the second ones when the start no longer needs its registers: with two waves on a SIMD it makes way for others
+    __builtin_amdgcn_sched_barrier(0);
+    first_block(sb[1], 1, a.self_kv, a.self_sc, self0, n_cached);
+    first_block(cb[1], 1, a.cross_kv, a.cross_sc, cross0, n_cross);
   }
   if (pg == 0) {
     if constexpr (FOLD) {  // the bias of the self-attention's output, which no projection adds, and the values' column scales
@@ -783,8 +788,8 @@ __global__ __launch_bounds__(NWAVES * 64) void dec1_kernel(Dec1Args a) {
         d1_quantize_store<NE>(vx, dst + D, a.self_sc + p * 2 + 1, lane);
       }
     }
-    if constexpr (FOLD) attend(sb, std::true_type{}, q, a.self_kv, a.self_sc, self0, n_cached, rel, st, add_self_context);
-    else attend(sb, std::false_type{}, q, a.self_kv, a.self_sc, self0, n_cached, rel, st, store_planes);
+    if constexpr (FOLD) attend(sb, std::integral_constant<int, 2>{}, q, a.self_kv, a.self_sc, self0, n_cached, rel, st, add_self_context);
+    else attend(sb, std::integral_constant<int, 0>{}, q, a.self_kv, a.self_sc, self0, n_cached, rel, st, store_planes);
   }
   // ---- output projection + residual, LayerNorm, cross-attention query ----
   if constexpr (!FOLD) {
@@ -801,7 +806,7 @@ __global__ __launch_bounds__(NWAVES * 64) void dec1_kernel(Dec1Args a) {
     Part st[PW];
 #pragma unroll
     for (int u = 0; u < PW; u++) st[u].clear();
-    attend(cb, std::true_type{}, q, a.cross_kv, a.cross_sc, cross0, n_cross, D1Rel{}, st, add_context);
+    attend(cb, std::integral_constant<int, 2>{}, q, a.cross_kv, a.cross_sc, cross0, n_cross, D1Rel{}, st, add_context);
   } else {
     {
       float y[NE];
@@ -824,7 +829,7 @@ __global__ __launch_bounds__(NWAVES * 64) void dec1_kernel(Dec1Args a) {
 #pragma unroll
       for (int u = 0; u < PW; u++) st[u].clear();
       d1_load<NE>(sQ + rw * ZLD + lane * NE, q);
-      attend(cb, std::false_type{}, q, a.cross_kv, a.cross_sc, cross0, n_cross, D1Rel{}, st, store_planes);
+      attend(cb, std::integral_constant<int, 0>{}, q, a.cross_kv, a.cross_sc, cross0, n_cross, D1Rel{}, st, store_planes);
     }
     if (!EARLY) preload(a.Wo_cross);
     project(a.Wo_cross, sA);
@@ -902,8 +907,11 @@ static hipError_t d1_launch(const Dec1Args &a, hipStream_t s) {
   } while (0)
   if constexpr (!HEADS) {
     if (a.folded) {
-      if constexpr (FFN) NT_D1(2, 8, 4, true);
-      else NT_D1(1, 4, 4, true);
+      // one row per workgroup has 266 registers and a CU to itself; two rows have 256 (15 spilled) and still four waves each, so that
+      // more than 256 rows are one round (a step of 250 / 300 / 400 / 511 rows alone: 31.8 / 40.3 / 41.9 / 45.3 us and 32.4 / 36.1 / 37.9 / 41.6;
+      // of one and 45 rows 15.1 / 22.5 and 15.6 / 23.0)
+      if (FFN || shape > 256) NT_D1(2, 8, 4, true);
+      else if constexpr (!FFN) NT_D1(1, 4, 4, true);
       return hipGetLastError();
     }
   }
