@@ -504,6 +504,8 @@ __global__ __launch_bounds__(NWAVES * 64) void dec1_kernel(Dec1Args a) {
   __shared__ __attribute__((aligned(16))) float sQ[RW * (D + 8)];                 // FOLD: scales; cross-attention query, later:
   _Float16 *sU = (_Float16 *)sQ;                                                  // FFN hidden state, head rows, then tail rows
   __shared__ float sPart[WR > 1 ? RW * (PARTS - PW) * (NE + 2) * 64 : 1];         // partial softmaxes of the waves pg > 0
+  constexpr int NV = FFN ? 6 : 4, LN2 = 0, LN3 = 2, LNF = NV - 2;  // vectors of the normalisations
+  __shared__ __attribute__((aligned(16))) float sNorm[NV * D];
   __shared__ float sRel[HEADS ? RW * (D1_MAX_CLIP + 1) * 8 : 1];                  // per row: [distance][head]
   const int tid = threadIdx.x, lane = tid & 63, h = lane >> 4, c16 = lane & 15;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -512,6 +514,12 @@ __global__ __launch_bounds__(NWAVES * 64) void dec1_kernel(Dec1Args a) {
   const bool valid = row0 + rw < a.rows;
   D1Token token;
   if (a.table.rows) token.request(a, row0 + rw, lane);
+  // the normalisations' gains and offsets go to the LDS while the start of the row travels, a vector per wave: read where they are used,
+  // each would be another turn of the memory system in the row's chain
+  float norm[NE];
+  const GemmLayerNorm &norm_of = wave < 2 ? a.ln2 : FFN && wave < 4 ? a.ln3 : a.lnf;
+  const float *norm_src = wave >= NV ? nullptr : wave & 1 ? norm_of.beta : norm_of.gamma;  // (no final one: nullptr)
+  if (norm_src) d1_load<NE>(norm_src + lane * NE, norm);
   const int r = valid ? row0 + rw : 0;
   int rc = r;
   if (IND) rc = valid ? a.origin[r] : -1;
@@ -585,10 +593,12 @@ __global__ __launch_bounds__(NWAVES * 64) void dec1_kernel(Dec1Args a) {
 #pragma unroll
       for (int v = 0; v < (RW < 4 ? RW : 4); v++) f((RW == 16 ? h : h & 1) * 4 + v, n0 + t * 16 + c16, acc[t][v]);
   };
-  auto add_residual = [&](const float *b) {
-    float bias[NT];
+  float bias[NT];  // of the wave's columns, requested ahead of the product
+  auto request_bias = [&](const float *b) {
 #pragma unroll
     for (int t = 0; t < NT; t++) bias[t] = b[n0 + t * 16 + c16];
+  };
+  auto add_residual = [&]() {
     results([&](int i, int n, float x) { float *z = sZ + i * ZLD + n; *z = x + bias[(n - n0) >> 4] + *z; });
   };
   auto store_planes = [&](const float (&y)[NE]) {
@@ -604,10 +614,10 @@ __global__ __launch_bounds__(NWAVES * 64) void dec1_kernel(Dec1Args a) {
     *(halfNE *)(sA + (RW + rw) * LD + lane * NE) = lo;
   };
   // LayerNorm of this wave's row of the residual stream: fp32, mean first, then the variance of the centred values
-  auto normalise = [&](const float *gamma, const float *beta, float (&y)[NE]) {
+  auto normalise = [&](int which, float (&y)[NE]) {
     float ga[NE], be[NE];
-    d1_load<NE>(gamma + lane * NE, ga);
-    d1_load<NE>(beta + lane * NE, be);
+    d1_load<NE>(sNorm + which * D + lane * NE, ga);
+    d1_load<NE>(sNorm + (which + 1) * D + lane * NE, be);
     d1_load<NE>(sZ + rw * ZLD + lane * NE, y);
     float s = 0.f;
 #pragma unroll
@@ -719,6 +729,10 @@ __global__ __launch_bounds__(NWAVES * 64) void dec1_kernel(Dec1Args a) {
       d1_load<NE>(a.kv_new + (long)r * 2 * D + D + lane * NE, vx);
     }
   }
+  if (norm_src) {
+#pragma unroll
+    for (int e = 0; e < NE; e += 4) *(float4 *)(sNorm + wave * D + lane * NE + e) = make_float4(norm[e], norm[e + 1], norm[e + 2], norm[e + 3]);
+  }
   if constexpr (FOLD) {  // the second ones when the start no longer needs its registers: with two waves on a SIMD it makes way for others
     __builtin_amdgcn_sched_barrier(0);
     first_block(sb[1], 1, a.self_kv, a.self_sc, self0, n_cached);
@@ -794,14 +808,15 @@ __global__ __launch_bounds__(NWAVES * 64) void dec1_kernel(Dec1Args a) {
   // ---- output projection + residual, LayerNorm, cross-attention query ----
   if constexpr (!FOLD) {
     if (!EARLY) preload(a.Wo_self);
+    request_bias(a.bo_self);
     project(a.Wo_self, sA);
     preload(a.Wq);
-    add_residual(a.bo_self);
+    add_residual();
     __syncthreads();
   }
   if constexpr (FOLD) {
     // ---- cross-attention over the folded cache: the normalised row is the query, the context adds to the residual ----
-    normalise(a.ln2.gamma, a.ln2.beta, q);
+    normalise(LN2, q);
     if (FFN) preload(a.W1);
     Part st[PW];
 #pragma unroll
@@ -810,16 +825,14 @@ __global__ __launch_bounds__(NWAVES * 64) void dec1_kernel(Dec1Args a) {
   } else {
     {
       float y[NE];
-      normalise(a.ln2.gamma, a.ln2.beta, y);
+      normalise(LN2, y);
       if (pg == 0) store_planes(y);
     }
     __syncthreads();
+    request_bias(a.bq);
     project(a.Wq, sA);
     if (EARLY) preload(a.Wo_cross);
     {
-      float bias[NT];
-#pragma unroll
-      for (int t = 0; t < NT; t++) bias[t] = a.bq[n0 + t * 16 + c16];
       results([&](int i, int n, float x) { sQ[i * ZLD + n] = (x + bias[(n - n0) >> 4]) * a.q_scale; });
     }
     __syncthreads();
@@ -832,21 +845,20 @@ __global__ __launch_bounds__(NWAVES * 64) void dec1_kernel(Dec1Args a) {
       attend(cb, std::integral_constant<int, 0>{}, q, a.cross_kv, a.cross_sc, cross0, n_cross, D1Rel{}, st, store_planes);
     }
     if (!EARLY) preload(a.Wo_cross);
+    request_bias(a.bo_cross);
     project(a.Wo_cross, sA);
     if (FFN) preload(a.W1);
-    add_residual(a.bo_cross);
+    add_residual();
     __syncthreads();
   }
   if constexpr (FFN) {
     float y[NE];
-    normalise(a.ln3.gamma, a.ln3.beta, y);
+    normalise(LN3, y);
     if (pg == 0) store_planes(y);
     __syncthreads();
+    request_bias(a.b1);
     project(a.W1, sA);
     preload(a.W2);
-    float bias[NT];
-#pragma unroll
-    for (int t = 0; t < NT; t++) bias[t] = a.b1[n0 + t * 16 + c16];
     results([&](int i, int n, float x) {
       const float u = as_f32(fmaxf(x + bias[(n - n0) >> 4], 0.f));
       const _Float16 hi = (_Float16)u;
@@ -854,8 +866,9 @@ __global__ __launch_bounds__(NWAVES * 64) void dec1_kernel(Dec1Args a) {
       sU[(RW + i) * LD + n] = (_Float16)(u - (float)hi);
     });
     __syncthreads();
+    request_bias(a.b2);
     project(a.W2, sU);
-    add_residual(a.b2);
+    add_residual();
     __syncthreads();
   }
   // ---- the residual stream back, and / or the final hidden state as planes with the norm of the tail ----
@@ -869,7 +882,7 @@ __global__ __launch_bounds__(NWAVES * 64) void dec1_kernel(Dec1Args a) {
   if (a.h_hi) {
     typedef _Float16 halfNE __attribute__((ext_vector_type(NE)));
     float y[NE];
-    normalise(a.lnf.gamma, a.lnf.beta, y);
+    normalise(LNF, y);
     halfNE hi, lo;
     float tail2 = 0.f;
 #pragma unroll
