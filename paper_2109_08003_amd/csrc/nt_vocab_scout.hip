@@ -21,10 +21,11 @@
 // places and a bound on the third, in two integers, so that only a group that may hold three candidates (one row in a thousand)
 // has all its entries computed; four instructions per product.
 //
-// Measured, d = 512, 32,000 entries: scout 30.5 us (2.0 POP/s) and pick 13.5 us at 1,460 rows on average (40,000 sentences, 65,536-token budget),
-// 11.5 and 9.2 at 400, 8.0 and 8.9 at 260, where a pass over the head plane that certified its winners, the certification and the recompute
+// Measured, d = 512, 32,000 entries: scout 30.5 us (2.0 POP/s) and pick 10.5 us at 1,460 rows on average (40,000 sentences, 65,536-token budget),
+// 11.5 and 7.7 at 400, 8.0 and 5.6 at 260, where a pass over the head plane that certified its winners, the certification and the recompute
 // of the rest took 61, 5.5 and 11 us at 1,900 rows, and a pass with both planes 14 to 28 us for 65 to 512.  The scout is bound by the matrix
-// cores (operand loads, folds and the ends of strips take a good half, as in nt_vocab_q8.hip), the pick by its chain of dependent loads.
+// cores (operand loads, folds and the ends of strips take a good half, as in nt_vocab_q8.hip; a wave's
+// priority, waves started apart and a ring of eight slots changed nothing), the pick by its chain of dependent loads.
 // One scale per strip instead of per entry costs 16 candidates a row instead of 13 and saves two instructions per product.
 #include "nt_kernels.h"
 
@@ -300,12 +301,15 @@ __global__ __launch_bounds__(SC_WAVES * 64) void vocab_scout_kernel(const int8_t
 }
 
 // ---------------------------------------------------------------------------------------------------------------------
-// The candidates the scout has left, their exact logits, the arg-max: four rows per workgroup.  Two waves find a row's candidates;
-// the logits of all its rows are then dealt to groups of 16 lanes, because the rows differ (16 on average, 70 at most in a thousand)
-// and one wave with its own row's took as long as the worst row.
+// The candidates the scout has left, their exact logits, the arg-max: one or two rows per workgroup of eight waves.  All waves of a
+// row find its candidates; the logits are then dealt to groups of 16 lanes, because the rows differ (16 on average, 70 at most in a
+// thousand) and one wave with its own row's took as long as the worst row.
+// Bound by its chain of dependent loads (the scout's groups, then the candidates' rows of the matrix), so a row is spread over as many
+// waves as find work in it.  With four rows per workgroup and four entries in flight per group - most of them loads of an entry that
+// was not there, 16 to 64 candidates for 128 places - it took 7.6, 8.2, 9.9 and 12.6 us at 45, 260, 400 and 1,000 rows on average,
+// now 5.3, 5.6, 7.7 and 9.9.
 // Rows with more than kPickCap candidates have every entry computed, by the same function, once all others are done.
 // ---------------------------------------------------------------------------------------------------------------------
-constexpr int PK_ROWS = 4, PK_WAVES = 8;  // two waves find a row's candidates
 
 // Reductions over a wave in the vector unit (data-parallel primitives: rows of 16 lanes, then their broadcasts): a tenth of the
 // latency of an exchange through the LDS unit.
@@ -341,24 +345,30 @@ __device__ __forceinline__ float pk_sum16(float x) {  // over 16 lanes (rotation
   return x + __int_as_float(pk_dpp<0x121, 0xf>(0, __float_as_int(x)));
 }
 
-template <int K>
+constexpr int PK_WAVES = 8;
+// Up to so many rows, a workgroup each: 5.3 us against 5.8 with two (45 rows), 5.6 against 5.8 (260), 7.7 against 7.8 (400), but 11.8
+// against 9.9 at 1,000, where the workgroups no longer fit the chip at once.
+constexpr int kPickOneRow = 512;
+
+template <int K, int PK_ROWS>
 __global__ __launch_bounds__(PK_WAVES * 64) void vocab_pick_kernel(const i32x4 *__restrict__ part, const float4 *__restrict__ row_consts,
                                                                    const float4 *__restrict__ strip_consts, const int32_t *__restrict__ ids,
                                                                    int NS, int row0, int M, float distrust,
                                                                    const _Float16 *__restrict__ h_hi, const _Float16 *__restrict__ h_lo, long ldh,
                                                                    const _Float16 *__restrict__ Ws, int32_t *tok, int32_t *slot_of_row) {
-  constexpr int CH = 4;               // strips per lane at a time
-  constexpr int STEP = 2 * 64 * CH;   // both waves of a row
+  constexpr int WPR = PK_WAVES / PK_ROWS;  // waves that find a row's candidates
+  constexpr int CH = 8 / WPR;              // strips per lane at a time
+  constexpr int STEP = WPR * 64 * CH;
   constexpr int KC = K / 128;         // runs of 128 elements: 16 lanes x 8
   constexpr int NG = PK_WAVES * 4;    // groups of 16 lanes
-  constexpr int NE = K / 64, FLY = 4;  // entries in flight per group
+  constexpr int NE = K / 64;
   __shared__ __attribute__((aligned(16))) float sx[PK_ROWS][K];
   __shared__ int32_t cand[PK_ROWS][kPickCap];
   __shared__ int count[PK_ROWS];
   __shared__ float floors[PK_WAVES];
   __shared__ unsigned long long best[PK_ROWS];
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), e16 = lane & 15, group = threadIdx.x >> 4;
-  const int own_row = wave >> 1, half = wave & 1;
+  const int own_row = wave / WPR, half = wave % WPR;
   const int i = blockIdx.x * PK_ROWS + own_row;
   const bool valid = i < M;
   const int r = row0 + (valid ? i : 0);
@@ -370,7 +380,7 @@ __global__ __launch_bounds__(PK_WAVES * 64) void vocab_pick_kernel(const i32x4 *
     auto load = [&](int s0) {
 #pragma unroll
       for (int c = 0; c < CH; c++) {
-        const int s = s0 + (2 * c + half) * 64 + lane;
+        const int s = s0 + (WPR * c + half) * 64 + lane;
         const int at = s < NS ? s : NS - 1;  // past the end: the last strip again, left out below
         p[c] = mine[at];
         sc[c] = strip_consts[at];
@@ -403,7 +413,9 @@ __global__ __launch_bounds__(PK_WAVES * 64) void vocab_pick_kernel(const i32x4 *
                                                              (float)xh[e + 2] + (float)xl[e + 2], (float)xh[e + 3] + (float)xl[e + 3]);
     }
     __syncthreads();
-    floor_ = fmaxf(floors[2 * own_row], floors[2 * own_row + 1]);
+    floor_ = floors[WPR * own_row];
+#pragma unroll
+    for (int w = 1; w < WPR; w++) floor_ = fmaxf(floor_, floors[WPR * own_row + w]);
     // every lane counts its own groups' candidates, then all write theirs
     for (int s0 = 0; s0 < NS && valid; s0 += STEP) {
       if (NS > STEP) load(s0);
@@ -411,7 +423,7 @@ __global__ __launch_bounds__(PK_WAVES * 64) void vocab_pick_kernel(const i32x4 *
 #pragma unroll
       for (int c = 0; c < CH; c++) {
         const float unit = rc.x * sc[c].x, least = floor_ - bound(sc[c]);
-        const bool there = s0 + (2 * c + half) * 64 + lane < NS;
+        const bool there = s0 + (WPR * c + half) * 64 + lane < NS;
 #pragma unroll
         for (int g = 0; g < 2; g++) {
           const int second = p[c][2 * g + 1] >> 8, apart = p[c][2 * g + 1] >> 5 & 7;
@@ -430,7 +442,7 @@ __global__ __launch_bounds__(PK_WAVES * 64) void vocab_pick_kernel(const i32x4 *
       int at = __builtin_amdgcn_readfirstlane(base) + upto - own;
       auto add = [&](int c, int g, int code) {
         if (at < kPickCap)
-          cand[own_row][at] = (s0 + (2 * c + half) * 64 + lane) * 64 + (code >> 4) * 32 + ((code & 15) >> 2) * 8 + g * 4 + (code & 3);
+          cand[own_row][at] = (s0 + (WPR * c + half) * 64 + lane) * 64 + (code >> 4) * 32 + ((code & 15) >> 2) * 8 + g * 4 + (code & 3);
         at++;
       };
 #pragma unroll
@@ -470,26 +482,20 @@ __global__ __launch_bounds__(PK_WAVES * 64) void vocab_pick_kernel(const i32x4 *
     many |= n > kPickCap ? 1u << w : 0u;
     first[w + 1] = first[w] + (n > kPickCap ? 0 : n);
   }
-  for (int c0 = 0; c0 < first[PK_ROWS]; c0 += FLY * NG) {
-    int id[FLY], row[FLY];
-    half8 w[FLY][KC];
+  // (a wave without a candidate left drops out; within a wave all groups load, which is faster than a branch around the loads)
+  for (int c0 = wave * 4; c0 < first[PK_ROWS]; c0 += NG) {
+    const int c = c0 + (lane >> 4);
+    int row = 0, from = 0;
 #pragma unroll
-    for (int u = 0; u < FLY; u++) {
-      const int c = c0 + u * NG + group;
-      int from = 0;
-      row[u] = 0;
-#pragma unroll
-      for (int q = 1; q < PK_ROWS; q++)
-        if (c >= first[q]) row[u] = q, from = first[q];
-      const int place = c < first[PK_ROWS] ? cand[row[u]][c - from] : 0;
-      fetch(w[u], place);
-      id[u] = c < first[PK_ROWS] ? ids[place] : -1;
-    }
-#pragma unroll
-    for (int u = 0; u < FLY; u++) {
-      const float s = dot(w[u], row[u]);
-      if (e16 == 0 && id[u] >= 0) atomicMax(&best[row[u]], argmax_key(s, id[u]));
-    }
+    for (int q = 1; q < PK_ROWS; q++)
+      if (c >= first[q]) row = q, from = first[q];
+    const bool there = c < first[PK_ROWS];
+    const int place = there ? cand[row][c - from] : 0;
+    half8 w[KC];
+    fetch(w, place);
+    const int id = there ? ids[place] : -1;
+    const float s = dot(w, row);
+    if (e16 == 0 && id >= 0) atomicMax(&best[row], argmax_key(s, id));
   }
   if (many) {
     unsigned long long mine[PK_ROWS] = {};
@@ -545,8 +551,13 @@ static hipError_t scout_launch(const VocabScout &v, const _Float16 *h, const _Fl
                        p.m_tiles, p.G, p.per_xcd, NS / p.G, NS % p.G, magic, (i32x2 *)v.scratch);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((vocab_pick_kernel<K>), dim3((rows + PK_ROWS - 1) / PK_ROWS), dim3(PK_WAVES * 64), 0, s, (const i32x4 *)v.scratch,
-                       (const float4 *)v.row_consts, consts, ids, NS, r0, rows, distrust ? INFINITY : 0.f, h, h_lo, ldh, (const _Float16 *)(ids + 64 * NS), tok, slot_of_row);
+    auto pick = [&](auto rows_tag) {
+      constexpr int PR = decltype(rows_tag)::value;
+      hipLaunchKernelGGL((vocab_pick_kernel<K, PR>), dim3((rows + PR - 1) / PR), dim3(PK_WAVES * 64), 0, s, (const i32x4 *)v.scratch,
+                         (const float4 *)v.row_consts, consts, ids, NS, r0, rows, distrust ? INFINITY : 0.f, h, h_lo, ldh,
+                         (const _Float16 *)(ids + 64 * NS), tok, slot_of_row);
+    };
+    if (rows <= kPickOneRow) pick(std::integral_constant<int, 1>{}); else pick(std::integral_constant<int, 2>{});
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
   return hipSuccess;
