@@ -290,8 +290,9 @@ int nt_debug_teacher_forced_logits(nt_model *m, const int32_t *d_tgt_in, int32_t
  * every pipeline lane of the model and on the calls that follow):
  *   nt_debug_set_vocab_tiled(m, 1)    take the LDS-tiled arg-max kernels that other model widths use,
  *                                     instead of the streaming kernels;
- *   nt_debug_set_cert_distrust(m, 1)  certify no row in the single-pass arg-max, so that every row
- *                                     takes the head+tail recompute pass.
+ *   nt_debug_set_cert_distrust(m, 1)  rule no entry out by the bound of the 8-bit pass (tiled kernels: certify
+ *                                     no row by the head plane), so that every row has every logit computed
+ *                                     from both planes.
  *   nt_debug_set_encoder_tails(m, mask)  which encoder projections multiply the tail plane of their activations
  *                                     (about 22 significant bits) and which the head plane only (fp16, half the
  *                                     matrix-core work): bit 0 LayerNorm -> Q|K|V, bit 1 attention context -> output

@@ -9,7 +9,7 @@
 // attn_decode: one query per (row, head) against a key/value cache - the incremental decoder's
 // self-attention (fp32 cache, t+1 keys) and cross-attention (fp16 cache, len keys).  Pure HBM
 // streaming: every key and value is read once, coalesced 16/32 bytes per lane, with an online
-// softmax in registers and a butterfly merge across key groups and waves.
+// softmax in registers and a merge across key groups and waves.
 //
 // Relative position keys (Sec. 2.1, clip distance c): score_ij += q_i . rk[clamp(j-i,-c,c)+c].
 #include <math.h>

@@ -13,8 +13,8 @@
 // Attention phases: streams of 16-bit integer keys and values with one fp32 scale per vector (value = code * scale,
 // absmax / 32767: an rms error of about 3e-5 of a vector's spread where fp16 leaves 2.8e-4 of every element); the query,
 // scores, softmax and context are fp32 (Sec. 3.1 "FP16 Inference").  Lane l holds elements l * NE .. l * NE + NE - 1 of
-// every vector, so a wave instruction reads one whole vector.  Keys are taken four at a time: reduce-scatter butterfly,
-// wave-uniform scores, one rescale of the online softmax per block.  A row's blocks are dealt to 1 (1,024 rows or more)
+// every vector, so a wave instruction reads one whole vector.  Keys are taken four at a time: their sums are reduced together in the
+// vector unit (wave_fold), wave-uniform scores, one rescale of the online softmax per block.  A row's blocks are dealt to 1 (1,024 rows or more)
 // or 4 partial softmaxes that are merged in order, however many waves compute them.
 //
 // First layer: token -> z, query, key and value by table (Dec1Table in nt_kernels.h), so the step starts here: one sentence reads
@@ -50,10 +50,11 @@
 // 45 rows 26 and 17.8; with the self values too, one sentence 1119 -> 1012 us, 45 sentences 3742 -> 3207 us, 8 sentences of
 // the 256-wide model 1253 -> 1175 us, a 4,096-token budget 28.0 -> 27.5 ms (each with the projection as a launch of its own).
 //
-// Registers: three forms spill some of theirs - eight heads with two rows (6, 28 bytes of scratch per lane) and with eight rows
-// (13, 56 bytes), folded with the FFN at d = 512 (35, 76 bytes).  The others use no scratch.
+// Registers: four forms spill some of theirs - eight heads with two rows (6, 28 bytes of scratch per lane) and with eight rows
+// (13, 56 bytes), folded with two rows at d = 512 without (17, 64 bytes) and with the FFN (37, 84 bytes).  The others use no scratch.
 //
-// Measured per step of 1,900 / 45 / 1 rows, alone: 92 / 42 / 38 us as four launches, 71 / 30 / 25 us as one.
+// Measured per step of 1,900 / 45 / 1 rows, alone: 92 / 42 / 38 us as four launches, 71 / 30 / 25 us as one, without
+// the launch that projected Q | K | V (21 / 11 / 9 us).  With the table in its place and folded caches one row now takes 7.7 us.
 //
 // Eight heads of 64 (HEADS): the caches stay fp32 (self) and fp16 (cross); a vector still lies across one wave instruction, a
 // head on eight of its lanes, so that every lane keeps its own head's softmax and a score costs three DPP adds.  Relative keys
@@ -920,7 +921,7 @@ static hipError_t d1_launch(const Dec1Args &a, hipStream_t s) {
   } while (0)
   if constexpr (!HEADS) {
     if (a.folded) {
-      // one row per workgroup has 266 registers and a CU to itself; two rows have 256 (15 spilled) and still four waves each, so that
+      // one row per workgroup has 267 registers and a CU to itself; two rows have 256 (17 spilled) and still four waves each, so that
       // more than 256 rows are one round (a step of 250 / 300 / 400 / 511 rows alone: 31.8 / 40.3 / 41.9 / 45.3 us and 32.4 / 36.1 / 37.9 / 41.6;
       // of one and 45 rows 15.1 / 22.5 and 15.6 / 23.0)
       if (FFN || shape > 256) NT_D1(2, 8, 4, true);

@@ -19,7 +19,7 @@
 // registers that runs seven k-steps ahead, both planes are multiplied with the same weight fragment into one fp32
 // accumulator.  Between the two projections of a chain the tile lives in the LDS as fp32: the eight waves each own
 // 64 output columns of the first projection, so a row's LayerNorm statistics need all of them; the row is then
-// normalised by one wave (butterfly reductions), split into planes and becomes the A tile of the second projection.
+// normalised by one wave (reductions in the vector unit), split into planes and becomes the A tile of the second projection.
 //
 // Fragment order of the weights: [strip = n / 64][ks = k / 16][nb = (n % 64) / 32][lane][8 halfs] with
 // lane = n % 32 + 32 * ((k % 16) / 8)  (vocab_pack).
@@ -158,7 +158,7 @@ __device__ __forceinline__ void dc_store_strip(const floatx16 (&acc)[2], const G
 
 // LayerNorm of the rows a wave owns (rows wave, wave + 8, ... of the tile; xv[i][j] is element lane * NE + j of the
 // i-th of them), fp32 statistics: mean first, then the biased variance (or mean absolute deviation) of the centred
-// values.  The butterflies of all rows advance together, one exchange step at a time.  Output: y in place.
+// values.  The reductions of all rows advance together, one step at a time.  Output: y in place.
 template <int K>
 __device__ __forceinline__ void dc_layer_norm(float (&xv)[DC_TM / DC_WAVES][DcShape<K>::NE], const float *gamma,
                                               const float *beta, LnEps eps, int lane) {

@@ -196,10 +196,11 @@ void vocab_pack(const _Float16 *Wt, int N, int K, _Float16 *dst);
 // n_partials of the launch configuration used with M rows (exact: head + tail planes; certified: tiled kernels' head plane
 // first, none in the scout's).
 // wide: up to kVocabWideRows rows take a kernel of its own, more the scout (whose sums run in another order, so a caller whose M
-// depends on timing decides by a row count that does not, and nobody by what else is running).  A decoder step of 32 / 48 / 64 rows
-// alone takes 21.4 / 24.6 / 26.1 us with the wide kernel and 24.5 / 24.9 / 25.3 with the scout; a 4,096-token budget, whose lanes
-// share the chip, 21.9 ms with the line at 64 rows and 21.1 at 8.  In between.
-constexpr int kVocabWideRows = 40;
+// depends on timing decides by a row count that does not, and nobody by what else is running).  A decoder step of 24 / 32 / 40 / 64 rows
+// alone takes 17.3 / 18.0 / 20.6 / 22.8 us with the wide kernel, whose tile has 32 rows, and 19.2 / 19.3 / 19.9 / 20.3 with the scout.
+// Beside other lanes the line would lie lower (a 4,096-token budget 19.9 ms with it at 40, 19.6 at 8), a page of 45 rows is 2 % slower
+// with it at 8.
+constexpr int kVocabWideRows = 32;
 int vocab_argmax_partials(const VocabWeights &w, int M, bool certified, bool wide);
 // h is a head/tail pair of fp16 planes.
 hipError_t launch_vocab_argmax(const _Float16 *h, const _Float16 *h_lo, long ldh, const VocabWeights &w, int M,

@@ -1,7 +1,7 @@
 // Row-wise kernels: embedding gather + sinusoidal positions, LayerNorm, the start-of-step kernel
 // of the decoder (arg-max reduction of the previous step + embedding + LayerNorm), and helpers.
 // One wave64 per row; a row of d <= 1024 values lives in at most 16 registers per lane and
-// every reduction is a wavefront butterfly (no LDS).  Statistics are fp32: mean first, then the
+// every reduction stays inside the wavefront (no LDS).  Statistics are fp32: mean first, then the
 // biased variance of the centred values.
 #include "nt_kernels.h"
 

@@ -36,15 +36,18 @@ void vocab_pack(const _Float16 *Wt, int N, int K, _Float16 *dst) {
 // arrive, and with a strip per wave, streamed through a ring of registers, it arrived at 2.6 TB/s.  Here KP waves share a strip,
 // each a range of its k-steps, all of whose fragments are requested at once (16 KB per wave, 128 KB per CU, the whole
 // matrix in one round of workgroups); the rows' operands come straight from memory in the same way, so nothing waits for
-// a tile to be filled.  Partial logits meet in the LDS.  The matrix is read past the L2 (non-temporal): it does not fit
-// there and would evict the decoder's other weights at every step.
-// One row: 7.0 us against 12.7, 45 rows: 9.8 against 12.6, and 20 instead of 25 us for the decoder layer that follows.  Where
-// the scout (nt_vocab_scout.hip) takes over: kVocabWideRows.
+// a tile to be filled.  They are requested first (loads return in order, and theirs are short) and a scheduling barrier keeps every
+// load ahead of the first product: a step of 1 / 8 rows 14.8 / 15.6 us, with the rows last 15.0 / 16.0, left to the compiler, which
+// requests the matrix in portions, 16.1 / 16.9.  Partial logits meet in the LDS.  The matrix is read past the L2 (non-temporal): it
+// does not fit there and would evict the decoder's other weights at every step.
+// One row: 7.0 us against 12.7, and 20 instead of 25 us for the decoder layer that follows.  Where the scout
+// (nt_vocab_scout.hip) takes over: kVocabWideRows.
 // ---------------------------------------------------------------------------------------------------------------------
 template <int K, int SPW>
 __global__ __launch_bounds__(512) void vocab_wide_kernel(const _Float16 *__restrict__ h_hi, const _Float16 *__restrict__ h_lo,
                                                          long ldh, int M, const _Float16 *__restrict__ Wp, int N, int G,
                                                          unsigned long long *__restrict__ pk) {
+  static_assert(kVocabWideRows <= 32, "one tile of rows");
   constexpr int KP = 8 / SPW, KS = K / 16, KSW = KS / KP, GPW = 8 / KP;  // k-parts; k-steps and register groups of a wave
   typedef float f32x4 __attribute__((ext_vector_type(4)));
   __shared__ f32x4 red[8 * 8 * 64];  // [wave][register group][lane]
@@ -56,65 +59,65 @@ __global__ __launch_bounds__(512) void vocab_wide_kernel(const _Float16 *__restr
   const int strip = strip_want < NS ? strip_want : NS - 1;  // past the end: the last strip again (same keys)
   const __amdgpu_buffer_rsrc_t wrs = __builtin_amdgcn_make_buffer_rsrc((void *)Wp, 0, NS * 64 * K * 2, 0x00020000);
   const int w0 = (strip * KS + kp * KSW) * 2048;
+  const int m = li < M ? li : M - 1;
+  const long at_ = (long)m * ldh + kp * (KSW * 16) + g * 8;
+  half8 xh[KSW], xl[KSW];
+#pragma unroll
+  for (int ks = 0; ks < KSW; ks++) {
+    xh[ks] = *(const half8 *)(h_hi + at_ + ks * 16);
+    xl[ks] = *(const half8 *)(h_lo + at_ + ks * 16);
+  }
+  __builtin_amdgcn_sched_barrier(0);
   half8 w[KSW][2];
 #pragma unroll
   for (int ks = 0; ks < KSW; ks++)
 #pragma unroll
     for (int nb = 0; nb < 2; nb++)
       w[ks][nb] = __builtin_bit_cast(half8, __builtin_amdgcn_raw_buffer_load_b128(wrs, lane * 16 + nb * 1024, w0 + ks * 2048, 2));
-  for (int m0 = 0; m0 < M; m0 += 32) {
-    const int m = m0 + li < M ? m0 + li : M - 1;
-    const long at_ = (long)m * ldh + kp * (KSW * 16) + g * 8;
-    half8 xh[KSW], xl[KSW];
+  __builtin_amdgcn_sched_barrier(0);
+  floatx16 acc[2];
 #pragma unroll
-    for (int ks = 0; ks < KSW; ks++) {
-      xh[ks] = *(const half8 *)(h_hi + at_ + ks * 16);
-      xl[ks] = *(const half8 *)(h_lo + at_ + ks * 16);
+  for (int nb = 0; nb < 2; nb++)
+#pragma unroll
+    for (int v = 0; v < 16; v++) acc[nb][v] = 0.f;
+#pragma unroll
+  for (int ks = 0; ks < KSW; ks++)
+#pragma unroll
+    for (int nb = 0; nb < 2; nb++) {
+      acc[nb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(w[ks][nb], xh[ks], acc[nb], 0, 0, 0);
+      acc[nb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(w[ks][nb], xl[ks], acc[nb], 0, 0, 0);
     }
-    floatx16 acc[2];
 #pragma unroll
-    for (int nb = 0; nb < 2; nb++)
+  for (int q = 0; q < 8; q++)
+    red[(wave * 8 + q) * 64 + lane] = f32x4{acc[q >> 2][(q & 3) * 4], acc[q >> 2][(q & 3) * 4 + 1], acc[q >> 2][(q & 3) * 4 + 2], acc[q >> 2][(q & 3) * 4 + 3]};
+  __syncthreads();
+  // this wave sums and folds register groups kp * GPW .. + GPW - 1 of its strip; columns ascend
+  float best = -INFINITY;
+  int at_best = 0;
 #pragma unroll
-      for (int v = 0; v < 16; v++) acc[nb][v] = 0.f;
+  for (int u = 0; u < GPW; u++) {
+    const int q = kp * GPW + u;
+    f32x4 t = red[(slot * KP * 8 + q) * 64 + lane];
 #pragma unroll
-    for (int ks = 0; ks < KSW; ks++)
+    for (int p = 1; p < KP; p++) t += red[((slot * KP + p) * 8 + q) * 64 + lane];
 #pragma unroll
-      for (int nb = 0; nb < 2; nb++) {
-        acc[nb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(w[ks][nb], xh[ks], acc[nb], 0, 0, 0);
-        acc[nb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(w[ks][nb], xl[ks], acc[nb], 0, 0, 0);
-      }
-#pragma unroll
-    for (int q = 0; q < 8; q++)
-      red[(wave * 8 + q) * 64 + lane] = f32x4{acc[q >> 2][(q & 3) * 4], acc[q >> 2][(q & 3) * 4 + 1], acc[q >> 2][(q & 3) * 4 + 2], acc[q >> 2][(q & 3) * 4 + 3]};
-    __syncthreads();
-    // this wave sums and folds register groups kp * GPW .. + GPW - 1 of its strip; columns ascend
-    float best = -INFINITY;
-    int at_best = 0;
-#pragma unroll
-    for (int u = 0; u < GPW; u++) {
-      const int q = kp * GPW + u;
-      f32x4 t = red[(slot * KP * 8 + q) * 64 + lane];
-#pragma unroll
-      for (int p = 1; p < KP; p++) t += red[((slot * KP + p) * 8 + q) * 64 + lane];
-#pragma unroll
-      for (int e = 0; e < 4; e++) {
-        const int n = strip * 64 + (q >> 2) * 32 + (q & 3) * 8 + g * 4 + e;
-        const bool gt = n < N && t[e] > best;
-        best = gt ? t[e] : best;
-        at_best = gt ? n : at_best;
-      }
+    for (int e = 0; e < 4; e++) {
+      const int n = strip * 64 + (q >> 2) * 32 + (q & 3) * 8 + g * 4 + e;
+      const bool gt = n < N && t[e] > best;
+      best = gt ? t[e] : best;
+      at_best = gt ? n : at_best;
     }
-    unsigned long long key = best == -INFINITY ? 0ull : argmax_key(best, at_best);
-    const unsigned long long other = shfl_xor_u64(key, 32);
-    key = other > key ? other : key;
-    if (g == 0) skey[wave][li] = key;
-    __syncthreads();
-    if (tid < 32 && m0 + tid < M) {
-      unsigned long long k = skey[0][tid];
+  }
+  unsigned long long key = best == -INFINITY ? 0ull : argmax_key(best, at_best);
+  const unsigned long long other = shfl_xor_u64(key, 32);
+  key = other > key ? other : key;
+  if (g == 0) skey[wave][li] = key;
+  __syncthreads();
+  if (tid < M) {
+    unsigned long long k = skey[0][tid];
 #pragma unroll
-      for (int i = 1; i < 8; i++) k = skey[i][tid] > k ? skey[i][tid] : k;
-      pk[(long)(m0 + tid) * G + blockIdx.x] = k;
-    }
+    for (int i = 1; i < 8; i++) k = skey[i][tid] > k ? skey[i][tid] : k;
+    pk[(long)tid * G + blockIdx.x] = k;
   }
 }
 
