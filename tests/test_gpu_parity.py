@@ -439,8 +439,8 @@ def test_certified_argmax_equals_full_recompute(nt):
 @pytest.mark.parametrize("d,V", [(512, 40), (512, 64), (512, 4001), (256, 4033), (512, 33000)])
 @pytest.mark.parametrize("what", ["plain", "offset", "outliers", "equal"])
 def test_scouted_argmax(nt, torch_cuda, d, V, what):
-    """The arg-max of more than 64 rows: an 8-bit pass with a bound, exact logits of what it leaves.  Vocabularies below one strip
-    of 64 entries, of one, with a ragged end, of more strips than a workgroup scans at once; row counts around a tile; a
+    """The arg-max of more than 32 rows: an 8-bit pass with a bound, exact logits of what it leaves.  Vocabularies below one strip
+    of 64 entries, of one, with a ragged end, of more strips than a workgroup scans at once; row counts around the line and a tile; a
     matrix whose entries share a large offset, one with entries 16 times the others, one of equal entries (everything is a candidate,
     the lowest id wins).  Every token has the largest of the logits that the GEMM path computes, to fp32 rounding: two sums
     of 512 products, 2 * 2^-24 sqrt(512) of |h| |w|, about 3e-6; four times that."""
@@ -458,7 +458,7 @@ def test_scouted_argmax(nt, torch_cuda, d, V, what):
     norm = float(np.linalg.norm(W.astype(np.float64), axis=1).max())
     gm = nt.Model(cfg, blob, max_batch_tokens=2048, pipeline_lanes=1)
     T = 3
-    for rows in (65, 127, 128, 129, 517):
+    for rows in (32, 33, 65, 127, 128, 129, 517):
         src = torch.from_numpy(rng.integers(0, V, size=(rows, 2)).astype(np.int32)).cuda()
         lens = torch.full((rows,), 2, dtype=torch.int32, device="cuda")
         out = torch.empty(rows, T, dtype=torch.int32, device="cuda")
