@@ -35,8 +35,8 @@
 //
 // Folded attention (one-layer decoders, batches of up to kDec1FoldRows rows).  q . k = (W y + b) . k = y . (W^T k) + b . k,
 // and Wo (sum p v) + bo = sum p (Wo v + bo).  With the cross keys and values of a sentence multiplied by the two matrices once,
-// when the batch is encoded, and the self values projected by the product of value and output matrix (formed at load, kept as
-// head + tail), a step's attention half has no projection left.  The self values are cached without their constant, which a
+// when the batch is encoded, and the self values projected by the product of value and output matrix (formed at load, a fourth
+// group of columns of the table), a step's attention half has no projection left.  The self values are cached without their constant, which a
 // softmax passes through unchanged, and with every column divided by its norm: either would set the one scale of a vector's
 // integers for all its elements (eight output biases of 16, or eight output columns 16 times as large, leave 1.3e-5 / 1.1e-4 of
 // the context's norm instead of 2.5e-6 / 2.7e-5).  The cross products are formed from the rounded (integer)
