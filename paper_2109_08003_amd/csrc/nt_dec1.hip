@@ -422,7 +422,7 @@ struct D1Token {
           }
           y = (int)(0xFFFFFFFFu - (unsigned int)wave_max_u64(top));
         }
-        if (y < 0 || y >= b.vocab) y = b.pad_id;  // cannot happen: every key holds a valid id
+        if (y < 0 || y >= b.vocab) y = b.pad_id;  // a row none of whose logits is a number
         if (first_wave && lane == 0) b.out[(long)row * b.out_ld + b.t - 1] = y;
       }
       if (b.forced && row < a.rows) {

@@ -303,7 +303,7 @@ __global__ __launch_bounds__(DC_WAVES * 64) void dec_qkv_kernel(DecQkvArgs a, in
 #pragma unroll
     for (int i = 0; i < RPW; i++) {
       const int r = m0 + wave + DC_WAVES * i;
-      if (y[i] < 0 || y[i] >= sb.vocab) y[i] = sb.pad_id;  // cannot happen: every key holds a valid id
+      if (y[i] < 0 || y[i] >= sb.vocab) y[i] = sb.pad_id;  // a row none of whose logits is a number
       if (cg == 0 && lane == 0 && r < sb.rows_prev) sb.out[(long)r * sb.out_ld + sb.t - 1] = y[i];
     }
   } else {

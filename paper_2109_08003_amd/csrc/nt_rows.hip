@@ -272,7 +272,7 @@ __global__ __launch_bounds__(256) void step_begin_kernel(StepBeginArgs a) {
   if (a.t > 0 && a.prev_cert) {
     const int sl = a.slot_of_row[r];
     y = (sl < 0) ? a.tok[r] : (int)(0xFFFFFFFFu - (unsigned int)a.final_key[sl]);
-    if (y < 0 || y >= a.vocab) y = a.pad_id;  // cannot happen: every key holds a valid id
+    if (y < 0 || y >= a.vocab) y = a.pad_id;  // a row none of whose logits is a number
     if (lane == 0) a.out[(long)r * a.out_ld + a.t - 1] = y;
   } else if (a.t > 0 && a.pk) {
     unsigned long long k = 0ull;
@@ -283,7 +283,7 @@ __global__ __launch_bounds__(256) void step_begin_kernel(StepBeginArgs a) {
     }
     k = wave_max_u64(k);
     y = (int)(0xFFFFFFFFu - (unsigned int)k);
-    if (y < 0 || y >= a.vocab) y = a.pad_id;  // cannot happen: every partial holds a valid id
+    if (y < 0 || y >= a.vocab) y = a.pad_id;  // a row none of whose logits is a number
     if (lane == 0) a.out[(long)r * a.out_ld + a.t - 1] = y;
   }
   if (r >= a.rows_now) return;
@@ -331,7 +331,7 @@ __global__ __launch_bounds__(256) void eos_collect_kernel(EosStepArgs a) {
     k = wave_max_u64(k);
     y = (int)(0xFFFFFFFFu - (unsigned int)k);
   }
-  if (y < 0 || y >= a.vocab) y = a.pad_id;  // cannot happen: every key holds a valid id
+  if (y < 0 || y >= a.vocab) y = a.pad_id;  // a row none of whose logits is a number
   if (lane == 0) {
     a.out[(long)b * a.out_ld + a.t - 1] = y;
     const bool ends = (y == a.eos_id) || (a.t >= a.cap[b]);

@@ -59,10 +59,17 @@ size_t vocab_scout_bytes(int N, int K) { return scout_code_bytes(N, K) + (size_t
 // ---- at load, on the device (50 MB for 32,000 x 512; the same loops on the host took 350 ms of a load of 200) ----------------------
 constexpr int SP_ROWS = 256;  // rows per partial sum of the mean
 
+// Elements that are no finite numbers stay out of the mean and of the codes; the strip of such an entry has norms without end, which
+// makes its entries candidates of every row, and the exact logits decide.
+__device__ __forceinline__ bool scout_finite(_Float16 w) { return fabsf((float)w) <= 65504.f; }
+
 __global__ __launch_bounds__(512) void scout_sum_kernel(const _Float16 *W, int N, int K, double *sums) {
   const int k = threadIdx.x, v0 = blockIdx.x * SP_ROWS, v1 = v0 + SP_ROWS < N ? v0 + SP_ROWS : N;
   double s = 0.0;
-  for (int v = v0; v < v1; v++) s += (double)(float)W[(long)v * K + k];
+  for (int v = v0; v < v1; v++) {
+    const _Float16 w = W[(long)v * K + k];
+    s += scout_finite(w) ? (double)(float)w : 0.0;
+  }
   sums[(long)blockIdx.x * K + k] = s;
 }
 __global__ __launch_bounds__(512) void scout_mean_kernel(const double *sums, int n, int N, int K, float *mean) {
@@ -70,12 +77,15 @@ __global__ __launch_bounds__(512) void scout_mean_kernel(const double *sums, int
   for (int i = 0; i < n; i++) s += sums[(long)i * K + threadIdx.x];
   mean[threadIdx.x] = (float)(s / (double)N);
 }
-// largest centred element of every row, a wave each
+// largest centred element of every row, a wave each; infinite (last in the order) where an element is not finite
 __global__ __launch_bounds__(256) void scout_top_kernel(const _Float16 *W, int N, int K, const float *mean, float *top) {
   const int lane = threadIdx.x & 63, v = blockIdx.x * 4 + (threadIdx.x >> 6);
   if (v >= N) return;
   float m = 0.f;
-  for (int k = lane; k < K; k += 64) m = fmaxf(m, fabsf((float)W[(long)v * K + k] - mean[k]));
+  for (int k = lane; k < K; k += 64) {
+    const _Float16 w = W[(long)v * K + k];
+    m = fmaxf(m, scout_finite(w) ? fabsf((float)w - mean[k]) : INFINITY);
+  }
   m = wave_max(m);
   if (lane == 0) top[v] = m;
 }
@@ -85,7 +95,8 @@ __global__ __launch_bounds__(256) void scout_pack_kernel(const _Float16 *W, int 
   __shared__ float norms[2][4];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, s = blockIdx.x, KS = K / 32;
   const int n = N - s * 64 < 64 ? N - s * 64 : 64;
-  const float largest = top[order[s * 64 + n - 1]], scale = largest > 0.f ? largest / 127.f : 1.f, inv = 1.f / scale;
+  const float own = lane < n ? top[order[s * 64 + lane]] : 0.f, largest = wave_max(own < INFINITY ? own : 0.f);
+  const float scale = largest > 0.f ? largest / 127.f : 1.f, inv = 1.f / scale;
   float wn = 0.f, fn = 0.f;
   for (int i = wave * 16; i < wave * 16 + 16; i++) {
     const int v = i < n ? order[s * 64 + i] : -1;
@@ -93,11 +104,12 @@ __global__ __launch_bounds__(256) void scout_pack_kernel(const _Float16 *W, int 
     double w2 = 0.0, f2 = 0.0;
     for (int k = lane; k < K; k += 64) {
       const _Float16 w = v >= 0 ? W[(long)v * K + k] : (_Float16)0.f;
-      const float x = v >= 0 ? (float)w - mean[k] : 0.f;
+      const bool finite = scout_finite(w);
+      const float x = v >= 0 && finite ? (float)w - mean[k] : 0.f;
       const float c = fminf(fmaxf(rintf(x * inv), -127.f), 127.f);
       const double f = (double)x - (double)c * (double)scale;
-      w2 += (double)x * (double)x;
-      f2 += f * f;
+      w2 += finite ? (double)x * (double)x : INFINITY;
+      f2 += finite ? f * f : INFINITY;
       sorted[((long)s * 64 + i) * K + k] = w;
       // the fragment order of nt_vocab_q8.hip
       codes[((((long)s * KS + k / 32) * 2 + i / 32) * 64 + i % 32 + 32 * ((k % 32) / 16)) * 16 + k % 16] = (int8_t)(int)c;
@@ -139,7 +151,6 @@ hipError_t vocab_scout_build(const _Float16 *W, int N, int K, void *dst, hipStre
   if (e == hipSuccess) e = hipMemcpyAsync(h_top.data(), top, (size_t)N * 4, hipMemcpyDeviceToHost, s);
   if (e == hipSuccess) e = hipStreamSynchronize(s);
   std::iota(h_order.begin(), h_order.end(), 0);
-  for (float &t : h_top) t = t == t ? t : INFINITY;  // an order for every matrix
   std::stable_sort(h_order.begin(), h_order.end(), [&](int32_t a, int32_t b) { return h_top[(size_t)a] < h_top[(size_t)b]; });
   if (e == hipSuccess) e = hipMemcpyAsync(order, h_order.data(), (size_t)N * 4, hipMemcpyHostToDevice, s);
   if (e == hipSuccess) {
@@ -469,6 +480,7 @@ __global__ __launch_bounds__(PK_WAVES * 64) void vocab_pick_kernel(const i32x4 *
     }
     return pk_sum16(s);
   };
+  auto key = [](float s, int id) { return s > -INFINITY ? argmax_key(s, id) : 0ull; };  // (not for a NaN, which argmax_key ranks first)
   auto fetch = [&](half8 (&w)[KC], int place) {
 #pragma unroll
     for (int j = 0; j < KC; j++) w[j] = *(const half8 *)(Ws + (long)place * K + j * 128 + e16 * 8);
@@ -494,8 +506,8 @@ __global__ __launch_bounds__(PK_WAVES * 64) void vocab_pick_kernel(const i32x4 *
     half8 w[KC];
     fetch(w, place);
     const int id = there ? ids[place] : -1;
-    const float s = dot(w, row);
-    if (e16 == 0 && id >= 0) atomicMax(&best[row], argmax_key(s, id));
+    const unsigned long long k = key(dot(w, row), id);
+    if (e16 == 0 && id >= 0) atomicMax(&best[row], k);
   }
   if (many) {
     unsigned long long mine[PK_ROWS] = {};
@@ -506,8 +518,8 @@ __global__ __launch_bounds__(PK_WAVES * 64) void vocab_pick_kernel(const i32x4 *
 #pragma unroll
       for (int q = 0; q < PK_ROWS; q++)
         if (many >> q & 1u) {
-          const unsigned long long key = argmax_key(dot(w, q), id);
-          mine[q] = id >= 0 && key > mine[q] ? key : mine[q];
+          const unsigned long long k = key(dot(w, q), id);
+          mine[q] = id >= 0 && k > mine[q] ? k : mine[q];
         }
     }
 #pragma unroll

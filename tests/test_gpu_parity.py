@@ -477,6 +477,59 @@ def test_scouted_argmax(nt, torch_cuda, d, V, what):
     gm.close()
 
 
+def decode_with_logits(nt, torch, gm, cfg, rows, T, rng):
+    """Tokens of a greedy decode of random sentences, and the logits that the GEMM path computes for them."""
+    V = cfg["vocab"]
+    src = torch.from_numpy(rng.integers(4, V, size=(rows, 2)).astype(np.int32)).cuda()
+    lens = torch.full((rows,), 2, dtype=torch.int32, device="cuda")
+    out = torch.empty(rows, T, dtype=torch.int32, device="cuda")
+    gm.encode(src, lens)
+    gm.decode_greedy(rows, T, out)
+    given = torch.cat([torch.full((rows, 1), cfg["bos_id"], dtype=torch.int32, device="cuda"), out[:, :-1]], dim=1).contiguous()
+    logits = torch.empty(rows, T, V, dtype=torch.float32, device="cuda")
+    gm.encode(src, lens)
+    gm.debug_teacher_forced_logits(given, logits)
+    return out.long(), logits
+
+
+@pytest.mark.parametrize("d", [256, 512])
+@pytest.mark.parametrize("what", ["element", "entry", "infinity", "state"])
+def test_scouted_argmax_with_values_that_are_no_numbers(nt, torch_cuda, d, what):
+    """A logit that is not a number never wins and costs no other entry its place; a state that is not one gives the padding
+    token.  As the kernel of up to 32 rows has it.  Bound as in test_scouted_argmax."""
+    torch = torch_cuda
+    V, bad = 4001, 1234
+    cfg = nt_synth.model_config("C1", d_model=d, vocab=V, n_enc=0, max_len=16, pad_id=3)
+    blob = nt_synth.make_weights(cfg, seed=19, random_affine=True)
+    W = nt_synth.blob_view(cfg, blob, "W_out")
+    norm = float(np.linalg.norm(W.astype(np.float64), axis=1).max())
+    if what == "element":
+        W[bad, 7] = np.nan
+    elif what == "entry":
+        W[bad] = np.nan
+    elif what == "infinity":
+        W[bad, 7] = np.inf
+    else:
+        nt_synth.blob_view(cfg, blob, "dec_final.b")[5] = np.nan
+    gm = nt.Model(cfg, blob, max_batch_tokens=2048, pipeline_lanes=1)
+    rng = np.random.default_rng(d)
+    for rows in (32, 33, 129, 517):
+        out, logits = decode_with_logits(nt, torch, gm, cfg, rows, 3, rng)
+        if what == "state":
+            assert bool((out == cfg["pad_id"]).all()), rows
+            continue
+        of_bad = logits[:, :, bad]  # (an infinite weight: the sum of the state's head and tail may be inf - inf)
+        chosen = out == bad
+        assert not bool((chosen & (of_bad == -np.inf)).any()) and not bool((~chosen & (of_bad == np.inf)).any())
+        assert what == "infinity" or not bool(chosen.any())
+        logits[:, :, bad] = -np.inf
+        got = logits.gather(2, out.unsqueeze(2)).squeeze(2)
+        short = torch.where(chosen, torch.zeros_like(got), logits.max(dim=2).values - got)
+        print(f"{what} {d}, {rows} rows: short of the largest by {float(short.max()) / (norm * d ** 0.5):.1e} of |h| |w|")
+        assert float(short.max()) / (norm * d ** 0.5) <= 1.2e-5, rows
+    gm.close()
+
+
 # ------------------------------------------------------------------------------ restored components (C3) and teacher shape (C4)
 def _check_workload_sample(nt, oracle, name, n_sent, budget, n_audit=None, **overrides):
     """Translate n_sent sentences of a workload at a token budget and audit a seeded sample of n_audit of them (all,
