@@ -883,6 +883,8 @@ __global__ __launch_bounds__(NWAVES * 64) void dec1_kernel(Dec1Args a) {
   if (a.h_hi) {
     typedef _Float16 halfNE __attribute__((ext_vector_type(NE)));
     float y[NE];
+    unsigned int level[NE / 4];
+    if (a.scout.codes) scout_levels<NE>(a.scout, lane, level);
     normalise(LNF, y);
     halfNE hi, lo;
     float tail2 = 0.f;
@@ -897,7 +899,7 @@ __global__ __launch_bounds__(NWAVES * 64) void dec1_kernel(Dec1Args a) {
     *(halfNE *)(a.h_hi + (long)r * D + lane * NE) = hi;
     *(halfNE *)(a.h_hi + a.h_lo_offset + (long)r * D + lane * NE) = lo;
     if (lane == 0) a.lo_norm[r] = sqrtf(tail2) * 1.0001f;  // rounded up: it is used as a bound
-    if (a.scout.codes) scout_emit<NE>(y, a.scout, r, lane);
+    if (a.scout.codes) scout_emit<NE>(y, level, a.scout, r, lane);
   }
 }
 

@@ -528,6 +528,8 @@ __global__ __launch_bounds__(DC_WAVES * 64) void dec_chain_kernel(DecChainArgs a
       xv[i][j] = t[0], xv[i][j + 1] = t[1], xv[i][j + 2] = t[2], xv[i][j + 3] = t[3];
     }
   }
+  unsigned int level[NE / 4];
+  if (!SECOND && a.scout.codes) scout_levels<NE>(a.scout, lane, level);
   dc_layer_norm<K>(xv, a.gamma, a.beta, a.eps, lane);
   if (!SECOND) {
     // final hidden state: head / tail planes and the Euclidean norm of the tail (rounded up: it is used as a bound)
@@ -549,7 +551,7 @@ __global__ __launch_bounds__(DC_WAVES * 64) void dec_chain_kernel(DecChainArgs a
         *(halfNE *)(a.h_hi + (long)m * K + lane * NE) = hi;
         *(halfNE *)(a.h_hi + a.h_lo_offset + (long)m * K + lane * NE) = lo;
         if (a.lo_norm && lane == 0) a.lo_norm[m] = sqrtf(tail2) * 1.0001f;
-        if (a.scout.codes) scout_emit<NE>(xv[i], a.scout, m, lane);
+        if (a.scout.codes) scout_emit<NE>(xv[i], level, a.scout, m, lane);
       }
     }
     return;

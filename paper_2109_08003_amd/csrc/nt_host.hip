@@ -795,7 +795,7 @@ int nt_load_weights(const nt_config *cfg, const void *h_blob_fp16, size_t blob_b
   if (m->Wout_frag && !cfg->q8_output) {
     m->scout_bytes = nt::vocab_scout_bytes(V, d);
     if (hipMalloc(&m->Wscout, m->scout_bytes) != hipSuccess) return fail(NT_ENOMEM, "hipMalloc of %zu bytes failed", m->scout_bytes);
-    HIP_TRY(nt::vocab_scout_build(m->Wout, V, d, m->Wscout, s));
+    HIP_TRY(nt::vocab_scout_build(m->Wout, V, d, m->dec_final.g, m->dec_final.b, m->Wscout, s));
   }
   {  // largest row norm of the output matrix, rounded up (bound used by the certified arg-max)
     const _Float16 *Wo = (const _Float16 *)h_blob_fp16 + (cfg->tie_output ? 0 : (int64_t)V * d);
@@ -1132,7 +1132,7 @@ int decode_step(nt_model *m, DecodeCursor &cu, hipStream_t s) {
     const bool wide = rows_for_choice <= nt::kVocabWideRows;
     const bool scouted = nt::vocab_scouted(m->vw, wide) && m->Wscout;
     const bool certified = !d_logits && !c.q8_output && (scouted || (nt::vocab_tiled(m->vw) && R >= kCertMinRows));
-    const nt::ScoutOut scout_out = certified && scouted ? nt::ScoutOut{m->scout_codes, m->scout_rc} : nt::ScoutOut{};
+    const nt::ScoutOut scout_out = certified && scouted ? nt::ScoutOut{m->scout_codes, m->scout_rc, nt::vocab_scout_levels(m->Wscout, V, d)} : nt::ScoutOut{};
     // final hidden state as a head/tail plane pair (the planes share the a32 buffer)
     _Float16 *h_hi = (_Float16 *)m->a32, *h_lo = h_hi + (long)m->max_rows * d;
     bool final_ln_done = false;

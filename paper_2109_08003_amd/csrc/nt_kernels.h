@@ -211,20 +211,51 @@ hipError_t launch_vocab_argmax(const _Float16 *h, const _Float16 *h_lo, long ldh
 struct VocabScout {
   const void *matrix;   // vocab_scout_build of the output matrix
   int8_t *codes;        // [rows][K] and
-  float4 *row_consts;   // [rows]: written by the kernel that writes the hidden state (scout_round)
+  float4 *row_consts;   // [rows]: written by the kernel that writes the hidden state (scout_emit)
   void *scratch;        // vocab_scout_scratch_bytes
 };
 size_t vocab_scout_bytes(int N, int K);
-// dst [vocab_scout_bytes] <- W [N][K], both on the device; returns when it is done (load time)
-hipError_t vocab_scout_build(const _Float16 *W, int N, int K, void *dst, hipStream_t s);
+// dst [vocab_scout_bytes] <- W [N][K], gamma / beta [K]: the final normalisation, all on the device; returns when it is done (load time)
+hipError_t vocab_scout_build(const _Float16 *W, int N, int K, const float *gamma, const float *beta, void *dst, hipStream_t s);
+const int8_t *vocab_scout_levels(const void *matrix, int N, int K);  // within the packed matrix
 size_t vocab_scout_scratch_bytes(int N, int rows);
-// Where a hidden state goes besides its planes (codes == nullptr: nowhere)
+// Where a hidden state goes besides its planes (codes == nullptr: nowhere), and the powers of two that level its columns
 struct ScoutOut {
   int8_t *codes = nullptr;
   float4 *row_consts = nullptr;
+  const int8_t *levels = nullptr;
 };
 #ifdef __HIPCC__
-// One row, NE elements per lane of a wave: codes in [-127, 127] and {scale, ||y - scale code||, ||scale code||, 0}, the norms
+// An orthogonal matrix of signs, times the root of NE, on a lane's elements.  (The two signs in front: equal elements stay spread.)
+template <int NE, typename T>
+__device__ __forceinline__ void scout_mix(T (&x)[NE]) {
+  static_assert(NE == 4 || NE == 8, "");
+  x[3] = -x[3];
+  if (NE == 8) x[6] = -x[6];
+#pragma unroll
+  for (int m = 1; m < NE; m *= 2)
+#pragma unroll
+    for (int e = 0; e < NE; e++)
+      if (!(e & m)) {
+        const T a = x[e], b = x[e | m];
+        x[e] = a + b;
+        x[e | m] = a - b;
+      }
+}
+// the same where element lane & (NE - 1) of a group is this lane's
+template <int NE>
+__device__ __forceinline__ float scout_mix_lanes(float x, int lane) {
+  auto step = [&](float v, float o, int m) { return lane & m ? o - v : v + o; };
+  auto from = [](float v, auto ctrl) { return __uint_as_float(wave_dpp<decltype(ctrl)::value>(__float_as_uint(v))); };
+  const int e = lane & (NE - 1);
+  if (e == 3 || (NE == 8 && e == 6)) x = -x;
+  x = step(x, from(x, std::integral_constant<int, 0xB1>{}), 1);  // quad_perm: lane ^ 1, lane ^ 2
+  x = step(x, from(x, std::integral_constant<int, 0x4E>{}), 2);
+  if (NE == 8)  // row_half_mirror, quad_perm: (lane ^ 7) ^ 3
+    x = step(x, from(from(x, std::integral_constant<int, 0x141>{}), std::integral_constant<int, 0x1B>{}), 4);
+  return x;
+}
+// One levelled and mixed row, NE elements per lane of a wave: codes in [-127, 127] and {scale, ||y - scale code||, ||scale code||, 0}, the norms
 // rounded up (they are bounds).
 template <int NE>
 __device__ __forceinline__ float4 scout_round(const float (&y)[NE], int (&code)[NE]) {
@@ -245,16 +276,25 @@ __device__ __forceinline__ float4 scout_round(const float (&y)[NE], int (&code)[
   a2 = wave_sum(a2);
   return make_float4(scale, sqrtf(e2) * 1.001f, sqrtf(a2) * 1.0001f, 0.f);
 }
-// the same for a row whose lanes hold consecutive elements
+// the same for a row whose lanes hold consecutive elements; level: theirs, four to a word
 template <int NE>
-__device__ __forceinline__ void scout_emit(const float (&y)[NE], const ScoutOut &o, long row, int lane) {
+__device__ __forceinline__ void scout_emit(const float (&y)[NE], const unsigned int (&level)[NE / 4], const ScoutOut &o, long row, int lane) {
   int code[NE];
-  const float4 rc = scout_round<NE>(y, code);
+  float x[NE];
+#pragma unroll
+  for (int e = 0; e < NE; e++) x[e] = ldexpf(y[e], (int)(int8_t)(level[e / 4] >> (e % 4 * 8)));
+  scout_mix<NE>(x);
+  const float4 rc = scout_round<NE>(x, code);
 #pragma unroll
   for (int e = 0; e < NE; e += 4)
     *(unsigned int *)(o.codes + row * (NE * 64) + lane * NE + e) =
         (code[e] & 0xFF) | (code[e + 1] & 0xFF) << 8 | (code[e + 2] & 0xFF) << 16 | (unsigned int)code[e + 3] << 24;
   if (lane == 0) o.row_consts[row] = rc;
+}
+template <int NE>
+__device__ __forceinline__ void scout_levels(const ScoutOut &o, int lane, unsigned int (&level)[NE / 4]) {
+#pragma unroll
+  for (int w = 0; w < NE / 4; w++) level[w] = ((const unsigned int *)(o.levels + lane * NE))[w];
 }
 #endif
 // Results: tok[m], and slot_of_row[m] = -1.  distrust: every row has every logit computed.

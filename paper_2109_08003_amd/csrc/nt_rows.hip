@@ -126,7 +126,7 @@ __global__ __launch_bounds__(256) void layer_norm_kernel(const float *x, int M, 
       float y[NE];
       int code[NE];
 #pragma unroll
-      for (int i = 0; i < NE; i++) y[i] = v[i];
+      for (int i = 0; i < NE; i++) y[i] = scout_mix_lanes<NE>(ldexpf(v[i], (int)scout.levels[lane + 64 * i]), lane);
       const float4 rc = scout_round<NE>(y, code);
 #pragma unroll
       for (int i = 0; i < NE; i++) scout.codes[r * d + lane + 64 * i] = (int8_t)code[i];

@@ -15,6 +15,18 @@
 // a common offset of the entries would only widen the range of the codes.  Entries are sorted by their largest element, so that the
 // 64 entries of a strip, which share one scale, are alike.
 //
+// The columns are levelled and mixed before either side is rounded, because a row has one scale: a column that is larger than the
+// others (an offset or a gain of the final normalisation, a column of the matrix) would leave the others few of its steps.
+//   levelled: x . w = sum (x_k 2^l_k) (w_k 2^-l_k), where l_k takes half of the column's size, x_k against the spread of w_k, to either
+//   side (all of it on one side only moves the trouble to the other);
+//   mixed: eight columns at a time (four at d = 256), the elements of a lane, by an orthogonal matrix of signs on both sides, which
+//   spreads what is left of such a column over eight.
+// Candidates of a row, d = 512, 32,000 flat random entries, median / largest of 400 states (with the groups of which all are taken,
+// see below; neither: without them), both, levelled only, neither: an offset of 25 on one column 45 / 336, 483 / 1,700, 802 / 2,600; two gains of 16 15 / 253,
+// 194 / 1,678, 277 / 3,104; a column of the matrix 16 times the others 15 / 302, 85 / 1,719, 842 / 2,626; none of these 12 / 85 each way.
+// Eight steps of 400 rows with any of these 0.24 to 0.29 ms, 0.24 with none; before, when one row or another of every launch had each
+// logit computed, 4.8 to 5.1 ms.  The 4,096-, 16,384- and 65,536-token budgets take the same time as without, to 0.3 %.
+//
 // The scout has the shape of the 8-bit output layer's kernel (nt_vocab_q8.hip): 128 rows of codes in the LDS, fragments of the
 // matrix through a ring of registers, a wave owns a strip of 64 entries for all rows of the tile, a lane owns a row of each 32-row
 // block.  A lane's 32 products of a strip are one group (|sum| <= 127^2 512 < 2^23): the largest and the runner-up leave with their
@@ -49,12 +61,15 @@ constexpr int SC_ROWS = 128, SC_WAVES = 8;
 constexpr int SC_NONE = -(1 << 30);  // below every packed product (places past the end of the vocabulary)
 constexpr int SC_LOW = -(1 << 23);   // below every product
 constexpr int SC_APART = 13;         // the distance to the third leaves in units of 2^13
-constexpr int kPickCap = 256;        // candidates of a row
+constexpr int kPickCap = 1024;       // candidates of a row
+constexpr int SC_LEVEL = 32;         // largest power of two of a column
 
 static size_t scout_code_bytes(int N, int K) { return (size_t)((N + 63) / 64) * 64 * K; }
 // codes, then per strip {scale, largest ||w||, largest ||f||, unused}, then the id of every place (-1: none), then the matrix's rows in
-// the order of the places (the exact logits then need no look-up before their row)
-size_t vocab_scout_bytes(int N, int K) { return scout_code_bytes(N, K) + (size_t)((N + 63) / 64) * (16 + 64 * 4 + 64 * (size_t)K * 2); }
+// the order of the places (the exact logits then need no look-up before their row), then the states' levels l_k
+static size_t scout_level_at(int N, int K) { return scout_code_bytes(N, K) + (size_t)((N + 63) / 64) * (16 + 64 * 4 + 64 * (size_t)K * 2); }
+size_t vocab_scout_bytes(int N, int K) { return scout_level_at(N, K) + (size_t)K; }
+const int8_t *vocab_scout_levels(const void *matrix, int N, int K) { return (const int8_t *)matrix + scout_level_at(N, K); }
 
 // ---- at load, on the device (50 MB for 32,000 x 512; the same loops on the host took 350 ms of a load of 200) ----------------------
 constexpr int SP_ROWS = 256;  // rows per partial sum of the mean
@@ -65,35 +80,79 @@ __device__ __forceinline__ bool scout_finite(_Float16 w) { return fabsf((float)w
 
 __global__ __launch_bounds__(512) void scout_sum_kernel(const _Float16 *W, int N, int K, double *sums) {
   const int k = threadIdx.x, v0 = blockIdx.x * SP_ROWS, v1 = v0 + SP_ROWS < N ? v0 + SP_ROWS : N;
-  double s = 0.0;
+  double s = 0.0, s2 = 0.0;
   for (int v = v0; v < v1; v++) {
     const _Float16 w = W[(long)v * K + k];
-    s += scout_finite(w) ? (double)(float)w : 0.0;
+    const double x = scout_finite(w) ? (double)(float)w : 0.0;
+    s += x;
+    s2 += x * x;
   }
-  sums[(long)blockIdx.x * K + k] = s;
+  sums[((long)blockIdx.x * 2) * K + k] = s;
+  sums[((long)blockIdx.x * 2 + 1) * K + k] = s2;
 }
-__global__ __launch_bounds__(512) void scout_mean_kernel(const double *sums, int n, int N, int K, float *mean) {
-  double s = 0.0;
-  for (int i = 0; i < n; i++) s += sums[(long)i * K + threadIdx.x];
-  mean[threadIdx.x] = (float)(s / (double)N);
+// Mean of every column, and its level: half the ratio of what the final normalisation makes of the state there (gain and offset; 3.3: the
+// largest of 512 normal deviates) to the column's spread, against the mean of all columns' halves.  A column that is always 0 on
+// one side gives all of its size to the other.
+__global__ __launch_bounds__(512) void scout_mean_kernel(const double *sums, int n, int N, int K, const float *gamma, const float *beta, float *mean,
+                                                         int8_t *level) {
+  __shared__ float ratio[512];
+  const int k = threadIdx.x;
+  double s = 0.0, s2 = 0.0;
+  for (int i = 0; i < n; i++) s += sums[((long)i * 2) * K + k], s2 += sums[((long)i * 2 + 1) * K + k];
+  s /= (double)N;
+  mean[k] = (float)s;
+  const double spread2 = s2 / (double)N - s * s;
+  const float state = fabsf(beta[k]) + 3.3f * fabsf(gamma[k]), matrix = spread2 > 0.0 ? (float)sqrt(spread2) : 0.f;
+  const bool both = state > 0.f && state < INFINITY && matrix > 0.f;
+  const float half = both ? 0.5f * log2f(state / matrix) : 0.f;
+  ratio[k] = both ? half : INFINITY;
+  __syncthreads();
+  float all = 0.f;
+  int of = 0;
+  for (int i = 0; i < K; i++)
+    if (ratio[i] < INFINITY) all += ratio[i], of++;
+  int l = 0;
+  if (both) l = (int)rintf(half - all / (float)of);
+  else if (state == 0.f && matrix > 0.f) l = -SC_LEVEL;
+  else if (matrix == 0.f && state > 0.f && state < INFINITY) l = SC_LEVEL;
+  level[k] = (int8_t)-(l < -SC_LEVEL ? -SC_LEVEL : l > SC_LEVEL ? SC_LEVEL : l);
 }
-// largest centred element of every row, a wave each; infinite (last in the order) where an element is not finite
-__global__ __launch_bounds__(256) void scout_top_kernel(const _Float16 *W, int N, int K, const float *mean, float *top) {
+// This lane's elements of row v as they are coded: centred, levelled, mixed (which on both sides multiplies a product by NE).
+// false: one of them is no finite number; it counts as 0.
+template <int NE>
+__device__ __forceinline__ bool scout_entry(const _Float16 *W, long v, const float *mean, const int8_t *level, int lane, _Float16 (&w)[NE], double (&x)[NE]) {
+  bool finite = true;
+#pragma unroll
+  for (int e = 0; e < NE; e++) {
+    const int k = lane * NE + e;
+    w[e] = W[v * (NE * 64) + k];
+    const bool f = scout_finite(w[e]);
+    x[e] = f ? ldexp((double)(float)w[e] - (double)mean[k], -level[k]) * (1.0 / NE) : 0.0;
+    finite &= f;
+  }
+  scout_mix<NE>(x);
+  return finite;
+}
+// largest of them in every row, a wave each; infinite (last in the order) where an element is not finite
+template <int NE>
+__global__ __launch_bounds__(256) void scout_top_kernel(const _Float16 *W, int N, const float *mean, const int8_t *level, float *top) {
   const int lane = threadIdx.x & 63, v = blockIdx.x * 4 + (threadIdx.x >> 6);
   if (v >= N) return;
-  float m = 0.f;
-  for (int k = lane; k < K; k += 64) {
-    const _Float16 w = W[(long)v * K + k];
-    m = fmaxf(m, scout_finite(w) ? fabsf((float)w - mean[k]) : INFINITY);
-  }
+  _Float16 w[NE];
+  double x[NE];
+  float m = scout_entry<NE>(W, v, mean, level, lane, w, x) ? 0.f : INFINITY;
+#pragma unroll
+  for (int e = 0; e < NE; e++) m = fmaxf(m, fabsf((float)x[e]));
   m = wave_max(m);
   if (lane == 0) top[v] = m;
 }
 // one strip per workgroup, sixteen rows per wave
-__global__ __launch_bounds__(256) void scout_pack_kernel(const _Float16 *W, int N, int K, const float *mean, const float *top, const int32_t *order,
-                                                         int8_t *codes, float4 *consts, int32_t *ids, _Float16 *sorted) {
+template <int NE>
+__global__ __launch_bounds__(256) void scout_pack_kernel(const _Float16 *W, int N, const float *mean, const int8_t *level, const float *top,
+                                                         const int32_t *order, int8_t *codes, float4 *consts, int32_t *ids, _Float16 *sorted) {
+  constexpr int K = NE * 64, KS = K / 32;
   __shared__ float norms[2][4];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, s = blockIdx.x, KS = K / 32;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, s = blockIdx.x;
   const int n = N - s * 64 < 64 ? N - s * 64 : 64;
   const float own = lane < n ? top[order[s * 64 + lane]] : 0.f, largest = wave_max(own < INFINITY ? own : 0.f);
   const float scale = largest > 0.f ? largest / 127.f : 1.f, inv = 1.f / scale;
@@ -101,23 +160,24 @@ __global__ __launch_bounds__(256) void scout_pack_kernel(const _Float16 *W, int 
   for (int i = wave * 16; i < wave * 16 + 16; i++) {
     const int v = i < n ? order[s * 64 + i] : -1;
     if (lane == 0) ids[s * 64 + i] = v;
-    double w2 = 0.0, f2 = 0.0;
-    for (int k = lane; k < K; k += 64) {
-      const _Float16 w = v >= 0 ? W[(long)v * K + k] : (_Float16)0.f;
-      const bool finite = scout_finite(w);
-      const float x = v >= 0 && finite ? (float)w - mean[k] : 0.f;
-      const float c = fminf(fmaxf(rintf(x * inv), -127.f), 127.f);
-      const double f = (double)x - (double)c * (double)scale;
-      w2 += finite ? (double)x * (double)x : INFINITY;
-      f2 += finite ? f * f : INFINITY;
-      sorted[((long)s * 64 + i) * K + k] = w;
+    _Float16 w[NE] = {};
+    double x[NE] = {}, w2 = 0.0, f2 = 0.0;
+    if (v >= 0 && !scout_entry<NE>(W, v, mean, level, lane, w, x)) w2 = f2 = INFINITY;
+#pragma unroll
+    for (int e = 0; e < NE; e++) {
+      const int k = lane * NE + e;
+      const float c = fminf(fmaxf(rintf((float)x[e] * inv), -127.f), 127.f);
+      const double f = x[e] - (double)c * (double)scale;
+      w2 += x[e] * x[e];
+      f2 += f * f;
+      sorted[((long)s * 64 + i) * K + k] = w[e];
       // the fragment order of nt_vocab_q8.hip
       codes[((((long)s * KS + k / 32) * 2 + i / 32) * 64 + i % 32 + 32 * ((k % 32) / 16)) * 16 + k % 16] = (int8_t)(int)c;
     }
 #pragma unroll
-    for (int x = 32; x >= 1; x >>= 1) {
-      w2 += __shfl_xor(w2, x, 64);
-      f2 += __shfl_xor(f2, x, 64);
+    for (int m = 32; m >= 1; m >>= 1) {
+      w2 += __shfl_xor(w2, m, 64);
+      f2 += __shfl_xor(f2, m, 64);
     }
     wn = fmaxf(wn, (float)(sqrt(w2) * 1.0001));
     fn = fmaxf(fn, (float)(sqrt(f2) * 1.0001));
@@ -129,22 +189,23 @@ __global__ __launch_bounds__(256) void scout_pack_kernel(const _Float16 *W, int 
                             fmaxf(fmaxf(norms[1][0], norms[1][1]), fmaxf(norms[1][2], norms[1][3])), 0.f);
 }
 
-hipError_t vocab_scout_build(const _Float16 *W, int N, int K, void *dst, hipStream_t s) {
+hipError_t vocab_scout_build(const _Float16 *W, int N, int K, const float *gamma, const float *beta, void *dst, hipStream_t s) {
   if (K != 256 && K != 512) return hipErrorInvalidValue;
   const int NS = (N + 63) / 64, parts = (N + SP_ROWS - 1) / SP_ROWS;
   int8_t *codes = (int8_t *)dst;
   float4 *consts = (float4 *)(codes + scout_code_bytes(N, K));
   int32_t *ids = (int32_t *)(consts + NS);
   _Float16 *sorted = (_Float16 *)(ids + 64 * (size_t)NS);
+  int8_t *level = (int8_t *)dst + scout_level_at(N, K);
   char *tmp = nullptr;
-  hipError_t e = hipMalloc((void **)&tmp, (size_t)parts * K * 8 + (size_t)K * 4 + (size_t)N * 8);
+  hipError_t e = hipMalloc((void **)&tmp, (size_t)parts * K * 16 + (size_t)K * 4 + (size_t)N * 8);
   if (e != hipSuccess) return e;
   double *sums = (double *)tmp;
-  float *mean = (float *)(sums + (size_t)parts * K), *top = mean + K;
+  float *mean = (float *)(sums + (size_t)parts * 2 * K), *top = mean + K;
   int32_t *order = (int32_t *)(top + N);
   hipLaunchKernelGGL(scout_sum_kernel, dim3(parts), dim3(K), 0, s, W, N, K, sums);
-  hipLaunchKernelGGL(scout_mean_kernel, dim3(1), dim3(K), 0, s, sums, parts, N, K, mean);
-  hipLaunchKernelGGL(scout_top_kernel, dim3((N + 3) / 4), dim3(256), 0, s, W, N, K, mean, top);
+  hipLaunchKernelGGL(scout_mean_kernel, dim3(1), dim3(K), 0, s, sums, parts, N, K, gamma, beta, mean, level);
+  hipLaunchKernelGGL(K == 512 ? scout_top_kernel<8> : scout_top_kernel<4>, dim3((N + 3) / 4), dim3(256), 0, s, W, N, mean, level, top);
   e = hipGetLastError();
   std::vector<float> h_top((size_t)N);
   std::vector<int32_t> h_order((size_t)N);
@@ -154,7 +215,8 @@ hipError_t vocab_scout_build(const _Float16 *W, int N, int K, void *dst, hipStre
   std::stable_sort(h_order.begin(), h_order.end(), [&](int32_t a, int32_t b) { return h_top[(size_t)a] < h_top[(size_t)b]; });
   if (e == hipSuccess) e = hipMemcpyAsync(order, h_order.data(), (size_t)N * 4, hipMemcpyHostToDevice, s);
   if (e == hipSuccess) {
-    hipLaunchKernelGGL(scout_pack_kernel, dim3(NS), dim3(256), 0, s, W, N, K, mean, top, order, codes, consts, ids, sorted);
+    hipLaunchKernelGGL(K == 512 ? scout_pack_kernel<8> : scout_pack_kernel<4>, dim3(NS), dim3(256), 0, s, W, N, mean, level, top, order, codes,
+                       consts, ids, sorted);
     e = hipGetLastError();
   }
   const hipError_t done = hipStreamSynchronize(s);
@@ -314,7 +376,7 @@ __global__ __launch_bounds__(SC_WAVES * 64) void vocab_scout_kernel(const int8_t
 // ---------------------------------------------------------------------------------------------------------------------
 // The candidates the scout has left, their exact logits, the arg-max: one or two rows per workgroup of eight waves.  All waves of a
 // row find its candidates; the logits are then dealt to groups of 16 lanes, because the rows differ (16 on average, 70 at most in a
-// thousand) and one wave with its own row's took as long as the worst row.
+// thousand on flat random logits) and one wave with its own row's took as long as the worst row.
 // Bound by its chain of dependent loads (the scout's groups, then the candidates' rows of the matrix), so a row is spread over as many
 // waves as find work in it.  With four rows per workgroup and four entries in flight per group - most of them loads of an entry that
 // was not there, 16 to 64 candidates for 128 places - it took 7.6, 8.2, 9.9 and 12.6 us at 45, 260, 400 and 1,000 rows on average,
@@ -401,7 +463,7 @@ __global__ __launch_bounds__(PK_WAVES * 64) void vocab_pick_kernel(const i32x4 *
     const float4 rc = row_consts[r];  // {scale, ||e||, ||a||}
     const halfNE xh = *(const halfNE *)(h_hi + (long)r * ldh + lane * NE), xl = *(const halfNE *)(h_lo + (long)r * ldh + lane * NE);
     // what a strip's scout logits may be off by, with what fp32 loses on either side
-    auto bound = [&](const float4 &c) { return 1.0001f * (rc.y * c.y + rc.z * c.z) + 2e-6f * (rc.y + rc.z) * c.y + distrust; };
+    auto bound = [&](const float4 &c) { return 1.0001f * (rc.y * c.y + rc.z * c.z) + 3e-6f * (rc.y + rc.z) * c.y + distrust; };
     float floor_ = -INFINITY;
     for (int s0 = 0;;) {
 #pragma unroll

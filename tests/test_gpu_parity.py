@@ -530,6 +530,47 @@ def test_scouted_argmax_with_values_that_are_no_numbers(nt, torch_cuda, d, what)
     gm.close()
 
 
+def test_scouted_argmax_with_columns_of_unequal_size(nt, torch_cuda):
+    """A final normalisation with a large offset or gain on a column, and a column of the output matrix that is larger than the
+    others, leave the 8-bit pass its precision: as few entries remain as need no other way.  Where they do not, each row
+    has all 32,000 logits computed by one workgroup and the decode takes more than ten times as long; three times is the line,
+    far from both.  Tokens as in test_scouted_argmax."""
+    torch = torch_cuda
+    rows, T, ms = 400, 8, {}
+    for what in ("plain", "offset 12", "offset 25", "gains", "matrix", "offset and matrix"):
+        cfg = nt_synth.model_config("C1", n_enc=0, max_len=16)
+        blob = nt_synth.make_weights(cfg, seed=23)
+        W, gain, offset = (nt_synth.blob_view(cfg, blob, n) for n in ("W_out", "dec_final.g", "dec_final.b"))
+        if what.startswith("offset"):
+            offset[7] = 12 if what == "offset 12" else 25
+        if what == "gains":
+            gain[[7, 300]] = 16
+        if what.endswith("matrix"):
+            W[:, 7 if what == "offset and matrix" else 9] *= np.float16(1 / 16 if what == "offset and matrix" else 16)
+        gm = nt.Model(cfg, blob, max_batch_tokens=2048, pipeline_lanes=1)
+        rng = np.random.default_rng(5)
+        out, logits = decode_with_logits(nt, torch, gm, cfg, rows, 3, rng)
+        got = logits.gather(2, out.unsqueeze(2)).squeeze(2)
+        norm = float(np.linalg.norm(W.astype(np.float64), axis=1).max() * np.sqrt(float((gain.astype(np.float64) ** 2 + offset.astype(np.float64) ** 2).sum())))
+        short = float((logits.max(dim=2).values - got).max()) / norm
+        src = torch.from_numpy(rng.integers(4, 32000, size=(rows, 2)).astype(np.int32)).cuda()
+        lens = torch.full((rows,), 2, dtype=torch.int32, device="cuda")
+        tokens, times = torch.empty(rows, T, dtype=torch.int32, device="cuda"), []
+        for _ in range(6):
+            gm.encode(src, lens)
+            begin, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            begin.record()
+            gm.decode_greedy(rows, T, tokens)
+            end.record()
+            end.synchronize()
+            times.append(begin.elapsed_time(end))
+        ms[what] = float(np.median(times))
+        print(f"{what}: short of the largest by {short:.1e} of |h| |w|, {ms[what]:.3f} ms", flush=True)
+        assert short <= 1.2e-5
+        gm.close()
+    assert all(t <= 3 * ms["plain"] for t in ms.values()), ms
+
+
 # ------------------------------------------------------------------------------ restored components (C3) and teacher shape (C4)
 def _check_workload_sample(nt, oracle, name, n_sent, budget, n_audit=None, **overrides):
     """Translate n_sent sentences of a workload at a token budget and audit a seeded sample of n_audit of them (all,
