@@ -368,16 +368,17 @@ int alloc_lane_state(nt_model *m, hipStream_t s) {
   const int64_t Mt = m->max_tokens, Br = m->max_rows;
   m->self_positions = (6 * Mt + 4) / 5 + 3 * Br + 8;
   if (m->self_positions < Br * 1) m->self_positions = Br;
-  {  // arg-max partials: the count per row depends only on the number of row tiles (64 or 128 rows each)
-    int64_t worst = 0;
+  {  // arg-max partials: of the few-row kernel, and of the others, whose count per row depends only on the number of row tiles (64 or
+     // 128 rows each)
+    const int few = (int)std::min<int64_t>(Br, nt::kVocabWideRows);
+    int64_t worst = (int64_t)few * nt::vocab_argmax_partials(m->vw, few, false, true);
     for (int64_t mt = 1; (mt - 1) * 64 < Br; mt++) {
       const int64_t rows = std::min<int64_t>(mt * 64, Br);
       for (int tiled = 0; tiled < 2; tiled++) {  // either family of arg-max kernels may be selected later
         nt::VocabWeights w = m->vw;
         w.force_tiled = tiled != 0;
-        for (int wide = 0; wide < 2; wide++)
-          worst = std::max(worst, rows * nt::vocab_argmax_partials(w, (int)rows, false, wide != 0));
-        worst = std::max(worst, rows * nt::vocab_argmax_partials(w, (int)rows, true, false));
+        for (int certified = 0; certified < 2; certified++)
+          worst = std::max(worst, rows * nt::vocab_argmax_partials(w, (int)rows, certified != 0, false));
       }
       if (cfg->q8_output) worst = std::max(worst, rows * nt::vocab_q8_partials((int)rows));
     }
