@@ -370,8 +370,9 @@ int alloc_lane_state(nt_model *m, hipStream_t s) {
   if (m->self_positions < Br * 1) m->self_positions = Br;
   {  // arg-max partials: of the few-row kernel, and of the others, whose count per row depends only on the number of row tiles (64 or
      // 128 rows each)
-    const int few = (int)std::min<int64_t>(Br, nt::kVocabWideRows);
-    int64_t worst = (int64_t)few * nt::vocab_argmax_partials(m->vw, few, false, true);
+    int64_t worst = 0;
+    for (int64_t rows = Br; rows > 0 && worst == 0; rows--)  // the most it is taken for
+      if (nt::vocab_wide(m->vw, (int)rows)) worst = rows * nt::vocab_argmax_partials(m->vw, (int)rows, false, true);
     for (int64_t mt = 1; (mt - 1) * 64 < Br; mt++) {
       const int64_t rows = std::min<int64_t>(mt * 64, Br);
       for (int tiled = 0; tiled < 2; tiled++) {  // either family of arg-max kernels may be selected later
@@ -1130,7 +1131,7 @@ int decode_step(nt_model *m, DecodeCursor &cu, hipStream_t s) {
     int rc;
     // The scout's sums run in another order than the wide kernel's: chosen as above.  (The tiled kernels' certified form gives the
     // full pass's result at any row count.)
-    const bool wide = rows_for_choice <= nt::kVocabWideRows;
+    const bool wide = nt::vocab_wide(m->vw, rows_for_choice);
     const bool scouted = nt::vocab_scouted(m->vw, wide) && m->Wscout;
     const bool certified = !d_logits && !c.q8_output && (scouted || (nt::vocab_tiled(m->vw) && R >= kCertMinRows));
     const nt::ScoutOut scout_out = certified && scouted ? nt::ScoutOut{m->scout_codes, m->scout_rc, nt::vocab_scout_levels(m->Wscout, V, d)} : nt::ScoutOut{};

@@ -2,8 +2,8 @@
 // choice among the kernels.
 //
 // The log-softmax of the output layer is not needed for greedy search (Sec. 3.3 "Graph Optimization"), and the logits never reach
-// memory: a lane owns a row and folds the logits in its accumulators into the row's best.  Up to kVocabWideRows rows take vocab_wide_kernel
-// below, more the scout of nt_vocab_scout.hip, model widths other than 256 and 512 the tiled kernels of nt_gemm.hip.
+// memory: a lane owns a row and folds the logits in its accumulators into the row's best.  A few rows, or a
+// few hundred with a small vocabulary, take vocab_wide_kernel below (vocab_wide), more the scout of nt_vocab_scout.hip, model widths other than 256 and 512 the tiled kernels of nt_gemm.hip.
 //
 // Fragment order of Wp: [strip = v / 64][ks = k / 16][nb = (v % 64) / 32][lane][8 halfs] with
 // lane = v % 32 + 32 * ((k % 16) / 8): lane l of the MFMA row operand holds W[v = l % 32][k = 8 * (l / 32) .. + 7].  A wave fetches a
@@ -39,15 +39,15 @@ void vocab_pack(const _Float16 *Wt, int N, int K, _Float16 *dst) {
 // a tile to be filled.  They are requested first (loads return in order, and theirs are short) and a scheduling barrier keeps every
 // load ahead of the first product: a step of 1 / 8 rows 14.8 / 15.6 us, with the rows last 15.0 / 16.0, left to the compiler, which
 // requests the matrix in portions, 16.1 / 16.9.  Partial logits meet in the LDS.  The matrix is read past the L2 (non-temporal): it
-// does not fit there and would evict the decoder's other weights at every step.
-// One row: 7.0 us against 12.7, and 20 instead of 25 us for the decoder layer that follows.  Where the scout
-// (nt_vocab_scout.hip) takes over: kVocabWideRows.
+// does not fit there and would evict the decoder's other weights at every step.  (Several tiles of 32 rows, which share a small one,
+// read it through the L2.)
+// One row: 7.0 us against 12.7, and 20 instead of 25 us for the decoder layer that follows.
 // ---------------------------------------------------------------------------------------------------------------------
-template <int K, int SPW>
+constexpr int VW_ROWS = 32;
+template <int K, int SPW, bool TILES>
 __global__ __launch_bounds__(512) void vocab_wide_kernel(const _Float16 *__restrict__ h_hi, const _Float16 *__restrict__ h_lo,
                                                          long ldh, int M, const _Float16 *__restrict__ Wp, int N, int G,
                                                          unsigned long long *__restrict__ pk) {
-  static_assert(kVocabWideRows <= 32, "one tile of rows");
   constexpr int KP = 8 / SPW, KS = K / 16, KSW = KS / KP, GPW = 8 / KP;  // k-parts; k-steps and register groups of a wave
   typedef float f32x4 __attribute__((ext_vector_type(4)));
   __shared__ f32x4 red[8 * 8 * 64];  // [wave][register group][lane]
@@ -59,7 +59,7 @@ __global__ __launch_bounds__(512) void vocab_wide_kernel(const _Float16 *__restr
   const int strip = strip_want < NS ? strip_want : NS - 1;  // past the end: the last strip again (same keys)
   const __amdgpu_buffer_rsrc_t wrs = __builtin_amdgcn_make_buffer_rsrc((void *)Wp, 0, NS * 64 * K * 2, 0x00020000);
   const int w0 = (strip * KS + kp * KSW) * 2048;
-  const int m = li < M ? li : M - 1;
+  const int m0 = TILES ? blockIdx.y * VW_ROWS : 0, m = m0 + li < M ? m0 + li : M - 1;
   const long at_ = (long)m * ldh + kp * (KSW * 16) + g * 8;
   half8 xh[KSW], xl[KSW];
 #pragma unroll
@@ -73,7 +73,7 @@ __global__ __launch_bounds__(512) void vocab_wide_kernel(const _Float16 *__restr
   for (int ks = 0; ks < KSW; ks++)
 #pragma unroll
     for (int nb = 0; nb < 2; nb++)
-      w[ks][nb] = __builtin_bit_cast(half8, __builtin_amdgcn_raw_buffer_load_b128(wrs, lane * 16 + nb * 1024, w0 + ks * 2048, 2));
+      w[ks][nb] = __builtin_bit_cast(half8, __builtin_amdgcn_raw_buffer_load_b128(wrs, lane * 16 + nb * 1024, w0 + ks * 2048, TILES ? 0 : 2));
   __builtin_amdgcn_sched_barrier(0);
   floatx16 acc[2];
 #pragma unroll
@@ -113,38 +113,43 @@ __global__ __launch_bounds__(512) void vocab_wide_kernel(const _Float16 *__restr
   key = other > key ? other : key;
   if (g == 0) skey[wave][li] = key;
   __syncthreads();
-  if (tid < M) {
+  if (tid < VW_ROWS && m0 + tid < M) {
     unsigned long long k = skey[0][tid];
 #pragma unroll
     for (int i = 1; i < 8; i++) k = skey[i][tid] > k ? skey[i][tid] : k;
-    pk[(long)tid * G + blockIdx.x] = k;
+    pk[(long)(m0 + tid) * G + blockIdx.x] = k;
   }
 }
 
 // Strips per workgroup of the wide kernel: one (eight k-parts) as long as that is one round of workgroups, else two
 static int vw_strips(int N) { return (N + 63) / 64 <= 256 ? 1 : 2; }
 static int vw_groups(int N) { return ((N + 63) / 64 + vw_strips(N) - 1) / vw_strips(N); }
-// Taken for few rows and vocabularies that need at most two rounds of workgroups.
-static bool use_wide(const VocabWeights &w, int M, bool wide) { return wide && M <= kVocabWideRows && vw_groups(w.N) <= 512; }
-
 static bool use_stream(const VocabWeights &w) { return !w.force_tiled && w.Wp && vocab_stream_supported(w.K); }
 
 bool vocab_tiled(const VocabWeights &w) { return !use_stream(w); }
-bool vocab_scouted(const VocabWeights &w, bool wide) { return use_stream(w) && !use_wide(w, 1, wide); }
+bool vocab_wide(const VocabWeights &w, int rows) {
+  if (!use_stream(w)) return false;
+  const long tiles = (rows + VW_ROWS - 1) / VW_ROWS;
+  return tiles == 1 ? vw_groups(w.N) <= 512 : tiles * ((w.N + 63) / 64) <= kVocabWideStrips;
+}
+bool vocab_scouted(const VocabWeights &w, bool wide) { return use_stream(w) && !wide; }
 
 int vocab_argmax_partials(const VocabWeights &w, int M, bool certified, bool wide) {
   if (!use_stream(w)) return vocab_argmax_partials_tiled(M, w.N);
-  return !certified && use_wide(w, M, wide) ? vw_groups(w.N) : 0;
+  return !certified && wide ? vw_groups(w.N) : 0;
 }
 
 hipError_t launch_vocab_argmax(const _Float16 *h, const _Float16 *h_lo, long ldh, const VocabWeights &w, int M,
                                unsigned long long *pk, bool wide, hipStream_t s) {
   if (M <= 0) return hipSuccess;
   if (!use_stream(w)) return launch_vocab_argmax_tiled(h, h_lo, ldh, w.Wt, M, w.N, w.K, pk, s);
-  if (!use_wide(w, M, wide)) return hipErrorInvalidValue;
+  if (!wide) return hipErrorInvalidValue;
   const int G = vw_groups(w.N), spw = vw_strips(w.N);
 #define NT_VW(K_, S_) \
-  if (w.K == K_ && spw == S_) hipLaunchKernelGGL((vocab_wide_kernel<K_, S_>), dim3(G), dim3(512), 0, s, h, h_lo, ldh, M, w.Wp, w.N, G, pk);
+  if (w.K == K_ && spw == S_) {                                                                                                       \
+    if (M <= VW_ROWS) hipLaunchKernelGGL((vocab_wide_kernel<K_, S_, false>), dim3(G), dim3(512), 0, s, h, h_lo, ldh, M, w.Wp, w.N, G, pk); \
+    else hipLaunchKernelGGL((vocab_wide_kernel<K_, S_, true>), dim3(G, (M + VW_ROWS - 1) / VW_ROWS), dim3(512), 0, s, h, h_lo, ldh, M, w.Wp, w.N, G, pk); \
+  }
   NT_VW(512, 1) NT_VW(512, 2) NT_VW(256, 1) NT_VW(256, 2)
 #undef NT_VW
   return hipGetLastError();

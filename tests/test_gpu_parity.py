@@ -530,6 +530,38 @@ def test_scouted_argmax_with_values_that_are_no_numbers(nt, torch_cuda, d, what)
     gm.close()
 
 
+def short_of_the_largest(nt, torch, d, V, rows_list, T, max_tokens, seed):
+    """Largest distance of a decode's tokens from the largest logit of the GEMM path, in |h| |w|."""
+    cfg = nt_synth.model_config("C1", d_model=d, vocab=V, n_enc=0, max_len=16)
+    blob = nt_synth.make_weights(cfg, seed=seed, random_affine=True)
+    norm = float(np.linalg.norm(nt_synth.blob_view(cfg, blob, "W_out").astype(np.float64), axis=1).max())
+    gm = nt.Model(cfg, blob, max_batch_tokens=max_tokens, pipeline_lanes=1)
+    rng, worst = np.random.default_rng(seed), 0.0
+    for rows in rows_list:
+        out, logits = decode_with_logits(nt, torch, gm, cfg, rows, T, rng)
+        got = logits.gather(2, out.unsqueeze(2)).squeeze(2)
+        short = float((logits.max(dim=2).values - got).max()) / (norm * d ** 0.5)
+        print(f"{d} x {V}, {rows} rows: short of the largest by {short:.1e} of |h| |w|")
+        worst = max(worst, short)
+    gm.close()
+    return worst
+
+
+@pytest.mark.parametrize("d", [256, 512])
+@pytest.mark.parametrize("V,rows", [(4001, [33, 63, 64, 65, 320, 321]), (17000, [33, 64, 65]), (64, [33, 1000])])
+def test_argmax_of_several_tiles_of_rows(nt, torch_cuda, d, V, rows):
+    """The kernel of a few rows with more than one tile of 32, the last one full or of a single row, up to its line (4,001 entries: 320
+    rows; 17,000, two strips of 64 to a workgroup, an odd number of them: 64) and one row past it.  Bound as in test_scouted_argmax."""
+    assert short_of_the_largest(nt, torch_cuda, d, V, rows, 3, 4096, seed=29) <= 1.2e-5
+
+
+@pytest.mark.parametrize("d,V,rows", [(256, 4033, 8192 + 129), (512, 40, 20480 + 33)])
+def test_scouted_argmax_in_chunks_of_rows(nt, torch_cuda, d, V, rows):
+    """The scout takes 8,192 rows at a time: a second chunk that ends inside a tile, and a third, of a vocabulary below a strip.  Bound
+    as in test_scouted_argmax."""
+    assert short_of_the_largest(nt, torch_cuda, d, V, [rows], 2, 2 * rows, seed=31) <= 1.2e-5
+
+
 def test_scouted_argmax_with_columns_of_unequal_size(nt, torch_cuda):
     """A final normalisation with a large offset or gain on a column, and a column of the output matrix that is larger than the
     others, leave the 8-bit pass its precision: as few entries remain as need no other way.  Where they do not, each row
