@@ -199,14 +199,18 @@ def main():
     # (2) solo: the same batches one after the other on lane 0, each kernel alone on the GPU.
     peaks = model.probe_peaks(stream=streams[0])   # what this machine reaches on plain probes, in this run
 
+    # the arg-max of many rows (its scout pass, or the 8-bit output layer) runs on the int8 matrix cores, at twice the fp16 peak;
+    # the tiled kernels of other widths do not
+    argmax_in_8_bits = cfg["d_model"] in (256, 512)
+
     def kernel_table(kern):
         """Per family: algorithmic GB/s and TFLOP/s over the event-to-event time of its launches, as percentages of
-        the datasheet peaks (HBM 8 TB/s, fp16 MFMA 2.5 PFLOP/s; the arg-max of many rows, in 8 bits, against 5 POP/s) and of the
+        the datasheet peaks (HBM 8 TB/s, fp16 MFMA 2.5 PFLOP/s; the arg-max of many rows, where it is in 8 bits, against 5 POP/s) and of the
         peaks the probes measured in this run."""
         tab = {}
         for name, k in kern.items():
             gbs, tfs = k["bytes"] / k["ms"] / 1e6, k["flops"] / k["ms"] / 1e9
-            mfma_peak = MFMA_I8_PEAK_TOPS if name == "vocab_argmax" else MFMA_F16_PEAK_TFLOPS
+            mfma_peak = MFMA_I8_PEAK_TOPS if argmax_in_8_bits and name == "vocab_argmax" else MFMA_F16_PEAK_TFLOPS
             tab[name] = dict(launches=k["launches"], total_ms=round(k["ms"], 3), avg_us=round(1e3 * k["ms"] / k["launches"], 2),
                              GBps=round(gbs, 1), TFLOPs=round(tfs, 2),
                              pct_hbm_peak=round(100 * gbs / HBM_PEAK_GBS, 1), pct_mfma_peak=round(100 * tfs / mfma_peak, 1),
@@ -217,8 +221,7 @@ def main():
 
     def roof(k, name=None):
         intensity = k["flops"] / k["bytes"]
-        # the arg-max (its scout pass, or the 8-bit output layer) runs on the int8 matrix cores: twice the fp16 peak
-        mfma_peak, unit = (MFMA_I8_PEAK_TOPS, "TOP/s") if name == "vocab_argmax" else (MFMA_F16_PEAK_TFLOPS, "TFLOP/s")
+        mfma_peak, unit = (MFMA_I8_PEAK_TOPS, "TOP/s") if argmax_in_8_bits and name == "vocab_argmax" else (MFMA_F16_PEAK_TFLOPS, "TFLOP/s")
         if intensity > mfma_peak * 1e12 / (HBM_PEAK_GBS * 1e9):
             bound, achieved, peak = "mfma", k["flops"] / k["ms"] / 1e9, mfma_peak
         else:

@@ -420,15 +420,17 @@ def test_tiled_argmax_kernels_agree_with_streaming_kernels(nt):
     assert same >= 1014   # summation order differs, so an exact tie of fp32 logits may fall the other way
 
 
-def test_certified_argmax_equals_full_recompute(nt):
-    """The single-pass arg-max certifies a row only if the head-only winner provably wins the head+tail logits
-    too, so its tokens must be exactly those of recomputing every row with both planes.
-    nt_debug_set_cert_distrust makes the bound infinite: every row of every step with >= 512 active rows goes through the gathered
-    recompute kernel (thousands of rows: several list chunks and several tiles per workgroup)."""
+@pytest.mark.parametrize("tiled", [False, True])
+def test_certified_argmax_equals_full_recompute(nt, tiled):
+    """What a bound rules out is not computed, so the tokens must be exactly those of computing everything with both planes.
+    nt_debug_set_cert_distrust makes the bound infinite.  The 8-bit pass (steps of more than 32 rows) then leaves every entry, and each
+    row has all its logits computed; the tiled kernels, which certify the winner of the head plane in steps of 512 rows and more,
+    send every row through the gathered recompute (thousands of rows: several tiles per workgroup)."""
     cfg = nt_synth.model_config("C1")
     blob = nt_synth.make_weights(cfg, seed=0)
     tokens, offsets = nt_synth.workload("C2", 6000)
     gm = nt.Model(cfg, blob, max_batch_tokens=65536)
+    gm.debug_set_vocab_tiled(tiled)
     ref, ro = gm.translate_batch(tokens, offsets, token_budget=65536)
     gm.debug_set_cert_distrust(True)
     out, oo = gm.translate_batch(tokens, offsets, token_budget=65536)
