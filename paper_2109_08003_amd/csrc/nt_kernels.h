@@ -91,7 +91,10 @@ hipError_t launch_gemm_stream(bool c_f32, const _Float16 *A, const _Float16 *A_l
 // x [M][512] += relu(LayerNorm(x) W1^T + b1) W2^T + b2 in one launch; both matrices in fragment order, hidden width F.  A tile of 32 rows takes
 // its workgroup 65 us at F = 2,048, so the line lies where two launches, which spread a tile over several, take as long: six layers with 8
 // heads at 2,048 / 3,072 / 4,096 tokens 469 / 509 / 541 us with it and 418 / 562 / 625 without; 8,192, 16,384, 65,536: 832 / 1,535 / 6,079
-// against 976 / 1,828 / 6,581.
+// against 976 / 1,828 / 6,581.  Past a full round of 8,192 tokens, where a few workgroups take one tile more, the two launches have begun a
+// round of theirs: 8,224 / 9,216 / 10,240 / 12,288 tokens 1,247 / 1,171 / 1,183 / 1,241 against 1,332 / 1,189 / 1,235 / 1,370; 16,416, 24,608,
+// 32,800: 2,109 / 2,704 / 3,680 against 2,716 / 3,151 / 4,333.  F = 1,024 crosses at the same place: 2,048 / 2,560 / 3,072 tokens 361 / 383 / 403
+// against 349 / 408 / 425; 8,224, 9,216, 10,240: 963 / 905 / 933 against 1,056 / 935 / 971; 16,416, 65,536: 1,659 / 4,552 against 2,040 / 4,891.
 constexpr int kFfnMinRows = 2560;
 bool gemm_ffn_supported(int M, int d, int F);  // and worth it
 hipError_t launch_gemm_ffn(float *x, int M, int F, const GemmLayerNorm &ln, const _Float16 *W1p, const float *b1, const _Float16 *W2p, const float *b2,
