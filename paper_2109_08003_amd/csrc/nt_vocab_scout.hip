@@ -197,6 +197,8 @@ hipError_t vocab_scout_build(const _Float16 *W, int N, int K, const float *gamma
   int32_t *ids = (int32_t *)(consts + NS);
   _Float16 *sorted = (_Float16 *)(ids + 64 * (size_t)NS);
   int8_t *level = (int8_t *)dst + scout_level_at(N, K);
+  std::vector<float> h_top((size_t)N);  // (before the device memory: they may throw)
+  std::vector<int32_t> h_order((size_t)N);
   char *tmp = nullptr;
   hipError_t e = hipMalloc((void **)&tmp, (size_t)parts * K * 16 + (size_t)K * 4 + (size_t)N * 8);
   if (e != hipSuccess) return e;
@@ -207,8 +209,6 @@ hipError_t vocab_scout_build(const _Float16 *W, int N, int K, const float *gamma
   hipLaunchKernelGGL(scout_mean_kernel, dim3(1), dim3(K), 0, s, sums, parts, N, K, gamma, beta, mean, level);
   hipLaunchKernelGGL(K == 512 ? scout_top_kernel<8> : scout_top_kernel<4>, dim3((N + 3) / 4), dim3(256), 0, s, W, N, mean, level, top);
   e = hipGetLastError();
-  std::vector<float> h_top((size_t)N);
-  std::vector<int32_t> h_order((size_t)N);
   if (e == hipSuccess) e = hipMemcpyAsync(h_top.data(), top, (size_t)N * 4, hipMemcpyDeviceToHost, s);
   if (e == hipSuccess) e = hipStreamSynchronize(s);
   std::iota(h_order.begin(), h_order.end(), 0);
