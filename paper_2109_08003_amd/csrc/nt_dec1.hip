@@ -33,25 +33,28 @@
 // times the matrix time.)  The weight fragments of the next projection are requested before the attention or LayerNorm
 // phase that precedes it.
 //
-// Folded attention (one-layer decoders, batches of up to kDec1FoldRows rows).  q . k = (W y + b) . k = y . (W^T k) + b . k,
+// Folded attention (one-layer decoders).  q . k = (W y + b) . k = y . (W^T k) + b . k,
 // and Wo (sum p v) + bo = sum p (Wo v + bo).  With the cross keys and values of a sentence multiplied by the two matrices once,
 // when the batch is encoded, and the self values projected by the product of value and output matrix (formed at load, a fourth
 // group of columns of the table), a step's attention half has no projection left.  The self values are cached without their constant, which a
 // softmax passes through unchanged, and with every column divided by its norm: either would set the one scale of a vector's
 // integers for all its elements (eight output biases of 16, or eight output columns 16 times as large, leave 1.3e-5 / 1.1e-4 of
-// the context's norm instead of 2.5e-6 / 2.7e-5).  The cross products are formed from the rounded (integer)
-// vectors, so nothing is rounded that was not before, and kept in fp32: twice the bytes, which is why larger batches, whose
-// time is those bytes, do without (a 4,096-token budget, batches of 36 to 341 rows: 27.5 ms folded up to 256 rows, 26.7 up to
+// the context's norm instead of 2.5e-6 / 2.7e-5).  Batches of up to kDec1FoldRows rows: the cross products are formed from the rounded
+// (integer) vectors, so nothing is rounded that was not before, and kept in fp32: twice the bytes (a 4,096-token budget, batches of 36 to 341 rows: 27.5 ms folded up to 256 rows, 26.7 up to
 // 512; batches alone on the chip, 300 / 450 rows of 35 padded tokens: 3.14 -> 2.74 / 3.89 -> 3.52 ms folded; 320 rows of 180:
-// 24.0 ms with, 23.9 without, which puts the line for kDec1FoldTokens below that.  Beside other lanes, who share the
-// bandwidth, it lies lower - a 16,384-token budget 80.0 ms folded, 78.8 without - but a batch's tokens may not depend on what
-// runs beside it).  What is left is latency: a row per workgroup of four waves, the
+// 24.0 ms with, 23.9 without, which puts the line for kDec1FoldTokens below that).  What is left is latency: a row per workgroup of four waves, the
 // first cross keys requested before the self-attention.  One row 20.6 us without folding, 12.8 with the cross cache folded,
 // 45 rows 26 and 17.8; with the self values too, one sentence 1119 -> 1012 us, 45 sentences 3742 -> 3207 us, 8 sentences of
 // the 256-wide model 1253 -> 1175 us, a 4,096-token budget 28.0 -> 27.5 ms (each with the projection as a launch of its own).
 //
-// Registers: four forms spill some of theirs - eight heads with two rows (6, 28 bytes of scratch per lane) and with eight rows
-// (13, 56 bytes), folded with two rows at d = 512 without (17, 64 bytes) and with the FFN (37, 84 bytes).  The others use no scratch.
+// Larger batches keep the products as 16-bit integers, the same bytes as without folding (nt_cross_fold.hip).  A step's layer alone, us,
+// against three matrices per workgroup: 2,000 rows of 27 tokens 55 -> 40, 700 of 40 44 -> 25, 1,000 of 55 55 -> 34, 320 of 150 49 -> 32;
+// with an FFN of the model's width 70 -> 57, 55 -> 37 (700 of 40), 58 -> 44.  200,000 sentences at 65,536 tokens 457 -> 430 ms, 320 rows of 150
+// tokens 18.7 -> 14.9 ms, 32,768 through the submitted student 96 -> 89.5 ms.  Not before an 8-bit output layer (fold_all in
+// nt_host.hip); several layers have no folded form.
+//
+// Registers: three forms spill some of theirs - eight heads with two rows (28 bytes of scratch per lane) and with eight rows
+// (56 bytes), folded in fp32 with two rows and the FFN at d = 512 (44 bytes).  The others use no scratch.
 //
 // Measured per step of 1,900 / 45 / 1 rows, alone: 92 / 42 / 38 us as four launches, 71 / 30 / 25 us as one, without
 // the launch that projected Q | K | V (21 / 11 / 9 us).  With the table in its place and folded caches one row now takes 7.7 us.
@@ -258,15 +261,20 @@ struct D1Rel {
 };
 
 // The keys of one block and their fold into a partial softmax; positions past the end repeat the last key and get
-// weight 0.  F32: fp32 keys and values, each key with an additive constant (sc[p]), instead of integers with scales.
-template <int NE, bool F32>
+// weight 0.  KIND: integers with scales (sc[2 p], sc[2 p + 1]); fp32 keys and values, each key with an additive constant (sc[p]); or
+// integers with scales and such a constant (sc[4 p .. 4 p + 2]).
+// These numbers, which every lane needs, come through scalar loads (earlier launches wrote them): 16 to 24 vector registers less, which
+// are what two blocks in flight take in a wave of 128, and a third of the load instructions (a 4,096-token budget 19.7 -> 19.4 ms).
+enum D1Kind { D1_CODES, D1_FLOATS, D1_CODES_CONST };
+template <int NE, D1Kind KIND>
 struct D1Block {
+  static constexpr bool F32 = KIND == D1_FLOATS;
   typedef short shortNE __attribute__((ext_vector_type(NE)));
   typedef float floatNE __attribute__((ext_vector_type(NE)));
   typedef typename std::conditional<F32, floatNE, shortNE>::type Vec;
   typedef typename std::conditional<F32, float, short>::type Elt;
   Vec k[D1_NK], v[D1_NK];
-  float ks[D1_NK], vs[D1_NK];
+  float ks[D1_NK], vs[D1_NK], kc[D1_NK];
 
   __device__ __forceinline__ void load(const void *kv, const float *sc, long pos0, int j0, int n, int lane) {
     constexpr int D = NE * 64;
@@ -277,8 +285,11 @@ struct D1Block {
       const Elt *kp = (const Elt *)kv + p * 2 * D + lane * NE;
       k[i] = *(const Vec *)kp;
       v[i] = *(const Vec *)(kp + D);
-      ks[i] = F32 ? sc[p] : sc[p * 2];
-      vs[i] = F32 ? 1.f : sc[p * 2 + 1];
+      typedef const __attribute__((address_space(4))) float *Uniform;
+      const Uniform u = (Uniform)(unsigned long long)(sc + p * (F32 ? 1 : KIND == D1_CODES ? 2 : 4));
+      ks[i] = F32 ? 1.f : u[0];
+      vs[i] = F32 ? 1.f : u[1];
+      kc[i] = F32 ? u[0] : KIND == D1_CODES_CONST ? u[2] : 0.f;
     }
   }
   __device__ __forceinline__ void fold(const float (&q)[NE], int j0, int n, int lane, D1Part<NE> &a, const D1Rel &) const {
@@ -299,7 +310,7 @@ struct D1Block {
 #pragma unroll
     for (int i = 0; i < D1_NK; i++) {
       const float dot = __uint_as_float((unsigned)__builtin_amdgcn_readlane((int)__float_as_uint(r1), 16 * i));
-      s[i] = F32 ? dot + ks[i] : dot * ks[i];
+      s[i] = F32 ? dot + kc[i] : KIND == D1_CODES_CONST ? dot * ks[i] + kc[i] : dot * ks[i];
       if (j0 + i >= n) s[i] = -INFINITY;
       bm = fmaxf(bm, s[i]);
     }
@@ -453,10 +464,10 @@ __device__ __forceinline__ void first_layer_start(const Dec1Args &a, int y, int 
   float pv[NE], tq[NE], tk[NE], tv[NE];
   d1_load<NE>(a.sb.pe + (long)a.sb.t * D + lane * NE, pv);
   d1_load<NE>(by_token, tq);
-  const int vcol = (a.table.parts - 1) * D;
+  const int vcol = a.folded ? (a.table.parts - 1) * D : 2 * D;
   if (first_wave) {
     d1_load<NE>(by_token + D, tk);
-    d1_load<NE>(by_token + (a.folded ? vcol : 2 * D), tv);
+    d1_load<NE>(by_token + vcol, tv);
   }
   const float sc = sqrtf((float)D);
   float s = 0.f;
@@ -480,14 +491,15 @@ __device__ __forceinline__ void first_layer_start(const Dec1Args &a, int y, int 
   combine(tq, 0, q);
   if (first_wave) {
     combine(tk, D, kx);
-    combine(tv, a.folded ? vcol : 2 * D, vx);
+    combine(tv, vcol, vx);
   }
 }
 
 // D: model width.  RW: rows per workgroup, NWAVES / RW waves each.  PARTS: partial softmaxes per row.  IND: row r uses cache
-// row origin[r] (< 0: no row, zero context).  FFN: the layer's FFN (of width D) is part of the chain.  FOLD: the cross cache
-// holds folded fp32 vectors.  HEADS: eight heads of 64 columns, self cache fp32, cross cache fp16, optional relative keys.
-template <int D, int RW, int NWAVES, int PARTS, bool IND, bool FFN, bool FOLD, bool HEADS>
+// row origin[r] (< 0: no row, zero context).  FFN: the layer's FFN (of width D) is part of the chain.  FOLD32, FOLD16 (0 / 1): the
+// caches hold folded vectors, in fp32 or as integers.  HEADS: eight heads of 64 columns, self cache fp32, cross cache fp16, optional
+// relative keys.
+template <int D, int RW, int NWAVES, int PARTS, int FOLD16, bool IND, bool FFN, bool FOLD32, bool HEADS>
 __global__ __launch_bounds__(NWAVES * 64) void dec1_kernel(Dec1Args a) {
   constexpr int NE = D / 64, WR = NWAVES / RW, PW = PARTS / WR;  // elements per lane; waves per row; partials per wave
   constexpr int NC = D / NWAVES, NT = NC / 16;                   // output columns of a wave, in tiles of 16
@@ -496,17 +508,23 @@ __global__ __launch_bounds__(NWAVES * 64) void dec1_kernel(Dec1Args a) {
   // whether the next matrix's first fragments are requested before an attention phase: 32 of 128 registers, which a wave
   // with several partial softmaxes does not have
   constexpr bool EARLY = !(NWAVES == 16 && (PW > 1 || HEADS));
+  constexpr bool FOLD = FOLD32 || FOLD16;
+  constexpr bool ALONE = FOLD && WR == 1;  // no wave of the attention phases needs another's results
+  // what is requested before it is needed: 2 both caches' first blocks before the step's start, 1 a cache's at a time, 0 nothing
+  constexpr int AHEAD = !FOLD ? 0 : NWAVES < 16 ? 2 : FFN ? 0 : 1;
   static_assert(!HEADS || (D == 512 && !FOLD && !FFN), "heads are eight lanes of eight elements");
-  typedef typename std::conditional<HEADS, D1HeadBlock<NE, float>, D1Block<NE, false>>::type SelfBlock;
-  typedef typename std::conditional<HEADS, D1HeadBlock<NE, _Float16>, D1Block<NE, FOLD>>::type CrossBlock;
+  typedef typename std::conditional<HEADS, D1HeadBlock<NE, float>, D1Block<NE, D1_CODES>>::type SelfBlock;
+  typedef typename std::conditional<HEADS, D1HeadBlock<NE, _Float16>,
+                                    D1Block<NE, FOLD32 ? D1_FLOATS : FOLD16 ? D1_CODES_CONST : D1_CODES>>::type CrossBlock;
   typedef D1Part<NE> Part;
-  __shared__ __attribute__((aligned(16))) _Float16 sA[2 * RW * LD];               // head rows, then tail rows
+  __shared__ __attribute__((aligned(16))) _Float16 sA[FOLD && !FFN ? 8 : 2 * RW * LD];  // head rows, then tail rows
   __shared__ __attribute__((aligned(16))) float sZ[RW * ZLD];                     // residual stream
-  __shared__ __attribute__((aligned(16))) float sQ[RW * (D + 8)];                 // FOLD: scales; cross-attention query, later:
+  __shared__ __attribute__((aligned(16))) float sQ[FOLD16 && !FFN ? 4 : RW * (D + 8)];  // FOLD32: scales; cross-attention query, later:
   _Float16 *sU = (_Float16 *)sQ;                                                  // FFN hidden state, head rows, then tail rows
   __shared__ float sPart[WR > 1 ? RW * (PARTS - PW) * (NE + 2) * 64 : 1];         // partial softmaxes of the waves pg > 0
   constexpr int NV = FFN ? 6 : 4, LN2 = 0, LN3 = 2, LNF = NV - 2;  // vectors of the normalisations
-  __shared__ __attribute__((aligned(16))) float sNorm[NV * D];
+  constexpr int NVT = NV + (FOLD16 ? 4 : 0), NVW = (NVT + NWAVES - 1) / NWAVES;  // FOLD16: and scale and constant of either context
+  __shared__ __attribute__((aligned(16))) float sNorm[NVT * D];
   __shared__ float sRel[HEADS ? RW * (D1_MAX_CLIP + 1) * 8 : 1];                  // per row: [distance][head]
   const int tid = threadIdx.x, lane = tid & 63, h = lane >> 4, c16 = lane & 15;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -517,10 +535,17 @@ __global__ __launch_bounds__(NWAVES * 64) void dec1_kernel(Dec1Args a) {
   if (a.table.rows) token.request(a, row0 + rw, lane);
   // the normalisations' gains and offsets go to the LDS while the start of the row travels, a vector per wave: read where they are used,
   // each would be another turn of the memory system in the row's chain
-  float norm[NE];
-  const GemmLayerNorm &norm_of = wave < 2 ? a.ln2 : FFN && wave < 4 ? a.ln3 : a.lnf;
-  const float *norm_src = wave >= NV ? nullptr : wave & 1 ? norm_of.beta : norm_of.gamma;  // (no final one: nullptr)
-  if (norm_src) d1_load<NE>(norm_src + lane * NE, norm);
+  float norm[NVW][NE];
+  const float *norm_src[NVW];
+#pragma unroll
+  for (int u = 0; u < NVW; u++) {
+    const int i = wave + u * NWAVES;
+    const GemmLayerNorm &of = i < 2 ? a.ln2 : FFN && i < 4 ? a.ln3 : a.lnf;
+    norm_src[u] = i < NV ? (i & 1 ? of.beta : of.gamma) : nullptr;  // (no final one: nullptr)
+    if (FOLD16 && i >= NV)
+      norm_src[u] = i == NV ? a.fold_scale : i == NV + 1 ? a.bo_self : i == NV + 2 ? a.cross_scale : i == NV + 3 ? a.bo_cross : nullptr;
+    if (norm_src[u]) d1_load<NE>(norm_src[u] + lane * NE, norm[u]);
+  }
   const int r = valid ? row0 + rw : 0;
   int rc = r;
   if (IND) rc = valid ? a.origin[r] : -1;
@@ -641,7 +666,7 @@ __global__ __launch_bounds__(NWAVES * 64) void dec1_kernel(Dec1Args a) {
     if (j_first + which * STEP < n) b.load(kv, sc, pos0, j_first + which * STEP, n, lane);
   };
   auto attend = [&](auto (&b)[2], auto preloaded, const float (&q)[NE], const void *kv, const float *sc, long pos0, int n, const D1Rel &rel, Part (&st)[PW], auto done) {
-    if constexpr (NWAVES == 16) {  // 128 registers: one block at a time
+    if constexpr (NWAVES == 16 && AHEAD == 0) {  // 128 registers: one block at a time
       for (int j = j_first; j < n; j += STEP)
 #pragma unroll
         for (int u = 0; u < PW; u++)
@@ -702,7 +727,7 @@ __global__ __launch_bounds__(NWAVES * 64) void dec1_kernel(Dec1Args a) {
       for (int e = 0; e < NE; e++) ctx[e] = t.acc[e] * inv;
       done(ctx);
     }
-    __syncthreads();
+    if (!ALONE) __syncthreads();
   };
 
   // ---- self-attention ----
@@ -713,10 +738,10 @@ __global__ __launch_bounds__(NWAVES * 64) void dec1_kernel(Dec1Args a) {
   CrossBlock cb[2];
   const long cross0 = (long)rc * a.cross_positions, self0 = (long)rc * a.self_positions;
   const int n_cached = n_self > 0 ? n_self - 1 : 0;
-  if constexpr (FOLD) {  // the first blocks of both caches depend on nothing computed here
-    first_block(sb[0], 0, a.self_kv, a.self_sc, self0, n_cached);
-    first_block(cb[0], 0, a.cross_kv, a.cross_sc, cross0, n_cross);
-  }
+  // the first blocks of both caches depend on nothing computed here
+  if constexpr (AHEAD == 2) first_block(sb[0], 0, a.self_kv, a.self_sc, self0, n_cached);
+  if constexpr (AHEAD == 2) first_block(cb[0], 0, a.cross_kv, a.cross_sc, cross0, n_cross);
+
   float q[NE], z[NE], kx[NE], vx[NE];  // z, kx, vx: the row's first wave
   if (a.table.rows) {
     const int y = token.resolve(a, row0 + rw, pg == 0, lane);
@@ -730,17 +755,20 @@ __global__ __launch_bounds__(NWAVES * 64) void dec1_kernel(Dec1Args a) {
       d1_load<NE>(a.kv_new + (long)r * 2 * D + D + lane * NE, vx);
     }
   }
-  if (norm_src) {
 #pragma unroll
-    for (int e = 0; e < NE; e += 4) *(float4 *)(sNorm + wave * D + lane * NE + e) = make_float4(norm[e], norm[e + 1], norm[e + 2], norm[e + 3]);
-  }
-  if constexpr (FOLD) {  // the second ones when the start no longer needs its registers: with two waves on a SIMD it makes way for others
+  for (int u = 0; u < NVW; u++)
+    if (norm_src[u]) {
+#pragma unroll
+      for (int e = 0; e < NE; e += 4)
+        *(float4 *)(sNorm + (wave + u * NWAVES) * D + lane * NE + e) = make_float4(norm[u][e], norm[u][e + 1], norm[u][e + 2], norm[u][e + 3]);
+    }
+  if constexpr (AHEAD > 0) {  // the second ones when the start no longer needs its registers: with two waves on a SIMD it makes way for others
     __builtin_amdgcn_sched_barrier(0);
-    first_block(sb[1], 1, a.self_kv, a.self_sc, self0, n_cached);
-    first_block(cb[1], 1, a.cross_kv, a.cross_sc, cross0, n_cross);
+    first_block(sb[AHEAD == 2], AHEAD == 2, a.self_kv, a.self_sc, self0, n_cached);
+    if constexpr (AHEAD == 2) first_block(cb[1], 1, a.cross_kv, a.cross_sc, cross0, n_cross);
   }
   if (pg == 0) {
-    if constexpr (FOLD) {  // the bias of the self-attention's output, which no projection adds, and the values' column scales
+    if constexpr (FOLD32) {  // the bias of the self-attention's output, which no projection adds, and the values' column scales
       float b[NE], c[NE];
       d1_load<NE>(a.bo_self + lane * NE, b);
       d1_load<NE>(a.fold_scale + lane * NE, c);
@@ -752,12 +780,26 @@ __global__ __launch_bounds__(NWAVES * 64) void dec1_kernel(Dec1Args a) {
 #pragma unroll
     for (int e = 0; e < NE; e += 4) *(float4 *)(sZ + rw * ZLD + lane * NE + e) = make_float4(z[e], z[e + 1], z[e + 2], z[e + 3]);
   }
+  if constexpr (ALONE) __syncthreads();  // the vectors
+  // folded contexts, column by column times its scale, and their constants
+  auto add_scaled = [&](const float (&ctx)[NE], int which) {
+    float z[NE], c[NE], b[NE];
+    d1_load<NE>(sZ + rw * ZLD + lane * NE, z);
+    d1_load<NE>(sNorm + which * D + lane * NE, c);
+    d1_load<NE>(sNorm + (which + 1) * D + lane * NE, b);
+#pragma unroll
+    for (int e = 0; e < NE; e++) z[e] += ctx[e] * c[e] + b[e];
+#pragma unroll
+    for (int e = 0; e < NE; e += 4) *(float4 *)(sZ + rw * ZLD + lane * NE + e) = make_float4(z[e], z[e + 1], z[e + 2], z[e + 3]);
+  };
   auto add_context = [&](const float (&ctx)[NE]) {
+    if constexpr (FOLD16) return add_scaled(ctx, NV + 2);
     float *z = sZ + rw * ZLD + lane * NE;
 #pragma unroll
     for (int e = 0; e < NE; e++) z[e] += ctx[e];
   };
   auto add_self_context = [&](const float (&ctx)[NE]) {
+    if constexpr (FOLD16) return add_scaled(ctx, NV);
     float *z = sZ + rw * ZLD + lane * NE;
 #pragma unroll
     for (int e = 0; e < NE; e++) z[e] += ctx[e] * sQ[rw * ZLD + lane * NE + e];
@@ -803,7 +845,11 @@ __global__ __launch_bounds__(NWAVES * 64) void dec1_kernel(Dec1Args a) {
         d1_quantize_store<NE>(vx, dst + D, a.self_sc + p * 2 + 1, lane);
       }
     }
-    if constexpr (FOLD) attend(sb, std::integral_constant<int, 2>{}, q, a.self_kv, a.self_sc, self0, n_cached, rel, st, add_self_context);
+    if constexpr (AHEAD == 1) {
+      __builtin_amdgcn_sched_barrier(0);
+      first_block(sb[1], 1, a.self_kv, a.self_sc, self0, n_cached);
+    }
+    if constexpr (FOLD) attend(sb, std::integral_constant<int, AHEAD ? 2 : 0>{}, q, a.self_kv, a.self_sc, self0, n_cached, rel, st, add_self_context);
     else attend(sb, std::integral_constant<int, 0>{}, q, a.self_kv, a.self_sc, self0, n_cached, rel, st, store_planes);
   }
   // ---- output projection + residual, LayerNorm, cross-attention query ----
@@ -817,12 +863,18 @@ __global__ __launch_bounds__(NWAVES * 64) void dec1_kernel(Dec1Args a) {
   }
   if constexpr (FOLD) {
     // ---- cross-attention over the folded cache: the normalised row is the query, the context adds to the residual ----
+    if constexpr (AHEAD == 1) {
+      __builtin_amdgcn_sched_barrier(0);
+      first_block(cb[0], 0, a.cross_kv, a.cross_sc, cross0, n_cross);
+      first_block(cb[1], 1, a.cross_kv, a.cross_sc, cross0, n_cross);
+    }
     normalise(LN2, q);
-    if (FFN) preload(a.W1);
+    if (FFN && EARLY) preload(a.W1);
     Part st[PW];
 #pragma unroll
     for (int u = 0; u < PW; u++) st[u].clear();
-    attend(cb, std::integral_constant<int, 2>{}, q, a.cross_kv, a.cross_sc, cross0, n_cross, D1Rel{}, st, add_context);
+    attend(cb, std::integral_constant<int, AHEAD ? 2 : 0>{}, q, a.cross_kv, a.cross_sc, cross0, n_cross, D1Rel{}, st, add_context);
+    if (FFN && !EARLY) preload(a.W1);
   } else {
     {
       float y[NE];
@@ -915,13 +967,32 @@ static hipError_t d1_launch(const Dec1Args &a, hipStream_t s) {
   // from 257 on.
   const int shape = a.shape_rows > 0 ? a.shape_rows : a.rows;
   const int rows = a.table.rows && !a.tok_in ? std::max(a.rows, a.sb.rows_prev) : a.rows;  // those that only collect a token, too
-#define NT_D1(RW_, NW_, P_, F_)                                                                                          \
-  do {                                                                                                                  \
-    const dim3 grid((unsigned)((rows + RW_ - 1) / RW_));                                                                \
-    if (a.origin) hipLaunchKernelGGL((dec1_kernel<D, RW_, NW_, P_, true, FFN, F_, HEADS>), grid, dim3(64 * NW_), 0, s, a);     \
-    else hipLaunchKernelGGL((dec1_kernel<D, RW_, NW_, P_, false, FFN, F_, HEADS>), grid, dim3(64 * NW_), 0, s, a);             \
+#define NT_D1F(RW_, NW_, P_, F16_, F32_)                                                                                  \
+  do {                                                                                                                   \
+    const dim3 grid((unsigned)((rows + RW_ - 1) / RW_));                                                                 \
+    if (a.origin) hipLaunchKernelGGL((dec1_kernel<D, RW_, NW_, P_, F16_, true, FFN, F32_, HEADS>), grid, dim3(64 * NW_), 0, s, a); \
+    else hipLaunchKernelGGL((dec1_kernel<D, RW_, NW_, P_, F16_, false, FFN, F32_, HEADS>), grid, dim3(64 * NW_), 0, s, a);         \
   } while (0)
+#define NT_D1(RW_, NW_, P_, F32_) NT_D1F(RW_, NW_, P_, 0, F32_)
   if constexpr (!HEADS) {
+    if (a.folded == 2) {
+      // Integer folded caches.  1,024 rows and more: a wave per row, sixteen rows per workgroup, which fills half of the chip's CUs and
+      // leaves the other lanes' kernels the rest (2,000 rows of 27 tokens / 1,100 of 40 alone 40 / 39 us; four or eight rows of a wave each 34 /
+      // 30 to 32, two rows of four waves 56 / 40; 200,000 sentences at 65,536 tokens 430 ms, 432 to 446 and 495).  Fewer rows: two waves each,
+      // and four up to 520 (900 rows of 40, 620 of 55, 520 of 100, 300 of 130, 180 of 190 tokens: 25 / 28 / 39 / 34 / 38 us with two, 31 /
+      // 31 / 40 / 28 / 27 with four).  With an FFN, whose matrices every workgroup pulls: sixteen rows, four (900 rows of 40 / 560 of 60:
+      // 39 / 40 us, with eight 44 / 48, with two 52 / 56), two up to 520 (480 rows of 90, 320 of 150: 40 / 44 us, with four 45 / 56).
+      if constexpr (FFN) {
+        if (shape >= 1024) NT_D1F(16, 16, 1, 1, false);
+        else if (shape > 520) NT_D1F(4, 16, 4, 1, false);
+        else NT_D1F(2, 8, 4, 1, false);
+      } else {
+        if (shape >= 1024) NT_D1F(16, 16, 1, 1, false);
+        else if (shape > 520) NT_D1F(2, 4, 2, 1, false);
+        else NT_D1F(1, 4, 4, 1, false);
+      }
+      return hipGetLastError();
+    }
     if (a.folded) {
       // one row per workgroup has 267 registers and a CU to itself; two rows have 256 (17 spilled) and still four waves each, so that
       // more than 256 rows are one round (a step of 250 / 300 / 400 / 511 rows alone: 31.8 / 40.3 / 41.9 / 45.3 us and 32.4 / 36.1 / 37.9 / 41.6;
@@ -945,6 +1016,7 @@ static hipError_t d1_launch(const Dec1Args &a, hipStream_t s) {
     NT_D1(8, 16, 4, false);
   }
 #undef NT_D1
+#undef NT_D1F
   return hipGetLastError();
 }
 

@@ -226,12 +226,14 @@ struct nt_model {
   // bit 1: attention context -> output projection, bit 2: final LayerNorm -> cross K|V, bit 3: the FFN's first matrix;
   // with bit 0 clear, bits 4 / 5 / 6: the q / k / v columns of Q|K|V alone; bit 7: q and k stored as plain fp16)
   unsigned enc_tails = kEncTailsAll;
-  // One-layer decoders: small batches additionally keep the cross cache multiplied by the query and output matrices, in fp32,
-  // and their self values are computed with the output matrix already in them (nt_dec1.hip): per decoder layer [fold_positions, 2d] and one constant per key; folded says whether the encoded batch has it
+  // One-layer decoders: the self values are computed with the output matrix already in them, and the cross cache is multiplied by the
+  // query and output matrices (nt_dec1.hip): in fp32 for small batches (folded == 1; per decoder layer [fold_positions, 2d] and one
+  // constant per key, beside the cache they are made from), as integers for larger ones (2); what the encoded batch has is in folded
   std::vector<float *> cross_fold, fold_const;
   int64_t fold_positions = 0;
-  bool folded = false;
-  std::vector<float *> cross_sc, self_sc;  // per decoder layer [Mt,2] / [self_positions,2] scales
+  int folded = 0;
+  nt::CrossFold fold{};
+  std::vector<float *> cross_sc, self_sc;  // per decoder layer [Mt,2] ([Mt,4] where it can be folded) / [self_positions,2] scales
   float *z = nullptr, *a32 = nullptr, *q32 = nullptr, *ctx32 = nullptr, *u32 = nullptr;  // [Br, d|F]
   unsigned long long *pk = nullptr;
   float *ps = nullptr, *lo_norm = nullptr;             // certified arg-max: runner-up partials, tail norms
@@ -398,7 +400,7 @@ int alloc_lane_state(nt_model *m, hipStream_t s) {
   std::vector<size_t> o_cross(cfg->n_dec), o_self(cfg->n_dec), o_cross_sc(cfg->n_dec), o_self_sc(cfg->n_dec);
   for (int l = 0; l < cfg->n_dec; l++) o_cross[l] = cv.take((size_t)Mt * 2 * d * (m->kv_i16 ? 2 : kCrossElt));
   for (int l = 0; l < cfg->n_dec; l++) o_self[l] = cv.take((size_t)m->self_positions * 2 * d * (m->kv_i16 ? 2 : 4));
-  for (int l = 0; l < cfg->n_dec; l++) o_cross_sc[l] = cv.take(m->kv_i16 ? (size_t)Mt * 2 * 4 : 16);
+  for (int l = 0; l < cfg->n_dec; l++) o_cross_sc[l] = cv.take(m->kv_i16 ? (size_t)Mt * (cfg->n_dec == 1 ? 4 : 2) * 4 : 16);
   for (int l = 0; l < cfg->n_dec; l++) o_self_sc[l] = cv.take(m->kv_i16 ? (size_t)m->self_positions * 2 * 4 : 16);
   const size_t o_z = cv.take((size_t)Br * d * 4), o_a32 = cv.take((size_t)Br * d * 4), o_q32 = cv.take((size_t)Br * d * 4),
                o_ctx32 = cv.take((size_t)Br * d * 4), o_u32 = cv.take((size_t)Br * std::max(Fd, 1) * 4),
@@ -643,7 +645,11 @@ int nt_load_weights(const nt_config *cfg, const void *h_blob_fp16, size_t blob_b
   const bool fold_dec = m->kv_i16 && cfg->n_dec == 1;
   // The first decoder layer's Q | K | V comes from a table (Dec1Table); what it is made of: matrix [d][parts d] and bias, in double
   const bool tabled = m->kv_i16 || (!kCrossF32 && nt::dec1_heads_supported(d, dec_heads(cfg)));
-  const int parts = tabled ? (fold_dec ? 4 : 3) : 0;
+  // Larger batches fold their caches, too (CrossFold), but not before the 8-bit output layer: that the integers then round other vectors
+  // moves a state by 2e-5, one of its codes every few steps, and 0.9 % of the tokens of 25-token sentences (all near-ties; 0.05 % with
+  // the fp16 output layer).  So such a model's table has both forms of the value.
+  const bool fold_all = fold_dec && !cfg->q8_output;
+  const int parts = !tabled ? 0 : fold_dec && !fold_all ? 4 : 3;
   std::vector<double> tabW((size_t)d * parts * d), tabB((size_t)parts * d);
   auto put_attn = [&](Attn &a, bool cross, bool rpr, int dh, bool fold = false, bool table = false) {
     const _Float16 *W[4], *b[4];
@@ -663,7 +669,7 @@ int nt_load_weights(const nt_config *cfg, const void *h_blob_fp16, size_t blob_b
     };
     if (table) {
       const double qscale = (double)(1.0f / std::sqrt((float)dh));
-      for (int p = 0; p < 3; p++)
+      for (int p = 0; p < (fold && parts == 3 ? 2 : 3); p++)  // (folded values: below)
         for (int j = 0; j < d; j++) {
           for (int k = 0; k < d; k++)
             tabW[((size_t)k * parts + p) * d + j] = (double)(float)W[p][(int64_t)k * d + j] * (p == 0 ? qscale : 1.0);
@@ -697,7 +703,7 @@ int nt_load_weights(const nt_config *cfg, const void *h_blob_fp16, size_t blob_b
       for (int j = 0; j < d; j++)
         if (norm2[(size_t)j] > 0.0) scale[(size_t)j] = (double)(float)std::sqrt(norm2[(size_t)j]);
       for (int i = 0; i < d; i++)
-        for (int j = 0; j < d; j++) tabW[((size_t)i * parts + 3) * d + j] = prod[(size_t)i * d + j] / scale[(size_t)j];
+        for (int j = 0; j < d; j++) tabW[((size_t)i * parts + parts - 1) * d + j] = prod[(size_t)i * d + j] / scale[(size_t)j];
       const size_t ob = pk.reserve((size_t)d * 4);
       for (int j = 0; j < d; j++) ((float *)(pk.img.data() + ob))[j] = (float)bias[(size_t)j];
       fixes.push_back({ob, (const void **)&a.bvo});
@@ -773,6 +779,7 @@ int nt_load_weights(const nt_config *cfg, const void *h_blob_fp16, size_t blob_b
       }
     fixes.push_back({o, (const void **)&m->pe});
   }
+  const size_t o_fold = fold_all ? pk.reserve(nt::cross_fold_bytes(d)) : 0;
   m->w_bytes = pk.img.size();
   if (hipMalloc((void **)&m->d_w, m->w_bytes) != hipSuccess) return fail(NT_ENOMEM, "hipMalloc of %zu weight bytes failed", m->w_bytes);
   HIP_TRY(hipMemcpyAsync(m->d_w, pk.img.data(), m->w_bytes, hipMemcpyHostToDevice, s));
@@ -792,6 +799,13 @@ int nt_load_weights(const nt_config *cfg, const void *h_blob_fp16, size_t blob_b
     HIP_TRY(nt::launch_dec1_table(m->E, m->pe, m->dec[0].ln1.g, m->dec[0].ln1.b, (const double *)tab.p, (const double *)((char *)tab.p + wb), V,
                                   cfg->max_len, d, parts, m->d_table, s));
     m->dec_table = nt::Dec1Table{m->d_table, parts, cfg->max_len};
+  }
+  if (fold_all) {
+    const DecLayer &L = m->dec[0];
+    const nt::CrossFoldWeights w{L.cross.Wkv, L.cross.Wq, L.cross.Wo, L.cross.bkv, L.cross.bq, L.cross.bo, m->enc_final.g, m->enc_final.b,
+                                 L.ln2.g, L.ln2.b, 1.0f / std::sqrt((float)d)};
+    HIP_TRY(nt::cross_fold_build(w, d, m->d_w + o_fold, s));
+    m->fold = nt::cross_fold_at(m->d_w + o_fold, d);
   }
   m->vw.Wt = m->Wout; m->vw.Wp = m->Wout_frag; m->vw.N = V; m->vw.K = d;
   if (m->Wout_frag && !cfg->q8_output) {
@@ -943,10 +957,14 @@ int nt_encode(nt_model *m, const int32_t *d_src, const int32_t *d_len, int32_t B
   if (!all_fused)
     KT(K_LN_ENC, Md * dd * (4 + ea), 8 * Md * dd,
        nt::launch_layer_norm(m->x, M, d, m->enc_final.g, m->enc_final.b, lne, m->enc_out, ln_mode, lo_d, s));
-  m->folded = m->kv_i16 && c.n_dec == 1 && B <= nt::kDec1FoldRows &&
-              M <= std::min<int64_t>(nt::kDec1FoldTokens, m->fold_positions);
+  m->folded = !m->kv_i16 || c.n_dec != 1 ? 0 : B <= nt::kDec1FoldRows && M <= std::min<int64_t>(nt::kDec1FoldTokens, m->fold_positions) ? 1 : m->fold.W ? 2 : 0;
   const float dec_qscale = 1.0f / std::sqrt((float)(d / dec_heads(&c)));
   for (int l = 0; l < c.n_dec; l++) {
+    if (m->folded == 2) {
+      KT(K_GEMM_CROSS_KV, Md * dd * 8 + 8 * dd * dd, 4 * Md * dd * dd,
+         nt::launch_cross_fold(m->x, M, d, lne, m->fold, (m->enc_tails & 4u) != 0, (short *)m->cross[l], m->cross_sc[l], s));
+      continue;
+    }
     nt::GemmEpilogue e;
     e.bias = m->dec[l].cross.bkv; e.dst0 = m->cross[l]; e.ld0 = 2 * d; e.n_split = 2 * d;
     // integer caches: the projection leaves fp32 keys | values in the (now free) q|k|v buffer, a row kernel then finds
@@ -963,8 +981,8 @@ int nt_encode(nt_model *m, const int32_t *d_src, const int32_t *d_len, int32_t B
     if (m->kv_i16) {
       const nt::KvPlanes pl{(_Float16 *)m->ctx_enc, (_Float16 *)m->a_enc, lo_d, m->dec[l].cross.bq, dec_qscale, m->fold_const[l]};
       KT(K_KV_QUANT, Md * 2 * dd * 6, Md * 2 * dd * 4,
-         nt::launch_quantize_kv_i16((const float *)m->qkv, M, d, (short *)m->cross[l], m->cross_sc[l], m->folded ? &pl : nullptr, s));
-      if (m->folded) {  // keys times the query matrix (and its scale), values times the output matrix (and its bias)
+         nt::launch_quantize_kv_i16((const float *)m->qkv, M, d, (short *)m->cross[l], m->cross_sc[l], m->folded == 1 ? &pl : nullptr, s));
+      if (m->folded == 1) {  // keys times the query matrix (and its scale), values times the output matrix (and its bias)
         nt::GemmEpilogue k, v;
         k.scale = dec_qscale; k.scale_cols = d; k.dst0 = m->cross_fold[l]; k.ld0 = 2 * d; k.n_split = d;
         v.bias = m->dec[l].cross.bo; v.dst0 = m->cross_fold[l] + d; v.ld0 = 2 * d; v.n_split = d;
@@ -1183,9 +1201,13 @@ int decode_step(nt_model *m, DecodeCursor &cu, hipStream_t s) {
           at.self_positions = T; at.n_keys = t + 1; at.heads = heads_layer ? H : 1; at.rk = L.self.rk; at.clip = c.rpr_clip;
           at.Wo_self = L.self.Wo_p; at.bo_self = m->folded ? L.self.bvo : L.self.bo; at.fold_scale = L.self.vo_scale; at.Wq = L.cross.Wq_p; at.bq = L.cross.bq; at.Wo_cross = L.cross.Wo_p;
           at.bo_cross = L.cross.bo; at.q_scale = qscale; at.ln2 = nt::GemmLayerNorm{L.ln2.g, L.ln2.b, lne};
+          if (m->folded == 2) {
+            at.ln2 = nt::GemmLayerNorm{m->fold.gamma2, m->fold.beta2, lne};
+            at.bo_cross = m->fold.value_const; at.cross_scale = m->fold.value_scale;
+          }
           at.folded = m->folded; at.cross_positions = S; at.len = m->len;
-          at.cross_kv = m->folded ? (const void *)m->cross_fold[l] : m->cross[l];
-          at.cross_sc = m->folded ? m->fold_const[l] : m->cross_sc[l];
+          at.cross_kv = m->folded == 1 ? (const void *)m->cross_fold[l] : m->cross[l];
+          at.cross_sc = m->folded == 1 ? m->fold_const[l] : m->cross_sc[l];
           if (ffn_inside) {
             at.ln3 = nt::GemmLayerNorm{L.ln3.g, L.ln3.b, lne}; at.W1 = L.ffn.W1_p; at.b1 = L.ffn.b1; at.W2 = L.ffn.W2_p; at.b2 = L.ffn.b2;
           }

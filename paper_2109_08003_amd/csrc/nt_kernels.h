@@ -530,8 +530,8 @@ bool dec1_heads_supported(int d, int heads);
 // the row once its scale r is known: with c(v) = v - mean(v),
 //   q|k|v = r (sqrt(d) (gamma c(E[y])) W + (gamma c(PE[t])) W) + (beta W + b).
 // The three products are formed at load, in double, and kept in fp32: rows 0 .. vocab - 1 by token, then max_len rows by
-// position, then beta W + b.  A row has `parts` groups of d columns: scaled query, key, value, and (folded batches,
-// parts == 4) the value multiplied by the output matrix with its columns scaled.
+// position, then beta W + b.  A row has `parts` groups of d columns: scaled query, key, value, and, last, for folded batches the
+// value multiplied by the output matrix with its columns scaled (three where all batches are folded, or none; else four).
 struct Dec1Table {
   const float *rows;  // nullptr: no table
   int parts, max_len;
@@ -567,13 +567,15 @@ struct Dec1Args {
   const float *bo_self, *bq, *bo_cross;
   float q_scale;
   GemmLayerNorm ln2;
-  const void *cross_kv;  // integers with scales in cross_sc, or (folded) fp32 [position][2 d] with one constant per key in
+  const void *cross_kv;  // integers with scales in cross_sc, or (folded == 1) fp32 [position][2 d] with one constant per key in
   const float *cross_sc; // cross_sc: keys multiplied by the query matrix and scale, values by the output matrix (+ bias)
   // folded: the self values (kv_new, self cache) then are already multiplied by the output matrix, too, column j divided by
   // fold_scale[j]; bo_self is the whole constant, b_v W_o + b_o.  Neither a bias nor the columns' different sizes may enter the
-  // cache: its integers have one scale per vector, which the largest element sets for all
+  // cache: its integers have one scale per vector, which the largest element sets for all.
+  // folded == 2: the cross cache as integers of the products (CrossFold; {key scale, value scale, key's constant, unused} per
+  // position in cross_sc); ln2 is CrossFold's, bo_cross and cross_scale its value_const and value_scale
   int folded;
-  const float *fold_scale;
+  const float *fold_scale, *cross_scale;
   long cross_positions;
   const int32_t *len;    // keys of each cache row
   // FFN of width d (W1 == nullptr: none, or not part of this launch)
@@ -589,6 +591,25 @@ struct Dec1Args {
 };
 hipError_t launch_dec1(const Dec1Args &a, int d, hipStream_t s);
 constexpr int kDec1FoldRows = 512, kDec1FoldTokens = 32768;
+// What larger batches of one-layer one-head decoders fold (nt_cross_fold.hip): the encoder's final normalisation without gain and offset
+// times [gain (Wk Wq^T) | gain (Wv Wo)], each column divided by its size, and what that leaves for the decoder.
+struct CrossFold {
+  const _Float16 *W;                      // the matrix as head and tail planes in fragment order
+  const float *u;                         // [d]: a key's constant is its row . u
+  const float *gamma2, *beta2;            // [d]: normalisation before the cross-attention, times the key columns' sizes
+  const float *value_scale, *value_const; // [d]: sizes of the value columns; b_v Wo + b_o with the encoder's offset in it
+};
+size_t cross_fold_bytes(int d);
+CrossFold cross_fold_at(void *dst, int d);
+// dst [cross_fold_bytes] <- the matrices ([out][in], as the projections have them), all on the device; returns when it is done (load time)
+struct CrossFoldWeights {
+  const _Float16 *Wkv, *Wq, *Wo;
+  const float *bkv, *bq, *bo, *enc_gamma, *enc_beta, *gamma2, *beta2;
+  float q_scale;
+};
+hipError_t cross_fold_build(const CrossFoldWeights &w, int d, void *dst, hipStream_t s);
+// x [M][d]: the encoder's residual stream -> codes [M][2][d], sc [M][4] (see Dec1Args).  tail: the normalised rows keep head + tail.
+hipError_t launch_cross_fold(const float *x, int M, int d, LnEps eps, const CrossFold &f, bool tail, short *cache, float *sc, hipStream_t s);
 // x [M][2 d] fp32 (key | value of M positions) -> codes [M][2][d] and scales [M][2]; planes (optional): the rounded
 // vectors as head / tail planes [M][d] (tail lo_offset elements after the head) and key_const[m] = scale * (u . key)
 struct KvPlanes {

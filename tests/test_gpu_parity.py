@@ -1316,3 +1316,80 @@ def test_batches_at_the_line_of_the_folded_caches(nt, oracle, torch_cuda, rows, 
     print(f"{rows} x {S}: {err:.1e}")
     assert err <= 1.5e-4
     gm.close()
+
+
+@pytest.mark.parametrize("d,rows,S,tails", [(512, 513, 1, 15), (512, 520, 5, 11), (512, 521, 16, 11), (512, 1023, 8, 15), (512, 1030, 8, 11),
+                                            (512, 1024, 17, 15), (512, 300, 110, 11), (256, 513, 3, 11), (256, 1100, 9, 11),
+                                            (256, 520, 20, 15), (256, 170, 200, 11)])
+def test_integer_folded_caches(nt, oracle, torch_cuda, d, rows, S, tails):
+    """Batches beyond the fp32 folded caches' lines: row counts around the forms of the decoder layer, token counts around the tiles of
+    32 and 64 rows (8,192 tokens) and the line of 128 tiles, with and without the tail plane of the encoder's rows: logits of the
+    first, last and middle rows over five steps against the oracle.  Bound: as for batches at the line of the folded caches, 1.5e-4;
+    without the tail a row's elements are off by 2^-11 / sqrt(12) = 1.4e-4, and so are its key and its value: 4e-4."""
+    torch = torch_cuda
+    cfg = nt_synth.model_config("C1", d_model=d, vocab=300, n_enc=1)
+    blob = nt_synth.make_weights(cfg, seed=22, random_affine=True)
+    gm, om = nt.Model(cfg, blob, max_batch_tokens=36000, pipeline_lanes=1), oracle.Model(cfg, blob)
+    gm.debug_set_encoder_tails(tails)
+    rng = np.random.default_rng(rows + S)
+    lens = np.sort(np.concatenate([[S, S], rng.integers(1, S + 1, size=rows - 3), [1]]))[::-1]
+    lens = np.concatenate([lens[:-1], [S]])          # the last row reaches the batch's last position
+    src = [rng.integers(4, 300, size=n).astype(np.int32) for n in lens]
+    tgt = rng.integers(4, 300, size=(rows, 5)).astype(np.int32)
+    ids, ln = pad(src, cfg["pad_id"])
+    gm.encode(torch.from_numpy(ids).cuda(), torch.from_numpy(ln).cuda())
+    logits = torch.empty(rows, 5, 300, dtype=torch.float32, device="cuda")
+    gm.debug_teacher_forced_logits(torch.from_numpy(tgt).cuda(), logits)
+    gm.check_device_flags()
+    logits = logits.cpu().numpy().astype(np.float64)
+    err = max(rel_l2(logits[i], om.teacher_forced(src[i], tgt[i])) for i in (0, 1, rows // 2, rows - 2, rows - 1))
+    print(f"d {d}, {rows} x {S}, tails {tails}: {err:.1e}")
+    assert err <= (1.5e-4 if tails & 4 else 4e-4)
+    gm.close()
+
+
+@pytest.mark.parametrize("ffn", [0, 512])
+@pytest.mark.parametrize("what", ["plain", "encoder offset", "encoder gain", "query gain", "query columns", "value columns", "biases"])
+def test_integer_folded_cross_caches_are_as_exact_as_the_others(nt, oracle, torch_cuda, what, ffn):
+    """A few large elements on either side of the folded products must not cost the other elements of a key or value their precision:
+    the state after a step (the identity as output matrix shows it) has, at 600 rows (integers of the products), at most 1.3 times the
+    error that it has at 60 (integers of the factors, products in fp32) and no more than 4e-5 (see above; the outputs left out are the
+    large ones).  1.3: the two are other roundings of the same 16 bits."""
+    torch = torch_cuda
+    d = 512
+    cfg = nt_synth.model_config("C1", vocab=d, n_enc=1, max_len=64, dec_d_ffn=ffn or -1)
+    blob = nt_synth.make_weights(cfg, seed=14, random_affine=True)
+    view = lambda name: nt_synth.blob_view(cfg, blob, name)
+    view("W_out")[:] = np.eye(d)
+    large = np.arange(0, d, 64)
+    if what == "encoder offset":
+        view("enc_final.b")[large] = 25
+    if what == "encoder gain":
+        view("enc_final.g")[large] *= np.float16(16)
+    if what == "query gain":
+        view("dec0.ln2.g")[large] *= np.float16(16)
+    if what == "query columns":
+        view("dec0.cross.Wq")[large] *= np.float16(8)
+    if what == "value columns":
+        view("dec0.cross.Wo")[:, large] *= np.float16(16)
+    if what == "biases":
+        view("dec0.cross.bq")[large], view("dec0.cross.bk")[large], view("dec0.cross.bv")[large], view("dec0.cross.bo")[large] = 4, 4, 8, 16
+    gm, om = nt.Model(cfg, blob, max_batch_tokens=8192, pipeline_lanes=1), oracle.Model(cfg, blob)
+    gm.debug_set_encoder_tails(15)
+    rng = np.random.default_rng(4)
+    src = [rng.integers(4, d, size=11).astype(np.int32) for _ in range(600)]
+    T = 3
+    tgt = rng.integers(4, d, size=(600, T)).astype(np.int32)
+    want = np.stack([om.teacher_forced(x, t) for x, t in zip(src, tgt)])
+    rest = np.setdiff1d(np.arange(d), large)
+    rms = {}
+    for rows in (60, 600):
+        ids, lens = pad(src[:rows], cfg["pad_id"])
+        gm.encode(torch.from_numpy(ids).cuda(), torch.from_numpy(lens).cuda())
+        logits = torch.empty(rows, T, d, dtype=torch.float32, device="cuda")
+        gm.debug_teacher_forced_logits(torch.from_numpy(tgt[:rows].copy()).cuda(), logits)
+        err, ref = (logits.cpu().numpy() - want[:rows])[:, :, rest], want[:rows][:, :, rest]
+        rms[rows] = float(np.sqrt((err ** 2).mean() / (ref ** 2).mean()))
+    print(f"{what}, ffn {ffn}: 60 rows {rms[60]:.1e}, 600 rows {rms[600]:.1e}")
+    assert rms[600] <= min(1.3 * rms[60], 4e-5)
+    gm.close()
