@@ -42,10 +42,18 @@
 // the context's norm instead of 2.5e-6 / 2.7e-5).  Batches of up to kDec1FoldRows rows: the cross products are formed from the rounded
 // (integer) vectors, so nothing is rounded that was not before, and kept in fp32: twice the bytes (a 4,096-token budget, batches of 36 to 341 rows: 27.5 ms folded up to 256 rows, 26.7 up to
 // 512; batches alone on the chip, 300 / 450 rows of 35 padded tokens: 3.14 -> 2.74 / 3.89 -> 3.52 ms folded; 320 rows of 180:
-// 24.0 ms with, 23.9 without, which puts the line for kDec1FoldTokens below that).  What is left is latency: a row per workgroup of four waves, the
-// first cross keys requested before the self-attention.  One row 20.6 us without folding, 12.8 with the cross cache folded,
+// 24.0 ms with, 23.9 without, which puts the line for kDec1FoldTokens below that).  What is left is latency: a row per workgroup of four or eight waves.  One row 20.6 us without folding, 12.8 with the cross cache folded,
 // 45 rows 26 and 17.8; with the self values too, one sentence 1119 -> 1012 us, 45 sentences 3742 -> 3207 us, 8 sentences of
 // the 256-wide model 1253 -> 1175 us, a 4,096-token budget 28.0 -> 27.5 ms (each with the projection as a launch of its own).
+//
+// A folded row's time is its chain of dependent steps, by the clock of one wave (a sentence of 22 tokens, about 2.4 clocks per ns): 4,500 until
+// the arguments and the last step's partial keys are there, 1,300 for the token, 2,300 for the table's rows, 1,000 for their
+// combination, 1,200 per four keys of a wave, 900 for a merge of partial softmaxes, 800 per normalisation, 1,400 to the end.  So what
+// depends on no row is staged in the LDS meanwhile (fold_const, fold_pos; requested where it was used it came to three more turns of
+// the memory system), the caches' first keys travel with the table's rows, the row's waves all hold it and merge a share of the
+// columns each, and the pair that is appended is rounded by the wave with the fewest keys.  One row of 22 tokens 10.3 -> 9.2 us, 45 rows
+// 13.4 -> 11.6, 300 of 13 14.0 -> 12.8, integer caches 320 rows of 150 31.8 -> 30.1, 2,000 of 27 40.4 -> 37.6; with an FFN 45 rows
+// 24.0 -> 21.6.  One sentence 690 -> 655 us, 45 sentences 2,120 -> 1,970, a 4,096-token budget 19.2 -> 18.8 ms.
 //
 // Larger batches keep the products as 16-bit integers, the same bytes as without folding (nt_cross_fold.hip).  A step's layer alone, us,
 // against three matrices per workgroup: 2,000 rows of 27 tokens 55 -> 40, 700 of 40 44 -> 25, 1,000 of 55 55 -> 34, 320 of 150 49 -> 32;
@@ -231,6 +239,33 @@ hipError_t launch_dec1_table(const _Float16 *E, const float *pe, const float *ga
   return hipGetLastError();
 }
 
+// Dec1Args::fold_const (for either form of the caches, 13 vectors each) and fold_pos, one vector per workgroup
+constexpr int DF_CONST = 13;
+__global__ __launch_bounds__(256) void dec1_fold_vectors_kernel(Dec1FoldVectors v, int d, float *dst) {
+  const int i = blockIdx.x, form = i / DF_CONST, u = i % DF_CONST, ffn = v.ln3.gamma != nullptr;
+  const long ld = (long)v.table.parts * d;
+  const float *src = nullptr;
+  if (form < 2) {
+    const float *offset = v.table.rows + (v.vocab + v.table.max_len) * ld;
+    const bool two = form == 1 && v.gamma2;
+    const float *all[DF_CONST] = {two ? v.gamma2 : v.ln2.gamma, two ? v.beta2 : v.ln2.beta, v.ln3.gamma, v.ln3.beta, v.lnf.gamma, v.lnf.beta,
+                                  v.fold_scale, v.fold_bias, v.cross_scale, v.cross_const, offset, offset + d, offset + ld - d};
+    src = u < 2 || ffn ? all[u] : u + 2 < DF_CONST ? all[u + 2] : nullptr;
+  } else {
+    const int t = (i - 2 * DF_CONST) / 4, w = (i - 2 * DF_CONST) % 4;
+    const float *pos = v.table.rows + (v.vocab + t) * ld;
+    src = w == 3 ? v.pe + (long)t * d : w == 2 ? pos + ld - d : pos + w * d;
+  }
+  for (int k = threadIdx.x; k < d; k += 256) dst[(long)i * d + k] = src ? src[k] : 0.f;
+}
+size_t dec1_fold_vectors_bytes(int d, int max_len) { return (size_t)(2 * DF_CONST + 4 * max_len) * d * sizeof(float); }
+hipError_t launch_dec1_fold_vectors(const Dec1FoldVectors &v, int d, float *dst, hipStream_t s) {
+  hipLaunchKernelGGL(dec1_fold_vectors_kernel, dim3((unsigned)(2 * DF_CONST + 4 * v.table.max_len)), dim3(256), 0, s, v, d, dst);
+  return hipGetLastError();
+}
+const float *dec1_fold_const(const float *vectors, int d, int folded) { return vectors + (long)(folded - 1) * DF_CONST * d; }
+const float *dec1_fold_pos(const float *vectors, int d) { return vectors + 2L * DF_CONST * d; }
+
 // One partial softmax over some of a row's keys.
 template <int NE>
 struct D1Part {
@@ -282,9 +317,9 @@ struct D1Block {
     for (int i = 0; i < D1_NK; i++) {
       const int j = j0 + i < n ? j0 + i : n - 1;
       const long p = pos0 + j;
-      const Elt *kp = (const Elt *)kv + p * 2 * D + lane * NE;
-      k[i] = *(const Vec *)kp;
-      v[i] = *(const Vec *)(kp + D);
+      const char *kp = (const char *)kv + p * (2 * D * (long)sizeof(Elt));  // (uniform)
+      k[i] = *(const Vec *)(kp + (unsigned)lane * sizeof(Vec));
+      v[i] = *(const Vec *)(kp + (unsigned)lane * sizeof(Vec) + D * sizeof(Elt));
       typedef const __attribute__((address_space(4))) float *Uniform;
       const Uniform u = (Uniform)(unsigned long long)(sc + p * (F32 ? 1 : KIND == D1_CODES ? 2 : 4));
       ks[i] = F32 ? 1.f : u[0];
@@ -356,9 +391,9 @@ struct D1HeadBlock {
 #pragma unroll
     for (int i = 0; i < D1_NK; i++) {
       const int j = j0 + i < n ? j0 + i : n - 1;
-      const Elt *kp = (const Elt *)kv + (pos0 + j) * 2 * D + lane * NE;
-      k[i] = *(const Vec *)kp;
-      v[i] = *(const Vec *)(kp + D);
+      const char *kp = (const char *)kv + (pos0 + j) * (2 * D * (long)sizeof(Elt));  // (uniform)
+      k[i] = *(const Vec *)(kp + (unsigned)lane * sizeof(Vec));
+      v[i] = *(const Vec *)(kp + (unsigned)lane * sizeof(Vec) + D * sizeof(Elt));
     }
   }
   __device__ __forceinline__ void fold(const float (&q)[NE], int j0, int n, int, D1Part<NE> &a, const D1Rel &rel) const {
@@ -509,9 +544,9 @@ __global__ __launch_bounds__(NWAVES * 64) void dec1_kernel(Dec1Args a) {
   // with several partial softmaxes does not have
   constexpr bool EARLY = !(NWAVES == 16 && (PW > 1 || HEADS));
   constexpr bool FOLD = FOLD32 || FOLD16;
-  constexpr bool ALONE = FOLD && WR == 1;  // no wave of the attention phases needs another's results
-  // what is requested before it is needed: 2 both caches' first blocks before the step's start, 1 a cache's at a time, 0 nothing
+  // folded: what is requested before it is needed: 2 both caches' first blocks before the row's start, 1 a cache's at a time, 0 nothing
   constexpr int AHEAD = !FOLD ? 0 : NWAVES < 16 ? 2 : FFN ? 0 : 1;
+  static_assert(!FOLD || PW == 1, "");
   static_assert(!HEADS || (D == 512 && !FOLD && !FFN), "heads are eight lanes of eight elements");
   typedef typename std::conditional<HEADS, D1HeadBlock<NE, float>, D1Block<NE, D1_CODES>>::type SelfBlock;
   typedef typename std::conditional<HEADS, D1HeadBlock<NE, _Float16>,
@@ -519,11 +554,14 @@ __global__ __launch_bounds__(NWAVES * 64) void dec1_kernel(Dec1Args a) {
   typedef D1Part<NE> Part;
   __shared__ __attribute__((aligned(16))) _Float16 sA[FOLD && !FFN ? 8 : 2 * RW * LD];  // head rows, then tail rows
   __shared__ __attribute__((aligned(16))) float sZ[RW * ZLD];                     // residual stream
-  __shared__ __attribute__((aligned(16))) float sQ[FOLD16 && !FFN ? 4 : RW * (D + 8)];  // FOLD32: scales; cross-attention query, later:
+  __shared__ __attribute__((aligned(16))) float sQ[FOLD && !FFN ? 4 : RW * (D + 8)];    // cross-attention query, later:
   _Float16 *sU = (_Float16 *)sQ;                                                  // FFN hidden state, head rows, then tail rows
-  __shared__ float sPart[WR > 1 ? RW * (PARTS - PW) * (NE + 2) * 64 : 1];         // partial softmaxes of the waves pg > 0
+  // partial softmaxes: of the waves pg > 0, or (folded) of all waves
+  __shared__ __attribute__((aligned(16))) float sPart[WR > 1 ? RW * (FOLD ? PARTS * (D + 2) : (PARTS - PW) * (NE + 2) * 64) : 4];
   constexpr int NV = FFN ? 6 : 4, LN2 = 0, LN3 = 2, LNF = NV - 2;  // vectors of the normalisations
-  constexpr int NVT = NV + (FOLD16 ? 4 : 0), NVW = (NVT + NWAVES - 1) / NWAVES;  // FOLD16: and scale and constant of either context
+  // folded: and, as in Dec1Args::fold_const, scale and constant of either context (VC) and the first layer's constants (VS), and as in
+  // fold_pos what goes by the position (VP)
+  constexpr int VC = NV, VS = VC + 4, VP = VS + 3, NVT = FOLD ? VP + 4 : NV, NVW = (NVT + NWAVES - 1) / NWAVES;
   __shared__ __attribute__((aligned(16))) float sNorm[NVT * D];
   __shared__ float sRel[HEADS ? RW * (D1_MAX_CLIP + 1) * 8 : 1];                  // per row: [distance][head]
   const int tid = threadIdx.x, lane = tid & 63, h = lane >> 4, c16 = lane & 15;
@@ -532,7 +570,7 @@ __global__ __launch_bounds__(NWAVES * 64) void dec1_kernel(Dec1Args a) {
   const int row0 = blockIdx.x * RW;
   const bool valid = row0 + rw < a.rows;
   D1Token token;
-  if (a.table.rows) token.request(a, row0 + rw, lane);
+  if (FOLD || a.table.rows) token.request(a, row0 + rw, lane);
   // the normalisations' gains and offsets go to the LDS while the start of the row travels, a vector per wave: read where they are used,
   // each would be another turn of the memory system in the row's chain
   float norm[NVW][NE];
@@ -540,10 +578,12 @@ __global__ __launch_bounds__(NWAVES * 64) void dec1_kernel(Dec1Args a) {
 #pragma unroll
   for (int u = 0; u < NVW; u++) {
     const int i = wave + u * NWAVES;
-    const GemmLayerNorm &of = i < 2 ? a.ln2 : FFN && i < 4 ? a.ln3 : a.lnf;
-    norm_src[u] = i < NV ? (i & 1 ? of.beta : of.gamma) : nullptr;  // (no final one: nullptr)
-    if (FOLD16 && i >= NV)
-      norm_src[u] = i == NV ? a.fold_scale : i == NV + 1 ? a.bo_self : i == NV + 2 ? a.cross_scale : i == NV + 3 ? a.bo_cross : nullptr;
+    if constexpr (FOLD) {
+      norm_src[u] = i < VP ? a.fold_const + i * D : i < NVT ? a.fold_pos + (a.sb.t * 4L + (i - VP)) * D : nullptr;
+    } else {
+      const GemmLayerNorm &of = i < 2 ? a.ln2 : FFN && i < 4 ? a.ln3 : a.lnf;
+      norm_src[u] = i < NV ? (i & 1 ? of.beta : of.gamma) : nullptr;  // (no final one: nullptr)
+    }
     if (norm_src[u]) d1_load<NE>(norm_src[u] + lane * NE, norm[u]);
   }
   const int r = valid ? row0 + rw : 0;
@@ -639,12 +679,20 @@ __global__ __launch_bounds__(NWAVES * 64) void dec1_kernel(Dec1Args a) {
     *(halfNE *)(sA + rw * LD + lane * NE) = hi;
     *(halfNE *)(sA + (RW + rw) * LD + lane * NE) = lo;
   };
-  // LayerNorm of this wave's row of the residual stream: fp32, mean first, then the variance of the centred values
-  auto normalise = [&](int which, float (&y)[NE]) {
+  auto store_norms = [&]() {
+#pragma unroll
+    for (int u = 0; u < NVW; u++)
+      if (norm_src[u]) {
+#pragma unroll
+        for (int e = 0; e < NE; e += 4)
+          *(float4 *)(sNorm + (wave + u * NWAVES) * D + lane * NE + e) = make_float4(norm[u][e], norm[u][e + 1], norm[u][e + 2], norm[u][e + 3]);
+      }
+  };
+  // LayerNorm of a row of the residual stream: fp32, mean first, then the variance of the centred values
+  auto normalise_row = [&](int which, float (&y)[NE]) {
     float ga[NE], be[NE];
     d1_load<NE>(sNorm + which * D + lane * NE, ga);
     d1_load<NE>(sNorm + (which + 1) * D + lane * NE, be);
-    d1_load<NE>(sZ + rw * ZLD + lane * NE, y);
     float s = 0.f;
 #pragma unroll
     for (int e = 0; e < NE; e++) s += y[e];
@@ -656,17 +704,21 @@ __global__ __launch_bounds__(NWAVES * 64) void dec1_kernel(Dec1Args a) {
 #pragma unroll
     for (int e = 0; e < NE; e++) y[e] = ga[e] * ((y[e] - mean) * rs) + be[e];
   };
+  auto normalise = [&](int which, float (&y)[NE]) {  // of this wave's row in the LDS
+    d1_load<NE>(sZ + rw * ZLD + lane * NE, y);
+    normalise_row(which, y);
+  };
   // attention of this wave's row over n cached keys; the partials may hold the newest key already.  The merged context
   // goes to done(ctx) in the row's first wave
-  // Two blocks in flight: the next one of the wave's only partial, or one of each of its two.  b holds the first
-  // `preloaded` blocks of a single partial already (see first_block)
+  // Two blocks in flight: the next one of the wave's only partial, or one of each of its two.
   constexpr int STEP = PARTS * D1_NK;
   const int j_first = pg * PW * D1_NK;
   auto first_block = [&](auto &b, int which, const void *kv, const float *sc, long pos0, int n) {
     if (j_first + which * STEP < n) b.load(kv, sc, pos0, j_first + which * STEP, n, lane);
   };
-  auto attend = [&](auto (&b)[2], auto preloaded, const float (&q)[NE], const void *kv, const float *sc, long pos0, int n, const D1Rel &rel, Part (&st)[PW], auto done) {
-    if constexpr (NWAVES == 16 && AHEAD == 0) {  // 128 registers: one block at a time
+  // the wave's share of the keys; b holds the first two blocks already if `preloaded`
+  auto fold_keys = [&](auto (&b)[2], auto preloaded, const float (&q)[NE], const void *kv, const float *sc, long pos0, int n, const D1Rel &rel, Part (&st)[PW]) {
+    if constexpr (NWAVES == 16 && !decltype(preloaded)::value) {  // 128 registers: one block at a time
       for (int j = j_first; j < n; j += STEP)
 #pragma unroll
         for (int u = 0; u < PW; u++)
@@ -675,8 +727,10 @@ __global__ __launch_bounds__(NWAVES * 64) void dec1_kernel(Dec1Args a) {
             b[0].fold(q, j + u * D1_NK, n, lane, st[u], rel);
           }
     } else if constexpr (PW == 1) {
-#pragma unroll
-      for (int u = decltype(preloaded)::value; u < 2; u++) first_block(b[u], u, kv, sc, pos0, n);
+      if constexpr (!decltype(preloaded)::value) {
+        first_block(b[0], 0, kv, sc, pos0, n);
+        first_block(b[1], 1, kv, sc, pos0, n);
+      }
       for (int j = j_first; j < n; j += 2 * STEP) {
         b[0].fold(q, j, n, lane, st[0], rel);
         if (j + 2 * STEP < n) b[0].load(kv, sc, pos0, j + 2 * STEP, n, lane);
@@ -692,6 +746,9 @@ __global__ __launch_bounds__(NWAVES * 64) void dec1_kernel(Dec1Args a) {
         if (j + D1_NK < n) b[1].fold(q, j + D1_NK, n, lane, st[1], rel);
       }
     }
+  };
+  auto attend = [&](auto (&b)[2], const float (&q)[NE], const void *kv, const float *sc, long pos0, int n, const D1Rel &rel, Part (&st)[PW], auto done) {
+    fold_keys(b, std::false_type{}, q, kv, sc, pos0, n, rel, st);
     if constexpr (WR > 1) {
       if (pg > 0) {
 #pragma unroll
@@ -727,22 +784,170 @@ __global__ __launch_bounds__(NWAVES * 64) void dec1_kernel(Dec1Args a) {
       for (int e = 0; e < NE; e++) ctx[e] = t.acc[e] * inv;
       done(ctx);
     }
-    if (!ALONE) __syncthreads();
+    __syncthreads();
   };
 
-  // ---- self-attention ----
   const int n_self = __builtin_amdgcn_readfirstlane(live ? a.n_keys : 0);
   const int n_cross = __builtin_amdgcn_readfirstlane(live ? a.len[rc] : 0);
-  if (EARLY && !FOLD) preload(a.Wo_self);
   SelfBlock sb[2];
   CrossBlock cb[2];
   const long cross0 = (long)rc * a.cross_positions, self0 = (long)rc * a.self_positions;
   const int n_cached = n_self > 0 ? n_self - 1 : 0;
-  // the first blocks of both caches depend on nothing computed here
-  if constexpr (AHEAD == 2) first_block(sb[0], 0, a.self_kv, a.self_sc, self0, n_cached);
-  if constexpr (AHEAD == 2) first_block(cb[0], 0, a.cross_kv, a.cross_sc, cross0, n_cross);
-
-  float q[NE], z[NE], kx[NE], vx[NE];  // z, kx, vx: the row's first wave
+  float q[NE], z[NE], kx[NE], vx[NE];
+  if constexpr (FOLD) {
+    // ---- folded: start of the row, two attentions; the row stays in the registers of all its waves, each of which merges their partial
+    // softmaxes for itself, so that an attention costs one exchange ----
+    typedef std::integral_constant<bool, (AHEAD > 0)> Ahead;
+    const int y = token.resolve(a, row0 + rw, pg == 0, lane);
+    if (row0 >= a.rows) return;  // rows that were kept to collect their last tokens
+    typedef _Float16 halfNE __attribute__((ext_vector_type(NE)));
+    const float *by_token = a.table.rows + (long)y * a.table.parts * D + lane * NE;
+    const halfNE ev = *(const halfNE *)(a.sb.E + (long)y * D + lane * NE);
+    d1_load<NE>(by_token, q);
+    d1_load<NE>(by_token + D, kx);
+    d1_load<NE>(by_token + (a.table.parts - 1) * D, vx);
+    store_norms();
+    __syncthreads();
+    if constexpr (AHEAD == 2) {  // the first blocks of both caches travel with the table's rows
+      first_block(sb[0], 0, a.self_kv, a.self_sc, self0, n_cached);
+      first_block(cb[0], 0, a.cross_kv, a.cross_sc, cross0, n_cross);
+    }
+    {  // z = sqrt(d) E[y] + PE[t]; query, key and value by table (Dec1Table)
+      float pv[NE];
+      d1_load<NE>(sNorm + (VP + 3) * D + lane * NE, pv);
+      const float sc = sqrtf((float)D);
+      float s = 0.f;
+#pragma unroll
+      for (int e = 0; e < NE; e++) {
+        z[e] = sc * (float)ev[e] + pv[e];
+        s += z[e];
+      }
+      const float mean = wave_sum(s) / (float)D;
+      float v = 0.f;
+#pragma unroll
+      for (int e = 0; e < NE; e++) v += ln_term(z[e] - mean, a.eps.l1);
+      const float rs = ln_rscale(wave_sum(v) / (float)D, a.eps);
+      auto combine = [&](float (&x)[NE], int which) {
+        float p[NE], c[NE];
+        d1_load<NE>(sNorm + (VP + which) * D + lane * NE, p);
+        d1_load<NE>(sNorm + (VS + which) * D + lane * NE, c);
+#pragma unroll
+        for (int e = 0; e < NE; e++) x[e] = rs * (x[e] + p[e]) + c[e];
+      };
+      combine(q, 0);
+      combine(kx, 1);
+      combine(vx, 2);
+    }
+    if constexpr (AHEAD == 1) {
+      __builtin_amdgcn_sched_barrier(0);
+      first_block(sb[0], 0, a.self_kv, a.self_sc, self0, n_cached);
+    }
+    auto put_z = [&]() {
+#pragma unroll
+      for (int e = 0; e < NE; e += 4) *(float4 *)(sZ + rw * ZLD + lane * NE + e) = make_float4(z[e], z[e + 1], z[e + 2], z[e + 3]);
+    };
+    if (pg == 0) put_z();
+    // A context into the residual stream.  The partial softmaxes of a row's waves meet in the LDS; each wave merges its share of the columns,
+    // all with one set of weights (in the chain of pairwise merges in one wave, which the others waited for, a context took 1,000 clocks).
+    auto add_context = [&](const Part &st, int which) {
+      // (FOLD32: of the folded values of the cross cache nothing is left to do)
+      auto added = [&](float z_, float ctx, float c, float b) {
+        if (FOLD32) return which == 0 ? z_ + b + ctx * c : z_ + ctx;
+        return z_ + (ctx * c + b);
+      };
+      const float *scale = sNorm + (VC + 2 * which) * D, *constant = scale + D;
+      if constexpr (WR == 1) {
+        float c[NE], b[NE];
+        d1_load<NE>(sZ + rw * ZLD + lane * NE, z);
+        d1_load<NE>(scale + lane * NE, c);
+        d1_load<NE>(constant + lane * NE, b);
+        const float inv = (st.l > 0.f) ? 1.f / st.l : 0.f;
+#pragma unroll
+        for (int e = 0; e < NE; e++) z[e] = added(z[e], st.acc[e] * inv, c[e], b[e]);
+        put_z();
+      } else {
+        constexpr int CW = D / WR, CL = CW < 64 ? 1 : CW / 64;  // columns of a wave, of a lane
+        float *base = sPart + rw * PARTS * (D + 2);
+        float2 *ml = (float2 *)(base + PARTS * D);
+#pragma unroll
+        for (int e = 0; e < NE; e += 4)
+          *(float4 *)(base + pg * D + lane * NE + e) = make_float4(st.acc[e], st.acc[e + 1], st.acc[e + 2], st.acc[e + 3]);
+        if (lane == 0) ml[pg] = make_float2(st.m, st.l);
+        __syncthreads();
+        if (CW >= 64 || lane < CW) {
+          const int col = pg * CW + lane * CL;
+          float m[PARTS], l = 0.f, top = -INFINITY, ctx[CL] = {}, x[PARTS][CL];
+#pragma unroll
+          for (int k = 0; k < PARTS; k++) {
+#pragma unroll
+            for (int c = 0; c < CL; c++) x[k][c] = base[k * D + col + c];
+          }
+#pragma unroll
+          for (int k = 0; k < PARTS; k++) m[k] = ml[k].x, top = fmaxf(top, m[k]);
+#pragma unroll
+          for (int k = 0; k < PARTS; k++) {
+            const float w = m[k] == -INFINITY ? 0.f : __expf(m[k] - top);
+            l += w * ml[k].y;
+#pragma unroll
+            for (int c = 0; c < CL; c++) ctx[c] += w * x[k][c];
+          }
+          const float inv = (l > 0.f) ? 1.f / l : 0.f;
+          float *zc = sZ + rw * ZLD + col;
+#pragma unroll
+          for (int c = 0; c < CL; c++) zc[c] = added(zc[c], ctx[c] * inv, scale[col + c], constant[col + c]);
+        }
+        __syncthreads();
+      }
+    };
+    // (z is in the LDS while keys are read: the registers are theirs)
+    {
+      Part st[1];
+      st[0].clear();
+      if (pg == 0 && n_self > 0) {  // the pair computed in this step: used as it is
+        float s = 0.f;
+#pragma unroll
+        for (int e = 0; e < NE; e++) s += q[e] * kx[e];
+        st[0].m = wave_sum(s);
+        st[0].l = 1.f;
+#pragma unroll
+        for (int e = 0; e < NE; e++) st[0].acc[e] = vx[e];
+      }
+      if (pg == WR - 1 && n_self > 0) {  // and appended in integer form, by the wave with the fewest other keys
+        const long p = self0 + (n_self - 1);
+        short *dst = (short *)a.self_kv + p * 2 * D;
+        d1_quantize_store<NE>(kx, dst, a.self_sc + p * 2, lane);
+        d1_quantize_store<NE>(vx, dst + D, a.self_sc + p * 2 + 1, lane);
+      }
+      if constexpr (AHEAD > 0) {  // the second blocks when the start no longer needs its registers
+        __builtin_amdgcn_sched_barrier(0);
+        first_block(sb[1], 1, a.self_kv, a.self_sc, self0, n_cached);
+        if constexpr (AHEAD == 2) first_block(cb[1], 1, a.cross_kv, a.cross_sc, cross0, n_cross);
+      }
+      fold_keys(sb, Ahead{}, q, a.self_kv, a.self_sc, self0, n_cached, D1Rel{}, st);
+      add_context(st[0], 0);
+    }
+    if constexpr (AHEAD == 1) {
+      __builtin_amdgcn_sched_barrier(0);
+      first_block(cb[0], 0, a.cross_kv, a.cross_sc, cross0, n_cross);
+      first_block(cb[1], 1, a.cross_kv, a.cross_sc, cross0, n_cross);
+    }
+    // ---- cross-attention: the normalised row is the query ----
+    normalise(LN2, q);
+    if (FFN && EARLY) preload(a.W1);
+    Part st[1];
+    st[0].clear();
+    fold_keys(cb, Ahead{}, q, a.cross_kv, a.cross_sc, cross0, n_cross, D1Rel{}, st);
+    if (FFN && !EARLY) preload(a.W1);
+    add_context(st[0], 1);
+    if constexpr (FFN) {
+      if (pg == 0) {
+        normalise(LN3, q);
+        store_planes(q);
+      }
+    }
+  } else {
+  // ---- self-attention ----
+  if (EARLY) preload(a.Wo_self);
   if (a.table.rows) {
     const int y = token.resolve(a, row0 + rw, pg == 0, lane);
     if (row0 >= a.rows) return;  // rows that were kept to collect their last tokens
@@ -755,55 +960,11 @@ __global__ __launch_bounds__(NWAVES * 64) void dec1_kernel(Dec1Args a) {
       d1_load<NE>(a.kv_new + (long)r * 2 * D + D + lane * NE, vx);
     }
   }
-#pragma unroll
-  for (int u = 0; u < NVW; u++)
-    if (norm_src[u]) {
-#pragma unroll
-      for (int e = 0; e < NE; e += 4)
-        *(float4 *)(sNorm + (wave + u * NWAVES) * D + lane * NE + e) = make_float4(norm[u][e], norm[u][e + 1], norm[u][e + 2], norm[u][e + 3]);
-    }
-  if constexpr (AHEAD > 0) {  // the second ones when the start no longer needs its registers: with two waves on a SIMD it makes way for others
-    __builtin_amdgcn_sched_barrier(0);
-    first_block(sb[AHEAD == 2], AHEAD == 2, a.self_kv, a.self_sc, self0, n_cached);
-    if constexpr (AHEAD == 2) first_block(cb[1], 1, a.cross_kv, a.cross_sc, cross0, n_cross);
-  }
-  if (pg == 0) {
-    if constexpr (FOLD32) {  // the bias of the self-attention's output, which no projection adds, and the values' column scales
-      float b[NE], c[NE];
-      d1_load<NE>(a.bo_self + lane * NE, b);
-      d1_load<NE>(a.fold_scale + lane * NE, c);
-#pragma unroll
-      for (int e = 0; e < NE; e++) z[e] += b[e];
-#pragma unroll
-      for (int e = 0; e < NE; e += 4) *(float4 *)(sQ + rw * ZLD + lane * NE + e) = make_float4(c[e], c[e + 1], c[e + 2], c[e + 3]);
-    }
+  store_norms();
+  if (pg == 0) {  // (z, kx, vx: the row's first wave)
 #pragma unroll
     for (int e = 0; e < NE; e += 4) *(float4 *)(sZ + rw * ZLD + lane * NE + e) = make_float4(z[e], z[e + 1], z[e + 2], z[e + 3]);
   }
-  if constexpr (ALONE) __syncthreads();  // the vectors
-  // folded contexts, column by column times its scale, and their constants
-  auto add_scaled = [&](const float (&ctx)[NE], int which) {
-    float z[NE], c[NE], b[NE];
-    d1_load<NE>(sZ + rw * ZLD + lane * NE, z);
-    d1_load<NE>(sNorm + which * D + lane * NE, c);
-    d1_load<NE>(sNorm + (which + 1) * D + lane * NE, b);
-#pragma unroll
-    for (int e = 0; e < NE; e++) z[e] += ctx[e] * c[e] + b[e];
-#pragma unroll
-    for (int e = 0; e < NE; e += 4) *(float4 *)(sZ + rw * ZLD + lane * NE + e) = make_float4(z[e], z[e + 1], z[e + 2], z[e + 3]);
-  };
-  auto add_context = [&](const float (&ctx)[NE]) {
-    if constexpr (FOLD16) return add_scaled(ctx, NV + 2);
-    float *z = sZ + rw * ZLD + lane * NE;
-#pragma unroll
-    for (int e = 0; e < NE; e++) z[e] += ctx[e];
-  };
-  auto add_self_context = [&](const float (&ctx)[NE]) {
-    if constexpr (FOLD16) return add_scaled(ctx, NV);
-    float *z = sZ + rw * ZLD + lane * NE;
-#pragma unroll
-    for (int e = 0; e < NE; e++) z[e] += ctx[e] * sQ[rw * ZLD + lane * NE + e];
-  };
   D1Rel rel;
   if constexpr (HEADS) {
     if (a.rk) {  // this row's query against the relative keys it can meet (distances -clip .. 0), shared by the row's waves
@@ -845,69 +1006,49 @@ __global__ __launch_bounds__(NWAVES * 64) void dec1_kernel(Dec1Args a) {
         d1_quantize_store<NE>(vx, dst + D, a.self_sc + p * 2 + 1, lane);
       }
     }
-    if constexpr (AHEAD == 1) {
-      __builtin_amdgcn_sched_barrier(0);
-      first_block(sb[1], 1, a.self_kv, a.self_sc, self0, n_cached);
-    }
-    if constexpr (FOLD) attend(sb, std::integral_constant<int, AHEAD ? 2 : 0>{}, q, a.self_kv, a.self_sc, self0, n_cached, rel, st, add_self_context);
-    else attend(sb, std::integral_constant<int, 0>{}, q, a.self_kv, a.self_sc, self0, n_cached, rel, st, store_planes);
+    attend(sb, q, a.self_kv, a.self_sc, self0, n_cached, rel, st, store_planes);
   }
   // ---- output projection + residual, LayerNorm, cross-attention query ----
-  if constexpr (!FOLD) {
-    if (!EARLY) preload(a.Wo_self);
-    request_bias(a.bo_self);
-    project(a.Wo_self, sA);
-    preload(a.Wq);
-    add_residual();
-    __syncthreads();
+  if (!EARLY) preload(a.Wo_self);
+  request_bias(a.bo_self);
+  project(a.Wo_self, sA);
+  preload(a.Wq);
+  add_residual();
+  __syncthreads();
+  {
+    float y[NE];
+    normalise(LN2, y);
+    if (pg == 0) store_planes(y);
   }
-  if constexpr (FOLD) {
-    // ---- cross-attention over the folded cache: the normalised row is the query, the context adds to the residual ----
-    if constexpr (AHEAD == 1) {
-      __builtin_amdgcn_sched_barrier(0);
-      first_block(cb[0], 0, a.cross_kv, a.cross_sc, cross0, n_cross);
-      first_block(cb[1], 1, a.cross_kv, a.cross_sc, cross0, n_cross);
-    }
-    normalise(LN2, q);
-    if (FFN && EARLY) preload(a.W1);
+  __syncthreads();
+  request_bias(a.bq);
+  project(a.Wq, sA);
+  if (EARLY) preload(a.Wo_cross);
+  {
+    results([&](int i, int n, float x) { sQ[i * ZLD + n] = (x + bias[(n - n0) >> 4]) * a.q_scale; });
+  }
+  __syncthreads();
+  // ---- cross-attention, output projection + residual ----
+  {
     Part st[PW];
 #pragma unroll
     for (int u = 0; u < PW; u++) st[u].clear();
-    attend(cb, std::integral_constant<int, AHEAD ? 2 : 0>{}, q, a.cross_kv, a.cross_sc, cross0, n_cross, D1Rel{}, st, add_context);
-    if (FFN && !EARLY) preload(a.W1);
-  } else {
-    {
-      float y[NE];
-      normalise(LN2, y);
-      if (pg == 0) store_planes(y);
-    }
-    __syncthreads();
-    request_bias(a.bq);
-    project(a.Wq, sA);
-    if (EARLY) preload(a.Wo_cross);
-    {
-      results([&](int i, int n, float x) { sQ[i * ZLD + n] = (x + bias[(n - n0) >> 4]) * a.q_scale; });
-    }
-    __syncthreads();
-    // ---- cross-attention, output projection + residual ----
-    {
-      Part st[PW];
-#pragma unroll
-      for (int u = 0; u < PW; u++) st[u].clear();
-      d1_load<NE>(sQ + rw * ZLD + lane * NE, q);
-      attend(cb, std::integral_constant<int, 0>{}, q, a.cross_kv, a.cross_sc, cross0, n_cross, D1Rel{}, st, store_planes);
-    }
-    if (!EARLY) preload(a.Wo_cross);
-    request_bias(a.bo_cross);
-    project(a.Wo_cross, sA);
-    if (FFN) preload(a.W1);
-    add_residual();
-    __syncthreads();
+    d1_load<NE>(sQ + rw * ZLD + lane * NE, q);
+    attend(cb, q, a.cross_kv, a.cross_sc, cross0, n_cross, D1Rel{}, st, store_planes);
   }
+  if (!EARLY) preload(a.Wo_cross);
+  request_bias(a.bo_cross);
+  project(a.Wo_cross, sA);
+  if (FFN) preload(a.W1);
+  add_residual();
+  __syncthreads();
   if constexpr (FFN) {
     float y[NE];
     normalise(LN3, y);
     if (pg == 0) store_planes(y);
+  }
+  }
+  if constexpr (FFN) {
     __syncthreads();
     request_bias(a.b1);
     project(a.W1, sA);
@@ -926,18 +1067,17 @@ __global__ __launch_bounds__(NWAVES * 64) void dec1_kernel(Dec1Args a) {
   }
   // ---- the residual stream back, and / or the final hidden state as planes with the norm of the tail ----
   if (pg != 0 || !valid) return;
+  d1_load<NE>(sZ + rw * ZLD + lane * NE, z);
   if (a.write_z) {
-    float z[NE];
-    d1_load<NE>(sZ + rw * ZLD + lane * NE, z);
 #pragma unroll
     for (int e = 0; e < NE; e += 4) *(float4 *)(a.z + (long)r * D + lane * NE + e) = make_float4(z[e], z[e + 1], z[e + 2], z[e + 3]);
   }
   if (a.h_hi) {
     typedef _Float16 halfNE __attribute__((ext_vector_type(NE)));
-    float y[NE];
     unsigned int level[NE / 4];
     if (a.scout.codes) scout_levels<NE>(a.scout, lane, level);
-    normalise(LNF, y);
+    float (&y)[NE] = z;
+    normalise_row(LNF, y);
     halfNE hi, lo;
     float tail2 = 0.f;
 #pragma unroll
@@ -994,11 +1134,16 @@ static hipError_t d1_launch(const Dec1Args &a, hipStream_t s) {
       return hipGetLastError();
     }
     if (a.folded) {
-      // one row per workgroup has 267 registers and a CU to itself; two rows have 256 (17 spilled) and still four waves each, so that
-      // more than 256 rows are one round (a step of 250 / 300 / 400 / 511 rows alone: 31.8 / 40.3 / 41.9 / 45.3 us and 32.4 / 36.1 / 37.9 / 41.6;
-      // of one and 45 rows 15.1 / 22.5 and 15.6 / 23.0)
+      // A row per workgroup, up to 256 rows, which is one round; more, two of them with four waves each (a step of 250 / 300 / 400 / 511 rows
+      // alone: 31.8 / 40.3 / 41.9 / 45.3 us and 32.4 / 36.1 / 37.9 / 41.6).  Eight waves for a row up to 64 rows: 45 rows of 22 tokens 11.6
+      // us with eight and 12.2 with four, 60 of 100 17.4 and 18.7; 100 rows of 30 11.2 both ways, 200 of 20 11.9 and 11.4, and beside other
+      // lanes they cost more (a 4,096-token budget 19.5 against 18.8 ms).  Four for a row alone, which is mostly a short sentence: 22
+      // tokens 9.5 us with eight and 9.3 with four (150: 15.3 and 16.5).
       if (FFN || shape > 256) NT_D1(2, 8, 4, true);
-      else if constexpr (!FFN) NT_D1(1, 4, 4, true);
+      else if constexpr (!FFN) {
+        if (shape > 1 && shape <= 64) NT_D1(1, 8, 8, true);
+        else NT_D1(1, 4, 4, true);
+      }
       return hipGetLastError();
     }
   }
@@ -1023,6 +1168,7 @@ static hipError_t d1_launch(const Dec1Args &a, hipStream_t s) {
 hipError_t launch_dec1(const Dec1Args &a, int d, hipStream_t s) {
   if (a.rows <= 0) return hipSuccess;
   const bool ffn = a.W1 != nullptr;
+  if (a.folded && !a.table.rows) return hipErrorInvalidValue;
   if (a.heads > 1) {
     if (!dec1_heads_supported(d, a.heads) || ffn || a.folded || a.clip > D1_MAX_CLIP) return hipErrorInvalidValue;
     return d1_launch<512, false, true>(a, s);

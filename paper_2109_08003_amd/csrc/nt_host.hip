@@ -233,6 +233,7 @@ struct nt_model {
   int64_t fold_positions = 0;
   int folded = 0;
   nt::CrossFold fold{};
+  float *fold_vectors = nullptr;  // Dec1Args::fold_const, fold_pos
   std::vector<float *> cross_sc, self_sc;  // per decoder layer [Mt,2] ([Mt,4] where it can be folded) / [self_positions,2] scales
   float *z = nullptr, *a32 = nullptr, *q32 = nullptr, *ctx32 = nullptr, *u32 = nullptr;  // [Br, d|F]
   unsigned long long *pk = nullptr;
@@ -284,6 +285,11 @@ int dec_heads(const nt_config *c) { return c->dec_n_heads > 0 ? c->dec_n_heads :
 int dec_ffn(const nt_config *c) { return c->dec_d_ffn == 0 ? c->d_ffn : std::max(c->dec_d_ffn, 0); }
 
 nt::LnEps ln_eps_of(const nt_config &c) { return nt::LnEps{c.ln_eps, c.ln_l1}; }
+
+// an FFN as wide as the model is part of a one-head decoder layer's launch
+bool ffn_inside_layer(const nt_model *m, const DecLayer &L) {
+  return m->kv_i16 && dec_ffn(&m->c) == m->c.d_model && L.ffn.W1_p != nullptr && L.ffn.W2_p != nullptr;
+}
 
 int check_config(const nt_config *c) {
   if (!c) return fail(NT_EINVAL, "config is null");
@@ -779,6 +785,7 @@ int nt_load_weights(const nt_config *cfg, const void *h_blob_fp16, size_t blob_b
       }
     fixes.push_back({o, (const void **)&m->pe});
   }
+  const size_t o_vec = fold_dec ? pk.reserve(nt::dec1_fold_vectors_bytes(d, cfg->max_len)) : 0;
   const size_t o_fold = fold_all ? pk.reserve(nt::cross_fold_bytes(d)) : 0;
   m->w_bytes = pk.img.size();
   if (hipMalloc((void **)&m->d_w, m->w_bytes) != hipSuccess) return fail(NT_ENOMEM, "hipMalloc of %zu weight bytes failed", m->w_bytes);
@@ -800,12 +807,22 @@ int nt_load_weights(const nt_config *cfg, const void *h_blob_fp16, size_t blob_b
                                   cfg->max_len, d, parts, m->d_table, s));
     m->dec_table = nt::Dec1Table{m->d_table, parts, cfg->max_len};
   }
-  if (fold_all) {
+  if (fold_dec) {
     const DecLayer &L = m->dec[0];
+    nt::Dec1FoldVectors v{};
+    v.ln2 = nt::GemmLayerNorm{L.ln2.g, L.ln2.b, nt::LnEps{}}; v.lnf = nt::GemmLayerNorm{m->dec_final.g, m->dec_final.b, nt::LnEps{}};
+    if (ffn_inside_layer(m, L)) v.ln3 = nt::GemmLayerNorm{L.ln3.g, L.ln3.b, nt::LnEps{}};
+    v.fold_scale = L.self.vo_scale; v.fold_bias = L.self.bvo;
     const nt::CrossFoldWeights w{L.cross.Wkv, L.cross.Wq, L.cross.Wo, L.cross.bkv, L.cross.bq, L.cross.bo, m->enc_final.g, m->enc_final.b,
                                  L.ln2.g, L.ln2.b, 1.0f / std::sqrt((float)d)};
-    HIP_TRY(nt::cross_fold_build(w, d, m->d_w + o_fold, s));
-    m->fold = nt::cross_fold_at(m->d_w + o_fold, d);
+    if (fold_all) {
+      HIP_TRY(nt::cross_fold_build(w, d, m->d_w + o_fold, s));
+      m->fold = nt::cross_fold_at(m->d_w + o_fold, d);
+      v.gamma2 = m->fold.gamma2; v.beta2 = m->fold.beta2; v.cross_scale = m->fold.value_scale; v.cross_const = m->fold.value_const;
+    }
+    v.pe = m->pe; v.table = m->dec_table; v.vocab = V;
+    m->fold_vectors = (float *)(m->d_w + o_vec);
+    HIP_TRY(nt::launch_dec1_fold_vectors(v, d, m->fold_vectors, s));
   }
   m->vw.Wt = m->Wout; m->vw.Wp = m->Wout_frag; m->vw.N = V; m->vw.K = d;
   if (m->Wout_frag && !cfg->q8_output) {
@@ -1192,18 +1209,18 @@ int decode_step(nt_model *m, DecodeCursor &cu, hipStream_t s) {
         } else if ((rc = dec_gemm(K_GEMM_DEC_QKV, m->z, d, L.self.Wqkv, L.self.Wqkv_p, 3 * d, &L.ln1, e))) return rc;
         if (layer1) {
           // everything between the projection and the output layer in one launch; an FFN as wide as the model is part of it
-          const bool ffn_inside = m->kv_i16 && F == d && L.ffn.W1_p != nullptr && L.ffn.W2_p != nullptr;
+          const bool ffn_inside = ffn_inside_layer(m, L);
           const bool to_final = last && (F == 0 || ffn_inside) && !c.q8_output;
           nt::Dec1Args at{};
           if (by_table) { at.table = m->dec_table; at.sb = start; at.tok_in = eos ? m->eos_tok : nullptr; }
           at.rows = R; at.shape_rows = rows_for_choice; at.origin = origin; at.eps = lne; at.z = m->z; at.write_z = !to_final;
           at.q = m->q32; at.kv_new = m->kv_new; at.self_kv = m->self_kv[l]; at.self_sc = m->self_sc[l];
           at.self_positions = T; at.n_keys = t + 1; at.heads = heads_layer ? H : 1; at.rk = L.self.rk; at.clip = c.rpr_clip;
-          at.Wo_self = L.self.Wo_p; at.bo_self = m->folded ? L.self.bvo : L.self.bo; at.fold_scale = L.self.vo_scale; at.Wq = L.cross.Wq_p; at.bq = L.cross.bq; at.Wo_cross = L.cross.Wo_p;
+          at.Wo_self = L.self.Wo_p; at.bo_self = L.self.bo; at.Wq = L.cross.Wq_p; at.bq = L.cross.bq; at.Wo_cross = L.cross.Wo_p;
           at.bo_cross = L.cross.bo; at.q_scale = qscale; at.ln2 = nt::GemmLayerNorm{L.ln2.g, L.ln2.b, lne};
-          if (m->folded == 2) {
-            at.ln2 = nt::GemmLayerNorm{m->fold.gamma2, m->fold.beta2, lne};
-            at.bo_cross = m->fold.value_const; at.cross_scale = m->fold.value_scale;
+          if (m->folded) {
+            at.fold_const = nt::dec1_fold_const(m->fold_vectors, d, m->folded);
+            at.fold_pos = nt::dec1_fold_pos(m->fold_vectors, d);
           }
           at.folded = m->folded; at.cross_positions = S; at.len = m->len;
           at.cross_kv = m->folded == 1 ? (const void *)m->cross_fold[l] : m->cross[l];

@@ -569,13 +569,17 @@ struct Dec1Args {
   GemmLayerNorm ln2;
   const void *cross_kv;  // integers with scales in cross_sc, or (folded == 1) fp32 [position][2 d] with one constant per key in
   const float *cross_sc; // cross_sc: keys multiplied by the query matrix and scale, values by the output matrix (+ bias)
-  // folded: the self values (kv_new, self cache) then are already multiplied by the output matrix, too, column j divided by
-  // fold_scale[j]; bo_self is the whole constant, b_v W_o + b_o.  Neither a bias nor the columns' different sizes may enter the
-  // cache: its integers have one scale per vector, which the largest element sets for all.
+  // folded: the self values then are already multiplied by the output matrix, too, column j divided by a scale; the whole constant of the
+  // self context is b_v W_o + b_o.  Neither a bias nor the columns' different sizes may enter the cache: its integers have one scale per
+  // vector, which the largest element sets for all.
   // folded == 2: the cross cache as integers of the products (CrossFold; {key scale, value scale, key's constant, unused} per
-  // position in cross_sc); ln2 is CrossFold's, bo_cross and cross_scale its value_const and value_scale
+  // position in cross_sc).
+  // What a row's start and its contexts need besides the row, one behind the other as a workgroup stages it (dec1_fold_vectors):
+  // fold_const: gain and offset before the cross-attention, [before the FFN,] of the final normalisation; scale and constant of the self
+  // context, of the cross context (folded == 2); the table's constants of query, key and value.
+  // fold_pos [position][4]: the table's query, key and value of a position, and the embedding's offset
   int folded;
-  const float *fold_scale, *cross_scale;
+  const float *fold_const, *fold_pos;
   long cross_positions;
   const int32_t *len;    // keys of each cache row
   // FFN of width d (W1 == nullptr: none, or not part of this launch)
@@ -590,6 +594,19 @@ struct Dec1Args {
   ScoutOut scout;
 };
 hipError_t launch_dec1(const Dec1Args &a, int d, hipStream_t s);
+// dst [dec1_fold_vectors_bytes] <- the above, at load: constants (of folded == 1, then of folded == 2 if fold2), then positions
+struct Dec1FoldVectors {
+  GemmLayerNorm ln2, ln3, lnf;         // ln3.gamma == nullptr: no FFN inside the layer
+  const float *fold_scale, *fold_bias; // of the self context
+  const float *gamma2, *beta2, *cross_scale, *cross_const;  // folded == 2 (gamma2 == nullptr: not used)
+  const float *pe;
+  Dec1Table table;
+  int vocab;
+};
+size_t dec1_fold_vectors_bytes(int d, int max_len);
+hipError_t launch_dec1_fold_vectors(const Dec1FoldVectors &v, int d, float *dst, hipStream_t s);
+const float *dec1_fold_const(const float *vectors, int d, int folded);
+const float *dec1_fold_pos(const float *vectors, int d);
 constexpr int kDec1FoldRows = 512, kDec1FoldTokens = 32768;
 // What larger batches of one-layer one-head decoders fold (nt_cross_fold.hip): the encoder's final normalisation without gain and offset
 // times [gain (Wk Wq^T) | gain (Wv Wo)], each column divided by its size, and what that leaves for the decoder.
