@@ -82,6 +82,7 @@
 #include <type_traits>
 
 #include "nt_kernels.h"
+#include "nt_pick.h"
 
 namespace nt {
 
@@ -439,7 +440,8 @@ struct D1Token {
     if (a.tok_in) {
       if (row < a.rows) tok = a.tok_in[row];
     } else if (b.t > 0 && row < b.rows_prev) {
-      if (b.prev_cert) {
+      if (b.prev_cert == kPrevPick) {
+      } else if (b.prev_cert) {
         tok = b.tok[row];
         slot = b.slot_of_row[row];
       } else if (b.pk) {
@@ -449,14 +451,17 @@ struct D1Token {
       }
     }
   }
-  __device__ __forceinline__ int resolve(const Dec1Args &a, int row, bool first_wave, int lane) {
+  // picked: the row's key, where the launch has picked it
+  __device__ __forceinline__ int resolve(const Dec1Args &a, int row, bool first_wave, int lane, unsigned long long picked) {
     const StepBeginArgs &b = a.sb;
     int y = tok;
     if (!a.tok_in) {
       if (b.t == 0) {
         y = b.bos_id;
       } else if (row < b.rows_prev && (b.prev_cert || b.pk)) {
-        if (b.prev_cert) {
+        if (b.prev_cert == kPrevPick) {
+          y = (int)(0xFFFFFFFFu - (unsigned int)picked);
+        } else if (b.prev_cert) {
           if (slot >= 0) y = (int)(0xFFFFFFFFu - (unsigned int)b.final_key[slot]);
         } else {
           unsigned long long top = 0ull;
@@ -563,6 +568,8 @@ __global__ __launch_bounds__(NWAVES * 64) void dec1_kernel(Dec1Args a) {
   // fold_pos what goes by the position (VP)
   constexpr int VC = NV, VS = VC + 4, VP = VS + 3, NVT = FOLD ? VP + 4 : NV, NVW = (NVT + NWAVES - 1) / NWAVES;
   __shared__ __attribute__((aligned(16))) float sNorm[NVT * D];
+  constexpr bool PICKS = WR > 1 && !IND && !HEADS;  // dec1_picks; the EOS mode's steps start with launches that want the tokens
+  __shared__ typename std::conditional<PICKS, PickShared<D, PICKS ? RW : 1, NWAVES>, int>::type sPick;
   __shared__ float sRel[HEADS ? RW * (D1_MAX_CLIP + 1) * 8 : 1];                  // per row: [distance][head]
   const int tid = threadIdx.x, lane = tid & 63, h = lane >> 4, c16 = lane & 15;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -585,6 +592,13 @@ __global__ __launch_bounds__(NWAVES * 64) void dec1_kernel(Dec1Args a) {
       norm_src[u] = i < NV ? (i & 1 ? of.beta : of.gamma) : nullptr;  // (no final one: nullptr)
     }
     if (norm_src[u]) d1_load<NE>(norm_src[u] + lane * NE, norm[u]);
+  }
+  unsigned long long picked = 0ull;
+  if constexpr (PICKS) {
+    if (a.sb.prev_cert == kPrevPick) {
+      pick_rows<D, RW, NWAVES>(a.sb.pick, sPick, row0, a.sb.rows_prev);
+      picked = sPick.best[rw];
+    }
   }
   const int r = valid ? row0 + rw : 0;
   int rc = r;
@@ -798,7 +812,7 @@ __global__ __launch_bounds__(NWAVES * 64) void dec1_kernel(Dec1Args a) {
     // ---- folded: start of the row, two attentions; the row stays in the registers of all its waves, each of which merges their partial
     // softmaxes for itself, so that an attention costs one exchange ----
     typedef std::integral_constant<bool, (AHEAD > 0)> Ahead;
-    const int y = token.resolve(a, row0 + rw, pg == 0, lane);
+    const int y = token.resolve(a, row0 + rw, pg == 0, lane, picked);
     if (row0 >= a.rows) return;  // rows that were kept to collect their last tokens
     typedef _Float16 halfNE __attribute__((ext_vector_type(NE)));
     const float *by_token = a.table.rows + (long)y * a.table.parts * D + lane * NE;
@@ -949,7 +963,7 @@ __global__ __launch_bounds__(NWAVES * 64) void dec1_kernel(Dec1Args a) {
   // ---- self-attention ----
   if (EARLY) preload(a.Wo_self);
   if (a.table.rows) {
-    const int y = token.resolve(a, row0 + rw, pg == 0, lane);
+    const int y = token.resolve(a, row0 + rw, pg == 0, lane, picked);
     if (row0 >= a.rows) return;  // rows that were kept to collect their last tokens
     first_layer_start<NE>(a, y, lane, pg == 0, q, z, kx, vx);
   } else {
@@ -1165,10 +1179,18 @@ static hipError_t d1_launch(const Dec1Args &a, hipStream_t s) {
   return hipGetLastError();
 }
 
+// The pick of the last step's arg-max inside the layer saves its launch: 400 rows of 30 tokens 2.76 -> 2.67 ms, 320 of 150 13.6 -> 13.2, 700 of 40
+// 3.91 -> 3.82, 45 of 22 1.94 -> 1.89, with an FFN 300 / 700 rows of 30 2.65 -> 2.57 / 3.90 -> 3.74 (batches alone); 4,096- and
+// 16,384-token budgets 18.4 -> 18.2 and 49.5 -> 46.2 ms.  Not where a row has one wave for it, nor with eight heads (the 30 + 6 layer teacher's
+// batch of 250 rows 20.4 -> 20.6 ms: sixteen waves wait for four rows' picks in one layer of six).
+bool dec1_picks(int shape_rows, int heads) { return heads <= 1 && shape_rows < 1024; }
+
 hipError_t launch_dec1(const Dec1Args &a, int d, hipStream_t s) {
   if (a.rows <= 0) return hipSuccess;
   const bool ffn = a.W1 != nullptr;
   if (a.folded && !a.table.rows) return hipErrorInvalidValue;
+  if (a.table.rows && a.sb.prev_cert == kPrevPick && (a.origin || a.tok_in || !dec1_picks(a.shape_rows > 0 ? a.shape_rows : a.rows, a.heads)))
+    return hipErrorInvalidValue;
   if (a.heads > 1) {
     if (!dec1_heads_supported(d, a.heads) || ffn || a.folded || a.clip > D1_MAX_CLIP) return hipErrorInvalidValue;
     return d1_launch<512, false, true>(a, s);

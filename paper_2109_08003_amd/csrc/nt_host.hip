@@ -1030,6 +1030,8 @@ struct DecodeCursor {
   float *d_logits = nullptr;
   int t = 0, partials_prev = 0, rows_prev = 0;
   bool prev_cert = false, finished = false;
+  bool prev_pick = false;  // the scout of the last step has run, the pick starts the next one
+  nt::PickArgs pick{};
   // EOS mode (eos_id >= 0)
   int32_t eos_id = -1;
   int32_t *d_out_len = nullptr;
@@ -1114,8 +1116,8 @@ int decode_step(nt_model *m, DecodeCursor &cu, hipStream_t s) {
       a.pk = d_logits ? nullptr : m->pk; a.n_partials = partials_prev; a.out = d_out; a.out_ld = T;
       a.forced = d_forced; a.forced_ld = T; a.E = m->E; a.pe = m->pe; a.gamma = m->dec[0].ln1.g; a.beta = m->dec[0].ln1.b;
       a.eps = lne; a.z = m->z; a.a = nullptr; a.flags = m->flags;
-      a.prev_cert = prev_cert ? 1 : 0; a.tok = m->tok; a.slot_of_row = m->slot_of_row; a.final_key = m->final_key;
-      a.cert_count = m->flags + 4;
+      a.prev_cert = cu.prev_pick ? nt::kPrevPick : prev_cert ? 1 : 0; a.tok = m->tok; a.slot_of_row = m->slot_of_row; a.final_key = m->final_key;
+      a.cert_count = m->flags + 4; a.pick = cu.pick;
       if (d_logits && rows_now == 0) { cu.finished = true; return NT_OK; }  // no tokens to collect in this mode (pk == nullptr)
       if (!fused_start)
         KT(K_STEP_BEGIN, rows_prev * (partials_prev * 8.0 + 4) + rows_now * dd * 14, rows_now * dd * 10,
@@ -1318,7 +1320,7 @@ int decode_step(nt_model *m, DecodeCursor &cu, hipStream_t s) {
         const int np_ = nt::vocab_q8_partials(R);
         KT(K_VOCAB_ARGMAX, (double)V * dd + Rd * dd + Rd * np_ * 8, 2 * Rd * dd * V,
            nt::launch_vocab_q8_argmax(m->q8_codes, m->q8_c, m->q8_sa, R, m->Wq8, m->q8_consts, V, d, m->pk, s));
-        cu.prev_cert = false;
+        cu.prev_cert = cu.prev_pick = false;
         cu.partials_prev = np_;
       }
       return NT_OK;
@@ -1335,12 +1337,17 @@ int decode_step(nt_model *m, DecodeCursor &cu, hipStream_t s) {
          nt::launch_gemm(nt::A_PLANES, true, h_hi, h_lo, d, m->Wout, R, V, d, e, s));
     } else {
       cu.prev_cert = certified;
+      // The next step's first layer picks among the scout's candidates where its form does, unless there is no next step or its start is a
+      // launch that wants the tokens
+      const int rows_next = eos ? 0 : rows_at(cu, cu.t);
+      cu.prev_pick = certified && scouted && !d_forced && layer1 && rows_next > 0 && nt::dec1_picks(rows_next, heads_layer ? H : 1) &&
+                     nt::vocab_scout_one_launch(V, R);
       const int np_ = nt::vocab_argmax_partials(m->vw, R, cu.prev_cert, wide);
       if (cu.prev_cert)
         KT(K_VOCAB_ARGMAX, scouted ? (double)V * dd + Rd * dd * 5 + Rd * V * 0.5 : (double)V * dd * 2 + Rd * dd * 4 + Rd * np_ * 8, 2 * Rd * dd * V,
            nt::launch_vocab_argmax_certified(nt::VocabScout{m->Wscout, m->scout_codes, m->scout_rc, m->scout_scratch}, h_hi, h_lo, d, m->vw,
                                              R, m->lo_norm, m->w_norm_max, m->pk, m->ps, m->tok, m->slot_of_row, m->cert_list, m->flags + 4,
-                                             m->final_key, s));
+                                             m->final_key, cu.prev_pick ? &cu.pick : nullptr, s));
       else
         KT(K_VOCAB_ARGMAX_SMALL, (double)V * dd * 2 + Rd * dd * 4 + Rd * np_ * 8, 2 * Rd * dd * V,
            nt::launch_vocab_argmax(h_hi, h_lo, d, m->vw, R, m->pk, wide, s));

@@ -305,9 +305,22 @@ __device__ __forceinline__ void scout_levels(const ScoutOut &o, int lane, unsign
   for (int w = 0; w < NE / 4; w++) level[w] = ((const unsigned int *)(o.levels + lane * NE))[w];
 }
 #endif
-// Results: tok[m], and slot_of_row[m] = -1.  distrust: every row has every logit computed.
+// What the second half, the pick, reads (nt_pick.h)
+struct PickArgs {
+  const void *part;            // the scout's groups
+  const float4 *row_consts, *strip_consts;
+  const int32_t *ids;
+  int NS, row0;
+  float distrust;
+  const _Float16 *h_hi, *h_lo; // the states
+  long ldh;
+  const _Float16 *Ws;          // the matrix in the scout's order
+};
+// Results: tok[m], and slot_of_row[m] = -1.  distrust: every row has every logit computed.  later: only the scout runs; the first decoder
+// layer of the next step picks (StepBeginArgs::pick), which takes rows that are one launch.
+bool vocab_scout_one_launch(int N, int rows);
 hipError_t launch_vocab_scout(const VocabScout &v, const _Float16 *h, const _Float16 *h_lo, long ldh, const VocabWeights &w, int M,
-                              bool distrust, int32_t *tok, int32_t *slot_of_row, hipStream_t s);
+                              bool distrust, int32_t *tok, int32_t *slot_of_row, PickArgs *later, hipStream_t s);
 
 // Same result as launch_vocab_argmax for many rows, usually at less work: the scout above, or (tiled kernels) a head-only
 // pass whose winner is certified against a rigorous bound on the contribution of the tail (lo_norm[m] = ||tail of row m||,
@@ -319,7 +332,7 @@ bool vocab_scouted(const VocabWeights &w, bool wide);  // the scout is the kerne
 hipError_t launch_vocab_argmax_certified(const VocabScout &v, const _Float16 *h, const _Float16 *h_lo, long ldh,
                                          const VocabWeights &w, int M, const float *lo_norm, float w_norm_max,
                                          unsigned long long *pk, float *ps, int32_t *tok, int32_t *slot_of_row, int32_t *list,
-                                         int32_t *count, unsigned long long *final_key, hipStream_t s);
+                                         int32_t *count, unsigned long long *final_key, PickArgs *later, hipStream_t s);
 
 // the tiled implementations (nt_gemm.hip) and their certification kernel
 int vocab_argmax_partials_tiled(int M, int N);
@@ -405,11 +418,14 @@ struct StepBeginArgs {
   int32_t *flags;
   // certified arg-max of the previous step (prev_cert != 0): token = tok[r], or the key in
   // final_key[slot_of_row[r]] when the row had to be recomputed; cert_count is cleared for this step
+  // prev_cert == kPrevPick: the token is picked here (first decoder layer in one launch, dec1_picks)
   int prev_cert;
   const int32_t *tok, *slot_of_row;
   const unsigned long long *final_key;
   int32_t *cert_count;
+  PickArgs pick;
 };
+constexpr int kPrevPick = 2;
 hipError_t launch_step_begin(const StepBeginArgs &a, hipStream_t s);
 
 // ---- fused decoder-step kernels (nt_decoder.hip), model widths 256 / 512 ----------------------------------------
@@ -607,6 +623,8 @@ size_t dec1_fold_vectors_bytes(int d, int max_len);
 hipError_t launch_dec1_fold_vectors(const Dec1FoldVectors &v, int d, float *dst, hipStream_t s);
 const float *dec1_fold_const(const float *vectors, int d, int folded);
 const float *dec1_fold_pos(const float *vectors, int d);
+// whether the layer's form for so many rows takes the pick of the previous step's arg-max into its start
+bool dec1_picks(int shape_rows, int heads);
 constexpr int kDec1FoldRows = 512, kDec1FoldTokens = 32768;
 // What larger batches of one-layer one-head decoders fold (nt_cross_fold.hip): the encoder's final normalisation without gain and offset
 // times [gain (Wk Wq^T) | gain (Wv Wo)], each column divided by its size, and what that leaves for the decoder.

@@ -158,12 +158,13 @@ hipError_t launch_vocab_argmax(const _Float16 *h, const _Float16 *h_lo, long ldh
 hipError_t launch_vocab_argmax_certified(const VocabScout &v, const _Float16 *h, const _Float16 *h_lo, long ldh,
                                          const VocabWeights &w, int M, const float *lo_norm, float w_norm_max,
                                          unsigned long long *pk, float *ps, int32_t *tok, int32_t *slot_of_row, int32_t *list,
-                                         int32_t *count, unsigned long long *final_key, hipStream_t s) {
+                                         int32_t *count, unsigned long long *final_key, PickArgs *later, hipStream_t s) {
   if (M <= 0) return hipSuccess;
+  if (!use_stream(w) && later) return hipErrorInvalidValue;
   if (!use_stream(w))
     return launch_vocab_argmax_certified_tiled(h, h_lo, ldh, w.Wt, M, w.N, w.K, lo_norm, w_norm_max, pk, ps, tok,
                                                slot_of_row, list, count, final_key, s);
-  return launch_vocab_scout(v, h, h_lo, ldh, w, M, w_norm_max > 1e29f, tok, slot_of_row, s);
+  return launch_vocab_scout(v, h, h_lo, ldh, w, M, w_norm_max > 1e29f, tok, slot_of_row, later, s);
 }
 
 }  // namespace nt

@@ -1393,3 +1393,28 @@ def test_integer_folded_cross_caches_are_as_exact_as_the_others(nt, oracle, torc
     print(f"{what}, ffn {ffn}: 60 rows {rms[60]:.1e}, 600 rows {rms[600]:.1e}")
     assert rms[600] <= min(1.3 * rms[60], 4e-5)
     gm.close()
+
+
+@pytest.mark.parametrize("kw", [dict(), dict(dec_d_ffn=512), dict(d_model=256), dict(n_dec=2), dict(n_heads=8)])
+@pytest.mark.parametrize("rows", [33, 65, 257, 530, 1030])
+def test_arg_max_picked_inside_the_layer(nt, kw, rows):
+    """The first decoder layer picks the last step's token among the scout's candidates, in every form that does, while rows end at
+    different steps and the form changes with their number: the same tokens as the EOS mode, whose picks are launches of their own,
+    with an end symbol that is never emitted.  Also with every logit computed (no bound trusted)."""
+    vocab = 21000  # (a smaller one has more rows in the few-row kernel)
+    cfg = nt_synth.model_config("C1", vocab=vocab, n_enc=1, **kw)
+    gm = nt.Model(cfg, nt_synth.make_weights(cfg, seed=31, random_affine=True), max_batch_tokens=16384, pipeline_lanes=1)
+    rng = np.random.default_rng(rows)
+    lens = rng.integers(1, 13, size=rows)
+    tokens = rng.integers(4, vocab, size=int(lens.sum())).astype(np.int32)
+    offsets = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+    out, _ = gm.translate_batch(tokens, offsets, token_budget=16384)
+    never = int(np.setdiff1d(np.arange(4, vocab), out)[0])
+    by_eos, _, out_len = gm.translate_batch_eos(tokens, offsets, 16384, never)
+    assert np.array_equal(by_eos, out) and int(out_len.sum()) == out.size
+    n = min(rows, 40)
+    few = [gm.translate_batch(tokens[:offsets[n]], offsets[:n + 1], token_budget=16384)[0]]
+    gm.debug_set_cert_distrust(True)
+    few.append(gm.translate_batch(tokens[:offsets[n]], offsets[:n + 1], token_budget=16384)[0])
+    assert np.array_equal(few[0], few[1])
+    gm.close()
