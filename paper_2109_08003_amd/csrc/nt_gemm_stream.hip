@@ -97,11 +97,12 @@ __device__ __forceinline__ void gs_normalise(const float (&xv)[RPW][NE], const G
 // NC > 1: the contraction runs over NC * K columns of A in NC passes over the K-wide tile (K = 512, planes from memory):
 // between passes the tile is refilled behind a barrier while the weight ring keeps streaming, and every wave keeps the
 // accumulators of its one strip (N is 512 per column group) - the second matrix of an FFN, whose K is the FFN width.
-template <int RB, int K, bool C_F32, bool LN, bool TAIL, int NC, int NB>
+// CHAIN: the rows that are normalised are made here, x += A * Wo^T + bias (A: planes, Wo: K x K), see GemmChain.
+template <int RB, int K, bool C_F32, bool LN, bool TAIL, int NC, int NB, bool CHAIN = false>
 __global__ __launch_bounds__(GS_WAVES * 64) void gemm_stream_kernel(const _Float16 *__restrict__ A_hi,
                                                                    const _Float16 *__restrict__ A_lo, long lda, int M,
                                                                    const _Float16 *__restrict__ Wp, int N, int col_groups,
-                                                                   GemmEpilogue e, GemmLayerNorm ln) {
+                                                                   GemmEpilogue e, GemmLayerNorm ln, GemmChain ch) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   _Float16 *sh = (_Float16 *)smem;
   constexpr int TM = 32 * RB, ROWS = (TAIL ? 2 : 1) * TM;  // LDS fragment rows: head rows, then tail rows
@@ -115,6 +116,7 @@ __global__ __launch_bounds__(GS_WAVES * 64) void gemm_stream_kernel(const _Float
   constexpr int NOPS = (TAIL ? 2 : 1) * RB;
   static_assert(KS % SL == 0, "the ring of W slots must divide the k-steps of a strip");
   static_assert(NC == 1 || (K == 512 && !LN), "several passes: 512-wide tiles of planes only");
+  static_assert(!CHAIN || (K == 512 && LN && TAIL && NC == 1 && NB == 2), "the chain's tile has both planes of 512 columns");
   constexpr int KST = NC * KS;  // k-steps of a whole strip
   const int tid = threadIdx.x, lane = tid & 63, li = lane & 31, g = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -159,7 +161,118 @@ __global__ __launch_bounds__(GS_WAVES * 64) void gemm_stream_kernel(const _Float
           (__attribute__((address_space(3))) void *)(sh + R * LD), 16, 0, RB == 2 ? 2 : 0);
     }
   };
-  if constexpr (LN) {
+  floatx16 acc[RB][NB];
+  // fragment row of operand op: head rows of block op % RB, then the tail rows; two base registers, because the
+  // byte offsets of the upper half do not fit the 16-bit offset field
+  const _Float16 *hrow = sh + li * LD + g * 8;
+  constexpr int HALF = ROWS > 32 ? ROWS / 2 : ROWS;  // LDS rows reached from the first base register
+  int off2 = HALF * LD;
+  asm volatile("" : "+v"(off2));
+  const _Float16 *hrow2 = hrow + off2;
+  auto frag = [&](int op, int ks) -> half8 {
+    const int R0 = op * 32;  // ops 0 .. RB-1: head planes, RB .. 2RB-1: tail planes
+    return *(const half8 *)((R0 < HALF ? hrow : hrow2) + (R0 % HALF) * LD + ks * 16);
+  };
+  half8 hf[NOPS];
+  if constexpr (CHAIN) {
+    // The projection before: one strip of 64 columns per wave, both planes; its ring runs on into this product's first strip.  The
+    // product goes through the LDS, where the planes were, to be normalised as rows that come from memory are: the same sums in
+    // the same order as two launches.
+    constexpr int NE = K / 64, RPW = TM / GS_WAVES, LDX = K + 8;
+    typedef float f32x4 __attribute__((ext_vector_type(4)));
+    const __amdgpu_buffer_rsrc_t ors = __builtin_amdgcn_make_buffer_rsrc((void *)ch.Wo, 0, K * K * 2, 0x00020000);
+    auto oload = [&](int soff, int nb) -> half8 {
+      return __builtin_bit_cast(half8, (u32x4)__builtin_amdgcn_raw_buffer_load_b128(ors, wlane + nb * 1024, soff, 0));
+    };
+    const int ocur = wave * (KS * 2048), onext = strip_at(strip);
+    float obias[NB], xv[RPW][NE];
+    fill_planes(0);
+#pragma unroll
+    for (int nb = 0; nb < NB; nb++) obias[nb] = ch.bias[wave * 64 + nb * 32 + li];
+#pragma unroll
+    for (int q = 0; q < LA; q++)
+#pragma unroll
+      for (int nb = 0; nb < NB; nb++) wb[q][nb] = oload(ocur + q * 2048, nb);
+    __builtin_amdgcn_s_waitcnt(0x0F70);
+    __syncthreads();
+    auto request_rows = [&]() {
+#pragma unroll
+      for (int i = 0; i < RPW; i++) {
+        const float *xr = ch.x + (long)min(m0 + wave + GS_WAVES * i, M - 1) * K + lane * NE;
+#pragma unroll
+        for (int j = 0; j < NE; j += 4) {
+          const f32x4 t = *(const f32x4 *)(xr + j);
+          xv[i][j] = t[0], xv[i][j + 1] = t[1], xv[i][j + 2] = t[2], xv[i][j + 3] = t[3];
+        }
+      }
+    };
+#pragma unroll
+    for (int op = 0; op < NOPS; op++) hf[op] = frag(op, 0);
+#pragma unroll
+    for (int ks = 0; ks < KS; ks++) {
+      const int tgt = ks + LA;
+      // the residual rows, behind the last fragments of this product: nothing of it waits for them (from the start 1 to 2 % slower).
+      // Cached, unlike the rows of the other form: 16,375 tokens 841 -> 797 us a whole encoder
+      if (tgt == KS) {
+        request_rows();
+        __builtin_amdgcn_sched_barrier(0);
+      }
+#pragma unroll
+      for (int op = 0; op < NOPS; op++) {
+#pragma unroll
+        for (int nb = 0; nb < NB; nb++) {
+          if (ks == 0 && op < RB) {
+            const floatx16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+            acc[op % RB][nb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(hf[op], wb[ks % SL][nb], zero, 0, 0, 0);
+          } else {
+            acc[op % RB][nb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(hf[op], wb[ks % SL][nb], acc[op % RB][nb], 0, 0, 0);
+          }
+        }
+        if (ks + 1 < KS) hf[op] = frag(op, ks + 1);
+        if (op == 0) {
+#pragma unroll
+          for (int nb = 0; nb < NB; nb++) wb[tgt % SL][nb] = tgt < KS ? oload(ocur + tgt * 2048, nb) : wload(onext + (tgt - KS) * 2048, nb);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+    __syncthreads();  // every wave is done with the planes: the product takes their place, whole rows of it are read back
+    float *sx = (float *)smem;
+#pragma unroll
+    for (int rb = 0; rb < RB; rb++)
+#pragma unroll
+      for (int nb = 0; nb < NB; nb++)
+#pragma unroll
+        for (int v = 0; v < 16; v++)
+          sx[(rb * 32 + (v >> 2) * 8 + g * 4 + (v & 3)) * LDX + wave * 64 + nb * 32 + li] = acc[rb][nb][v] + obias[nb];
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < RPW; i++)
+#pragma unroll
+      for (int j = 0; j < NE; j += 4) {
+        const f32x4 t = *(const f32x4 *)(sx + (wave + GS_WAVES * i) * LDX + lane * NE + j);
+        xv[i][j] += t[0], xv[i][j + 1] += t[1], xv[i][j + 2] += t[2], xv[i][j + 3] += t[3];
+      }
+    __syncthreads();
+    gs_normalise<NE, RPW, TM, TAIL>(xv, ln, sh, wave, lane);
+    auto put_row = [&](int i) {
+      float *xr = ch.x + (long)(m0 + wave + GS_WAVES * i) * K + lane * NE;
+#pragma unroll
+      for (int j = 0; j < NE; j += 4) {
+        const f32x4 t = {xv[i][j], xv[i][j + 1], xv[i][j + 2], xv[i][j + 3]};
+        if (RB == 2) __builtin_nontemporal_store(t, (f32x4 *)(xr + j));
+        else *(f32x4 *)(xr + j) = t;
+      }
+    };
+    if (__builtin_expect(m0 + TM <= M, 1)) {
+#pragma unroll
+      for (int i = 0; i < RPW; i++) put_row(i);
+    } else {
+#pragma unroll
+      for (int i = 0; i < RPW; i++)
+        if (m0 + wave + GS_WAVES * i < M) put_row(i);
+    }
+  } else if constexpr (LN) {
     // a wave takes rows wave, wave + 8, ...; a lane holds NE consecutive elements of the row
     constexpr int NE = K / 64, RPW = TM / GS_WAVES;
     const float *X = (const float *)A_hi;
@@ -206,8 +319,10 @@ __global__ __launch_bounds__(GS_WAVES * 64) void gemm_stream_kernel(const _Float
       *(u32x4 *)(sh + R * LD + kc * 8) = fr[i];
     }
   }
-  if (NB == 2) preload();
-  __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): this wave's rows have landed in the LDS before the barrier
+  if (!CHAIN) {
+    if (NB == 2) preload();
+    __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): this wave's rows have landed in the LDS before the barrier
+  }
   __syncthreads();
   if (!have) {
     if (NC > 1) {  // a wave without a strip still fills its rows of every pass
@@ -226,19 +341,6 @@ __global__ __launch_bounds__(GS_WAVES * 64) void gemm_stream_kernel(const _Float
   // idles.  Giving one of them priority makes the phases alternate instead.
   if (wave < GS_WAVES / 2) __builtin_amdgcn_s_setprio(2);
 
-  floatx16 acc[RB][NB];
-  // fragment row of operand op: head rows of block op % RB, then the tail rows; two base registers, because the
-  // byte offsets of the upper half do not fit the 16-bit offset field
-  const _Float16 *hrow = sh + li * LD + g * 8;
-  constexpr int HALF = ROWS > 32 ? ROWS / 2 : ROWS;  // LDS rows reached from the first base register
-  int off2 = HALF * LD;
-  asm volatile("" : "+v"(off2));
-  const _Float16 *hrow2 = hrow + off2;
-  auto frag = [&](int op, int ks) -> half8 {
-    const int R0 = op * 32;  // ops 0 .. RB-1: head planes, RB .. 2RB-1: tail planes
-    return *(const half8 *)((R0 < HALF ? hrow : hrow2) + (R0 % HALF) * LD + ks * 16);
-  };
-  half8 hf[NOPS];
 #pragma unroll
   for (int op = 0; op < NOPS; op++) hf[op] = frag(op, 0);
 
@@ -582,10 +684,10 @@ __global__ __launch_bounds__(GS_WAVES * 64) void gemm_ffn_kernel(float *__restri
 // workgroups per row tile with 32-column strips: four strips each, or two where N is an odd multiple of 64
 static int gs_narrow_groups(int N) { return N % 128 == 0 ? N / 128 : N / 64; }
 
-template <int RB, int K, bool C_F32, bool LN, bool TAIL, int NC = 1, int NB = 2>
+template <int RB, int K, bool C_F32, bool LN, bool TAIL, int NC = 1, int NB = 2, bool CHAIN = false>
 static hipError_t gs_launch(const _Float16 *A, const _Float16 *A_lo, long lda, int M, const _Float16 *Wp, int N,
-                            const GemmEpilogue &e, const GemmLayerNorm &ln, hipStream_t s) {
-  auto kern = gemm_stream_kernel<RB, K, C_F32, LN, TAIL, NC, NB>;
+                            const GemmEpilogue &e, const GemmLayerNorm &ln, hipStream_t s, const GemmChain &ch = GemmChain{}) {
+  auto kern = gemm_stream_kernel<RB, K, C_F32, LN, TAIL, NC, NB, CHAIN>;
   const size_t lds = (size_t)(TAIL ? 64 : 32) * RB * (K + 8) * 2;
   // raising the dynamic LDS limit is per kernel, once per process (several host threads may get here at once)
   static std::once_flag once;
@@ -602,7 +704,7 @@ static hipError_t gs_launch(const _Float16 *A, const _Float16 *A_lo, long lda, i
   // a round: the same both ways).
   int col_groups = 1;
   long best = 0;
-  for (int cg = 1; cg * GS_WAVES <= NS; cg++) {
+  for (int cg = 1; cg * GS_WAVES <= NS && !CHAIN; cg++) {
     if (NS % cg != 0) continue;
     const long cost = ((long)row_tiles * cg + 255) / 256 * (1 + (NS / cg + GS_WAVES - 1) / GS_WAVES);
     if (best == 0 || cost < best) best = cost, col_groups = cg;
@@ -610,7 +712,7 @@ static hipError_t gs_launch(const _Float16 *A, const _Float16 *A_lo, long lda, i
   if (NC > 1) col_groups = NS / GS_WAVES;  // several passes: exactly one strip per wave
   if (NB == 1) col_groups = gs_narrow_groups(N);
   hipLaunchKernelGGL(kern, dim3(row_tiles * col_groups), dim3(GS_WAVES * 64), lds, s, A, A_lo, lda, M, Wp, N, col_groups, e,
-                     ln);
+                     ln, ch);
   return hipGetLastError();
 }
 
@@ -755,6 +857,16 @@ hipError_t launch_gemm_ffn(float *x, int M, int F, const GemmLayerNorm &ln, cons
 hipError_t launch_gemm_stream(bool c_f32, const _Float16 *A, const _Float16 *A_lo, long lda, const _Float16 *Wp, int M,
                               int N, int K, const GemmEpilogue &e, hipStream_t s, bool tail) {
   return gs_dispatch<false>(c_f32, A, A_lo, lda, Wp, M, N, K, e, GemmLayerNorm{}, tail && A_lo != nullptr, s);
+}
+
+bool gemm_chain_supported(int M, int N, int K) { return K == 512 && N % 512 == 0 && M > kChainRows; }
+
+hipError_t launch_gemm_chain(const _Float16 *A, const _Float16 *A_lo, long lda, const GemmChain &ch, const GemmLayerNorm &ln, const _Float16 *Wp, int M,
+                             int N, const GemmEpilogue &e, hipStream_t s) {
+  if (M <= 0) return hipSuccess;
+  if (N <= 0 || N % 512 != 0 || e.n_split % 32 != 0) return hipErrorInvalidValue;
+  return M <= 8192 ? gs_launch<1, 512, true, true, true, 1, 2, true>(A, A_lo, lda, M, Wp, N, e, ln, s, ch)
+                   : gs_launch<2, 512, true, true, true, 1, 2, true>(A, A_lo, lda, M, Wp, N, e, ln, s, ch);
 }
 
 hipError_t launch_gemm_stream_ln(bool c_f32, const float *X, long ldx, const GemmLayerNorm &ln, const _Float16 *Wp, int M,

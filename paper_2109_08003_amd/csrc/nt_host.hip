@@ -904,25 +904,34 @@ int nt_encode(nt_model *m, const int32_t *d_src, const int32_t *d_len, int32_t B
   // With plane pairs and a supported width the LayerNorm runs inside the projection that consumes it (the tile is
   // normalised while it is loaded), otherwise as a kernel of its own.
   auto fused_ln = [&](const _Float16 *Wp, int N) { return kEncF32 && Wp != nullptr && nt::gemm_stream_supported(N, d); };
-  for (auto &L : m->enc) {
-    nt::GemmEpilogue e;
-    e.bias = L.self.bqkv; e.scale = qscale; e.scale_cols = d; e.dst0 = m->qkv; e.ld0 = 3 * d; e.n_split = 3 * d;
-    // bits 4 / 5 / 6 of the plan: the tail plane only for the q / k / v columns (when bit 0 is clear)
-    if (!(m->enc_tails & 1u) && (m->enc_tails & 0x70u)) {
-      const unsigned sel = (m->enc_tails >> 4) & 7u;  // contiguous column groups only: q, k, v, q|k, k|v, q|k|v
-      int g0 = 0, g1 = 3;
-      while (g0 < 3 && !((sel >> g0) & 1u)) g0++;
-      while (g1 > g0 && !((sel >> (g1 - 1)) & 1u)) g1--;
-      e.tail_col0 = g0 * d; e.tail_col1 = g1 * d;
-    }
-    // bit 7 of the plan: the scaled query and the key leave the projection as plain fp16 (q | k in one array, the
-    // value as fp32 behind it in the same buffer) and the attention kernel multiplies them with one MFMA per product
+  // The output projection of a layer without FFN and the next layer's Q|K|V as one launch, where both stream and take their tails
+  // (planes are multiplied whole, the choice of columns is the epilogue's).
+  bool projected = false;  // this layer's q|k|v came with the projection before
+  for (size_t l = 0; l < m->enc.size(); l++) {
+    EncLayer &L = m->enc[l];
     const bool qk16 = (m->enc_tails & 128u) && kEncF32 && fused_ln(L.self.Wqkv_p, 3 * d) &&
                       nt::enc_attention_qk16_supported(S, d, H, L.self.rk);
     _Float16 *qk_half = (_Float16 *)m->qkv;
     float *v_f32 = (float *)((char *)m->qkv + (size_t)m->max_tokens * 2 * d * 2);
-    if (qk16) { e.first_f16 = 1; e.dst0 = qk_half; e.ld0 = 2 * d; e.n_split = 2 * d; e.dst1 = v_f32; e.ld1 = d; }
-    if (fused_ln(L.self.Wqkv_p, 3 * d)) {
+    auto qkv_epilogue = [&](const EncLayer &P) {
+      nt::GemmEpilogue e;
+      e.bias = P.self.bqkv; e.scale = qscale; e.scale_cols = d; e.dst0 = m->qkv; e.ld0 = 3 * d; e.n_split = 3 * d;
+      // bits 4 / 5 / 6 of the plan: the tail plane only for the q / k / v columns (when bit 0 is clear)
+      if (!(m->enc_tails & 1u) && (m->enc_tails & 0x70u)) {
+        const unsigned sel = (m->enc_tails >> 4) & 7u;  // contiguous column groups only: q, k, v, q|k, k|v, q|k|v
+        int g0 = 0, g1 = 3;
+        while (g0 < 3 && !((sel >> g0) & 1u)) g0++;
+        while (g1 > g0 && !((sel >> (g1 - 1)) & 1u)) g1--;
+        e.tail_col0 = g0 * d; e.tail_col1 = g1 * d;
+      }
+      // bit 7 of the plan: the scaled query and the key leave the projection as plain fp16 (q | k in one array, the
+      // value as fp32 behind it in the same buffer) and the attention kernel multiplies them with one MFMA per product
+      if (qk16) { e.first_f16 = 1; e.dst0 = qk_half; e.ld0 = 2 * d; e.n_split = 2 * d; e.dst1 = v_f32; e.ld1 = d; }
+      return e;
+    };
+    const nt::GemmEpilogue e = qkv_epilogue(L);
+    if (projected) {
+    } else if (fused_ln(L.self.Wqkv_p, 3 * d)) {
       KT(K_GEMM_ENC_QKV, gemm_bytes(Md, dd, 3 * dd, 4, qk16 ? 8.0 / 3.0 : ea, false), 6 * Md * dd * dd,
          nt::launch_gemm_stream_ln(true, m->x, d, nt::GemmLayerNorm{L.ln1.g, L.ln1.b, lne}, L.self.Wqkv_p, M, 3 * d, d, e, s,
                                    (m->enc_tails & 0x71u) != 0));
@@ -938,6 +947,15 @@ int nt_encode(nt_model *m, const int32_t *d_src, const int32_t *d_len, int32_t B
     else
     KT(K_ATTN_ENC, Md * 4 * dd * ea, 4.0 * B * S * S * dd,
        nt::launch_enc_attention(m->qkv, kEncF32, m->len, m->ctx_enc, lo_d, B, S, d, H, L.self.rk, c.rpr_clip, s));
+    projected = kEncF32 && F == 0 && l + 1 < m->enc.size() && (m->enc_tails & 2u) && (m->enc_tails & 0x71u) && L.self.Wo_p &&
+                fused_ln(m->enc[l + 1].self.Wqkv_p, 3 * d) && nt::gemm_chain_supported(M, 3 * d, d);
+    if (projected) {
+      const EncLayer &P = m->enc[l + 1];
+      KT(K_GEMM_ENC_QKV, gemm_bytes(Md, dd, dd, ea, 4, true) + gemm_bytes(Md, 0, 3 * dd, 4, qk16 ? 8.0 / 3.0 : ea, false) + 6 * dd * dd, 8 * Md * dd * dd,
+         nt::launch_gemm_chain((const _Float16 *)m->ctx_enc, (const _Float16 *)lo_of(m->ctx_enc, lo_d), d, nt::GemmChain{L.self.Wo_p, L.self.bo, m->x},
+                               nt::GemmLayerNorm{P.ln1.g, P.ln1.b, lne}, P.self.Wqkv_p, M, 3 * d, qkv_epilogue(P), s));
+      continue;
+    }
     nt::GemmEpilogue o;
     o.bias = L.self.bo; o.resid = m->x; o.ldr = d; o.dst0 = m->x; o.ld0 = d; o.n_split = d;
     KT(K_GEMM_ENC_O, gemm_bytes(Md, dd, dd, ea, 4, true), 2 * Md * dd * dd,

@@ -100,6 +100,24 @@ bool gemm_ffn_supported(int M, int d, int F);  // and worth it
 hipError_t launch_gemm_ffn(float *x, int M, int F, const GemmLayerNorm &ln, const _Float16 *W1p, const float *b1, const _Float16 *W2p, const float *b2,
                            hipStream_t s);
 
+// The output projection of an attention and the LayerNorm + projection that follow it, one launch: x += A Wo^T + bias (rows of 512, in
+// place), then as launch_gemm_stream_ln with both planes (e.tail_col0 .. tail_col1) over those rows.  Wp, Wo: vocab_pack order.
+// The launch keeps the rows on the chip where two wrote and read them, 2 KB a row, and fill a tile twice; it stays bound by the phases
+// of its workgroups that follow one another (context in, product, residual in, product with stores between its strips: at 65,536 tokens
+// 275 us where the matrix cores need 110 at the clock they hold and the memory 137).  A tile is a workgroup's from end to end: up to
+// kChainRows rows two launches, which spread one over several, are as fast.  Six layers, one head, no FFN, tokens as sentences
+// of 25, 100 and 200: 2,500 / 3,075 / 4,000 (100) / 4,000 (200) tokens 323 / 324 / 432 / 625 us with it and 293 / 313 / 424 / 613
+// without; 4,100, 5,000, 8,200, 16,375, 32,750, 65,525: 350, 367, 567, 825, 1,345, 2,402 against 371, 392, 612, 883, 1,424, 2,534.
+struct GemmChain {
+  const _Float16 *Wo = nullptr;
+  const float *bias = nullptr;
+  float *x = nullptr;
+};
+constexpr int kChainRows = 4096;
+bool gemm_chain_supported(int M, int N, int K);  // and worth it
+hipError_t launch_gemm_chain(const _Float16 *A, const _Float16 *A_lo, long lda, const GemmChain &ch, const GemmLayerNorm &ln, const _Float16 *Wp, int M,
+                             int N, const GemmEpilogue &e, hipStream_t s);
+
 // Decoder-step variant for small M (fp32 A and C): 32 x 32 tiles, whole-K operand panels loaded
 // in one round trip.  If ln_g != nullptr the rows of A are LayerNorm-ed first (requires K to be
 // the row width, 256 or 512).  K must be a multiple of 256.

@@ -1418,3 +1418,32 @@ def test_arg_max_picked_inside_the_layer(nt, kw, rows):
     few.append(gm.translate_batch(tokens[:offsets[n]], offsets[:n + 1], token_budget=16384)[0])
     assert np.array_equal(few[0], few[1])
     gm.close()
+
+
+@pytest.mark.parametrize("heads,tails,l1", [(1, 2 | 64 | 128, 0), (1, 15, 1), (8, 15, 0), (8, 2 | 16, 0)])
+@pytest.mark.parametrize("B,S", [(241, 17), (257, 31), (431, 19), (513, 32), (33, 249)])
+def test_encoder_chain_makes_the_same_rows(nt, torch_cuda, heads, tails, l1, B, S):
+    """Beyond 4,096 tokens an output projection and the next layer's Q|K|V are one launch, from 32- and from 64-row tiles, the last one
+    partly filled (4,097, 7,967, 8,189, 8,217 rows; a whole one 16,416): the same encoder outputs, bit for bit, as the same sentences in
+    batches that take two launches."""
+    torch = torch_cuda
+    cfg = nt_synth.model_config("C1", vocab=4000, n_enc=3, n_heads=heads, ln_l1=l1)
+    gm = nt.Model(cfg, nt_synth.make_weights(cfg, seed=41, random_affine=True), max_batch_tokens=16416, pipeline_lanes=1)
+    gm.debug_set_encoder_tails(tails)
+    rng = np.random.default_rng(B)
+    lens = rng.integers(1, S + 1, size=B).astype(np.int32)
+    lens[::16] = S
+    ids = np.where(np.arange(S)[None, :] < lens[:, None], rng.integers(4, 4000, size=(B, S)), cfg["pad_id"]).astype(np.int32)
+
+    def encode(a, b):
+        out = torch.empty(b - a, S, 512, dtype=torch.float32, device="cuda")
+        gm.encode(torch.from_numpy(ids[a:b].copy()).cuda(), torch.from_numpy(lens[a:b].copy()).cuda())
+        gm.debug_encoder_out(out)
+        return out.cpu().numpy()
+
+    whole, step = encode(0, B), 4096 // S
+    for a in range(0, B, step):
+        b = min(a + step, B)
+        for i, row in enumerate(encode(a, b), start=a):
+            assert np.array_equal(row[:lens[i]], whole[i, :lens[i]]), f"sentence {i}"
+    gm.close()
