@@ -71,7 +71,7 @@
 // head on eight of its lanes, so that every lane keeps its own head's softmax and a score costs three DPP adds.  Relative keys
 // enter as one number per (head, clipped distance), computed once per row.  Against two attention launches, two chains and a
 // projection per layer: 2,048 sentences through the 30 + 6 layer teacher 139 -> 123 ms, 16,384 through the model with 8 heads
-// and FFN 2,048 119 -> 115 ms.  (Four instead of eight rows per workgroup from 257 rows on: 115.5 and 125 ms.)
+// and FFN 2,048 119 -> 115 ms.
 //
 // Caches: row c (a sentence), position p: keys at kv[((c * row_positions + p) * 2) * d], values d elements later; scales
 // at sc[(c * row_positions + p) * 2 + {0: key, 1: value}].  The newest pair arrives as fp32 from the projection, is used
@@ -1117,8 +1117,12 @@ static hipError_t d1_launch(const Dec1Args &a, hipStream_t s) {
   // its 238 workgroups pull the matrices through twice as many CUs for the same rows; with 119 the other lanes' matrix
   // kernels get the rest of the chip and the job is 4 % faster (200,000 sentences: 560 against 582 ms).
   // Up to 512 rows two per workgroup (320 rows of 180 tokens alone: 24.4 against 26.7 ms with four), in between eight
-  // (65,536 tokens: 550 against 554 ms with four).  Eight heads, whose waves hold fp32 keys: four from 65 rows on and eight
-  // from 257 on.
+  // (65,536 tokens: 550 against 554 ms with four).  Eight heads, whose keys are fp32: a CU pulls some 55 KB of them a us whatever is in
+  // flight, so few rows are spread over more CUs: two per workgroup up to 192 rows (a step of the 30 + 6 layer teacher, 100 / 160 rows
+  // alone: 320 / 326 us, with four 344 / 350; with 8 heads and FFN 2,048, 160 rows of 100 70 and 80), four up to 512 (teacher, 260 /
+  // 320 rows 402 / 414 us, with eight 473 / 486; 300 / 500 rows with FFN 2,048 73.5 / 79.2 and 83.4 / 87.5).  Beside other lanes the CUs are not
+  // idle: 2,048 sentences through the teacher 97.9 ms with these lines, 100.2 with 64 and 256, 98.9 with 256 and 512, 100.5 with 512 for
+  // two; the model with FFN 2,048 takes the same time but for 1,023 in place of 512 (92 against 91 ms).
   const int shape = a.shape_rows > 0 ? a.shape_rows : a.rows;
   const int rows = a.table.rows && !a.tok_in ? std::max(a.rows, a.sb.rows_prev) : a.rows;  // those that only collect a token, too
 #define NT_D1F(RW_, NW_, P_, F16_, F32_)                                                                                  \
@@ -1163,11 +1167,11 @@ static hipError_t d1_launch(const Dec1Args &a, hipStream_t s) {
   }
   if (shape >= 1024) {
     NT_D1(16, 16, 1, false);
-  } else if (shape <= (HEADS ? 64 : 512)) {
+  } else if (shape <= (HEADS ? 192 : 512)) {
     NT_D1(2, 8, 4, false);
   } else {
     if constexpr (HEADS) {
-      if (shape <= 256) {
+      if (shape <= 512) {
         NT_D1(4, 16, 4, false);
         return hipGetLastError();
       }
