@@ -216,16 +216,16 @@ void vocab_pack(const _Float16 *Wt, int N, int K, _Float16 *dst);
 
 // n_partials of the launch configuration used with M rows (exact: head + tail planes; certified: tiled kernels' head plane
 // first, none in the scout's).
-// wide: vocab_wide of a row count at least M.  Up to 32 rows, and more where the strips of 64 entries times the tiles of 32 rows are at most
-// kVocabWideStrips, take a kernel of its own, more the scout, which is two launches (and whose sums run in another order, so a caller
+// wide: vocab_wide of a row count at least M.  Up to kVocabWideRows rows, and, of up to 256 strips of 64 entries (one to a workgroup), more where strips times
+// tiles of 32 rows are at most kVocabWideStrips, take a kernel of its own, more the scout, which is two launches (and whose sums run in another order, so a caller
 // whose M depends on timing decides by a row count that does not, and nobody by what else is running).  A decoder step alone, us, d = 512,
 // wide / scout, with strips x tiles: 1,000 entries, 33 rows (32) 12.3 / 20.2, 512 rows (256) 16.6 / 27.5; 4,000 entries, 128 rows (252) 13.2 / 21.5,
 // 300 rows (630) 21.1 / 24.4, 512 rows (1,008) 26.1 / 26.4; 8,000 entries, 64 rows (250) 12.9 / 19.2, 160 rows (625) 19.5 / 20.2, 200 rows (875)
-// 21.5 / 20.5; 16,000 entries, 48 rows (500) 15.4 / 18.6, 128 rows (1,000) 22.2 / 20.0; 32,000 entries, 24 / 32 / 40 / 64 rows 17.3 / 18.0 / 20.6 /
-// 22.8 and 19.2 / 19.3 / 19.9 / 20.3.  d = 256: 4,000 entries, 300 rows (630) 14.6 / 19.0; 16,000, 96 rows (750) 14.0 / 17.0.
-// Beside other lanes the line would lie lower (32,000 entries, a 4,096-token budget 19.9 ms with it at 40 rows, 19.6 at 8), a page of 45
-// rows is 2 % slower with it at 8.
-constexpr int kVocabWideStrips = 640;
+// 21.5 / 20.5.  d = 256: 4,000 entries, 300 rows (630) 14.6 / 19.0.  With the scout's form for few rows: 16,000 entries, 32 / 40 / 64 rows 13.8 /
+// 15.7 / 16.9 and 15.5 / 16.1 / 16.3; 24,000, 8 / 16 / 32 rows 14.5 / 15.2 / 16.8 and 15.1 / 15.4 / 15.8; 32,000, 4 / 8 / 16 / 24 / 32 rows 14.2 / 15.3 /
+// 15.8 / 16.5 / 17.4 and 15.0 / 15.5 / 15.9 / 16.3 / 16.5; d = 256, 32,000, 16 / 32 rows 12.2 / 12.8 and 12.7 / 12.7.
+// Beside other lanes, which want the memory system the wide kernel fills, a 4,096-token budget 17.4 ms with the line at 4 to 16 rows, 17.9 at 32.
+constexpr int kVocabWideStrips = 640, kVocabWideRows = 16;
 bool vocab_wide(const VocabWeights &w, int rows);
 int vocab_argmax_partials(const VocabWeights &w, int M, bool certified, bool wide);
 // h is a head/tail pair of fp16 planes.

@@ -130,7 +130,7 @@ bool vocab_tiled(const VocabWeights &w) { return !use_stream(w); }
 bool vocab_wide(const VocabWeights &w, int rows) {
   if (!use_stream(w)) return false;
   const long tiles = (rows + VW_ROWS - 1) / VW_ROWS;
-  return tiles == 1 ? vw_groups(w.N) <= 512 : tiles * ((w.N + 63) / 64) <= kVocabWideStrips;
+  return rows <= kVocabWideRows ? vw_groups(w.N) <= 512 : vw_strips(w.N) == 1 && tiles * ((w.N + 63) / 64) <= kVocabWideStrips;
 }
 bool vocab_scouted(const VocabWeights &w, bool wide) { return use_stream(w) && !wide; }
 

@@ -233,6 +233,13 @@ static ScSplit sc_split(int M, int NS) {
   return p;
 }
 
+// What a group leaves, of its three largest products << 5 | place
+__device__ __forceinline__ i32x2 scout_pair(const int (&top)[3]) {
+  const int apart = ((top[1] >> 5) - (top[2] >> 5)) >> SC_APART;
+  const int second = top[1] > SC_NONE / 2 ? top[1] : SC_LOW * 32;
+  return i32x2{top[0], (second >> 5) << 8 | (apart > 7 ? 7 : apart) << 5 | (second & 31)};
+}
+
 // part[m][2 strip + g]: {largest product << 5 | place, runner-up << 8 | min(7, distance to the third >> SC_APART) << 5 | place}
 template <int K>
 __global__ __launch_bounds__(SC_WAVES * 64) void vocab_scout_kernel(const int8_t *__restrict__ codes, int M, const int8_t *__restrict__ Wq,
@@ -352,11 +359,7 @@ __global__ __launch_bounds__(SC_WAVES * 64) void vocab_scout_kernel(const int8_t
             top[a][0] = top[a][0] > x ? top[a][0] : x;
           }
     };
-    auto pair = [&](int a) {
-      const int apart = ((top[a][1] >> 5) - (top[a][2] >> 5)) >> SC_APART;
-      const int second = top[a][1] > SC_NONE / 2 ? top[a][1] : SC_LOW << 5;
-      return i32x2{top[a][0], (second >> 5) << 8 | (apart > 7 ? 7 : apart) << 5 | (second & 31)};
-    };
+    auto pair = [&](int a) { return scout_pair(top[a]); };
     if (strip * 64 + 64 <= N) fold(std::false_type{}); else fold(std::true_type{});
     // straight-line stores for whole tiles (a guard around each makes it wait for the one before)
     if (full) {
@@ -368,6 +371,68 @@ __global__ __launch_bounds__(SC_WAVES * 64) void vocab_scout_kernel(const int8_t
         if (m0 + a * 32 + li < M) out[(long)a * 32 * (2 * NS) + 2 * strip] = pair(a);
     }
   }
+}
+
+// The same for up to 64 rows (32 RBS): a wave per strip and block of 32 rows, four to a workgroup.  The launch is one wave's latency there: all
+// fragments of the strip are requested at once, behind the tile's codes, and a wave has a quarter of the products that a strip of the kernel
+// above has, where 45 rows waited for 128.  A step of 33 / 45 / 64 rows alone 17.6 / 17.8 / 18.1 us -> 16.9 / 17.1 / 17.5; 65 / 90 / 128 rows, four
+// blocks of 32, would take 19.9 / 20.6 / 21.4 where the kernel above takes 19.4 / 20.2 / 20.7.
+template <int K, int RBS>
+__global__ __launch_bounds__(256) void vocab_scout_few_kernel(const int8_t *__restrict__ codes, int M, const int8_t *__restrict__ Wq, int N,
+                                                              i32x2 *__restrict__ part) {
+  constexpr int LD = K + 16, KS = K / 32, CPR = K / 16, PER_T = 32 * RBS * CPR / 256;
+  __shared__ __attribute__((aligned(16))) unsigned char smem[32 * RBS * LD];
+  const int tid = threadIdx.x, lane = tid & 63, li = lane & 31, g = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), rb = wave % RBS;
+  const int NS = (N + 63) >> 6, strip = blockIdx.x * (4 / RBS) + wave / RBS;
+  const __amdgpu_buffer_rsrc_t wrs = __builtin_amdgcn_make_buffer_rsrc((void *)Wq, 0, NS * 64 * K, 0x00020000);
+  u32x4 fr[PER_T];
+#pragma unroll
+  for (int i = 0; i < PER_T; i++) {  // rows past M repeat row M - 1 (never stored)
+    const int c = tid + 256 * i, R = c / CPR, kc = c % CPR;
+    fr[i] = *(const u32x4 *)(codes + (long)min(R, M - 1) * K + kc * 16);
+  }
+  __builtin_amdgcn_sched_barrier(0);
+  i32x4 w[KS][2];  // (past the end of the matrix: zeros)
+#pragma unroll
+  for (int ks = 0; ks < KS; ks++)
+#pragma unroll
+    for (int nb = 0; nb < 2; nb++)
+      w[ks][nb] = __builtin_bit_cast(i32x4, (u32x4)__builtin_amdgcn_raw_buffer_load_b128(wrs, lane * 16 + nb * 1024, (strip * KS + ks) * 2048, 0));
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int i = 0; i < PER_T; i++) {
+    const int c = tid + 256 * i, R = c / CPR, kc = c % CPR;
+    *(u32x4 *)(smem + R * LD + kc * 16) = fr[i];
+  }
+  __syncthreads();
+  i32x16 acc[2];
+#pragma unroll
+  for (int nb = 0; nb < 2; nb++)
+#pragma unroll
+    for (int v = 0; v < 16; v++) acc[nb][v] = 0;
+  const unsigned char *hrow = smem + (rb * 32 + li) * LD + g * 16;
+#pragma unroll
+  for (int ks = 0; ks < KS; ks++) {
+    const i32x4 x = *(const i32x4 *)(hrow + ks * 32);
+#pragma unroll
+    for (int nb = 0; nb < 2; nb++) acc[nb] = __builtin_amdgcn_mfma_i32_32x32x32_i8(w[ks][nb], x, acc[nb], 0, 0, 0);
+  }
+  int top[3] = {SC_NONE, SC_NONE, SC_NONE};
+#pragma unroll
+  for (int nb = 0; nb < 2; nb++)
+#pragma unroll
+    for (int v = 0; v < 16; v++) {
+      int x = (acc[nb][v] << 5) | (nb * 16 + v), second, third;
+      x = strip * 64 + nb * 32 + (v >> 2) * 8 + g * 4 + (v & 3) < N ? x : SC_NONE;
+      asm("v_med3_i32 %0, %1, %2, %3" : "=v"(third) : "v"(top[1]), "v"(top[2]), "v"(x));
+      asm("v_med3_i32 %0, %1, %2, %3" : "=v"(second) : "v"(top[0]), "v"(top[1]), "v"(x));
+      top[2] = third;
+      top[1] = second;
+      top[0] = top[0] > x ? top[0] : x;
+    }
+  const int m = rb * 32 + li;
+  if (strip < NS && m < M) part[(long)m * (2 * NS) + 2 * strip + g] = scout_pair(top);
 }
 
 constexpr int PK_WAVES = 8;
@@ -403,6 +468,14 @@ static PickArgs pick_args(const VocabScout &v, const _Float16 *h, const _Float16
   return PickArgs{v.scratch, v.row_consts, consts, ids, NS, row0, distrust ? INFINITY : 0.f, h, h_lo, ldh, (const _Float16 *)(ids + 64 * (size_t)NS)};
 }
 
+constexpr int kScoutFewRows = 64;
+template <int K, int RBS>
+static hipError_t scout_few_launch(const VocabScout &v, int M, int N, hipStream_t s) {
+  const int NS = (N + 63) / 64, per = 4 / RBS;
+  hipLaunchKernelGGL((vocab_scout_few_kernel<K, RBS>), dim3((NS + per - 1) / per), dim3(256), 0, s, v.codes, M, (const int8_t *)v.matrix, N, (i32x2 *)v.scratch);
+  return hipGetLastError();
+}
+
 template <int K>
 static hipError_t scout_launch(const VocabScout &v, const _Float16 *h, const _Float16 *h_lo, long ldh, const VocabWeights &w, int M, bool distrust,
                                int32_t *tok, int32_t *slot_of_row, PickArgs *later, hipStream_t s) {
@@ -416,11 +489,16 @@ static hipError_t scout_launch(const VocabScout &v, const _Float16 *h, const _Fl
   if (attr_err != hipSuccess) return attr_err;
   for (int r0 = 0; r0 < M; r0 += chunk) {
     const int rows = std::min(chunk, M - r0);
-    const ScSplit p = sc_split(rows, NS);
-    const unsigned int magic = p.m_tiles > 1 ? (unsigned int)((0x100000000ull + (unsigned)p.m_tiles - 1) / (unsigned)p.m_tiles) : 0u;
-    hipLaunchKernelGGL((vocab_scout_kernel<K>), dim3(8 * p.per_xcd), dim3(SC_WAVES * 64), lds, s, v.codes + (long)r0 * K, rows, Wq, w.N,
-                       p.m_tiles, p.G, p.per_xcd, NS / p.G, NS % p.G, magic, (i32x2 *)v.scratch);
-    hipError_t e = hipGetLastError();
+    hipError_t e;
+    if (M <= kScoutFewRows) {
+      e = M <= 32 ? scout_few_launch<K, 1>(v, M, w.N, s) : scout_few_launch<K, 2>(v, M, w.N, s);
+    } else {
+      const ScSplit p = sc_split(rows, NS);
+      const unsigned int magic = p.m_tiles > 1 ? (unsigned int)((0x100000000ull + (unsigned)p.m_tiles - 1) / (unsigned)p.m_tiles) : 0u;
+      hipLaunchKernelGGL((vocab_scout_kernel<K>), dim3(8 * p.per_xcd), dim3(SC_WAVES * 64), lds, s, v.codes + (long)r0 * K, rows, Wq, w.N,
+                         p.m_tiles, p.G, p.per_xcd, NS / p.G, NS % p.G, magic, (i32x2 *)v.scratch);
+      e = hipGetLastError();
+    }
     if (e != hipSuccess) return e;
     if (later) {  // (vocab_scout_one_launch)
       *later = pick_args(v, h, h_lo, ldh, w, 0, distrust);

@@ -553,8 +553,17 @@ def short_of_the_largest(nt, torch, d, V, rows_list, T, max_tokens, seed):
 @pytest.mark.parametrize("V,rows", [(4001, [33, 63, 64, 65, 320, 321]), (17000, [33, 64, 65]), (64, [33, 1000])])
 def test_argmax_of_several_tiles_of_rows(nt, torch_cuda, d, V, rows):
     """The kernel of a few rows with more than one tile of 32, the last one full or of a single row, up to its line (4,001 entries: 320
-    rows; 17,000, two strips of 64 to a workgroup, an odd number of them: 64) and one row past it.  Bound as in test_scouted_argmax."""
+    rows) and one row past it; 17,000 entries, past its 256 strips: the scout.  Bound as in test_scouted_argmax."""
     assert short_of_the_largest(nt, torch_cuda, d, V, rows, 3, 4096, seed=29) <= 1.2e-5
+
+
+@pytest.mark.parametrize("d", [256, 512])
+@pytest.mark.parametrize("V", [16450, 33000])
+def test_scouted_argmax_of_few_rows(nt, torch_cuda, d, V):
+    """The scout's form of up to 64 rows, which more than 256 strips of 64 entries take from 17 rows on: one block of 32 rows and two, partly
+    filled and full, an odd number of strips (258 and 516 with two or four to a workgroup) with a ragged last one; and one row less and
+    more than it takes.  Bound as in test_scouted_argmax."""
+    assert short_of_the_largest(nt, torch_cuda, d, V, [16, 17, 31, 32, 33, 63, 64, 65], 3, 4096, seed=37) <= 1.2e-5
 
 
 @pytest.mark.parametrize("d,V,rows", [(256, 4033, 8192 + 129), (512, 40, 20480 + 33)])
