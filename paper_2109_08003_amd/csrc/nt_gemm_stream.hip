@@ -98,11 +98,10 @@ __device__ __forceinline__ void gs_normalise(const float (&xv)[RPW][NE], const G
 // between passes the tile is refilled behind a barrier while the weight ring keeps streaming, and every wave keeps the
 // accumulators of its one strip (N is 512 per column group) - the second matrix of an FFN, whose K is the FFN width.
 // CHAIN: the rows that are normalised are made here, x += A * Wo^T + bias (A: planes, Wo: K x K), see GemmChain.
-template <int RB, int K, bool C_F32, bool LN, bool TAIL, int NC, int NB, bool CHAIN = false>
-__global__ __launch_bounds__(GS_WAVES * 64) void gemm_stream_kernel(const _Float16 *__restrict__ A_hi,
-                                                                   const _Float16 *__restrict__ A_lo, long lda, int M,
-                                                                   const _Float16 *__restrict__ Wp, int N, int col_groups,
-                                                                   GemmEpilogue e, GemmLayerNorm ln, GemmChain ch) {
+template <int RB, int K, bool C_F32, bool LN, bool TAIL, int NC, int NB, bool CHAIN>
+__device__ __forceinline__ void gs_tile(const _Float16 *__restrict__ A_hi, const _Float16 *__restrict__ A_lo, long lda, int M,
+                                        const _Float16 *__restrict__ Wp, int N, int col_groups, const GemmEpilogue &e, const GemmLayerNorm &ln,
+                                        const GemmChain &ch) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   _Float16 *sh = (_Float16 *)smem;
   constexpr int TM = 32 * RB, ROWS = (TAIL ? 2 : 1) * TM;  // LDS fragment rows: head rows, then tail rows
@@ -534,6 +533,20 @@ __global__ __launch_bounds__(GS_WAVES * 64) void gemm_stream_kernel(const _Float
   }
 }
 
+template <int RB, int K, bool C_F32, bool LN, bool TAIL, int NC, int NB>
+__global__ __launch_bounds__(GS_WAVES * 64) void gemm_stream_kernel(const _Float16 *__restrict__ A_hi,
+                                                                   const _Float16 *__restrict__ A_lo, long lda, int M,
+                                                                   const _Float16 *__restrict__ Wp, int N, int col_groups,
+                                                                   GemmEpilogue e, GemmLayerNorm ln) {
+  gs_tile<RB, K, C_F32, LN, TAIL, NC, NB, false>(A_hi, A_lo, lda, M, Wp, N, col_groups, e, ln, GemmChain{});
+}
+template <int RB>
+__global__ __launch_bounds__(GS_WAVES * 64) void gemm_chain_kernel(const _Float16 *__restrict__ A_hi, const _Float16 *__restrict__ A_lo, long lda,
+                                                                  int M, const _Float16 *__restrict__ Wp, int N, GemmEpilogue e, GemmLayerNorm ln,
+                                                                  GemmChain ch) {
+  gs_tile<RB, 512, true, true, true, 1, 2, true>(A_hi, A_lo, lda, M, Wp, N, 1, e, ln, ch);
+}
+
 // ---------------------------------------------------------------------------------------------------------------------
 // An FFN in one launch: x += relu(LayerNorm(x) W1^T + b1) W2^T + b2, d = 512, hidden width 512 NC.  A workgroup has 32 rows; 512 hidden
 // columns at a time go from the first product's accumulators through ReLU and the split into a second pair of planes in the LDS
@@ -684,10 +697,10 @@ __global__ __launch_bounds__(GS_WAVES * 64) void gemm_ffn_kernel(float *__restri
 // workgroups per row tile with 32-column strips: four strips each, or two where N is an odd multiple of 64
 static int gs_narrow_groups(int N) { return N % 128 == 0 ? N / 128 : N / 64; }
 
-template <int RB, int K, bool C_F32, bool LN, bool TAIL, int NC = 1, int NB = 2, bool CHAIN = false>
+template <int RB, int K, bool C_F32, bool LN, bool TAIL, int NC = 1, int NB = 2>
 static hipError_t gs_launch(const _Float16 *A, const _Float16 *A_lo, long lda, int M, const _Float16 *Wp, int N,
-                            const GemmEpilogue &e, const GemmLayerNorm &ln, hipStream_t s, const GemmChain &ch = GemmChain{}) {
-  auto kern = gemm_stream_kernel<RB, K, C_F32, LN, TAIL, NC, NB, CHAIN>;
+                            const GemmEpilogue &e, const GemmLayerNorm &ln, hipStream_t s) {
+  auto kern = gemm_stream_kernel<RB, K, C_F32, LN, TAIL, NC, NB>;
   const size_t lds = (size_t)(TAIL ? 64 : 32) * RB * (K + 8) * 2;
   // raising the dynamic LDS limit is per kernel, once per process (several host threads may get here at once)
   static std::once_flag once;
@@ -704,7 +717,7 @@ static hipError_t gs_launch(const _Float16 *A, const _Float16 *A_lo, long lda, i
   // a round: the same both ways).
   int col_groups = 1;
   long best = 0;
-  for (int cg = 1; cg * GS_WAVES <= NS && !CHAIN; cg++) {
+  for (int cg = 1; cg * GS_WAVES <= NS; cg++) {
     if (NS % cg != 0) continue;
     const long cost = ((long)row_tiles * cg + 255) / 256 * (1 + (NS / cg + GS_WAVES - 1) / GS_WAVES);
     if (best == 0 || cost < best) best = cost, col_groups = cg;
@@ -712,7 +725,7 @@ static hipError_t gs_launch(const _Float16 *A, const _Float16 *A_lo, long lda, i
   if (NC > 1) col_groups = NS / GS_WAVES;  // several passes: exactly one strip per wave
   if (NB == 1) col_groups = gs_narrow_groups(N);
   hipLaunchKernelGGL(kern, dim3(row_tiles * col_groups), dim3(GS_WAVES * 64), lds, s, A, A_lo, lda, M, Wp, N, col_groups, e,
-                     ln, ch);
+                     ln);
   return hipGetLastError();
 }
 
@@ -861,12 +874,24 @@ hipError_t launch_gemm_stream(bool c_f32, const _Float16 *A, const _Float16 *A_l
 
 bool gemm_chain_supported(int M, int N, int K) { return K == 512 && N % 512 == 0 && M > kChainRows; }
 
+template <int RB>
+static hipError_t gc_launch(const _Float16 *A, const _Float16 *A_lo, long lda, const GemmChain &ch, const GemmLayerNorm &ln, const _Float16 *Wp, int M,
+                            int N, const GemmEpilogue &e, hipStream_t s) {
+  auto kern = gemm_chain_kernel<RB>;
+  constexpr int lds = 2 * 32 * RB * (512 + 8) * 2;
+  static std::once_flag once;
+  static hipError_t attr_err = hipSuccess;
+  std::call_once(once, [&] { attr_err = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds); });
+  if (attr_err != hipSuccess) return attr_err;
+  hipLaunchKernelGGL(kern, dim3((unsigned)((M + 32 * RB - 1) / (32 * RB))), dim3(GS_WAVES * 64), lds, s, A, A_lo, lda, M, Wp, N, e, ln, ch);
+  return hipGetLastError();
+}
+
 hipError_t launch_gemm_chain(const _Float16 *A, const _Float16 *A_lo, long lda, const GemmChain &ch, const GemmLayerNorm &ln, const _Float16 *Wp, int M,
                              int N, const GemmEpilogue &e, hipStream_t s) {
   if (M <= 0) return hipSuccess;
   if (N <= 0 || N % 512 != 0 || e.n_split % 32 != 0) return hipErrorInvalidValue;
-  return M <= 8192 ? gs_launch<1, 512, true, true, true, 1, 2, true>(A, A_lo, lda, M, Wp, N, e, ln, s, ch)
-                   : gs_launch<2, 512, true, true, true, 1, 2, true>(A, A_lo, lda, M, Wp, N, e, ln, s, ch);
+  return M <= 8192 ? gc_launch<1>(A, A_lo, lda, ch, ln, Wp, M, N, e, s) : gc_launch<2>(A, A_lo, lda, ch, ln, Wp, M, N, e, s);
 }
 
 hipError_t launch_gemm_stream_ln(bool c_f32, const float *X, long ldx, const GemmLayerNorm &ln, const _Float16 *Wp, int M,
