@@ -205,7 +205,8 @@ int nt_debug_q8_quantize_row(const void *h_w_fp16, int32_t K, int8_t *h_codes, f
  * stops launching once it reads zero.  The host never waits for the stream to drain, but it
  * enqueues at most a few steps ahead of the device, so the call returns when the device is
  * within those few steps of the end; the outputs are complete once hip_stream has been
- * synchronised.  Tokens are those nt_decode_greedy produces, cut after the first EOS.
+ * synchronised.  Tokens are those nt_decode_greedy produces, cut after the first EOS (where the caps
+ * leave 17 to 32 rows the output layer's kernel may be another one: to within the last bit, as above).
  * Errors: as nt_decode_greedy; NT_ERANGE for eos_id outside the vocabulary; NT_EHIP if the device
  * publishes no progress for 30 seconds.
  */

@@ -380,7 +380,7 @@ int alloc_lane_state(nt_model *m, hipStream_t s) {
      // 128 rows each)
     int64_t worst = 0;
     for (int64_t rows = Br; rows > 0 && worst == 0; rows--)  // the most it is taken for
-      if (nt::vocab_wide(m->vw, (int)rows)) worst = rows * nt::vocab_argmax_partials(m->vw, (int)rows, false, true);
+      if (nt::vocab_wide(m->vw, (int)rows, nt::kVocabWideRows)) worst = rows * nt::vocab_argmax_partials(m->vw, (int)rows, false, true);
     for (int64_t mt = 1; (mt - 1) * 64 < Br; mt++) {
       const int64_t rows = std::min<int64_t>(mt * 64, Br);
       for (int tiled = 0; tiled < 2; tiled++) {  // either family of arg-max kernels may be selected later
@@ -1186,7 +1186,9 @@ int decode_step(nt_model *m, DecodeCursor &cu, hipStream_t s) {
     int rc;
     // The scout's sums run in another order than the wide kernel's: chosen as above.  (The tiled kernels' certified form gives the
     // full pass's result at any row count.)
-    const bool wide = nt::vocab_wide(m->vw, rows_for_choice);
+    const bool picked = !eos && layer1 && F == 0 && nt::dec1_picks(rows_for_choice, heads_layer ? H : 1);
+    const bool wide = nt::vocab_wide(m->vw, rows_for_choice,
+                                     !picked ? nt::kVocabWideRows : d == 512 && c.n_dec == 1 ? nt::kVocabPickedRows : nt::kVocabPickedRowsLate);
     const bool scouted = nt::vocab_scouted(m->vw, wide) && m->Wscout;
     const bool certified = !d_logits && !c.q8_output && (scouted || (nt::vocab_tiled(m->vw) && R >= kCertMinRows));
     const nt::ScoutOut scout_out = certified && scouted ? nt::ScoutOut{m->scout_codes, m->scout_rc, nt::vocab_scout_levels(m->Wscout, V, d)} : nt::ScoutOut{};

@@ -216,17 +216,22 @@ void vocab_pack(const _Float16 *Wt, int N, int K, _Float16 *dst);
 
 // n_partials of the launch configuration used with M rows (exact: head + tail planes; certified: tiled kernels' head plane
 // first, none in the scout's).
-// wide: vocab_wide of a row count at least M.  Up to kVocabWideRows rows, and, of up to 256 strips of 64 entries (one to a workgroup), more where strips times
-// tiles of 32 rows are at most kVocabWideStrips, take a kernel of its own, more the scout, which is two launches (and whose sums run in another order, so a caller
-// whose M depends on timing decides by a row count that does not, and nobody by what else is running).  A decoder step alone, us, d = 512,
+// wide: vocab_wide of a row count at least M.  Up to a tile of 32 rows, and, of up to 256 strips of 64 entries (one to a workgroup), more where strips
+// times tiles are at most kVocabWideStrips, take a kernel of its own, more the scout, which is two launches (and whose sums run in another order, so a
+// caller whose M depends on timing decides by a row count that does not, and nobody by what else is running).  A decoder step alone, us, d = 512,
 // wide / scout, with strips x tiles: 1,000 entries, 33 rows (32) 12.3 / 20.2, 512 rows (256) 16.6 / 27.5; 4,000 entries, 128 rows (252) 13.2 / 21.5,
 // 300 rows (630) 21.1 / 24.4, 512 rows (1,008) 26.1 / 26.4; 8,000 entries, 64 rows (250) 12.9 / 19.2, 160 rows (625) 19.5 / 20.2, 200 rows (875)
-// 21.5 / 20.5.  d = 256: 4,000 entries, 300 rows (630) 14.6 / 19.0.  With the scout's form for few rows: 16,000 entries, 32 / 40 / 64 rows 13.8 /
-// 15.7 / 16.9 and 15.5 / 16.1 / 16.3; 24,000, 8 / 16 / 32 rows 14.5 / 15.2 / 16.8 and 15.1 / 15.4 / 15.8; 32,000, 4 / 8 / 16 / 24 / 32 rows 14.2 / 15.3 /
-// 15.8 / 16.5 / 17.4 and 15.0 / 15.5 / 15.9 / 16.3 / 16.5; d = 256, 32,000, 16 / 32 rows 12.2 / 12.8 and 12.7 / 12.7.
-// Beside other lanes, which want the memory system the wide kernel fills, a 4,096-token budget 17.4 ms with the line at 4 to 16 rows, 17.9 at 32.
-constexpr int kVocabWideStrips = 640, kVocabWideRows = 16;
-bool vocab_wide(const VocabWeights &w, int rows);
+// 21.5 / 20.5.  d = 256: 4,000 entries, 300 rows (630) 14.6 / 19.0.  More than 256 strips, rows of 22 tokens, 17 / 24 / 32 rows and the scout from 33 rows on: eight
+// heads 29.3 / 30.1 / 31.1 and 34.5 / 34.5 / 34.5, the EOS mode of one head 21.9 / 22.8 / 23.6 and 24.5, d = 256 18.5 / 18.9 / 19.3 and 20.2, with an FFN of the
+// model's width 25.8 / 26.9 / 27.9 and 28.7.
+// line: the largest row count that takes the wide kernel with more than 256 strips; kVocabWideRows, but less where the pick is no launch but part of the next
+// step's first layer (DecodeCursor::prev_pick) and the layer has no FFN: 17 / 20 / 24 / 28 / 32 rows, 32,000 entries 15.7 / 16.0 / 16.3 / 16.7 / 17.1 and 15.7 / 15.9 /
+// 16.0 / 16.4 / 16.5, 20,000 15.1 / 15.3 / 15.8 / 16.2 / 16.6 and 15.2 / 15.5 / 15.7 / 15.9 / 16.0, 16,500 14.8 / 15.2 / 15.6 / 16.0 / 16.4 and 14.8 / 15.1 / 15.2 / 15.3 / 15.3,
+// beside other lanes, which want the memory system the wide kernel fills, a 4,096-token budget 17.4 ms with the line at 4 to 16 rows, 17.9 at 32: kVocabPickedRows.
+// d = 256, 32,000 entries, 20 / 24 / 28 / 32 rows 12.3 / 12.3 / 12.5 / 12.8 and 12.5 / 12.6 / 12.5 / 12.8, 16,500 12.0 / 12.1 / 12.4 / 12.6 and 12.3 / 12.2 / 12.2 / 12.2;
+// two decoder layers, d = 512, 18 / 24 / 28 / 32 rows 67.8 / 68.7 / 69.7 / 67.6 and 68.9 / 69.0 / 69.2 / 66.6: kVocabPickedRowsLate.
+constexpr int kVocabWideStrips = 640, kVocabWideRows = 32, kVocabPickedRows = 16, kVocabPickedRowsLate = 24;
+bool vocab_wide(const VocabWeights &w, int rows, int line);
 int vocab_argmax_partials(const VocabWeights &w, int M, bool certified, bool wide);
 // h is a head/tail pair of fp16 planes.
 hipError_t launch_vocab_argmax(const _Float16 *h, const _Float16 *h_lo, long ldh, const VocabWeights &w, int M,

@@ -44,6 +44,7 @@ void vocab_pack(const _Float16 *Wt, int N, int K, _Float16 *dst) {
 // One row: 7.0 us against 12.7, and 20 instead of 25 us for the decoder layer that follows.
 // ---------------------------------------------------------------------------------------------------------------------
 constexpr int VW_ROWS = 32;
+static_assert(kVocabWideRows == VW_ROWS, "two strips per workgroup: one tile");
 template <int K, int SPW, bool TILES>
 __global__ __launch_bounds__(512) void vocab_wide_kernel(const _Float16 *__restrict__ h_hi, const _Float16 *__restrict__ h_lo,
                                                          long ldh, int M, const _Float16 *__restrict__ Wp, int N, int G,
@@ -127,10 +128,11 @@ static int vw_groups(int N) { return ((N + 63) / 64 + vw_strips(N) - 1) / vw_str
 static bool use_stream(const VocabWeights &w) { return !w.force_tiled && w.Wp && vocab_stream_supported(w.K); }
 
 bool vocab_tiled(const VocabWeights &w) { return !use_stream(w); }
-bool vocab_wide(const VocabWeights &w, int rows) {
+bool vocab_wide(const VocabWeights &w, int rows, int line) {
   if (!use_stream(w)) return false;
-  const long tiles = (rows + VW_ROWS - 1) / VW_ROWS;
-  return rows <= kVocabWideRows ? vw_groups(w.N) <= 512 : vw_strips(w.N) == 1 && tiles * ((w.N + 63) / 64) <= kVocabWideStrips;
+  const int tiles = (rows + VW_ROWS - 1) / VW_ROWS, NS = (w.N + 63) / 64;
+  if (vw_strips(w.N) == 1) return tiles == 1 || (long)tiles * NS <= kVocabWideStrips;
+  return rows <= line && vw_groups(w.N) <= 512;
 }
 bool vocab_scouted(const VocabWeights &w, bool wide) { return use_stream(w) && !wide; }
 

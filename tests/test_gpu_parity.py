@@ -560,7 +560,7 @@ def test_argmax_of_several_tiles_of_rows(nt, torch_cuda, d, V, rows):
 @pytest.mark.parametrize("d", [256, 512])
 @pytest.mark.parametrize("V", [16450, 33000])
 def test_scouted_argmax_of_few_rows(nt, torch_cuda, d, V):
-    """The scout's form of up to 64 rows, which more than 256 strips of 64 entries take from 17 rows on: one block of 32 rows and two, partly
+    """The scout's form of up to 64 rows, which more than 256 strips of 64 entries take from 17 rows on (d = 256: from 25): one block of 32 rows and two, partly
     filled and full, an odd number of strips (258 and 516 with two or four to a workgroup) with a ragged last one; and one row less and
     more than it takes.  Bound as in test_scouted_argmax."""
     assert short_of_the_largest(nt, torch_cuda, d, V, [16, 17, 31, 32, 33, 63, 64, 65], 3, 4096, seed=37) <= 1.2e-5

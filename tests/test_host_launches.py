@@ -149,6 +149,32 @@ print(json.dumps(out))
     assert folded == [True, False, True, False, True, False, True, False]
 
 
+def test_arg_max_of_17_to_32_rows(host):
+    """More than 256 strips of the output matrix, up to 32 rows: the kernel that reads all of it; but from 17 rows on (256-wide models
+    and two decoder layers: 25) the scout where the pick is no launch, that is in fixed-length decoding of one head without an FFN."""
+    got = host("""
+out = []
+for name, kw in (("one head", dict()), ("narrow", dict(d_model=256)), ("deep", dict(n_dec=2)), ("ffn", dict(dec_d_ffn=512)), ("heads", dict(n_heads=8))):
+    model = load(dict(config(n_enc=1, **kw), vocab=16450), tokens=4096)
+    a = np.zeros(4096, dtype=np.int32)
+    for rows in (16, 17, 24, 25, 32, 33):
+        for eos in (False, True):
+            encode(model, rows, 2)
+            stub.stub_clear()
+            args = model._h, rows, 2, None
+            if eos:  # (two steps: the host does not wait for the device yet)
+                nt.binding._check(nt.binding.lib().nt_decode_greedy_eos(*args, 2, a.ctypes.data, a.ctypes.data, None))
+            else:
+                nt.binding._check(nt.binding.lib().nt_decode_greedy(*args, a.ctypes.data, None))
+            kinds = {k for n, _ in launches() for k in ("vocab_wide", "vocab_scout_few", "vocab_pick") if k in n}
+            out.append((name, rows, eos, sorted(kinds)))
+print(json.dumps(out))
+""")
+    for name, rows, eos, kinds in got:
+        wide = rows <= (32 if eos or name in ("ffn", "heads") else 24 if name in ("narrow", "deep") else 16)
+        assert kinds == (["vocab_wide"] if wide else ["vocab_pick", "vocab_scout_few"]), (name, rows, eos, kinds)  # (the last step's pick)
+
+
 def test_lanes_with_different_sentence_lengths_share_a_kernel(host):
     """Four threads meet the tiled encoder attention for the first time with four lengths: none may lower the LDS limit under
     another's launches."""
