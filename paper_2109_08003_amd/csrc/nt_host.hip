@@ -1186,9 +1186,8 @@ int decode_step(nt_model *m, DecodeCursor &cu, hipStream_t s) {
     int rc;
     // The scout's sums run in another order than the wide kernel's: chosen as above.  (The tiled kernels' certified form gives the
     // full pass's result at any row count.)
-    const bool picked = !eos && layer1 && F == 0 && nt::dec1_picks(rows_for_choice, heads_layer ? H : 1);
-    const bool wide = nt::vocab_wide(m->vw, rows_for_choice,
-                                     !picked ? nt::kVocabWideRows : d == 512 && c.n_dec == 1 ? nt::kVocabPickedRows : nt::kVocabPickedRowsLate);
+    const bool picked = !eos && layer1 && c.n_dec == 1 && F == 0 && nt::dec1_picks(rows_for_choice, heads_layer ? H : 1);
+    const bool wide = nt::vocab_wide(m->vw, rows_for_choice, !picked ? nt::kVocabWideRows : d == 512 ? nt::kVocabPickedRows : nt::kVocabPickedRows256);
     const bool scouted = nt::vocab_scouted(m->vw, wide) && m->Wscout;
     const bool certified = !d_logits && !c.q8_output && (scouted || (nt::vocab_tiled(m->vw) && R >= kCertMinRows));
     const nt::ScoutOut scout_out = certified && scouted ? nt::ScoutOut{m->scout_codes, m->scout_rc, nt::vocab_scout_levels(m->Wscout, V, d)} : nt::ScoutOut{};

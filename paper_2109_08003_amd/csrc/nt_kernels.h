@@ -225,12 +225,12 @@ void vocab_pack(const _Float16 *Wt, int N, int K, _Float16 *dst);
 // heads 29.3 / 30.1 / 31.1 and 34.5 / 34.5 / 34.5, the EOS mode of one head 21.9 / 22.8 / 23.6 and 24.5, d = 256 18.5 / 18.9 / 19.3 and 20.2, with an FFN of the
 // model's width 25.8 / 26.9 / 27.9 and 28.7.
 // line: the largest row count that takes the wide kernel with more than 256 strips; kVocabWideRows, but less where the pick is no launch but part of the next
-// step's first layer (DecodeCursor::prev_pick) and the layer has no FFN: 17 / 20 / 24 / 28 / 32 rows, 32,000 entries 15.7 / 16.0 / 16.3 / 16.7 / 17.1 and 15.7 / 15.9 /
+// step's only layer (DecodeCursor::prev_pick), without an FFN: 17 / 20 / 24 / 28 / 32 rows, 32,000 entries 15.7 / 16.0 / 16.3 / 16.7 / 17.1 and 15.7 / 15.9 /
 // 16.0 / 16.4 / 16.5, 20,000 15.1 / 15.3 / 15.8 / 16.2 / 16.6 and 15.2 / 15.5 / 15.7 / 15.9 / 16.0, 16,500 14.8 / 15.2 / 15.6 / 16.0 / 16.4 and 14.8 / 15.1 / 15.2 / 15.3 / 15.3,
 // beside other lanes, which want the memory system the wide kernel fills, a 4,096-token budget 17.4 ms with the line at 4 to 16 rows, 17.9 at 32: kVocabPickedRows.
-// d = 256, 32,000 entries, 20 / 24 / 28 / 32 rows 12.3 / 12.3 / 12.5 / 12.8 and 12.5 / 12.6 / 12.5 / 12.8, 16,500 12.0 / 12.1 / 12.4 / 12.6 and 12.3 / 12.2 / 12.2 / 12.2;
-// two decoder layers, d = 512, 18 / 24 / 28 / 32 rows 67.8 / 68.7 / 69.7 / 67.6 and 68.9 / 69.0 / 69.2 / 66.6: kVocabPickedRowsLate.
-constexpr int kVocabWideStrips = 640, kVocabWideRows = 32, kVocabPickedRows = 16, kVocabPickedRowsLate = 24;
+// d = 256, 32,000 entries, 20 / 24 / 28 / 32 rows 12.3 / 12.3 / 12.5 / 12.8 and 12.5 / 12.6 / 12.5 / 12.8, 16,500 12.0 / 12.1 / 12.4 / 12.6 and 12.3 / 12.2 / 12.2 / 12.2.
+// (Two decoder layers of 512, 18 / 24 / 28 / 32 rows 67.8 / 68.7 / 69.7 / 67.6 and 68.9 / 69.0 / 69.2 / 66.6; of 256, 28 rows 35.6 and 36.3: no line of their own.)
+constexpr int kVocabWideStrips = 640, kVocabWideRows = 32, kVocabPickedRows = 16, kVocabPickedRows256 = 24;
 bool vocab_wide(const VocabWeights &w, int rows, int line);
 int vocab_argmax_partials(const VocabWeights &w, int M, bool certified, bool wide);
 // h is a head/tail pair of fp16 planes.

@@ -150,8 +150,8 @@ print(json.dumps(out))
 
 
 def test_arg_max_of_17_to_32_rows(host):
-    """More than 256 strips of the output matrix, up to 32 rows: the kernel that reads all of it; but from 17 rows on (256-wide models
-    and two decoder layers: 25) the scout where the pick is no launch, that is in fixed-length decoding of one head without an FFN."""
+    """More than 256 strips of the output matrix, up to 32 rows: the kernel that reads all of it; but from 17 rows on (256-wide models: 25)
+    the scout where the pick is no launch, that is in fixed-length decoding of one head, in one layer without an FFN."""
     got = host("""
 out = []
 for name, kw in (("one head", dict()), ("narrow", dict(d_model=256)), ("deep", dict(n_dec=2)), ("ffn", dict(dec_d_ffn=512)), ("heads", dict(n_heads=8))):
@@ -171,7 +171,7 @@ for name, kw in (("one head", dict()), ("narrow", dict(d_model=256)), ("deep", d
 print(json.dumps(out))
 """)
     for name, rows, eos, kinds in got:
-        wide = rows <= (32 if eos or name in ("ffn", "heads") else 24 if name in ("narrow", "deep") else 16)
+        wide = rows <= (32 if eos or name in ("deep", "ffn", "heads") else 24 if name == "narrow" else 16)
         assert kinds == (["vocab_wide"] if wide else ["vocab_pick", "vocab_scout_few"]), (name, rows, eos, kinds)  # (the last step's pick)
 
 
