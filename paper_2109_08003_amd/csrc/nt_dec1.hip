@@ -540,7 +540,7 @@ __device__ __forceinline__ void first_layer_start(const Dec1Args &a, int y, int 
 // caches hold folded vectors, in fp32 or as integers.  HEADS: eight heads of 64 columns, self cache fp32, cross cache fp16, optional
 // relative keys.
 template <int D, int RW, int NWAVES, int PARTS, int FOLD16, bool IND, bool FFN, bool FOLD32, bool HEADS>
-__global__ __launch_bounds__(NWAVES * 64) void dec1_kernel(Dec1Args a) {
+__global__ __launch_bounds__(NWAVES * 64) void dec1_kernel(Dec1Args args) {
   constexpr int NE = D / 64, WR = NWAVES / RW, PW = PARTS / WR;  // elements per lane; waves per row; partials per wave
   constexpr int NC = D / NWAVES, NT = NC / 16;                   // output columns of a wave, in tiles of 16
   constexpr int LD = D + 8, ZLD = D + 4, KS = D / 32, KS16 = D / 16;
@@ -575,9 +575,9 @@ __global__ __launch_bounds__(NWAVES * 64) void dec1_kernel(Dec1Args a) {
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int rw = wave / WR, pg = wave % WR;
   const int row0 = blockIdx.x * RW;
-  const bool valid = row0 + rw < a.rows;
+  const bool valid = row0 + rw < args.rows;
   D1Token token;
-  if (FOLD || a.table.rows) token.request(a, row0 + rw, lane);
+  if (FOLD || args.table.rows) token.request(args, row0 + rw, lane);
   // the normalisations' gains and offsets go to the LDS while the start of the row travels, a vector per wave: read where they are used,
   // each would be another turn of the memory system in the row's chain
   float norm[NVW][NE];
@@ -586,20 +586,31 @@ __global__ __launch_bounds__(NWAVES * 64) void dec1_kernel(Dec1Args a) {
   for (int u = 0; u < NVW; u++) {
     const int i = wave + u * NWAVES;
     if constexpr (FOLD) {
-      norm_src[u] = i < VP ? a.fold_const + i * D : i < NVT ? a.fold_pos + (a.sb.t * 4L + (i - VP)) * D : nullptr;
+      norm_src[u] = i < VP ? args.fold_const + i * D : i < NVT ? args.fold_pos + (args.sb.t * 4L + (i - VP)) * D : nullptr;
     } else {
-      const GemmLayerNorm &of = i < 2 ? a.ln2 : FFN && i < 4 ? a.ln3 : a.lnf;
+      const GemmLayerNorm &of = i < 2 ? args.ln2 : FFN && i < 4 ? args.ln3 : args.lnf;
       norm_src[u] = i < NV ? (i & 1 ? of.beta : of.gamma) : nullptr;  // (no final one: nullptr)
     }
     if (norm_src[u]) d1_load<NE>(norm_src[u] + lane * NE, norm[u]);
   }
   unsigned long long picked = 0ull;
   if constexpr (PICKS) {
-    if (a.sb.prev_cert == kPrevPick) {
-      pick_rows<D, RW, NWAVES>(a.sb.pick, sPick, row0, a.sb.rows_prev);
+    if (args.sb.prev_cert == kPrevPick) {
+      pick_rows<D, RW, NWAVES>(args.sb.pick, sPick, row0, args.sb.rows_prev);
       picked = sPick.best[rw];
     }
   }
+  // Without folding the arguments are read again from here on: kept across the pick they took 59 to 85 scalar registers more than there
+  // are, moved to vector registers and back in launches that do not pick as well (two such layers, 1 / 16 / 300 rows, us a step: d = 512 56.9 / 66.8 /
+  // 71.4 -> 55.9 / 65.5 / 70.0, d = 256 30.2 / 35.6 / 43.4 -> 28.7 / 33.8 / 41.5).
+  const Dec1Args *later = &args;
+  if constexpr (PICKS && !FOLD) {
+    typedef const __attribute__((address_space(4))) Dec1Args *Segment;
+    Segment segment = (Segment)__builtin_amdgcn_kernarg_segment_ptr();  // (starts with the only argument)
+    asm volatile("" : "+s"(segment));
+    later = (const Dec1Args *)segment;
+  }
+  const Dec1Args &a = *later;
   const int r = valid ? row0 + rw : 0;
   int rc = r;
   if (IND) rc = valid ? a.origin[r] : -1;

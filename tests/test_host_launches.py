@@ -1,12 +1,14 @@
 """Host side of libnt on a HIP runtime that runs nothing (hip_stub.c): which kernels a call launches with which grids, what a
 load puts on the device, and what happens when the device reports an error.  Each case is a child process, because the stub
 has to be loaded before the library."""
+import io
 import json
 import os
 import re
 import subprocess
 import sys
 
+import msgpack
 import pytest
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
@@ -130,6 +132,20 @@ print(json.dumps(sorted(out)))
         built = {n.decode() for n in re.findall(rb"_ZN2nt11dec1_kernelI(?:Li\d+E)+(?:Lb[01]E)+EEvNS_8Dec1ArgsE", f.read())}
     rows_direct = {n for n in built if re.search(r"Li\d+ELb0E", n)}
     assert len(used) > 10 and rows_direct == set(used)
+
+
+def test_decoder_layer_without_folding_keeps_its_arguments_out_of_the_pick():
+    """A form that can pick reads its arguments again afterwards: kept across the pick they were 59 and 85 spilled scalar registers (d = 512,
+    two and eight rows per workgroup), in launches that do not pick as well."""
+    with open(os.path.join(ROOT, "paper_2109_08003_amd", "libnt.so"), "rb") as f:
+        so = f.read()
+    spilled = {}
+    for at in (m.start() for m in re.finditer(rb"AMDGPU\0\0\x83", so)):  # code objects' notes: a map of three
+        for kernel in msgpack.Unpacker(io.BytesIO(so[at + 8:]), raw=False).unpack()["amdhsa.kernels"]:
+            spilled[kernel[".name"]] = kernel[".sgpr_spill_count"]
+    form = re.compile(r"_ZN2nt11dec1_kernelILi\d+ELi(2ELi8|8ELi16)ELi4ELi0ELb0ELb[01]ELb0ELb0E")
+    got = {n: v for n, v in spilled.items() if form.match(n)}
+    assert len(got) == 8 and max(got.values()) <= 32, got
 
 
 def test_folded_caches_end_at_512_rows_and_32768_tokens(host):
