@@ -95,6 +95,22 @@ print(json.dumps((size(n_enc=3) - size(n_enc=2), size(n_enc=1, n_dec=3) - size(n
     assert abs(dec - 2 * attention - ffn - caches) <= 256 * parts, dec
 
 
+def test_a_load_copies_what_the_host_makes(host):
+    """The vectors and matrices of the folded caches are made on the device: 128 more positions are 128 more rows of the position table to
+    copy, and none of the four rows each that the folded layer's start reads; the device has both (and the first layer's table)."""
+    d = 512
+    copied, there = host("""
+out = []
+for max_len in (128, 256):
+    before = C.c_int64.in_dll(stub, "stub_copied").value
+    model = load(dict(config(n_enc=1), max_len=max_len), tokens=64)
+    out.append((C.c_int64.in_dll(stub, "stub_copied").value - before, model.device_bytes()))
+print(json.dumps([b - a for a, b in zip(*out)]))
+""")
+    assert copied == 128 * d * 4
+    assert there == 128 * d * 4 * (1 + 4 + 3)
+
+
 def test_narrow_projections_are_one_round_of_workgroups(host):
     """The form with 32-column strips is for launches of at most 256 workgroups, whatever the matrix's width (an FFN of 192
     columns, an odd multiple of 64, has three groups of them), and for the matrix with one wide strip, of 64 columns."""
