@@ -490,8 +490,8 @@ struct D1Token {
   }
 };
 
-// First layer: z = sqrt(d) E[y] + PE[t], and from its mean and scale the query, and (first wave of a row) the key and value,
-// by the table (see Dec1Table).  Every wave of a row computes the statistics for itself.
+// First layer without folding: z = sqrt(d) E[y] + PE[t], and from its mean and scale the query, and (first wave of a row) the key and
+// value, by the table (see Dec1Table).  Every wave of a row computes the statistics for itself.
 template <int NE>
 __device__ __forceinline__ void first_layer_start(const Dec1Args &a, int y, int lane, bool first_wave, float (&q)[NE], float (&z)[NE],
                                                   float (&kx)[NE], float (&vx)[NE]) {
@@ -504,10 +504,9 @@ __device__ __forceinline__ void first_layer_start(const Dec1Args &a, int y, int 
   float pv[NE], tq[NE], tk[NE], tv[NE];
   d1_load<NE>(a.sb.pe + (long)a.sb.t * D + lane * NE, pv);
   d1_load<NE>(by_token, tq);
-  const int vcol = a.folded ? (a.table.parts - 1) * D : 2 * D;
   if (first_wave) {
     d1_load<NE>(by_token + D, tk);
-    d1_load<NE>(by_token + vcol, tv);
+    d1_load<NE>(by_token + 2 * D, tv);
   }
   const float sc = sqrtf((float)D);
   float s = 0.f;
@@ -531,7 +530,7 @@ __device__ __forceinline__ void first_layer_start(const Dec1Args &a, int y, int 
   combine(tq, 0, q);
   if (first_wave) {
     combine(tk, D, kx);
-    combine(tv, vcol, vx);
+    combine(tv, 2 * D, vx);
   }
 }
 

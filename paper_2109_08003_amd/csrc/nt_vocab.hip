@@ -147,14 +147,14 @@ hipError_t launch_vocab_argmax(const _Float16 *h, const _Float16 *h_lo, long ldh
   if (!use_stream(w)) return launch_vocab_argmax_tiled(h, h_lo, ldh, w.Wt, M, w.N, w.K, pk, s);
   if (!wide) return hipErrorInvalidValue;
   const int G = vw_groups(w.N), spw = vw_strips(w.N);
-#define NT_VW(K_, S_) \
-  if (w.K == K_ && spw == S_) {                                                                                                       \
-    if (M <= VW_ROWS) hipLaunchKernelGGL((vocab_wide_kernel<K_, S_, false>), dim3(G), dim3(512), 0, s, h, h_lo, ldh, M, w.Wp, w.N, G, pk); \
-    else hipLaunchKernelGGL((vocab_wide_kernel<K_, S_, true>), dim3(G, (M + VW_ROWS - 1) / VW_ROWS), dim3(512), 0, s, h, h_lo, ldh, M, w.Wp, w.N, G, pk); \
+#define NT_VW(K_, S_, T_) \
+  if (w.K == K_ && spw == S_ && (M > VW_ROWS) == T_) {                                                                                            \
+    hipLaunchKernelGGL((vocab_wide_kernel<K_, S_, T_>), dim3(G, (M + VW_ROWS - 1) / VW_ROWS), dim3(512), 0, s, h, h_lo, ldh, M, w.Wp, w.N, G, pk); \
+    return hipGetLastError();                                                                                                                     \
   }
-  NT_VW(512, 1) NT_VW(512, 2) NT_VW(256, 1) NT_VW(256, 2)
+  NT_VW(512, 1, false) NT_VW(512, 1, true) NT_VW(512, 2, false) NT_VW(256, 1, false) NT_VW(256, 1, true) NT_VW(256, 2, false)
 #undef NT_VW
-  return hipGetLastError();
+  return hipErrorInvalidValue;  // (two strips per workgroup: one tile, see vocab_wide)
 }
 
 hipError_t launch_vocab_argmax_certified(const VocabScout &v, const _Float16 *h, const _Float16 *h_lo, long ldh,
