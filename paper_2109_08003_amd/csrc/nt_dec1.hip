@@ -1146,17 +1146,20 @@ static hipError_t d1_launch(const Dec1Args &a, hipStream_t s) {
     if (a.folded == 2) {
       // Integer folded caches.  1,024 rows and more: a wave per row, sixteen rows per workgroup, which fills half of the chip's CUs and
       // leaves the other lanes' kernels the rest (2,000 rows of 27 tokens / 1,100 of 40 alone 40 / 39 us; four or eight rows of a wave each 34 /
-      // 30 to 32, two rows of four waves 56 / 40; 200,000 sentences at 65,536 tokens 430 ms, 432 to 446 and 495).  Fewer rows: two waves each,
-      // and four up to 520 (900 rows of 40, 620 of 55, 520 of 100, 300 of 130, 180 of 190 tokens: 25 / 28 / 39 / 34 / 38 us with two, 31 /
-      // 31 / 40 / 28 / 27 with four).  With an FFN, whose matrices every workgroup pulls: sixteen rows, four (900 rows of 40 / 560 of 60:
-      // 39 / 40 us, with eight 44 / 48, with two 52 / 56), two up to 520 (480 rows of 90, 320 of 150: 40 / 44 us, with four 45 / 56).
+      // 30 to 32, two rows of four waves 56 / 40; 200,000 sentences at 65,536 tokens 430 ms, 432 to 446 and 495).  Fewer rows: two waves each
+      // (900 rows of 40, 620 of 55: 25 / 28 us, with four 31 / 31), and four as long as their workgroups, two to a CU at d = 512, are one round, that is up
+      // to 512 rows (a step, four waves / two: 301 rows of 110 tokens 35.4 / 36.3, 400 36.7 / 38.4, 512 42.4 / 43.3, 513 49.6 / 45.1, of 22 tokens 35.7 /
+      // 32.3; d = 256, more to a CU, 520 rows of 110 32.4 / 34.7, of 22 23.7 / 24.7).  With an FFN, whose matrices every workgroup pulls: sixteen rows,
+      // four (900 rows of 40 / 560 of 60: 39 / 40 us, with eight 44 / 48, with two 52 / 56), two up to the same line (a step, two rows / four: 301 rows of 110
+      // tokens 43.2 / 48.3, 400 46.6 / 50.3, 512 52.5 / 54.2, 513 71.3 / 56.0, of 22 tokens 56.3 / 44.2).
+      constexpr int kOneRound = D == 512 ? 512 : 520;
       if constexpr (FFN) {
         if (shape >= 1024) NT_D1F(16, 16, 1, 1, false);
-        else if (shape > 520) NT_D1F(4, 16, 4, 1, false);
+        else if (shape > kOneRound) NT_D1F(4, 16, 4, 1, false);
         else NT_D1F(2, 8, 4, 1, false);
       } else {
         if (shape >= 1024) NT_D1F(16, 16, 1, 1, false);
-        else if (shape > 520) NT_D1F(2, 4, 2, 1, false);
+        else if (shape > kOneRound) NT_D1F(2, 4, 2, 1, false);
         else NT_D1F(1, 4, 4, 1, false);
       }
       return hipGetLastError();

@@ -136,10 +136,10 @@ def test_decoder_layer_forms_are_all_in_use(host):
 out = set()
 for kw in (dict(), dict(dec_d_ffn=512), dict(n_heads=8), dict(n_dec=2), dict(n_dec=2, dec_d_ffn=512), dict(d_model=256),
            dict(d_model=256, dec_d_ffn=256), dict(d_model=256, n_dec=2), dict(d_model=256, n_dec=2, dec_d_ffn=256)):
-    model = load(config(**dict(kw, n_enc=1)), tokens=4096)
-    a = np.zeros(4096, dtype=np.int32)
-    for rows in (1, 64, 65, 256, 257, 512, 513, 1023, 1024, 2000):
-        encode(model, rows, 2)
+    model = load(config(**dict(kw, n_enc=1)), tokens=33000)
+    a = np.zeros(33000, dtype=np.int32)
+    for rows, length in [(rows, 2) for rows in (1, 64, 65, 256, 257, 512, 513, 1023, 1024, 2000)] + [(300, 110)]:
+        encode(model, rows, length)
         nt.binding._check(nt.binding.lib().nt_decode_greedy(model._h, rows, 1, None, a.ctypes.data, None))
         out |= {n for n, _ in launches() if "dec1_kernel" in n}
 print(json.dumps(sorted(out)))
@@ -205,6 +205,25 @@ print(json.dumps(out))
     for name, rows, eos, kinds in got:
         wide = rows <= (32 if eos or name in ("deep", "ffn", "heads") else 24 if name == "narrow" else 16)
         assert kinds == (["vocab_wide"] if wide else ["vocab_pick", "vocab_scout_few"]), (name, rows, eos, kinds)  # (the last step's pick)
+
+
+def test_integer_folded_layers_are_one_round_of_workgroups(host):
+    """At d = 512, where a CU holds two of them, the forms with the fewest rows per workgroup end at 512 rows."""
+    got = host("""
+out = []
+for ffn in (-1, 512):
+    model = load(config(n_enc=1, dec_d_ffn=ffn), tokens=40000)
+    a = np.zeros(40000, dtype=np.int32)
+    for rows in (512, 513, 1023):
+        encode(model, rows, 32800 // rows + 1)  # past the fp32 caches' 32,768 tokens
+        stub.stub_clear()
+        nt.binding._check(nt.binding.lib().nt_decode_greedy(model._h, rows, 1, None, a.ctypes.data, None))
+        out += [(rows, n, b) for n, b in launches() if "dec1_kernel" in n]
+print(json.dumps(out))
+""")
+    form = lambda n: tuple(int(x) for x in re.search(r"dec1_kernelILi512ELi(\d+)ELi(\d+)ELi\d+ELi1ELb0", n).groups())
+    assert [(rows, *form(n), b) for rows, n, b in got] == [(512, 1, 4, 512), (513, 2, 4, 257), (1023, 2, 4, 512),
+                                                          (512, 2, 8, 256), (513, 4, 16, 129), (1023, 4, 16, 256)]
 
 
 def test_lanes_with_different_sentence_lengths_share_a_kernel(host):
