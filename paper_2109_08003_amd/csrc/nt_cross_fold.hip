@@ -12,9 +12,9 @@
 // kept as head and tail planes, 22 bits, as the factors of 11 bits they are made of are exact.
 //
 // 54,069 tokens, d = 512: 171 us without the tail plane and 262 with it, where projection and quantisation as two launches, the keys and
-// values in fp32 between them, took 195 and 229; what a step gains is in nt_dec1.hip.  Two thirds of the time are the matrix cores' (1.1
-// PFLOP/s issued: both planes of the matrix, 1.5 times the products with the tail), the rest the fill of a tile and the two exchanges per
-// vector.
+// values in fp32 between them, took 195 and 229; what a step gains is in nt_dec1.hip.  0.66 PFLOP/s are issued (both planes of the matrix,
+// 1.5 times the products with the tail) and the matrix pipes are busy for 38 % of the time: the fill of a tile, the products and the two
+// exchanges per vector follow one another.
 //
 // The kernel has the shape of nt_gemm_stream.hip's: a tile of 32 or 64 normalised rows in the LDS, the matrix through a ring of
 // registers.  The matrix is the row operand, so that a lane owns a row of the tile and half of a wave's 64 columns: the largest element of

@@ -4,9 +4,8 @@
 //   self-attention -> output projection + residual -> LayerNorm -> query projection -> cross-attention ->
 //   output projection + residual -> [LayerNorm -> FFN + residual ->] final LayerNorm,
 // and no step of it reads another row.  A workgroup carries its rows through the whole chain - 2 with eight waves, 4 to 16 with
-// sixteen, 1 with four where nothing is left but attention (the paper's cure for many small dependent nodes is fewer, larger
-// ones, Sec. 3.3 "Graph Optimization"); what passes from one
-// phase to the next stays in the LDS.  As four launches (two attention kernels with a wave per row, two kernels that
+// sixteen, and where nothing is left but attention also 1 with four or eight and 2 with four (the paper's cure for many small dependent
+// nodes is fewer, larger ones, Sec. 3.3 "Graph Optimization"); what passes from one phase to the next stays in the LDS.  As four launches (two attention kernels with a wave per row, two kernels that
 // streamed the 512 KB matrices for 32-row tiles) the chain took 24 + 24 + 28 + 16 us at 1,900 rows and 38 us at one row,
 // most of it the start and end of launches and, in the projections, 60 workgroups or fewer on 256 CUs.
 //
@@ -15,12 +14,12 @@
 // scores, softmax and context are fp32 (Sec. 3.1 "FP16 Inference").  Lane l holds elements l * NE .. l * NE + NE - 1 of
 // every vector, so a wave instruction reads one whole vector.  Keys are taken four at a time: their sums are reduced together in the
 // vector unit (wave_fold), wave-uniform scores, one rescale of the online softmax per block.  A row's blocks are dealt to 1 (1,024 rows or more)
-// or 4 partial softmaxes that are merged in order, however many waves compute them.
+// or 4 partial softmaxes (folded: also 2 or 8) that are merged in order, however many waves compute them.
 //
 // First layer: token -> z, query, key and value by table (Dec1Table in nt_kernels.h), so the step starts here: one sentence reads
-// one row of 8 KB where a launch of its own streamed the 1.5 MB matrix (9 to 11 us up to 512 rows, 15 to 21 us from there on, of
+// one row of 6 KB where a launch of its own streamed the 1.5 MB matrix (9 to 11 us up to 512 rows, 15 to 21 us from there on, of
 // which 1 to 3 us remain here, most of them hidden behind the caches' first blocks).  The table of a 32,000-entry vocabulary at
-// d = 512 has 262 MB with the folded values and takes 2.7 ms of a load of 200 ms.  With the launch against by table: one sentence
+// d = 512 has 198 MB (264 where batches of both kinds occur, folded and not) and takes 2 ms of a load of 200 ms.  With the launch against by table: one sentence
 // 1,008 -> 811 us, 45 sentences 3,225 -> 2,505, 8 sentences of the 256-wide model 1,188 -> 920 us, a 4,096-token budget
 // 28.4 -> 25.2 ms, 16,384 tokens 76.0 -> 68.2, 65,536 tokens 559 -> 521, 320 rows of 180 tokens 22.7 -> 20.5, the model with
 // 8 heads and FFN 2,048 116.8 -> 109.0 ms, the 30 + 6 layer teacher 110.4 -> 109.1.  It is the faster form at every row count, so
@@ -35,7 +34,7 @@
 //
 // Folded attention (one-layer decoders).  q . k = (W y + b) . k = y . (W^T k) + b . k,
 // and Wo (sum p v) + bo = sum p (Wo v + bo).  With the cross keys and values of a sentence multiplied by the two matrices once,
-// when the batch is encoded, and the self values projected by the product of value and output matrix (formed at load, a fourth
+// when the batch is encoded, and the self values projected by the product of value and output matrix (formed at load, the last
 // group of columns of the table), a step's attention half has no projection left.  The self values are cached without their constant, which a
 // softmax passes through unchanged, and with every column divided by its norm: either would set the one scale of a vector's
 // integers for all its elements (eight output biases of 16, or eight output columns 16 times as large, leave 1.3e-5 / 1.1e-4 of
@@ -62,10 +61,10 @@
 // nt_host.hip); several layers have no folded form.
 //
 // Registers: three forms spill some of theirs - eight heads with two rows (28 bytes of scratch per lane) and with eight rows
-// (56 bytes), folded in fp32 with two rows and the FFN at d = 512 (44 bytes).  The others use no scratch.
+// (56 bytes), folded in fp32 with two rows and the FFN at d = 512 (56 bytes, 44 with a row map).  The others use no scratch.
 //
 // Measured per step of 1,900 / 45 / 1 rows, alone: 92 / 42 / 38 us as four launches, 71 / 30 / 25 us as one, without
-// the launch that projected Q | K | V (21 / 11 / 9 us).  With the table in its place and folded caches one row now takes 7.7 us.
+// the launch that projected Q | K | V (21 / 11 / 9 us).  With the table in its place and folded caches one row now takes 7.1 to 7.4 us.
 //
 // Eight heads of 64 (HEADS): the caches stay fp32 (self) and fp16 (cross); a vector still lies across one wave instruction, a
 // head on eight of its lanes, so that every lane keeps its own head's softmax and a score costs three DPP adds.  Relative keys
@@ -1199,7 +1198,7 @@ static hipError_t d1_launch(const Dec1Args &a, hipStream_t s) {
 // The pick of the last step's arg-max inside the layer saves its launch: 400 rows of 30 tokens 2.76 -> 2.67 ms, 320 of 150 13.6 -> 13.2, 700 of 40
 // 3.91 -> 3.82, 45 of 22 1.94 -> 1.89, with an FFN 300 / 700 rows of 30 2.65 -> 2.57 / 3.90 -> 3.74 (batches alone); 4,096- and
 // 16,384-token budgets 18.4 -> 18.2 and 49.5 -> 46.2 ms.  Not where a row has one wave for it, nor with eight heads (the 30 + 6 layer teacher's
-// batch of 250 rows 20.4 -> 20.6 ms: sixteen waves wait for four rows' picks in one layer of six).
+// batch of 250 rows 20.4 -> 20.6 ms: sixteen waves wait for four rows' picks in one layer of six; with a single eight-head layer it has not been tried).
 bool dec1_picks(int shape_rows, int heads) { return heads <= 1 && shape_rows < 1024; }
 
 hipError_t launch_dec1(const Dec1Args &a, int d, hipStream_t s) {

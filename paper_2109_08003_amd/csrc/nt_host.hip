@@ -653,7 +653,8 @@ int nt_load_weights(const nt_config *cfg, const void *h_blob_fp16, size_t blob_b
   const bool tabled = m->kv_i16 || (!kCrossF32 && nt::dec1_heads_supported(d, dec_heads(cfg)));
   // Larger batches fold their caches, too (CrossFold), but not before the 8-bit output layer: that the integers then round other vectors
   // moves a state by 2e-5, one of its codes every few steps, and 0.9 % of the tokens of 25-token sentences (all near-ties; 0.05 % with
-  // the fp16 output layer).  So such a model's table has both forms of the value.
+  // the fp16 output layer).  (That is the distance of the two forms; which of them is nearer to exact arithmetic has not been measured.)
+  // So such a model's table has both forms of the value.
   const bool fold_all = fold_dec && !cfg->q8_output;
   const int parts = !tabled ? 0 : fold_dec && !fold_all ? 4 : 3;
   std::vector<double> tabW((size_t)d * parts * d), tabB((size_t)parts * d);

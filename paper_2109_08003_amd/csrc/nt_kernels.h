@@ -633,7 +633,7 @@ struct Dec1Args {
   ScoutOut scout;
 };
 hipError_t launch_dec1(const Dec1Args &a, int d, hipStream_t s);
-// dst [dec1_fold_vectors_bytes] <- the above, at load: constants (of folded == 1, then of folded == 2 if fold2), then positions
+// dst [dec1_fold_vectors_bytes] <- the above, at load: constants (of folded == 1, then of folded == 2 where gamma2 is given), then positions
 struct Dec1FoldVectors {
   GemmLayerNorm ln2, ln3, lnf;         // ln3.gamma == nullptr: no FFN inside the layer
   const float *fold_scale, *fold_bias; // of the self context
