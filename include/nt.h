@@ -148,8 +148,9 @@ int nt_encode(nt_model *m, const int32_t *d_src, const int32_t *d_len, int32_t B
  *   NULL = every row runs n_steps steps.  A row's arithmetic never reads another row.  The number of
  *   active rows does select between kernel forms whose fp32 summation order differs (how many waves
  *   share a row's keys in the attention kernels; for model widths other than 256 / 512 a
- *   one-round-trip projection kernel below 128 rows), so the same sentence decoded in batches of very
- *   different size can differ in the last bit of a logit, and therefore in a token where two logits
+ *   one-round-trip projection kernel below 128 rows; with 17 to 32 rows the output layer's kernel also
+ *   depends on whether the batch is one of several of a translate call and on the mode), so the same
+ *   sentence decoded in batches of very different size can differ in the last bit of a logit, and therefore in a token where two logits
  *   tie to within that bit; the EOS-terminated call below fixes the choice by the caps alone.
  * Errors: NT_EINVAL, NT_ESTATE (B differs from the encoded batch), NT_ERANGE (n_steps >
  * max_len, h_row_steps not non-increasing), NT_ENOMEM (B * n_steps beyond the self cache), NT_EHIP.
@@ -205,8 +206,8 @@ int nt_debug_q8_quantize_row(const void *h_w_fp16, int32_t K, int8_t *h_codes, f
  * stops launching once it reads zero.  The host never waits for the stream to drain, but it
  * enqueues at most a few steps ahead of the device, so the call returns when the device is
  * within those few steps of the end; the outputs are complete once hip_stream has been
- * synchronised.  Tokens are those nt_decode_greedy produces, cut after the first EOS (where the caps
- * leave 17 to 32 rows the output layer's kernel may be another one: to within the last bit, as above).
+ * synchronised.  Tokens are those nt_decode_greedy produces, cut after the first EOS (with 17 to 32
+ * rows to within a last bit, see there).
  * Errors: as nt_decode_greedy; NT_ERANGE for eos_id outside the vocabulary; NT_EHIP if the device
  * publishes no progress for 30 seconds.
  */

@@ -1052,6 +1052,7 @@ struct DecodeCursor {
   float *d_logits = nullptr;
   int t = 0, partials_prev = 0, rows_prev = 0;
   bool prev_cert = false, finished = false;
+  bool beside = false;     // one of several batches of a translate call (by their number, not by how many lanes there are or what runs)
   bool prev_pick = false;  // the scout of the last step has run, the pick starts the next one
   nt::PickArgs pick{};
   // EOS mode (eos_id >= 0)
@@ -1191,7 +1192,8 @@ int decode_step(nt_model *m, DecodeCursor &cu, hipStream_t s) {
     // The scout's sums run in another order than the wide kernel's: chosen as above.  (The tiled kernels' certified form gives the
     // full pass's result at any row count.)
     const bool picked = !eos && layer1 && c.n_dec == 1 && F == 0 && nt::dec1_picks(rows_for_choice, heads_layer ? H : 1);
-    const bool wide = nt::vocab_wide(m->vw, rows_for_choice, !picked ? nt::kVocabWideRows : d == 512 ? nt::kVocabPickedRows : nt::kVocabPickedRows256);
+    const int line = cu.beside || (picked && d == 512) ? nt::kVocabFewRows : picked ? nt::kVocabFewRows256 : nt::kVocabWideRows;
+    const bool wide = nt::vocab_wide(m->vw, rows_for_choice, line);
     const bool scouted = nt::vocab_scouted(m->vw, wide) && m->Wscout;
     const bool certified = !d_logits && !c.q8_output && (scouted || (nt::vocab_tiled(m->vw) && R >= kCertMinRows));
     const nt::ScoutOut scout_out = certified && scouted ? nt::ScoutOut{m->scout_codes, m->scout_rc, nt::vocab_scout_levels(m->Wscout, V, d)} : nt::ScoutOut{};
@@ -1402,8 +1404,9 @@ bool eos_may_advance(const DecodeCursor &cu) { return cu.t - cu.step_seen <= kEo
 
 // Decoder loop shared by fixed-length greedy decoding and the teacher-forced debug path.
 int run_decoder(nt_model *m, int32_t B, int32_t T, const int32_t *h_row_steps, const int32_t *d_forced,
-                int32_t *d_out, float *d_logits, hipStream_t s) {
+                int32_t *d_out, float *d_logits, bool beside, hipStream_t s) {
   DecodeCursor cu;
+  cu.beside = beside;
   cu.B = B; cu.T = T; cu.h_row_steps = h_row_steps; cu.d_forced = d_forced; cu.d_out = d_out; cu.d_logits = d_logits;
   while (!cu.finished) {
     int rc = decode_step(m, cu, s);
@@ -1420,12 +1423,7 @@ int check_decode_args(nt_model *m, int32_t B, int32_t T) {
   return NT_OK;
 }
 
-}  // namespace
-
-extern "C" {
-
-int nt_decode_greedy(nt_model *m, int32_t B, int32_t n_steps, const int32_t *h_row_steps, int32_t *d_out,
-                     void *hip_stream) {
+int decode_greedy(nt_model *m, int32_t B, int32_t n_steps, const int32_t *h_row_steps, int32_t *d_out, bool beside, void *hip_stream) {
   int rc = check_decode_args(m, B, n_steps);
   if (rc) return rc;
   if (!d_out) return fail(NT_EINVAL, "d_out is null");
@@ -1438,7 +1436,16 @@ int nt_decode_greedy(nt_model *m, int32_t B, int32_t n_steps, const int32_t *h_r
     }
     HIP_TRY(nt::launch_fill_i32(d_out, (long)B * n_steps, m->c.pad_id, s));
   }
-  return run_decoder(m, B, n_steps, h_row_steps, nullptr, d_out, nullptr, s);
+  return run_decoder(m, B, n_steps, h_row_steps, nullptr, d_out, nullptr, beside, s);
+}
+
+}  // namespace
+
+extern "C" {
+
+int nt_decode_greedy(nt_model *m, int32_t B, int32_t n_steps, const int32_t *h_row_steps, int32_t *d_out,
+                     void *hip_stream) {
+  return decode_greedy(m, B, n_steps, h_row_steps, d_out, false, hip_stream);
 }
 
 int nt_decode_greedy_eos(nt_model *m, int32_t B, int32_t n_steps, const int32_t *h_row_steps, int32_t eos_id,
@@ -1483,7 +1490,7 @@ int nt_debug_teacher_forced_logits(nt_model *m, const int32_t *d_tgt_in, int32_t
   if (rc) return rc;
   if (!d_tgt_in || !d_logits) return fail(NT_EINVAL, "null argument");
   if (T == 0) return NT_OK;
-  return run_decoder(m, B, T, nullptr, d_tgt_in, nullptr, d_logits, as_stream(hip_stream));
+  return run_decoder(m, B, T, nullptr, d_tgt_in, nullptr, d_logits, false, as_stream(hip_stream));
 }
 
 int nt_debug_q8_quantize_row(const void *h_w_fp16, int32_t K, int8_t *h_codes, float *h_scale, int32_t *h_zero) {
@@ -1857,7 +1864,7 @@ int nt_translate_batch(nt_model *m, const int32_t *h_tokens, const int64_t *h_of
     nt_model::Staging &st = ln->stage[nth % nt_model::kStagings];
     int32_t B = 0, T = 0;
     int e = pl.start(ln, st, k, &B, &T);
-    if (e || (e = nt_decode_greedy(ln, B, T, st.steps.data(), ln->d_out, ln->lane_stream))) return e;
+    if (e || (e = decode_greedy(ln, B, T, st.steps.data(), ln->d_out, plan.nb > 1, ln->lane_stream))) return e;
     return pl.finish(ln, st);
   };
   int first_err = NT_OK, dev = 0;
@@ -1960,6 +1967,7 @@ int nt_translate_batch_eos(nt_model *m, const int32_t *h_tokens, const int64_t *
     if (e || (e = check_decode_args(ln, B, T))) return e;
     HIP_TRY(nt::launch_fill_i32(ln->d_out, (long)B * T, m->c.pad_id, ln->lane_stream));
     begin_eos_decode(ln, L.cu, B, T, st.steps.data(), eos_id, ln->d_out, ln->d_out_len);
+    L.cu.beside = plan.nb > 1;
     L.st = &st;
     L.started++;
     L.active = true;

@@ -218,19 +218,25 @@ void vocab_pack(const _Float16 *Wt, int N, int K, _Float16 *dst);
 // first, none in the scout's).
 // wide: vocab_wide of a row count at least M.  Up to a tile of 32 rows, and, of up to 256 strips of 64 entries (one to a workgroup), more where strips
 // times tiles are at most kVocabWideStrips, take a kernel of its own, more the scout, which is two launches (and whose sums run in another order, so a
-// caller whose M depends on timing decides by a row count that does not, and nobody by what else is running).  A decoder step alone, us, d = 512,
+// caller whose M depends on timing decides by a row count that does not, and nobody by what happens to be running).  A decoder step alone, us, d = 512,
 // wide / scout, with strips x tiles: 1,000 entries, 33 rows (32) 12.3 / 20.2, 512 rows (256) 16.6 / 27.5; 4,000 entries, 128 rows (252) 13.2 / 21.5,
 // 300 rows (630) 21.1 / 24.4, 512 rows (1,008) 26.1 / 26.4; 8,000 entries, 64 rows (250) 12.9 / 19.2, 160 rows (625) 19.5 / 20.2, 200 rows (875)
 // 21.5 / 20.5.  d = 256: 4,000 entries, 300 rows (630) 14.6 / 19.0.  More than 256 strips, rows of 22 tokens, 17 / 24 / 32 rows and the scout from 33 rows on: eight
 // heads 29.3 / 30.1 / 31.1 and 34.5 / 34.5 / 34.5, the EOS mode of one head 21.9 / 22.8 / 23.6 and 24.5, d = 256 18.5 / 18.9 / 19.3 and 20.2, with an FFN of the
 // model's width 25.8 / 26.9 / 27.9 and 28.7.
-// line: the largest row count that takes the wide kernel with more than 256 strips; kVocabWideRows, but less where the pick is no launch but part of the next
-// step's only layer (DecodeCursor::prev_pick), without an FFN: 17 / 20 / 24 / 28 / 32 rows, 32,000 entries 15.7 / 16.0 / 16.3 / 16.7 / 17.1 and 15.7 / 15.9 /
-// 16.0 / 16.4 / 16.5, 20,000 15.1 / 15.3 / 15.8 / 16.2 / 16.6 and 15.2 / 15.5 / 15.7 / 15.9 / 16.0, 16,500 14.8 / 15.2 / 15.6 / 16.0 / 16.4 and 14.8 / 15.1 / 15.2 / 15.3 / 15.3,
-// beside other lanes, which want the memory system the wide kernel fills, a 4,096-token budget 17.4 ms with the line at 4 to 16 rows, 17.9 at 32: kVocabPickedRows.
-// d = 256, 32,000 entries, 20 / 24 / 28 / 32 rows 12.3 / 12.3 / 12.5 / 12.8 and 12.5 / 12.6 / 12.5 / 12.8, 16,500 12.0 / 12.1 / 12.4 / 12.6 and 12.3 / 12.2 / 12.2 / 12.2.
-// (Two decoder layers of 512, 18 / 24 / 28 / 32 rows 67.8 / 68.7 / 69.7 / 67.6 and 68.9 / 69.0 / 69.2 / 66.6; of 256, 28 rows 35.6 and 36.3: no line of their own.)
-constexpr int kVocabWideStrips = 640, kVocabWideRows = 32, kVocabPickedRows = 16, kVocabPickedRows256 = 24;
+// line: the largest row count that takes the wide kernel with more than 256 strips.
+//  - kVocabWideRows for a batch that is alone (figures above).
+//  - Alone, and the pick is no launch but part of the next step's only layer (DecodeCursor::prev_pick), without an FFN: kVocabFewRows, d = 256 kVocabFewRows256.
+//    17 / 20 / 24 / 28 / 32 rows, 32,000 entries 15.7 / 16.0 / 16.3 / 16.7 / 17.1 and 15.7 / 15.9 / 16.0 / 16.4 / 16.5, 20,000 15.1 / 15.3 / 15.8 / 16.2 / 16.6 and 15.2 /
+//    15.5 / 15.7 / 15.9 / 16.0, 16,500 14.8 / 15.2 / 15.6 / 16.0 / 16.4 and 14.8 / 15.1 / 15.2 / 15.3 / 15.3; d = 256, 32,000 entries, 20 / 24 / 28 / 32 rows 12.3 / 12.3 /
+//    12.5 / 12.8 and 12.5 / 12.6 / 12.5 / 12.8, 16,500 12.0 / 12.1 / 12.4 / 12.6 and 12.3 / 12.2 / 12.2 / 12.2.  (Two decoder layers of 512, 18 / 24 / 28 / 32 rows 67.8 /
+//    68.7 / 69.7 / 67.6 and 68.9 / 69.0 / 69.2 / 66.6; of 256, 28 rows 35.6 and 36.3: no line of their own.)
+//  - A call with several batches, whose lanes share the memory system that one wide kernel fills: kVocabFewRows.  1,500 sentences in batches of at most 24 and 32
+//    rows, wide against scout: the submitted student 30.7 against 24.0 and 25.0 against 18.8 ms, eight heads and FFN 2,048 47.3 against 42.2 and 37.7 against 33.1,
+//    the 256-wide model (24 rows) 13.1 against 10.8; a 4,096-token budget of one head 17.9 with the line at 32 rows, 17.4 at 4 to 16.  In the EOS mode, which the
+//    host paces, 24 rows of one head 29.3 against 30.8, of the submitted student 33.4 against 31.1: the same line, so that its tokens are those of the
+//    fixed-length call by construction.
+constexpr int kVocabWideStrips = 640, kVocabWideRows = 32, kVocabFewRows = 16, kVocabFewRows256 = 24;
 bool vocab_wide(const VocabWeights &w, int rows, int line);
 int vocab_argmax_partials(const VocabWeights &w, int M, bool certified, bool wide);
 // h is a head/tail pair of fp16 planes.

@@ -183,28 +183,33 @@ print(json.dumps(out))
 
 def test_arg_max_of_17_to_32_rows(host):
     """More than 256 strips of the output matrix, up to 32 rows: the kernel that reads all of it; but from 17 rows on (256-wide models: 25)
-    the scout where the pick is no launch, that is in fixed-length decoding of one head, in one layer without an FFN."""
+    the scout where the pick is no launch, that is in fixed-length decoding of one head, in one layer without an FFN, and from 17 rows on
+    in every batch of a call that has several."""
     got = host("""
-out = []
+out, kinds = [], lambda: sorted({k for n, _ in launches() for k in ("vocab_wide", "vocab_scout_few", "vocab_pick") if k in n})
 for name, kw in (("one head", dict()), ("narrow", dict(d_model=256)), ("deep", dict(n_dec=2)), ("ffn", dict(dec_d_ffn=512)), ("heads", dict(n_heads=8))):
-    model = load(dict(config(n_enc=1, **kw), vocab=16450), tokens=4096)
+    model = load(dict(config(n_enc=1, **kw), vocab=16450), tokens=4096, lanes=2)
     a = np.zeros(4096, dtype=np.int32)
     for rows in (16, 17, 24, 25, 32, 33):
-        for eos in (False, True):
+        for mode in ("fixed", "eos"):
             encode(model, rows, 2)
             stub.stub_clear()
             args = model._h, rows, 2, None
-            if eos:  # (two steps: the host does not wait for the device yet)
+            if mode == "eos":  # (two steps: the host does not wait for the device yet)
                 nt.binding._check(nt.binding.lib().nt_decode_greedy_eos(*args, 2, a.ctypes.data, a.ctypes.data, None))
             else:
                 nt.binding._check(nt.binding.lib().nt_decode_greedy(*args, a.ctypes.data, None))
-            kinds = {k for n, _ in launches() for k in ("vocab_wide", "vocab_scout_few", "vocab_pick") if k in n}
-            out.append((name, rows, eos, sorted(kinds)))
+            out.append((name, rows, mode, kinds()))
+        for batches in (1, 2):
+            stub.stub_clear()
+            model.translate_batch(np.full(2 * rows * batches, 5, dtype=np.int32), np.arange(0, 2 * rows * batches + 1, 2, dtype=np.int64), 4096,
+                                  max_rows=rows, stream=Stream)
+            out.append((name, rows, "several" if batches > 1 else "fixed", kinds()))
 print(json.dumps(out))
 """)
-    for name, rows, eos, kinds in got:
-        wide = rows <= (32 if eos or name in ("deep", "ffn", "heads") else 24 if name == "narrow" else 16)
-        assert kinds == (["vocab_wide"] if wide else ["vocab_pick", "vocab_scout_few"]), (name, rows, eos, kinds)  # (the last step's pick)
+    for name, rows, mode, kinds in got:
+        line = 16 if mode == "several" else 32 if mode == "eos" or name in ("deep", "ffn", "heads") else 24 if name == "narrow" else 16
+        assert kinds == (["vocab_wide"] if rows <= line else ["vocab_pick", "vocab_scout_few"]), (name, rows, mode, kinds)  # (the last step's pick)
 
 
 def test_integer_folded_layers_are_one_round_of_workgroups(host):
