@@ -149,9 +149,10 @@ int nt_encode(nt_model *m, const int32_t *d_src, const int32_t *d_len, int32_t B
  *   active rows does select between kernel forms whose fp32 summation order differs (how many waves
  *   share a row's keys in the attention kernels; for model widths other than 256 / 512 a
  *   one-round-trip projection kernel below 128 rows; with 17 to 32 rows the output layer's kernel also
- *   depends on whether the batch is one of several of a translate call and on the mode), so the same
- *   sentence decoded in batches of very different size can differ in the last bit of a logit, and therefore in a token where two logits
- *   tie to within that bit; the EOS-terminated call below fixes the choice by the caps alone.
+ *   depends on whether the batch is one of several of a translate call and, if not, on the mode), so the
+ *   same sentence decoded in batches of very different size can differ in the last bit of a logit, and
+ *   therefore in a token where two logits tie to within that bit; the EOS-terminated call below fixes
+ *   the choice by the caps alone.
  * Errors: NT_EINVAL, NT_ESTATE (B differs from the encoded batch), NT_ERANGE (n_steps >
  * max_len, h_row_steps not non-increasing), NT_ENOMEM (B * n_steps beyond the self cache), NT_EHIP.
  */

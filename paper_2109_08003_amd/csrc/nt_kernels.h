@@ -234,8 +234,8 @@ void vocab_pack(const _Float16 *Wt, int N, int K, _Float16 *dst);
 //  - A call with several batches, whose lanes share the memory system that one wide kernel fills: kVocabFewRows.  1,500 sentences in batches of at most 24 and 32
 //    rows, wide against scout: the submitted student 30.7 against 24.0 and 25.0 against 18.8 ms, eight heads and FFN 2,048 47.3 against 42.2 and 37.7 against 33.1,
 //    the 256-wide model (24 rows) 13.1 against 10.8; a 4,096-token budget of one head 17.9 with the line at 32 rows, 17.4 at 4 to 16.  In the EOS mode, which the
-//    host paces, 24 rows of one head 29.3 against 30.8, of the submitted student 33.4 against 31.1: the same line, so that its tokens are those of the
-//    fixed-length call by construction.
+//    host paces, one launch less is worth more: 24 rows of one head 29.3 against 30.8 (37 against 43 in processes whose host is the slower), of the submitted
+//    student 33.4 against 31.1 (39 against 42): the same line all the same, so that its tokens are those of the fixed-length call by construction.
 constexpr int kVocabWideStrips = 640, kVocabWideRows = 32, kVocabFewRows = 16, kVocabFewRows256 = 24;
 bool vocab_wide(const VocabWeights &w, int rows, int line);
 int vocab_argmax_partials(const VocabWeights &w, int M, bool certified, bool wide);
